@@ -101,10 +101,10 @@ typedef struct {
 typedef struct mmm_maps mmm_maps;
 
 /* Bytes of device workspace that maps for this shape need: the maps and their
- * derived forms, the blocked lists of A at their worst-case size (8 bytes per
- * element of X), room for the row-compacted copy of Y (4 bytes per element of
- * Y, used only when keep_rows is given), and the partial-sum area of the split-K
- * multiplication (at most 64 MiB).
+ * derived forms, the image of A (4 bytes per element of X), packed B at its
+ * worst-case size (4 bytes per element of Y, and 2 bytes per row of Y and 16
+ * columns), room for the inspection lists of A (8 bytes per element of X), and
+ * the partial-sum area of the split-K multiplication (at most 64 MiB).
  * Errors: MMM_ERR_SHAPE, MMM_ERR_INVALID_ARG (bytes NULL). */
 mmm_status mmm_maps_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t block_width, size_t *bytes);
 
@@ -124,17 +124,17 @@ void mmm_maps_release(mmm_maps *maps);
  * sparse row preprocessing" for A -- here both become bitmaps):
  *     a_bits[i,k]  = pred(X[i,k]) & keep_bits[i,k] & (X[i,k] != 0)
  *     b_bits[k,jb] = keep_rows[k] & keep_blocks[k,jb] & (some Y[k, jb*bw .. jb*bw+bw) != 0)
- * plus derived forms the multiplication reads: column-any words of A per 32-row
- * tile, the B map transposed to one bit-row per block column, and, for every
- * 64 x 128 block of A, the count and a compacted list of its non-zero elements
- * with their values (the count-and-offsets form of Fig. "Blocked sparse row
- * preprocessing", with the value stored beside the offset).
+ * plus derived forms: column-any words of A per 32-row tile, the B map transposed
+ * to one bit-row per block column, and the operands of the matrix kernel: an image
+ * of A (64 x 128 blocks in the byte order the kernel keeps them in LDS, masked-out
+ * elements zero) and packed B (per 16-column group and 128 values of k the occupied
+ * rows one after another, with the list of their k).
  * Either side may be skipped by passing X == NULL (then ma is ignored) or
  * Y == NULL: that side's maps from an earlier call are kept -- the B side of a
  * weight matrix is built once and reused (section 3: rows of B are preprocessed
  * once and used many times).  Lanes of Y whose block is switched off by the keep
  * bitmaps are not read.  With mb->keep_rows the B side is built in row-compacted
- * mode (see mmm_maps_view_compacted), which ties the lists of A to this B side.
+ * mode (see mmm_maps_view_compacted), which ties the image of A to this B side.
  * Errors: MMM_ERR_INVALID_ARG (maps NULL, both X and Y NULL, mask struct NULL for
  * a present side, bad pred), MMM_ERR_SHAPE (ld too small, block_width differs
  * from the handle's), MMM_ERR_DTYPE, MMM_ERR_DEVICE. */
@@ -167,24 +167,22 @@ mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany
  *   a_colany_c  : ceil(M/32) x ceil(K/64) words; bit k' of row t = OR of a_bits[i, kmap[k']], i in [32t, 32t+32)
  *   btc_bits    : NB x ceil(K/64) words; bit k' of row jb = b_bits[kmap[k'], jb]
  *   (bits k' >= K' up to the next multiple of 128 are zero; words beyond are unspecified)
- * and keeps a copy of the kept blocks of the live rows of Y (row k' of the copy = row kmap[k'] of
- * Y), from which the matrix kernel takes B; Y itself is still what MMM_PATH_PAIRS and
- * mmm_matmul_fused read.  The blocked lists of A (mmm_maps_view_lists) are then over k' as well.
- * *on says whether the B side was last built this way.  Because the lists of A depend on the
+ * and packs B and lays out A over k'.  a_colany_c serves inspection only: this call makes it (on the
+ * stream of the last mmm_build_maps).  The blocked lists of A (mmm_maps_view_lists) are then over k' as well.
+ * *on says whether the B side was last built this way.  Because the image of A depends on the
  * numbering, building the B side alone (X == NULL) with keep_rows, or after it had been built with
  * keep_rows, leaves the A side unbuilt: build A in the same call or afterwards.
- * Any out pointer may be NULL.  Errors: MMM_ERR_INVALID_ARG. */
+ * Any out pointer may be NULL.  Errors: MMM_ERR_INVALID_ARG, MMM_ERR_DEVICE. */
 mmm_status mmm_maps_view_compacted(const mmm_maps *maps, int32_t *on, const uint32_t **live_count,
                                    const uint32_t **kmap, const uint64_t **a_colany_c,
                                    const uint64_t **btc_bits);
 
-/* The per-tile active-k lists, for inspection.  The matrix kernel walks, for every row tile
- * of 64 rows, every group of 16 columns and every step of 128 values of k (of k' in
- * row-compacted mode), the ascending list of the k in that step for which the group's
- * block(s) of B are occupied and some row of the tile has a non-zero element of A; it makes
- * these lists itself, a window of steps at a time, from the transposed B map and the
- * column-any words.  This call runs exactly that list construction (for the default tile
- * shape) and writes the lists to `out` (device memory) instead of multiplying:
+/* The per-tile active-k lists, for inspection: for every row tile of 64 rows, every group of 16
+ * columns and every step of 128 values of k (of k' in row-compacted mode), the ascending list of
+ * the k in that step for which the group's block(s) of B are occupied and some row of the tile has a
+ * non-zero element of A.  (The matrix kernel walks the lists of packed B, which are these without
+ * the condition on A.)  Derived from the transposed B map and the column-any words and written to
+ * `out` (device memory):
  *     record (tile t, group G, step c) at byte ((t * groups + G) * steps + c) * 132, where
  *     groups = 16 * ceil(N / 256), steps = ceil(K / 128):
  *     uint32 count, then `count` bytes k - 128 c (ascending), then unspecified bytes.
@@ -195,7 +193,9 @@ mmm_status mmm_maps_view_compacted(const mmm_maps *maps, int32_t *on, const uint
 mmm_status mmm_debug_k_lists(const mmm_maps *maps, void *out, size_t out_bytes, size_t *bytes_needed,
                              void *hip_stream);
 
-/* Device pointers to the blocked non-zero lists of A, for inspection.  A is cut
+/* Device pointers to the blocked non-zero lists of A (the count-and-offsets form of Fig. "Blocked
+ * sparse row preprocessing", with the values), for inspection: this call makes them from the image
+ * of A, on the stream of the last mmm_build_maps.  A is cut
  * into *blocks_m x *blocks_k blocks of 64 rows x 128 columns (ragged at the far
  * edges); block (bm, bk) has index bm * *blocks_k + bk.
  *   counts [block]            : number of non-zero elements of A in the block
@@ -208,7 +208,7 @@ mmm_status mmm_debug_k_lists(const mmm_maps *maps, void *out, size_t out_bytes, 
  * In row-compacted mode (see mmm_maps_view_compacted) the columns are the live columns k': block
  * (bm, bk) holds k' in [128 bk, 128 bk + 128), column_in_block = k' - 128 bk, and only the blocks
  * with 128 bk < K' are written.
- * Errors: MMM_ERR_INVALID_ARG. */
+ * Errors: MMM_ERR_INVALID_ARG, MMM_ERR_DEVICE. */
 mmm_status mmm_maps_view_lists(const mmm_maps *maps, const uint32_t **counts, const uint64_t **entries,
                                int64_t *blocks_m, int64_t *blocks_k, int64_t *capacity);
 
@@ -224,11 +224,12 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
 /* C = A x B (accumulate == 0) or C += A x B (accumulate != 0) using the maps:
  *     C[i,j] (+)= sum over k with a_bits[i,k] & b_bits[k, j div bw] of X[i,k] * Y[k,j]
  * (paper, section 3 "Matrix Multiplication", Fig. "MMM Pseudocode").  X and Y
- * must hold the same values the maps were built from: the values of A are taken
- * from the lists mmm_build_maps wrote (X is not read again), those of B from Y.
- * WARNING: after X has been changed in place the A side must be rebuilt
- * (mmm_build_maps with Y == NULL) before the next mmm_matmul; otherwise C is
- * computed from the old values without any error.  What can be checked is: X
+ * must hold the same values the maps were built from: MMM_PATH_MATRIX takes the
+ * values of A and B from the image and the packed form mmm_build_maps wrote (X and
+ * Y are not read again), MMM_PATH_PAIRS from X and Y.
+ * WARNING: after X or Y has been changed in place its side must be rebuilt
+ * (mmm_build_maps with the other side NULL) before the next mmm_matmul; otherwise C
+ * may be computed from the old values without any error.  What can be checked is: X
  * and ldx must be the ones the A side was built from (MMM_ERR_MAPS_MISMATCH).
  * Products the maps skip contribute exactly 0, whatever the skipped operands
  * hold (see the conventions above for non-finite kept values).  Every element
@@ -242,14 +243,13 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
                       void *C, int64_t ldc, int32_t accumulate, void *hip_stream);
 
 /* Which kernel mmm_matmul uses.
- *   MMM_PATH_MATRIX: matrix instructions over the compacted k lists of each 16-column group; skips
- *       B's empty blocks exactly and A's zeros only where a whole column of a 64-row tile is zero.
- *       Work grows with B's density alone.
+ *   MMM_PATH_MATRIX: matrix instructions over the packed rows of each 16-column group; skips B's
+ *       empty blocks exactly, multiplies A's zeros.  Work grows with B's density alone.
  *   MMM_PATH_PAIRS : vector FMAs over exactly the products that survive both maps (the loop of
  *       Fig. "MMM Pseudocode": skip when the element of A is zero, skip the empty blocks of the row
  *       of B), found by AND-ing the bitmap row of A with the transposed B map.  Work grows with
- *       the product of both densities, at a higher cost per product.  Reads X itself (not the
- *       lists of the maps).  Needs ldy * sizeof(element) below 2^20 bytes; beyond that mmm_matmul
+ *       the product of both densities, at a higher cost per product.  Reads X and Y
+ *       themselves.  Needs ldy * sizeof(element) below 2^20 bytes; beyond that mmm_matmul
  *       uses MATRIX whatever was asked for.
  * Automatic choice (path -1): MATRIX if a tile variant has been fixed (mmm_maps_set_plan or the
  * "matmul_variant" option).  Else, with p_A and p_B the densities of A's elements and B's

@@ -28,7 +28,7 @@ std::atomic<int64_t> g_opt_path{-1};
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t a_bits, a_colany, a_cnt, a_ent, b_bits, bt_bits, stats, kinfo, kmap, a_colany_c, btc_bits, Bc, partials, partial_bytes, total;
+    size_t a_bits, a_colany, a_cnt, a_ent, a_img, b_bits, bt_bits, stats, kinfo, kmap, rows_copy, a_colany_c, btc_bits, bp_val, bp_list, bp_cnt, partials, partial_bytes, total;
 };
 
 bool shape_ok(int64_t M, int64_t K, int64_t N, int32_t bw)
@@ -55,23 +55,33 @@ Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw)
     off += align_up(blocks * 4);
     l.a_ent = off;
     off += align_up(blocks * MMM_AB_CAP * 8);
+    l.a_img = off;   // room for the widest element type with an image
+    off += align_up(blocks * MMM_AB_CAP * 4);
     l.b_bits = off;
     off += align_up((size_t)K * WB * 8);
     l.bt_bits = off;
     off += align_up((size_t)NB * WA * 8);
     l.stats = off;
     off += align_up(4 * 8);
-    // row-compacted mode: numbering of the live rows, maps over it, and room for every row of Y in its widest type
+    // row-compacted mode: numbering of the live rows and maps over it
     l.kinfo = off;
     off += align_up(64);
     l.kmap = off;
     off += align_up((size_t)K * 4);
+    l.rows_copy = off;
+    off += align_up((size_t)WA * 8);
     l.a_colany_c = off;
     off += align_up((size_t)MT * WA * 8);
     l.btc_bits = off;
     off += align_up((size_t)NB * WA * 8);
-    l.Bc = off;
-    off += align_up((size_t)K * (size_t)N * 4);
+    // packed B: every row of every 16-column group, in the widest element type that is packed
+    const size_t segs = (size_t)((N + MMM_GROUP_COLS - 1) / MMM_GROUP_COLS) * (size_t)((K + MMM_AB_COLS - 1) / MMM_AB_COLS);
+    l.bp_val = off;
+    off += align_up(segs * MMM_AB_COLS * MMM_GROUP_COLS * 4);
+    l.bp_list = off;
+    off += align_up(segs * MMM_AB_COLS * 2);
+    l.bp_cnt = off;
+    off += align_up(segs * 4);
     l.partials = off;
     // room for up to 32 splits of C, capped
     size_t want = (size_t)M * (size_t)N * sizeof(float) * 32;
@@ -99,7 +109,7 @@ mmm_plan make_plan(const mmm_maps *m, int32_t dt)
         // still gives every CU a workgroup, else the 128-column tile (eight waves); matrices too small
         // to fill the machine that way, and too short in K for a split to pay, take the 64-column tile
         if (m->M <= 32) {
-            v = 5;
+            v = 3;
         } else {
             const int64_t tm = (m->M + 63) / 64, chunks = (m->K + MMM_AB_COLS - 1) / MMM_AB_COLS;
             const int64_t t256 = tm * ((m->N + 255) / 256), t128 = tm * ((m->N + 127) / 128);
@@ -211,6 +221,8 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->MBA = (M + MMM_AB_ROWS - 1) / MMM_AB_ROWS;
     m->KBA = (K + MMM_AB_COLS - 1) / MMM_AB_COLS;
     m->a_cnt = reinterpret_cast<uint32_t *>(base + l.a_cnt);
+    m->NG = (N + MMM_GROUP_COLS - 1) / MMM_GROUP_COLS;
+    m->a_img = base + l.a_img;
     m->a_ent = reinterpret_cast<uint64_t *>(base + l.a_ent);
     m->b_bits = reinterpret_cast<uint64_t *>(base + l.b_bits);
     m->bt_bits = reinterpret_cast<uint64_t *>(base + l.bt_bits);
@@ -219,7 +231,10 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->kmap = reinterpret_cast<uint32_t *>(base + l.kmap);
     m->a_colany_c = reinterpret_cast<uint64_t *>(base + l.a_colany_c);
     m->btc_bits = reinterpret_cast<uint64_t *>(base + l.btc_bits);
-    m->Bc = base + l.Bc;
+    m->rows_copy = reinterpret_cast<uint64_t *>(base + l.rows_copy);
+    m->bp_val = base + l.bp_val;
+    m->bp_list = reinterpret_cast<uint16_t *>(base + l.bp_list);
+    m->bp_cnt = reinterpret_cast<uint32_t *>(base + l.bp_cnt);
     m->partials = reinterpret_cast<float *>(base + l.partials);
     m->partial_bytes = l.partial_bytes;
     m->ws = dev_workspace;
@@ -227,6 +242,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->a_built = m->b_built = false;
     m->a_compact = m->b_compact = false;
     m->a_dtype = m->b_dtype = -1;
+    m->build_stream = nullptr;
     m->a_src = nullptr;
     m->a_src_ld = 0;
     m->plan_variant = -1;
@@ -274,8 +290,8 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         a.keep_blocks = mb->keep_blocks;
     }
     // Row-compacted mode: when keep_rows switches whole rows of B off, the live rows are numbered k' and the
-    // matrix kernel walks k' (steps of 128 live rows instead of 128 rows of which few are live).  The lists of
-    // A are then made over k', so they are only good for the numbering they were made for.
+    // matrix kernel walks k' (steps of 128 live rows instead of 128 rows of which few are live).  A is then laid
+    // out over k', so its image is only good for the numbering it was made for.
     a.b_compact = Y != nullptr && mb->keep_rows != nullptr && dt != MMM_F64;
     const bool compact_after = Y != nullptr ? a.b_compact : maps->b_compact;
     a.a_compact = X != nullptr && compact_after;
@@ -285,8 +301,9 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         note_device_error("map builder launch", e);
         return MMM_ERR_DEVICE;
     }
+    maps->build_stream = static_cast<hipStream_t>(hip_stream);
     if (Y != nullptr) {
-        // lists of A made for another numbering of k (or for none) do not fit the new B side
+        // an image of A made for another numbering of k (or for none) do not fit the new B side
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
         maps->b_compact = a.b_compact;
     }
@@ -334,6 +351,12 @@ mmm_status mmm_maps_view_compacted(const mmm_maps *maps, int32_t *on, const uint
     if (kmap) *kmap = maps->kmap;
     if (a_colany_c) *a_colany_c = maps->a_colany_c;
     if (btc_bits) *btc_bits = maps->btc_bits;
+    // the multiplication does not read the column-any words over k': they are made here
+    if (a_colany_c != nullptr && maps->a_built && maps->a_compact)
+        if (hipError_t e = mmm_launch_colany_compact(maps, maps->build_stream); e != hipSuccess) {
+            note_device_error("column-any words over the live rows", e);
+            return MMM_ERR_DEVICE;
+        }
     return MMM_OK;
 }
 
@@ -363,6 +386,12 @@ mmm_status mmm_maps_view_lists(const mmm_maps *maps, const uint32_t **counts, co
     if (blocks_m) *blocks_m = maps->MBA;
     if (blocks_k) *blocks_k = maps->KBA;
     if (capacity) *capacity = MMM_AB_CAP;
+    // the multiplication reads the image of A, not lists: they are made here, from the image
+    if ((counts != nullptr || entries != nullptr) && maps->a_built && maps->a_dtype != MMM_F64)
+        if (hipError_t e = mmm_launch_lists(maps, maps->build_stream); e != hipSuccess) {
+            note_device_error("lists of A", e);
+            return MMM_ERR_DEVICE;
+        }
     return MMM_OK;
 }
 
@@ -416,7 +445,7 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
     if (dt == MMM_F64 && !mmm_pairs_supports(dt, ldy)) return MMM_ERR_SHAPE;   // double inputs have the pair kernel only
     if (!maps->a_built || !maps->b_built) return MMM_ERR_MAPS_MISMATCH;
     if (maps->a_dtype != dt || maps->b_dtype != dt) return MMM_ERR_MAPS_MISMATCH;
-    // the values of A travel in the lists that were copied from X at build time: another X is another A
+    // the values of A travel in the image that was made from X at build time: another X is another A
     if (maps->a_src != X || maps->a_src_ld != ldx) return MMM_ERR_MAPS_MISMATCH;
     if (dt == MMM_F64 || (choose_path(maps) == MMM_PATH_PAIRS && mmm_pairs_supports(dt, ldy))) {   // no scratch at all on this path
         if (hipError_t e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, false, 0, 0.f, nullptr,
@@ -444,7 +473,7 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
         }
         partial_bytes = (size_t)MMM_STATIC_SCRATCH_BYTES;
     }
-    if (hipError_t e = mmm_launch_matmul(maps, p, dt, X, ldx, Y, ldy, static_cast<float *>(C), ldc, accumulate ? 1 : 0, partials,
+    if (hipError_t e = mmm_launch_matmul(maps, p, dt, static_cast<float *>(C), ldc, accumulate ? 1 : 0, partials,
                                          partial_bytes, static_cast<hipStream_t>(hip_stream));
         e != hipSuccess) {
         note_device_error("masked GEMM launch", e);

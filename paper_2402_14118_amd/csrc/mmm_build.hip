@@ -1,28 +1,32 @@
-// Map builder: evaluates the masks M and N on the device and writes the
-// sparsity maps (paper, section 3 "Preprocessing": a single sequential, aligned
-// pass per matrix).  Everything here is integer work on float bit patterns,
-// bound by HBM bandwidth.
+// Map builder: evaluates the masks M and N on the device, writes the sparsity maps (paper, section 3
+// "Preprocessing": a single sequential, aligned pass per matrix) and lays both operands out for the
+// matrix kernel.  Everything here is integer work on bit patterns, bound by HBM bandwidth.
 //
-// A side (section 3 "Optimizations", Fig. "Blocked sparse row preprocessing"):
-// per block of 64 rows x 128 columns the count of non-zero elements and their
-// positions inside the block, here together with the values, in row-major order;
-// plus the plain non-zero bitmap and its column-any summary.
-// B side (section 3 "Block-Random Sparsity in B", Fig. "Preprocessing
-// patterns"): one bit per block, 1 = some non-zero value; plus the same map
-// transposed to one bit-row per block column.
+// A side (section 3 "Optimizations", Fig. "Blocked sparse row preprocessing"): the non-zero bitmap, its
+// column-any summary, and an image of A: blocks of 64 rows x 128 columns with the masked-out elements
+// replaced by zero, in exactly the byte order the matrix kernel keeps a block in LDS, so that the
+// kernel's copy is one asynchronous load per 1 KiB and needs no registers, no conversion and no
+// per-element work.  (Lists of {offset, value} per block, scattered with LDS atomics by every one of
+// the N/256 workgroups that need the block, cost the kernel about 0.4 us per step of 128 k.)
+// B side (section 3 "Block-Random Sparsity in B", Fig. "Preprocessing patterns"): one bit per block,
+// 1 = some non-zero value; the same map transposed to one bit-row per block column; and B packed: for
+// every group of 16 columns and segment of 128 k the occupied pieces of rows one after another, with
+// the list of their k.  A wave of the matrix kernel owns one group and reads both linearly.
 //
-// One launch covers both matrices: the first n_a workgroups scan X, the rest
-// scan Y.  Every output word in device memory has exactly one producer, so no
+// One launch covers both matrices.  Every output word in device memory has exactly one producer, so no
 // global atomics are used and nothing needs clearing beforehand.
 #include "mmm_internal.h"
 
 namespace {
 
-constexpr int BUILD_WAVES = 8;
+constexpr int BUILD_WAVES = 16;
 constexpr int BUILD_THREADS = BUILD_WAVES * 64;
-constexpr int A_ROWS_PER_WAVE = MMM_AB_ROWS / BUILD_WAVES;   // 8
-constexpr int A_WORDS = MMM_AB_COLS / 64;                    // 2
-constexpr int B_ROWS_PER_WAVE = MMM_BT_PIECE / BUILD_WAVES;  // 2
+constexpr int SEG = MMM_AB_COLS;                      // rows of B (values of k) per workgroup = k per step of the matrix kernel
+constexpr int B_ROWS = SEG / BUILD_WAVES;             // 8 rows per wave
+constexpr int B_COLS = 256;                           // columns of B per workgroup: four per lane
+constexpr int B_GROUPS = B_COLS / MMM_GROUP_COLS;     // 16
+constexpr int A_ROWS = MMM_AB_ROWS / BUILD_WAVES;     // 4 rows of A per wave
+constexpr int A_WORDS = MMM_AB_COLS / 64;             // 2
 
 struct BuildParams {
     const void *X;
@@ -30,26 +34,30 @@ struct BuildParams {
     const uint64_t *keep_a;
     uint64_t *a_bits;
     uint64_t *a_colany;
-    uint32_t *a_cnt;
-    uint2 *a_ent;
+    char *a_img;
     const void *Y;
     int64_t ldy;
     const uint64_t *keep_rows;
     const uint64_t *keep_blocks;
     uint64_t *b_bits;
-    uint16_t *bt_pieces;   // the transposed B map seen as pieces of MMM_BT_PIECE bits
-    int64_t M, K, N, NB, WA, WB, MT, KBA;
+    uint64_t *bt_bits;
+    char *bp_val;         // packed B: [group][segment][128 slots][16 columns]
+    uint16_t *bp_list;    // [group][segment][128]
+    uint32_t *bp_cnt;     // [group][segment]
+    int64_t M, K, N, NB, WA, WB, MT, KBA, NG;
     uint32_t thr_bits;
     int32_t pred;
-    uint32_t n_a;    // workgroups that scan X block by block (bitmaps and, unless row-compacted, lists)
-    uint32_t n_ac;   // row-compacted mode: workgroups that list the blocks of A over the live k only
-    uint32_t n_b;    // workgroups that scan Y
-    // row-compacted mode (whole rows of B switched off by keep_rows): k' = 0 .. *kinfo - 1 numbers the live rows
-    const uint32_t *kinfo;   // [0] = number of live k
-    const uint32_t *kmap;    // k' -> k
-    uint64_t *a_colany_c;    // column-any words of A over k'
-    uint16_t *btc_pieces;    // transposed B map over k'
-    void *Bc;                // the live rows of Y, row k' at Bc + k' * N elements (kept blocks only)
+    int32_t y_unaligned;  // 16-bit Y whose rows do not start on 4-byte boundaries
+    uint32_t n_a;         // workgroups that scan X, one per block
+    uint32_t n_b;         // workgroups that scan Y (row-compacted mode: bitmaps only)
+    uint32_t n_bc;        // row-compacted mode: workgroups that pack the live rows of Y
+    uint32_t ctiles;      // column tiles of 256 per segment
+    // row-compacted mode (whole rows of B switched off): k' = 0 .. K' - 1 numbers the rows `rows` leaves on
+    const uint64_t *rows;    // keep_rows, or the copy of it a cached B side was built with; else null
+    uint64_t *rows_copy;     // where that copy goes (B side built in this call)
+    uint32_t *kinfo;         // [0] = K'
+    uint32_t *kmap;          // k' -> k
+    uint64_t *btc_bits;      // transposed B map over k'
 };
 
 template <typename T> __device__ __forceinline__ uint32_t f32_bits(T v);
@@ -84,383 +92,514 @@ __device__ __forceinline__ uint32_t mbcnt64(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// ---- A side: one workgroup = one block of 64 rows x 128 columns ------------------------------
-// Wave w scans rows 8w..8w+7, one 64-column word per load.  Lane 2j+h of the wave ends up
-// holding the bitmap word (row j, half h); entries are appended in (row, column) order.
-// MODE A_FULL: bitmap words, column-any words and the block's list, all over the original k.
-// MODE A_MAPS: bitmap and column-any words only (row-compacted mode: the lists are made by A_LISTS).
-// MODE A_LISTS: the block is 64 rows x 128 *live* k (k' = 128 bj ..): its elements are gathered through
-//   kmap; it writes the list and the column-any words over k'.
-enum { A_FULL = 0, A_MAPS = 1, A_LISTS = 2 };
-
-template <typename T, int PRED, int MODE>
-__device__ __forceinline__ void scan_a(const BuildParams &p, uint32_t b, int lane, int wave, uint64_t *red,
-                                       uint32_t *tot)
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
 {
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), l) << 32) |
+           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)v, l);
+}
+
+// Bits of two wave-uniform 32-bit masks interleaved: bit 2i = bit i of e, bit 2i + 1 = bit i of o.
+__device__ __forceinline__ uint64_t interleave(uint32_t e, uint32_t o)
+{
+    uint64_t a, b;   // s_bitreplicate writes every bit twice
+    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(a) : "s"(e));
+    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(b) : "s"(o));
+    return (a & 0x5555555555555555ull) | (b & 0xaaaaaaaaaaaaaaaaull);
+}
+
+// word w of a bitmap row of K bits with the bits past K cleared
+__device__ __forceinline__ uint64_t row_word(const uint64_t *row, int64_t w, int64_t K)
+{
+    const uint64_t m = row[w];
+    const int64_t left = K - w * 64;
+    return left >= 64 ? m : m & ((1ull << left) - 1ull);
+}
+
+// ---- A side: one workgroup = one block of 64 rows x 128 columns ------------------------------
+// A wave takes the four rows that are neighbours in an LDS column: w, w+16, w+32, w+48 for 4-byte
+// elements (one 16-byte read of the matrix kernel yields one element for each of its four 16-row
+// tiles), 4w .. 4w+3 for 16-bit ones (natural order: the transposing LDS read wants contiguous rows).
+// The block is turned around in LDS (16-byte or 8-byte pieces whose position is rotated with k, so that
+// the 64 lanes of a write do not fall on the same banks) and leaves as whole cache lines.
+// Measured on 4096^2 fp32: see the note at mmm_launch_build.
+struct AShared {
+    char stage[MMM_AB_COLS * MMM_AB_ROWS * 4];
+    uint64_t any[BUILD_WAVES][2][A_WORDS];   // [wave][32-row half of the block][word]
+    uint8_t live[MMM_AB_COLS];               // row-compacted mode: live columns of the block
+    uint32_t base, nlive;                    // k' of the first of them, and how many
+};
+
+template <typename T, int PRED>
+__device__ __forceinline__ void scan_a(const BuildParams &p, uint32_t b, int lane, int wave, AShared &sh)
+{
+    constexpr bool WIDE = sizeof(T) == 4;
     const int64_t bi = b / p.KBA, bj = b % p.KBA;
-    const int64_t k_lo = bj * MMM_AB_COLS;
-    const int64_t rbase = bi * MMM_AB_ROWS + wave * A_ROWS_PER_WAVE;
-    const int64_t w_lo = k_lo / 64;
-    const T *X = static_cast<const T *>(p.X);
-    const int64_t klim = MODE == A_LISTS ? (int64_t)*p.kinfo : p.K;   // number of (live) k
-    if (MODE == A_LISTS && k_lo >= klim) return;                      // no live k left for this block (whole workgroup)
-    // Every load below is unconditional: indices are clamped into the matrix and the results masked
-    // afterwards.  A load inside a branch is waited for before the next one is issued; written this way
-    // the wave's 16 row pieces and its keep words are all in flight together.
+    const int64_t k_lo = bj * MMM_AB_COLS, w_lo = k_lo / 64;
+    const int64_t row0 = bi * MMM_AB_ROWS;
+    auto row_of = [&](int t) -> int64_t { return row0 + (WIDE ? wave + 16 * t : wave * 4 + t); };
     const bool has_keep = p.keep_a != nullptr;
-    // keep words of the wave's 16 (row, half) pairs, one per lane 2j+h (lanes 16.. repeat them; unused)
-    uint64_t kw = ~0ull;
-    if (MODE != A_LISTS && has_keep) {   // wave-uniform
-        const int64_t kr = min(rbase + ((lane & 15) >> 1), p.M - 1), kwd = min(w_lo + (lane & 1), p.WA - 1);
-        kw = p.keep_a[kr * p.WA + kwd];
-    }
-    int64_t korig[A_WORDS];   // A_LISTS: the original k of this lane's two columns (-1: none)
+    const bool compact = p.rows != nullptr;
+    // Every load below is unconditional (indices are clamped, results masked afterwards): a load inside a
+    // branch is waited for before the next one is issued.
+    uint64_t kw = ~0ull;   // keep words of the wave's (row, half) pairs, one per lane 2t + h
+    if (has_keep) kw = p.keep_a[min(row_of((lane >> 1) & 3), p.M - 1) * p.WA + min(w_lo + (lane & 1), p.WA - 1)];
+    uint64_t word[A_ROWS][A_WORDS];   // bitmap words (wave-uniform)
+    if constexpr (WIDE) {
+        uint32_t u[A_ROWS][A_WORDS];
 #pragma unroll
-    for (int h = 0; h < A_WORDS; ++h) {
-        const int64_t k = k_lo + 64 * h + lane;
-        korig[h] = k < p.K ? k : -1;
-        if (MODE == A_LISTS) {
-            const uint32_t km = p.kmap[min(k, p.K - 1)];
-            korig[h] = k < klim ? (int64_t)km : -1;
-        }
-    }
-    uint32_t u[A_ROWS_PER_WAVE][A_WORDS];
-    uint32_t kbyte[A_ROWS_PER_WAVE][A_WORDS];   // A_LISTS with a keep bitmap: the byte that holds the element's keep bit
+        for (int t = 0; t < A_ROWS; ++t)
 #pragma unroll
-    for (int j = 0; j < A_ROWS_PER_WAVE; ++j) {
+            for (int h = 0; h < A_WORDS; ++h)
+                u[t][h] = f32_bits<T>(static_cast<const T *>(p.X)[min(row_of(t), p.M - 1) * p.ldx + min(k_lo + 64 * h + lane, p.K - 1)]);
 #pragma unroll
-        for (int h = 0; h < A_WORDS; ++h) {
-            const int64_t rc = min(rbase + j, p.M - 1), kc = max(korig[h], (int64_t)0);
-            u[j][h] = f32_bits<T>(X[rc * p.ldx + kc]);
-            kbyte[j][h] = 0xffu;
-            if (MODE == A_LISTS && has_keep)   // wave-uniform
-                kbyte[j][h] = reinterpret_cast<const uint8_t *>(p.keep_a)[(rc * p.WA) * 8 + (kc >> 3)];
-        }
-    }
-    uint32_t kbit[A_ROWS_PER_WAVE] = {};   // A_LISTS: keep bits of this lane's elements, bit h of entry j
+        for (int t = 0; t < A_ROWS; ++t)
 #pragma unroll
-    for (int j = 0; j < A_ROWS_PER_WAVE; ++j) {
-#pragma unroll
-        for (int h = 0; h < A_WORDS; ++h) {
-            const bool inside = rbase + j < p.M && korig[h] >= 0;
-            if (!inside) u[j][h] = 0;   // +0: never kept
-            if (MODE == A_LISTS) kbit[j] |= (inside ? (kbyte[j][h] >> (korig[h] & 7)) & 1u : 0u) << h;
-        }
-    }
-    uint64_t colany[A_WORDS] = {0, 0};
-    uint32_t mine_lo = 0, mine_hi = 0;   // lane 2j+h: the bitmap word of (row j, half h)
-#pragma unroll
-    for (int j = 0; j < A_ROWS_PER_WAVE; ++j) {
-#pragma unroll
-        for (int h = 0; h < A_WORDS; ++h) {
-            uint64_t m;
-            if (MODE == A_LISTS) {
-                m = ballot64(keep_element<PRED>(u[j][h], p.thr_bits) && ((kbit[j] >> h) & 1u));
-            } else {
-                m = ballot64(keep_element<PRED>(u[j][h], p.thr_bits));   // lanes past K or M hold +0
-                m &= ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(kw >> 32), 2 * j + h) << 32) |
-                     (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)kw, 2 * j + h);
+            for (int h = 0; h < A_WORDS; ++h) {
+                const bool inside = row_of(t) < p.M && k_lo + 64 * h + lane < p.K;
+                const uint64_t m = ballot64(inside && keep_element<PRED>(u[t][h], p.thr_bits)) & readlane64(kw, 2 * t + h);
+                word[t][h] = m;
+                u[t][h] = __builtin_amdgcn_inverse_ballot_w64(m) ? u[t][h] : 0u;   // the word is the lane mask of what stays
             }
-            colany[h] |= m;
-            const bool owner = __builtin_amdgcn_inverse_ballot_w64(1ull << (2 * j + h));   // lane 2j+h, as a constant mask
-            mine_lo = owner ? (uint32_t)m : mine_lo;
-            mine_hi = owner ? (uint32_t)(m >> 32) : mine_hi;
-        }
-    }
-    const uint64_t mine = ((uint64_t)mine_hi << 32) | mine_lo;
-    // bitmap words and per-wave entry offsets
-    const bool have_word = lane < 2 * A_ROWS_PER_WAVE && rbase + (lane >> 1) < p.M && w_lo + (lane & 1) < p.WA;
-    if (MODE != A_LISTS && have_word) p.a_bits[(rbase + (lane >> 1)) * p.WA + w_lo + (lane & 1)] = mine;
-    const uint32_t my_cnt = (uint32_t)__popcll(mine);   // lanes past the wave's words hold 0
-    uint32_t incl = my_cnt;
 #pragma unroll
-    for (int d = 1; d < 2 * A_ROWS_PER_WAVE; d <<= 1) {
-        const uint32_t o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
+        for (int h = 0; h < A_WORDS; ++h) {
+            const int k = 64 * h + lane;
+            *reinterpret_cast<uint4 *>(sh.stage + k * 256 + ((wave ^ (k & 15)) << 4)) = make_uint4(u[0][h], u[1][h], u[2][h], u[3][h]);
+        }
+    } else {
+        // two neighbouring k per lane and load, at any 2-byte alignment; the last column of an odd K is read
+        // together with the one before it, so that nothing past the row is touched
+        typedef uint32_t u32_any __attribute__((aligned(2)));
+        uint32_t d[A_ROWS], kb[A_ROWS];
+        const int64_t k = k_lo + 2 * lane;
+#pragma unroll
+        for (int t = 0; t < A_ROWS; ++t) {
+            const int64_t r = min(row_of(t), p.M - 1);
+            const T *xr = static_cast<const T *>(p.X) + r * p.ldx;
+            d[t] = p.K > 1 ? *reinterpret_cast<const u32_any *>(xr + min(k, p.K - 2)) : (uint32_t)*reinterpret_cast<const uint16_t *>(xr);
+            kb[t] = 0xffu;
+            if (has_keep) kb[t] = reinterpret_cast<const uint8_t *>(p.keep_a + r * p.WA)[min(k, p.K - 1) >> 3];
+        }
+#pragma unroll
+        for (int t = 0; t < A_ROWS; ++t) {
+            if (k == p.K - 1 && p.K > 1) d[t] >>= 16;
+            const bool in0 = row_of(t) < p.M && k < p.K, in1 = row_of(t) < p.M && k + 1 < p.K;
+            const uint32_t kbit = kb[t] >> (k & 7);
+            const bool e = in0 && (kbit & 1u) && keep_element<PRED>(f32_bits<T>(__builtin_bit_cast(T, (uint16_t)d[t])), p.thr_bits);
+            const bool o = in1 && (kbit & 2u) && keep_element<PRED>(f32_bits<T>(__builtin_bit_cast(T, (uint16_t)(d[t] >> 16))), p.thr_bits);
+            const uint64_t me = ballot64(e), mo = ballot64(o);
+            word[t][0] = interleave((uint32_t)me, (uint32_t)mo);
+            word[t][1] = interleave((uint32_t)(me >> 32), (uint32_t)(mo >> 32));
+            d[t] = (e ? d[t] & 0xffffu : 0u) | (o ? d[t] & 0xffff0000u : 0u);
+        }
+        // rows 4w .. 4w+3 of columns 2 lane and 2 lane + 1
+        char *at = sh.stage + (2 * lane) * 128 + ((wave ^ ((lane & 7) << 1)) << 3);
+        *reinterpret_cast<uint2 *>(at) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u));
+        *reinterpret_cast<uint2 *>(at + 128) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u));
     }
-    const uint32_t excl = incl - my_cnt;
-    if (lane == 2 * A_ROWS_PER_WAVE - 1) tot[wave] = incl;
-    if (lane == 0) {
-        red[wave * A_WORDS + 0] = colany[0];
-        red[wave * A_WORDS + 1] = colany[1];
+    // bitmap words: lane 2t + h stores the word of (row t, half h)
+    uint64_t mine = 0;
+#pragma unroll
+    for (int t = 0; t < A_ROWS; ++t)
+#pragma unroll
+        for (int h = 0; h < A_WORDS; ++h) mine = __builtin_amdgcn_inverse_ballot_w64(1ull << (2 * t + h)) ? word[t][h] : mine;
+    if (lane < 2 * A_ROWS && row_of(lane >> 1) < p.M && w_lo + (lane & 1) < p.WA)
+        p.a_bits[row_of(lane >> 1) * p.WA + w_lo + (lane & 1)] = mine;
+    if (lane < 4) {   // column-any words of this wave's rows, by 32-row half of the block
+        const int t32 = lane >> 1, h = lane & 1;
+        uint64_t any;
+        if (WIDE)
+            any = t32 ? (h ? word[2][1] | word[3][1] : word[2][0] | word[3][0]) : (h ? word[0][1] | word[1][1] : word[0][0] | word[1][0]);
+        else
+            any = t32 != wave / (BUILD_WAVES / 2) ? 0ull
+                : h ? word[0][1] | word[1][1] | word[2][1] | word[3][1] : word[0][0] | word[1][0] | word[2][0] | word[3][0];
+        sh.any[wave][t32][h] = any;
+    }
+    if (compact && wave == BUILD_WAVES - 1) {   // which columns of the block are live, and the k' of the first
+        uint32_t before = 0;
+        for (int64_t w = lane; w < w_lo; w += 64) before += (uint32_t)__popcll(p.rows[w]);
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d, 64);
+        const uint64_t m0 = row_word(p.rows, w_lo, p.K), m1 = w_lo + 1 < p.WA ? row_word(p.rows, w_lo + 1, p.K) : 0ull;
+        if ((m0 >> lane) & 1ull) sh.live[mbcnt64(m0)] = (uint8_t)lane;
+        const uint32_t n0 = (uint32_t)__popcll(m0);
+        if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
+        if (lane == 0) {
+            sh.base = before;
+            sh.nlive = n0 + (uint32_t)__popcll(m1);
+        }
     }
     __syncthreads();
-    uint32_t base = 0;
-    for (int w = 0; w < wave; ++w) base += tot[w];
-    uint32_t total = 0;
-    for (int w = 0; w < BUILD_WAVES; ++w) total += tot[w];
-    if (MODE != A_MAPS && threadIdx.x == 0) p.a_cnt[b] = total;
-    if (threadIdx.x < 2 * A_WORDS) {   // column-any words of the two 32-row tiles of this block
-        const int t = threadIdx.x >> 1, h = threadIdx.x & 1;
-        const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t;
-        if (tile < p.MT && w_lo + h < p.WA)
-        {
-            uint64_t any = 0;   // waves t*W/2 .. (t+1)*W/2-1 cover the 32 rows of tile t
-            for (int w = t * (BUILD_WAVES / 2); w < (t + 1) * (BUILD_WAVES / 2); ++w) any |= red[w * A_WORDS + h];
-            (MODE == A_LISTS ? p.a_colany_c : p.a_colany)[tile * p.WA + w_lo + h] = any;
-        }
-    }
-    if (MODE == A_MAPS) return;
-    // compacted entries {byte offset inside the multiplier's LDS slab, value}, in (row, column) order
-    uint2 *ent = p.a_ent + (size_t)b * MMM_AB_CAP;
+    if (wave == 0) {   // lane (t32, h, wave): OR over the sixteen waves
+        const int t32 = lane >> 5, h = (lane >> 4) & 1;
+        uint64_t any = sh.any[lane & 15][t32][h];
+        uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
 #pragma unroll
-    for (int j = 0; j < A_ROWS_PER_WAVE; ++j) {
-#pragma unroll
-        for (int h = 0; h < A_WORDS; ++h) {
-            const uint32_t lo = __builtin_amdgcn_readlane(mine_lo, 2 * j + h);
-            const uint32_t hi = __builtin_amdgcn_readlane(mine_hi, 2 * j + h);
-            const uint64_t m = ((uint64_t)hi << 32) | lo;
-            if (m == 0) continue;
-            const uint32_t off = base + __builtin_amdgcn_readlane(excl, 2 * j + h);
-            if (__builtin_amdgcn_inverse_ballot_w64(m)) {   // the word is the lane mask of its own non-zero elements
-                const uint32_t slab = mmm_slab_pos((uint32_t)(wave * A_ROWS_PER_WAVE + j), (uint32_t)(64 * h + lane));
-                ent[off + mbcnt64(m)] = make_uint2(slab, u[j][h]);
-            }
+        for (int d = 1; d < 16; d <<= 1) {
+            lo |= (uint32_t)__shfl_xor((int)lo, d, 64);
+            hi |= (uint32_t)__shfl_xor((int)hi, d, 64);
         }
+        const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
+        if ((lane & 15) == 0 && tile < p.MT && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
     }
-    // pad the list to a whole number of wavefronts with entries that write 0 to a spare slab cell
-    if (wave == BUILD_WAVES - 1) {
-        const uint32_t e = total + lane;
-        if (e < ((total + 63u) & ~63u)) ent[e] = make_uint2(MMM_SLAB_SPARE, 0u);
+    // the image: column k (or k') of block row bi is one run of 64 elements
+    constexpr int UNITS = MMM_AB_ROWS * (int)sizeof(T) / 16;   // 16-byte units per column
+    const uint32_t base = compact ? sh.base : (uint32_t)k_lo;
+    const int cols = compact ? (int)sh.nlive : MMM_AB_COLS;
+    char *img = p.a_img + ((size_t)bi * p.KBA * MMM_AB_COLS + base) * (UNITS * 16);
+    for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
+        const int j = q / UNITS, unit = q % UNITS;
+        const int k = compact ? (int)sh.live[j] : j;
+        int at;
+        if (WIDE)
+            at = k * 256 + ((unit ^ (k & 15)) << 4);
+        else   // undo the rotation of the stage, apply that of the image (see mmm_img_swizzle)
+            at = k * 128 + ((unit ^ (int)mmm_img_swizzle(base + j) ^ ((k >> 1) & 7)) << 4);
+        *reinterpret_cast<uint4 *>(img + (size_t)q * 16) = *reinterpret_cast<const uint4 *>(sh.stage + at);
     }
 }
 
-// ---- B side: one workgroup = 16 rows (values of k) x 64 blocks -------------------------------
-template <typename T> __device__ __forceinline__ T raw_zero();
-template <> __device__ __forceinline__ float raw_zero<float>() { return 0.f; }
-template <> __device__ __forceinline__ uint16_t raw_zero<uint16_t>() { return 0; }
-template <> __device__ __forceinline__ _Float16 raw_zero<_Float16>() { return (_Float16)0; }
+// ---- B side: one workgroup = 128 rows (values of k) x 256 columns ----------------------------
+// A wave takes 8 rows; a lane owns four neighbouring columns of each, so that 4 lanes are one 16-column
+// group.  The 8 loads of a lane are in flight together; blocks the keep bitmaps switch off are given an
+// offset past the buffer's end, for which the hardware returns zero without touching memory.  The 128
+// occupancy bits of every lane's block are gathered in LDS, one byte per wave; from them follow the map
+// words, the transposed map words and the rank of every row within its group's segment, which is its
+// slot in the packed operand.
+struct BShared {
+    uint8_t gbits[64][BUILD_WAVES];   // [lane][wave]: rows in which the lane's 16-column group is occupied
+    uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
+    uint16_t list[B_GROUPS][SEG];
+    uint16_t pack[B_GROUPS / 2 * SEG * MMM_GROUP_COLS];   // 16-bit types: half of the groups, packed
+    int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
+    uint32_t sums[BUILD_WAVES];
+};
 
-// COMPACT (row-compacted mode): the workgroup's 16 rows are the live rows k' = 16 piece ..; they are read
-// through kmap, their kept blocks are copied to row k' of Bc, and the transposed map over k' is written
-// instead of b_bits and the transposed map over k (which the plain workgroups write).
-template <typename T, int BW, bool COMPACT>
-__device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int lane, int wave, uint32_t *pieces,
-                                       uint8_t (*gpos)[B_ROWS_PER_WAVE][64], uint64_t (*gword)[B_ROWS_PER_WAVE])
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Rows k' = seg*128 .. of the numbering given by `rows`, into sh.kk; returns K'.
+__device__ __forceinline__ uint32_t number_rows(const BuildParams &p, int64_t seg, int lane, int wave, BShared &sh)
 {
-    constexpr int BPL = 64 / BW;   // blocks covered by one 64-lane load
-    const int64_t piece = bb / p.WB, w = bb % p.WB;
-    const int64_t kbase = piece * MMM_BT_PIECE + wave * B_ROWS_PER_WAVE;
-    const T *Y = static_cast<const T *>(p.Y);
-    const int64_t klive = COMPACT ? (int64_t)*p.kinfo : 0;
-    // pieces past the last 128-step that holds a live k are never looked at (whole workgroup leaves)
-    if (COMPACT && piece * MMM_BT_PIECE >= (klive + MMM_AB_COLS - 1) / MMM_AB_COLS * MMM_AB_COLS) return;
-    const int64_t nb_left = p.NB - w * 64;
-    const uint64_t valid = nb_left >= 64 ? ~0ull : ((1ull << nb_left) - 1ull);
-    uint32_t piece_bits = 0;
-    // which blocks of the wave's rows the keep bitmaps leave switched on: lane r fetches the two
-    // keep words of row r, so that all of them are in flight together
-    uint64_t krw = ~0ull, kbw = ~0ull;
-    int64_t krow = -1;   // lane r: the row of Y behind the wave's row r (-1: none)
-    {
-        const int64_t kl = kbase + lane;
-        const int64_t kmapped = COMPACT ? (int64_t)p.kmap[min(kl, p.K - 1)] : kl;   // loaded unconditionally
-        if (lane < B_ROWS_PER_WAVE && kl < (COMPACT ? klive : p.K)) krow = kmapped;
-        const bool mine = krow >= 0;
-        const int64_t kc = max(krow, (int64_t)0);   // unconditional loads at clamped rows, masked below
-        if (p.keep_rows != nullptr) krw = p.keep_rows[kc >> 6];        // wave-uniform branches
-        if (p.keep_blocks != nullptr) kbw = p.keep_blocks[kc * p.WB + w];
-        if (!mine) krw = kbw = ~0ull;
+    const int tid = threadIdx.x;
+    if (tid < SEG) sh.kk[tid] = -1;
+    const int64_t per = (p.WA + BUILD_THREADS - 1) / BUILD_THREADS;   // every thread counts a run of words
+    const int64_t w0 = tid * per, w1 = min(p.WA, w0 + per);
+    uint32_t cnt = 0;
+    for (int64_t w = w0; w < w1; ++w) cnt += (uint32_t)__popcll(row_word(p.rows, w, p.K));
+    uint32_t incl = cnt;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = (uint32_t)__shfl_up((int)incl, d, 64);
+        if (lane >= d) incl += o;
     }
-    uint64_t kept[B_ROWS_PER_WAVE];
-    int64_t korig[B_ROWS_PER_WAVE];
+    if (lane == 63) sh.sums[wave] = incl;
+    __syncthreads();
+    uint32_t pos = incl - cnt, total = 0;
 #pragma unroll
-    for (int r = 0; r < B_ROWS_PER_WAVE; ++r) {
-        korig[r] = ((int64_t)__builtin_amdgcn_readlane((int32_t)(krow >> 32), r) << 32) |
-                   (int64_t)(uint32_t)__builtin_amdgcn_readlane((int32_t)krow, r);
+    for (int w = 0; w < BUILD_WAVES; ++w) {
+        const uint32_t s = sh.sums[w];
+        if (w < wave) pos += s;
+        total += s;
     }
-#pragma unroll
-    for (int r = 0; r < B_ROWS_PER_WAVE; ++r) {
-        const int64_t k = korig[r];
-        const uint64_t kr = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(krw >> 32), r) << 32) |
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)krw, r);
-        const uint64_t kb = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(kbw >> 32), r) << 32) |
-                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)kbw, r);
-        kept[r] = k >= 0 ? valid & kb & (0ull - ((kr >> (k & 63)) & 1ull)) : 0ull;
+    const uint32_t lo = (uint32_t)seg * SEG;
+    if (pos < lo + SEG && pos + cnt > lo) {
+        for (int64_t w = w0; w < w1; ++w)
+            for (uint64_t m = row_word(p.rows, w, p.K); m != 0; m &= m - 1, ++pos)
+                if (pos >= lo && pos < lo + SEG) sh.kk[pos - lo] = (int32_t)(w * 64 + __builtin_ctzll(m));
     }
-    constexpr int PER = BW <= 8 ? BW : 8;     // loads in flight per lane and row
-#pragma unroll
-    for (int r = 0; r < B_ROWS_PER_WAVE; ++r) {
-        const int64_t k = korig[r];
-        uint64_t word = 0;
-        if (kept[r] != 0) {
-            const T *row = Y + k * p.ldy + w * 64 * BW;
-            T *crow = COMPACT ? static_cast<T *>(p.Bc) + (kbase + r) * p.N + w * 64 * BW : nullptr;
-            const uint64_t bwmask = BW == 32 ? 0xffffffffull : ((1ull << BW) - 1ull);
-            constexpr int ROUNDS = 4;   // gather path: at most ROUNDS loads of BPL kept blocks each
-            const int nkept = __popcll(kept[r]);
-            if (nkept <= ROUNDS * BPL) {
-                // Few blocks are switched on: their positions are compacted into a short list (lane b
-                // writes b at the rank of bit b), and one load fetches BPL listed blocks, wherever
-                // they are.  The list and the result word are private to the wave and the row; LDS
-                // executes the wave's accesses in order.
-                uint8_t *plist = gpos[wave][r];
-                uint64_t *res = &gword[wave][r];
-                if ((kept[r] >> lane) & 1ull) plist[mbcnt64(kept[r])] = (uint8_t)lane;
-                if (lane == 0) *res = 0;
-                const int slot = lane / BW;   // which of the load's blocks this lane reads
-                // Loads are unconditional, so that all of them are in flight together (a load inside a
-                // branch is waited for at once): slots past the end of the list read the first listed
-                // block again, which is a block that may be read, and are masked afterwards.
-                uint32_t u[ROUNDS];
-                int pos[ROUNDS];
-                T raw[ROUNDS];
-#pragma unroll
-                for (int t = 0; t < ROUNDS; ++t) {
-                    const int j = t * BPL + slot;
-                    const int pj = (int)plist[j < nkept ? j : 0];
-                    pos[t] = j < nkept ? pj : -1;
-                    raw[t] = row[pj * BW + lane % BW];
-                }
-#pragma unroll
-                for (int t = 0; t < ROUNDS; ++t) {
-                    u[t] = pos[t] >= 0 ? f32_bits<T>(raw[t]) : 0u;
-                    if (COMPACT && pos[t] >= 0) crow[pos[t] * BW + lane % BW] = raw[t];
-                }
-#pragma unroll
-                for (int t = 0; t < ROUNDS; ++t) {
-                    if (t * BPL >= nkept) break;   // wave-uniform
-                    const uint64_t m = ballot64((u[t] & 0x7fffffffu) != 0);
-                    if (lane % BW == 0 && pos[t] >= 0 && ((m >> (slot * BW)) & bwmask) != 0)
-                        __hip_atomic_fetch_or(res, 1ull << pos[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
-                word = *res;
-            } else {
-                uint64_t mine = 0;
-#pragma unroll
-                for (int j0 = 0; j0 < BW; j0 += PER) {
-                    // unconditional loads (see above): lanes whose block is switched off read the first
-                    // switched-on block of the word instead, and are masked afterwards
-                    uint32_t u[PER];
-                    T raw[PER];
-                    const int first_on = __builtin_ctzll(kept[r]) * BW + lane % BW;
-#pragma unroll
-                    for (int j = 0; j < PER; ++j) {
-                        const int blk = (j0 + j) * BPL + lane / BW;   // block (inside this word) of this lane's element
-                        raw[j] = row[(kept[r] >> blk) & 1ull ? (j0 + j) * 64 + lane : first_on];
-                    }
-#pragma unroll
-                    for (int j = 0; j < PER; ++j) {
-                        const int blk = (j0 + j) * BPL + lane / BW;
-                        const bool on = (kept[r] >> blk) & 1ull;
-                        u[j] = on ? f32_bits<T>(raw[j]) : 0u;
-                        if (COMPACT && on) crow[(j0 + j) * 64 + lane] = raw[j];
-                    }
-#pragma unroll
-                    for (int j = 0; j < PER; ++j) {
-                        const uint64_t m = ballot64((u[j] & 0x7fffffffu) != 0);
-                        if (lane / BPL == j0 + j) mine = m;   // lane L collects the load that holds block L
-                    }
-                }
-                word = ballot64(((mine >> ((lane % BPL) * BW)) & bwmask) != 0);
+    __syncthreads();
+    return total;
+}
+
+// bits of x at multiples of LPB, moved together
+template <int LPB> __device__ __forceinline__ uint32_t squeeze(uint64_t x)
+{
+    if (LPB == 2) {
+        x &= 0x5555555555555555ull;
+        x = (x | x >> 1) & 0x3333333333333333ull;
+        x = (x | x >> 2) & 0x0f0f0f0f0f0f0f0full;
+        x = (x | x >> 4) & 0x00ff00ff00ff00ffull;
+        x = (x | x >> 8) & 0x0000ffff0000ffffull;
+        return (uint32_t)(x | x >> 16);
+    }
+    if (LPB == 4) {
+        x &= 0x1111111111111111ull;
+        x = (x | x >> 3) & 0x0303030303030303ull;
+        x = (x | x >> 6) & 0x000f000f000f000full;
+        x = (x | x >> 12) & 0x000000ff000000ffull;
+        return (uint32_t)((x | x >> 24) & 0xffffull);
+    }
+    return (uint32_t)(((x & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
+}
+
+// MAPS: write b_bits and bt_bits.  PACK: write the packed operand (ROWS: of the live rows, and btc_bits).
+template <typename T, int BW, bool MAPS, bool PACK, bool ROWS>
+__device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int lane, int wave, BShared &sh)
+{
+    constexpr int LPB = BW / 4;                 // lanes per block
+    constexpr int BPW = B_COLS / BW;            // blocks per workgroup
+    constexpr int ESZ = (int)sizeof(T);
+    constexpr bool WIDE = ESZ == 4;
+    constexpr uint64_t REP = LPB == 2 ? 0x5555555555555555ull : LPB == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;
+    constexpr uint64_t GREP = 0x1111111111111111ull;
+    const int64_t seg = bb / p.ctiles, ct = bb % p.ctiles;
+    const int64_t col0 = ct * B_COLS, blk0 = ct * BPW;
+    if (ROWS) {
+        const uint32_t live = number_rows(p, seg, lane, wave, sh);
+        if (ct == 0) {   // publish the numbering
+            if (threadIdx.x < SEG && sh.kk[threadIdx.x] >= 0) p.kmap[seg * SEG + threadIdx.x] = (uint32_t)sh.kk[threadIdx.x];
+            if (seg == 0) {
+                if (threadIdx.x == 0) p.kinfo[0] = live;
+                for (int64_t w = threadIdx.x; w < p.WA; w += BUILD_THREADS) p.rows_copy[w] = row_word(p.rows, w, p.K);
             }
         }
-        if (!COMPACT && k >= 0 && lane == 0) p.b_bits[k * p.WB + w] = word;
-        piece_bits |= (uint32_t)((word >> lane) & 1ull) << (wave * B_ROWS_PER_WAVE + r);
+        if (seg * SEG >= (int64_t)live) return;   // no live row left (whole workgroup)
     }
-    pieces[wave * 64 + lane] = piece_bits;
+    // lane j < 8: row j of the wave and which of its blocks are switched on
+    int64_t krow = -1;
+    uint32_t piece = 0;
+    {
+        const int j = lane & (B_ROWS - 1);
+        const int64_t k = ROWS ? (int64_t)sh.kk[wave * B_ROWS + j] : seg * SEG + wave * B_ROWS + j;
+        krow = k >= 0 && k < p.K ? k : -1;
+        const int64_t kc = max(krow, (int64_t)0);
+        uint64_t w = ~0ull;
+        if (p.keep_blocks != nullptr) w = p.keep_blocks[kc * p.WB + (blk0 >> 6)];   // wave-uniform branches
+        if (p.keep_rows != nullptr && !((p.keep_rows[kc >> 6] >> (kc & 63)) & 1ull)) w = 0;
+        piece = krow >= 0 ? (uint32_t)(w >> (blk0 & 63)) : 0u;
+    }
+    u32x4 raw[B_ROWS];
+    const uint32_t nrec = (uint32_t)min((int64_t)B_COLS, p.N - col0) * ESZ;
+#pragma unroll
+    for (int j = 0; j < B_ROWS; ++j) {
+        const int64_t k = max((int64_t)readlane64((uint64_t)krow, j), (int64_t)0);
+        const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)piece, j);
+        const char *row = static_cast<const char *>(p.Y) + (k * p.ldy + col0) * ESZ;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), 0, (int)nrec, 0x00020000);
+        const int off = (pj >> (lane / LPB)) & 1u ? lane * (4 * ESZ) : 0x40000000;
+        if constexpr (WIDE) {
+            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+        } else if (!p.y_unaligned) {
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+            raw[j] = u32x4{v.x, v.y, 0, 0};
+        } else {
+            uint32_t e[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) e[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off + 2 * i, 0, 0);
+            raw[j] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, 0, 0};
+        }
+    }
+    uint32_t gb = 0, bbm = 0;   // rows (bit j) in which this lane's group / block is occupied
+    uint64_t mine = 0;          // lane j: the occupied blocks of row j, at multiples of LPB
+#pragma unroll
+    for (int j = 0; j < B_ROWS; ++j) {
+        const uint32_t nz = WIDE ? (raw[j].x | raw[j].y | raw[j].z | raw[j].w) & 0x7fffffffu : (raw[j].x | raw[j].y) & 0x7fff7fffu;
+        uint64_t m = ballot64(nz != 0);
+        m |= m >> 1;
+        if (LPB >= 4) m |= m >> 2;
+        if (LPB >= 8) m |= m >> 4;
+        m &= REP;
+        const uint64_t blocks = m * ((1u << LPB) - 1u);   // spread over the block's lanes
+        uint64_t groups = blocks;
+        if (LPB == 2) groups = ((m | m >> 2) & GREP) * 15u;
+        gb |= __builtin_amdgcn_inverse_ballot_w64(groups) ? 1u << j : 0u;
+        if (LPB == 2) bbm |= __builtin_amdgcn_inverse_ballot_w64(blocks) ? 1u << j : 0u;
+        mine = __builtin_amdgcn_inverse_ballot_w64(1ull << j) ? m : mine;
+    }
+    sh.gbits[lane][wave] = (uint8_t)gb;
+    if (LPB == 2) sh.bbits[lane][wave] = (uint8_t)bbm;
+    if (MAPS && lane < B_ROWS && krow >= 0) {   // this workgroup's piece of the map row: 4, 2 or 1 bytes
+        const uint32_t v = squeeze<LPB>(mine);
+        char *dst = reinterpret_cast<char *>(p.b_bits + krow * p.WB) + blk0 / 8;
+        if (LPB == 2)
+            *reinterpret_cast<uint32_t *>(dst) = v;
+        else if (LPB == 4)
+            *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v;
+        else
+            *reinterpret_cast<uint8_t *>(dst) = (uint8_t)v;
+        if (ct == p.ctiles - 1)   // pad bits of the row
+            for (int64_t q = (blk0 + BPW) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
+    }
+    constexpr uint32_t ZERO_ENTRY = mmm_list_entry(sizeof(T), MMM_ZERO_COL);
+    if (PACK) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
+    static_assert(B_GROUPS * SEG * 2 == BUILD_THREADS * 4, "one list word per thread");
     __syncthreads();
-    if (wave == 0) {
-        uint32_t v = 0;
-        for (int w = 0; w < BUILD_WAVES; ++w) v |= pieces[w * 64 + lane];
-        const int64_t blk = w * 64 + lane;
-        if (blk < p.NB) (COMPACT ? p.btc_pieces : p.bt_pieces)[blk * (p.WA * (64 / MMM_BT_PIECE)) + piece] = (uint16_t)v;
+    if (wave == 0 && (lane % LPB) == 0) {   // transposed map words of this lane's block
+        const uint64_t *t = reinterpret_cast<const uint64_t *>(LPB == 2 ? sh.bbits[lane] : sh.gbits[lane]);
+        const int64_t blk = blk0 + lane / LPB;
+        if (blk < p.NB) {
+            uint64_t *dst = (ROWS ? p.btc_bits : p.bt_bits) + blk * p.WA + seg * 2;
+            if (MAPS || ROWS) {
+                dst[0] = t[0];
+                if (seg * 2 + 1 < p.WA) dst[1] = t[1];
+            }
+        }
     }
+    if (!PACK) return;
+    const uint64_t *gt = reinterpret_cast<const uint64_t *>(sh.gbits[lane]);
+    const uint64_t glo = gt[0], ghi = gt[1];
+    const uint32_t n = (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi);   // rows of this lane's group
+    const uint64_t below = (1ull << (8 * (wave & 7))) - 1ull;
+    const uint32_t slot0 = wave < 8 ? (uint32_t)__popcll(glo & below) : (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi & below);
+    const int64_t G = ct * B_GROUPS + (lane >> 2);   // this lane's group
+    const bool group_ok = G < p.NG;
+    uint32_t slots[B_ROWS];
+    {
+        uint32_t s = slot0;
+#pragma unroll
+        for (int j = 0; j < B_ROWS; ++j) {
+            slots[j] = s;
+            s += (gb >> j) & 1u;
+        }
+    }
+    if ((lane & 3) == 0) {
+#pragma unroll
+        for (int j = 0; j < B_ROWS; ++j)
+            if ((gb >> j) & 1u)
+                sh.list[lane >> 2][mmm_list_pos(sizeof(T), slots[j])] =
+                    (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & 1u) * SEG + (uint32_t)(wave * B_ROWS + j));
+        if (wave == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
+    }
+    char *val = p.bp_val + (size_t)(G * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);   // this lane's group
+    if constexpr (WIDE) {
+        // slot-major rows of 64 bytes; the slots that fill up the last quad are zero
+        if (group_ok) {
+#pragma unroll
+            for (int j = 0; j < B_ROWS; ++j)
+                if ((gb >> j) & 1u) *reinterpret_cast<u32x4 *>(val + slots[j] * 64 + (lane & 3) * 16) = raw[j];
+            if (wave < 3 && n + wave < ((n + 3u) & ~3u)) *reinterpret_cast<u32x4 *>(val + (n + wave) * 64 + (lane & 3) * 16) = u32x4{0, 0, 0, 0};
+        }
+        __syncthreads();
+    } else {
+        // 16 slots at a time are stored as [slot / 4][column][slot % 4]: the four values of k a lane of the matrix
+        // instruction needs for its column are 8 contiguous bytes.  Composed in LDS, half of the groups at a time;
+        // the slots that fill up the last 16 are zero.
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            if ((lane >> 5) == half) {
+                uint16_t *g = sh.pack + ((lane >> 2) & 7) * (SEG * MMM_GROUP_COLS);
+                auto put = [&](uint32_t slot, uint32_t x, uint32_t y) {
+                    uint16_t *at = g + (slot >> 4) * 256 + ((slot >> 2) & 3) * 64 + (lane & 3) * 16 + (slot & 3);
+                    at[0] = (uint16_t)x;
+                    at[4] = (uint16_t)(x >> 16);
+                    at[8] = (uint16_t)y;
+                    at[12] = (uint16_t)(y >> 16);
+                };
+#pragma unroll
+                for (int j = 0; j < B_ROWS; ++j)
+                    if ((gb >> j) & 1u) put(slots[j], raw[j].x, raw[j].y);
+                if (n + wave < ((n + 15u) & ~15u)) put(n + wave, 0u, 0u);
+            }
+            __syncthreads();
+            // 128 threads per group copy its rounded-up length
+            const int cg = threadIdx.x >> 7;
+            const int64_t CG = ct * B_GROUPS + half * 8 + cg;
+            if (CG < p.NG) {
+                const uint64_t *ct_bits = reinterpret_cast<const uint64_t *>(sh.gbits[(half * 8 + cg) * 4]);
+                const uint32_t cn = ((uint32_t)(__popcll(ct_bits[0]) + __popcll(ct_bits[1])) + 15u) & ~15u;
+                char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
+                for (uint32_t q = threadIdx.x & 127u; q < cn * 2; q += 128)
+                    *reinterpret_cast<uint4 *>(cval + q * 16) = reinterpret_cast<const uint4 *>(sh.pack + cg * (SEG * MMM_GROUP_COLS))[q];
+            }
+            __syncthreads();
+        }
+    }
+    {   // the lists, one word per thread
+        const int64_t LG = ct * B_GROUPS + (threadIdx.x >> 6);
+        if (LG < p.NG)
+            reinterpret_cast<uint32_t *>(p.bp_list + (LG * p.KBA + seg) * SEG)[lane] = reinterpret_cast<const uint32_t *>(sh.list)[threadIdx.x];
+    }
+}
+
+template <typename T, bool MAPS, bool PACK, bool ROWS>
+__device__ __forceinline__ void scan_b_width(const BuildParams &p, uint32_t bb, int lane, int wave, BShared &sh)
+{
+    const int64_t bw = p.N / p.NB;
+    if (bw == 8)
+        scan_b<T, 8, MAPS, PACK, ROWS>(p, bb, lane, wave, sh);
+    else if (bw == 16)
+        scan_b<T, 16, MAPS, PACK, ROWS>(p, bb, lane, wave, sh);
+    else
+        scan_b<T, 32, MAPS, PACK, ROWS>(p, bb, lane, wave, sh);
 }
 
 template <typename T>
-__global__ __launch_bounds__(BUILD_THREADS) void mmm_build_kernel(const BuildParams p)
+__global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void mmm_build_kernel(const BuildParams p)
 {
-    __shared__ uint64_t red[BUILD_WAVES * A_WORDS];
-    __shared__ uint32_t tot[BUILD_WAVES];
-    __shared__ uint32_t pieces[BUILD_WAVES * 64];
-    __shared__ uint8_t gpos[BUILD_WAVES][B_ROWS_PER_WAVE][64];   // B side: positions of the kept blocks of a row word
-    __shared__ uint64_t gword[BUILD_WAVES][B_ROWS_PER_WAVE];     // B side: occupancy word gathered from them
+    __shared__ __align__(16) union { AShared a; BShared b; } sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t b = blockIdx.x;
-    // workgroup ranges: [blocks of A over k | blocks of A over the live k | rows of Y | live rows of Y]
-    if (b < p.n_a + p.n_ac) {
-        const bool lists = b >= p.n_a;   // row-compacted mode: the second range makes the lists
-        const uint32_t ba = lists ? b - p.n_a : b;
-        if (p.n_ac == 0) {
-            if (p.pred == MMM_PRED_NONZERO)
-                scan_a<T, MMM_PRED_NONZERO, A_FULL>(p, ba, lane, wave, red, tot);
-            else if (p.pred == MMM_PRED_GT)
-                scan_a<T, MMM_PRED_GT, A_FULL>(p, ba, lane, wave, red, tot);
-            else
-                scan_a<T, MMM_PRED_ABS_GT, A_FULL>(p, ba, lane, wave, red, tot);
-        } else if (!lists) {
-            if (p.pred == MMM_PRED_NONZERO)
-                scan_a<T, MMM_PRED_NONZERO, A_MAPS>(p, ba, lane, wave, red, tot);
-            else if (p.pred == MMM_PRED_GT)
-                scan_a<T, MMM_PRED_GT, A_MAPS>(p, ba, lane, wave, red, tot);
-            else
-                scan_a<T, MMM_PRED_ABS_GT, A_MAPS>(p, ba, lane, wave, red, tot);
-        } else {
-            if (p.pred == MMM_PRED_NONZERO)
-                scan_a<T, MMM_PRED_NONZERO, A_LISTS>(p, ba, lane, wave, red, tot);
-            else if (p.pred == MMM_PRED_GT)
-                scan_a<T, MMM_PRED_GT, A_LISTS>(p, ba, lane, wave, red, tot);
-            else
-                scan_a<T, MMM_PRED_ABS_GT, A_LISTS>(p, ba, lane, wave, red, tot);
-        }
+    // workgroup ranges: [blocks of A | segments of B | segments of live rows of B]
+    if (b < p.n_a) {
+        if (p.pred == MMM_PRED_NONZERO)
+            scan_a<T, MMM_PRED_NONZERO>(p, b, lane, wave, sh.a);
+        else if (p.pred == MMM_PRED_GT)
+            scan_a<T, MMM_PRED_GT>(p, b, lane, wave, sh.a);
+        else
+            scan_a<T, MMM_PRED_ABS_GT>(p, b, lane, wave, sh.a);
+    } else if (b < p.n_a + p.n_b) {
+        if (p.n_bc == 0)
+            scan_b_width<T, true, true, false>(p, b - p.n_a, lane, wave, sh.b);
+        else
+            scan_b_width<T, true, false, false>(p, b - p.n_a, lane, wave, sh.b);
     } else {
-        const uint32_t bb = b - p.n_a - p.n_ac;
-        const int64_t bw = p.N / p.NB;
-        if (bb < p.n_b) {
-            if (bw == 8)
-                scan_b<T, 8, false>(p, bb, lane, wave, pieces, gpos, gword);
-            else if (bw == 16)
-                scan_b<T, 16, false>(p, bb, lane, wave, pieces, gpos, gword);
-            else
-                scan_b<T, 32, false>(p, bb, lane, wave, pieces, gpos, gword);
-        } else {
-            if (bw == 8)
-                scan_b<T, 8, true>(p, bb - p.n_b, lane, wave, pieces, gpos, gword);
-            else if (bw == 16)
-                scan_b<T, 16, true>(p, bb - p.n_b, lane, wave, pieces, gpos, gword);
-            else
-                scan_b<T, 32, true>(p, bb - p.n_b, lane, wave, pieces, gpos, gword);
-        }
+        scan_b_width<T, false, true, true>(p, b - p.n_a - p.n_b, lane, wave, sh.b);
     }
 }
 
-// Row-compacted mode: number the rows of B that keep_rows leaves on.  One workgroup: every thread
-// counts a contiguous run of map words, a prefix sum over the threads places the runs, and every
-// thread then writes out the positions of its own bits:  kmap[k'] = k.  kinfo[0] = number of live k.
-__global__ __launch_bounds__(1024) void mmm_kmap_kernel(const uint64_t *keep_rows, int64_t K, int64_t WA, uint32_t *kinfo,
-                                                        uint32_t *kmap)
+// ---- forms that only inspection reads, made when they are asked for ---------------------------
+// Column-any words of A over k': bit k' of a row is bit kmap[k'] of the row over k.
+__global__ __launch_bounds__(256) void mmm_colany_compact_kernel(const uint64_t *a_colany, const uint32_t *kinfo, const uint32_t *kmap,
+                                                                 uint64_t *a_colany_c, int64_t MT, int64_t WA)
 {
-    __shared__ uint32_t sums[1024];
-    const int t = threadIdx.x;
-    const int64_t per = (WA + 1023) / 1024;
-    const int64_t w0 = (int64_t)t * per, w1 = min(WA, w0 + per);
-    auto word = [&](int64_t w) -> uint64_t {
-        uint64_t m = keep_rows[w];
-        const int64_t left = K - w * 64;   // bits past K do not count
-        if (left < 64) m &= (1ull << left) - 1ull;
-        return m;
-    };
-    uint32_t cnt = 0;
-    for (int64_t w = w0; w < w1; ++w) cnt += (uint32_t)__popcll(word(w));
-    sums[t] = cnt;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {   // inclusive prefix sum in LDS
-        const uint32_t o = t >= d ? sums[t - d] : 0u;
-        __syncthreads();
-        sums[t] += o;
-        __syncthreads();
+    const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // one wave per word
+    if (idx >= MT * WA) return;
+    const int64_t t = idx / WA, w = idx % WA, kc = w * 64 + (threadIdx.x & 63);
+    bool any = false;
+    if (kc < (int64_t)*kinfo) {
+        const uint32_t k = kmap[kc];
+        any = (a_colany[t * WA + (k >> 6)] >> (k & 63)) & 1ull;
     }
-    uint32_t pos = sums[t] - cnt;
-    for (int64_t w = w0; w < w1; ++w) {
-        uint64_t m = word(w);
-        while (m != 0) {
-            kmap[pos++] = (uint32_t)(w * 64 + __builtin_ctzll(m));
-            m &= m - 1;
+    const uint64_t m = ballot64(any);
+    if ((threadIdx.x & 63) == 0) a_colany_c[idx] = m;
+}
+
+// Counts and lists of the non-zero elements of every block of A, from its image: one workgroup per
+// block, a thread per column.  The order is by column, then by place in the column.
+template <typename T>
+__global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_img, const uint64_t *a_bits, const uint32_t *kinfo,
+                                                                const uint32_t *kmap, uint32_t *a_cnt, uint2 *a_ent, int64_t M,
+                                                                int64_t K, int64_t WA, int64_t KBA)
+{
+    __shared__ uint32_t off[MMM_AB_COLS];
+    const int64_t b = blockIdx.x, bi = b / KBA, bj = b % KBA;
+    const int c = threadIdx.x;
+    const int64_t kc = bj * MMM_AB_COLS + c, klim = kinfo ? (int64_t)*kinfo : K;
+    if (kinfo && bj * MMM_AB_COLS >= klim) return;
+    const int64_t k = kc < klim ? (kinfo ? (int64_t)kmap[kc] : kc) : -1;
+    uint64_t rows = 0;
+    if (k >= 0)
+        for (int r = 0; r < MMM_AB_ROWS; ++r) {
+            const int64_t row = bi * MMM_AB_ROWS + r;
+            if (row < M && ((a_bits[row * WA + (k >> 6)] >> (k & 63)) & 1ull)) rows |= 1ull << r;
         }
+    off[c] = (uint32_t)__popcll(rows);
+    __syncthreads();
+    uint32_t at = 0, total = 0;
+    for (int q = 0; q < MMM_AB_COLS; ++q) {
+        if (q < c) at += off[q];
+        total += off[q];
     }
-    if (t == 1023) kinfo[0] = sums[1023];
+    uint2 *ent = a_ent + (size_t)b * MMM_AB_CAP;
+    const char *col = a_img + ((size_t)bi * KBA * MMM_AB_COLS + kc) * (MMM_AB_ROWS * sizeof(T));
+    for (uint64_t m = rows; m != 0; m &= m - 1) {
+        const int r = __builtin_ctzll(m);
+        const T v = *reinterpret_cast<const T *>(col + mmm_img_row(sizeof(T), (uint32_t)kc, (uint32_t)r));
+        ent[at++] = make_uint2(mmm_slab_pos((uint32_t)r, (uint32_t)c), f32_bits<T>(v));
+    }
+    if (c == 0) a_cnt[b] = total;
+    if (total + c < ((total + 63u) & ~63u)) ent[total + c] = make_uint2(MMM_SLAB_SPARE, 0u);
 }
 
 // ---- statistics (off the hot path) -----------------------------------------------------------
@@ -503,7 +642,6 @@ __global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, 
 // What keep_element compares against.  GT: x > t  <=>  key(x) > key(t) on the order-preserving key
 // (both zeros map to the same key).  ABS_GT: |x| > t; a negative t passes every non-zero x (magnitude
 // bits of x > 0), t = -0 is t = 0.  A NaN threshold passes nothing (nothing exceeds 0xffffffff).
-static_assert(MMM_BT_PIECE == 16, "pieces of the transposed map are stored as 16-bit words");
 
 static uint32_t threshold_key(int32_t pred, float threshold)
 {
@@ -528,14 +666,16 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.keep_a = a.keep_a;
     p.a_bits = m->a_bits;
     p.a_colany = m->a_colany;
-    p.a_cnt = m->a_cnt;
-    p.a_ent = reinterpret_cast<uint2 *>(m->a_ent);
+    p.a_img = m->a_img;
     p.Y = a.Y;
     p.ldy = a.ldy;
     p.keep_rows = a.keep_rows;
     p.keep_blocks = a.keep_blocks;
     p.b_bits = m->b_bits;
-    p.bt_pieces = reinterpret_cast<uint16_t *>(m->bt_bits);
+    p.bt_bits = m->bt_bits;
+    p.bp_val = m->bp_val;
+    p.bp_list = m->bp_list;
+    p.bp_cnt = m->bp_cnt;
     p.M = m->M;
     p.K = m->K;
     p.N = m->N;
@@ -544,28 +684,26 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.WB = m->WB;
     p.MT = m->MT;
     p.KBA = m->KBA;
+    p.NG = m->NG;
     p.pred = a.pred;
     p.thr_bits = threshold_key(a.pred, a.threshold);
+    p.y_unaligned = a.dtype != MMM_F32 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
     p.kinfo = m->kinfo;
     p.kmap = m->kmap;
-    p.a_colany_c = m->a_colany_c;
-    p.btc_pieces = reinterpret_cast<uint16_t *>(m->btc_bits);
-    p.Bc = m->Bc;
+    p.btc_bits = m->btc_bits;
+    p.rows_copy = m->rows_copy;
+    // the numbering the A side follows: that of the B side built in this call, or of the cached one
+    p.rows = a.b_compact ? a.keep_rows : a.a_compact ? m->rows_copy : nullptr;
+    p.ctiles = (uint32_t)((m->N + B_COLS - 1) / B_COLS);
     const int64_t n_a = a.X ? m->MBA * m->KBA : 0;
-    const int64_t n_ac = a.X && a.a_compact ? n_a : 0;
-    const int64_t n_b = a.Y ? (m->WA * (64 / MMM_BT_PIECE)) * m->WB : 0;
+    const int64_t n_b = a.Y ? m->KBA * p.ctiles : 0;
     const int64_t n_bc = a.Y && a.b_compact ? n_b : 0;
-    const int64_t n_all = n_a + n_ac + n_b + n_bc;
+    const int64_t n_all = n_a + n_b + n_bc;
     if (n_all <= 0 || n_all > 0x7fffffffLL) return hipErrorInvalidValue;
     p.n_a = (uint32_t)n_a;
-    p.n_ac = (uint32_t)n_ac;
     p.n_b = (uint32_t)n_b;
+    p.n_bc = (uint32_t)n_bc;
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
-    (void)hipGetLastError();   // drop any stale error another library left on this thread
-    if (a.Y && a.b_compact) {   // number the live rows first: the scans below read the numbering
-        hipLaunchKernelGGL(mmm_kmap_kernel, dim3(1), dim3(1024), 0, s, a.keep_rows, m->K, m->WA, m->kinfo, m->kmap);
-        if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    }
     (void)hipGetLastError();   // drop any stale error another library left on this thread
     if (a.dtype == MMM_BF16)
         hipLaunchKernelGGL(mmm_build_kernel<uint16_t>, grid, block, 0, s, p);
@@ -573,6 +711,72 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
         hipLaunchKernelGGL(mmm_build_kernel<_Float16>, grid, block, 0, s, p);
     else
         hipLaunchKernelGGL(mmm_build_kernel<float>, grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t mmm_launch_colany_compact(const mmm_maps *m, hipStream_t s)
+{
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(mmm_colany_compact_kernel, dim3((uint32_t)((m->MT * m->WA + 3) / 4)), dim3(256), 0, s, m->a_colany, m->kinfo,
+                       m->kmap, m->a_colany_c, m->MT, m->WA);
+    return hipGetLastError();
+}
+
+hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s)
+{
+    (void)hipGetLastError();
+    const dim3 grid((uint32_t)(m->MBA * m->KBA)), block(MMM_AB_COLS);
+    const uint32_t *kinfo = m->a_compact ? m->kinfo : nullptr;
+    uint2 *ent = reinterpret_cast<uint2 *>(m->a_ent);
+    if (m->a_dtype == MMM_BF16)
+        hipLaunchKernelGGL(mmm_lists_kernel<uint16_t>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
+    else if (m->a_dtype == MMM_F16)
+        hipLaunchKernelGGL(mmm_lists_kernel<_Float16>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
+    else
+        hipLaunchKernelGGL(mmm_lists_kernel<float>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
+    return hipGetLastError();
+}
+
+// Per-tile active-k lists (see mmm_debug_k_lists): one wave per (row tile of 64, 16-column group,
+// step of 128 k).
+__global__ __launch_bounds__(64) void mmm_k_lists_kernel(const uint64_t *a_colany, const uint64_t *bt_bits, const uint32_t *kinfo,
+                                                         uint8_t *out, int64_t K, int64_t NB, int64_t WA, int64_t MT, int64_t bw,
+                                                         int64_t groups, int64_t steps)
+{
+    const int lane = threadIdx.x;
+    const int64_t c = blockIdx.x % steps, G = (blockIdx.x / steps) % groups, t = blockIdx.x / (steps * groups);
+    if (kinfo && c * MMM_AB_COLS >= (int64_t)*kinfo) return;
+    uint8_t *rec = out + ((t * groups + G) * steps + c) * 132;
+    uint32_t n = 0;
+    for (int h = 0; h < 2; ++h) {
+        const int64_t w = 2 * c + h;
+        uint64_t m = 0;
+        if (w < WA) {
+            const int64_t b0 = G * MMM_GROUP_COLS / bw, b1 = (G * MMM_GROUP_COLS + MMM_GROUP_COLS - 1) / bw;
+            for (int64_t b = b0; b <= b1 && b < NB; ++b) m |= bt_bits[b * WA + w];
+            uint64_t any = 0;
+            for (int64_t tt = 2 * t; tt < 2 * t + 2 && tt < MT; ++tt) any |= a_colany[tt * WA + w];
+            m &= any;
+        }
+        if ((m >> lane) & 1ull) rec[4 + n + mbcnt64(m)] = (uint8_t)(64 * h + lane);
+        n += (uint32_t)__popcll(m);
+    }
+    if (lane == 0) *reinterpret_cast<uint32_t *>(rec) = n;
+}
+
+hipError_t mmm_launch_dump_lists(const mmm_maps *m, uint8_t *out, size_t out_bytes, size_t *need, hipStream_t s)
+{
+    const int64_t groups = 16 * ((m->N + 255) / 256);
+    const int64_t wgs = m->MBA * groups * m->KBA;
+    const size_t bytes = (size_t)wgs * 132;
+    if (need) *need = bytes;
+    if (out == nullptr || out_bytes < bytes || wgs > 0x7fffffffLL) return hipErrorInvalidValue;
+    if (m->b_compact)
+        if (hipError_t e = mmm_launch_colany_compact(m, s); e != hipSuccess) return e;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(mmm_k_lists_kernel, dim3((uint32_t)wgs), dim3(64), 0, s, m->b_compact ? m->a_colany_c : m->a_colany,
+                       m->b_compact ? m->btc_bits : m->bt_bits, m->b_compact ? m->kinfo : nullptr, out, m->K, m->NB, m->WA, m->MT,
+                       (int64_t)m->bw, groups, m->KBA);
     return hipGetLastError();
 }
 

@@ -9,26 +9,48 @@
 
 // Rows of A summarised by one column-any word.
 constexpr int MMM_COLANY_ROWS = 32;
-// Rows of B (values of k) one workgroup of the B-side map builder covers; the
-// transposed map is written in pieces of this many bits.
-constexpr int MMM_BT_PIECE = 16;
-// Geometry of the blocks of A whose non-zero elements are listed (count, offsets, values).
+// Geometry of the blocks of A: 64 rows x 128 columns, what one step of the matrix kernel keeps in LDS.
 constexpr int MMM_AB_ROWS = 64;
 constexpr int MMM_AB_COLS = 128;
 constexpr int MMM_AB_CAP = MMM_AB_ROWS * MMM_AB_COLS;   // list capacity per block: the worst case
-// The LDS slab a block is scattered into is column-major: a column takes MMM_SLAB_COL_BYTES, its
-// first 256 bytes hold the 64 rows with the rows r, r+16, r+32, r+48 next to each other, so one
-// 16-byte read yields the A operands of all four 16-row MFMA tiles for one k and the 16 lanes of an
-// operand read 256 contiguous bytes.  The 16 spare bytes per column shift neighbouring columns by
-// four LDS banks, which spreads the entries of one row of a block (neighbours in its list) over
-// the banks.  Column MMM_AB_COLS is spare and always zero.
+// Lists of the non-zero elements of a block (inspection only, mmm_maps_view_lists): positions as byte
+// offsets in a column-major block with 272-byte columns.
 constexpr uint32_t MMM_SLAB_COL_BYTES = 272;
-constexpr int MMM_SLAB_FLOATS = (MMM_AB_COLS + 1) * (int)(MMM_SLAB_COL_BYTES / 4);
 __host__ __device__ constexpr uint32_t mmm_slab_pos(uint32_t row, uint32_t col)   // byte offset of element (row, col)
 {
     return col * MMM_SLAB_COL_BYTES + (row & 15u) * 16u + (row >> 4) * 4u;
 }
 constexpr uint32_t MMM_SLAB_SPARE = mmm_slab_pos(0, MMM_AB_COLS);
+
+// What the builder hands to the matrix kernel.
+//
+// Image of A: [row block of 64][k, padded to whole blocks][64 rows], element type of X, zeros where the
+// mask drops an element.  4-byte elements: the rows r, r+16, r+32, r+48 of a column are neighbours, so that
+// one 16-byte LDS read yields the operands of all four 16-row tiles for one k, and the 16 lanes of an
+// operand read 256 contiguous bytes.  16-bit elements: natural order, as the transposing LDS read needs;
+// the column's 16-byte units are rotated with k (xor), so that the columns k .. k+7 of one row tile lie in
+// different LDS banks.
+__host__ __device__ constexpr uint32_t mmm_img_swizzle(uint32_t col) { return ((col >> 1) & 3u) << 1; }
+__host__ __device__ constexpr uint32_t mmm_img_row(size_t esz, uint32_t col, uint32_t row)   // byte offset inside a column
+{
+    return esz == 4 ? (row & 15u) * 16u + (row >> 4) * 4u : (((row >> 3) ^ mmm_img_swizzle(col)) << 4) + (row & 7u) * 2u;
+}
+// Packed B: per group of 16 columns and segment of 128 k the occupied rows, one after another ("slots"),
+// at [group][segment][128 slots][16 columns]; the number of slots; and per slot where its column of A
+// sits in the kernel's LDS ring of two blocks: column 128 * (segment & 1) + k, in units of the column
+// size (4-byte elements) or of 16 bytes with the rotation folded in (16-bit elements).  Slots past the
+// last name the ring's zero column.  The order of the list is the one in which a lane reads it: 4-byte
+// elements take slots 4u + s (u = 0..3) of every 16, 16-bit elements slot lane / 4.
+constexpr int MMM_GROUP_COLS = 16;
+constexpr uint32_t MMM_ZERO_COL = 2 * MMM_AB_COLS;
+__host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
+{
+    return esz == 4 ? col : (col << 3) | (col == MMM_ZERO_COL ? 0u : mmm_img_swizzle(col));
+}
+__host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
+{
+    return esz == 4 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : slot;
+}
 struct mmm_maps {
     int64_t M, K, N;
     int32_t bw;
@@ -37,12 +59,14 @@ struct mmm_maps {
     int64_t WB;        // ceil(NB/64): words per row of b_bits
     int64_t MT;        // ceil(M/32): rows of a_colany
     int64_t MBA, KBA;  // blocks of A: ceil(M/64) x ceil(K/128)
+    int64_t NG;        // groups of 16 columns: ceil(N/16)
     // device pointers into the caller's workspace
     uint64_t *a_bits;
     uint64_t *a_colany;
-    uint32_t *a_cnt;   // [MBA][KBA] non-zeros per block
-    uint64_t *a_ent;   // [MBA*KBA][MMM_AB_CAP] entries {byte offset mmm_slab_pos(row, column) in the slab, value bits},
-                       // padded to a multiple of 64 with {spare cell, 0}
+    char *a_img;       // image of A (see above)
+    uint32_t *a_cnt;   // [MBA][KBA] non-zeros per block            (inspection: written by mmm_launch_lists)
+    uint64_t *a_ent;   // [MBA*KBA][MMM_AB_CAP] entries {mmm_slab_pos(row, column), value bits}, padded to a
+                       // multiple of 64 with {spare cell, 0}       (inspection)
     uint64_t *b_bits;
     uint64_t *bt_bits;
     uint64_t *stats;   // 4 words
@@ -50,9 +74,13 @@ struct mmm_maps {
     // matrix kernel walks k' instead of k.
     uint32_t *kinfo;       // [0] = number of live k (device)
     uint32_t *kmap;        // [K]: k' -> k
-    uint64_t *a_colany_c;  // [MT][WA]: column-any words of A over k'
+    uint64_t *rows_copy;   // [WA]: the keep_rows bitmap the B side was built with
+    uint64_t *a_colany_c;  // [MT][WA]: column-any words of A over k'   (inspection)
     uint64_t *btc_bits;    // [NB][WA]: the B map transposed, over k'
-    void *Bc;              // [K][N] elements: the kept blocks of live row k' of Y at row k'
+    // packed B (see above; over k' in row-compacted mode)
+    char *bp_val;
+    uint16_t *bp_list;
+    uint32_t *bp_cnt;
     float *partials;   // split-K partial sums
     size_t partial_bytes;
     void *ws;
@@ -60,8 +88,9 @@ struct mmm_maps {
     // state
     bool a_built, b_built;
     bool b_compact;   // the B side was built in row-compacted mode
-    bool a_compact;   // the lists of A were built over k' (for the numbering of the current B side)
+    bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
+    hipStream_t build_stream;   // of the last build: the inspection calls that derive something launch there
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)
     int64_t a_src_ld;
     // launch plan fixed for this handle (-1 / 0: none, follow the process-wide options)
@@ -84,8 +113,8 @@ struct mmm_build_args {
     const uint64_t *keep_rows;
     const uint64_t *keep_blocks;
     int32_t dtype;
-    bool a_compact;   // list the blocks of A over the live k (the numbering exists or is made in this call)
-    bool b_compact;   // number the live rows (keep_rows given) and write the compacted B side too
+    bool a_compact;   // lay A out over the live k (the numbering exists or is made in this call)
+    bool b_compact;   // number the live rows (keep_rows given) and pack those
 };
 
 struct mmm_plan {
@@ -99,7 +128,7 @@ struct mmm_plan {
 
 struct mmm_variant_info {
     const char *name;
-    int32_t TM, TN, KC, threads, groups, rows;   // rows: rows of C actually computed (64, or 32 for short matrices)
+    int32_t TM, TN, KC, rows;   // rows: rows of C actually computed (64, or 32 for short matrices)
 };
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
@@ -107,11 +136,13 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
 hipError_t mmm_launch_build64(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
 uint64_t mmm_threshold_key64(int32_t pred, float threshold);
 hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s);
+// forms that only inspection reads: column-any words over k'; counts and lists of the blocks of A
+hipError_t mmm_launch_colany_compact(const mmm_maps *m, hipStream_t s);
+hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s);
 int32_t mmm_variant_count();
 const mmm_variant_info &mmm_variant(int32_t i);
 // partials / partial_bytes: where the split-K partial sums go (used only when p.split_k > 1)
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, const void *X, int64_t ldx,
-                             const void *Y, int64_t ldy, float *C, int64_t ldc, int32_t accumulate, float *partials,
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, float *C, int64_t ldc, int32_t accumulate, float *partials,
                              size_t partial_bytes, hipStream_t s);
 // The multiplication over exactly the surviving products, on the vector ALUs.  fused: evaluate M
 // (pred, threshold, keep_a) on X inside the kernel; otherwise a_bits of the maps are used.
@@ -120,7 +151,7 @@ hipError_t mmm_launch_pairs(const mmm_maps *m, int32_t dtype, const void *X, int
                             const uint64_t *keep_a, hipStream_t s);
 // whether that kernel can address a Y of this leading dimension (it forms 32-bit offsets inside 4096 rows)
 bool mmm_pairs_supports(int32_t dtype, int64_t ldy);
-// the k lists the matrix kernel's default tile shape walks, written out (need: bytes required)
+// the active-k lists of every row tile and column group, written out (need: bytes required)
 hipError_t mmm_launch_dump_lists(const mmm_maps *m, uint8_t *out, size_t out_bytes, size_t *need, hipStream_t s);
 // device address of the library's own scratch array on the current device (MMM_STATIC_SCRATCH_BYTES bytes)
 hipError_t mmm_static_scratch(float **ptr);
