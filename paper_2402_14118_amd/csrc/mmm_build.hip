@@ -16,6 +16,7 @@
 // One launch covers both matrices.  Every output word in device memory has exactly one producer, so no
 // global atomics are used and nothing needs clearing beforehand.
 #include "mmm_internal.h"
+#include <cstring>
 
 namespace {
 
@@ -28,6 +29,17 @@ constexpr int B_GROUPS = B_COLS / MMM_GROUP_COLS;     // 16
 constexpr int A_ROWS = MMM_AB_ROWS / BUILD_WAVES;     // 4 rows of A per wave
 constexpr int A_WORDS = MMM_AB_COLS / 64;             // 2
 
+// Element predicate of M, decided on the bit pattern so that no denormal mode of the float pipeline can
+// change a map bit.  Every predicate, the non-zero test included, is membership of the pattern (or of the
+// pattern without its sign) in one or two ranges that the host works out (see element_test): two or three
+// integer instructions per element, where comparing order-preserving keys took about ten and made the scan
+// of X bound by the vector ALUs (2048 x 16384 ReLU: 276 of them per wave and block, 38 us).
+enum { TEST_MAGNITUDE = 0, TEST_ONE_RANGE = 1, TEST_TWO_RANGES = 2 };
+struct ElementTest {
+    int32_t mode;
+    uint32_t lo1, len1, lo2, len2;   // lo <= pattern < lo + len
+};
+
 struct BuildParams {
     const void *X;
     int64_t ldx;
@@ -37,20 +49,18 @@ struct BuildParams {
     char *a_img;
     const void *Y;
     int64_t ldy;
-    const uint64_t *keep_rows;
     const uint64_t *keep_blocks;
     uint64_t *b_bits;
     uint64_t *bt_bits;
     char *bp_val;         // packed B: [group][segment][128 slots][16 columns]
     uint16_t *bp_list;    // [group][segment][128]
     uint32_t *bp_cnt;     // [group][segment]
-    int64_t M, K, N, NB, WA, WB, MT, KBA, NG;
-    uint32_t thr_bits;
-    int32_t pred;
+    int64_t M, K, N, NB, WA, WB, MT, MBA, KBA, NG;
+    ElementTest test;
     int32_t y_unaligned;  // 16-bit Y whose rows do not start on 4-byte boundaries
-    uint32_t n_a;         // workgroups that scan X, one per block
-    uint32_t n_b;         // workgroups that scan Y (row-compacted mode: bitmaps only)
-    uint32_t n_bc;        // row-compacted mode: workgroups that pack the live rows of Y
+    uint32_t n_b;               // segments x column tiles of B
+    uint32_t n_a_wg, n_b_wg;    // workgroups for them
+    uint32_t a_per_wg;          // blocks of A per workgroup
     uint32_t ctiles;      // column tiles of 256 per segment
     // row-compacted mode (whole rows of B switched off): k' = 0 .. K' - 1 numbers the rows `rows` leaves on
     const uint64_t *rows;    // keep_rows, or the copy of it a cached B side was built with; else null
@@ -64,26 +74,6 @@ template <typename T> __device__ __forceinline__ uint32_t f32_bits(T v);
 template <> __device__ __forceinline__ uint32_t f32_bits<float>(float v) { return __float_as_uint(v); }
 template <> __device__ __forceinline__ uint32_t f32_bits<uint16_t>(uint16_t v) { return (uint32_t)v << 16; }   // bf16
 template <> __device__ __forceinline__ uint32_t f32_bits<_Float16>(_Float16 v) { return __float_as_uint((float)v); }
-
-// Order-preserving key of a non-NaN float with both zeros mapped to +0.
-__device__ __forceinline__ uint32_t order_key(uint32_t u)
-{
-    if ((u & 0x7fffffffu) == 0) u = 0;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-// Element predicate of M, decided on the bit pattern so that no denormal mode
-// of the float pipeline can change a map bit.  Includes the non-zero test.
-// `thr` is prepared by the host (see threshold_key): for GT the order key of the
-// threshold, for ABS_GT its magnitude bits; NaN never passes GT / ABS_GT.
-template <int PRED> __device__ __forceinline__ bool keep_element(uint32_t u, uint32_t thr)
-{
-    const uint32_t a = u & 0x7fffffffu;
-    if (PRED == MMM_PRED_NONZERO) return a != 0;
-    const bool ok = a != 0 && a <= 0x7f800000u;
-    if (PRED == MMM_PRED_GT) return ok && order_key(u) > thr;
-    return ok && a > thr;
-}
 
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 
@@ -107,154 +97,215 @@ __device__ __forceinline__ uint64_t interleave(uint32_t e, uint32_t o)
     return (a & 0x5555555555555555ull) | (b & 0xaaaaaaaaaaaaaaaaull);
 }
 
+// the first `left` (at least 1) bits of a word
+__device__ __forceinline__ uint64_t bits_below(uint64_t m, int64_t left) { return left >= 64 ? m : m & ((1ull << left) - 1ull); }
 // word w of a bitmap row of K bits with the bits past K cleared
-__device__ __forceinline__ uint64_t row_word(const uint64_t *row, int64_t w, int64_t K)
-{
-    const uint64_t m = row[w];
-    const int64_t left = K - w * 64;
-    return left >= 64 ? m : m & ((1ull << left) - 1ull);
-}
+__device__ __forceinline__ uint64_t row_word(const uint64_t *row, int64_t w, int64_t K) { return bits_below(row[w], K - w * 64); }
 
-// ---- A side: one workgroup = one block of 64 rows x 128 columns ------------------------------
+// ---- A side: one workgroup = a few blocks of 64 rows x 128 columns, one below the other ---------
 // A wave takes the four rows that are neighbours in an LDS column: w, w+16, w+32, w+48 for 4-byte
 // elements (one 16-byte read of the matrix kernel yields one element for each of its four 16-row
 // tiles), 4w .. 4w+3 for 16-bit ones (natural order: the transposing LDS read wants contiguous rows).
 // The block is turned around in LDS (16-byte or 8-byte pieces whose position is rotated with k, so that
-// the 64 lanes of a write do not fall on the same banks) and leaves as whole cache lines.
-// Measured on 4096^2 fp32: see the note at mmm_launch_build.
+// the 64 lanes of a write do not fall on the same banks) and leaves as whole cache lines.  The loads of
+// the next block are issued before the barrier of the current one and two stages alternate, so that the
+// memory system always has work of a workgroup although only two of this size fit on a compute unit.
 struct AShared {
-    char stage[MMM_AB_COLS * MMM_AB_ROWS * 4];
-    uint64_t any[BUILD_WAVES][2][A_WORDS];   // [wave][32-row half of the block][word]
-    uint8_t live[MMM_AB_COLS];               // row-compacted mode: live columns of the block
-    uint32_t base, nlive;                    // k' of the first of them, and how many
+    char stage[2][MMM_AB_COLS * MMM_AB_ROWS * 4];
+    uint64_t any[2][BUILD_WAVES][2][A_WORDS];   // [stage][wave][32-row half of the block][word]
+    uint8_t live[MMM_AB_COLS];                  // row-compacted mode: live columns of the blocks
+    uint32_t before[BUILD_WAVES];               // row-compacted mode: live rows before them, by wave
 };
 
-template <typename T, int PRED>
-__device__ __forceinline__ void scan_a(const BuildParams &p, uint32_t b, int lane, int wave, AShared &sh)
+template <typename T> struct ABlock {   // one block in a wave's registers
+    uint32_t x[A_ROWS][sizeof(T) == 4 ? A_WORDS : 1];   // 4-byte: lane <-> k; 16-bit: two neighbouring k per lane
+    uint32_t kb[A_ROWS];                                // 16-bit: the byte that holds the lane's keep bits
+    uint64_t kw;                                        // 4-byte: keep word of (row, half), in lane 2t + h
+};
+
+template <typename T, int TEST, bool ROWS>
+__device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
 {
     constexpr bool WIDE = sizeof(T) == 4;
-    const int64_t bi = b / p.KBA, bj = b % p.KBA;
-    const int64_t k_lo = bj * MMM_AB_COLS, w_lo = k_lo / 64;
-    const int64_t row0 = bi * MMM_AB_ROWS;
-    auto row_of = [&](int t) -> int64_t { return row0 + (WIDE ? wave + 16 * t : wave * 4 + t); };
+    constexpr int UNITS = MMM_AB_ROWS * (int)sizeof(T) / 16;   // 16-byte units per column
     const bool has_keep = p.keep_a != nullptr;
-    const bool compact = p.rows != nullptr;
+    constexpr bool compact = ROWS;
+    auto row_of = [&](int64_t bi, int t) -> int64_t { return bi * MMM_AB_ROWS + (WIDE ? wave + 16 * t : wave * 4 + t); };
+
     // Every load below is unconditional (indices are clamped, results masked afterwards): a load inside a
     // branch is waited for before the next one is issued.
-    uint64_t kw = ~0ull;   // keep words of the wave's (row, half) pairs, one per lane 2t + h
-    if (has_keep) kw = p.keep_a[min(row_of((lane >> 1) & 3), p.M - 1) * p.WA + min(w_lo + (lane & 1), p.WA - 1)];
-    uint64_t word[A_ROWS][A_WORDS];   // bitmap words (wave-uniform)
-    if constexpr (WIDE) {
-        uint32_t u[A_ROWS][A_WORDS];
+    // Addresses are a wave-uniform row base plus one 32-bit lane offset that all rows share.
+    const int64_t k_lo = bj * MMM_AB_COLS, w_lo = bj * A_WORDS;
+    const int tail = (int)min(p.K - k_lo, (int64_t)MMM_AB_COLS);   // columns of these blocks that exist
+    auto load = [&](int64_t bi, ABlock<T> &r) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            r.kw = ~0ull;
+            if (has_keep) r.kw = p.keep_a[min(row_of(bi, (lane >> 1) & 3), p.M - 1) * p.WA + min(w_lo + (lane & 1), p.WA - 1)];
+            const uint32_t off0 = (uint32_t)min(lane, tail - 1) * 4u, off1 = (uint32_t)min(lane + 64, tail - 1) * 4u;
 #pragma unroll
-        for (int t = 0; t < A_ROWS; ++t)
+            for (int t = 0; t < A_ROWS; ++t) {
+                const char *xr = reinterpret_cast<const char *>(static_cast<const T *>(p.X) + min(row_of(bi, t), p.M - 1) * p.ldx + k_lo);
+                r.x[t][0] = *reinterpret_cast<const uint32_t *>(xr + off0);
+                r.x[t][1] = *reinterpret_cast<const uint32_t *>(xr + off1);
+            }
+        } else {
+            // two neighbouring k per lane and load, at any 2-byte alignment; the last column of an odd K is read
+            // together with the one before it, so that nothing past the row is touched
+            typedef uint32_t u32_any __attribute__((aligned(2), may_alias));
+            typedef uint16_t u16_any __attribute__((may_alias));
+            const uint32_t off = (uint32_t)min(2 * lane + 2, tail) * 2u;   // from two elements before the block
+            const uint32_t koff = (uint32_t)min(2 * lane, tail - 1) >> 3;
 #pragma unroll
-            for (int h = 0; h < A_WORDS; ++h)
-                u[t][h] = f32_bits<T>(static_cast<const T *>(p.X)[min(row_of(t), p.M - 1) * p.ldx + min(k_lo + 64 * h + lane, p.K - 1)]);
+            for (int t = 0; t < A_ROWS; ++t) {
+                const int64_t row = min(row_of(bi, t), p.M - 1);
+                const char *xr = reinterpret_cast<const char *>(static_cast<const T *>(p.X) + row * p.ldx + k_lo);
+                r.x[t][0] = p.K > 1 ? *reinterpret_cast<const u32_any *>(xr - 4 + off) : (uint32_t)*reinterpret_cast<const u16_any *>(xr);
+                r.kb[t] = 0xffu;
+                if (has_keep) r.kb[t] = (reinterpret_cast<const uint8_t *>(p.keep_a + row * p.WA + w_lo))[koff];
+            }
+        }
+    };
+
+    ABlock<T> cur;
+    load(bi0, cur);
+    uint32_t base = (uint32_t)k_lo;   // image column of the blocks' first
+    int cols = MMM_AB_COLS;           // and how many there are
+    if (compact) {   // the blocks' live columns, and how many live rows come before them
+        uint32_t n = 0;
+        for (int64_t w = threadIdx.x; w < w_lo; w += BUILD_THREADS) n += (uint32_t)__popcll(p.rows[w]);
+        const uint64_t m0 = row_word(p.rows, w_lo, p.K), m1 = w_lo + 1 < p.WA ? row_word(p.rows, w_lo + 1, p.K) : 0ull;
 #pragma unroll
-        for (int t = 0; t < A_ROWS; ++t)
+        for (int d = 32; d > 0; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d, 64);
+        if (lane == 0) sh.before[wave] = n;
+        const uint32_t n0 = (uint32_t)__popcll(m0);
+        cols = (int)(n0 + (uint32_t)__popcll(m1));
+        if (wave == 0) {
+            if ((m0 >> lane) & 1ull) sh.live[mbcnt64(m0)] = (uint8_t)lane;
+            if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
+        }
+    }
+    for (int64_t bi = bi0; bi < bi1; ++bi) {
+        const int st = (int)(bi - bi0) & 1;
+        char *const stage = sh.stage[st];
+        uint64_t word[A_ROWS][A_WORDS];   // bitmap words (wave-uniform)
+        // elements past the edge of X become +0, which is never kept
+        const bool edge = tail < MMM_AB_COLS || (bi + 1) * MMM_AB_ROWS > p.M;   // wave-uniform
+        if constexpr (WIDE) {
+            if (edge) {
+#pragma unroll
+                for (int t = 0; t < A_ROWS; ++t)
+#pragma unroll
+                    for (int h = 0; h < A_WORDS; ++h)
+                        if (row_of(bi, t) >= p.M || 64 * h + lane >= tail) cur.x[t][h] = 0;
+            }
+            uint32_t u[A_ROWS][A_WORDS];
+#pragma unroll
+            for (int t = 0; t < A_ROWS; ++t)
+#pragma unroll
+                for (int h = 0; h < A_WORDS; ++h) {
+                    const uint32_t x = cur.x[t][h], v = TEST == TEST_MAGNITUDE ? x & 0x7fffffffu : x;
+                    uint64_t m = ballot64(v - p.test.lo1 < p.test.len1);
+                    if (TEST == TEST_TWO_RANGES) m |= ballot64(v - p.test.lo2 < p.test.len2);
+                    if (has_keep) m &= readlane64(cur.kw, 2 * t + h);   // wave-uniform branch
+                    word[t][h] = m;
+                    u[t][h] = __builtin_amdgcn_inverse_ballot_w64(m) ? x : 0u;   // the word is the lane mask of what stays
+                }
 #pragma unroll
             for (int h = 0; h < A_WORDS; ++h) {
-                const bool inside = row_of(t) < p.M && k_lo + 64 * h + lane < p.K;
-                const uint64_t m = ballot64(inside && keep_element<PRED>(u[t][h], p.thr_bits)) & readlane64(kw, 2 * t + h);
-                word[t][h] = m;
-                u[t][h] = __builtin_amdgcn_inverse_ballot_w64(m) ? u[t][h] : 0u;   // the word is the lane mask of what stays
+                const int k = 64 * h + lane;
+                *reinterpret_cast<uint4 *>(stage + k * 256 + ((wave ^ (k & 15)) << 4)) = make_uint4(u[0][h], u[1][h], u[2][h], u[3][h]);
             }
+        } else {
+            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+            if (edge) {
 #pragma unroll
-        for (int h = 0; h < A_WORDS; ++h) {
-            const int k = 64 * h + lane;
-            *reinterpret_cast<uint4 *>(sh.stage + k * 256 + ((wave ^ (k & 15)) << 4)) = make_uint4(u[0][h], u[1][h], u[2][h], u[3][h]);
+                for (int t = 0; t < A_ROWS; ++t) {
+                    if (2 * lane == tail - 1 && p.K > 1) cur.x[t][0] >>= 16;
+                    if (row_of(bi, t) >= p.M || 2 * lane >= tail) cur.x[t][0] = 0;
+                    if (2 * lane + 1 >= tail) cur.x[t][0] &= 0xffffu;
+                }
+            }
+            uint32_t d[A_ROWS];
+#pragma unroll
+            for (int t = 0; t < A_ROWS; ++t) {
+                d[t] = cur.x[t][0];
+                if (has_keep) {   // wave-uniform branch; dropped elements become +0, which fails every test
+                    const uint32_t kbit = cur.kb[t] >> ((2 * lane) & 7);
+                    d[t] &= (uint32_t)((int)(kbit << 31) >> 31) & 0xffffu | (uint32_t)((int)(kbit << 30) >> 31) & 0xffff0000u;
+                }
+                const uint32_t v = TEST == TEST_MAGNITUDE ? d[t] & 0x7fff7fffu : d[t];
+                const u16x2 lo1 = {(uint16_t)p.test.lo1, (uint16_t)p.test.lo1}, lo2 = {(uint16_t)p.test.lo2, (uint16_t)p.test.lo2};
+                const u16x2 y = __builtin_bit_cast(u16x2, v) - lo1;
+                uint64_t me = ballot64(y.x < (uint16_t)p.test.len1), mo = ballot64(y.y < (uint16_t)p.test.len1);
+                if (TEST == TEST_TWO_RANGES) {
+                    const u16x2 z = __builtin_bit_cast(u16x2, v) - lo2;
+                    me |= ballot64(z.x < (uint16_t)p.test.len2);
+                    mo |= ballot64(z.y < (uint16_t)p.test.len2);
+                }
+                word[t][0] = interleave((uint32_t)me, (uint32_t)mo);
+                word[t][1] = interleave((uint32_t)(me >> 32), (uint32_t)(mo >> 32));
+                d[t] &= (__builtin_amdgcn_inverse_ballot_w64(me) ? 0xffffu : 0u) | (__builtin_amdgcn_inverse_ballot_w64(mo) ? 0xffff0000u : 0u);
+            }
+            // rows 4w .. 4w+3 of columns 2 lane and 2 lane + 1
+            char *at = stage + (2 * lane) * 128 + ((wave ^ ((lane & 7) << 1)) << 3);
+            *reinterpret_cast<uint2 *>(at) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u));
+            *reinterpret_cast<uint2 *>(at + 128) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u));
         }
-    } else {
-        // two neighbouring k per lane and load, at any 2-byte alignment; the last column of an odd K is read
-        // together with the one before it, so that nothing past the row is touched
-        typedef uint32_t u32_any __attribute__((aligned(2)));
-        uint32_t d[A_ROWS], kb[A_ROWS];
-        const int64_t k = k_lo + 2 * lane;
+        // bitmap words: lane 2t + h stores the word of (row t, half h)
+        uint64_t mine = 0;
 #pragma unroll
-        for (int t = 0; t < A_ROWS; ++t) {
-            const int64_t r = min(row_of(t), p.M - 1);
-            const T *xr = static_cast<const T *>(p.X) + r * p.ldx;
-            d[t] = p.K > 1 ? *reinterpret_cast<const u32_any *>(xr + min(k, p.K - 2)) : (uint32_t)*reinterpret_cast<const uint16_t *>(xr);
-            kb[t] = 0xffu;
-            if (has_keep) kb[t] = reinterpret_cast<const uint8_t *>(p.keep_a + r * p.WA)[min(k, p.K - 1) >> 3];
+        for (int t = 0; t < A_ROWS; ++t)
+#pragma unroll
+            for (int h = 0; h < A_WORDS; ++h) mine = __builtin_amdgcn_inverse_ballot_w64(1ull << (2 * t + h)) ? word[t][h] : mine;
+        if (lane < 4) {   // column-any words of this wave's rows, by 32-row half of the block
+            const int t32 = lane >> 1, h = lane & 1;
+            uint64_t any;
+            if (WIDE)
+                any = t32 ? (h ? word[2][1] | word[3][1] : word[2][0] | word[3][0]) : (h ? word[0][1] | word[1][1] : word[0][0] | word[1][0]);
+            else
+                any = t32 != wave / (BUILD_WAVES / 2) ? 0ull
+                    : h ? word[0][1] | word[1][1] | word[2][1] | word[3][1] : word[0][0] | word[1][0] | word[2][0] | word[3][0];
+            sh.any[st][wave][t32][h] = any;
         }
+        if (bi + 1 < bi1) load(bi + 1, cur);
+        if (lane < 2 * A_ROWS && row_of(bi, lane >> 1) < p.M && w_lo + (lane & 1) < p.WA)
+            p.a_bits[row_of(bi, lane >> 1) * p.WA + w_lo + (lane & 1)] = mine;
+        __syncthreads();
+        if (wave == 0) {   // lane (t32, h, wave): OR over the sixteen waves
+            const int t32 = lane >> 5, h = (lane >> 4) & 1;
+            const uint64_t any = sh.any[st][lane & 15][t32][h];
+            uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
 #pragma unroll
-        for (int t = 0; t < A_ROWS; ++t) {
-            if (k == p.K - 1 && p.K > 1) d[t] >>= 16;
-            const bool in0 = row_of(t) < p.M && k < p.K, in1 = row_of(t) < p.M && k + 1 < p.K;
-            const uint32_t kbit = kb[t] >> (k & 7);
-            const bool e = in0 && (kbit & 1u) && keep_element<PRED>(f32_bits<T>(__builtin_bit_cast(T, (uint16_t)d[t])), p.thr_bits);
-            const bool o = in1 && (kbit & 2u) && keep_element<PRED>(f32_bits<T>(__builtin_bit_cast(T, (uint16_t)(d[t] >> 16))), p.thr_bits);
-            const uint64_t me = ballot64(e), mo = ballot64(o);
-            word[t][0] = interleave((uint32_t)me, (uint32_t)mo);
-            word[t][1] = interleave((uint32_t)(me >> 32), (uint32_t)(mo >> 32));
-            d[t] = (e ? d[t] & 0xffffu : 0u) | (o ? d[t] & 0xffff0000u : 0u);
+            for (int d = 1; d < 16; d <<= 1) {
+                lo |= (uint32_t)__shfl_xor((int)lo, d, 64);
+                hi |= (uint32_t)__shfl_xor((int)hi, d, 64);
+            }
+            const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
+            if ((lane & 15) == 0 && tile < p.MT && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
         }
-        // rows 4w .. 4w+3 of columns 2 lane and 2 lane + 1
-        char *at = sh.stage + (2 * lane) * 128 + ((wave ^ ((lane & 7) << 1)) << 3);
-        *reinterpret_cast<uint2 *>(at) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u));
-        *reinterpret_cast<uint2 *>(at + 128) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u));
-    }
-    // bitmap words: lane 2t + h stores the word of (row t, half h)
-    uint64_t mine = 0;
-#pragma unroll
-    for (int t = 0; t < A_ROWS; ++t)
-#pragma unroll
-        for (int h = 0; h < A_WORDS; ++h) mine = __builtin_amdgcn_inverse_ballot_w64(1ull << (2 * t + h)) ? word[t][h] : mine;
-    if (lane < 2 * A_ROWS && row_of(lane >> 1) < p.M && w_lo + (lane & 1) < p.WA)
-        p.a_bits[row_of(lane >> 1) * p.WA + w_lo + (lane & 1)] = mine;
-    if (lane < 4) {   // column-any words of this wave's rows, by 32-row half of the block
-        const int t32 = lane >> 1, h = lane & 1;
-        uint64_t any;
-        if (WIDE)
-            any = t32 ? (h ? word[2][1] | word[3][1] : word[2][0] | word[3][0]) : (h ? word[0][1] | word[1][1] : word[0][0] | word[1][0]);
-        else
-            any = t32 != wave / (BUILD_WAVES / 2) ? 0ull
-                : h ? word[0][1] | word[1][1] | word[2][1] | word[3][1] : word[0][0] | word[1][0] | word[2][0] | word[3][0];
-        sh.any[wave][t32][h] = any;
-    }
-    if (compact && wave == BUILD_WAVES - 1) {   // which columns of the block are live, and the k' of the first
-        uint32_t before = 0;
-        for (int64_t w = lane; w < w_lo; w += 64) before += (uint32_t)__popcll(p.rows[w]);
-#pragma unroll
-        for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d, 64);
-        const uint64_t m0 = row_word(p.rows, w_lo, p.K), m1 = w_lo + 1 < p.WA ? row_word(p.rows, w_lo + 1, p.K) : 0ull;
-        if ((m0 >> lane) & 1ull) sh.live[mbcnt64(m0)] = (uint8_t)lane;
-        const uint32_t n0 = (uint32_t)__popcll(m0);
-        if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
-        if (lane == 0) {
-            sh.base = before;
-            sh.nlive = n0 + (uint32_t)__popcll(m1);
+        // the image: column k (or k') of block row bi is one run of 64 elements
+        if (compact && bi == bi0) {
+            base = 0;
+            for (int w = 0; w < BUILD_WAVES; ++w) base += sh.before[w];
         }
-    }
-    __syncthreads();
-    if (wave == 0) {   // lane (t32, h, wave): OR over the sixteen waves
-        const int t32 = lane >> 5, h = (lane >> 4) & 1;
-        uint64_t any = sh.any[lane & 15][t32][h];
-        uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
+        char *img = p.a_img + ((size_t)bi * p.KBA * MMM_AB_COLS + base) * (UNITS * 16);
+        auto stage_of = [&](int k, int unit, uint32_t col) -> int {   // where unit `unit` of image column `col` waits in the stage
+            // (16-bit: undo the rotation of the stage, apply that of the image, see mmm_img_swizzle)
+            return WIDE ? k * 256 + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
+        };
+        if (compact) {
+            for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
+                const int j = q / UNITS, k = (int)sh.live[j];
+                *reinterpret_cast<uint4 *>(img + (uint32_t)q * 16u) = *reinterpret_cast<const uint4 *>(stage + stage_of(k, q % UNITS, base + j));
+            }
+        } else {   // two (16-bit: one) units per thread, 64 columns apart
+            const int j = threadIdx.x / UNITS;
+            const int at = stage_of(j, threadIdx.x % UNITS, (uint32_t)j);
 #pragma unroll
-        for (int d = 1; d < 16; d <<= 1) {
-            lo |= (uint32_t)__shfl_xor((int)lo, d, 64);
-            hi |= (uint32_t)__shfl_xor((int)hi, d, 64);
+            for (int i = 0; i < MMM_AB_COLS * UNITS / BUILD_THREADS; ++i)
+                *reinterpret_cast<uint4 *>(img + (threadIdx.x * 16u + (uint32_t)(i * BUILD_THREADS * 16))) =
+                    *reinterpret_cast<const uint4 *>(stage + at + i * (BUILD_THREADS * 16));
         }
-        const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
-        if ((lane & 15) == 0 && tile < p.MT && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
-    }
-    // the image: column k (or k') of block row bi is one run of 64 elements
-    constexpr int UNITS = MMM_AB_ROWS * (int)sizeof(T) / 16;   // 16-byte units per column
-    const uint32_t base = compact ? sh.base : (uint32_t)k_lo;
-    const int cols = compact ? (int)sh.nlive : MMM_AB_COLS;
-    char *img = p.a_img + ((size_t)bi * p.KBA * MMM_AB_COLS + base) * (UNITS * 16);
-    for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
-        const int j = q / UNITS, unit = q % UNITS;
-        const int k = compact ? (int)sh.live[j] : j;
-        int at;
-        if (WIDE)
-            at = k * 256 + ((unit ^ (k & 15)) << 4);
-        else   // undo the rotation of the stage, apply that of the image (see mmm_img_swizzle)
-            at = k * 128 + ((unit ^ (int)mmm_img_swizzle(base + j) ^ ((k >> 1) & 7)) << 4);
-        *reinterpret_cast<uint4 *>(img + (size_t)q * 16) = *reinterpret_cast<const uint4 *>(sh.stage + at);
     }
 }
 
@@ -269,7 +320,7 @@ struct BShared {
     uint8_t gbits[64][BUILD_WAVES];   // [lane][wave]: rows in which the lane's 16-column group is occupied
     uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
     uint16_t list[B_GROUPS][SEG];
-    uint16_t pack[B_GROUPS / 2 * SEG * MMM_GROUP_COLS];   // 16-bit types: half of the groups, packed
+    uint16_t pack[B_GROUPS / 2][SEG * MMM_GROUP_COLS + 16];   // 16-bit types: half of the groups, packed (rows 8 banks apart)
     int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
 };
@@ -332,9 +383,10 @@ template <int LPB> __device__ __forceinline__ uint32_t squeeze(uint64_t x)
     return (uint32_t)(((x & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
 }
 
-// MAPS: write b_bits and bt_bits.  PACK: write the packed operand (ROWS: of the live rows, and btc_bits).
-template <typename T, int BW, bool MAPS, bool PACK, bool ROWS>
-__device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int lane, int wave, BShared &sh)
+// ROWS (row-compacted mode): the rows are the live rows k' = 128 seg .., and the transposed map is over k'.
+// Returns false where ROWS finds no live row in the segment.
+template <typename T, int BW, bool ROWS>
+__device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int lane, int wave, BShared &sh)
 {
     constexpr int LPB = BW / 4;                 // lanes per block
     constexpr int BPW = B_COLS / BW;            // blocks per workgroup
@@ -353,7 +405,7 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
                 for (int64_t w = threadIdx.x; w < p.WA; w += BUILD_THREADS) p.rows_copy[w] = row_word(p.rows, w, p.K);
             }
         }
-        if (seg * SEG >= (int64_t)live) return;   // no live row left (whole workgroup)
+        if (seg * SEG >= (int64_t)live) return false;   // the whole workgroup
     }
     // lane j < 8: row j of the wave and which of its blocks are switched on
     int64_t krow = -1;
@@ -364,8 +416,7 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
         krow = k >= 0 && k < p.K ? k : -1;
         const int64_t kc = max(krow, (int64_t)0);
         uint64_t w = ~0ull;
-        if (p.keep_blocks != nullptr) w = p.keep_blocks[kc * p.WB + (blk0 >> 6)];   // wave-uniform branches
-        if (p.keep_rows != nullptr && !((p.keep_rows[kc >> 6] >> (kc & 63)) & 1ull)) w = 0;
+        if (p.keep_blocks != nullptr) w = p.keep_blocks[kc * p.WB + (blk0 >> 6)];   // wave-uniform branch
         piece = krow >= 0 ? (uint32_t)(w >> (blk0 & 63)) : 0u;
     }
     u32x4 raw[B_ROWS];
@@ -408,7 +459,7 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
     }
     sh.gbits[lane][wave] = (uint8_t)gb;
     if (LPB == 2) sh.bbits[lane][wave] = (uint8_t)bbm;
-    if (MAPS && lane < B_ROWS && krow >= 0) {   // this workgroup's piece of the map row: 4, 2 or 1 bytes
+    if (lane < B_ROWS && krow >= 0) {   // this workgroup's piece of the map row: 4, 2 or 1 bytes
         const uint32_t v = squeeze<LPB>(mine);
         char *dst = reinterpret_cast<char *>(p.b_bits + krow * p.WB) + blk0 / 8;
         if (LPB == 2)
@@ -421,7 +472,7 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
             for (int64_t q = (blk0 + BPW) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
     }
     constexpr uint32_t ZERO_ENTRY = mmm_list_entry(sizeof(T), MMM_ZERO_COL);
-    if (PACK) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
+    reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
     static_assert(B_GROUPS * SEG * 2 == BUILD_THREADS * 4, "one list word per thread");
     __syncthreads();
     if (wave == 0 && (lane % LPB) == 0) {   // transposed map words of this lane's block
@@ -429,13 +480,10 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
         const int64_t blk = blk0 + lane / LPB;
         if (blk < p.NB) {
             uint64_t *dst = (ROWS ? p.btc_bits : p.bt_bits) + blk * p.WA + seg * 2;
-            if (MAPS || ROWS) {
-                dst[0] = t[0];
-                if (seg * 2 + 1 < p.WA) dst[1] = t[1];
-            }
+            dst[0] = t[0];
+            if (seg * 2 + 1 < p.WA) dst[1] = t[1];
         }
     }
-    if (!PACK) return;
     const uint64_t *gt = reinterpret_cast<const uint64_t *>(sh.gbits[lane]);
     const uint64_t glo = gt[0], ghi = gt[1];
     const uint32_t n = (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi);   // rows of this lane's group
@@ -477,7 +525,7 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             if ((lane >> 5) == half) {
-                uint16_t *g = sh.pack + ((lane >> 2) & 7) * (SEG * MMM_GROUP_COLS);
+                uint16_t *g = sh.pack[(lane >> 2) & 7];
                 auto put = [&](uint32_t slot, uint32_t x, uint32_t y) {
                     uint16_t *at = g + (slot >> 4) * 256 + ((slot >> 2) & 3) * 64 + (lane & 3) * 16 + (slot & 3);
                     at[0] = (uint16_t)x;
@@ -499,7 +547,7 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
                 const uint32_t cn = ((uint32_t)(__popcll(ct_bits[0]) + __popcll(ct_bits[1])) + 15u) & ~15u;
                 char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
                 for (uint32_t q = threadIdx.x & 127u; q < cn * 2; q += 128)
-                    *reinterpret_cast<uint4 *>(cval + q * 16) = reinterpret_cast<const uint4 *>(sh.pack + cg * (SEG * MMM_GROUP_COLS))[q];
+                    *reinterpret_cast<uint4 *>(cval + q * 16) = reinterpret_cast<const uint4 *>(sh.pack[cg])[q];
             }
             __syncthreads();
         }
@@ -509,42 +557,69 @@ __device__ __forceinline__ void scan_b(const BuildParams &p, uint32_t bb, int la
         if (LG < p.NG)
             reinterpret_cast<uint32_t *>(p.bp_list + (LG * p.KBA + seg) * SEG)[lane] = reinterpret_cast<const uint32_t *>(sh.list)[threadIdx.x];
     }
+    if (ROWS) __syncthreads();   // the shared arrays may be reused
+    return true;
 }
 
-template <typename T, bool MAPS, bool PACK, bool ROWS>
-__device__ __forceinline__ void scan_b_width(const BuildParams &p, uint32_t bb, int lane, int wave, BShared &sh)
-{
-    const int64_t bw = p.N / p.NB;
-    if (bw == 8)
-        scan_b<T, 8, MAPS, PACK, ROWS>(p, bb, lane, wave, sh);
-    else if (bw == 16)
-        scan_b<T, 16, MAPS, PACK, ROWS>(p, bb, lane, wave, sh);
-    else
-        scan_b<T, 32, MAPS, PACK, ROWS>(p, bb, lane, wave, sh);
-}
-
-template <typename T>
-__global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8))) void mmm_build_kernel(const BuildParams p)
+// ROWS: row-compacted mode (A laid out over the live rows of B; B built over them).
+template <typename T, int TEST, int BW, bool ROWS>
+__global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void mmm_build_kernel(const BuildParams p)
 {
     __shared__ __align__(16) union { AShared a; BShared b; } sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t b = blockIdx.x;
-    // workgroup ranges: [blocks of A | segments of B | segments of live rows of B]
-    if (b < p.n_a) {
-        if (p.pred == MMM_PRED_NONZERO)
-            scan_a<T, MMM_PRED_NONZERO>(p, b, lane, wave, sh.a);
-        else if (p.pred == MMM_PRED_GT)
-            scan_a<T, MMM_PRED_GT>(p, b, lane, wave, sh.a);
-        else
-            scan_a<T, MMM_PRED_ABS_GT>(p, b, lane, wave, sh.a);
-    } else if (b < p.n_a + p.n_b) {
-        if (p.n_bc == 0)
-            scan_b_width<T, true, true, false>(p, b - p.n_a, lane, wave, sh.b);
-        else
-            scan_b_width<T, true, false, false>(p, b - p.n_a, lane, wave, sh.b);
+    // Workgroups of B come first: they are bound by latency (keep bits, then scattered rows), and what is left of them
+    // when the first finish runs beside the streaming of A.  (Alternating them with those of A, or putting them last,
+    // measured the same or slower: 36.8 and 35.6 against 35.3 us for both sides of 4096^2 at p = .05.)
+    const bool is_b = b < p.n_b_wg;
+    const uint32_t i = is_b ? b : b - p.n_b_wg;
+    if (is_b) {
+        if (ROWS) {
+            for (int64_t w = i; w < p.WA; w += p.n_b_wg) {   // zero map rows for the rows that are off
+                const uint64_t live = row_word(p.rows, w, p.K);
+                const uint32_t words = (uint32_t)(min((int64_t)64, p.K - w * 64) * p.WB);
+                for (uint32_t q = threadIdx.x; q < words; q += BUILD_THREADS)
+                    if (!((live >> (q / (uint32_t)p.WB)) & 1ull)) p.b_bits[w * 64 * p.WB + q] = 0;
+            }
+            for (uint32_t bb = i; bb < p.n_b; bb += p.n_b_wg) {   // ends at the first segment without a live row
+                int l = lane;
+                asm volatile("" : "+v"(l));   // keeps what depends on the lane from being carried around the loop (it would spill)
+                if (!scan_b<T, BW, true>(p, bb, l, wave, sh.b)) break;
+            }
+        } else {
+            scan_b<T, BW, false>(p, i, lane, wave, sh.b);
+        }
     } else {
-        scan_b_width<T, false, true, true>(p, b - p.n_a - p.n_b, lane, wave, sh.b);
+        const int64_t bi0 = (int64_t)(i / (uint32_t)p.KBA) * p.a_per_wg;
+        scan_a<T, TEST, ROWS>(p, i % (uint32_t)p.KBA, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+    }
+}
+
+// Row-compacted mode: bt_bits (over k) by spreading the bits of btc_bits to the places rows_copy names.  One wave per
+// word of 64 k.
+__global__ __launch_bounds__(256) void mmm_expand_rows_kernel(const uint64_t *rows, const uint64_t *btc_bits, uint64_t *bt_bits,
+                                                              int64_t K, int64_t NB, int64_t WA)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= WA) return;
+    uint32_t before = 0;
+    for (int64_t q = lane; q < w; q += 64) before += (uint32_t)__popcll(rows[q]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d, 64);
+    const uint64_t live = readlane64(rows[w], 0);
+    const int64_t at = (int64_t)(before >> 6);
+    const int sh = (int)(before & 63u);
+    for (int64_t blk = lane; blk < NB; blk += 64) {
+        uint64_t bits = btc_bits[blk * WA + min(at, WA - 1)] >> sh;
+        if (sh != 0) bits |= btc_bits[blk * WA + min(at + 1, WA - 1)] << (64 - sh);
+        uint64_t out = 0;
+        for (uint64_t m = live; m != 0; m &= m - 1) {   // wave-uniform
+            out |= (bits & 1ull) << __builtin_ctzll(m);
+            bits >>= 1;
+        }
+        bt_bits[blk * WA + w] = out;
     }
 }
 
@@ -639,23 +714,76 @@ __global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, 
 
 }   // namespace
 
-// What keep_element compares against.  GT: x > t  <=>  key(x) > key(t) on the order-preserving key
-// (both zeros map to the same key).  ABS_GT: |x| > t; a negative t passes every non-zero x (magnitude
-// bits of x > 0), t = -0 is t = 0.  A NaN threshold passes nothing (nothing exceeds 0xffffffff).
-
-static uint32_t threshold_key(int32_t pred, float threshold)
+// The ranges of bit patterns a predicate accepts.  `value` maps a magnitude pattern 0 .. inf of the element type to its
+// value, rising with the pattern.
+template <typename F> static ElementTest element_test(int32_t pred, float threshold, uint32_t inf, uint32_t sign, F value)
 {
-    union { float f; uint32_t u; } cv;
-    cv.f = threshold;
-    uint32_t t = cv.u;
-    const uint32_t at = t & 0x7fffffffu;
-    if (at > 0x7f800000u) return 0xffffffffu;
-    if (pred == MMM_PRED_GT) {
-        if (at == 0) t = 0;
-        return (t & 0x80000000u) ? ~t : (t | 0x80000000u);
+    auto first = [&](auto &&is) -> uint32_t {   // smallest magnitude pattern for which `is` holds, inf + 1 if none
+        uint32_t lo = 0, hi = inf + 1;
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2;
+            if (is(value(mid)))
+                hi = mid;
+            else
+                lo = mid + 1;
+        }
+        return lo;
+    };
+    const float t = threshold;
+    ElementTest e{TEST_MAGNITUDE, 1, sign - 1, 0, 0};   // non-zero, NaN included
+    if (pred == MMM_PRED_NONZERO) return e;
+    e.mode = pred == MMM_PRED_GT ? TEST_ONE_RANGE : TEST_MAGNITUDE;
+    e.len1 = 0;
+    if (t != t) return e;   // NaN threshold: nothing passes
+    if (t >= 0.f) {         // -0 included
+        e.lo1 = first([&](float v) { return v > t; });
+        e.len1 = inf + 1 - e.lo1;
+    } else {                // every non-negative number; of the negative ones those smaller in magnitude
+        e.lo1 = 1;
+        e.len1 = inf;
+        if (pred == MMM_PRED_GT) {
+            e.mode = TEST_TWO_RANGES;
+            e.lo2 = sign + 1;
+            e.len2 = first([&](float v) { return v >= -t; }) - 1;
+        }
     }
-    if (pred == MMM_PRED_ABS_GT) return (t & 0x80000000u) ? 0u : at;
-    return 0;
+    return e;
+}
+
+static ElementTest element_test(int32_t dtype, int32_t pred, float threshold)
+{
+    auto bits = [](uint32_t u) {
+        float f;
+        std::memcpy(&f, &u, 4);
+        return f;
+    };
+    if (dtype == MMM_BF16) return element_test(pred, threshold, 0x7f80u, 0x8000u, [&](uint32_t v) { return bits(v << 16); });
+    if (dtype == MMM_F16)
+        return element_test(pred, threshold, 0x7c00u, 0x8000u, [](uint32_t v) { return (float)__builtin_bit_cast(_Float16, (uint16_t)v); });
+    return element_test(pred, threshold, 0x7f800000u, 0x80000000u, bits);
+}
+
+typedef void (*build_kernel_fn)(const BuildParams);
+
+template <typename T, int TEST, bool ROWS> static build_kernel_fn build_kernel_width(int32_t bw)
+{
+    return bw == 8 ? mmm_build_kernel<T, TEST, 8, ROWS> : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS> : mmm_build_kernel<T, TEST, 32, ROWS>;
+}
+template <typename T, bool ROWS> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
+{
+    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS>(bw)
+         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS>(bw)
+                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS>(bw);
+}
+template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows)
+{
+    return rows ? build_kernel_test<T, true>(mode, bw) : build_kernel_test<T, false>(mode, bw);
+}
+static build_kernel_fn build_kernel(int32_t dtype, int32_t mode, int32_t bw, bool rows)
+{
+    return dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows)
+         : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows)
+                             : build_kernel_rows<float>(mode, bw, rows);
 }
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s)
@@ -669,7 +797,6 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.a_img = m->a_img;
     p.Y = a.Y;
     p.ldy = a.ldy;
-    p.keep_rows = a.keep_rows;
     p.keep_blocks = a.keep_blocks;
     p.b_bits = m->b_bits;
     p.bt_bits = m->bt_bits;
@@ -683,10 +810,10 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.WA = m->WA;
     p.WB = m->WB;
     p.MT = m->MT;
+    p.MBA = m->MBA;
     p.KBA = m->KBA;
     p.NG = m->NG;
-    p.pred = a.pred;
-    p.thr_bits = threshold_key(a.pred, a.threshold);
+    p.test = element_test(a.dtype, a.pred, a.threshold);
     p.y_unaligned = a.dtype != MMM_F32 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
     p.kinfo = m->kinfo;
     p.kmap = m->kmap;
@@ -697,20 +824,33 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.ctiles = (uint32_t)((m->N + B_COLS - 1) / B_COLS);
     const int64_t n_a = a.X ? m->MBA * m->KBA : 0;
     const int64_t n_b = a.Y ? m->KBA * p.ctiles : 0;
-    const int64_t n_bc = a.Y && a.b_compact ? n_b : 0;
-    const int64_t n_all = n_a + n_b + n_bc;
-    if (n_all <= 0 || n_all > 0x7fffffffLL) return hipErrorInvalidValue;
-    p.n_a = (uint32_t)n_a;
+    // Row-compacted B: how many segments have a live row is known on the device only; at most one workgroup per CU loops
+    // over them.
+    const int64_t n_b_wg = a.b_compact && n_b > 256 ? 256 : n_b;
+    // Blocks of A per workgroup: as many as leave every CU the two workgroups that fit, up to eight, so that one load
+    // phase stands in front of several blocks and the others hide behind the stores of the block before (2048 x 16384
+    // ReLU: 50.7, 42.1, 38.2 us with one, two, four; a 2048^2 matrix, 512 blocks, wants one: 10.0 against 13.4 with four).
+    int64_t per_wg = n_a / 512;
+    per_wg = per_wg < 1 ? 1 : per_wg > 8 ? 8 : per_wg;
+    if (per_wg > m->MBA) per_wg = m->MBA;
+    const int64_t n_a_wg = a.X ? (m->MBA + per_wg - 1) / per_wg * m->KBA : 0;
+    const int64_t n_all = n_a_wg + n_b_wg;
+    if (n_all <= 0 || n_a > 0x7fffffffLL || n_b > 0x7fffffffLL || n_all > 0x7fffffffLL) return hipErrorInvalidValue;
     p.n_b = (uint32_t)n_b;
-    p.n_bc = (uint32_t)n_bc;
+    p.n_a_wg = (uint32_t)n_a_wg;
+    p.n_b_wg = (uint32_t)n_b_wg;
+    p.a_per_wg = (uint32_t)per_wg;
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    if (a.dtype == MMM_BF16)
-        hipLaunchKernelGGL(mmm_build_kernel<uint16_t>, grid, block, 0, s, p);
-    else if (a.dtype == MMM_F16)
-        hipLaunchKernelGGL(mmm_build_kernel<_Float16>, grid, block, 0, s, p);
-    else
-        hipLaunchKernelGGL(mmm_build_kernel<float>, grid, block, 0, s, p);
+    hipLaunchKernelGGL(build_kernel(a.dtype, p.test.mode, m->bw, p.rows != nullptr), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t mmm_launch_expand_rows(const mmm_maps *m, hipStream_t s)
+{
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(mmm_expand_rows_kernel, dim3((uint32_t)((m->WA + 3) / 4)), dim3(256), 0, s, m->rows_copy, m->btc_bits, m->bt_bits,
+                       m->K, m->NB, m->WA);
     return hipGetLastError();
 }
 
