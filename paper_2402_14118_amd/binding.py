@@ -1,4 +1,4 @@
-"""ctypes binding of the C ABI in include/mmm.h.
+"""Binding of the C ABI in include/mmm.h: ctypes, and native entry points for the calls made in every step.
 
 Argument marshalling only: every step of the path runs in the HIP library.
 PyTorch tensors are used as device buffers and for the stream handle.  There is
@@ -88,6 +88,9 @@ def _load() -> ctypes.CDLL:
 
 lib = _load()
 
+# after the library: linked against it, and against the runtime PyTorch has loaded
+from . import _mmm_native as native  # noqa: E402
+
 
 def status_string(st: int) -> str:
     return lib.mmm_status_string(int(st)).decode()
@@ -111,9 +114,15 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+# The current stream's handle straight from torch's runtime: building a Stream object takes 2.8 us a call.
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+_get_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
+        if _get_raw_stream is not None and _get_device is not None and torch.cuda.is_initialized():
+            return _get_raw_stream(_get_device()) or None
         return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None
@@ -137,11 +146,14 @@ def mmm_maps_release(maps: Optional[int]) -> None:
     lib.mmm_maps_release(maps)
 
 
+_NO_MASK = (0, 0, None)
+
+
 def mmm_build_maps(maps: int, dt: int, X, ldx: int, ma: Optional[MaskA], Y, ldy: int, mb: Optional[MaskB],
                    stream=None) -> None:
-    _check(lib.mmm_build_maps(maps, dt, _ptr(X), ldx, ctypes.byref(ma) if ma is not None else None,
-                              _ptr(Y), ldy, ctypes.byref(mb) if mb is not None else None, _stream(stream)),
-           "mmm_build_maps")
+    _check(native.build_maps(maps, dt, _ptr(X), ldx, ma is not None, *((ma.pred, ma.threshold, ma.keep_bits) if ma is not None else _NO_MASK),
+                             _ptr(Y), ldy, mb is not None, *((mb.block_width, mb.keep_rows, mb.keep_blocks) if mb is not None else _NO_MASK),
+                             _stream(stream)), "mmm_build_maps")
 
 
 def mmm_maps_view(maps: int):
@@ -194,8 +206,7 @@ def mmm_maps_stats(maps: int, stream=None):
 
 
 def mmm_matmul(maps: int, dt: int, X, ldx: int, Y, ldy: int, C, ldc: int, accumulate: int = 0, stream=None) -> None:
-    _check(lib.mmm_matmul(maps, dt, _ptr(X), ldx, _ptr(Y), ldy, _ptr(C), ldc, int(accumulate), _stream(stream)),
-           "mmm_matmul")
+    _check(native.matmul(maps, dt, _ptr(X), ldx, _ptr(Y), ldy, _ptr(C), ldc, int(accumulate), _stream(stream)), "mmm_matmul")
 
 
 def mmm_matmul_static_scratch(maps: int, dt: int, X, ldx: int, Y, ldy: int, C, ldc: int, accumulate: int = 0,
@@ -206,8 +217,8 @@ def mmm_matmul_static_scratch(maps: int, dt: int, X, ldx: int, Y, ldy: int, C, l
 
 def mmm_matmul_fused(maps: int, dt: int, X, ldx: int, ma: MaskA, Y, ldy: int, C, ldc: int, accumulate: int = 0,
                      stream=None) -> None:
-    _check(lib.mmm_matmul_fused(maps, dt, _ptr(X), ldx, ctypes.byref(ma), _ptr(Y), ldy, _ptr(C), ldc, int(accumulate),
-                                _stream(stream)), "mmm_matmul_fused")
+    _check(native.matmul_fused(maps, dt, _ptr(X), ldx, ma.pred, ma.threshold, ma.keep_bits, _ptr(Y), ldy, _ptr(C), ldc,
+                               int(accumulate), _stream(stream)), "mmm_matmul_fused")
 
 
 def mmm_maps_set_path(maps: int, path: int = -1) -> None:

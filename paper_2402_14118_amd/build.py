@@ -4,15 +4,19 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmmm_hip.so")
+NATIVE = os.path.join(PKG, "_mmm_native.so")       # CPython entry points, linked against the library
+NATIVE_SOURCE = os.path.join(CSRC, "mmm_python.cpp")
 SOURCES = ["mmm_api.hip", "mmm_build.hip", "mmm_matmul.hip", "mmm_pairs.hip", "mmm_build64.hip"]
 HEADERS = [os.path.join(CSRC, "mmm_internal.h"), os.path.join(ROOT, "include", "mmm.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+CXX = os.environ.get("CXX", "g++")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     # packed fp32 VALU forms are kept off for all device code
@@ -22,15 +26,15 @@ FLAGS = [
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(NATIVE):
         return True
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS
+    t = min(os.path.getmtime(LIB), os.path.getmtime(NATIVE))
+    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS + [NATIVE_SOURCE]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every source and link libmmm_hip.so next to this file."""
+    """Compile every source and link libmmm_hip.so and the CPython entry points next to this file."""
     if not force and not stale():
         return LIB
     objs = []
@@ -54,7 +58,10 @@ def build(force: bool = True, verbose: bool = False) -> str:
             print(out)
     if failed:
         raise RuntimeError("hipcc failed")
-    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", LIB, *objs]
+    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-Wl,-soname,libmmm_hip.so", "-o", LIB, *objs]
+    subprocess.run(cmd, check=True)
+    cmd = [CXX, "-O2", "-std=c++17", "-shared", "-fPIC", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], NATIVE_SOURCE, "-o", NATIVE, "-L", PKG, "-l:libmmm_hip.so", "-Wl,-rpath,$ORIGIN"]
     subprocess.run(cmd, check=True)
     return LIB
 

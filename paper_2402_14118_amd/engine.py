@@ -38,16 +38,15 @@ class MaskedMatmul:
                    threshold: float = 0.0, keep_a: Optional[torch.Tensor] = None,
                    keep_rows: Optional[torch.Tensor] = None, keep_blocks: Optional[torch.Tensor] = None,
                    stream=None) -> None:
-        ma = mb = None
-        if X is not None:
-            ma = B.MaskA(pred, threshold, B._ptr(keep_a))
-        if Y is not None:
-            mb = B.MaskB(self.bw, B._ptr(keep_rows), B._ptr(keep_blocks))
-        B.mmm_build_maps(self.maps, self.dtype, X, X.stride(0) if X is not None else 0, ma,
-                         Y, Y.stride(0) if Y is not None else 0, mb, stream)
+        B._check(B.native.build_maps(
+            self.maps, self.dtype,
+            None if X is None else X.data_ptr(), 0 if X is None else X.stride(0), X is not None, pred, threshold, B._ptr(keep_a),
+            None if Y is None else Y.data_ptr(), 0 if Y is None else Y.stride(0), Y is not None, self.bw, B._ptr(keep_rows),
+            B._ptr(keep_blocks), B._stream(stream)), "mmm_build_maps")
 
     def matmul(self, X: torch.Tensor, Y: torch.Tensor, C: torch.Tensor, accumulate: bool = False, stream=None) -> None:
-        B.mmm_matmul(self.maps, self.dtype, X, X.stride(0), Y, Y.stride(0), C, C.stride(0), int(accumulate), stream)
+        B._check(B.native.matmul(self.maps, self.dtype, X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), C.data_ptr(),
+                                 C.stride(0), accumulate, B._stream(stream)), "mmm_matmul")
 
     def matmul_static_scratch(self, X: torch.Tensor, Y: torch.Tensor, C: torch.Tensor, accumulate: bool = False,
                               stream=None) -> None:
@@ -58,9 +57,9 @@ class MaskedMatmul:
                      threshold: float = 0.0, keep_a: Optional[torch.Tensor] = None, accumulate: bool = False,
                      stream=None) -> None:
         """C (+)= M(X) x B with M evaluated inside the multiplication; only the B side of the maps is used."""
-        ma = B.MaskA(pred, threshold, B._ptr(keep_a))
-        B.mmm_matmul_fused(self.maps, self.dtype, X, X.stride(0), ma, Y, Y.stride(0), C, C.stride(0), int(accumulate),
-                           stream)
+        B._check(B.native.matmul_fused(self.maps, self.dtype, X.data_ptr(), X.stride(0), pred, threshold, B._ptr(keep_a),
+                                       Y.data_ptr(), Y.stride(0), C.data_ptr(), C.stride(0), accumulate, B._stream(stream)),
+                 "mmm_matmul_fused")
 
     def set_path(self, path: int = -1) -> None:
         B.mmm_maps_set_path(self.maps, path)
