@@ -63,10 +63,9 @@ typedef enum {
 /* Element type of X and Y.  BF16 is the upper half of an IEEE float, F16 the IEEE
  * half format; both are widened to float exactly, products are accumulated in
  * float and C is float.  F64: X, Y and C are double, products are accumulated in
- * double (the paper reports float and double runs, section 4).  Double inputs
- * are multiplied by the MMM_PATH_PAIRS kernel only, and mmm_build_maps writes the
- * bitmaps and derived maps for them but no blocked lists (mmm_maps_view_lists is
- * then meaningless) and does not use the row-compacted mode. */
+ * double (the paper reports float and double runs, section 4).  For double inputs
+ * there are no blocked lists (mmm_maps_view_lists is then meaningless) and no
+ * row-compacted mode, and matrices of at most 64 rows always take MMM_PATH_PAIRS. */
 typedef enum { MMM_F32 = 0, MMM_BF16 = 1, MMM_F16 = 2, MMM_F64 = 3 } mmm_dtype;
 
 /* Element predicate of M.  An element of A is non-zero iff the predicate holds,
@@ -102,8 +101,9 @@ typedef struct mmm_maps mmm_maps;
 
 /* Bytes of device workspace that maps for this shape need: the maps and their
  * derived forms, the image of A (4 bytes per element of X), packed B at its
- * worst-case size (4 bytes per element of Y, and 2 bytes per row of Y and 16
- * columns), room for the inspection lists of A (8 bytes per element of X), and
+ * worst-case size (8 bytes per element of Y, 4 if M is at most 64, and 2 bytes per
+ * row of Y and 16 columns), room for the inspection lists of A or the image of a
+ * double A (8 bytes per element of X), and
  * the partial-sum area of the split-K multiplication (at most 64 MiB).
  * Errors: MMM_ERR_SHAPE, MMM_ERR_INVALID_ARG (bytes NULL). */
 mmm_status mmm_maps_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t block_width, size_t *bytes);
@@ -258,7 +258,8 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
  * across rebuilds): for matrices of at most 64 rows PAIRS unless p_A * p_B is known to exceed
  * 0.02; for larger ones PAIRS iff the densities are known and p_B * (1 - 24.5 * p_A) > 0.015
  * (A keeps fewer than 4 % of its elements and B is not nearly empty), or the problem is small
- * (fewer than 128 tiles of 64 x 128 in C) with at most 64 surviving k per element of C; else MATRIX.  The
+ * (fewer than 128 tiles of 64 x 128 in C) with at most 64 surviving k per element of C; else MATRIX.
+ * Double inputs: MATRIX iff M * K * N is at least 2^27 (and M above 64).  The
  * thresholds are fitted to timings on an MI355X.  The paper leaves this
  * per-workload choice of method to the caller (section 6, choosing between methods by
  * sparsity). */

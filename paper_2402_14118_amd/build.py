@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libmmm_hip.so")
 NATIVE = os.path.join(PKG, "_mmm_native.so")       # CPython entry points, linked against the library
 NATIVE_SOURCE = os.path.join(CSRC, "mmm_python.cpp")
-SOURCES = ["mmm_api.hip", "mmm_build.hip", "mmm_matmul.hip", "mmm_pairs.hip", "mmm_build64.hip"]
+SOURCES = ["mmm_api.hip", "mmm_build.hip", "mmm_matmul.hip", "mmm_pairs.hip"]
 HEADERS = [os.path.join(CSRC, "mmm_internal.h"), os.path.join(ROOT, "include", "mmm.h")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

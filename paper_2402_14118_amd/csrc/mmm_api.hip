@@ -77,7 +77,7 @@ Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw)
     // packed B: every row of every 16-column group, in the widest element type that is packed
     const size_t segs = (size_t)((N + MMM_GROUP_COLS - 1) / MMM_GROUP_COLS) * (size_t)((K + MMM_AB_COLS - 1) / MMM_AB_COLS);
     l.bp_val = off;
-    off += align_up(segs * MMM_AB_COLS * MMM_GROUP_COLS * 4);
+    off += align_up(segs * MMM_AB_COLS * MMM_GROUP_COLS * (mmm_packs(M, MMM_F64) ? 8 : 4));
     l.bp_list = off;
     off += align_up(segs * MMM_AB_COLS * 2);
     l.bp_cnt = off;
@@ -98,7 +98,6 @@ size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 
 mmm_plan make_plan(const mmm_maps *m, int32_t dt)
 {
-    (void)dt;
     mmm_plan p{};
     int64_t v = m->plan_variant >= 0 ? m->plan_variant : g_opt_variant.load();
     if (v >= 0 && v < mmm_variant_count() && mmm_variant((int32_t)v).rows < MMM_AB_ROWS && m->M > mmm_variant((int32_t)v).rows)
@@ -130,7 +129,7 @@ mmm_plan make_plan(const mmm_maps *m, int32_t dt)
             if (split > p.chunks_total / 8) split = p.chunks_total / 8;
         }
     }
-    const int64_t max_by_ws = (int64_t)(m->partial_bytes / ((size_t)m->M * (size_t)m->N * sizeof(float)));
+    const int64_t max_by_ws = (int64_t)(m->partial_bytes / ((size_t)m->M * (size_t)m->N * c_elem_size(dt)));
     if (split > max_by_ws) split = max_by_ws;
     if (split > p.chunks_total) split = p.chunks_total;
     if (split < 1) split = 1;
@@ -154,11 +153,13 @@ mmm_plan make_plan(const mmm_maps *m, int32_t dt)
 // known only after a mmm_maps_stats call (the counts of the most recent one are kept as the
 // estimate, also across rebuilds: emergent sparsity levels are stable from step to step); without
 // one the shape decides alone.
-int32_t choose_path(const mmm_maps *m)
+int32_t choose_path(const mmm_maps *m, int32_t dt)
 {
+    if (!mmm_packs(m->M, dt)) return MMM_PATH_PAIRS;
     int64_t path = m->plan_path >= 0 ? m->plan_path : g_opt_path.load();
     if (path == MMM_PATH_MATRIX || path == MMM_PATH_PAIRS) return (int32_t)path;
     if (m->plan_variant >= 0 || g_opt_variant.load() >= 0) return MMM_PATH_MATRIX;   // a tile variant was asked for
+    if (dt == MMM_F64) return (double)m->M * (double)m->K * (double)m->N >= 134217728.0 ? MMM_PATH_MATRIX : MMM_PATH_PAIRS;
     const bool known = m->stats_a_valid && m->stats_b_valid;
     const double p_a = known ? (double)m->stats_nnz_a / ((double)m->M * (double)m->K) : 0.0;
     const double p_b = known ? (double)m->stats_occ_b / ((double)m->K * (double)m->NB) : 0.0;
@@ -229,6 +230,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->a_cnt = reinterpret_cast<uint32_t *>(base + l.a_cnt);
     m->NG = (N + MMM_GROUP_COLS - 1) / MMM_GROUP_COLS;
     m->a_img = base + l.a_img;
+    m->a_img64 = base + l.a_ent;
     m->a_ent = reinterpret_cast<uint64_t *>(base + l.a_ent);
     m->b_bits = reinterpret_cast<uint64_t *>(base + l.b_bits);
     m->bt_bits = reinterpret_cast<uint64_t *>(base + l.bt_bits);
@@ -302,9 +304,7 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
     a.b_compact = Y != nullptr && mb->keep_rows != nullptr && dt != MMM_F64;
     const bool compact_after = Y != nullptr ? a.b_compact : maps->b_compact;
     a.a_compact = X != nullptr && compact_after;
-    if (hipError_t e = dt == MMM_F64 ? mmm_launch_build64(maps, a, static_cast<hipStream_t>(hip_stream))
-                                      : mmm_launch_build(maps, a, static_cast<hipStream_t>(hip_stream));
-        e != hipSuccess) {
+    if (hipError_t e = mmm_launch_build(maps, a, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
         note_device_error("map builder launch", e);
         return MMM_ERR_DEVICE;
     }
@@ -314,7 +314,7 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
         maps->b_compact = a.b_compact;
         maps->bt_ready = !a.b_compact;
-        if (a.b_compact && (maps->M <= 64 || choose_path(maps) == MMM_PATH_PAIRS)) {
+        if (a.b_compact && (maps->M <= 64 || choose_path(maps, dt) == MMM_PATH_PAIRS)) {
             if (hipError_t e = mmm_launch_expand_rows(maps, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
                 note_device_error("transposed map launch", e);
                 return MMM_ERR_DEVICE;
@@ -462,12 +462,12 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
     if (reinterpret_cast<uintptr_t>(X) % esz != 0 || reinterpret_cast<uintptr_t>(Y) % esz != 0 ||
         reinterpret_cast<uintptr_t>(C) % c_elem_size(dt) != 0)
         return MMM_ERR_DTYPE;
-    if (dt == MMM_F64 && !mmm_pairs_supports(dt, ldy)) return MMM_ERR_SHAPE;   // double inputs have the pair kernel only
+    if (dt == MMM_F64 && !mmm_pairs_supports(dt, ldy)) return MMM_ERR_SHAPE;   // for every double Y, whichever kernel it is
     if (!maps->a_built || !maps->b_built) return MMM_ERR_MAPS_MISMATCH;
     if (maps->a_dtype != dt || maps->b_dtype != dt) return MMM_ERR_MAPS_MISMATCH;
     // the values of A travel in the image that was made from X at build time: another X is another A
     if (maps->a_src != X || maps->a_src_ld != ldx) return MMM_ERR_MAPS_MISMATCH;
-    if (dt == MMM_F64 || (choose_path(maps) == MMM_PATH_PAIRS && mmm_pairs_supports(dt, ldy))) {   // no scratch at all on this path
+    if (choose_path(maps, dt) == MMM_PATH_PAIRS && mmm_pairs_supports(dt, ldy)) {   // no scratch at all on this path
         hipError_t e = ensure_bt(maps, static_cast<hipStream_t>(hip_stream));
         if (e == hipSuccess)
             e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, false, 0, 0.f, nullptr,
@@ -479,23 +479,23 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
         return MMM_OK;
     }
     const mmm_plan p = make_plan(maps, dt);
-    float *partials = maps->partials;
+    void *partials = maps->partials;
     size_t partial_bytes = maps->partial_bytes;
     if (static_scratch) {
-        const size_t need = p.split_k > 1 ? (size_t)p.split_k * (size_t)maps->M * (size_t)maps->N * sizeof(float) : 0;
+        const size_t need = p.split_k > 1 ? (size_t)p.split_k * (size_t)maps->M * (size_t)maps->N * c_elem_size(dt) : 0;
         if (need > (size_t)MMM_STATIC_SCRATCH_BYTES) {
             std::snprintf(g_detail, sizeof(g_detail),
                           "mmm_matmul_static_scratch: %d partial sums of C need %zu bytes, the static scratch holds %zu",
                           (int)p.split_k, need, (size_t)MMM_STATIC_SCRATCH_BYTES);
             return MMM_ERR_WORKSPACE;
         }
-        if (hipError_t e = mmm_static_scratch(&partials); e != hipSuccess) {
+        if (hipError_t e = mmm_static_scratch(reinterpret_cast<float **>(&partials)); e != hipSuccess) {
             note_device_error("address of the static scratch", e);
             return MMM_ERR_DEVICE;
         }
         partial_bytes = (size_t)MMM_STATIC_SCRATCH_BYTES;
     }
-    if (hipError_t e = mmm_launch_matmul(maps, p, dt, static_cast<float *>(C), ldc, accumulate ? 1 : 0, partials,
+    if (hipError_t e = mmm_launch_matmul(maps, p, dt, C, ldc, accumulate ? 1 : 0, partials,
                                          partial_bytes, static_cast<hipStream_t>(hip_stream));
         e != hipSuccess) {
         note_device_error("masked GEMM launch", e);
@@ -565,7 +565,7 @@ mmm_status mmm_maps_set_path(mmm_maps *maps, int32_t path)
 mmm_status mmm_matmul_path(const mmm_maps *maps, int32_t *path)
 {
     if (maps == nullptr || path == nullptr) return MMM_ERR_INVALID_ARG;
-    *path = (maps->a_built && maps->a_dtype == MMM_F64) || (maps->b_built && maps->b_dtype == MMM_F64) ? MMM_PATH_PAIRS : choose_path(maps);
+    *path = choose_path(maps, maps->a_built ? maps->a_dtype : maps->b_built ? maps->b_dtype : MMM_F32);
     return MMM_OK;
 }
 

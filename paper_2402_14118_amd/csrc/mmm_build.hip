@@ -24,10 +24,15 @@ constexpr int BUILD_WAVES = 16;
 constexpr int BUILD_THREADS = BUILD_WAVES * 64;
 constexpr int SEG = MMM_AB_COLS;                      // rows of B (values of k) per workgroup = k per step of the matrix kernel
 constexpr int B_ROWS = SEG / BUILD_WAVES;             // 8 rows per wave
-constexpr int B_COLS = 256;                           // columns of B per workgroup: four per lane
-constexpr int B_GROUPS = B_COLS / MMM_GROUP_COLS;     // 16
 constexpr int A_ROWS = MMM_AB_ROWS / BUILD_WAVES;     // 4 rows of A per wave
-constexpr int A_WORDS = MMM_AB_COLS / 64;             // 2
+
+template <typename T> struct Tile {   // what a workgroup takes at a time, by element size
+    static constexpr int ESZ = (int)sizeof(T);
+    static constexpr int A_WORDS = ESZ == 8 ? 1 : 2;             // A: 64 rows x 64 A_WORDS columns
+    static constexpr int LANE_COLS = ESZ == 8 ? 2 : 4;           // B: 128 rows x 64 LANE_COLS columns, so many per lane
+    static constexpr int B_COLS = 64 * LANE_COLS;
+    static constexpr int B_GROUPS = B_COLS / MMM_GROUP_COLS;
+};
 
 // Element predicate of M, decided on the bit pattern so that no denormal mode of the float pipeline can
 // change a map bit.  Every predicate, the non-zero test included, is membership of the pattern (or of the
@@ -37,7 +42,7 @@ constexpr int A_WORDS = MMM_AB_COLS / 64;             // 2
 enum { TEST_MAGNITUDE = 0, TEST_ONE_RANGE = 1, TEST_TWO_RANGES = 2 };
 struct ElementTest {
     int32_t mode;
-    uint32_t lo1, len1, lo2, len2;   // lo <= pattern < lo + len
+    uint64_t lo1, len1, lo2, len2;   // lo <= pattern < lo + len
 };
 
 struct BuildParams {
@@ -50,6 +55,7 @@ struct BuildParams {
     const void *Y;
     int64_t ldy;
     const uint64_t *keep_blocks;
+    const uint64_t *keep_rows;   // doubles only
     uint64_t *b_bits;
     uint64_t *bt_bits;
     char *bp_val;         // packed B: [group][segment][128 slots][16 columns]
@@ -57,11 +63,13 @@ struct BuildParams {
     uint32_t *bp_cnt;     // [group][segment]
     int64_t M, K, N, NB, WA, WB, MT, MBA, KBA, NG;
     ElementTest test;
+    int32_t pack;         // write packed B
     int32_t y_unaligned;  // 16-bit Y whose rows do not start on 4-byte boundaries
     uint32_t n_b;               // segments x column tiles of B
     uint32_t n_a_wg, n_b_wg;    // workgroups for them
     uint32_t a_per_wg;          // blocks of A per workgroup
-    uint32_t ctiles;      // column tiles of 256 per segment
+    uint32_t ctiles;      // column tiles per segment of B
+    int64_t a_units;      // blocks of A side by side
     // row-compacted mode (whole rows of B switched off): k' = 0 .. K' - 1 numbers the rows `rows` leaves on
     const uint64_t *rows;    // keep_rows, or the copy of it a cached B side was built with; else null
     uint64_t *rows_copy;     // where that copy goes (B side built in this call)
@@ -74,6 +82,10 @@ template <typename T> __device__ __forceinline__ uint32_t f32_bits(T v);
 template <> __device__ __forceinline__ uint32_t f32_bits<float>(float v) { return __float_as_uint(v); }
 template <> __device__ __forceinline__ uint32_t f32_bits<uint16_t>(uint16_t v) { return (uint32_t)v << 16; }   // bf16
 template <> __device__ __forceinline__ uint32_t f32_bits<_Float16>(_Float16 v) { return __float_as_uint((float)v); }
+
+// bit patterns of the 4- and 8-byte types
+template <int ESZ> struct Pattern { typedef uint32_t type; static constexpr type magnitude = 0x7fffffffu; };
+template <> struct Pattern<8> { typedef uint64_t type; static constexpr type magnitude = 0x7fffffffffffffffull; };
 
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 
@@ -103,31 +115,35 @@ __device__ __forceinline__ uint64_t bits_below(uint64_t m, int64_t left) { retur
 __device__ __forceinline__ uint64_t row_word(const uint64_t *row, int64_t w, int64_t K) { return bits_below(row[w], K - w * 64); }
 
 // ---- A side: one workgroup = a few blocks of 64 rows x 128 columns, one below the other ---------
-// A wave takes the four rows that are neighbours in an LDS column: w, w+16, w+32, w+48 for 4-byte
-// elements (one 16-byte read of the matrix kernel yields one element for each of its four 16-row
+// A wave takes the four rows that are neighbours in an LDS column: w, w+16, w+32, w+48 for 4- and 8-byte
+// elements (one or two 16-byte reads of the matrix kernel yield one element for each of its four 16-row
 // tiles), 4w .. 4w+3 for 16-bit ones (natural order: the transposing LDS read wants contiguous rows).
+// Blocks of doubles are 64 columns wide.
 // The block is turned around in LDS (16-byte or 8-byte pieces whose position is rotated with k, so that
 // the 64 lanes of a write do not fall on the same banks) and leaves as whole cache lines.  The loads of
 // the next block are issued before the barrier of the current one and two stages alternate, so that the
 // memory system always has work of a workgroup although only two of this size fit on a compute unit.
 struct AShared {
     char stage[2][MMM_AB_COLS * MMM_AB_ROWS * 4];
-    uint64_t any[2][BUILD_WAVES][2][A_WORDS];   // [stage][wave][32-row half of the block][word]
+    uint64_t any[2][BUILD_WAVES][2][2];         // [stage][wave][32-row half of the block][word]
     uint8_t live[MMM_AB_COLS];                  // row-compacted mode: live columns of the blocks
     uint32_t before[BUILD_WAVES];               // row-compacted mode: live rows before them, by wave
 };
 
 template <typename T> struct ABlock {   // one block in a wave's registers
-    uint32_t x[A_ROWS][sizeof(T) == 4 ? A_WORDS : 1];   // 4-byte: lane <-> k; 16-bit: two neighbouring k per lane
-    uint32_t kb[A_ROWS];                                // 16-bit: the byte that holds the lane's keep bits
-    uint64_t kw;                                        // 4-byte: keep word of (row, half), in lane 2t + h
+    typename Pattern<sizeof(T)>::type x[A_ROWS][sizeof(T) == 4 ? 2 : 1];   // lane <-> k; 16-bit: two neighbouring k per lane
+    uint32_t kb[A_ROWS];   // 16-bit: the byte that holds the lane's keep bits
+    uint64_t kw;           // otherwise: keep word of (row t, half h), in lane t * A_WORDS + h
 };
 
 template <typename T, int TEST, bool ROWS>
 __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
 {
-    constexpr bool WIDE = sizeof(T) == 4;
-    constexpr int UNITS = MMM_AB_ROWS * (int)sizeof(T) / 16;   // 16-byte units per column
+    typedef typename Pattern<sizeof(T)>::type pattern;
+    constexpr int ESZ = (int)sizeof(T);
+    constexpr bool WIDE = ESZ >= 4;
+    constexpr int A_WORDS = Tile<T>::A_WORDS, A_COLS = 64 * A_WORDS;
+    constexpr int UNITS = MMM_AB_ROWS * ESZ / 16;   // 16-byte units per column
     const bool has_keep = p.keep_a != nullptr;
     constexpr bool compact = ROWS;
     auto row_of = [&](int64_t bi, int t) -> int64_t { return bi * MMM_AB_ROWS + (WIDE ? wave + 16 * t : wave * 4 + t); };
@@ -135,18 +151,21 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
     // Every load below is unconditional (indices are clamped, results masked afterwards): a load inside a
     // branch is waited for before the next one is issued.
     // Addresses are a wave-uniform row base plus one 32-bit lane offset that all rows share.
-    const int64_t k_lo = bj * MMM_AB_COLS, w_lo = bj * A_WORDS;
-    const int tail = (int)min(p.K - k_lo, (int64_t)MMM_AB_COLS);   // columns of these blocks that exist
+    const int64_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;
+    const int tail = (int)min(p.K - k_lo, (int64_t)A_COLS);   // columns of these blocks that exist
     auto load = [&](int64_t bi, ABlock<T> &r) __attribute__((always_inline)) {
         if constexpr (WIDE) {
             r.kw = ~0ull;
-            if (has_keep) r.kw = p.keep_a[min(row_of(bi, (lane >> 1) & 3), p.M - 1) * p.WA + min(w_lo + (lane & 1), p.WA - 1)];
-            const uint32_t off0 = (uint32_t)min(lane, tail - 1) * 4u, off1 = (uint32_t)min(lane + 64, tail - 1) * 4u;
+            if (has_keep)
+                r.kw = p.keep_a[min(row_of(bi, (lane / A_WORDS) & 3), p.M - 1) * p.WA + min(w_lo + lane % A_WORDS, p.WA - 1)];
+            uint32_t off[A_WORDS];
+#pragma unroll
+            for (int h = 0; h < A_WORDS; ++h) off[h] = (uint32_t)min(lane + 64 * h, tail - 1) * (uint32_t)ESZ;
 #pragma unroll
             for (int t = 0; t < A_ROWS; ++t) {
                 const char *xr = reinterpret_cast<const char *>(static_cast<const T *>(p.X) + min(row_of(bi, t), p.M - 1) * p.ldx + k_lo);
-                r.x[t][0] = *reinterpret_cast<const uint32_t *>(xr + off0);
-                r.x[t][1] = *reinterpret_cast<const uint32_t *>(xr + off1);
+#pragma unroll
+                for (int h = 0; h < A_WORDS; ++h) r.x[t][h] = *reinterpret_cast<const pattern *>(xr + off[h]);
             }
         } else {
             // two neighbouring k per lane and load, at any 2-byte alignment; the last column of an odd K is read
@@ -169,7 +188,7 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
     ABlock<T> cur;
     load(bi0, cur);
     uint32_t base = (uint32_t)k_lo;   // image column of the blocks' first
-    int cols = MMM_AB_COLS;           // and how many there are
+    int cols = A_COLS;                // and how many there are
     if (compact) {   // the blocks' live columns, and how many live rows come before them
         uint32_t n = 0;
         for (int64_t w = threadIdx.x; w < w_lo; w += BUILD_THREADS) n += (uint32_t)__popcll(p.rows[w]);
@@ -189,7 +208,7 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
         char *const stage = sh.stage[st];
         uint64_t word[A_ROWS][A_WORDS];   // bitmap words (wave-uniform)
         // elements past the edge of X become +0, which is never kept
-        const bool edge = tail < MMM_AB_COLS || (bi + 1) * MMM_AB_ROWS > p.M;   // wave-uniform
+        const bool edge = tail < A_COLS || (bi + 1) * MMM_AB_ROWS > p.M;   // wave-uniform
         if constexpr (WIDE) {
             if (edge) {
 #pragma unroll
@@ -198,22 +217,29 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                     for (int h = 0; h < A_WORDS; ++h)
                         if (row_of(bi, t) >= p.M || 64 * h + lane >= tail) cur.x[t][h] = 0;
             }
-            uint32_t u[A_ROWS][A_WORDS];
+            pattern u[A_ROWS][A_WORDS];
+            const pattern lo1 = (pattern)p.test.lo1, len1 = (pattern)p.test.len1, lo2 = (pattern)p.test.lo2, len2 = (pattern)p.test.len2;
 #pragma unroll
             for (int t = 0; t < A_ROWS; ++t)
 #pragma unroll
                 for (int h = 0; h < A_WORDS; ++h) {
-                    const uint32_t x = cur.x[t][h], v = TEST == TEST_MAGNITUDE ? x & 0x7fffffffu : x;
-                    uint64_t m = ballot64(v - p.test.lo1 < p.test.len1);
-                    if (TEST == TEST_TWO_RANGES) m |= ballot64(v - p.test.lo2 < p.test.len2);
-                    if (has_keep) m &= readlane64(cur.kw, 2 * t + h);   // wave-uniform branch
+                    const pattern x = cur.x[t][h], v = TEST == TEST_MAGNITUDE ? x & Pattern<ESZ>::magnitude : x;
+                    uint64_t m = ballot64(v - lo1 < len1);
+                    if (TEST == TEST_TWO_RANGES) m |= ballot64(v - lo2 < len2);
+                    if (has_keep) m &= readlane64(cur.kw, t * A_WORDS + h);   // wave-uniform branch
                     word[t][h] = m;
-                    u[t][h] = __builtin_amdgcn_inverse_ballot_w64(m) ? x : 0u;   // the word is the lane mask of what stays
+                    u[t][h] = __builtin_amdgcn_inverse_ballot_w64(m) ? x : (pattern)0;   // the word is the lane mask of what stays
                 }
 #pragma unroll
             for (int h = 0; h < A_WORDS; ++h) {
                 const int k = 64 * h + lane;
-                *reinterpret_cast<uint4 *>(stage + k * 256 + ((wave ^ (k & 15)) << 4)) = make_uint4(u[0][h], u[1][h], u[2][h], u[3][h]);
+                char *at = stage + k * (UNITS * 16) + ((wave ^ (k & 15)) << 4);
+                if constexpr (ESZ == 4) {
+                    *reinterpret_cast<uint4 *>(at) = make_uint4(u[0][h], u[1][h], u[2][h], u[3][h]);
+                } else {
+                    *reinterpret_cast<ulong2 *>(at) = make_ulong2(u[0][h], u[1][h]);
+                    *reinterpret_cast<ulong2 *>(at + 256) = make_ulong2(u[2][h], u[3][h]);
+                }
             }
         } else {
             typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
@@ -251,25 +277,26 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
             *reinterpret_cast<uint2 *>(at) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u));
             *reinterpret_cast<uint2 *>(at + 128) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u));
         }
-        // bitmap words: lane 2t + h stores the word of (row t, half h)
+        // bitmap words: lane t * A_WORDS + h stores the word of (row t, half h)
         uint64_t mine = 0;
 #pragma unroll
         for (int t = 0; t < A_ROWS; ++t)
 #pragma unroll
-            for (int h = 0; h < A_WORDS; ++h) mine = __builtin_amdgcn_inverse_ballot_w64(1ull << (2 * t + h)) ? word[t][h] : mine;
+            for (int h = 0; h < A_WORDS; ++h) mine = __builtin_amdgcn_inverse_ballot_w64(1ull << (t * A_WORDS + h)) ? word[t][h] : mine;
         if (lane < 4) {   // column-any words of this wave's rows, by 32-row half of the block
             const int t32 = lane >> 1, h = lane & 1;
+            constexpr int H = A_WORDS - 1;   // h = 1 with one word: repeats it, not read
             uint64_t any;
             if (WIDE)
-                any = t32 ? (h ? word[2][1] | word[3][1] : word[2][0] | word[3][0]) : (h ? word[0][1] | word[1][1] : word[0][0] | word[1][0]);
+                any = t32 ? (h ? word[2][H] | word[3][H] : word[2][0] | word[3][0]) : (h ? word[0][H] | word[1][H] : word[0][0] | word[1][0]);
             else
                 any = t32 != wave / (BUILD_WAVES / 2) ? 0ull
-                    : h ? word[0][1] | word[1][1] | word[2][1] | word[3][1] : word[0][0] | word[1][0] | word[2][0] | word[3][0];
+                    : h ? word[0][H] | word[1][H] | word[2][H] | word[3][H] : word[0][0] | word[1][0] | word[2][0] | word[3][0];
             sh.any[st][wave][t32][h] = any;
         }
         if (bi + 1 < bi1) load(bi + 1, cur);
-        if (lane < 2 * A_ROWS && row_of(bi, lane >> 1) < p.M && w_lo + (lane & 1) < p.WA)
-            p.a_bits[row_of(bi, lane >> 1) * p.WA + w_lo + (lane & 1)] = mine;
+        if (lane < A_ROWS * A_WORDS && row_of(bi, lane / A_WORDS) < p.M && w_lo + lane % A_WORDS < p.WA)
+            p.a_bits[row_of(bi, lane / A_WORDS) * p.WA + w_lo + lane % A_WORDS] = mine;
         __syncthreads();
         if (wave == 0) {   // lane (t32, h, wave): OR over the sixteen waves
             const int t32 = lane >> 5, h = (lane >> 4) & 1;
@@ -281,7 +308,7 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                 hi |= (uint32_t)__shfl_xor((int)hi, d, 64);
             }
             const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
-            if ((lane & 15) == 0 && tile < p.MT && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
+            if ((lane & 15) == 0 && tile < p.MT && h < A_WORDS && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
         }
         // the image: column k (or k') of block row bi is one run of 64 elements
         if (compact && bi == bi0) {
@@ -291,27 +318,27 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
         char *img = p.a_img + ((size_t)bi * p.KBA * MMM_AB_COLS + base) * (UNITS * 16);
         auto stage_of = [&](int k, int unit, uint32_t col) -> int {   // where unit `unit` of image column `col` waits in the stage
             // (16-bit: undo the rotation of the stage, apply that of the image, see mmm_img_swizzle)
-            return WIDE ? k * 256 + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
+            return WIDE ? k * (UNITS * 16) + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
         };
         if (compact) {
             for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
                 const int j = q / UNITS, k = (int)sh.live[j];
                 *reinterpret_cast<uint4 *>(img + (uint32_t)q * 16u) = *reinterpret_cast<const uint4 *>(stage + stage_of(k, q % UNITS, base + j));
             }
-        } else {   // two (16-bit: one) units per thread, 64 columns apart
+        } else {   // two (16-bit: one) units per thread
             const int j = threadIdx.x / UNITS;
             const int at = stage_of(j, threadIdx.x % UNITS, (uint32_t)j);
 #pragma unroll
-            for (int i = 0; i < MMM_AB_COLS * UNITS / BUILD_THREADS; ++i)
+            for (int i = 0; i < A_COLS * UNITS / BUILD_THREADS; ++i)
                 *reinterpret_cast<uint4 *>(img + (threadIdx.x * 16u + (uint32_t)(i * BUILD_THREADS * 16))) =
                     *reinterpret_cast<const uint4 *>(stage + at + i * (BUILD_THREADS * 16));
         }
     }
 }
 
-// ---- B side: one workgroup = 128 rows (values of k) x 256 columns ----------------------------
-// A wave takes 8 rows; a lane owns four neighbouring columns of each, so that 4 lanes are one 16-column
-// group.  The 8 loads of a lane are in flight together; blocks the keep bitmaps switch off are given an
+// ---- B side: one workgroup = 128 rows (values of k) x 256 columns (doubles: twice 128) --------
+// A wave takes 8 rows; a lane owns four (two) neighbouring columns of each, so that 4 (8) lanes are one
+// 16-column group.  The 8 loads of a lane are in flight together; blocks the keep bitmaps switch off are given an
 // offset past the buffer's end, for which the hardware returns zero without touching memory.  The 128
 // occupancy bits of every lane's block are gathered in LDS, one byte per wave; from them follow the map
 // words, the transposed map words and the rank of every row within its group's segment, which is its
@@ -319,8 +346,8 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
 struct BShared {
     uint8_t gbits[64][BUILD_WAVES];   // [lane][wave]: rows in which the lane's 16-column group is occupied
     uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
-    uint16_t list[B_GROUPS][SEG];
-    uint16_t pack[B_GROUPS / 2][SEG * MMM_GROUP_COLS + 16];   // 16-bit types: half of the groups, packed (rows 8 banks apart)
+    uint16_t list[16][SEG];
+    uint16_t pack[8][SEG * MMM_GROUP_COLS + 16];   // 16-bit types: half of the groups, packed (rows 8 banks apart)
     int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
 };
@@ -380,21 +407,25 @@ template <int LPB> __device__ __forceinline__ uint32_t squeeze(uint64_t x)
         x = (x | x >> 12) & 0x000000ff000000ffull;
         return (uint32_t)((x | x >> 24) & 0xffffull);
     }
-    return (uint32_t)(((x & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
+    if (LPB == 8) return (uint32_t)(((x & 0x0101010101010101ull) * 0x0102040810204080ull) >> 56);
+    return (uint32_t)((x & 1u) | (x >> 15 & 2u) | (x >> 30 & 4u) | (x >> 45 & 8u));   // 16
 }
 
 // ROWS (row-compacted mode): the rows are the live rows k' = 128 seg .., and the transposed map is over k'.
-// Returns false where ROWS finds no live row in the segment.
+// Returns false where ROWS finds no live row in the segment.  carry: doubles in 32-wide blocks fill half a
+// byte of a map row per column tile, so the map bits of an even tile are handed to the odd one after it.
 template <typename T, int BW, bool ROWS>
-__device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int lane, int wave, BShared &sh)
+__device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_t ct, int lane, int wave, BShared &sh, uint32_t &carry)
 {
-    constexpr int LPB = BW / 4;                 // lanes per block
-    constexpr int BPW = B_COLS / BW;            // blocks per workgroup
     constexpr int ESZ = (int)sizeof(T);
-    constexpr bool WIDE = ESZ == 4;
-    constexpr uint64_t REP = LPB == 2 ? 0x5555555555555555ull : LPB == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;
-    constexpr uint64_t GREP = 0x1111111111111111ull;
-    const int64_t seg = bb / p.ctiles, ct = bb % p.ctiles;
+    constexpr int LANE_COLS = Tile<T>::LANE_COLS, B_COLS = Tile<T>::B_COLS, B_GROUPS = Tile<T>::B_GROUPS;
+    constexpr int LPB = BW / LANE_COLS;               // lanes per block
+    constexpr int LPG = MMM_GROUP_COLS / LANE_COLS;   // lanes per group
+    constexpr int BPW = B_COLS / BW;                  // blocks per column tile
+    constexpr bool WIDE = ESZ >= 4;
+    constexpr bool SPLIT = BW < MMM_GROUP_COLS;       // a group holds two blocks
+    constexpr uint64_t REP = LPB == 2 ? 0x5555555555555555ull : LPB == 4 ? 0x1111111111111111ull : LPB == 8 ? 0x0101010101010101ull : 0x0001000100010001ull;
+    constexpr uint64_t GREP = LPG == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;
     const int64_t col0 = ct * B_COLS, blk0 = ct * BPW;
     if (ROWS) {
         const uint32_t live = number_rows(p, seg, lane, wave, sh);
@@ -416,7 +447,8 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int la
         krow = k >= 0 && k < p.K ? k : -1;
         const int64_t kc = max(krow, (int64_t)0);
         uint64_t w = ~0ull;
-        if (p.keep_blocks != nullptr) w = p.keep_blocks[kc * p.WB + (blk0 >> 6)];   // wave-uniform branch
+        if (p.keep_blocks != nullptr) w = p.keep_blocks[kc * p.WB + (blk0 >> 6)];   // wave-uniform branches
+        if (ESZ == 8 && p.keep_rows != nullptr && !((p.keep_rows[kc >> 6] >> (kc & 63)) & 1ull)) w = 0;   // (not numbered)
         piece = krow >= 0 ? (uint32_t)(w >> (blk0 & 63)) : 0u;
     }
     u32x4 raw[B_ROWS];
@@ -427,7 +459,7 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int la
         const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)piece, j);
         const char *row = static_cast<const char *>(p.Y) + (k * p.ldy + col0) * ESZ;
         const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), 0, (int)nrec, 0x00020000);
-        const int off = (pj >> (lane / LPB)) & 1u ? lane * (4 * ESZ) : 0x40000000;
+        const int off = (pj >> (lane / LPB)) & 1u ? lane * (LANE_COLS * ESZ) : 0x40000000;
         if constexpr (WIDE) {
             raw[j] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
         } else if (!p.y_unaligned) {
@@ -444,39 +476,47 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int la
     uint64_t mine = 0;          // lane j: the occupied blocks of row j, at multiples of LPB
 #pragma unroll
     for (int j = 0; j < B_ROWS; ++j) {
-        const uint32_t nz = WIDE ? (raw[j].x | raw[j].y | raw[j].z | raw[j].w) & 0x7fffffffu : (raw[j].x | raw[j].y) & 0x7fff7fffu;
+        const uint32_t nz = ESZ == 8   ? raw[j].x | raw[j].z | ((raw[j].y | raw[j].w) & 0x7fffffffu)
+                          : ESZ == 4 ? (raw[j].x | raw[j].y | raw[j].z | raw[j].w) & 0x7fffffffu
+                                     : (raw[j].x | raw[j].y) & 0x7fff7fffu;
         uint64_t m = ballot64(nz != 0);
         m |= m >> 1;
         if (LPB >= 4) m |= m >> 2;
         if (LPB >= 8) m |= m >> 4;
+        if (LPB >= 16) m |= m >> 8;
         m &= REP;
         const uint64_t blocks = m * ((1u << LPB) - 1u);   // spread over the block's lanes
         uint64_t groups = blocks;
-        if (LPB == 2) groups = ((m | m >> 2) & GREP) * 15u;
+        if (SPLIT) groups = ((m | m >> LPB) & GREP) * ((1u << LPG) - 1u);
         gb |= __builtin_amdgcn_inverse_ballot_w64(groups) ? 1u << j : 0u;
-        if (LPB == 2) bbm |= __builtin_amdgcn_inverse_ballot_w64(blocks) ? 1u << j : 0u;
+        if (SPLIT) bbm |= __builtin_amdgcn_inverse_ballot_w64(blocks) ? 1u << j : 0u;
         mine = __builtin_amdgcn_inverse_ballot_w64(1ull << j) ? m : mine;
     }
     sh.gbits[lane][wave] = (uint8_t)gb;
-    if (LPB == 2) sh.bbits[lane][wave] = (uint8_t)bbm;
-    if (lane < B_ROWS && krow >= 0) {   // this workgroup's piece of the map row: 4, 2 or 1 bytes
-        const uint32_t v = squeeze<LPB>(mine);
+    if (SPLIT) sh.bbits[lane][wave] = (uint8_t)bbm;
+    if (lane < B_ROWS && krow >= 0) {   // this tile's piece of the map row: 4, 2, 1 or half a byte
+        uint32_t v = squeeze<LPB>(mine);
         char *dst = reinterpret_cast<char *>(p.b_bits + krow * p.WB) + blk0 / 8;
-        if (LPB == 2)
+        if (BPW == 32)
             *reinterpret_cast<uint32_t *>(dst) = v;
-        else if (LPB == 4)
+        else if (BPW == 16)
             *reinterpret_cast<uint16_t *>(dst) = (uint16_t)v;
-        else
+        else if (BPW == 8)
             *reinterpret_cast<uint8_t *>(dst) = (uint8_t)v;
+        else {
+            if (ct & 1) v = v << 4 | carry;
+            carry = v;
+            if ((ct & 1) != 0 || ct == p.ctiles - 1) *reinterpret_cast<uint8_t *>(dst) = (uint8_t)v;
+        }
         if (ct == p.ctiles - 1)   // pad bits of the row
-            for (int64_t q = (blk0 + BPW) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
+            for (int64_t q = (blk0 + BPW + 7) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
     }
     constexpr uint32_t ZERO_ENTRY = mmm_list_entry(sizeof(T), MMM_ZERO_COL);
-    reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
-    static_assert(B_GROUPS * SEG * 2 == BUILD_THREADS * 4, "one list word per thread");
+    static_assert(B_GROUPS * SEG * 2 <= BUILD_THREADS * 4, "at most one list word per thread");
+    if (threadIdx.x < B_GROUPS * SEG / 2) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
     __syncthreads();
     if (wave == 0 && (lane % LPB) == 0) {   // transposed map words of this lane's block
-        const uint64_t *t = reinterpret_cast<const uint64_t *>(LPB == 2 ? sh.bbits[lane] : sh.gbits[lane]);
+        const uint64_t *t = reinterpret_cast<const uint64_t *>(SPLIT ? sh.bbits[lane] : sh.gbits[lane]);
         const int64_t blk = blk0 + lane / LPB;
         if (blk < p.NB) {
             uint64_t *dst = (ROWS ? p.btc_bits : p.bt_bits) + blk * p.WA + seg * 2;
@@ -484,12 +524,13 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int la
             if (seg * 2 + 1 < p.WA) dst[1] = t[1];
         }
     }
+    if (ESZ == 8 && !p.pack) return true;
     const uint64_t *gt = reinterpret_cast<const uint64_t *>(sh.gbits[lane]);
     const uint64_t glo = gt[0], ghi = gt[1];
     const uint32_t n = (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi);   // rows of this lane's group
     const uint64_t below = (1ull << (8 * (wave & 7))) - 1ull;
     const uint32_t slot0 = wave < 8 ? (uint32_t)__popcll(glo & below) : (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi & below);
-    const int64_t G = ct * B_GROUPS + (lane >> 2);   // this lane's group
+    const int64_t G = ct * B_GROUPS + lane / LPG;   // this lane's group
     const bool group_ok = G < p.NG;
     uint32_t slots[B_ROWS];
     {
@@ -500,22 +541,23 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int la
             s += (gb >> j) & 1u;
         }
     }
-    if ((lane & 3) == 0) {
+    if (lane % LPG == 0) {
 #pragma unroll
         for (int j = 0; j < B_ROWS; ++j)
             if ((gb >> j) & 1u)
-                sh.list[lane >> 2][mmm_list_pos(sizeof(T), slots[j])] =
+                sh.list[lane / LPG][mmm_list_pos(sizeof(T), slots[j])] =
                     (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & 1u) * SEG + (uint32_t)(wave * B_ROWS + j));
         if (wave == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
     }
     char *val = p.bp_val + (size_t)(G * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);   // this lane's group
     if constexpr (WIDE) {
-        // slot-major rows of 64 bytes; the slots that fill up the last quad are zero
+        // slot-major rows of 64 (128) bytes; the slots that fill up the last quad are zero
+        constexpr int ROWB = MMM_GROUP_COLS * ESZ;
         if (group_ok) {
 #pragma unroll
             for (int j = 0; j < B_ROWS; ++j)
-                if ((gb >> j) & 1u) *reinterpret_cast<u32x4 *>(val + slots[j] * 64 + (lane & 3) * 16) = raw[j];
-            if (wave < 3 && n + wave < ((n + 3u) & ~3u)) *reinterpret_cast<u32x4 *>(val + (n + wave) * 64 + (lane & 3) * 16) = u32x4{0, 0, 0, 0};
+                if ((gb >> j) & 1u) *reinterpret_cast<u32x4 *>(val + slots[j] * ROWB + (lane % LPG) * 16) = raw[j];
+            if (wave < 3 && n + wave < ((n + 3u) & ~3u)) *reinterpret_cast<u32x4 *>(val + (n + wave) * ROWB + (lane % LPG) * 16) = u32x4{0, 0, 0, 0};
         }
         __syncthreads();
     } else {
@@ -554,7 +596,7 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, uint32_t bb, int la
     }
     {   // the lists, one word per thread
         const int64_t LG = ct * B_GROUPS + (threadIdx.x >> 6);
-        if (LG < p.NG)
+        if ((int)(threadIdx.x >> 6) < B_GROUPS && LG < p.NG)
             reinterpret_cast<uint32_t *>(p.bp_list + (LG * p.KBA + seg) * SEG)[lane] = reinterpret_cast<const uint32_t *>(sh.list)[threadIdx.x];
     }
     if (ROWS) __syncthreads();   // the shared arrays may be reused
@@ -575,6 +617,7 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
     const bool is_b = b < p.n_b_wg;
     const uint32_t i = is_b ? b : b - p.n_b_wg;
     if (is_b) {
+        uint32_t carry = 0;
         if (ROWS) {
             for (int64_t w = i; w < p.WA; w += p.n_b_wg) {   // zero map rows for the rows that are off
                 const uint64_t live = row_word(p.rows, w, p.K);
@@ -585,14 +628,24 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
             for (uint32_t bb = i; bb < p.n_b; bb += p.n_b_wg) {   // ends at the first segment without a live row
                 int l = lane;
                 asm volatile("" : "+v"(l));   // keeps what depends on the lane from being carried around the loop (it would spill)
-                if (!scan_b<T, BW, true>(p, bb, l, wave, sh.b)) break;
+                if (!scan_b<T, BW, true>(p, bb / p.ctiles, bb % p.ctiles, l, wave, sh.b, carry)) break;
             }
-        } else {
-            scan_b<T, BW, false>(p, i, lane, wave, sh.b);
+        } else if (sizeof(T) < 8) {
+            scan_b<T, BW, false>(p, i / p.ctiles, i % p.ctiles, lane, wave, sh.b, carry);
+        } else {   // two column tiles
+            const uint32_t pairs = (p.ctiles + 1) / 2;
+            const int64_t seg = i / pairs, ct = (int64_t)(i % pairs) * 2;
+            scan_b<T, BW, false>(p, seg, ct, lane, wave, sh.b, carry);
+            if (ct + 1 < p.ctiles) {
+                __syncthreads();
+                int l = lane;
+                asm volatile("" : "+v"(l));
+                scan_b<T, BW, false>(p, seg, ct + 1, l, wave, sh.b, carry);
+            }
         }
     } else {
-        const int64_t bi0 = (int64_t)(i / (uint32_t)p.KBA) * p.a_per_wg;
-        scan_a<T, TEST, ROWS>(p, i % (uint32_t)p.KBA, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+        const int64_t bi0 = (int64_t)(i / (uint32_t)p.a_units) * p.a_per_wg;
+        scan_a<T, TEST, ROWS>(p, i % (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
     }
 }
 
@@ -716,12 +769,12 @@ __global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, 
 
 // The ranges of bit patterns a predicate accepts.  `value` maps a magnitude pattern 0 .. inf of the element type to its
 // value, rising with the pattern.
-template <typename F> static ElementTest element_test(int32_t pred, float threshold, uint32_t inf, uint32_t sign, F value)
+template <typename F> static ElementTest element_test(int32_t pred, float threshold, uint64_t inf, uint64_t sign, F value)
 {
-    auto first = [&](auto &&is) -> uint32_t {   // smallest magnitude pattern for which `is` holds, inf + 1 if none
-        uint32_t lo = 0, hi = inf + 1;
+    auto first = [&](auto &&is) -> uint64_t {   // smallest magnitude pattern for which `is` holds, inf + 1 if none
+        uint64_t lo = 0, hi = inf + 1;
         while (lo < hi) {
-            const uint32_t mid = lo + (hi - lo) / 2;
+            const uint64_t mid = lo + (hi - lo) / 2;
             if (is(value(mid)))
                 hi = mid;
             else
@@ -729,14 +782,14 @@ template <typename F> static ElementTest element_test(int32_t pred, float thresh
         }
         return lo;
     };
-    const float t = threshold;
+    const double t = (double)threshold;
     ElementTest e{TEST_MAGNITUDE, 1, sign - 1, 0, 0};   // non-zero, NaN included
     if (pred == MMM_PRED_NONZERO) return e;
     e.mode = pred == MMM_PRED_GT ? TEST_ONE_RANGE : TEST_MAGNITUDE;
     e.len1 = 0;
     if (t != t) return e;   // NaN threshold: nothing passes
-    if (t >= 0.f) {         // -0 included
-        e.lo1 = first([&](float v) { return v > t; });
+    if (t >= 0.0) {         // -0 included
+        e.lo1 = first([&](double v) { return v > t; });
         e.len1 = inf + 1 - e.lo1;
     } else {                // every non-negative number; of the negative ones those smaller in magnitude
         e.lo1 = 1;
@@ -744,7 +797,7 @@ template <typename F> static ElementTest element_test(int32_t pred, float thresh
         if (pred == MMM_PRED_GT) {
             e.mode = TEST_TWO_RANGES;
             e.lo2 = sign + 1;
-            e.len2 = first([&](float v) { return v >= -t; }) - 1;
+            e.len2 = first([&](double v) { return v >= -t; }) - 1;
         }
     }
     return e;
@@ -752,15 +805,22 @@ template <typename F> static ElementTest element_test(int32_t pred, float thresh
 
 static ElementTest element_test(int32_t dtype, int32_t pred, float threshold)
 {
-    auto bits = [](uint32_t u) {
+    auto single = [](uint64_t v) {
+        const uint32_t u = (uint32_t)v;
         float f;
         std::memcpy(&f, &u, 4);
-        return f;
+        return (double)f;
     };
-    if (dtype == MMM_BF16) return element_test(pred, threshold, 0x7f80u, 0x8000u, [&](uint32_t v) { return bits(v << 16); });
+    if (dtype == MMM_BF16) return element_test(pred, threshold, 0x7f80u, 0x8000u, [&](uint64_t v) { return single(v << 16); });
     if (dtype == MMM_F16)
-        return element_test(pred, threshold, 0x7c00u, 0x8000u, [](uint32_t v) { return (float)__builtin_bit_cast(_Float16, (uint16_t)v); });
-    return element_test(pred, threshold, 0x7f800000u, 0x80000000u, bits);
+        return element_test(pred, threshold, 0x7c00u, 0x8000u, [](uint64_t v) { return (double)__builtin_bit_cast(_Float16, (uint16_t)v); });
+    if (dtype == MMM_F64)
+        return element_test(pred, threshold, 0x7ff0000000000000ull, 0x8000000000000000ull, [](uint64_t v) {
+            double d;
+            std::memcpy(&d, &v, 8);
+            return d;
+        });
+    return element_test(pred, threshold, 0x7f800000u, 0x80000000u, single);
 }
 
 typedef void (*build_kernel_fn)(const BuildParams);
@@ -781,7 +841,8 @@ template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int
 }
 static build_kernel_fn build_kernel(int32_t dtype, int32_t mode, int32_t bw, bool rows)
 {
-    return dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows)
+    return dtype == MMM_F64  ? build_kernel_test<double, false>(mode, bw)   // no row-compacted mode
+         : dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows)
          : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows)
                              : build_kernel_rows<float>(mode, bw, rows);
 }
@@ -794,10 +855,11 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.keep_a = a.keep_a;
     p.a_bits = m->a_bits;
     p.a_colany = m->a_colany;
-    p.a_img = m->a_img;
+    p.a_img = a.dtype == MMM_F64 ? m->a_img64 : m->a_img;
     p.Y = a.Y;
     p.ldy = a.ldy;
     p.keep_blocks = a.keep_blocks;
+    p.keep_rows = a.keep_rows;
     p.b_bits = m->b_bits;
     p.bt_bits = m->bt_bits;
     p.bp_val = m->bp_val;
@@ -813,17 +875,21 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.MBA = m->MBA;
     p.KBA = m->KBA;
     p.NG = m->NG;
+    p.pack = mmm_packs(m->M, a.dtype) ? 1 : 0;
     p.test = element_test(a.dtype, a.pred, a.threshold);
-    p.y_unaligned = a.dtype != MMM_F32 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
+    p.y_unaligned = a.dtype != MMM_F32 && a.dtype != MMM_F64 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
     p.kinfo = m->kinfo;
     p.kmap = m->kmap;
     p.btc_bits = m->btc_bits;
     p.rows_copy = m->rows_copy;
     // the numbering the A side follows: that of the B side built in this call, or of the cached one
     p.rows = a.b_compact ? a.keep_rows : a.a_compact ? m->rows_copy : nullptr;
-    p.ctiles = (uint32_t)((m->N + B_COLS - 1) / B_COLS);
-    const int64_t n_a = a.X ? m->MBA * m->KBA : 0;
-    const int64_t n_b = a.Y ? m->KBA * p.ctiles : 0;
+    const bool f64 = a.dtype == MMM_F64;
+    const int64_t b_cols = f64 ? Tile<double>::B_COLS : Tile<float>::B_COLS;
+    p.ctiles = (uint32_t)((m->N + b_cols - 1) / b_cols);
+    p.a_units = f64 ? m->WA : m->KBA;
+    const int64_t n_a = a.X ? m->MBA * p.a_units : 0;
+    const int64_t n_b = a.Y ? m->KBA * (f64 ? (p.ctiles + 1) / 2 : p.ctiles) : 0;
     // Row-compacted B: how many segments have a live row is known on the device only; at most one workgroup per CU loops
     // over them.
     const int64_t n_b_wg = a.b_compact && n_b > 256 ? 256 : n_b;
@@ -833,7 +899,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     int64_t per_wg = n_a / 512;
     per_wg = per_wg < 1 ? 1 : per_wg > 8 ? 8 : per_wg;
     if (per_wg > m->MBA) per_wg = m->MBA;
-    const int64_t n_a_wg = a.X ? (m->MBA + per_wg - 1) / per_wg * m->KBA : 0;
+    const int64_t n_a_wg = a.X ? (m->MBA + per_wg - 1) / per_wg * p.a_units : 0;
     const int64_t n_all = n_a_wg + n_b_wg;
     if (n_all <= 0 || n_a > 0x7fffffffLL || n_b > 0x7fffffffLL || n_all > 0x7fffffffLL) return hipErrorInvalidValue;
     p.n_b = (uint32_t)n_b;

@@ -27,29 +27,31 @@ constexpr uint32_t MMM_SLAB_SPARE = mmm_slab_pos(0, MMM_AB_COLS);
 // Image of A: [row block of 64][k, padded to whole blocks][64 rows], element type of X, zeros where the
 // mask drops an element.  4-byte elements: the rows r, r+16, r+32, r+48 of a column are neighbours, so that
 // one 16-byte LDS read yields the operands of all four 16-row tiles for one k, and the 16 lanes of an
-// operand read 256 contiguous bytes.  16-bit elements: natural order, as the transposing LDS read needs;
+// operand read 256 contiguous bytes.  8-byte elements: the same in two halves of a column, rows r, r+16 at
+// 16 r and rows r+32, r+48 at 256 + 16 r.  16-bit elements: natural order, as the transposing LDS read needs;
 // the column's 16-byte units are rotated with k (xor), so that the columns k .. k+7 of one row tile lie in
 // different LDS banks.
 __host__ __device__ constexpr uint32_t mmm_img_swizzle(uint32_t col) { return ((col >> 1) & 3u) << 1; }
 __host__ __device__ constexpr uint32_t mmm_img_row(size_t esz, uint32_t col, uint32_t row)   // byte offset inside a column
 {
-    return esz == 4 ? (row & 15u) * 16u + (row >> 4) * 4u : (((row >> 3) ^ mmm_img_swizzle(col)) << 4) + (row & 7u) * 2u;
+    return esz == 8   ? (row >> 5) * 256u + (row & 15u) * 16u + ((row >> 4) & 1u) * 8u
+           : esz == 4 ? (row & 15u) * 16u + (row >> 4) * 4u : (((row >> 3) ^ mmm_img_swizzle(col)) << 4) + (row & 7u) * 2u;
 }
 // Packed B: per group of 16 columns and segment of 128 k the occupied rows, one after another ("slots"),
 // at [group][segment][128 slots][16 columns]; the number of slots; and per slot where its column of A
-// sits in the kernel's LDS ring of two blocks: column 128 * (segment & 1) + k, in units of the column
-// size (4-byte elements) or of 16 bytes with the rotation folded in (16-bit elements).  Slots past the
-// last name the ring's zero column.  The order of the list is the one in which a lane reads it: 4-byte
+// sits in the kernel's LDS ring of two blocks: column 128 * (segment & 1) + k, in units of 256 bytes (4- and
+// 8-byte elements) or of 16 bytes with the rotation folded in (16-bit elements).  Slots past the
+// last name the ring's zero column.  The order of the list is the one in which a lane reads it: 4- and 8-byte
 // elements take slots 4u + s (u = 0..3) of every 16, 16-bit elements slot lane / 4.
 constexpr int MMM_GROUP_COLS = 16;
 constexpr uint32_t MMM_ZERO_COL = 2 * MMM_AB_COLS;
 __host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
 {
-    return esz == 4 ? col : (col << 3) | (col == MMM_ZERO_COL ? 0u : mmm_img_swizzle(col));
+    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3) | (col == MMM_ZERO_COL ? 0u : mmm_img_swizzle(col));
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
 {
-    return esz == 4 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : slot;
+    return esz >= 4 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : slot;
 }
 struct mmm_maps {
     int64_t M, K, N;
@@ -67,6 +69,7 @@ struct mmm_maps {
     uint32_t *a_cnt;   // [MBA][KBA] non-zeros per block            (inspection: written by mmm_launch_lists)
     uint64_t *a_ent;   // [MBA*KBA][MMM_AB_CAP] entries {mmm_slab_pos(row, column), value bits}, padded to a
                        // multiple of 64 with {spare cell, 0}       (inspection)
+    char *a_img64;     // image of A for double inputs, which have no lists: takes the place of a_ent
     uint64_t *b_bits;
     uint64_t *bt_bits;
     uint64_t *stats;   // 4 words
@@ -133,9 +136,9 @@ struct mmm_variant_info {
 };
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
-// double-precision inputs: bitmaps, column-any words and the transposed map only (no lists)
-hipError_t mmm_launch_build64(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
-uint64_t mmm_threshold_key64(int32_t pred, float threshold);
+// Whether B is packed (and the matrix kernel can run): always but for double inputs of so few rows that the pair kernel
+// is what runs, for which the workspace has no room.
+inline bool mmm_packs(int64_t M, int32_t dtype) { return dtype != MMM_F64 || M > 64; }
 hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s);
 // forms that only inspection reads: column-any words over k'; counts and lists of the blocks of A
 hipError_t mmm_launch_colany_compact(const mmm_maps *m, hipStream_t s);
@@ -145,7 +148,7 @@ hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s);
 int32_t mmm_variant_count();
 const mmm_variant_info &mmm_variant(int32_t i);
 // partials / partial_bytes: where the split-K partial sums go (used only when p.split_k > 1)
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, float *C, int64_t ldc, int32_t accumulate, float *partials,
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, void *C, int64_t ldc, int32_t accumulate, void *partials,
                              size_t partial_bytes, hipStream_t s);
 // The multiplication over exactly the surviving products, on the vector ALUs.  fused: evaluate M
 // (pred, threshold, keep_a) on X inside the kernel; otherwise a_bits of the maps are used.

@@ -41,9 +41,9 @@ constexpr int TM = MMM_AB_ROWS;   // rows of C per workgroup = rows of a block o
 constexpr int KC = MMM_AB_COLS;   // k per step = columns of a block of A
 
 struct MatmulParams {
-    float *C;
+    void *C;    // float, or double for double inputs
     int64_t ldc;
-    float *P;   // split-K partial sums, [split][M][N]
+    void *P;    // split-K partial sums, [split][M][N], of C's type
     const char *a_img;
     const char *bp_val;
     const uint16_t *bp_list;
@@ -53,6 +53,12 @@ struct MatmulParams {
     int32_t tiles_n, split_k, chunks_total, chunks_per_split;
     int32_t accumulate;
 };
+
+typedef double doublex2 __attribute__((ext_vector_type(2)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+// accumulators of one 16 x 16 tile, and of C
+template <typename T> struct Acc { typedef floatx4 tile; typedef float element; };
+template <> struct Acc<double> { typedef doublex4 tile; typedef double element; };
 
 // 16-bit inputs are contracted by the matrix instructions of their own type (fp32 accumulate).
 template <typename T> struct Mfma16;
@@ -106,10 +112,12 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 // GW  16-column groups per wave (2: bw = 32, the two groups of a block share their list), NW waves per
 //     workgroup: TN = 16*GW*NW columns
 template <int RT, int GW, int NW, typename T>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void mmm_matmul_kernel(const MatmulParams p)
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
-    constexpr bool WIDE = sizeof(T) == 4;
+    constexpr bool WIDE = sizeof(T) >= 4, F64 = sizeof(T) == 8;
     constexpr int ESZ = (int)sizeof(T);
+    typedef typename Acc<T>::tile tile_t;
+    typedef typename Acc<T>::element elem_t;
     constexpr int COLB = TM * ESZ;                  // bytes per LDS column
     constexpr int SLAB = KC * COLB;                 // bytes per block of A
     constexpr int ZERO_AT = 2 * SLAB;               // the ring's zero column (MMM_ZERO_COL)
@@ -118,7 +126,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     constexpr int OPS = WIDE ? 4 * GW + 1 : 2 * GW + 2;   // vector-memory operations issue() makes
     constexpr int SEGB = KC * MMM_GROUP_COLS * ESZ;       // bytes of a packed segment
     static_assert(DMA * NW * 1024 == SLAB, "whole copies");
-    typedef float avec __attribute__((ext_vector_type(RT)));   // fp32: A operands of the RT row tiles for one k
+    typedef elem_t avec __attribute__((ext_vector_type(RT)));   // 4- and 8-byte types: A operands of the RT row tiles for one k
 
     __shared__ __align__(1024) char ring[2 * SLAB + COLB];
 
@@ -145,11 +153,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     const int chunk_begin = min(split * per_split, chunks_live);
     const int chunk_end = min(chunk_begin + per_split, chunks_live);
 
-    floatx4 acc[GW][RT];
+    tile_t acc[GW][RT];
 #pragma unroll
     for (int g = 0; g < GW; ++g)
 #pragma unroll
-        for (int r = 0; r < RT; ++r) acc[g][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int r = 0; r < RT; ++r) acc[g][r] = tile_t{0, 0, 0, 0};
 
     // this wave's groups; a wave past the last column walks the last group's addresses and multiplies nothing
     const int64_t G0 = ((int64_t)tile_n * NW + wave) * GW;
@@ -189,9 +197,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 
     // ---- B: one batch of a group's list in registers
     struct Batch {
-        float bf[WIDE ? GW : 1][4];     // fp32: slot 4u + s of column c, u = 0..3
+        elem_t bf[WIDE ? GW : 1][4];    // 4- and 8-byte types: slot 4u + s of column c, u = 0..3
         u32x2 bh[WIDE ? 1 : GW][2];     // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
-        u32x2 list;                     // fp32: ring columns of those four slots (16 bits each)
+        u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
         uint32_t entry[2];              // 16-bit: ring position of slot lane / 4 of both halves
         int left;                       // live slots from the batch's first on; -1: past the end
         bool first;                     // first batch of its step
@@ -210,8 +218,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 #pragma unroll
             for (int g = 0; g < GW; ++g)
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    b.bf[g][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(val_rsrc, lane * 4 + u * 256, is_v + g * val_next, 0));
+                for (int u = 0; u < 4; ++u) {
+                    if constexpr (F64)
+                        b.bf[g][u] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(val_rsrc, lane * 8 + u * 512, is_v + g * val_next, 0));
+                    else
+                        b.bf[g][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(val_rsrc, lane * 4 + u * 256, is_v + g * val_next, 0));
+                }
         } else {
 #pragma unroll
             for (int h = 0; h < 2; ++h) b.entry[h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(list_rsrc, (lane >> 2) * 2 + h * 32, is_l, 0);
@@ -238,18 +250,38 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     const uint32_t chunk8 = (uint32_t)(lane & 3) * 8u;
     auto multiply = [&](const Batch &b) __attribute__((always_inline)) {
         if constexpr (WIDE) {
-            // ring address of a column: entry * 256 + 16 c, put together from bytes
+            // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
+            // entries count in 256)
             const uint32_t at[4] = {__builtin_amdgcn_perm(b.list.x, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.x, c16, 0x0c070600u),
                                     __builtin_amdgcn_perm(b.list.y, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.y, c16, 0x0c070600u)};
             avec a[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = *reinterpret_cast<const __attribute__((address_space(3))) avec *>(ring3 + at[u]);
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (F64) {
+                    typedef const __attribute__((address_space(3))) doublex2 lds_doublex2;
+                    const doublex2 lo = *(lds_doublex2 *)(ring3 + at[u]);
+                    a[u][0] = lo.x;
+                    a[u][1] = lo.y;
+                    if constexpr (RT == 4) {
+                        const doublex2 hi = *(lds_doublex2 *)(ring3 + at[u] + 256);
+                        a[u][2] = hi.x;
+                        a[u][3] = hi.y;
+                    }
+                } else {
+                    a[u] = *reinterpret_cast<const __attribute__((address_space(3))) avec *>(ring3 + at[u]);
+                }
+            }
             asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));   // all four requested before the first is used
             auto quad = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
                 for (int g = 0; g < GW; ++g)
 #pragma unroll
-                    for (int r = 0; r < RT; ++r) acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
+                    for (int r = 0; r < RT; ++r) {
+                        if constexpr (F64)
+                            acc[g][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
+                        else
+                            acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
+                    }
             };
             quad(0);
             if (b.left > 4) {
@@ -330,16 +362,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
     __syncthreads();   // the ring is free: the epilogue reuses it
 
     // ---- write C (or this split's partial sums): every element exactly once.
-    // Accumulator layout of the 16x16 MFMA: lane holds rows 4*s + v (v = 0..3) of column c.
+    // Accumulator layout of the 16x16 MFMA: lane holds rows 4*s + v (v = 0..3) of column c; doubles: rows s + 4*v.
     // Each wave lays 16 columns of its tile out row-major in its own piece of the (now free) ring, a few row tiles at a
     // time, then stores 64-byte row pieces with 16-byte lanes.
-    float *out = p.split_k > 1 ? p.P + (int64_t)split * p.M * p.N : p.C;
+    // (A row of doubles is 128 bytes in 16 lanes as it is.)
+    elem_t *out = p.split_k > 1 ? static_cast<elem_t *>(p.P) + (int64_t)split * p.M * p.N : static_cast<elem_t *>(p.C);
     const int64_t ldo = p.split_k > 1 ? p.N : p.ldc;
     const bool add = p.split_k == 1 && p.accumulate;
     constexpr int PIECE = 2 * SLAB / NW;   // bytes of the ring per wave
     constexpr int RP = PIECE / 1024 < RT ? PIECE / 1024 : RT;   // row tiles (1 KiB each) laid out at a time
     static_assert(RP >= 1 && RT % RP == 0, "whole passes");
-    const bool vec_ok = reinterpret_cast<uintptr_t>(out) % 16 == 0 && ldo % 4 == 0;
+    const bool vec_ok = !F64 && reinterpret_cast<uintptr_t>(out) % 16 == 0 && ldo % 4 == 0;
 #pragma unroll
     for (int g = 0; g < GW; ++g) {
         const int64_t col0 = (G0 + g) * 16;
@@ -352,7 +385,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 #pragma unroll
                 for (int r = 0; r < RP; ++r)
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) mine[(r * 16 + s * 4 + v) * 16 + c] = acc[g][r0 + r][v];
+                    for (int v = 0; v < 4; ++v) mine[(r * 16 + s * 4 + v) * 16 + c] = (float)acc[g][r0 + r][v];
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -360,7 +393,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
                     const int64_t row = row0 + (r0 + r) * 16 + (lane >> 2);
                     if (row < p.M) {
                         floatx4 val = *reinterpret_cast<const floatx4 *>(&mine[(r * 16 + (lane >> 2)) * 16 + 4 * (lane & 3)]);
-                        floatx4 *dst = reinterpret_cast<floatx4 *>(out + row * ldo + col0 + 4 * (lane & 3));
+                        floatx4 *dst = reinterpret_cast<floatx4 *>(reinterpret_cast<float *>(out) + row * ldo + col0 + 4 * (lane & 3));
                         if (add) val += *dst;
                         *dst = val;
                     }
@@ -373,9 +406,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
             for (int r = 0; r < RT; ++r) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int64_t row = row0 + r * 16 + s * 4 + v;
+                    const int64_t row = row0 + r * 16 + (F64 ? s + 4 * v : s * 4 + v);
                     if (row >= p.M) continue;
-                    float *dst = out + row * ldo + col;
+                    elem_t *dst = out + row * ldo + col;
                     *dst = add ? *dst + acc[g][r][v] : acc[g][r][v];
                 }
             }
@@ -385,15 +418,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
 
 // Sum of the split-K partials in a fixed order (split 0, 1, ...), so the result
 // does not depend on the order in which workgroups finish.
-__global__ __launch_bounds__(256) void mmm_splitk_reduce_kernel(const float *P, float *C, int64_t ldc, int64_t M,
+template <typename E>
+__global__ __launch_bounds__(256) void mmm_splitk_reduce_kernel(const E *P, E *C, int64_t ldc, int64_t M,
                                                                 int64_t N, int32_t splits, int32_t accumulate)
 {
     const int64_t total = M * N;
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         const int64_t row = e / N, col = e % N;
-        float sum = P[e];
+        E sum = P[e];
         for (int sp = 1; sp < splits; ++sp) sum += P[(int64_t)sp * total + e];
-        float *dst = C + row * ldc + col;
+        E *dst = C + row * ldc + col;
         *dst = accumulate ? *dst + sum : sum;
     }
 }
@@ -403,14 +437,16 @@ typedef void (*matmul_kernel_fn)(const MatmulParams);
 struct VariantEntry {
     mmm_variant_info info;
     int32_t waves;              // of 16 columns each; 32-wide blocks: half as many waves of 32 columns
-    matmul_kernel_fn fn[2][3];  // [bw == 32][f32, bf16, f16]
+    matmul_kernel_fn fn[2][4];  // [bw == 32][element type]
 };
 
 #define MMM_VARIANT(RT, NW)                                                                                              \
     {                                                                                                                    \
         {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT}, NW,                                                       \
-            {{mmm_matmul_kernel<RT, 1, NW, float>, mmm_matmul_kernel<RT, 1, NW, uint16_t>, mmm_matmul_kernel<RT, 1, NW, _Float16>}, \
-             {mmm_matmul_kernel<RT, 2, NW / 2, float>, mmm_matmul_kernel<RT, 2, NW / 2, uint16_t>, mmm_matmul_kernel<RT, 2, NW / 2, _Float16>}} \
+            {{mmm_matmul_kernel<RT, 1, NW, float>, mmm_matmul_kernel<RT, 1, NW, uint16_t>, mmm_matmul_kernel<RT, 1, NW, _Float16>,  \
+              mmm_matmul_kernel<RT, 1, NW, double>},                                                                       \
+             {mmm_matmul_kernel<RT, 2, NW / 2, float>, mmm_matmul_kernel<RT, 2, NW / 2, uint16_t>,                          \
+              mmm_matmul_kernel<RT, 2, NW / 2, _Float16>, mmm_matmul_kernel<RT, 2, NW / 2, double>}}                        \
     }
 
 const VariantEntry g_variants[] = {
@@ -455,17 +491,18 @@ hipError_t mmm_static_scratch(float **ptr)
 int32_t mmm_variant_count() { return kVariants; }
 const mmm_variant_info &mmm_variant(int32_t i) { return g_variants[i].info; }
 
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtype, float *C, int64_t ldc, int32_t accumulate,
-                             float *partials, size_t partial_bytes, hipStream_t s)
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtype, void *C, int64_t ldc, int32_t accumulate,
+                             void *partials, size_t partial_bytes, hipStream_t s)
 {
     if (pl.variant < 0 || pl.variant >= kVariants) return hipErrorInvalidValue;
     const VariantEntry &v = g_variants[pl.variant];
-    if (m->M > v.info.rows && v.info.rows < TM) return hipErrorInvalidValue;
+    if ((m->M > v.info.rows && v.info.rows < TM) || !mmm_packs(m->M, dtype)) return hipErrorInvalidValue;
+    const bool f64 = dtype == MMM_F64;
     MatmulParams p{};
     p.C = C;
     p.ldc = ldc;
     p.P = partials;
-    p.a_img = m->a_img;
+    p.a_img = f64 ? m->a_img64 : m->a_img;
     p.bp_val = m->bp_val;
     p.bp_list = m->bp_list;
     p.bp_cnt = m->bp_cnt;
@@ -480,10 +517,10 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     p.chunks_per_split = pl.chunks_per_split;
     p.accumulate = accumulate;
     if (pl.workgroups <= 0 || pl.workgroups > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (pl.split_k > 1 && (size_t)pl.split_k * (size_t)m->M * (size_t)m->N * sizeof(float) > partial_bytes)
+    if (pl.split_k > 1 && (size_t)pl.split_k * (size_t)m->M * (size_t)m->N * (f64 ? sizeof(double) : sizeof(float)) > partial_bytes)
         return hipErrorInvalidValue;
     const int wide = m->bw == 32 ? 1 : 0;
-    matmul_kernel_fn fn = v.fn[wide][dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
+    matmul_kernel_fn fn = v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
     (void)hipGetLastError();   // drop any stale error another library left on this thread
     hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.waves >> wide) * 64), 0, s, p);
     hipError_t e = hipGetLastError();
@@ -492,8 +529,12 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
         const int64_t total = m->M * m->N;
         int64_t blocks = (total + 255) / 256;
         if (blocks > 4096) blocks = 4096;
-        hipLaunchKernelGGL(mmm_splitk_reduce_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, partials, C, ldc,
-                           m->M, m->N, pl.split_k, accumulate);
+        if (f64)
+            hipLaunchKernelGGL(mmm_splitk_reduce_kernel<double>, dim3((uint32_t)blocks), dim3(256), 0, s, static_cast<const double *>(partials),
+                               static_cast<double *>(C), ldc, m->M, m->N, pl.split_k, accumulate);
+        else
+            hipLaunchKernelGGL(mmm_splitk_reduce_kernel<float>, dim3((uint32_t)blocks), dim3(256), 0, s, static_cast<const float *>(partials),
+                               static_cast<float *>(C), ldc, m->M, m->N, pl.split_k, accumulate);
         e = hipGetLastError();
     }
     return e;

@@ -349,6 +349,21 @@ uint32_t pairs_threshold_key(int32_t pred, float threshold)
     return 0;
 }
 
+uint64_t pairs_threshold_key64(int32_t pred, float threshold)
+{
+    union { double f; uint64_t u; } cv;
+    cv.f = (double)threshold;
+    uint64_t t = cv.u;
+    const uint64_t at = t & 0x7fffffffffffffffull;
+    if (at > 0x7ff0000000000000ull) return ~0ull;   // NaN threshold: nothing passes
+    if (pred == MMM_PRED_GT) {
+        if (at == 0) t = 0;
+        return (t & 0x8000000000000000ull) ? ~t : (t | 0x8000000000000000ull);
+    }
+    if (pred == MMM_PRED_ABS_GT) return (t & 0x8000000000000000ull) ? 0ull : at;
+    return 0;
+}
+
 }   // namespace
 
 bool mmm_pairs_supports(int32_t dtype, int64_t ldy)
@@ -378,7 +393,7 @@ hipError_t mmm_launch_pairs(const mmm_maps *m, int32_t dtype, const void *X, int
     p.NB = m->NB;
     p.WA = m->WA;
     p.pred = pred;
-    p.thr_bits = dtype == MMM_F64 ? mmm_threshold_key64(pred, threshold) : (uint64_t)pairs_threshold_key(pred, threshold);
+    p.thr_bits = dtype == MMM_F64 ? pairs_threshold_key64(pred, threshold) : (uint64_t)pairs_threshold_key(pred, threshold);
     p.accumulate = accumulate;
     // Workgroups of 8 waves x 64 columns; when that gives the machine too little to do (few rows:
     // the decode shape), fewer columns per workgroup and K shared out over several waves.

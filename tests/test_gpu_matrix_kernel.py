@@ -1,0 +1,101 @@
+"""The matrix kernel's operands at the edges of their geometry: blocks of A of 64 rows x 128 columns (64 for doubles in
+the builder), groups of 16 columns, segments of 128 k whose lists are walked in batches of 16 or 32 slots, column tiles of
+256 (128).  Exact on integer inputs, against the CPU oracle, for every element type."""
+import numpy as np
+import pytest
+import torch
+
+import mmm_synth as synth
+import oracle
+import paper_2402_14118_amd as mm
+from hip_harness import HipRun
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = [synth.DT_F32, synth.DT_BF16, synth.DT_F16, synth.DT_F64]
+IDS = ["f32", "bf16", "f16", "f64"]
+
+
+def _run(w, split=1, variant=-1, **ld):
+    ab, bb, C_ref, _ = oracle.run_workload(w)
+    run = HipRun(w, **ld)
+    run.eng.set_path(mm.MMM_PATH_MATRIX)
+    run.eng.set_plan(variant, split)
+    a, b, C = run.run()
+    assert run.eng.path() == mm.MMM_PATH_MATRIX
+    np.testing.assert_array_equal(a, ab)
+    np.testing.assert_array_equal(b, bb)
+    np.testing.assert_array_equal(C, C_ref)
+    return run, C_ref
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("M,K,N,bw", [
+    (65, 1, 8, 8),            # one k; half a column group
+    (65, 2, 136, 8),          # half a group behind whole ones, across a column tile of 128
+    (128, 64, 16, 16), (128, 65, 272, 16), (129, 127, 256, 16), (129, 128, 288, 32), (66, 129, 264, 8),
+    (190, 257, 544, 32),      # three segments, the ring reused; three column tiles of 256
+    (70, 1030, 48, 16),       # nine segments
+])
+def test_edges(M, K, N, bw, dtype):
+    w = synth.random_masked(M, K, N, bw, 0.4, 0.4, 31 * M + K + N, dist="smallint", dtype=dtype)
+    _run(w)
+    print("split", M, K, N, bw, flush=True)
+    _run(w, split=3)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_list_lengths(bw, dtype):
+    """Segments whose lists have every length around the batch and quad sizes: segment s of column group g holds
+    lengths[(s + g) % len] occupied rows; the rest of B is switched off and holds values that would show."""
+    lengths = [0, 1, 3, 4, 5, 15, 16, 17, 31, 32, 33, 127, 128, 0, 64]
+    M, segs, N = 80, 16, 128
+    K, NB = segs * 128, N // bw
+    keep = np.zeros((K, NB), bool)
+    rng = np.random.default_rng(bw)
+    for s in range(segs):
+        for b in range(NB):
+            n = lengths[(s + b * bw // max(16, bw)) % len(lengths)]
+            keep[s * 128 + rng.permutation(128)[:n], b] = True
+    w = synth.random_masked(M, K, N, bw, 0.5, 1.0, 77 + bw, dist="smallint", dtype=dtype)
+    w.keep_blocks = synth.pack_bits(keep)
+    _run(w)
+    _run(w, split=4)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+def test_every_variant_and_row_count(dtype):
+    for variant in range(mm.mmm_matmul_variant_count()):
+        short = mm.mmm_matmul_variant_name(variant).startswith("R2")
+        if short and dtype == synth.DT_F64:
+            continue      # doubles of so few rows take the pair kernel
+        for M in ((17, 32) if short else (65, 191)):
+            for bw in (16, 32):
+                print("variant", variant, M, bw, flush=True)
+                _run(synth.random_masked(M, 300, 544, bw, 0.3, 0.5, variant * 10 + M, dist="smallint", dtype=dtype), variant=variant)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+def test_leading_dimensions_and_accumulate(dtype):
+    """Odd leading dimensions put the rows of 16-bit matrices on 2-byte boundaries."""
+    w = synth.random_masked(100, 333, 80, 16, 0.4, 0.5, 5, dist="smallint", dtype=dtype, p_rows=0.6)
+    run, C_ref = _run(w, ldx=335, ldy=83, ldc=91)
+    run.eng.matmul(run.X, run.Y, run.C, accumulate=True)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(run.C.cpu().numpy(), 2 * C_ref)
+    assert torch.isnan(run.Cbuf[:, 80:]).all()
+
+
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16, synth.DT_F64], ids=["f32", "bf16", "f64"])
+def test_values_that_must_not_reach_the_arithmetic(dtype):
+    """NaN and Inf where the masks drop them, at the ragged edges of every tile."""
+    w = synth.random_masked(97, 200, 136, 8, 0.3, 0.3, 6, dist="smallint", dtype=dtype)
+    C_ref = oracle.run_workload(w)[2]
+    w.X = np.where(synth.unpack_bits(w.keep_a, w.K), w.X, np.nan).astype(w.X.dtype)
+    w.Y = np.where(np.repeat(synth.unpack_bits(w.keep_blocks, w.NB), w.bw, axis=1), w.Y, np.inf).astype(w.Y.dtype)
+    if dtype == synth.DT_BF16:
+        w.X_bits, w.Y_bits = synth.round_to_bf16(w.X)[0], synth.round_to_bf16(w.Y)[0]
+    run = HipRun(w)
+    run.eng.set_path(mm.MMM_PATH_MATRIX)
+    np.testing.assert_array_equal(run.run()[2], C_ref)
