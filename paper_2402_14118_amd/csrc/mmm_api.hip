@@ -102,6 +102,7 @@ mmm_plan make_plan(const mmm_maps *m, int32_t dt)
     int64_t v = m->plan_variant >= 0 ? m->plan_variant : g_opt_variant.load();
     if (v >= 0 && v < mmm_variant_count() && mmm_variant((int32_t)v).rows < MMM_AB_ROWS && m->M > mmm_variant((int32_t)v).rows)
         v = -1;   // that kernel computes too few rows for this matrix
+    if (v >= 0 && v < mmm_variant_count() && dt == MMM_F64 && mmm_variant((int32_t)v).k_ranges > 1) v = -1;   // no room for two rings of doubles
     if (v < 0 || v >= mmm_variant_count()) {
         // automatic: the shapes that put sixteen waves on a compute unit.  32-row kernel for short
         // matrices; otherwise the 256-column tile (one workgroup of sixteen waves per CU) when that

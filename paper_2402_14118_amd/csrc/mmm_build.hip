@@ -17,6 +17,7 @@
 // global atomics are used and nothing needs clearing beforehand.
 #include "mmm_internal.h"
 #include <cstring>
+#include <type_traits>
 
 namespace {
 
@@ -347,7 +348,7 @@ struct BShared {
     uint8_t gbits[64][BUILD_WAVES];   // [lane][wave]: rows in which the lane's 16-column group is occupied
     uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
     uint16_t list[16][SEG];
-    uint16_t pack[8][SEG * MMM_GROUP_COLS + 16];   // 16-bit types: half of the groups, packed (rows 8 banks apart)
+    char pack[16 * (SEG * MMM_GROUP_COLS * 2 + 16)];   // 16-bit types: the packed groups
     int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
 };
@@ -511,7 +512,8 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
         if (ct == p.ctiles - 1)   // pad bits of the row
             for (int64_t q = (blk0 + BPW + 7) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
     }
-    constexpr uint32_t ZERO_ENTRY = mmm_list_entry(sizeof(T), MMM_ZERO_COL);
+    constexpr int RING = mmm_ring(sizeof(T));
+    constexpr uint32_t ZERO_ENTRY = mmm_list_entry(sizeof(T), mmm_zero_col(RING));
     static_assert(B_GROUPS * SEG * 2 <= BUILD_THREADS * 4, "at most one list word per thread");
     if (threadIdx.x < B_GROUPS * SEG / 2) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
     __syncthreads();
@@ -546,12 +548,12 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
         for (int j = 0; j < B_ROWS; ++j)
             if ((gb >> j) & 1u)
                 sh.list[lane / LPG][mmm_list_pos(sizeof(T), slots[j])] =
-                    (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & 1u) * SEG + (uint32_t)(wave * B_ROWS + j));
+                    (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & (RING - 1u)) * SEG + (uint32_t)(wave * B_ROWS + j));
         if (wave == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
     }
     char *val = p.bp_val + (size_t)(G * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);   // this lane's group
     if constexpr (WIDE) {
-        // slot-major rows of 64 (128) bytes; the slots that fill up the last quad are zero
+        // slot-major rows of 64 or 128 bytes; the slots that fill up the last quad are zero
         constexpr int ROWB = MMM_GROUP_COLS * ESZ;
         if (group_ok) {
 #pragma unroll
@@ -561,37 +563,35 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
         }
         __syncthreads();
     } else {
-        // 16 slots at a time are stored as [slot / 4][column][slot % 4]: the four values of k a lane of the matrix
-        // instruction needs for its column are 8 contiguous bytes.  Composed in LDS, half of the groups at a time;
-        // the slots that fill up the last 16 are zero.
+        // Composed in LDS in the order of mmm_value_pos; the slots that fill up the last batch are zero.  Whole batches are
+        // copied out, 1 KiB each.
+        constexpr int GROUPB = SEG * MMM_GROUP_COLS * ESZ + 16;   // bytes per group (4 banks apart)
+        constexpr uint32_t SLOTS = 32;                            // per batch
+        static_assert(B_GROUPS * GROUPB <= (int)sizeof(sh.pack), "room for the groups");
+        uint16_t *g = reinterpret_cast<uint16_t *>(sh.pack + (lane / LPG) * GROUPB);
+        auto put = [&](uint32_t slot, const u32x4 &v) {
+            uint16_t *at = g + mmm_value_pos(ESZ, slot, (uint32_t)(lane & 3) * 4u);
+            at[0] = (uint16_t)v.x;
+            at[8] = (uint16_t)(v.x >> 16);
+            at[16] = (uint16_t)v.y;
+            at[24] = (uint16_t)(v.y >> 16);
+        };
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            if ((lane >> 5) == half) {
-                uint16_t *g = sh.pack[(lane >> 2) & 7];
-                auto put = [&](uint32_t slot, uint32_t x, uint32_t y) {
-                    uint16_t *at = g + (slot >> 4) * 256 + ((slot >> 2) & 3) * 64 + (lane & 3) * 16 + (slot & 3);
-                    at[0] = (uint16_t)x;
-                    at[4] = (uint16_t)(x >> 16);
-                    at[8] = (uint16_t)y;
-                    at[12] = (uint16_t)(y >> 16);
-                };
+        for (int j = 0; j < B_ROWS; ++j)
+            if ((gb >> j) & 1u) put(slots[j], raw[j]);
 #pragma unroll
-                for (int j = 0; j < B_ROWS; ++j)
-                    if ((gb >> j) & 1u) put(slots[j], raw[j].x, raw[j].y);
-                if (n + wave < ((n + 15u) & ~15u)) put(n + wave, 0u, 0u);
-            }
-            __syncthreads();
-            // 128 threads per group copy its rounded-up length
-            const int cg = threadIdx.x >> 7;
-            const int64_t CG = ct * B_GROUPS + half * 8 + cg;
-            if (CG < p.NG) {
-                const uint64_t *ct_bits = reinterpret_cast<const uint64_t *>(sh.gbits[(half * 8 + cg) * 4]);
-                const uint32_t cn = ((uint32_t)(__popcll(ct_bits[0]) + __popcll(ct_bits[1])) + 15u) & ~15u;
-                char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
-                for (uint32_t q = threadIdx.x & 127u; q < cn * 2; q += 128)
-                    *reinterpret_cast<uint4 *>(cval + q * 16) = reinterpret_cast<const uint4 *>(sh.pack[cg])[q];
-            }
-            __syncthreads();
+        for (uint32_t i = 0; i < SLOTS; i += BUILD_WAVES)
+            if (n + i + wave < ((n + SLOTS - 1) & ~(SLOTS - 1))) put(n + i + wave, u32x4{0, 0, 0, 0});
+        __syncthreads();
+        constexpr int TPG = BUILD_THREADS / B_GROUPS;   // threads per group
+        const int cg = threadIdx.x / TPG;
+        const int64_t CG = ct * B_GROUPS + cg;
+        if (CG < p.NG) {
+            const uint64_t *bits = reinterpret_cast<const uint64_t *>(sh.gbits[cg * LPG]);
+            const uint32_t batches = ((uint32_t)(__popcll(bits[0]) + __popcll(bits[1])) + SLOTS - 1u) / SLOTS;
+            char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
+            for (uint32_t q = threadIdx.x % TPG; q < batches * 64; q += TPG)
+                *reinterpret_cast<uint4 *>(cval + q * 16) = *reinterpret_cast<const uint4 *>(sh.pack + cg * GROUPB + q * 16);
         }
     }
     {   // the lists, one word per thread

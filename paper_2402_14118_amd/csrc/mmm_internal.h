@@ -39,19 +39,34 @@ __host__ __device__ constexpr uint32_t mmm_img_row(size_t esz, uint32_t col, uin
 }
 // Packed B: per group of 16 columns and segment of 128 k the occupied rows, one after another ("slots"),
 // at [group][segment][128 slots][16 columns]; the number of slots; and per slot where its column of A
-// sits in the kernel's LDS ring of two blocks: column 128 * (segment & 1) + k, in units of 256 bytes (4- and
+// sits in the kernel's LDS ring of `ring` blocks: column 128 * (segment mod ring) + k, in units of 256 bytes (4- and
 // 8-byte elements) or of 16 bytes with the rotation folded in (16-bit elements).  Slots past the
-// last name the ring's zero column.  The order of the list is the one in which a lane reads it: 4- and 8-byte
-// elements take slots 4u + s (u = 0..3) of every 16, 16-bit elements slot lane / 4.
+// last name the ring's zero column.
+// A vector-memory instruction occupies a compute unit for 8 cycles up to 4 bytes per lane and for 16 above, whether
+// it loads 8 or 16.  So the entries, and 16-bit values, are stored in the order in which the kernel's lanes take
+// them, one load per batch of slots.  s: lane / 16, c: column.
+// 4- and 8-byte elements, batches of 16 slots: slot 4u + s is entry u of [s][4]; values slot by slot.  (Floats in lane
+// order save the kernel 1 to 2% - 4096^3, p = .4: 431 against 437 us - and cost the builder more, for putting them
+// together in LDS: 2048 x 8192 x 2048 with half of B's blocks: 54 against 46 us.)
+// 16-bit elements, batches of 32: slot 16h + 4s + e is value 4h + e of [s][c][8], entry h of [4s + e][2].
 constexpr int MMM_GROUP_COLS = 16;
-constexpr uint32_t MMM_ZERO_COL = 2 * MMM_AB_COLS;
+// Blocks in the ring.  16-bit types take four (64 KiB): a step of the kernel is short then, and a block is requested three
+// steps before it is needed.  Floats and doubles take two (64, 128 KiB); four floats deep measured no faster (2048^3,
+// p = .1: 28.8 against 29.2 us) and leaves no room for a second ring or workgroup.
+constexpr int mmm_ring(size_t esz) { return esz == 2 ? 4 : 2; }
+__host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t)ring * MMM_AB_COLS; }
+// col: ring column (mmm_zero_col for the zero column: a multiple of 8, so the rotation is nil)
 __host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
 {
-    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3) | (col == MMM_ZERO_COL ? 0u : mmm_img_swizzle(col));
+    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3) | mmm_img_swizzle(col);
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
 {
-    return esz >= 4 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : slot;
+    return esz >= 4 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
+}
+__host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, uint32_t col)   // in elements
+{
+    return esz >= 4 ? slot * 16u + col : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
 }
 struct mmm_maps {
     int64_t M, K, N;
@@ -132,7 +147,7 @@ struct mmm_plan {
 
 struct mmm_variant_info {
     const char *name;
-    int32_t TM, TN, KC, rows;   // rows: rows of C actually computed (64, or 32 for short matrices)
+    int32_t TM, TN, KC, rows, k_ranges;   // k_ranges: ranges of K inside a workgroup; rows: rows of C actually computed (64, or 32 for short matrices)
 };
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);

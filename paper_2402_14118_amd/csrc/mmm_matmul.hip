@@ -11,7 +11,7 @@
 // 64 rows of a tile are multiplied (A's element sparsity is what the pair kernel exploits).  The iteration
 // is uniform across the wave.
 //
-// A workgroup owns 64 rows of C and keeps a ring of two blocks of A in LDS, filled by asynchronous
+// A workgroup owns 64 rows of C and keeps a ring of two or four blocks of A in LDS (see mmm_ring), filled by asynchronous
 // global-to-LDS loads of the builder's image, whose byte order is the one the operand reads want: no
 // registers, no vector instruction and no LDS atomic is spent on A.  One barrier per step of 128 k.
 //
@@ -20,8 +20,14 @@
 // multiply-adds on another take longer together, 709 us, than the sum of their times alone, 231 + 339 us),
 // so every vector instruction costs matrix time.  Per quad of four listed k the loop issues one v_perm_b32
 // (LDS address of the A operand), one ds_read_b128 (the operands of all four 16-row tiles), one
-// global_load_dword with an immediate offset (B) and four matrix instructions.  16-bit inputs use
-// v_mfma_f32_16x16x32 on 32 listed k, with ds_read_b64_tr_b16 gathering their A operands.
+// buffer_load_dword with an immediate offset (B) and four matrix instructions.  16-bit inputs use
+// v_mfma_f32_16x16x32 on 32 listed k, with ds_read_b64_tr_b16 gathering their A operands and one load of 16 bytes per
+// lane for B's.
+//
+// What bounds it: dense lists, the matrix cores (4096^3 fp32, p = .4: 437 us, of which 360 are matrix instructions at
+// the rate a large product reaches); sparse ones, whose steps are one short batch, the compute unit's scalar unit and vector-memory issue,
+// which all waves share.  Hence the schedule of `step` below: 4096^3 p = .05 fp32 118 -> 106 us, 2048^3 p = .1
+// 29.3 -> 27.6, 512 x 8192 x 4096 bf16 35.1 -> 32.7, against clamped offsets, one request per quad and a count load per step.
 #include <mutex>
 #include <type_traits>
 
@@ -33,7 +39,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -63,20 +68,12 @@ template <> struct Acc<double> { typedef doublex4 tile; typedef double element; 
 // 16-bit inputs are contracted by the matrix instructions of their own type (fp32 accumulate).
 template <typename T> struct Mfma16;
 template <> struct Mfma16<uint16_t> {   // bf16
-    static __device__ __forceinline__ floatx4 k16(u32x2 a, u32x2 b, floatx4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(shortx4, a), __builtin_bit_cast(shortx4, b), c, 0, 0, 0);
-    }
     static __device__ __forceinline__ floatx4 k32(u32x4 a, u32x4 b, floatx4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
 };
 template <> struct Mfma16<_Float16> {
-    static __device__ __forceinline__ floatx4 k16(u32x2 a, u32x2 b, floatx4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(halfx4, a), __builtin_bit_cast(halfx4, b), c, 0, 0, 0);
-    }
     static __device__ __forceinline__ floatx4 k32(u32x4 a, u32x4 b, floatx4 c)
     {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(halfx8, a), __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
@@ -95,12 +92,27 @@ __device__ __forceinline__ uint32_t xcd_contiguous_id(uint32_t b, uint32_t n)
 
 typedef __attribute__((address_space(3))) char lds_char;
 
-// 64 lanes x 16 bytes from `base` (wave-uniform) + voff to LDS byte offset `lds` (wave-uniform) + 16 * lane.  Written
-// as assembly because the compiler would wait for every outstanding one of these before each LDS read.  It counts as
-// one vector-memory operation of the wave, in order with the others (see wait_vmem).
-__device__ __forceinline__ void copy_to_lds(const char *base, uint32_t voff, uint32_t lds)
+// N times 64 lanes x 16 bytes from `base` (wave-uniform) + voff to LDS byte offset `lds` (wave-uniform) + 16 * lane, each
+// 1 KiB on (the immediate offset moves both addresses).  Written as assembly because the compiler would wait for every
+// outstanding one of these before each LDS read.  Each counts as one vector-memory operation of the wave, in order with
+// the others (see wait_vmem).
+template <int N> __device__ __forceinline__ void copy_to_lds(const char *base, uint32_t voff, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+    static_assert(N == 1 || N == 2 || N % 4 == 0, "");
+    if constexpr (N == 1) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+    } else if constexpr (N == 2) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" ::"s"(lds),
+                     "v"(voff), "s"(base)
+                     : "memory");
+    } else {
+#pragma unroll
+        for (int i = 0; i < N / 4; ++i)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %1, %2 offset:2048\n\tglobal_load_lds_dwordx4 %1, %2 offset:3072" ::"s"(lds + i * 4096),
+                         "v"(voff), "s"(base + i * 4096)
+                         : "memory");
+    }
 }
 // wait until at most N of the wave's vector-memory operations are outstanding (they complete in order)
 template <int N> __device__ __forceinline__ void wait_vmem()
@@ -111,29 +123,35 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 // RT  16-row MFMA sub-tiles computed (4: all 64 rows of the block; 2: matrices of at most 32 rows)
 // GW  16-column groups per wave (2: bw = 32, the two groups of a block share their list), NW waves per
 //     workgroup: TN = 16*GW*NW columns
-template <int RT, int GW, int NW, typename T>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : 4))) void mmm_matmul_kernel(const MatmulParams p)
+// KS  groups of NW waves that share the tile and take consecutive ranges of its K (each with a ring of its own); their
+//     sums are added in LDS at the end, in order
+template <int RT, int GW, int NW, int KS, typename T>
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
     constexpr bool WIDE = sizeof(T) >= 4, F64 = sizeof(T) == 8;
     constexpr int ESZ = (int)sizeof(T);
     typedef typename Acc<T>::tile tile_t;
     typedef typename Acc<T>::element elem_t;
+    constexpr int RING = mmm_ring(sizeof(T));
     constexpr int COLB = TM * ESZ;                  // bytes per LDS column
     constexpr int SLAB = KC * COLB;                 // bytes per block of A
-    constexpr int ZERO_AT = 2 * SLAB;               // the ring's zero column (MMM_ZERO_COL)
+    constexpr int ZERO_AT = RING * SLAB;            // the ring's zero column (mmm_zero_col)
     constexpr int DMA = SLAB / 1024 / NW;           // copies per wave and block
     constexpr int BATCH = WIDE ? 16 : 32;           // list slots per batch
-    constexpr int OPS = WIDE ? 4 * GW + 1 : 2 * GW + 2;   // vector-memory operations issue() makes
+    constexpr int OPS = WIDE ? 4 * GW + 1 : GW + 1;       // vector-memory operations request() makes
     constexpr int SEGB = KC * MMM_GROUP_COLS * ESZ;       // bytes of a packed segment
     static_assert(DMA * NW * 1024 == SLAB, "whole copies");
     typedef elem_t avec __attribute__((ext_vector_type(RT)));   // 4- and 8-byte types: A operands of the RT row tiles for one k
 
-    __shared__ __align__(1024) char ring[2 * SLAB + COLB];
+    constexpr int RING_BYTES = RING * SLAB + COLB;
+    __shared__ __align__(1024) char rings[KS * RING_BYTES];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = KS == 1 ? wave_all : wave_all % NW, ks = KS == 1 ? 0 : wave_all / NW;   // place in the tile, range of K
     const int c = lane & 15, s = lane >> 4;
+    char *const ring = rings + ks * RING_BYTES;
     lds_char *const ring3 = (lds_char *)ring;
     const uint32_t ring_off = (uint32_t)(uintptr_t)ring3;
 
@@ -150,8 +168,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
         chunks_live = (int)((*p.kinfo + (uint32_t)KC - 1) / (uint32_t)KC);
         per_split = __builtin_amdgcn_readfirstlane((chunks_live + p.split_k - 1) / p.split_k);
     }
-    const int chunk_begin = min(split * per_split, chunks_live);
-    const int chunk_end = min(chunk_begin + per_split, chunks_live);
+    const int wg_begin = min(split * per_split, chunks_live), wg_end = min(wg_begin + per_split, chunks_live);
+    const int steps = (wg_end - wg_begin + KS - 1) / KS;   // barriers of every wave
+    const int chunk_begin = min(wg_begin + ks * steps, wg_end);
+    const int chunk_end = min(chunk_begin + steps, wg_end);
 
     tile_t acc[GW][RT];
 #pragma unroll
@@ -172,83 +192,55 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     const int val_next = (int)(p.KBA * SEGB);   // second group of a 32-wide block (N is a multiple of 32 then)
     const uint32_t *const cnt0 = p.bp_cnt + Gc * p.KBA;
 
-    // ---- list lengths, 64 steps at a time: lane i holds that of step cnt_base + i
-    int cnt_base = chunk_begin;
-    uint32_t cntv = 0;
-    auto load_counts = [&](int base) __attribute__((always_inline)) {
-        cnt_base = base;
-        cntv = cnt0[min(base + lane, p.chunks_total - 1)];
-        asm volatile("" : "+v"(cntv));   // waited for here, once per 64 steps, and not at every use
-    };
-    auto count_of = [&](int ch) __attribute__((always_inline)) -> int {
-        if (ch >= cnt_base + 64) load_counts(ch);
-        return active ? (int)__builtin_amdgcn_readlane(cntv, ch - cnt_base) : 0;
-    };
-
-    // ---- A: block ch of this row tile to ring half ch & 1 (the builder's list entries assume that half)
-    const char *const img = p.a_img + (size_t)tile_m * p.KBA * SLAB;
+    // ---- A: block ch of this row tile to place ch mod RING (the builder's list entries assume that place)
+    const char *src = p.a_img + ((size_t)tile_m * p.KBA + chunk_begin) * SLAB;   // the next block to copy
+    int to_copy = chunk_end - chunk_begin;                                       // blocks from there on
     const uint32_t dma_v = (uint32_t)(wave * DMA * 1024 + lane * 16);
-    auto copy_block = [&](int ch) __attribute__((always_inline)) {
-        const char *src = img + (size_t)(uint32_t)ch * SLAB;
-        const uint32_t dst = ring_off + (uint32_t)(ch & 1) * SLAB + (uint32_t)(wave * DMA * 1024);
-#pragma unroll
-        for (int i = 0; i < DMA; ++i) copy_to_lds(src + i * 1024, dma_v, dst + i * 1024);
+    const uint32_t place0 = ring_off + (uint32_t)(wave * DMA * 1024);
+    uint32_t place = (uint32_t)(chunk_begin & (RING - 1)) * SLAB;
+    auto copy_block = [&]() __attribute__((always_inline)) {
+        copy_to_lds<DMA>(src, dma_v, place0 + place);
+        src += SLAB;
+        place = (place + SLAB) & (RING * SLAB - 1);
+        --to_copy;
     };
 
     // ---- B: one batch of a group's list in registers
     struct Batch {
         elem_t bf[WIDE ? GW : 1][4];    // 4- and 8-byte types: slot 4u + s of column c, u = 0..3
-        u32x2 bh[WIDE ? 1 : GW][2];     // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
+        u32x4 bh[WIDE ? 1 : GW];        // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
         u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
-        uint32_t entry[2];              // 16-bit: ring position of slot lane / 4 of both halves
-        int left;                       // live slots from the batch's first on; -1: past the end
-        bool first;                     // first batch of its step
+        uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each)
     };
     Batch B0, B1, B2;
-    // what issue() requests next: step, first slot and length of its list, byte offsets of the slot's values and entries
-    int is_ch = chunk_begin, is_at = 0, is_n = 0, is_v = chunk_begin * SEGB, is_l = chunk_begin * (KC * 2);
-    auto issue = [&](Batch &b) __attribute__((always_inline)) {
-        // Always the same number of loads, from addresses that lie inside the segment's area whatever the list holds
-        // (past the end: inside the last segment's), so that the waits at the steps' barriers can count them.
-        b.left = is_ch < chunk_end ? is_n - is_at : -1;
-        b.first = is_at == 0;
-        asm volatile("" ::: "memory");   // the loads of one call stay behind those of the call before
+    // The batch whose values and entries lie at these byte offsets of the group's area.  Always OPS loads, so that the waits
+    // can count them; past the end of the area they return zeros (and are not used).
+    auto request = [&](Batch &b, int off_v, int off_l) __attribute__((always_inline)) {
+        asm volatile("" ::: "memory");   // the loads of one call stay together and in their place: the waits count them
         if constexpr (WIDE) {
-            b.list = __builtin_amdgcn_raw_buffer_load_b64(list_rsrc, s * 8, is_l, 0);
+            b.list = __builtin_amdgcn_raw_buffer_load_b64(list_rsrc, s * 8, off_l, 0);
 #pragma unroll
-            for (int g = 0; g < GW; ++g)
+            for (int g = 0; g < GW; ++g) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if constexpr (F64)
-                        b.bf[g][u] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(val_rsrc, lane * 8 + u * 512, is_v + g * val_next, 0));
+                        b.bf[g][u] = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(val_rsrc, lane * 8 + u * 512, off_v + g * val_next, 0));
                     else
-                        b.bf[g][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(val_rsrc, lane * 4 + u * 256, is_v + g * val_next, 0));
+                        b.bf[g][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(val_rsrc, lane * 4 + u * 256, off_v + g * val_next, 0));
                 }
+            }
         } else {
+            b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, off_l, 0);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) b.entry[h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(list_rsrc, (lane >> 2) * 2 + h * 32, is_l, 0);
-#pragma unroll
-            for (int g = 0; g < GW; ++g)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) b.bh[g][h] = __builtin_amdgcn_raw_buffer_load_b64(val_rsrc, lane * 8 + h * 512, is_v + g * val_next, 0);
+            for (int g = 0; g < GW; ++g) b.bh[g] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16, off_v + g * val_next, 0);
         }
         asm volatile("" ::: "memory");
-        is_at += BATCH;
-        is_v += BATCH * MMM_GROUP_COLS * ESZ;
-        is_l += BATCH * 2;
-        if (is_at >= is_n) {
-            is_at = 0;
-            const int ch = ++is_ch;
-            const int in = min(ch, chunk_end - 1);
-            is_v = in * SEGB;
-            is_l = in * (KC * 2);
-            is_n = count_of(in);
-        }
     };
 
     const uint32_t c16 = (uint32_t)c * 16u;
     const uint32_t chunk8 = (uint32_t)(lane & 3) * 8u;
-    auto multiply = [&](const Batch &b) __attribute__((always_inline)) {
+    // left: slots of the list from the batch's first on (at least one)
+    auto multiply = [&](const Batch &b, int left) __attribute__((always_inline)) {
         if constexpr (WIDE) {
             // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
             // entries count in 256)
@@ -284,82 +276,123 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
                     }
             };
             quad(0);
-            if (b.left > 4) {
+            if (left > 4) {
                 quad(1);
-                if (b.left > 8) {
+                if (left > 8) {
                     quad(2);
-                    if (b.left > 12) quad(3);
+                    if (left > 12) quad(3);
                 }
             }
         } else {
             // ring address: entry * 16 with the rotation of the column's units in bits 5 and 6, plus this lane's four
             // rows; row tile r is 32 bytes on, before rotation
-            uint32_t at[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) at[h] = b.entry[h] << 4 | chunk8;
+            const uint32_t at[2] = {(b.entry << 4 & 0xffff0u) | chunk8, (b.entry >> 12 & 0xffff0u) | chunk8};
             auto operand = [&](int h, int r) __attribute__((always_inline)) -> u32x2 {
                 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
                 return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(ring3 + (at[h] ^ (uint32_t)(r * 32)))));
             };
-            if (b.left > 16) {
-                u32x2 a[2][RT];
+            // The whole batch whatever its length: slots past the end name the zero column and hold zeros.  (A branch to a
+            // 16-slot instruction for short lists costs more, in moved accumulators, than it saves in LDS reads.)
+            u32x2 a[2][RT];
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int r = 0; r < RT; ++r) a[h][r] = operand(h, r);
+                for (int r = 0; r < RT; ++r) a[h][r] = operand(h, r);
 #pragma unroll
-                for (int r = 0; r < RT; ++r)
+            for (int r = 0; r < RT; ++r)
 #pragma unroll
-                    for (int g = 0; g < GW; ++g)
-                        acc[g][r] = Mfma16<T>::k32(u32x4{a[0][r].x, a[0][r].y, a[1][r].x, a[1][r].y},
-                                                   u32x4{b.bh[g][0].x, b.bh[g][0].y, b.bh[g][1].x, b.bh[g][1].y}, acc[g][r]);
-            } else {
-                u32x2 a[RT];
-#pragma unroll
-                for (int r = 0; r < RT; ++r) a[r] = operand(0, r);
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-#pragma unroll
-                    for (int g = 0; g < GW; ++g) acc[g][r] = Mfma16<T>::k16(a[r], b.bh[g][0], acc[g][r]);
-            }
+                for (int g = 0; g < GW; ++g)
+                    acc[g][r] = Mfma16<T>::k32(u32x4{a[0][r].x, a[0][r].y, a[1][r].x, a[1][r].y}, b.bh[g], acc[g][r]);
         }
     };
 
-    // ---- a step begins.  Its block must have landed: the wave's own copies were made at the step before, and at least
-    // one issue() came after them, so all but the OPS youngest operations being done is enough.  After the barrier
-    // nobody reads the other half of the ring any more, and the next block's copies may start.
-    int ch_now = chunk_begin;
-    auto begin_step = [&]() __attribute__((always_inline)) {
-        wait_vmem<OPS>();
+    // ---- One step: the block in the ring against the n rows listed for it.  A compute unit has one scalar unit for all of
+    // its waves, and steps are short (a sparse one is one batch), so what is done per step is kept to about two dozen scalar
+    // instructions: offsets and pointers advance by constants, nothing is clamped, the list lengths sit in a register.
+    // (With 55 of them a 512 x 8192 x 4096 half-precision multiplication spent 11 of its 31 us on control alone.)
+    //
+    // b holds the first batch, requested two steps ago, and receives that of the step after the next; B2 holds the second,
+    // if there is one, requested at the end of the step before.  Further batches of a long list alternate between the two.
+    //
+    // The block must have landed.  The wave's share of it was requested RING - 1 steps ago; since then the wave has made at
+    // least OPS loads per step, and operations complete in order, so it is enough that all but that many are done.  After
+    // the barrier nobody reads the place of the block before any more, and the next copies may go there.
+    constexpr int BATCH_V = BATCH * MMM_GROUP_COLS * ESZ, BATCH_L = BATCH * 2, SEG_L = KC * 2;   // bytes
+    int off_v = chunk_begin * SEGB, off_l = chunk_begin * SEG_L;   // the current step's segment
+    auto step = [&](int n, int n_next, Batch &b) __attribute__((always_inline)) {
+        wait_vmem<(RING - 1) * OPS>();
         asm volatile("s_barrier" ::: "memory");
-        if (ch_now + 1 < chunk_end) copy_block(ch_now + 1);
-        ++ch_now;
-    };
-    auto consume = [&](const Batch &b) __attribute__((always_inline)) {
-        if (b.first && b.left >= 0) begin_step();
-        if (b.left > 0) multiply(b);
+        if (to_copy > 0) copy_block();
+        if (n > 0) {
+            multiply(b, n);
+            if (n > BATCH) {
+                // (Requests inside are unconditional, the last one repeating the batch in hand: a load on one side of a
+                // branch would be waited for as if nothing had been requested after the loads before it.)
+                const int end = (n - 1) / BATCH;   // the last batch
+                for (int i = 1;;) {
+                    const int j = min(i + 1, end);
+                    request(b, off_v + j * BATCH_V, off_l + j * BATCH_L);
+                    multiply(B2, n - i * BATCH);
+                    if (++i > end) break;
+                    const int k = min(i + 1, end);
+                    request(B2, off_v + k * BATCH_V, off_l + k * BATCH_L);
+                    multiply(b, n - i * BATCH);
+                    if (++i > end) break;
+                }
+            }
+        }
+        if (n_next > BATCH) request(B2, off_v + SEGB + BATCH_V, off_l + SEG_L + BATCH_L);
+        request(b, off_v + 2 * SEGB, off_l + 2 * SEG_L);
+        off_v += SEGB;
+        off_l += SEG_L;
     };
 
+    const int even_steps = (steps + 1) & ~1;   // steps go in pairs; the odd one past the end has no list
     if (chunk_begin < chunk_end) {
-        copy_block(chunk_begin);
-        for (int i = tid; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
-        load_counts(chunk_begin);
-        is_n = count_of(chunk_begin);
-        issue(B0);
-        issue(B1);
-        issue(B2);
-        // three batches in flight; unrolled so that the registers rotate by name, and left only at the end of a trip (an
-        // exit in the middle makes the compiler wait for loads as if they could be the latest ones)
-        do {
-            consume(B0);
-            issue(B0);
-            consume(B1);
-            issue(B1);
-            consume(B2);
-            issue(B2);
-        } while (B0.left >= 0);
+#pragma unroll
+        for (int i = 0; i < RING - 1; ++i)
+            if (to_copy > 0) copy_block();
+        for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
+        request(B0, off_v, off_l);
+        request(B1, off_v + SEGB, off_l + SEG_L);
+        wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
+        bool first = true;
+        for (int done = 0; done < even_steps; done += 62) {   // lane i: length of the list of step done + i
+            const int ch = chunk_begin + done + lane;
+            uint32_t counts = active && ch < chunk_end ? cnt0[ch] : 0u;
+            asm volatile("" : "+v"(counts));   // waited for here
+            if (first && (int)__builtin_amdgcn_readlane(counts, 0) > BATCH) request(B2, off_v + BATCH_V, off_l + BATCH_L);
+            first = false;
+            const int here = min(62, even_steps - done);
+            int n = (int)__builtin_amdgcn_readlane(counts, 0);
+            for (int i = 0; i < here; i += 2) {
+                const int n1 = (int)__builtin_amdgcn_readlane(counts, i + 1), n2 = (int)__builtin_amdgcn_readlane(counts, i + 2);
+                step(n, n1, B0);
+                step(n1, n2, B1);
+                n = n2;
+            }
+        }
+    } else if (KS > 1) {   // no step left for this range of K: only the barriers of the others
+        for (int i = 0; i < even_steps; ++i) asm volatile("s_barrier" ::: "memory");
     }
-    __syncthreads();   // the ring is free: the epilogue reuses it
+    __syncthreads();   // the rings are free: what follows reuses them
+    if constexpr (KS > 1) {   // sums of the later ranges of K, added in order
+        tile_t *sums = reinterpret_cast<tile_t *>(rings + RING_BYTES);   // (the first ring is what the layout below uses)
+        static_assert((KS - 1) * NW * 64 * GW * RT * (int)sizeof(tile_t) <= (KS - 1) * RING_BYTES, "room for them");
+        if (ks > 0)
+#pragma unroll
+            for (int g = 0; g < GW; ++g)
+#pragma unroll
+                for (int r = 0; r < RT; ++r) sums[((((ks - 1) * NW + wave) * GW + g) * RT + r) * 64 + lane] = acc[g][r];
+        __syncthreads();
+        if (ks > 0) return;
+#pragma unroll
+        for (int q = 0; q < KS - 1; ++q)
+#pragma unroll
+            for (int g = 0; g < GW; ++g)
+#pragma unroll
+                for (int r = 0; r < RT; ++r) acc[g][r] += sums[(((q * NW + wave) * GW + g) * RT + r) * 64 + lane];
+    }
 
     // ---- write C (or this split's partial sums): every element exactly once.
     // Accumulator layout of the 16x16 MFMA: lane holds rows 4*s + v (v = 0..3) of column c; doubles: rows s + 4*v.
@@ -369,7 +402,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(sizeof(
     elem_t *out = p.split_k > 1 ? static_cast<elem_t *>(p.P) + (int64_t)split * p.M * p.N : static_cast<elem_t *>(p.C);
     const int64_t ldo = p.split_k > 1 ? p.N : p.ldc;
     const bool add = p.split_k == 1 && p.accumulate;
-    constexpr int PIECE = 2 * SLAB / NW;   // bytes of the ring per wave
+    constexpr int PIECE = RING * SLAB / NW;   // bytes of the (first) ring per wave
     constexpr int RP = PIECE / 1024 < RT ? PIECE / 1024 : RT;   // row tiles (1 KiB each) laid out at a time
     static_assert(RP >= 1 && RT % RP == 0, "whole passes");
     const bool vec_ok = !F64 && reinterpret_cast<uintptr_t>(out) % 16 == 0 && ldo % 4 == 0;
@@ -437,25 +470,32 @@ typedef void (*matmul_kernel_fn)(const MatmulParams);
 struct VariantEntry {
     mmm_variant_info info;
     int32_t waves;              // of 16 columns each; 32-wide blocks: half as many waves of 32 columns
-    matmul_kernel_fn fn[2][4];  // [bw == 32][element type]
+    matmul_kernel_fn fn[2][4];  // [bw == 32][element type]; null: not built
 };
 
-#define MMM_VARIANT(RT, NW)                                                                                              \
-    {                                                                                                                    \
-        {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT}, NW,                                                       \
-            {{mmm_matmul_kernel<RT, 1, NW, float>, mmm_matmul_kernel<RT, 1, NW, uint16_t>, mmm_matmul_kernel<RT, 1, NW, _Float16>,  \
-              mmm_matmul_kernel<RT, 1, NW, double>},                                                                       \
-             {mmm_matmul_kernel<RT, 2, NW / 2, float>, mmm_matmul_kernel<RT, 2, NW / 2, uint16_t>,                          \
-              mmm_matmul_kernel<RT, 2, NW / 2, _Float16>, mmm_matmul_kernel<RT, 2, NW / 2, double>}}                        \
+#define MMM_KERNELS(RT, GW, NW, KS)                                                                                       \
+    mmm_matmul_kernel<RT, GW, NW, KS, float>, mmm_matmul_kernel<RT, GW, NW, KS, uint16_t>, mmm_matmul_kernel<RT, GW, NW, KS, _Float16>
+#define MMM_VARIANT(RT, NW)                                                                                               \
+    {                                                                                                                     \
+        {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT, 1}, NW,                                                    \
+            {{MMM_KERNELS(RT, 1, NW, 1), mmm_matmul_kernel<RT, 1, NW, 1, double>},                                        \
+             {MMM_KERNELS(RT, 2, NW / 2, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, double>}}                                \
+    }
+#define MMM_VARIANT_K2(RT, NW) /* two rings: not for doubles */                                                           \
+    {                                                                                                                     \
+        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2}, NW,                                                 \
+            {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}                              \
     }
 
 const VariantEntry g_variants[] = {
-    MMM_VARIANT(4, 8),    // 0: 64 x 128
-    MMM_VARIANT(4, 16),   // 1: 64 x 256
-    MMM_VARIANT(4, 4),    // 2: 64 x 64
-    MMM_VARIANT(2, 8),    // 3: 32 x 128   (matrices of at most 32 rows)
-    MMM_VARIANT(2, 16),   // 4: 32 x 256
-    MMM_VARIANT(2, 4),    // 5: 32 x 64
+    MMM_VARIANT(4, 8),      // 0: 64 x 128
+    MMM_VARIANT(4, 16),     // 1: 64 x 256
+    MMM_VARIANT(4, 4),      // 2: 64 x 64
+    MMM_VARIANT(2, 8),      // 3: 32 x 128   (matrices of at most 32 rows)
+    MMM_VARIANT_K2(2, 8),   // 4: 32 x 128, K in two ranges
+    MMM_VARIANT(2, 4),      // 5: 32 x 64
+    MMM_VARIANT_K2(4, 8),   // 6: 64 x 128, K in two ranges
+    MMM_VARIANT_K2(4, 4),   // 7: 64 x 64, K in two ranges
 };
 constexpr int32_t kVariants = (int32_t)(sizeof(g_variants) / sizeof(g_variants[0]));
 
@@ -521,8 +561,9 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
         return hipErrorInvalidValue;
     const int wide = m->bw == 32 ? 1 : 0;
     matmul_kernel_fn fn = v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
+    if (fn == nullptr) return hipErrorInvalidValue;
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.waves >> wide) * 64), 0, s, p);
+    hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.waves >> wide) * (uint32_t)v.info.k_ranges * 64), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.split_k > 1) {

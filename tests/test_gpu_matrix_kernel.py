@@ -65,6 +65,17 @@ def test_list_lengths(bw, dtype):
 
 
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+def test_many_steps(dtype):
+    """More steps than a wave holds list lengths for at a time (62), in whole and with K in two ranges, the last one of an
+    odd number of steps; waves without columns in the last column tile."""
+    for segs in (63, 125):
+        w = synth.random_masked(70, segs * 128 - 5, 80, 16, 0.05, 0.05, segs, dist="smallint", dtype=dtype)
+        for variant in (0, 1) if dtype == synth.DT_F64 else (0, 1, 6, 7):
+            print("segments", segs, "variant", variant, flush=True)
+            _run(w, variant=variant)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 def test_every_variant_and_row_count(dtype):
     for variant in range(mm.mmm_matmul_variant_count()):
         short = mm.mmm_matmul_variant_name(variant).startswith("R2")
