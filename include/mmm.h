@@ -253,16 +253,14 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
  *       themselves.  Needs ldy * sizeof(element) below 2^20 bytes; beyond that mmm_matmul
  *       uses MATRIX whatever was asked for.
  * Automatic choice (path -1): MATRIX if a tile variant has been fixed (mmm_maps_set_plan or the
- * "matmul_variant" option).  Else, with p_A and p_B the densities of A's elements and B's
- * blocks counted by the most recent mmm_maps_stats call on the handle (kept as the estimate
- * across rebuilds): for matrices of at most 64 rows PAIRS unless p_A * p_B is known to exceed
- * 0.02; for larger ones PAIRS iff the densities are known and p_B * (1 - 24.5 * p_A) > 0.015
- * (A keeps fewer than 4 % of its elements and B is not nearly empty), or the problem is small
- * (fewer than 128 tiles of 64 x 128 in C) with at most 64 surviving k per element of C; else MATRIX.
- * Double inputs: MATRIX iff M * K * N is at least 2^27 (and M above 64).  The
- * thresholds are fitted to timings on an MI355X.  The paper leaves this
- * per-workload choice of method to the caller (section 6, choosing between methods by
- * sparsity). */
+ * "matmul_variant" option).  Else, once a mmm_maps_stats call on the handle has counted the
+ * non-zeros, blocks and surviving products (the most recent counts are kept as the estimate
+ * across rebuilds), the kernel whose estimated time is less; the estimates are fitted to timings
+ * on an MI355X.  For A with fewer than 4 % of its elements and more than 64 rows: PAIRS iff
+ * p_B * (1 - 24.5 * p_A) > 0.015.  Without counts the shape decides: PAIRS for at most 64 rows, else
+ * MATRIX; double inputs: MATRIX iff M * K * N is at least 2^27 (and M above 64).  The paper
+ * leaves this per-workload choice of method to the caller (section 6, choosing between methods
+ * by sparsity). */
 #define MMM_PATH_MATRIX 0
 #define MMM_PATH_PAIRS 1
 /* Fix the kernel for one handle (-1: automatic).  Errors: MMM_ERR_INVALID_ARG. */

@@ -1,6 +1,7 @@
 // Host side of the C ABI declared in include/mmm.h: argument checks, workspace
 // layout, launch planning.  All checks run before any device call, so they can
 // be exercised on a machine without a GPU.
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <cstring>
@@ -96,80 +97,176 @@ bool dtype_ok(int32_t dt) { return dt == MMM_F32 || dt == MMM_BF16 || dt == MMM_
 size_t elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : dt == MMM_F32 ? 4 : 2; }
 size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 
-mmm_plan make_plan(const mmm_maps *m, int32_t dt)
+// ---- Which kernel, which tile, how many splits of K -------------------------------------------
+//
+// A table of thresholds cannot follow this choice: it depends on the shape, both densities and how evenly the
+// workgroups fall on 256 compute units.  So both kernels' times are estimated and the least is taken.  The
+// estimates are sums of terms with a meaning each; their coefficients were fitted to the measured times of about 45000
+// launches, every variant and a dozen splits on 1850 random problems (200 to 4096 in each dimension, few rows with K up
+// to 16384, densities .05 to 1, all types).  They are within 9 % (matrix) and 14 % (pairs) of the measurements, and the choice made
+// from them costs 2 to 3 % more than the best one; the former thresholds cost 17 % among the matrix kernel's plans and
+// 17 (doubles) to 37 % (16-bit) over all.
+struct MatrixCost {   // microseconds
+    double launch;        // per call (fitted with the operands in L2, and 1 us more: after a build they are not)
+    double latency;       // per step and batch of its longest lists: nobody hides the first wave's waiting
+    double step;          // per step of each workgroup on the fullest compute unit: barrier, copy of a block of A
+    double multiply;      // per 16 columns, row tile of 16 and list unit (quad of k; 16-bit: batch of 32) there
+    double wave;          // per 16 columns of each workgroup there: prologue, writing C
+    double workgroup;     // per workgroup there
+    double reduce;        // second launch that adds the splits (half of it is the host's: set, not fitted)
+    double reduce_mega;   // per 2^20 partial sums of C
+    double image_giga;    // per 10^9 bytes of A copied to LDS
+};
+constexpr MatrixCost kMatrixCost[3] = {   // 2-, 4-, 8-byte elements
+    {3.784, 0.1426, 0.0341, 0.0023, 0.0803, 0.494, 3.00, 1.371, 46.8},
+    {3.902, 0.1762, 0.0920, 0.0030, 0.0756, 0.185, 3.00, 1.101, 34.4},
+    {3.729, 0.2370, 0.1927, 0.0061, 0.1607, 0.870, 3.00, 2.385, 47.6},
+};
+struct PairsCost {   // microseconds
+    double launch;     // per call
+    double range;      // per range of 4096 k a wave goes through, one after another
+    double word;       // per 10^5 ranges of all rows and 64-column spans: intersecting the maps
+    double product[3]; // per 10^9 surviving products, blocks of 8, 16, 32
+    double list;       // per 100 entries of one wave's lists, one after another
+    double waves;      // per 10^5 waves
+};
+constexpr PairsCost kPairsCost[3] = {
+    {2.91, 3.49, 21.6, {751, 372, 248}, 1.48, 16.3},
+    {2.25, 3.98, 16.5, {751, 401, 251}, 2.73, 16.4},
+    {4.52, 0.00, 51.4, {1481, 1127, 864}, 16.8, 18.1},
+};
+
+int cost_class(int32_t dt) { return dt == MMM_F64 ? 2 : dt == MMM_F32 ? 1 : 0; }
+bool stats_known(const mmm_maps *m) { return m->stats_a_valid && m->stats_b_valid; }
+
+// Densities are known only after a mmm_maps_stats call (the counts of the most recent one are kept as the estimate, also
+// across rebuilds: emergent sparsity levels are stable from step to step); without one a fifth of B is assumed.
+struct MatrixProblem {
+    int64_t steps;   // of 128 k that the kernel walks
+    double units;    // per step and group: quads of listed k (16-bit: batches of 32)
+    double batches;  // batches of 16 (32) slots
+};
+MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt)
 {
+    const bool known = stats_known(m);
+    const int64_t rows = known && m->b_compact ? std::max<int64_t>((int64_t)m->stats_rows_b, 1) : m->K;
+    double p = known ? std::min(1.0, (double)m->stats_occ_b / ((double)rows * (double)m->NB)) : 0.2;
+    if (m->bw == 8) p = 1.0 - (1.0 - p) * (1.0 - p);   // a group lists k if either of its blocks does
+    const double listed = p * MMM_AB_COLS, batch = elem_size(dt) == 2 ? 32.0 : 16.0;
+    MatrixProblem q;
+    q.steps = (rows + MMM_AB_COLS - 1) / MMM_AB_COLS;
+    q.batches = listed > 0.5 * batch ? listed / batch + 0.5 : 1.0;
+    q.units = elem_size(dt) == 2 ? q.batches : listed / 4.0 + 0.5;
+    return q;
+}
+
+double matrix_cost(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const mmm_variant_info &vi, int64_t tiles, int64_t split)
+{
+    const MatrixCost &c = kMatrixCost[cost_class(dt)];
+    const int64_t per_split = (q.steps + split - 1) / split, steps = (per_split + vi.k_ranges - 1) / vi.k_ranges;
+    const int64_t wgs = tiles * split, per_cu = (wgs + 255) / 256;
+    const double groups = vi.TN / MMM_GROUP_COLS, work = (double)steps * vi.k_ranges;
+    double t = c.launch + (double)steps * q.batches * c.latency +
+               (double)per_cu * (work * (c.step + groups * (vi.rows / 16) * q.units * c.multiply) + groups * vi.k_ranges * c.wave + c.workgroup) +
+               1e-9 * c.image_giga * (double)wgs * work * (double)(MMM_AB_ROWS * MMM_AB_COLS * elem_size(dt));
+    if (split > 1) t += c.reduce + 1e-6 * c.reduce_mega * (double)split * (double)m->M * (double)m->N;
+    return t;
+}
+
+double pairs_cost(const mmm_maps *m, int32_t dt)
+{
+    const PairsCost &c = kPairsCost[cost_class(dt)];
+    const double spans = (double)m->M * (double)((m->N + 63) / 64), products = (double)m->stats_macs;
+    const int64_t ranges = (m->WA + 63) / 64, shares = (m->N + 511) / 512 * m->M >= 1024 ? 1 : 4;   // see mmm_launch_pairs
+    return c.launch + (double)((ranges + shares - 1) / shares) * c.range + 1e-5 * spans * (double)ranges * c.word +
+           1e-9 * products * c.product[m->bw == 8 ? 0 : m->bw == 16 ? 1 : 2] + 0.01 * products / (spans * (double)shares * 64.0) * c.list +
+           1e-5 * spans * (double)shares * c.waves;
+}
+
+mmm_plan tile_plan(const mmm_maps *m, int32_t variant)   // without the split
+{
+    const mmm_variant_info &vi = mmm_variant(variant);
     mmm_plan p{};
-    int64_t v = m->plan_variant >= 0 ? m->plan_variant : g_opt_variant.load();
-    if (v >= 0 && v < mmm_variant_count() && mmm_variant((int32_t)v).rows < MMM_AB_ROWS && m->M > mmm_variant((int32_t)v).rows)
-        v = -1;   // that kernel computes too few rows for this matrix
-    if (v >= 0 && v < mmm_variant_count() && dt == MMM_F64 && mmm_variant((int32_t)v).k_ranges > 1) v = -1;   // no room for two rings of doubles
-    if (v < 0 || v >= mmm_variant_count()) {
-        // automatic: the shapes that put sixteen waves on a compute unit.  32-row kernel for short
-        // matrices; otherwise the 256-column tile (one workgroup of sixteen waves per CU) when that
-        // still gives every CU a workgroup, else the 128-column tile (eight waves); matrices too small
-        // to fill the machine that way, and too short in K for a split to pay, take the 64-column tile
-        if (m->M <= 32) {
-            v = 3;
-        } else {
-            const int64_t tm = (m->M + 63) / 64, chunks = (m->K + MMM_AB_COLS - 1) / MMM_AB_COLS;
-            const int64_t t256 = tm * ((m->N + 255) / 256), t128 = tm * ((m->N + 127) / 128);
-            v = t256 >= 256 ? 1 : (t128 >= 192 || chunks >= 16) ? 0 : 2;
-        }
-    }
-    const mmm_variant_info &vi = mmm_variant((int32_t)v);
-    p.variant = (int32_t)v;
+    p.variant = variant;
     p.tiles_m = (int32_t)((m->M + vi.TM - 1) / vi.TM);
     p.tiles_n = (int32_t)((m->N + vi.TN - 1) / vi.TN);
     p.chunks_total = (int32_t)((m->K + vi.KC - 1) / vi.KC);
-    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-    int64_t split = m->plan_split > 0 ? m->plan_split : g_opt_split.load();
-    if (split <= 0) {
-        split = 1;
-        if (tiles < 256) {   // fewer tiles than CUs: split K to give every CU work, if every part keeps 8 steps
-            split = (512 + tiles - 1) / tiles;
-            if (split > p.chunks_total / 8) split = p.chunks_total / 8;
-        }
-    }
-    const int64_t max_by_ws = (int64_t)(m->partial_bytes / ((size_t)m->M * (size_t)m->N * c_elem_size(dt)));
-    if (split > max_by_ws) split = max_by_ws;
-    if (split > p.chunks_total) split = p.chunks_total;
-    if (split < 1) split = 1;
-    p.chunks_per_split = (int32_t)((p.chunks_total + split - 1) / split);
-    split = (p.chunks_total + p.chunks_per_split - 1) / p.chunks_per_split;   // drop empty splits
-    p.split_k = (int32_t)split;
-    p.workgroups = tiles * split;
     return p;
 }
 
-// Which kernel multiplies.  The matrix-instruction kernel issues work in proportion to B's block
-// density (every listed row of B meets all rows of a tile of A); the pair kernel does work in
-// proportion to the product of both densities but pays two gathers per product and a fixed cost
-// per row and 64 columns.  Fitted to measurements on an MI355X (4096^3, 2048 x 16384 x 4096 and
-// 32 ... 512 x 8192 x 4096, densities 0.02 ... 0.4):
-//     pairs  ~ 110 us + 24500 us * p_A * p_B      matrix ~ 95 us + 1000 us * p_B      (per 4096^3)
-// so for matrices of many rows the pair kernel is ahead iff p_B * (1 - 24.5 * p_A) > 0.015, which
-// needs p_A below 0.04; for matrices of at most 64 rows (one tile of the matrix kernel, mostly
-// empty, and a latency-bound launch) it is ahead up to p_A * p_B of about 0.02, and for small problems
-// (256^3) with short lists as well.  Densities are
-// known only after a mmm_maps_stats call (the counts of the most recent one are kept as the
-// estimate, also across rebuilds: emergent sparsity levels are stable from step to step); without
-// one the shape decides alone.
+bool variant_usable(const mmm_maps *m, int32_t dt, int64_t v)
+{
+    if (v < 0 || v >= mmm_variant_count()) return false;
+    const mmm_variant_info &vi = mmm_variant((int32_t)v);
+    return !(vi.rows < MMM_AB_ROWS && m->M > vi.rows)        // computes too few rows for this matrix
+           && !(dt == MMM_F64 && vi.k_ranges > 1);           // no room for two rings of doubles
+}
+
+void compute_plan(const mmm_maps *m, int32_t dt, int64_t variant, int64_t fixed_split, mmm_plan *plan, double *cost)
+{
+    const MatrixProblem q = matrix_problem(m, dt);
+    const size_t c_bytes = (size_t)m->M * (size_t)m->N * c_elem_size(dt);
+    double best = -1.0;
+    for (int32_t v = 0; v < mmm_variant_count(); ++v) {
+        if (!variant_usable(m, dt, v) || (variant_usable(m, dt, variant) && v != variant)) continue;
+        mmm_plan p = tile_plan(m, v);
+        const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
+        static constexpr int64_t kSplits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
+        for (int64_t s : kSplits) {
+            // an automatic split also fits the library's own scratch array, whichever entry point runs it
+            int64_t split = fixed_split > 0 ? fixed_split : s;
+            const size_t room = fixed_split > 0 ? m->partial_bytes : std::min(m->partial_bytes, (size_t)MMM_STATIC_SCRATCH_BYTES);
+            split = std::min<int64_t>(split, (int64_t)(room / c_bytes));
+            split = std::max<int64_t>(1, std::min<int64_t>(split, p.chunks_total));
+            p.chunks_per_split = (int32_t)((p.chunks_total + split - 1) / split);
+            split = (p.chunks_total + p.chunks_per_split - 1) / p.chunks_per_split;   // drop empty splits
+            const double t = matrix_cost(m, dt, q, mmm_variant(v), tiles, split);
+            if (best < 0.0 || t < best) {
+                best = t;
+                p.split_k = (int32_t)split;
+                p.workgroups = tiles * split;
+                *plan = p;
+            }
+            if (fixed_split > 0 || split < s) break;
+        }
+    }
+    *cost = best;
+}
+
+mmm_plan make_plan(const mmm_maps *m, int32_t dt, double *cost = nullptr)
+{
+    const int64_t v = m->plan_variant >= 0 ? m->plan_variant : g_opt_variant.load();
+    const int64_t split = m->plan_split > 0 ? m->plan_split : g_opt_split.load();
+    std::lock_guard<std::mutex> lock(m->plan_mutex);
+    const mmm_plan_key key{dt, v, split, m->stats_version, m->b_compact};
+    if (!(m->plan_valid && key == m->plan_key)) {
+        compute_plan(m, dt, v, split, &m->plan, &m->plan_cost);
+        m->plan_key = key;
+        m->plan_valid = true;
+    }
+    if (cost) *cost = m->plan_cost;
+    return m->plan;
+}
+
 int32_t choose_path(const mmm_maps *m, int32_t dt)
 {
     if (!mmm_packs(m->M, dt)) return MMM_PATH_PAIRS;
-    int64_t path = m->plan_path >= 0 ? m->plan_path : g_opt_path.load();
+    const int64_t path = m->plan_path >= 0 ? m->plan_path : g_opt_path.load();
     if (path == MMM_PATH_MATRIX || path == MMM_PATH_PAIRS) return (int32_t)path;
     if (m->plan_variant >= 0 || g_opt_variant.load() >= 0) return MMM_PATH_MATRIX;   // a tile variant was asked for
-    if (dt == MMM_F64) return (double)m->M * (double)m->K * (double)m->N >= 134217728.0 ? MMM_PATH_MATRIX : MMM_PATH_PAIRS;
-    const bool known = m->stats_a_valid && m->stats_b_valid;
-    const double p_a = known ? (double)m->stats_nnz_a / ((double)m->M * (double)m->K) : 0.0;
-    const double p_b = known ? (double)m->stats_occ_b / ((double)m->K * (double)m->NB) : 0.0;
-    if (m->M <= 64) return !known || p_a * p_b <= 0.02 ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
-    // small problems (the matrix kernel would fill less than half the machine) with short lists are bound by
-    // latency, of which the pair kernel has less
-    const int64_t tiles = ((m->M + 63) / 64) * ((m->N + 127) / 128);
-    if (known && tiles < 128 && p_a * p_b * (double)m->K <= 64.0) return MMM_PATH_PAIRS;
-    return known && p_b * (1.0 - 24.5 * p_a) > 0.015 ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
+    if (!stats_known(m)) {   // the shape alone: few rows make short lists
+        if (dt == MMM_F64) return (double)m->M * (double)m->K * (double)m->N >= 134217728.0 ? MMM_PATH_MATRIX : MMM_PATH_PAIRS;
+        return m->M <= 64 ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
+    }
+    // an A that keeps less than 4 % of its elements: outside the range of the fit, an earlier one holds (4096^3)
+    const double p_a = (double)m->stats_nnz_a / ((double)m->M * (double)m->K), p_b = (double)m->stats_occ_b / ((double)m->K * (double)m->NB);
+    if (m->M > 64 && p_a < 0.04) return p_b * (1.0 - 24.5 * p_a) > 0.015 ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
+    // doubles of a few tiles: the matrix kernel leaves nearly all of the chip idle, and the estimates are poor there
+    // (215 x 722 x 320: 7.1 against 8.7 us; from 28 tiles on it is the estimates that decide better)
+    if (dt == MMM_F64 && ((m->M + 63) / 64) * ((m->N + 63) / 64) <= 24) return MMM_PATH_PAIRS;
+    double matrix = 0.0;
+    make_plan(m, dt, &matrix);
+    return pairs_cost(m, dt) < matrix ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
 }
 
 // The transposed B map over k is read by the pair kernel and by inspection only.  In row-compacted mode it is made with
@@ -259,7 +356,8 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->plan_split = 0;
     m->plan_path = -1;
     m->stats_a_valid = m->stats_b_valid = false;
-    m->stats_nnz_a = m->stats_occ_b = 0;
+    m->stats_nnz_a = m->stats_occ_b = m->stats_macs = m->stats_rows_b = m->stats_version = 0;
+    m->plan_valid = false;
     *out = m;
     return MMM_OK;
 }
@@ -432,6 +530,9 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
     }
     maps->stats_nnz_a = host[0];
     maps->stats_occ_b = host[1];
+    maps->stats_macs = host[2];
+    maps->stats_rows_b = host[3];
+    ++maps->stats_version;
     maps->stats_a_valid = maps->stats_b_valid = true;
     if (nnz_a) *nnz_a = host[0];
     if (occupied_blocks_b) *occupied_blocks_b = host[1];

@@ -755,9 +755,9 @@ __global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, 
         uint64_t rowcount = 0;
         if (k < K)
             for (int64_t j = 0; j < WB; ++j) rowcount += (uint64_t)__popcll(b_bits[k * WB + j]);
-        uint64_t v[3] = {colcount, rowcount, colcount * rowcount * (uint64_t)bw};
+        uint64_t v[4] = {colcount, rowcount, colcount * rowcount * (uint64_t)bw, rowcount != 0 ? 1u : 0u};
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
+        for (int q = 0; q < 4; ++q) {
             uint64_t x = v[q];
             for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
             if (lane == 0 && x != 0) atomicAdd((unsigned long long *)&stats[q], (unsigned long long)x);

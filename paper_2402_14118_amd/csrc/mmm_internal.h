@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "mmm.h"
 
 // Rows of A summarised by one column-any word.
@@ -68,6 +70,24 @@ __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, 
 {
     return esz >= 4 ? slot * 16u + col : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
 }
+struct mmm_plan {
+    int32_t variant;
+    int32_t split_k;
+    int32_t tiles_m, tiles_n;
+    int32_t chunks_total;      // ceil(K / KC)
+    int32_t chunks_per_split;
+    int64_t workgroups;
+};
+// what a plan was made for, besides the shape
+struct mmm_plan_key {
+    int64_t dtype, variant, split, stats_version;
+    bool b_compact;
+    bool operator==(const mmm_plan_key &o) const
+    {
+        return dtype == o.dtype && variant == o.variant && split == o.split && stats_version == o.stats_version && b_compact == o.b_compact;
+    }
+};
+
 struct mmm_maps {
     int64_t M, K, N;
     int32_t bw;
@@ -116,7 +136,14 @@ struct mmm_maps {
     int32_t plan_variant, plan_split, plan_path;
     // what the most recent mmm_maps_stats call counted: the density estimate behind the choice of kernel
     mutable bool stats_a_valid, stats_b_valid;
-    mutable uint64_t stats_nnz_a, stats_occ_b;
+    mutable uint64_t stats_nnz_a, stats_occ_b, stats_macs, stats_rows_b;   // non-zeros, blocks, surviving products, rows of B with a block
+    mutable int64_t stats_version;
+    // the launch plan last made: it is made anew when its key changes
+    mutable std::mutex plan_mutex;
+    mutable bool plan_valid;
+    mutable mmm_plan_key plan_key;
+    mutable mmm_plan plan;
+    mutable double plan_cost;   // estimated microseconds
 };
 
 struct mmm_build_args {
@@ -134,15 +161,6 @@ struct mmm_build_args {
     int32_t dtype;
     bool a_compact;   // lay A out over the live k (the numbering exists or is made in this call)
     bool b_compact;   // number the live rows (keep_rows given) and pack those
-};
-
-struct mmm_plan {
-    int32_t variant;
-    int32_t split_k;
-    int32_t tiles_m, tiles_n;
-    int32_t chunks_total;      // ceil(K / KC)
-    int32_t chunks_per_split;
-    int64_t workgroups;
 };
 
 struct mmm_variant_info {

@@ -28,6 +28,7 @@
 // the rate a large product reaches); sparse ones, whose steps are one short batch, the compute unit's scalar unit and vector-memory issue,
 // which all waves share.  Hence the schedule of `step` below: 4096^3 p = .05 fp32 118 -> 106 us, 2048^3 p = .1
 // 29.3 -> 27.6, 512 x 8192 x 4096 bf16 35.1 -> 32.7, against clamped offsets, one request per quad and a count load per step.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -450,19 +451,47 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 }
 
 // Sum of the split-K partials in a fixed order (split 0, 1, ...), so the result
-// does not depend on the order in which workgroups finish.
-template <typename E>
-__global__ __launch_bounds__(256) void mmm_splitk_reduce_kernel(const E *P, E *C, int64_t ldc, int64_t M,
-                                                                int64_t N, int32_t splits, int32_t accumulate)
+// does not depend on the order in which workgroups finish.  Bound by latency: a thread takes VEC neighbours of a row, and
+// the loads of eight splits are in flight together.
+template <typename E, int VEC>
+__global__ __launch_bounds__(256) void mmm_splitk_reduce_kernel(const E *P, E *C, int64_t ldc, uint32_t M, uint32_t NV,
+                                                                int32_t splits, int32_t accumulate)
 {
-    const int64_t total = M * N;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t row = e / N, col = e % N;
-        E sum = P[e];
-        for (int sp = 1; sp < splits; ++sp) sum += P[(int64_t)sp * total + e];
-        E *dst = C + row * ldc + col;
+    typedef E vec __attribute__((ext_vector_type(VEC)));
+    typedef vec vec_u __attribute__((aligned(sizeof(E) * VEC)));
+    const vec_u *parts = reinterpret_cast<const vec_u *>(P);
+    const uint32_t col = blockIdx.x * 256u + threadIdx.x;
+    if (col >= NV) return;
+    const int64_t total = (int64_t)M * NV;
+    for (uint32_t row = blockIdx.y; row < M; row += gridDim.y) {
+        const int64_t e = (int64_t)row * NV + col;
+        vec sum = parts[e];
+        for (int32_t sp = 1; sp < splits; sp += 8) {
+            vec v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = sp + i < splits ? parts[(int64_t)(sp + i) * total + e] : vec(0);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (sp + i < splits) sum += v[i];
+        }
+        vec_u *dst = reinterpret_cast<vec_u *>(C + (int64_t)row * ldc + (int64_t)col * VEC);
         *dst = accumulate ? *dst + sum : sum;
     }
+}
+
+template <typename E>
+void launch_splitk_reduce(const void *P, void *C, int64_t ldc, int64_t M, int64_t N, int32_t splits, int32_t accumulate, hipStream_t s)
+{
+    constexpr int VEC = 16 / (int)sizeof(E);   // N is a multiple of 8
+    const bool vec = reinterpret_cast<uintptr_t>(C) % 16 == 0 && ldc % VEC == 0 && reinterpret_cast<uintptr_t>(P) % 16 == 0;
+    const uint32_t NV = (uint32_t)(vec ? N / VEC : N);
+    const dim3 grid((NV + 255) / 256, (uint32_t)std::min<int64_t>(M, 65535));
+    if (vec)
+        hipLaunchKernelGGL((mmm_splitk_reduce_kernel<E, VEC>), grid, dim3(256), 0, s, static_cast<const E *>(P), static_cast<E *>(C), ldc, (uint32_t)M,
+                           NV, splits, accumulate);
+    else
+        hipLaunchKernelGGL((mmm_splitk_reduce_kernel<E, 1>), grid, dim3(256), 0, s, static_cast<const E *>(P), static_cast<E *>(C), ldc, (uint32_t)M,
+                           NV, splits, accumulate);
 }
 
 typedef void (*matmul_kernel_fn)(const MatmulParams);
@@ -567,15 +596,10 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.split_k > 1) {
-        const int64_t total = m->M * m->N;
-        int64_t blocks = (total + 255) / 256;
-        if (blocks > 4096) blocks = 4096;
         if (f64)
-            hipLaunchKernelGGL(mmm_splitk_reduce_kernel<double>, dim3((uint32_t)blocks), dim3(256), 0, s, static_cast<const double *>(partials),
-                               static_cast<double *>(C), ldc, m->M, m->N, pl.split_k, accumulate);
+            launch_splitk_reduce<double>(partials, C, ldc, m->M, m->N, pl.split_k, accumulate, s);
         else
-            hipLaunchKernelGGL(mmm_splitk_reduce_kernel<float>, dim3((uint32_t)blocks), dim3(256), 0, s, static_cast<const float *>(partials),
-                               static_cast<float *>(C), ldc, m->M, m->N, pl.split_k, accumulate);
+            launch_splitk_reduce<float>(partials, C, ldc, m->M, m->N, pl.split_k, accumulate, s);
         e = hipGetLastError();
     }
     return e;
