@@ -27,6 +27,9 @@ constexpr int SEG = MMM_AB_COLS;                      // rows of B (values of k)
 constexpr int B_ROWS = SEG / BUILD_WAVES;             // 8 rows per wave
 constexpr int A_ROWS = MMM_AB_ROWS / BUILD_WAVES;     // 4 rows of A per wave
 
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
 template <typename T> struct Tile {   // what a workgroup takes at a time, by element size
     static constexpr int ESZ = (int)sizeof(T);
     static constexpr int A_WORDS = ESZ == 8 ? 1 : 2;             // A: 64 rows x 64 A_WORDS columns
@@ -90,6 +93,9 @@ template <> struct Pattern<8> { typedef uint64_t type; static constexpr type mag
 
 __device__ __forceinline__ uint64_t ballot64(bool p) { return __ballot(p); }
 
+// `old` with the wave-uniform v in one lane (v_writelane_b32, for which clang has the intrinsic but no builtin)
+extern "C" __device__ uint32_t mmm_writelane(uint32_t v, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
+
 __device__ __forceinline__ uint32_t mbcnt64(uint64_t m)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -101,13 +107,15 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)v, l);
 }
 
-// Bits of two wave-uniform 32-bit masks interleaved: bit 2i = bit i of e, bit 2i + 1 = bit i of o.
-__device__ __forceinline__ uint64_t interleave(uint32_t e, uint32_t o)
+// OR of a value over aligned runs of LANES lanes (2 .. 16), in all of them, without leaving the vector registers
+template <int LANES> __device__ __forceinline__ uint32_t or_lanes(uint32_t x)
 {
-    uint64_t a, b;   // s_bitreplicate writes every bit twice
-    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(a) : "s"(e));
-    asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(b) : "s"(o));
-    return (a & 0x5555555555555555ull) | (b & 0xaaaaaaaaaaaaaaaaull);
+    auto with = [](uint32_t v, auto ctrl) { return v | (uint32_t)__builtin_amdgcn_mov_dpp((int)v, decltype(ctrl)::value, 0xf, 0xf, true); };
+    if (LANES >= 2) x = with(x, std::integral_constant<int, 0xb1>{});    // quad_perm 1 0 3 2
+    if (LANES >= 4) x = with(x, std::integral_constant<int, 0x4e>{});    // quad_perm 2 3 0 1
+    if (LANES >= 8) x = with(x, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    if (LANES >= 16) x = with(x, std::integral_constant<int, 0x140>{});  // row_mirror
+    return x;
 }
 
 // the first `left` (at least 1) bits of a word
@@ -131,12 +139,15 @@ struct AShared {
     uint32_t before[BUILD_WAVES];               // row-compacted mode: live rows before them, by wave
 };
 
-template <typename T> struct ABlock {   // one block in a wave's registers
-    typename Pattern<sizeof(T)>::type x[A_ROWS][sizeof(T) == 4 ? 2 : 1];   // lane <-> k; 16-bit: two neighbouring k per lane
-    uint32_t kb[A_ROWS];   // 16-bit: the byte that holds the lane's keep bits
-    uint64_t kw;           // otherwise: keep word of (row t, half h), in lane t * A_WORDS + h
+template <typename T> struct ABlock {   // one block in a wave's registers: lane <-> k (and k + 64)
+    static constexpr int REGS = sizeof(T) == 2 ? A_ROWS / 2 : A_ROWS;   // 16-bit: rows 2t and 2t + 1 share a register
+    typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type x[REGS][Tile<T>::A_WORDS];
+    uint64_t kw;   // keep word of (row t, half h), in lane t * A_WORDS + h
 };
 
+// v_writelane_b32 and DPP instead of selects, wave-uniform words only where a lane mask is wanted, no branch per row and
+// one base per block: the sixteen waves of a block share one scalar unit, and the scan of half-precision matrices was
+// bound by it (2048 x 16384, one column in ten: 36.5 us with pairs of k per lane, whose masks had to be interleaved there).
 template <typename T, int TEST, bool ROWS>
 __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
 {
@@ -145,43 +156,51 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
     constexpr bool WIDE = ESZ >= 4;
     constexpr int A_WORDS = Tile<T>::A_WORDS, A_COLS = 64 * A_WORDS;
     constexpr int UNITS = MMM_AB_ROWS * ESZ / 16;   // 16-byte units per column
+    constexpr uint32_t OUTSIDE = 0x80000000u;       // past the end of every buffer resource below, whatever row offset is added
     const bool has_keep = p.keep_a != nullptr;
     constexpr bool compact = ROWS;
-    auto row_of = [&](int64_t bi, int t) -> int64_t { return bi * MMM_AB_ROWS + (WIDE ? wave + 16 * t : wave * 4 + t); };
 
-    // Every load below is unconditional (indices are clamped, results masked afterwards): a load inside a
-    // branch is waited for before the next one is issued.
-    // Addresses are a wave-uniform row base plus one 32-bit lane offset that all rows share.
+    // Buffer resources that end with the last row: what lies past it, and lanes past the last column, reads as +0, which
+    // is never kept, and is not stored.  64 rows are at most 2^31 bytes (leading dimensions are below 2^22).
     const int64_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;
     const int tail = (int)min(p.K - k_lo, (int64_t)A_COLS);   // columns of these blocks that exist
+    const uint32_t row_bytes = (uint32_t)p.ldx * ESZ, map_bytes = (uint32_t)p.WA * 8u;
+    const uint32_t row0 = WIDE ? (uint32_t)wave : (uint32_t)wave * A_ROWS;
+    constexpr uint32_t ROW_STEP = WIDE ? BUILD_WAVES : 1;
+    uint32_t off[A_WORDS];
+#pragma unroll
+    for (int h = 0; h < A_WORDS; ++h) off[h] = 64 * h + lane < tail ? (uint32_t)(64 * h + lane) * ESZ : OUTSIDE;
+    const uint32_t map_at = lane < A_ROWS * A_WORDS && w_lo + lane % A_WORDS < p.WA
+                                ? (row0 + ROW_STEP * (uint32_t)(lane / A_WORDS)) * map_bytes + (uint32_t)(lane % A_WORDS) * 8u
+                                : OUTSIDE;
+    auto rows_at = [&](int64_t bi) -> uint32_t { return (uint32_t)min(p.M - bi * MMM_AB_ROWS, (int64_t)MMM_AB_ROWS); };
+    auto map_rsrc = [&](const uint64_t *map, int64_t bi) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(map + bi * MMM_AB_ROWS * p.WA + w_lo), 0,
+                                                 (int)(rows_at(bi) * map_bytes - (uint32_t)w_lo * 8u), 0x00020000);
+    };
     auto load = [&](int64_t bi, ABlock<T> &r) __attribute__((always_inline)) {
-        if constexpr (WIDE) {
-            r.kw = ~0ull;
-            if (has_keep)
-                r.kw = p.keep_a[min(row_of(bi, (lane / A_WORDS) & 3), p.M - 1) * p.WA + min(w_lo + lane % A_WORDS, p.WA - 1)];
-            uint32_t off[A_WORDS];
+        r.kw = ~0ull;
+        if (has_keep) {
+            const u32x2 k = __builtin_amdgcn_raw_buffer_load_b64(map_rsrc(p.keep_a, bi), (int)map_at, 0, 0);
+            r.kw = (uint64_t)k.y << 32 | k.x;
+        }
+        const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<T *>(static_cast<const T *>(p.X) + bi * MMM_AB_ROWS * p.ldx + k_lo), 0, (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)), 0x00020000);
 #pragma unroll
-            for (int h = 0; h < A_WORDS; ++h) off[h] = (uint32_t)min(lane + 64 * h, tail - 1) * (uint32_t)ESZ;
+        for (int t = 0; t < A_ROWS; ++t) {
+            const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
 #pragma unroll
-            for (int t = 0; t < A_ROWS; ++t) {
-                const char *xr = reinterpret_cast<const char *>(static_cast<const T *>(p.X) + min(row_of(bi, t), p.M - 1) * p.ldx + k_lo);
-#pragma unroll
-                for (int h = 0; h < A_WORDS; ++h) r.x[t][h] = *reinterpret_cast<const pattern *>(xr + off[h]);
-            }
-        } else {
-            // two neighbouring k per lane and load, at any 2-byte alignment; the last column of an odd K is read
-            // together with the one before it, so that nothing past the row is touched
-            typedef uint32_t u32_any __attribute__((aligned(2), may_alias));
-            typedef uint16_t u16_any __attribute__((may_alias));
-            const uint32_t off = (uint32_t)min(2 * lane + 2, tail) * 2u;   // from two elements before the block
-            const uint32_t koff = (uint32_t)min(2 * lane, tail - 1) >> 3;
-#pragma unroll
-            for (int t = 0; t < A_ROWS; ++t) {
-                const int64_t row = min(row_of(bi, t), p.M - 1);
-                const char *xr = reinterpret_cast<const char *>(static_cast<const T *>(p.X) + row * p.ldx + k_lo);
-                r.x[t][0] = p.K > 1 ? *reinterpret_cast<const u32_any *>(xr - 4 + off) : (uint32_t)*reinterpret_cast<const u16_any *>(xr);
-                r.kb[t] = 0xffu;
-                if (has_keep) r.kb[t] = (reinterpret_cast<const uint8_t *>(p.keep_a + row * p.WA + w_lo))[koff];
+            for (int h = 0; h < A_WORDS; ++h) {
+                const int at = (int)(off[h] + row);
+                if constexpr (ESZ == 8) {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, 0);
+                    r.x[t][h] = (uint64_t)v.y << 32 | v.x;
+                } else if constexpr (ESZ == 4) {
+                    r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, 0);
+                } else {
+                    const uint32_t v = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, 0);
+                    r.x[t / 2][h] = t & 1 ? r.x[t / 2][h] | v << 16 : v;
+                }
             }
         }
     };
@@ -207,107 +226,98 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
     for (int64_t bi = bi0; bi < bi1; ++bi) {
         const int st = (int)(bi - bi0) & 1;
         char *const stage = sh.stage[st];
-        uint64_t word[A_ROWS][A_WORDS];   // bitmap words (wave-uniform)
-        // elements past the edge of X become +0, which is never kept
-        const bool edge = tail < A_COLS || (bi + 1) * MMM_AB_ROWS > p.M;   // wave-uniform
-        if constexpr (WIDE) {
-            if (edge) {
+        uint64_t word[A_ROWS][A_WORDS];   // bitmap words: wave-uniform, the lane masks of what stays
+        auto words = [&](auto keep) __attribute__((always_inline)) {
+            constexpr bool KEEP = decltype(keep)::value;
 #pragma unroll
-                for (int t = 0; t < A_ROWS; ++t)
-#pragma unroll
-                    for (int h = 0; h < A_WORDS; ++h)
-                        if (row_of(bi, t) >= p.M || 64 * h + lane >= tail) cur.x[t][h] = 0;
-            }
-            pattern u[A_ROWS][A_WORDS];
-            const pattern lo1 = (pattern)p.test.lo1, len1 = (pattern)p.test.len1, lo2 = (pattern)p.test.lo2, len2 = (pattern)p.test.len2;
-#pragma unroll
-            for (int t = 0; t < A_ROWS; ++t)
-#pragma unroll
-                for (int h = 0; h < A_WORDS; ++h) {
-                    const pattern x = cur.x[t][h], v = TEST == TEST_MAGNITUDE ? x & Pattern<ESZ>::magnitude : x;
-                    uint64_t m = ballot64(v - lo1 < len1);
-                    if (TEST == TEST_TWO_RANGES) m |= ballot64(v - lo2 < len2);
-                    if (has_keep) m &= readlane64(cur.kw, t * A_WORDS + h);   // wave-uniform branch
-                    word[t][h] = m;
-                    u[t][h] = __builtin_amdgcn_inverse_ballot_w64(m) ? x : (pattern)0;   // the word is the lane mask of what stays
-                }
-#pragma unroll
-            for (int h = 0; h < A_WORDS; ++h) {
-                const int k = 64 * h + lane;
-                char *at = stage + k * (UNITS * 16) + ((wave ^ (k & 15)) << 4);
-                if constexpr (ESZ == 4) {
-                    *reinterpret_cast<uint4 *>(at) = make_uint4(u[0][h], u[1][h], u[2][h], u[3][h]);
-                } else {
-                    *reinterpret_cast<ulong2 *>(at) = make_ulong2(u[0][h], u[1][h]);
-                    *reinterpret_cast<ulong2 *>(at + 256) = make_ulong2(u[2][h], u[3][h]);
-                }
-            }
-        } else {
-            typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-            if (edge) {
+            for (int h = 0; h < A_WORDS; ++h)
 #pragma unroll
                 for (int t = 0; t < A_ROWS; ++t) {
-                    if (2 * lane == tail - 1 && p.K > 1) cur.x[t][0] >>= 16;
-                    if (row_of(bi, t) >= p.M || 2 * lane >= tail) cur.x[t][0] = 0;
-                    if (2 * lane + 1 >= tail) cur.x[t][0] &= 0xffffu;
+                    uint64_t m;
+                    if constexpr (WIDE) {
+                        const pattern v = TEST == TEST_MAGNITUDE ? cur.x[t][h] & Pattern<ESZ>::magnitude : cur.x[t][h];
+                        m = ballot64(v - (pattern)p.test.lo1 < (pattern)p.test.len1);
+                        if (TEST == TEST_TWO_RANGES) m |= ballot64(v - (pattern)p.test.lo2 < (pattern)p.test.len2);
+                    } else {
+                        typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+                        const uint32_t v = TEST == TEST_MAGNITUDE ? cur.x[t / 2][h] & 0x7fff7fffu : cur.x[t / 2][h];
+                        const u16x2 lo1 = {(uint16_t)p.test.lo1, (uint16_t)p.test.lo1}, lo2 = {(uint16_t)p.test.lo2, (uint16_t)p.test.lo2};
+                        const u16x2 y = __builtin_bit_cast(u16x2, v) - lo1;
+                        m = ballot64(y[t & 1] < (uint16_t)p.test.len1);
+                        if (TEST == TEST_TWO_RANGES) {
+                            const u16x2 z = __builtin_bit_cast(u16x2, v) - lo2;
+                            m |= ballot64(z[t & 1] < (uint16_t)p.test.len2);
+                        }
+                    }
+                    if (KEEP) m &= readlane64(cur.kw, t * A_WORDS + h);
+                    word[t][h] = m;
                 }
-            }
-            uint32_t d[A_ROWS];
+        };
+        if (has_keep)
+            words(std::true_type{});
+        else
+            words(std::false_type{});
 #pragma unroll
-            for (int t = 0; t < A_ROWS; ++t) {
-                d[t] = cur.x[t][0];
-                if (has_keep) {   // wave-uniform branch; dropped elements become +0, which fails every test
-                    const uint32_t kbit = cur.kb[t] >> ((2 * lane) & 7);
-                    d[t] &= (uint32_t)((int)(kbit << 31) >> 31) & 0xffffu | (uint32_t)((int)(kbit << 30) >> 31) & 0xffff0000u;
+        for (int h = 0; h < A_WORDS; ++h) {
+            const int k = 64 * h + lane;
+            if constexpr (WIDE) {
+                pattern u[A_ROWS];
+#pragma unroll
+                for (int t = 0; t < A_ROWS; ++t) u[t] = __builtin_amdgcn_inverse_ballot_w64(word[t][h]) ? cur.x[t][h] : (pattern)0;
+                char *at = stage + k * (UNITS * 16) + ((wave ^ (k & 15)) << 4);
+                if constexpr (ESZ == 4) {
+                    *reinterpret_cast<uint4 *>(at) = make_uint4(u[0], u[1], u[2], u[3]);
+                } else {
+                    *reinterpret_cast<ulong2 *>(at) = make_ulong2(u[0], u[1]);
+                    *reinterpret_cast<ulong2 *>(at + 256) = make_ulong2(u[2], u[3]);
                 }
-                const uint32_t v = TEST == TEST_MAGNITUDE ? d[t] & 0x7fff7fffu : d[t];
-                const u16x2 lo1 = {(uint16_t)p.test.lo1, (uint16_t)p.test.lo1}, lo2 = {(uint16_t)p.test.lo2, (uint16_t)p.test.lo2};
-                const u16x2 y = __builtin_bit_cast(u16x2, v) - lo1;
-                uint64_t me = ballot64(y.x < (uint16_t)p.test.len1), mo = ballot64(y.y < (uint16_t)p.test.len1);
-                if (TEST == TEST_TWO_RANGES) {
-                    const u16x2 z = __builtin_bit_cast(u16x2, v) - lo2;
-                    me |= ballot64(z.x < (uint16_t)p.test.len2);
-                    mo |= ballot64(z.y < (uint16_t)p.test.len2);
-                }
-                word[t][0] = interleave((uint32_t)me, (uint32_t)mo);
-                word[t][1] = interleave((uint32_t)(me >> 32), (uint32_t)(mo >> 32));
-                d[t] &= (__builtin_amdgcn_inverse_ballot_w64(me) ? 0xffffu : 0u) | (__builtin_amdgcn_inverse_ballot_w64(mo) ? 0xffff0000u : 0u);
+            } else {   // rows 4w .. 4w+3
+                uint32_t d[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+                    d[t] = cur.x[t][h] & ((__builtin_amdgcn_inverse_ballot_w64(word[2 * t][h]) ? 0xffffu : 0u) |
+                                          (__builtin_amdgcn_inverse_ballot_w64(word[2 * t + 1][h]) ? 0xffff0000u : 0u));
+                *reinterpret_cast<uint2 *>(stage + k * 128 + ((wave ^ (((k >> 1) & 7) << 1)) << 3)) = make_uint2(d[0], d[1]);
             }
-            // rows 4w .. 4w+3 of columns 2 lane and 2 lane + 1
-            char *at = stage + (2 * lane) * 128 + ((wave ^ ((lane & 7) << 1)) << 3);
-            *reinterpret_cast<uint2 *>(at) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x05040100u), __builtin_amdgcn_perm(d[3], d[2], 0x05040100u));
-            *reinterpret_cast<uint2 *>(at + 128) = make_uint2(__builtin_amdgcn_perm(d[1], d[0], 0x07060302u), __builtin_amdgcn_perm(d[3], d[2], 0x07060302u));
         }
-        // bitmap words: lane t * A_WORDS + h stores the word of (row t, half h)
-        uint64_t mine = 0;
+        // lane t * A_WORDS + h takes the word of (row t, half h)
+        uint32_t mine_lo = 0, mine_hi = 0;
 #pragma unroll
         for (int t = 0; t < A_ROWS; ++t)
 #pragma unroll
-            for (int h = 0; h < A_WORDS; ++h) mine = __builtin_amdgcn_inverse_ballot_w64(1ull << (t * A_WORDS + h)) ? word[t][h] : mine;
-        if (lane < 4) {   // column-any words of this wave's rows, by 32-row half of the block
-            const int t32 = lane >> 1, h = lane & 1;
-            constexpr int H = A_WORDS - 1;   // h = 1 with one word: repeats it, not read
-            uint64_t any;
-            if (WIDE)
-                any = t32 ? (h ? word[2][H] | word[3][H] : word[2][0] | word[3][0]) : (h ? word[0][H] | word[1][H] : word[0][0] | word[1][0]);
-            else
-                any = t32 != wave / (BUILD_WAVES / 2) ? 0ull
-                    : h ? word[0][H] | word[1][H] | word[2][H] | word[3][H] : word[0][0] | word[1][0] | word[2][0] | word[3][0];
-            sh.any[st][wave][t32][h] = any;
+            for (int h = 0; h < A_WORDS; ++h) {
+                mine_lo = mmm_writelane((uint32_t)word[t][h], (uint32_t)(t * A_WORDS + h), mine_lo);
+                mine_hi = mmm_writelane((uint32_t)(word[t][h] >> 32), (uint32_t)(t * A_WORDS + h), mine_hi);
+            }
+        {   // column-any words of this wave's rows, by 32-row half of the block (4- and 8-byte types: rows t < 2 and t >= 2)
+            auto other = [](uint32_t v, auto ctrl) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, decltype(ctrl)::value, 0xf, 0xf, true); };
+            typedef std::integral_constant<int, 0xb1> Swap1;      // quad_perm 1 0 3 2
+            typedef std::integral_constant<int, 0x4e> Swap2;      // quad_perm 2 3 0 1
+            typedef std::integral_constant<int, 0x141> Mirror8;   // row_half_mirror
+            auto any_of = [&](uint32_t v) {
+                if constexpr (ESZ == 8) return v | other(v, Swap1{});
+                v |= other(v, Swap2{});
+                if constexpr (ESZ == 2) v |= other(other(v, Mirror8{}), Swap1{});
+                return v;
+            };
+            const uint64_t any = (uint64_t)any_of(mine_hi) << 32 | any_of(mine_lo);
+            if (ESZ == 8) {
+                if (lane < 4 && (lane & 1) == 0) sh.any[st][wave][lane >> 1][0] = any;
+            } else if (ESZ == 4) {
+                if (lane < 8 && (lane & 2) == 0) sh.any[st][wave][lane >> 2][lane & 1] = any;
+            } else {
+                if (lane < 4) sh.any[st][wave][lane >> 1][lane & 1] = lane >> 1 == wave / (BUILD_WAVES / 2) ? any : 0ull;
+            }
         }
         if (bi + 1 < bi1) load(bi + 1, cur);
-        if (lane < A_ROWS * A_WORDS && row_of(bi, lane / A_WORDS) < p.M && w_lo + lane % A_WORDS < p.WA)
-            p.a_bits[row_of(bi, lane / A_WORDS) * p.WA + w_lo + lane % A_WORDS] = mine;
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{mine_lo, mine_hi}, map_rsrc(p.a_bits, bi), (int)map_at, 0, 0);
         __syncthreads();
         if (wave == 0) {   // lane (t32, h, wave): OR over the sixteen waves
             const int t32 = lane >> 5, h = (lane >> 4) & 1;
             const uint64_t any = sh.any[st][lane & 15][t32][h];
             uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
-#pragma unroll
-            for (int d = 1; d < 16; d <<= 1) {
-                lo |= (uint32_t)__shfl_xor((int)lo, d, 64);
-                hi |= (uint32_t)__shfl_xor((int)hi, d, 64);
-            }
+            lo = or_lanes<16>(lo);
+            hi = or_lanes<16>(hi);
             const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
             if ((lane & 15) == 0 && tile < p.MT && h < A_WORDS && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
         }
@@ -352,9 +362,6 @@ struct BShared {
     int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
 };
-
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Rows k' = seg*128 .. of the numbering given by `rows`, into sh.kk; returns K'.
 __device__ __forceinline__ uint32_t number_rows(const BuildParams &p, int64_t seg, int lane, int wave, BShared &sh)
@@ -412,6 +419,10 @@ template <int LPB> __device__ __forceinline__ uint32_t squeeze(uint64_t x)
     return (uint32_t)((x & 1u) | (x >> 15 & 2u) | (x >> 30 & 4u) | (x >> 45 & 8u));   // 16
 }
 
+// What bounds this for a few workgroups is latency, and of that the scalar unit that the sixteen waves share: per row the
+// occupancy stays in the vector registers (one bit per lane, collected with the lane's other rows, then OR'ed over the
+// lanes of a block for all rows at once), addresses come from one buffer resource per wave, and lanes with nothing to
+// store are given an offset past its end instead of being branched around.
 // ROWS (row-compacted mode): the rows are the live rows k' = 128 seg .., and the transposed map is over k'.
 // Returns false where ROWS finds no live row in the segment.  carry: doubles in 32-wide blocks fill half a
 // byte of a map row per column tile, so the map bits of an even tile are handed to the odd one after it.
@@ -425,8 +436,7 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
     constexpr int BPW = B_COLS / BW;                  // blocks per column tile
     constexpr bool WIDE = ESZ >= 4;
     constexpr bool SPLIT = BW < MMM_GROUP_COLS;       // a group holds two blocks
-    constexpr uint64_t REP = LPB == 2 ? 0x5555555555555555ull : LPB == 4 ? 0x1111111111111111ull : LPB == 8 ? 0x0101010101010101ull : 0x0001000100010001ull;
-    constexpr uint64_t GREP = LPG == 4 ? 0x1111111111111111ull : 0x0101010101010101ull;
+    constexpr uint32_t NO_LOAD = 0x80000000u, NO_STORE = 0xfffffff0u;   // offsets past the ends of the buffer resources
     const int64_t col0 = ct * B_COLS, blk0 = ct * BPW;
     if (ROWS) {
         const uint32_t live = number_rows(p, seg, lane, wave, sh);
@@ -453,45 +463,55 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
         piece = krow >= 0 ? (uint32_t)(w >> (blk0 & 63)) : 0u;
     }
     u32x4 raw[B_ROWS];
-    const uint32_t nrec = (uint32_t)min((int64_t)B_COLS, p.N - col0) * ESZ;
+    const uint32_t lane_off = lane * LANE_COLS < p.N - col0 ? (uint32_t)(lane * LANE_COLS * ESZ) : NO_LOAD;   // N is a multiple of LANE_COLS
+    const uint32_t row_bytes = (uint32_t)p.ldy * ESZ;
+    const int64_t k_first = min(seg * SEG + wave * B_ROWS, p.K - 1);
+    __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(p.Y) + (k_first * p.ldy + col0) * ESZ), 0,
+                                                                 0x7fffffff, 0x00020000);
 #pragma unroll
     for (int j = 0; j < B_ROWS; ++j) {
-        const int64_t k = max((int64_t)readlane64((uint64_t)krow, j), (int64_t)0);
-        const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)piece, j);
-        const char *row = static_cast<const char *>(p.Y) + (k * p.ldy + col0) * ESZ;
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), 0, (int)nrec, 0x00020000);
-        const int off = (pj >> (lane / LPB)) & 1u ? lane * (LANE_COLS * ESZ) : 0x40000000;
+        const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)piece, j);   // nothing if there is no such row
+        const uint32_t off = (pj >> (lane / LPB)) & 1u ? lane_off : NO_LOAD;
+        uint32_t at = (uint32_t)j * row_bytes;
+        if (ROWS) {   // rows far from each other
+            const int64_t k = max((int64_t)readlane64((uint64_t)krow, j), (int64_t)0);
+            r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(p.Y) + (k * p.ldy + col0) * ESZ), 0, 0x7fffffff, 0x00020000);
+            at = 0;
+        }
         if constexpr (WIDE) {
-            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)at, 0);
         } else if (!p.y_unaligned) {
-            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)at, 0);
             raw[j] = u32x4{v.x, v.y, 0, 0};
         } else {
             uint32_t e[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) e[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, off + 2 * i, 0, 0);
+            for (int i = 0; i < 4; ++i) e[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, (int)at + 2 * i, 0);
             raw[j] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, 0, 0};
         }
     }
     uint32_t gb = 0, bbm = 0;   // rows (bit j) in which this lane's group / block is occupied
-    uint64_t mine = 0;          // lane j: the occupied blocks of row j, at multiples of LPB
+    uint64_t mine = 0;          // lane j: the lanes with a non-zero element in row j, then at multiples of LPB the occupied blocks
+    {
+        uint32_t lo = 0, hi = 0;
 #pragma unroll
-    for (int j = 0; j < B_ROWS; ++j) {
-        const uint32_t nz = ESZ == 8   ? raw[j].x | raw[j].z | ((raw[j].y | raw[j].w) & 0x7fffffffu)
-                          : ESZ == 4 ? (raw[j].x | raw[j].y | raw[j].z | raw[j].w) & 0x7fffffffu
-                                     : (raw[j].x | raw[j].y) & 0x7fff7fffu;
-        uint64_t m = ballot64(nz != 0);
-        m |= m >> 1;
-        if (LPB >= 4) m |= m >> 2;
-        if (LPB >= 8) m |= m >> 4;
-        if (LPB >= 16) m |= m >> 8;
-        m &= REP;
-        const uint64_t blocks = m * ((1u << LPB) - 1u);   // spread over the block's lanes
-        uint64_t groups = blocks;
-        if (SPLIT) groups = ((m | m >> LPB) & GREP) * ((1u << LPG) - 1u);
-        gb |= __builtin_amdgcn_inverse_ballot_w64(groups) ? 1u << j : 0u;
-        if (SPLIT) bbm |= __builtin_amdgcn_inverse_ballot_w64(blocks) ? 1u << j : 0u;
-        mine = __builtin_amdgcn_inverse_ballot_w64(1ull << j) ? m : mine;
+        for (int j = B_ROWS - 1; j >= 0; --j) {
+            const uint32_t nz = ESZ == 8   ? raw[j].x | raw[j].z | ((raw[j].y | raw[j].w) & 0x7fffffffu)
+                              : ESZ == 4 ? (raw[j].x | raw[j].y | raw[j].z | raw[j].w) & 0x7fffffffu
+                                         : (raw[j].x | raw[j].y) & 0x7fff7fffu;
+            const uint64_t m = ballot64(nz != 0);
+            gb = gb * 2 + (nz != 0 ? 1u : 0u);
+            lo = mmm_writelane((uint32_t)m, (uint32_t)j, lo);
+            hi = mmm_writelane((uint32_t)(m >> 32), (uint32_t)j, hi);
+        }
+        mine = (uint64_t)hi << 32 | lo;
+        mine |= mine >> 1;
+        if (LPB >= 4) mine |= mine >> 2;
+        if (LPB >= 8) mine |= mine >> 4;
+        if (LPB >= 16) mine |= mine >> 8;
+        gb = or_lanes<LPB>(gb);
+        bbm = gb;
+        if (SPLIT) gb = or_lanes<LPG>(gb);
     }
     sh.gbits[lane][wave] = (uint8_t)gb;
     if (SPLIT) sh.bbits[lane][wave] = (uint8_t)bbm;
@@ -534,33 +554,31 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
     const uint32_t slot0 = wave < 8 ? (uint32_t)__popcll(glo & below) : (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi & below);
     const int64_t G = ct * B_GROUPS + lane / LPG;   // this lane's group
     const bool group_ok = G < p.NG;
+    // the lists: the lanes of a group share the rows out
+#pragma unroll
+    for (int j0 = 0; j0 < B_ROWS; j0 += LPG) {
+        const uint32_t j = (uint32_t)(j0 + lane % LPG);
+        if ((gb >> j) & 1u)
+            sh.list[lane / LPG][mmm_list_pos(sizeof(T), slot0 + (uint32_t)__popc(gb & ((1u << j) - 1u)))] =
+                (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & (RING - 1u)) * SEG + (uint32_t)(wave * B_ROWS) + j);
+    }
+    if (wave == 0 && lane % LPG == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
     uint32_t slots[B_ROWS];
-    {
-        uint32_t s = slot0;
 #pragma unroll
-        for (int j = 0; j < B_ROWS; ++j) {
-            slots[j] = s;
-            s += (gb >> j) & 1u;
-        }
-    }
-    if (lane % LPG == 0) {
-#pragma unroll
-        for (int j = 0; j < B_ROWS; ++j)
-            if ((gb >> j) & 1u)
-                sh.list[lane / LPG][mmm_list_pos(sizeof(T), slots[j])] =
-                    (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & (RING - 1u)) * SEG + (uint32_t)(wave * B_ROWS + j));
-        if (wave == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
-    }
-    char *val = p.bp_val + (size_t)(G * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);   // this lane's group
+    for (int j = 0; j < B_ROWS; ++j) slots[j] = slot0 + (uint32_t)__popc(gb & ((1u << j) - 1u));
     if constexpr (WIDE) {
         // slot-major rows of 64 or 128 bytes; the slots that fill up the last quad are zero
-        constexpr int ROWB = MMM_GROUP_COLS * ESZ;
-        if (group_ok) {
+        constexpr uint32_t ROWB = MMM_GROUP_COLS * ESZ;
+        // the segment of the tile's first group; a group's area is at most 2^28 bytes, 2^29 for doubles (K < 2^22), and a tile
+        // has 16 groups, 8 of doubles
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(
+            p.bp_val + (size_t)(ct * B_GROUPS * p.KBA + seg) * (SEG * ROWB), 0, (int)0xf8000000u, 0x00020000);
+        const uint32_t mine_at = group_ok ? (uint32_t)(lane / LPG) * (uint32_t)p.KBA * (SEG * ROWB) + (uint32_t)(lane % LPG) * 16u : NO_STORE;
 #pragma unroll
-            for (int j = 0; j < B_ROWS; ++j)
-                if ((gb >> j) & 1u) *reinterpret_cast<u32x4 *>(val + slots[j] * ROWB + (lane % LPG) * 16) = raw[j];
-            if (wave < 3 && n + wave < ((n + 3u) & ~3u)) *reinterpret_cast<u32x4 *>(val + (n + wave) * ROWB + (lane % LPG) * 16) = u32x4{0, 0, 0, 0};
-        }
+        for (int j = 0; j < B_ROWS; ++j)
+            __builtin_amdgcn_raw_buffer_store_b128(raw[j], out, (int)(((gb >> j) & 1u) && group_ok ? mine_at + slots[j] * ROWB : NO_STORE), 0, 0);
+        if (wave < 3 && n + wave < ((n + 3u) & ~3u) && group_ok)
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4{0, 0, 0, 0}, out, (int)(mine_at + (n + wave) * ROWB), 0, 0);
         __syncthreads();
     } else {
         // Composed in LDS in the order of mmm_value_pos; the slots that fill up the last batch are zero.  Whole batches are
