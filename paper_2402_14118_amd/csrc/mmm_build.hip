@@ -140,15 +140,17 @@ struct AShared {
 };
 
 template <typename T> struct ABlock {   // one block in a wave's registers: lane <-> k (and k + 64)
-    static constexpr int REGS = sizeof(T) == 2 ? A_ROWS / 2 : A_ROWS;   // 16-bit: rows 2t and 2t + 1 share a register
-    typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type x[REGS][Tile<T>::A_WORDS];
+    typename std::conditional<sizeof(T) == 8, uint64_t, uint32_t>::type x[A_ROWS][Tile<T>::A_WORDS];
     uint64_t kw;   // keep word of (row t, half h), in lane t * A_WORDS + h
 };
 
 // v_writelane_b32 and DPP instead of selects, wave-uniform words only where a lane mask is wanted, no branch per row and
 // one base per block: the sixteen waves of a block share one scalar unit, and the scan of half-precision matrices was
 // bound by it (2048 x 16384, one column in ten: 36.5 us with pairs of k per lane, whose masks had to be interleaved there).
-template <typename T, int TEST, bool ROWS>
+// DEEP: two blocks ahead in registers instead of one, for 16-bit types, whose blocks are half as large, where a workgroup has
+// several (columns 2048 x 16384: 28 -> 26 us for A, 41 -> 35.4 with B; with one or two blocks per workgroup the loads past
+// the last one cost more than they gain, 6.6 -> 9 us for 512 x 8192, and so do more bytes in flight for the wider types).
+template <typename T, int TEST, bool ROWS, bool DEEP>
 __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
 {
     typedef typename Pattern<sizeof(T)>::type pattern;
@@ -159,7 +161,6 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
     constexpr uint32_t OUTSIDE = 0x80000000u;       // past the end of every buffer resource below, whatever row offset is added
     const bool has_keep = p.keep_a != nullptr;
     constexpr bool compact = ROWS;
-
     // Buffer resources that end with the last row: what lies past it, and lanes past the last column, reads as +0, which
     // is never kept, and is not stored.  64 rows are at most 2^31 bytes (leading dimensions are below 2^22).
     const int64_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;
@@ -174,18 +175,23 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                                 ? (row0 + ROW_STEP * (uint32_t)(lane / A_WORDS)) * map_bytes + (uint32_t)(lane % A_WORDS) * 8u
                                 : OUTSIDE;
     auto rows_at = [&](int64_t bi) -> uint32_t { return (uint32_t)min(p.M - bi * MMM_AB_ROWS, (int64_t)MMM_AB_ROWS); };
-    auto map_rsrc = [&](const uint64_t *map, int64_t bi) {
+    auto map_rsrc = [&](const uint64_t *map, int64_t bi, bool any) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(map + bi * MMM_AB_ROWS * p.WA + w_lo), 0,
-                                                 (int)(rows_at(bi) * map_bytes - (uint32_t)w_lo * 8u), 0x00020000);
+                                                 any ? (int)(rows_at(bi) * map_bytes - (uint32_t)w_lo * 8u) : 0, 0x00020000);
     };
+    // DEEP: always the same number of loads, so that waiting for one block's does not mean waiting for the next one's: where
+    // there is no block or no keep bitmap the buffer is empty.
     auto load = [&](int64_t bi, ABlock<T> &r) __attribute__((always_inline)) {
-        r.kw = ~0ull;
-        if (has_keep) {
-            const u32x2 k = __builtin_amdgcn_raw_buffer_load_b64(map_rsrc(p.keep_a, bi), (int)map_at, 0, 0);
+        asm volatile("" ::: "memory");
+        const bool there = bi < bi1;
+        r.kw = 0;
+        if (DEEP || has_keep) {
+            const u32x2 k = __builtin_amdgcn_raw_buffer_load_b64(map_rsrc(p.keep_a, bi, there && has_keep), (int)map_at, 0, 0);
             r.kw = (uint64_t)k.y << 32 | k.x;
         }
         const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<T *>(static_cast<const T *>(p.X) + bi * MMM_AB_ROWS * p.ldx + k_lo), 0, (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)), 0x00020000);
+            const_cast<T *>(static_cast<const T *>(p.X) + bi * MMM_AB_ROWS * p.ldx + k_lo), 0,
+            there ? (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)) : 0, 0x00020000);
 #pragma unroll
         for (int t = 0; t < A_ROWS; ++t) {
             const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
@@ -198,15 +204,16 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                 } else if constexpr (ESZ == 4) {
                     r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, 0);
                 } else {
-                    const uint32_t v = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, 0);
-                    r.x[t / 2][h] = t & 1 ? r.x[t / 2][h] | v << 16 : v;
+                    r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, 0);
                 }
             }
         }
+        asm volatile("" ::: "memory");
     };
 
-    ABlock<T> cur;
-    load(bi0, cur);
+    ABlock<T> even, odd;
+    load(bi0, even);
+    if (DEEP) load(bi0 + 1, odd);
     uint32_t base = (uint32_t)k_lo;   // image column of the blocks' first
     int cols = A_COLS;                // and how many there are
     if (compact) {   // the blocks' live columns, and how many live rows come before them
@@ -223,10 +230,16 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
             if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
         }
     }
-    for (int64_t bi = bi0; bi < bi1; ++bi) {
-        const int st = (int)(bi - bi0) & 1;
+    auto block = [&](int64_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
+        constexpr int AHEAD = decltype(ahead)::value;   // the block whose loads take this one's place
         char *const stage = sh.stage[st];
         uint64_t word[A_ROWS][A_WORDS];   // bitmap words: wave-uniform, the lane masks of what stays
+        uint32_t pair[2][A_WORDS];        // 16-bit: rows 2t and 2t + 1
+        if constexpr (!WIDE)
+#pragma unroll
+            for (int h = 0; h < A_WORDS; ++h)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) pair[t][h] = __builtin_amdgcn_perm(cur.x[2 * t + 1][h], cur.x[2 * t][h], 0x05040100u);
         auto words = [&](auto keep) __attribute__((always_inline)) {
             constexpr bool KEEP = decltype(keep)::value;
 #pragma unroll
@@ -240,7 +253,7 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                         if (TEST == TEST_TWO_RANGES) m |= ballot64(v - (pattern)p.test.lo2 < (pattern)p.test.len2);
                     } else {
                         typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-                        const uint32_t v = TEST == TEST_MAGNITUDE ? cur.x[t / 2][h] & 0x7fff7fffu : cur.x[t / 2][h];
+                        const uint32_t v = TEST == TEST_MAGNITUDE ? pair[t / 2][h] & 0x7fff7fffu : pair[t / 2][h];
                         const u16x2 lo1 = {(uint16_t)p.test.lo1, (uint16_t)p.test.lo1}, lo2 = {(uint16_t)p.test.lo2, (uint16_t)p.test.lo2};
                         const u16x2 y = __builtin_bit_cast(u16x2, v) - lo1;
                         m = ballot64(y[t & 1] < (uint16_t)p.test.len1);
@@ -275,7 +288,7 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                 uint32_t d[2];
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
-                    d[t] = cur.x[t][h] & ((__builtin_amdgcn_inverse_ballot_w64(word[2 * t][h]) ? 0xffffu : 0u) |
+                    d[t] = pair[t][h] & ((__builtin_amdgcn_inverse_ballot_w64(word[2 * t][h]) ? 0xffffu : 0u) |
                                           (__builtin_amdgcn_inverse_ballot_w64(word[2 * t + 1][h]) ? 0xffff0000u : 0u));
                 *reinterpret_cast<uint2 *>(stage + k * 128 + ((wave ^ (((k >> 1) & 7) << 1)) << 3)) = make_uint2(d[0], d[1]);
             }
@@ -309,8 +322,8 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                 if (lane < 4) sh.any[st][wave][lane >> 1][lane & 1] = lane >> 1 == wave / (BUILD_WAVES / 2) ? any : 0ull;
             }
         }
-        if (bi + 1 < bi1) load(bi + 1, cur);
-        __builtin_amdgcn_raw_buffer_store_b64(u32x2{mine_lo, mine_hi}, map_rsrc(p.a_bits, bi), (int)map_at, 0, 0);
+        if (AHEAD == 2 || bi + 1 < bi1) load(bi + AHEAD, cur);
+        __builtin_amdgcn_raw_buffer_store_b64(u32x2{mine_lo, mine_hi}, map_rsrc(p.a_bits, bi, true), (int)map_at, 0, 0);
         __syncthreads();
         if (wave == 0) {   // lane (t32, h, wave): OR over the sixteen waves
             const int t32 = lane >> 5, h = (lane >> 4) & 1;
@@ -344,6 +357,14 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
                 *reinterpret_cast<uint4 *>(img + (threadIdx.x * 16u + (uint32_t)(i * BUILD_THREADS * 16))) =
                     *reinterpret_cast<const uint4 *>(stage + at + i * (BUILD_THREADS * 16));
         }
+    };
+    if constexpr (DEEP) {
+        for (int64_t bi = bi0; bi < bi1; bi += 2) {
+            block(bi, even, 0, std::integral_constant<int, 2>{});
+            if (bi + 1 < bi1) block(bi + 1, odd, 1, std::integral_constant<int, 2>{});
+        }
+    } else {
+        for (int64_t bi = bi0; bi < bi1; ++bi) block(bi, even, (int)(bi - bi0) & 1, std::integral_constant<int, 1>{});
     }
 }
 
@@ -622,7 +643,7 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
 }
 
 // ROWS: row-compacted mode (A laid out over the live rows of B; B built over them).
-template <typename T, int TEST, int BW, bool ROWS>
+template <typename T, int TEST, int BW, bool ROWS, bool DEEP>
 __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void mmm_build_kernel(const BuildParams p)
 {
     __shared__ __align__(16) union { AShared a; BShared b; } sh;
@@ -663,7 +684,7 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
         }
     } else {
         const int64_t bi0 = (int64_t)(i / (uint32_t)p.a_units) * p.a_per_wg;
-        scan_a<T, TEST, ROWS>(p, i % (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+        scan_a<T, TEST, ROWS, DEEP>(p, i % (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
     }
 }
 
@@ -843,26 +864,30 @@ static ElementTest element_test(int32_t dtype, int32_t pred, float threshold)
 
 typedef void (*build_kernel_fn)(const BuildParams);
 
-template <typename T, int TEST, bool ROWS> static build_kernel_fn build_kernel_width(int32_t bw)
+template <typename T, int TEST, bool ROWS, bool DEEP> static build_kernel_fn build_kernel_width(int32_t bw)
 {
-    return bw == 8 ? mmm_build_kernel<T, TEST, 8, ROWS> : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS> : mmm_build_kernel<T, TEST, 32, ROWS>;
+    return bw == 8    ? mmm_build_kernel<T, TEST, 8, ROWS, DEEP>
+           : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS, DEEP>
+                      : mmm_build_kernel<T, TEST, 32, ROWS, DEEP>;
 }
-template <typename T, bool ROWS> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
+template <typename T, bool ROWS, bool DEEP> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
 {
-    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS>(bw)
-         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS>(bw)
-                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS>(bw);
+    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS, DEEP>(bw)
+         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS, DEEP>(bw)
+                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS, DEEP>(bw);
 }
-template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows)
+template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows, bool deep)
 {
-    return rows ? build_kernel_test<T, true>(mode, bw) : build_kernel_test<T, false>(mode, bw);
+    constexpr bool HALF = sizeof(T) == 2;
+    if (deep && HALF) return rows ? build_kernel_test<T, true, HALF>(mode, bw) : build_kernel_test<T, false, HALF>(mode, bw);
+    return rows ? build_kernel_test<T, true, false>(mode, bw) : build_kernel_test<T, false, false>(mode, bw);
 }
-static build_kernel_fn build_kernel(int32_t dtype, int32_t mode, int32_t bw, bool rows)
+static build_kernel_fn build_kernel(int32_t dtype, int32_t mode, int32_t bw, bool rows, bool deep)
 {
-    return dtype == MMM_F64  ? build_kernel_test<double, false>(mode, bw)   // no row-compacted mode
-         : dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows)
-         : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows)
-                             : build_kernel_rows<float>(mode, bw, rows);
+    return dtype == MMM_F64  ? build_kernel_test<double, false, false>(mode, bw)   // no row-compacted mode
+         : dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows, deep)
+         : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows, deep)
+                             : build_kernel_rows<float>(mode, bw, rows, deep);
 }
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s)
@@ -926,7 +951,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.a_per_wg = (uint32_t)per_wg;
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    hipLaunchKernelGGL(build_kernel(a.dtype, p.test.mode, m->bw, p.rows != nullptr), grid, block, 0, s, p);
+    hipLaunchKernelGGL(build_kernel(a.dtype, p.test.mode, m->bw, p.rows != nullptr, per_wg >= 4), grid, block, 0, s, p);
     return hipGetLastError();
 }
 

@@ -75,6 +75,13 @@ def test_many_steps(dtype):
             _run(w, variant=variant)
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16, synth.DT_F16], ids=["f32", "bf16", "f16"])
+@pytest.mark.parametrize("M,p_rows", [(389, 1.0), (261, 0.1)])      # seven, five blocks of A below each other, the last one ragged
+def test_many_blocks_per_builder_workgroup(M, p_rows, dtype):
+    w = synth.random_masked(M, 53001, 32, 16, 0.1, 0.1, M, dist="smallint", dtype=dtype, p_rows=p_rows)
+    _run(w)
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 def test_every_variant_and_row_count(dtype):
     for variant in range(mm.mmm_matmul_variant_count()):
