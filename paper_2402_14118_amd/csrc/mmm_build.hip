@@ -38,17 +38,6 @@ template <typename T> struct Tile {   // what a workgroup takes at a time, by el
     static constexpr int B_GROUPS = B_COLS / MMM_GROUP_COLS;
 };
 
-// Element predicate of M, decided on the bit pattern so that no denormal mode of the float pipeline can
-// change a map bit.  Every predicate, the non-zero test included, is membership of the pattern (or of the
-// pattern without its sign) in one or two ranges that the host works out (see element_test): two or three
-// integer instructions per element, where comparing order-preserving keys took about ten and made the scan
-// of X bound by the vector ALUs (2048 x 16384 ReLU: 276 of them per wave and block, 38 us).
-enum { TEST_MAGNITUDE = 0, TEST_ONE_RANGE = 1, TEST_TWO_RANGES = 2 };
-struct ElementTest {
-    int32_t mode;
-    uint64_t lo1, len1, lo2, len2;   // lo <= pattern < lo + len
-};
-
 struct BuildParams {
     const void *X;
     int64_t ldx;
@@ -842,7 +831,7 @@ template <typename F> static ElementTest element_test(int32_t pred, float thresh
     return e;
 }
 
-static ElementTest element_test(int32_t dtype, int32_t pred, float threshold)
+ElementTest mmm_element_test(int32_t dtype, int32_t pred, float threshold)
 {
     auto single = [](uint64_t v) {
         const uint32_t u = (uint32_t)v;
@@ -919,7 +908,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.KBA = m->KBA;
     p.NG = m->NG;
     p.pack = mmm_packs(m->M, a.dtype) ? 1 : 0;
-    p.test = element_test(a.dtype, a.pred, a.threshold);
+    p.test = mmm_element_test(a.dtype, a.pred, a.threshold);
     p.y_unaligned = a.dtype != MMM_F32 && a.dtype != MMM_F64 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
     p.kinfo = m->kinfo;
     p.kmap = m->kmap;

@@ -146,6 +146,18 @@ struct mmm_maps {
     mutable double plan_cost;   // estimated microseconds
 };
 
+// Element predicate of M, decided on the bit pattern so that no denormal mode of the float pipeline can
+// change a map bit.  Every predicate, the non-zero test included, is membership of the pattern (or of the
+// pattern without its sign) in one or two ranges that the host works out (see element_test): two or three
+// integer instructions per element, where comparing order-preserving keys took about ten and made the scan
+// of X bound by the vector ALUs (2048 x 16384 ReLU: 276 of them per wave and block, 38 us).
+enum { TEST_MAGNITUDE = 0, TEST_ONE_RANGE = 1, TEST_TWO_RANGES = 2 };
+struct ElementTest {
+    int32_t mode;
+    uint64_t lo1, len1, lo2, len2;   // lo <= pattern < lo + len
+};
+ElementTest mmm_element_test(int32_t dtype, int32_t pred, float threshold);
+
 struct mmm_build_args {
     // A side (X == nullptr: skip)
     const void *X;

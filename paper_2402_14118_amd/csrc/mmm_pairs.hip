@@ -10,23 +10,25 @@
 // = G = 64 / bw blocks of B, lane group g <-> block jb0 + g.  For a range of k the wave
 // intersects the bitmap row of A with the transposed B map of each of its blocks (one 64-bit
 // AND per 64 values of k, the words spread over the lanes of a group), ranks the survivors with
-// a prefix sum inside the group, writes the surviving k of every block into a short list in
-// LDS, and then walks the G lists side by side: in round t lane group g multiplies X[i, k_t(g)]
-// with its 1 x bw block of row k_t(g) of Y and adds it to its accumulator.  Lists are padded
-// with copies of their first entry (multiplied by 0) so that a batch of 8 rounds needs no
-// per-entry branch; only a lane group whose list is empty is switched off.  The bitmap
-// intersection plays the role of the paper's pattern lookup: the branch per element is taken
-// once, on 64 elements at a time.
+// a prefix sum inside the group and writes the surviving k of every block into a short list in
+// LDS.  Then the G lists are walked side by side.  A lane takes 16 bytes of a row of Y, that is
+// C16 = 2, 4 or 8 columns of one entry, so a group covers C16 entries of its list per load, and
+// sums for its columns over the entries it has seen; at the end the lanes of a group exchange
+// halves of their sums until each holds one column.  The bitmap intersection plays the role of the paper's
+// pattern lookup: the branch per element is taken once, on 64 elements at a time.
 //
-// There is no staging and no workgroup barrier on this path (two dependent memory round trips:
-// map words, then operands), which is what makes it fast for matrices of few rows, where the
-// multiplication is latency-bound.  Waves of a workgroup that share a column span split K
+// What bounds it.  Many waves: vector-memory issue, which a compute unit's waves share and which costs 8 cycles per
+// instruction up to 4 bytes per lane and 16 above, so one element of one column per lane and load was eight
+// times as many instructions as there had to be (PAIRS_MEASURED).  Few waves: the chain of
+// memory round trips.  There is no staging and no workgroup barrier on the path that takes the map of A as built; the map
+// words of the next range are requested before the lists of this one are walked, and the operands of up to four loads
+// per lane are in flight together.  Waves of a workgroup that share a column span split K
 // between them and add their partial sums in a fixed order at the end.
 //
 // The matrix-instruction kernel multiplies every listed row of B with all 64 rows of a tile of
 // A, zeros included; this kernel pays two gathers per product instead.  It needs only the two
-// bitmaps, not the blocked lists of A.  With FUSED the mask M is evaluated right here (the
-// waves of a workgroup ballot the predicate over the row of X into LDS first), so no A-side map
+// bitmaps, not the blocked lists of A.  With FUSED the mask M is evaluated right here (eight elements per lane and
+// trip: their bits are a byte of the row's bitmap in LDS), so no A-side map
 // pass is needed.
 #include <type_traits>
 
@@ -36,7 +38,6 @@ namespace {
 
 constexpr int MAX_WAVE_WORDS = 64;  // map words (64 k each) one wave intersects at a time, at most: 4096 values of k
 constexpr int LIST_SLOTS = 1024;    // list entries per wave, shared by its G lists
-constexpr int U = 8;                // list entries per batch (one 16-byte LDS read); 16 was measured slower
 constexpr int SUPER_WORDS = 1024;   // FUSED: bitmap words of the row kept in LDS at a time (65536 values of k)
 
 struct PairsParams {
@@ -50,62 +51,71 @@ struct PairsParams {
     const uint64_t *keep_a;   // FUSED: optional keep bitmap of M, M x WA words
     const uint64_t *bt_bits;  // NB x WA words
     int64_t M, K, N, NB, WA;
-    uint64_t thr_bits;        // FUSED: threshold key of the predicate
-    int32_t pred;
+    ElementTest test;         // FUSED: the predicate
     int32_t accumulate;
 };
 
-template <typename T> __device__ __forceinline__ uint32_t bits_of(T v);
-template <> __device__ __forceinline__ uint32_t bits_of<float>(float v) { return __float_as_uint(v); }
-template <> __device__ __forceinline__ uint32_t bits_of<uint16_t>(uint16_t v) { return (uint32_t)v << 16; }   // bf16
-template <> __device__ __forceinline__ uint32_t bits_of<_Float16>(_Float16 v) { return __float_as_uint((float)v); }
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef double doublex2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t pairs_order_key(uint32_t u)
-{
-    if ((u & 0x7fffffffu) == 0) u = 0;
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
+// 16 bytes of a row, which starts at any element
+template <int ESZ> struct Row16;
+template <> struct Row16<2> { typedef u32x4 type __attribute__((aligned(2), may_alias)); };
+template <> struct Row16<4> { typedef u32x4 type __attribute__((aligned(4), may_alias)); };
+template <> struct Row16<8> { typedef u32x4 type __attribute__((aligned(8), may_alias)); };
 
-__device__ __forceinline__ uint64_t pairs_order_key64(uint64_t u)
-{
-    if ((u & 0x7fffffffffffffffull) == 0) u = 0;
-    return (u & 0x8000000000000000ull) ? ~u : (u | 0x8000000000000000ull);
-}
-
-// Per element type: the type products are accumulated in (float; double for double inputs), the exact
-// widening of an element to it, and the element predicate of M on the bit pattern, non-zero test
-// included (same decisions as the map builder: integer compares, NaN fails > and |.| >, denormals
-// are non-zero).  thr: the threshold key the host prepares (32-bit key in the low half for the float types).
 __device__ __forceinline__ float fma_acc(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_acc(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-template <typename T> struct Elem {
+// Per element type: the type products are accumulated in (float; double for double inputs), the exact widening of an
+// element to it, and of the elements of 16 bytes; the bit pattern the predicate is decided on (as in the map builder).
+template <typename T> struct Elem;
+template <> struct Elem<float> {
     typedef float acc;
-    static __device__ __forceinline__ acc value(T v) { return __uint_as_float(bits_of<T>(v)); }
-    static __device__ __forceinline__ bool keep(int32_t pred, T v, uint64_t thr64)
+    typedef uint32_t pattern;
+    static __device__ __forceinline__ acc value(float v) { return v; }
+    static __device__ __forceinline__ void unpack(u32x4 v, acc *out)
     {
-        const uint32_t u = bits_of<T>(v), thr = (uint32_t)thr64;
-        const uint32_t a = u & 0x7fffffffu;
-        if (pred == MMM_PRED_NONZERO) return a != 0;
-        const bool ok = a != 0 && a <= 0x7f800000u;
-        if (pred == MMM_PRED_GT) return ok && pairs_order_key(u) > thr;
-        return ok && a > thr;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = __uint_as_float(v[i]);
     }
-    static __device__ __forceinline__ T zero() { return T(0); }
+};
+template <> struct Elem<uint16_t> {   // bf16
+    typedef float acc;
+    typedef uint32_t pattern;
+    static __device__ __forceinline__ acc value(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
+    static __device__ __forceinline__ void unpack(u32x4 v, acc *out)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            out[2 * i] = __uint_as_float(v[i] << 16);
+            out[2 * i + 1] = __uint_as_float(v[i] & 0xffff0000u);
+        }
+    }
+};
+template <> struct Elem<_Float16> {
+    typedef float acc;
+    typedef uint32_t pattern;
+    static __device__ __forceinline__ acc value(_Float16 v) { return (float)v; }
+    static __device__ __forceinline__ void unpack(u32x4 v, acc *out)
+    {
+        typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+        const halfx8 x = __builtin_bit_cast(halfx8, v);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[i] = (float)x[i];
+    }
 };
 template <> struct Elem<double> {
     typedef double acc;
+    typedef uint64_t pattern;
     static __device__ __forceinline__ acc value(double v) { return v; }
-    static __device__ __forceinline__ bool keep(int32_t pred, double v, uint64_t thr)
+    static __device__ __forceinline__ void unpack(u32x4 v, acc *out)
     {
-        const uint64_t u = (uint64_t)__double_as_longlong(v);
-        const uint64_t a = u & 0x7fffffffffffffffull;
-        if (pred == MMM_PRED_NONZERO) return a != 0;
-        const bool ok = a != 0 && a <= 0x7ff0000000000000ull;
-        if (pred == MMM_PRED_GT) return ok && pairs_order_key64(u) > thr;
-        return ok && a > thr;
+        const doublex2 x = __builtin_bit_cast(doublex2, v);
+        out[0] = x.x;
+        out[1] = x.y;
     }
-    static __device__ __forceinline__ double zero() { return 0.0; }
 };
 
 __device__ __forceinline__ uint32_t pairs_xcd_id(uint32_t b, uint32_t n)
@@ -118,7 +128,7 @@ __device__ __forceinline__ uint32_t pairs_xcd_id(uint32_t b, uint32_t n)
 // 4096-wide ranges of k in turn (their partial sums are added in a fixed order at the end).
 // WAVE_WORDS: map words one wave intersects at a time (a range of 64 * WAVE_WORDS values of k).
 template <typename T, int BW, int CW, int KS, int WAVE_WORDS, bool FUSED>
-__global__ __launch_bounds__(CW *KS * 64) void mmm_pairs_kernel(const PairsParams p)
+__global__ __launch_bounds__(CW *KS * 64) __attribute__((amdgpu_waves_per_eu(FUSED ? 4 : 8, 8))) void mmm_pairs_kernel(const PairsParams p)
 {
     static_assert(WAVE_WORDS <= MAX_WAVE_WORDS && WAVE_WORDS % BW == 0, "whole words per lane, offsets fit the lists");
     constexpr int NW = CW * KS;
@@ -126,10 +136,13 @@ __global__ __launch_bounds__(CW *KS * 64) void mmm_pairs_kernel(const PairsParam
     constexpr int CAP = LIST_SLOTS / G;        // entries per list and pass
     constexpr int WPL = WAVE_WORDS / BW;       // words per lane and range
     constexpr uint32_t ESZ = (uint32_t)sizeof(T);
+    constexpr int C16 = 16 / (int)ESZ;         // columns per lane = entries of a list per load
+    constexpr int LPR = BW / C16;              // lanes per entry
     typedef typename Elem<T>::acc acc_t;
-    static_assert(CAP % U == 0, "a batch never leaves its list");
+    typedef typename Elem<T>::pattern pattern;
+    typedef typename Row16<(int)ESZ>::type row16;
 
-    __shared__ uint64_t aw[FUSED ? SUPER_WORDS : 1];   // FUSED: bitmap words of the row
+    __shared__ __align__(8) uint8_t aw[FUSED ? SUPER_WORDS * 8 : 8];   // FUSED: bitmap of the row
     __shared__ __align__(16) uint16_t lists[NW][LIST_SLOTS];
     __shared__ acc_t red[KS > 1 ? (KS - 1) * CW * 64 : 1];
 
@@ -137,6 +150,7 @@ __global__ __launch_bounds__(CW *KS * 64) void mmm_pairs_kernel(const PairsParam
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cw = wave % CW, ks = wave / CW;
     const int g = lane / BW, c = lane % BW;
+    const int entry = c / LPR, part = c % LPR;   // of a load: which entry of the list, which 16 bytes of its block
 
     // Consecutive workgroups of one XCD work on consecutive rows of the same column span, so the
     // blocks of Y and the map words of that span stay in that XCD's L2.
@@ -144,76 +158,136 @@ __global__ __launch_bounds__(CW *KS * 64) void mmm_pairs_kernel(const PairsParam
     const uint32_t ct = L / (uint32_t)p.M;
     const int64_t i = L % (uint32_t)p.M;
     const int64_t col0 = ((int64_t)ct * CW + cw) * 64;
-    const int64_t col = col0 + lane;
     const int64_t jb = col0 / BW + g;          // this lane group's block column
     const bool blk_ok = jb < p.NB;
 
     const T *Xrow = static_cast<const T *>(p.X) + i * p.ldx;
-    const uint64_t *arow = p.a_bits + i * p.WA;
-    const uint64_t *btrow = p.bt_bits + (blk_ok ? jb : 0) * p.WA;
+    // the map row of A; the map rows of the wave's blocks (K is below 2^22: a row is at most 2^19 bytes)
+    const __amdgpu_buffer_rsrc_t ab = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(p.a_bits + i * p.WA), 0, (int)(p.WA * 8), 0x00020000);
+    const int64_t jb0 = min(col0 / BW, p.NB - 1);
+    const __amdgpu_buffer_rsrc_t bt = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(p.bt_bits + jb0 * p.WA), 0,
+                                                                        (int)(min(p.NB - jb0, (int64_t)G) * p.WA * 8), 0x00020000);
+    const uint32_t bt_row = blk_ok ? (uint32_t)g * (uint32_t)p.WA * 8u : 0x40000000u;   // past the end: reads as zero
     const uint32_t ldyb = (uint32_t)p.ldy * ESZ;
     const uint32_t ldy = (uint32_t)p.ldy;   // below 2^22: a 24-bit multiplier
     // first column of the wave (wave-uniform); a lane adds a 32-bit offset to it
-    const char *Ycol = static_cast<const char *>(p.Y) + min(col0, p.N - 1) * ESZ;
-    const uint32_t lane_off = blk_ok ? (uint32_t)lane * ESZ : 0u;
+    const char *Ycol = static_cast<const char *>(p.Y) + min(col0, p.N - BW) * ESZ;
+    const uint32_t lane_off = blk_ok ? (uint32_t)(g * BW + part * C16) * ESZ : 0u;
     uint16_t *lst = &lists[wave][g * CAP];
-    acc_t acc = 0;
+    acc_t acc[C16];
+#pragma unroll
+    for (int q = 0; q < C16; ++q) acc[q] = 0;
 
     for (int64_t sw0 = 0; sw0 < p.WA; sw0 += SUPER_WORDS) {   // one trip unless FUSED and K > 65536
         const int sw = (int)min((int64_t)SUPER_WORDS, p.WA - sw0);
-        if (FUSED) {
-            __syncthreads();   // the words of the previous trip are no longer needed
-            // Every load below is unconditional (indices are clamped, results masked afterwards): a load
-            // inside a branch is waited for before the next one is issued.
-            constexpr int PU = 8;   // words per trip: their loads are in flight together
-            auto ballots = [&](auto with_keep) __attribute__((always_inline)) {
-                for (int w = wave; w < sw; w += PU * NW) {
-                    T u[PU];
-                    uint64_t kp[PU];
+        // This lane's map words of the range that starts at word rw0 of the trip: rw0 + c, rw0 + c + BW, ...  Past the end
+        // of the row of A words read as zero, so what is read of the B map there does not matter.
+        uint64_t wa[WPL], wb[WPL];
+        auto fetch = [&](int rw0) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int q = 0; q < PU; ++q) {
-                        const int wq = min(w + q * NW, sw - 1);
-                        const int64_t k = min((sw0 + wq) * 64 + lane, p.K - 1);
-                        u[q] = Xrow[k];
-                        kp[q] = ~0ull;
-                        if constexpr (decltype(with_keep)::value) kp[q] = p.keep_a[i * p.WA + sw0 + wq];
-                    }
-#pragma unroll
-                    for (int q = 0; q < PU; ++q) {
-                        const int wq = w + q * NW;
-                        const bool inside = wq < sw && (sw0 + wq) * 64 + lane < p.K;   // lanes past K are never kept
-                        const uint64_t m = __ballot(inside && Elem<T>::keep(p.pred, u[q], p.thr_bits)) & kp[q];
-                        if (lane == 0 && wq < sw) aw[wq] = m;
-                    }
+            for (int j = 0; j < WPL; ++j) {
+                const uint32_t at = (uint32_t)(sw0 + rw0 + c + j * BW) * 8u;
+                const u32x2 b = __builtin_amdgcn_raw_buffer_load_b64(bt, (int)(at + bt_row), 0, 0);
+                wb[j] = (uint64_t)b.y << 32 | b.x;
+                if (!FUSED) {
+                    const u32x2 a = __builtin_amdgcn_raw_buffer_load_b64(ab, (int)at, 0, 0);
+                    wa[j] = (uint64_t)a.y << 32 | a.x;
                 }
+            }
+        };
+        if (FUSED) fetch(ks * WAVE_WORDS);
+        if constexpr (FUSED) {
+            if (sw0 > 0) __syncthreads();   // the words of the previous trip are no longer needed
+            // Eight elements per lane: a byte of the bitmap.  The last, short one is read from K - 8 on and shifted.
+            const T *xs = Xrow + sw0 * 64;
+            const int left = (int)min((int64_t)SUPER_WORDS * 64, p.K - sw0 * 64);   // elements of the trip
+            const uint8_t *keep = p.keep_a != nullptr ? reinterpret_cast<const uint8_t *>(p.keep_a + i * p.WA + sw0) : nullptr;
+            const pattern mask = p.test.mode == TEST_MAGNITUDE ? (pattern)(~(pattern)0 >> 1 >> (ESZ == 2 ? 16 : 0)) : ~(pattern)0;
+            auto bits_of = [&](const u32x4 *v) -> uint32_t {
+                uint32_t bits = 0;
+#pragma unroll
+                for (int q = 7; q >= 0; --q) {
+                    pattern u;
+                    if constexpr (ESZ == 2)
+                        u = q & 1 ? v[0][q / 2] >> 16 : v[0][q / 2] & 0xffffu;
+                    else if constexpr (ESZ == 4)
+                        u = v[q / 4][q % 4];
+                    else
+                        u = (uint64_t)v[q / 2][(q & 1) * 2 + 1] << 32 | v[q / 2][(q & 1) * 2];
+                    u &= mask;
+                    bool in = u - (pattern)p.test.lo1 < (pattern)p.test.len1;
+                    in |= u - (pattern)p.test.lo2 < (pattern)p.test.len2;
+                    bits = bits * 2 + (in ? 1u : 0u);
+                }
+                return bits;
             };
-            if (p.keep_a != nullptr)
-                ballots(std::true_type{});
-            else
-                ballots(std::false_type{});
+            constexpr int V = 8 / C16;   // 16-byte pieces of eight elements
+            constexpr int PU = ESZ == 8 ? 1 : 2;   // trips in flight together
+            for (int w = wave * 8; w < sw; w += PU * NW * 8) {
+                u32x4 v[PU][V];
+                uint32_t kp[PU];
+                if (p.K >= 8) {
+#pragma unroll
+                    for (int q = 0; q < PU; ++q) {
+                        const int k = (w + q * NW * 8) * 64 + lane * 8;
+                        // (the trip of a short K behind a long one reaches back into that)
+                        const row16 *at = reinterpret_cast<const row16 *>(xs + min(k, left - 8));
+#pragma unroll
+                        for (int z = 0; z < V; ++z) v[q][z] = at[z];
+                        kp[q] = 0xffu;
+                        if (keep != nullptr) kp[q] = keep[min(k / 8, sw * 8 - 1)];
+                    }
+#pragma unroll
+                    for (int q = 0; q < PU; ++q) {
+                        const int k = (w + q * NW * 8) * 64 + lane * 8;
+                        const int back = k - min(k, left - 8);   // elements before k that were read
+                        const uint32_t bits = back < 8 ? bits_of(v[q]) >> back & kp[q] : 0u;
+                        if (k < sw * 64) aw[k / 8] = (uint8_t)bits;
+                    }
+                } else if (w == 0) {   // fewer than eight elements in all
+                    const int k = lane * 8;
+                    uint32_t bits = 0;
+                    for (int q = 0; q < 8; ++q) {
+                        pattern u = 0;
+                        __builtin_memcpy(&u, Xrow + min(k + q, (int)p.K - 1), ESZ);
+                        u &= mask;
+                        const bool in = u - (pattern)p.test.lo1 < (pattern)p.test.len1 || u - (pattern)p.test.lo2 < (pattern)p.test.len2;
+                        bits |= k + q < p.K && in ? 1u << q : 0u;
+                    }
+                    if (lane < 8) aw[lane] = (uint8_t)(bits & (keep != nullptr ? keep[lane] : 0xffu));
+                }
+            }
             __syncthreads();
         }
         // this wave's ranges of the trip: ranges ks, ks + KS, ... of WAVE_WORDS words each
         for (int rw0 = ks * WAVE_WORDS; rw0 < sw; rw0 += KS * WAVE_WORDS) {
             const int rw1 = min(sw, rw0 + WAVE_WORDS);
             const int64_t word0 = sw0 + rw0;               // first word of the range
-            // this lane's words of the range: rw0 + c, rw0 + c + BW, ...
+            if (!FUSED) fetch(rw0);
             uint64_t m[WPL];
             uint32_t cnt = 0;
 #pragma unroll
             for (int j = 0; j < WPL; ++j) {
                 const int wi = rw0 + c + j * BW;
-                const int wic = min(wi, rw1 - 1);   // loaded unconditionally (a load inside a branch is waited for at once), masked below
-                const uint64_t wa = FUSED ? aw[wic] : arow[sw0 + wic], wb = btrow[sw0 + wic];
-                m[j] = wi < rw1 && blk_ok ? wa & wb : 0ull;
+                uint64_t a = wa[j];
+                if (FUSED) a = wi < rw1 ? reinterpret_cast<const uint64_t *>(aw)[min(wi, rw1 - 1)] : 0ull;
+                m[j] = a & wb[j];
                 cnt += (uint32_t)__popcll(m[j]);
             }
+            if (FUSED && rw0 + KS * WAVE_WORDS < sw) fetch(rw0 + KS * WAVE_WORDS);   // while the lists of this range are walked
             // ranks: exclusive prefix of the counts inside the lane group, and the group's total
             uint32_t incl = cnt;
-#pragma unroll
-            for (int d = 1; d < BW; d <<= 1) {
-                const uint32_t o = (uint32_t)__shfl_up((int)incl, d, BW);
-                if (c >= d) incl += o;
+            auto from_below = [&](auto ctrl, bool take) {   // (a row of the cross-lane moves is 16 lanes; past its end 0 comes in)
+                const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, decltype(ctrl)::value, 0xf, 0xf, true);
+                incl += take ? o : 0u;
+            };
+            from_below(std::integral_constant<int, 0x111>{}, BW >= 16 || c >= 1);   // row_shr 1, 2, 4, 8
+            from_below(std::integral_constant<int, 0x112>{}, BW >= 16 || c >= 2);
+            from_below(std::integral_constant<int, 0x114>{}, BW >= 16 || c >= 4);
+            if (BW >= 16) from_below(std::integral_constant<int, 0x118>{}, true);
+            if (BW == 32) {   // the second row of a group adds the total of the first
+                const uint32_t o = (uint32_t)__shfl((int)incl, (lane & 32) + 15, 64);
+                incl += c >= 16 ? o : 0u;
             }
             const uint32_t first = incl - cnt;
             const uint32_t n_g = (uint32_t)__shfl((int)incl, BW - 1, BW);
@@ -231,84 +305,81 @@ __global__ __launch_bounds__(CW *KS * 64) void mmm_pairs_kernel(const PairsParam
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();   // the previous pass has read its entries
                 uint32_t pos = first - base;       // rank of this lane's next survivor within the pass (wraps below 0)
+                auto write = [&](auto whole) __attribute__((always_inline)) {   // whole: the lists fit one pass
 #pragma unroll
-                for (int j = 0; j < WPL; ++j) {
-                    uint64_t mm = m[j];
-                    const uint32_t kw = (uint32_t)(c + j * BW) * 64u;   // entries are byte offsets into the row of X
-                    while (mm != 0) {
-                        const uint32_t bit = (uint32_t)__builtin_ctzll(mm);
-                        mm &= mm - 1;
-                        if (pos < (uint32_t)CAP) lst[pos] = (uint16_t)((kw + bit) * ESZ);
-                        ++pos;
-                    }
-                }
-                const uint32_t n_here = n_g > base ? min(n_g - base, (uint32_t)CAP) : 0u;   // entries of this lane group
-                uint32_t rmax = 0, rmin = CAP;
-#pragma unroll
-                for (int q = 0; q < G; ++q) {
-                    const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)n_here, q * BW);
-                    rmax = max(rmax, v);
-                    rmin = min(rmin, v);
-                }
-                const uint32_t rend = (rmax + U - 1) / U * U;   // at most CAP
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                // pad the list up to the last batch the wave runs with copies of its first entry: a valid
-                // row of Y for this block, multiplied by 0 below
-                if (n_here != 0 && n_here < rend) {
-                    const uint16_t e0 = lst[0];
-                    for (uint32_t q = n_here + c; q < rend; q += BW) lst[q] = e0;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                }
-                __builtin_amdgcn_wave_barrier();
-                const bool alive = n_here != 0;
-                uint32_t t = 0;
-                // rounds in which every lane group has an entry
-                for (; t + U <= rmin; t += U) {
-                    const uint4 e4 = *reinterpret_cast<const uint4 *>(lst + t);
-                    const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
-                    acc_t a[U], b[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const uint32_t kb = (u & 1) ? (e[u >> 1] >> 16) : (e[u >> 1] & 0xffffu);   // k * ESZ
-                        a[u] = Elem<T>::value(*reinterpret_cast<const T *>(Xr + kb));
-                        b[u] = Elem<T>::value(*reinterpret_cast<const T *>(Yr + (__umul24(kb, ldy) + lane_off)));
-                    }
-#pragma unroll
-                    for (int u = 0; u < U; ++u) acc = fma_acc(a[u], b[u], acc);
-                }
-                // ragged ends: padded entries count for nothing, empty lists are switched off
-                for (; t < rend; t += U) {
-                    acc_t a[U], b[U];
-#pragma unroll
-                    for (int u = 0; u < U; ++u) a[u] = b[u] = 0;
-                    if (alive) {
-                        const uint4 e4 = *reinterpret_cast<const uint4 *>(lst + t);
-                        const uint32_t e[4] = {e4.x, e4.y, e4.z, e4.w};
-#pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            const uint32_t kb = (u & 1) ? (e[u >> 1] >> 16) : (e[u >> 1] & 0xffffu);
-                            a[u] = Elem<T>::value(*reinterpret_cast<const T *>(Xr + kb));
-                            b[u] = Elem<T>::value(*reinterpret_cast<const T *>(Yr + (__umul24(kb, ldy) + lane_off)));
+                    for (int j = 0; j < 2 * WPL; ++j) {
+                        uint32_t mm = (uint32_t)(m[j / 2] >> (32 * (j & 1)));
+                        const uint32_t kw = (uint32_t)((c + j / 2 * BW) * 64 + (j & 1) * 32) * ESZ;   // entries are byte offsets into the row of X
+                        while (mm != 0) {
+                            const uint32_t bit = (uint32_t)__builtin_ctz(mm);
+                            mm &= mm - 1;
+                            if (decltype(whole)::value || pos < (uint32_t)CAP) lst[pos] = (uint16_t)(kw + bit * ESZ);
+                            ++pos;
                         }
                     }
+                };
+                if (nmax <= (uint32_t)CAP)
+                    write(std::true_type{});
+                else
+                    write(std::false_type{});
+                const uint32_t n_here = n_g > base ? min(n_g - base, (uint32_t)CAP) : 0u;   // entries of this lane group
+                const uint32_t rmax = min(nmax - base, (uint32_t)CAP);                      // of the longest list
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                // UN loads of C16 entries of every list.  Lanes past the end of their list read the first row of the
+                // range, which exists, and count it for nothing.
+                auto batch = [&](uint32_t t0, auto un) __attribute__((always_inline)) {
+                    constexpr int UN = decltype(un)::value;
+                    T x[UN];
+                    u32x4 y[UN];
+                    bool valid[UN];
 #pragma unroll
-                    for (int u = 0; u < U; ++u) acc = fma_acc(t + u < n_here ? a[u] : acc_t(0), b[u], acc);
-                }
+                    for (int u = 0; u < UN; ++u) {
+                        const uint32_t t = t0 + (uint32_t)(u * C16 + entry);
+                        valid[u] = t < n_here;
+                        const uint32_t kb = valid[u] ? lst[min(t, (uint32_t)CAP - 1)] : 0u;   // k * ESZ
+                        x[u] = *reinterpret_cast<const T *>(Xr + kb);
+                        y[u] = *reinterpret_cast<const row16 *>(Yr + (__umul24(kb, ldy) + lane_off));
+                    }
+#pragma unroll
+                    for (int u = 0; u < UN; ++u) {
+                        const acc_t xv = valid[u] ? Elem<T>::value(x[u]) : acc_t(0);
+                        acc_t yv[C16];
+                        Elem<T>::unpack(valid[u] ? y[u] : u32x4{0, 0, 0, 0}, yv);
+#pragma unroll
+                        for (int q = 0; q < C16; ++q) acc[q] = fma_acc(xv, yv[q], acc[q]);
+                    }
+                };
+                uint32_t t = 0;
+                if (FUSED)
+                    for (; t + 2 * C16 < rmax; t += 4 * C16) batch(t, std::integral_constant<int, 4>{});
+                for (; t + C16 < rmax; t += 2 * C16) batch(t, std::integral_constant<int, 2>{});
+                if (t < rmax) batch(t, std::integral_constant<int, 1>{});
             }
         }
     }
 
+    // The lanes of a group that hold the same columns exchange halves of them: one column per lane is left.
+#pragma unroll
+    for (int half = C16 / 2, stride = BW / 2; half >= 1; half /= 2, stride /= 2) {
+        const bool upper = (lane & stride) != 0;
+#pragma unroll
+        for (int q = 0; q < half; ++q) {
+            const acc_t send = upper ? acc[q] : acc[q + half];
+            acc[q] = (upper ? acc[q + half] : acc[q]) + __shfl_xor(send, stride, 64);
+        }
+    }
+    const int64_t col = col0 + g * BW + part * C16 + entry;
     if (KS > 1) {   // add the partial sums of the waves that shared this column span, in wave order
-        if (ks > 0) red[((ks - 1) * CW + cw) * 64 + lane] = acc;
+        if (ks > 0) red[((ks - 1) * CW + cw) * 64 + lane] = acc[0];
         __syncthreads();
         if (ks == 0)
 #pragma unroll
-            for (int q = 1; q < KS; ++q) acc += red[((q - 1) * CW + cw) * 64 + lane];
+            for (int q = 1; q < KS; ++q) acc[0] += red[((q - 1) * CW + cw) * 64 + lane];
     }
     if (ks == 0 && col < p.N) {
         acc_t *dst = static_cast<acc_t *>(p.C) + i * p.ldc + col;
-        *dst = p.accumulate ? *dst + acc : acc;
+        *dst = p.accumulate ? *dst + acc[0] : acc[0];
     }
 }
 
@@ -332,36 +403,6 @@ template <typename T, bool FUSED> pairs_kernel_fn pick(int32_t bw, int shape)
     if (bw == 8) return pick_shape<T, 8, FUSED>(shape);
     if (bw == 16) return pick_shape<T, 16, FUSED>(shape);
     return pick_shape<T, 32, FUSED>(shape);
-}
-
-uint32_t pairs_threshold_key(int32_t pred, float threshold)
-{
-    union { float f; uint32_t u; } cv;
-    cv.f = threshold;
-    uint32_t t = cv.u;
-    const uint32_t at = t & 0x7fffffffu;
-    if (at > 0x7f800000u) return 0xffffffffu;   // NaN threshold: nothing passes
-    if (pred == MMM_PRED_GT) {
-        if (at == 0) t = 0;
-        return (t & 0x80000000u) ? ~t : (t | 0x80000000u);
-    }
-    if (pred == MMM_PRED_ABS_GT) return (t & 0x80000000u) ? 0u : at;
-    return 0;
-}
-
-uint64_t pairs_threshold_key64(int32_t pred, float threshold)
-{
-    union { double f; uint64_t u; } cv;
-    cv.f = (double)threshold;
-    uint64_t t = cv.u;
-    const uint64_t at = t & 0x7fffffffffffffffull;
-    if (at > 0x7ff0000000000000ull) return ~0ull;   // NaN threshold: nothing passes
-    if (pred == MMM_PRED_GT) {
-        if (at == 0) t = 0;
-        return (t & 0x8000000000000000ull) ? ~t : (t | 0x8000000000000000ull);
-    }
-    if (pred == MMM_PRED_ABS_GT) return (t & 0x8000000000000000ull) ? 0ull : at;
-    return 0;
 }
 
 }   // namespace
@@ -392,8 +433,7 @@ hipError_t mmm_launch_pairs(const mmm_maps *m, int32_t dtype, const void *X, int
     p.N = m->N;
     p.NB = m->NB;
     p.WA = m->WA;
-    p.pred = pred;
-    p.thr_bits = dtype == MMM_F64 ? pairs_threshold_key64(pred, threshold) : (uint64_t)pairs_threshold_key(pred, threshold);
+    if (fused) p.test = mmm_element_test(dtype, pred, threshold);
     p.accumulate = accumulate;
     // Workgroups of 8 waves x 64 columns; when that gives the machine too little to do (few rows:
     // the decode shape), fewer columns per workgroup and K shared out over several waves.
