@@ -19,8 +19,9 @@
 //
 // What bounds it.  Many waves: vector-memory issue, which a compute unit's waves share and which costs 8 cycles per
 // instruction up to 4 bytes per lane and 16 above, so one element of one column per lane and load was eight
-// times as many instructions as there had to be (PAIRS_MEASURED).  Few waves: the chain of
-// memory round trips.  There is no staging and no workgroup barrier on the path that takes the map of A as built; the map
+// times as many instructions as there had to be (maps built, 64 x 4096 x 2048 half precision: 11.8 -> 6.6 us); then the vector ALUs,
+// which write the lists and widen 16-bit elements (32 x 16384 x 4096 bf16: 384 instructions per wave, more than half of 10.7 us).
+// Few waves: the chain of memory round trips.  There is no staging and no workgroup barrier on the path that takes the map of A as built; the map
 // words of the next range are requested before the lists of this one are walked, and the operands of up to four loads
 // per lane are in flight together.  Waves of a workgroup that share a column span split K
 // between them and add their partial sums in a fixed order at the end.
@@ -385,24 +386,34 @@ __global__ __launch_bounds__(CW *KS * 64) __attribute__((amdgpu_waves_per_eu(FUS
 
 typedef void (*pairs_kernel_fn)(const PairsParams);
 
-struct PairsShape { int cw, ks; };
+struct PairsShape { int cw, ks, words; };
 
-template <typename T, int BW, bool FUSED> pairs_kernel_fn pick_shape(int shape)
+// Workgroup shapes: CW waves side by side (64 columns each), KS that share K, and the map words a wave intersects at a time.
+//   8 x 1  512 columns: many rows, or a K so short that there is nothing to share out
+//   2 x 4  few rows: 128 columns, K in four shares
+//   8 x 2, 4 x 4, 2 x 8  few rows, mask evaluated here: the predicate work is shared by 512, 256, 128 columns
+// Words: the fewest that still give every share a part of K (64 k each), so that no wave stands idle: a K of 4096 in ranges
+// of 64 words was one range, for one wave in four.
+template <typename T, int BW, bool FUSED> pairs_kernel_fn pick_shape(const PairsShape &sh)
 {
-    switch (shape) {
-    case 1: return mmm_pairs_kernel<T, BW, 2, 4, 64, FUSED>;    // few rows: 128 columns, K in four shares
-    case 2: return mmm_pairs_kernel<T, BW, 8, 2, 64, FUSED>;    // few rows, mask evaluated here: the predicate work is shared by 512 columns
-    case 3: return mmm_pairs_kernel<T, BW, 4, 4, 64, FUSED>;    // very few rows, mask evaluated here: one range of k per wave
-    default: return mmm_pairs_kernel<T, BW, 8, 1, 64, FUSED>;   // 512 columns side by side
+    constexpr int W16 = BW == 32 ? 32 : 16;   // a lane takes at least one word
+    const int w = sh.words;
+    if (sh.ks == 1)
+        return w == 16 ? mmm_pairs_kernel<T, BW, 8, 1, W16, FUSED> : w == 32 ? mmm_pairs_kernel<T, BW, 8, 1, 32, FUSED> : mmm_pairs_kernel<T, BW, 8, 1, 64, FUSED>;
+    if constexpr (!FUSED) {
+        return w == 16 ? mmm_pairs_kernel<T, BW, 2, 4, W16, FUSED> : w == 32 ? mmm_pairs_kernel<T, BW, 2, 4, 32, FUSED> : mmm_pairs_kernel<T, BW, 2, 4, 64, FUSED>;
+    } else {
+        if (sh.ks == 8) return w == 16 ? mmm_pairs_kernel<T, BW, 2, 8, W16, FUSED> : mmm_pairs_kernel<T, BW, 2, 8, 32, FUSED>;
+        if (sh.ks == 4) return w <= 32 ? mmm_pairs_kernel<T, BW, 4, 4, 32, FUSED> : mmm_pairs_kernel<T, BW, 4, 4, 64, FUSED>;
+        return w <= 32 ? mmm_pairs_kernel<T, BW, 8, 2, 32, FUSED> : mmm_pairs_kernel<T, BW, 8, 2, 64, FUSED>;
     }
 }
-constexpr PairsShape kShapes[] = {{8, 1}, {2, 4}, {8, 2}, {4, 4}};
 
-template <typename T, bool FUSED> pairs_kernel_fn pick(int32_t bw, int shape)
+template <typename T, bool FUSED> pairs_kernel_fn pick(int32_t bw, const PairsShape &sh)
 {
-    if (bw == 8) return pick_shape<T, 8, FUSED>(shape);
-    if (bw == 16) return pick_shape<T, 16, FUSED>(shape);
-    return pick_shape<T, 32, FUSED>(shape);
+    if (bw == 8) return pick_shape<T, 8, FUSED>(sh);
+    if (bw == 16) return pick_shape<T, 16, FUSED>(sh);
+    return pick_shape<T, 32, FUSED>(sh);
 }
 
 }   // namespace
@@ -436,21 +447,36 @@ hipError_t mmm_launch_pairs(const mmm_maps *m, int32_t dtype, const void *X, int
     if (fused) p.test = mmm_element_test(dtype, pred, threshold);
     p.accumulate = accumulate;
     // Workgroups of 8 waves x 64 columns; when that gives the machine too little to do (few rows:
-    // the decode shape), fewer columns per workgroup and K shared out over several waves.
+    // the decode shape), fewer columns per workgroup and K shared out over several waves, unless there is next to nothing of it.
+    // With the mask evaluated here every column span repeats the predicate, so the spans are as wide as leaves every compute unit a
+    // workgroup (4 x 16384 x 4096 bf16: 128, 256 columns: 5.7, 6.6 us; 16 x 8192 x 4096, where 128 make two rounds: 8.7, 5.6).
     const int64_t wide = (m->N + 511) / 512 * m->M;
-    const int shape = wide >= 1024 ? 0 : !fused ? 1 : m->M <= 16 ? 3 : 2;
-    const PairsShape sh = kShapes[shape];
+    PairsShape sh{8, 1, 64};
+    if (wide < 1024 && (fused || m->WA > 32)) {
+        if (!fused)
+            sh = {2, 4, 64};
+        else if ((m->N + 127) / 128 * m->M <= 256)
+            sh = {2, 8, 32};
+        else if (m->M <= 16)
+            sh = {4, 4, 64};
+        else
+            sh = {8, 2, 64};
+    }
+    if (m->WA <= 16 * sh.ks)
+        sh.words = 16;
+    else if (m->WA <= 32 * sh.ks)
+        sh.words = 32;
     const int64_t span = sh.cw * 64;
     const int64_t ctiles = (m->N + span - 1) / span;
     const int64_t wgs = ctiles * m->M;
     if (wgs <= 0 || wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     pairs_kernel_fn fn;
     if (fused)
-        fn = dtype == MMM_F64 ? pick<double, true>(m->bw, shape) : dtype == MMM_BF16 ? pick<uint16_t, true>(m->bw, shape) : dtype == MMM_F16 ? pick<_Float16, true>(m->bw, shape)
-                                                                                         : pick<float, true>(m->bw, shape);
+        fn = dtype == MMM_F64 ? pick<double, true>(m->bw, sh) : dtype == MMM_BF16 ? pick<uint16_t, true>(m->bw, sh) : dtype == MMM_F16 ? pick<_Float16, true>(m->bw, sh)
+                                                                                         : pick<float, true>(m->bw, sh);
     else
-        fn = dtype == MMM_F64 ? pick<double, false>(m->bw, shape) : dtype == MMM_BF16 ? pick<uint16_t, false>(m->bw, shape) : dtype == MMM_F16 ? pick<_Float16, false>(m->bw, shape)
-                                                                                          : pick<float, false>(m->bw, shape);
+        fn = dtype == MMM_F64 ? pick<double, false>(m->bw, sh) : dtype == MMM_BF16 ? pick<uint16_t, false>(m->bw, sh) : dtype == MMM_F16 ? pick<_Float16, false>(m->bw, sh)
+                                                                                          : pick<float, false>(m->bw, sh);
     (void)hipGetLastError();
     hipLaunchKernelGGL(fn, dim3((uint32_t)wgs), dim3((uint32_t)(sh.cw * sh.ks * 64)), 0, s, p);
     return hipGetLastError();

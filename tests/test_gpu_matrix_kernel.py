@@ -1,4 +1,4 @@
-"""The matrix kernel's operands at the edges of their geometry: blocks of A of 64 rows x 128 columns (64 for doubles in
+"""The kernels at the edges of their geometry: blocks of A of 64 rows x 128 columns (64 for doubles in
 the builder), groups of 16 columns, segments of 128 k whose lists are walked in batches of 16 or 32 slots, column tiles of
 256 (128).  Exact on integer inputs, against the CPU oracle, for every element type."""
 import numpy as np
@@ -117,3 +117,30 @@ def test_values_that_must_not_reach_the_arithmetic(dtype):
     run = HipRun(w)
     run.eng.set_path(mm.MMM_PATH_MATRIX)
     np.testing.assert_array_equal(run.run()[2], C_ref)
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("M,K,N,bw", [
+    (1, 7, 8, 8), (3, 8, 72, 8), (2, 1025, 96, 32),     # fewer than eight k; a whole byte of k; one k behind the last whole byte
+    (5, 2049, 144, 16), (20, 4097, 272, 16), (40, 9001, 40, 8), (7, 17000, 64, 32),   # ranges of 16, 32, 64 words of k
+    (18, 66001, 32, 16),                                # more k than the bitmap in LDS holds
+    (300, 300, 520, 8), (1030, 70, 32, 16), (1040, 2100, 16, 16),   # many rows
+])
+def test_pair_kernel_shapes(M, K, N, bw, dtype):
+    """Every workgroup shape and range size of the pair kernel, with the map of A built and with the mask evaluated in the
+    multiplication, at odd leading dimensions."""
+    w = synth.random_masked(M, K, N, bw, 0.15, 0.3, M + K + N, dist="smallint", dtype=dtype)
+    C_ref = oracle.run_workload(w)[2]
+    run = HipRun(w, ldx=K + 1, ldy=N + 3, ldc=N + 1)
+    run.eng.set_path(mm.MMM_PATH_PAIRS)
+    run.build()
+    for fused in (False, True):
+        print("fused", fused, flush=True)
+        run.Cbuf.fill_(float("nan"))
+        if fused:
+            run.eng.matmul_fused(run.X, run.Y, run.C, w.pred, w.threshold, run.keep_a)
+        else:
+            run.matmul()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+        assert torch.isnan(run.Cbuf[:, N:]).all()
