@@ -104,7 +104,7 @@ size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 // estimates are sums of terms with a meaning each; their coefficients were fitted to the measured times of about 45000
 // launches, every variant and a dozen splits on 1850 random problems (200 to 4096 in each dimension, few rows with K up
 // to 16384, densities .05 to 1, all types).  They are within 9 % (matrix) and 14 % (pairs) of the measurements, and the choice made
-// from them costs 2 to 3 % more than the best one; the former thresholds cost 17 % among the matrix kernel's plans and
+// from them costs 1 to 2 % more than the best one; the former thresholds cost 17 % among the matrix kernel's plans and
 // 17 (doubles) to 37 % (16-bit) over all.
 struct MatrixCost {   // microseconds
     double launch;        // per call (fitted with the operands in L2, and 1 us more: after a build they are not)
@@ -131,9 +131,9 @@ struct PairsCost {   // microseconds
     double waves;      // per 10^5 waves
 };
 constexpr PairsCost kPairsCost[3] = {
-    {2.91, 3.49, 21.6, {751, 372, 248}, 1.48, 16.3},
-    {2.25, 3.98, 16.5, {751, 401, 251}, 2.73, 16.4},
-    {4.52, 0.00, 51.4, {1481, 1127, 864}, 16.8, 18.1},
+    {4.08, 2.24, 26.1, {510, 262, 132}, 2.32, 0.0},
+    {2.11, 3.73, 21.5, {676, 341, 209}, 4.45, 0.0},
+    {4.31, 0.00, 28.8, {860, 512, 496}, 15.4, 3.3},
 };
 
 int cost_class(int32_t dt) { return dt == MMM_F64 ? 2 : dt == MMM_F32 ? 1 : 0; }
