@@ -74,6 +74,7 @@ struct mmm_plan {
     int32_t variant;
     int32_t split_k;
     int32_t tiles_m, tiles_n;
+    int32_t panel;             // tile columns that are gone through together (see panel_width)
     int32_t chunks_total;      // ceil(K / KC)
     int32_t chunks_per_split;
     int64_t workgroups;
@@ -177,7 +178,8 @@ struct mmm_build_args {
 
 struct mmm_variant_info {
     const char *name;
-    int32_t TM, TN, KC, rows, k_ranges;   // k_ranges: ranges of K inside a workgroup; rows: rows of C actually computed (64, or 32 for short matrices)
+    int32_t TM, TN, KC, rows, k_ranges;   // rows: rows of C actually computed (64, or 32 for short matrices); k_ranges: ranges of K inside a workgroup
+    bool doubles;                         // takes double inputs
 };
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
