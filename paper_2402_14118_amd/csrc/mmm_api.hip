@@ -102,26 +102,26 @@ size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 //
 // A table of thresholds cannot follow this choice: it depends on the shape, both densities and how evenly the
 // workgroups fall on 256 compute units.  So both kernels' times are estimated and the least is taken.  The
-// estimates are sums of terms with a meaning each; their coefficients were fitted to the measured times of about 45000
-// launches, every variant and a dozen splits on 1850 random problems (200 to 4096 in each dimension, few rows with K up
-// to 16384, densities .05 to 1, all types).  They are within 9 % (matrix) and 14 % (pairs) of the measurements, and the choice made
-// from them costs 1 to 2 % more than the best one; the former thresholds cost 17 % among the matrix kernel's plans and
-// 17 (doubles) to 37 % (16-bit) over all.
+// estimates are sums of terms with a meaning each; their coefficients are a least-squares fit to 2000 random problems (200
+// to 4096 in each dimension, few rows with K up to 16384, densities .05 to 1, all types), built and multiplied in turn with
+// every variant and a dozen splits.  They are within 8 % (matrix) and 12 % (pairs) of the measurements, and what is chosen
+// from them takes 1 to 2 % longer than the best choice; the former thresholds, 17 % among the matrix kernel's
+// plans and 17 (doubles) to 37 % (16-bit) over both kernels.
 struct MatrixCost {   // microseconds
-    double launch;        // per call (fitted with the operands in L2, and 1 us more: after a build they are not)
+    double launch;        // per call
     double latency;       // per step and batch of its longest lists: nobody hides the first wave's waiting
     double step;          // per step of each workgroup on the fullest compute unit: barrier, copy of a block of A
     double multiply;      // per 16 columns, row tile of 16 and list unit (quad of k; 16-bit: batch of 32) there
     double wave;          // per 16 columns of each workgroup there: prologue, writing C
     double workgroup;     // per workgroup there
-    double reduce;        // second launch that adds the splits (half of it is the host's: set, not fitted)
+    double reduce;        // second launch that adds the splits
     double reduce_mega;   // per 2^20 partial sums of C
     double image_giga;    // per 10^9 bytes of A copied to LDS
 };
 constexpr MatrixCost kMatrixCost[3] = {   // 2-, 4-, 8-byte elements
-    {3.784, 0.1426, 0.0341, 0.0023, 0.0803, 0.494, 3.00, 1.371, 46.8},
-    {3.902, 0.1762, 0.0920, 0.0030, 0.0756, 0.185, 3.00, 1.101, 34.4},
-    {3.729, 0.2370, 0.1927, 0.0061, 0.1607, 0.870, 3.00, 2.385, 47.6},
+    {3.162, 0.2208, 0.0321, 0.0011, 0.1084, 0.571, 2.0, 1.094, 47.1},
+    {3.524, 0.1805, 0.1198, 0.0031, 0.0747, 0.561, 2.0, 1.159, 24.9},
+    {3.210, 0.3107, 0.4623, 0.0059, 0.1092, 1.362, 3.3, 2.257, 30.9},
 };
 struct PairsCost {   // microseconds
     double launch;     // per call
@@ -129,12 +129,11 @@ struct PairsCost {   // microseconds
     double word;       // per 10^5 ranges of all rows and 64-column spans: intersecting the maps
     double product[3]; // per 10^9 surviving products, blocks of 8, 16, 32
     double list;       // per 100 entries of one wave's lists, one after another
-    double waves;      // per 10^5 waves
 };
 constexpr PairsCost kPairsCost[3] = {
-    {4.08, 2.24, 26.1, {510, 262, 132}, 2.32, 0.0},
-    {2.11, 3.73, 21.5, {676, 341, 209}, 4.45, 0.0},
-    {4.31, 0.00, 28.8, {860, 512, 496}, 15.4, 3.3},
+    {3.39, 2.24, 26.3, {521, 275, 140}, 1.1},
+    {1.75, 3.50, 24.7, {632, 312, 191}, 4.8},
+    {3.90, 0.00, 30.2, {863, 549, 463}, 15.9},
 };
 
 int cost_class(int32_t dt) { return dt == MMM_F64 ? 2 : dt == MMM_F32 ? 1 : 0; }
@@ -184,8 +183,8 @@ int32_t panel_width(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const
     const double batch = elem_size(dt) == 2 ? 32.0 : 16.0;
     const double a = (double)(MMM_AB_ROWS * MMM_AB_COLS), b = (double)mmm_variant(p.variant).TN * q.batches * batch;   // elements per step
     const double t = std::max(1.0, (double)p.tiles_m * p.tiles_n / 8.0);
-    const int64_t w = (int64_t)(std::sqrt(t * a / b) + 0.5);
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(w, p.tiles_n));
+    const int64_t panels = std::max<int64_t>(1, (int64_t)((double)p.tiles_n / std::sqrt(t * a / b) + 0.5));   // of about equal width
+    return (int32_t)std::max<int64_t>(1, (p.tiles_n + panels - 1) / panels);
 }
 
 double pairs_cost(const mmm_maps *m, int32_t dt)
@@ -194,8 +193,7 @@ double pairs_cost(const mmm_maps *m, int32_t dt)
     const double spans = (double)m->M * (double)((m->N + 63) / 64), products = (double)m->stats_macs;
     const int64_t ranges = (m->WA + 63) / 64, shares = (m->N + 511) / 512 * m->M >= 1024 ? 1 : 4;   // see mmm_launch_pairs
     return c.launch + (double)((ranges + shares - 1) / shares) * c.range + 1e-5 * spans * (double)ranges * c.word +
-           1e-9 * products * c.product[m->bw == 8 ? 0 : m->bw == 16 ? 1 : 2] + 0.01 * products / (spans * (double)shares * 64.0) * c.list +
-           1e-5 * spans * (double)shares * c.waves;
+           1e-9 * products * c.product[m->bw == 8 ? 0 : m->bw == 16 ? 1 : 2] + 0.01 * products / (spans * (double)shares * 64.0) * c.list;
 }
 
 mmm_plan tile_plan(const mmm_maps *m, int32_t variant)   // without the split

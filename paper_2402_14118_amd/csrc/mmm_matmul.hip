@@ -122,11 +122,10 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 
 // RT  16-row MFMA sub-tiles computed (4: all 64 rows of the block; 2: matrices of at most 32 rows)
 // GW  16-column groups per wave (2: bw = 32, the two groups of a block share their list), NW waves per
-//     workgroup: TN = 16*GW*LW*NW columns
+//     workgroup: TN = 16*GW*NW columns
 // KS  groups of NW waves that share the tile and take consecutive ranges of its K (each with a ring of its own); their
 //     sums are added in LDS at the end, in order
-// LW  lists per wave: the groups, or pairs of groups, it takes one after another in each step
-template <int RT, int GW, int NW, int KS, int LW, typename T>
+template <int RT, int GW, int NW, int KS, typename T>
 __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
     constexpr bool WIDE = sizeof(T) >= 4, F64 = sizeof(T) == 8;
@@ -139,7 +138,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     constexpr int ZERO_AT = RING * SLAB;            // the ring's zero column (mmm_zero_col)
     constexpr int DMA = SLAB / 1024 / NW;           // copies per wave and block
     constexpr int BATCH = WIDE ? 16 : 32;           // list slots per batch
-    constexpr int OPS = LW * (WIDE ? 4 * GW + 1 : GW + 1);       // vector-memory operations of a step's requests
+    constexpr int OPS = WIDE ? 4 * GW + 1 : GW + 1;       // vector-memory operations request() makes
     constexpr int SEGB = KC * MMM_GROUP_COLS * ESZ;       // bytes of a packed segment
     static_assert(DMA * NW * 1024 == SLAB, "whole copies");
     typedef elem_t avec __attribute__((ext_vector_type(RT)));   // 4- and 8-byte types: A operands of the RT row tiles for one k
@@ -177,23 +176,23 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     const int chunk_begin = min(wg_begin + ks * steps, wg_end);
     const int chunk_end = min(chunk_begin + steps, wg_end);
 
-    tile_t acc[LW * GW][RT];
+    tile_t acc[GW][RT];
 #pragma unroll
-    for (int g = 0; g < LW * GW; ++g)
+    for (int g = 0; g < GW; ++g)
 #pragma unroll
         for (int r = 0; r < RT; ++r) acc[g][r] = tile_t{0, 0, 0, 0};
 
     // this wave's groups; a wave past the last column walks the last group's addresses and multiplies nothing
-    const int64_t G0 = ((int64_t)tile_n * NW + wave) * (GW * LW);
+    const int64_t G0 = ((int64_t)tile_n * NW + wave) * GW;
+    const bool active = G0 < p.NG;
     const int64_t Gc = min(G0, p.NG - 1);
     // Buffer resources: an operand load is then a register of lane offsets, a scalar step offset and an immediate, with
     // no address arithmetic on the vector ALU.  A group's area is below 2^31 bytes (K < 2^22).
     const __amdgpu_buffer_rsrc_t val_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char *>(p.bp_val) + Gc * p.KBA * SEGB, 0, (int)(min(p.NG - Gc, (int64_t)(GW * LW)) * p.KBA * SEGB), 0x00020000);
+        const_cast<char *>(p.bp_val) + Gc * p.KBA * SEGB, 0, (int)(min(p.NG - Gc, (int64_t)GW) * p.KBA * SEGB), 0x00020000);
     const __amdgpu_buffer_rsrc_t list_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(p.bp_list) + Gc * p.KBA * KC, 0, (int)(min(p.NG - Gc, (int64_t)(GW * LW)) * p.KBA * KC * 2), 0x00020000);
+        const_cast<uint16_t *>(p.bp_list) + Gc * p.KBA * KC, 0, (int)(p.KBA * KC * 2), 0x00020000);
     const int val_next = (int)(p.KBA * SEGB);   // second group of a 32-wide block (N is a multiple of 32 then)
-    const int list_next = (int)(p.KBA * KC * 2);
     const uint32_t *const cnt0 = p.bp_cnt + Gc * p.KBA;
 
     // ---- A: block ch of this row tile to place ch mod RING (the builder's list entries assume that place)
@@ -216,12 +215,10 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
         uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each)
     };
-    Batch B0[LW], B1[LW], B2[LW];
-    // The batch whose values and entries lie at these byte offsets of the first group's area.  Always OPS / LW loads, so that the waits
+    Batch B0, B1, B2;
+    // The batch whose values and entries lie at these byte offsets of the group's area.  Always OPS loads, so that the waits
     // can count them; past the end of the area they return zeros (and are not used).
-    auto request = [&](Batch &b, int off_v, int off_l, int w) __attribute__((always_inline)) {
-        off_v += w * GW * val_next;
-        off_l += w * GW * list_next;
+    auto request = [&](Batch &b, int off_v, int off_l) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");   // the loads of one call stay together and in their place: the waits count them
         if constexpr (WIDE) {
             b.list = __builtin_amdgcn_raw_buffer_load_b64(list_rsrc, s * 8, off_l, 0);
@@ -246,7 +243,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     const uint32_t c16 = (uint32_t)c * 16u;
     const uint32_t chunk8 = (uint32_t)(lane & 3) * 8u;
     // left: slots of the list from the batch's first on (at least one)
-    auto multiply = [&](const Batch &b, int left, int w) __attribute__((always_inline)) {
+    auto multiply = [&](const Batch &b, int left) __attribute__((always_inline)) {
         if constexpr (WIDE) {
             // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
             // entries count in 256)
@@ -276,9 +273,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll
                     for (int r = 0; r < RT; ++r) {
                         if constexpr (F64)
-                            acc[w * GW + g][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][r], b.bf[g][u], acc[w * GW + g][r], 0, 0, 0);
+                            acc[g][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
                         else
-                            acc[w * GW + g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], b.bf[g][u], acc[w * GW + g][r], 0, 0, 0);
+                            acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
                     }
             };
             quad(0);
@@ -308,7 +305,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             for (int r = 0; r < RT; ++r)
 #pragma unroll
                 for (int g = 0; g < GW; ++g)
-                    acc[w * GW + g][r] = Mfma16<T>::k32(u32x4{a[0][r].x, a[0][r].y, a[1][r].x, a[1][r].y}, b.bh[g], acc[w * GW + g][r]);
+                    acc[g][r] = Mfma16<T>::k32(u32x4{a[0][r].x, a[0][r].y, a[1][r].x, a[1][r].y}, b.bh[g], acc[g][r]);
         }
     };
 
@@ -325,38 +322,30 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // the barrier nobody reads the place of the block before any more, and the next copies may go there.
     constexpr int BATCH_V = BATCH * MMM_GROUP_COLS * ESZ, BATCH_L = BATCH * 2, SEG_L = KC * 2;   // bytes
     int off_v = chunk_begin * SEGB, off_l = chunk_begin * SEG_L;   // the current step's segment
-    struct Lengths { int n[LW]; };
-    auto step = [&](const Lengths &now, const Lengths &next, Batch *b) __attribute__((always_inline)) {
+    auto step = [&](int n, int n_next, Batch &b) __attribute__((always_inline)) {
         wait_vmem<(RING - 1) * OPS>();
         asm volatile("s_barrier" ::: "memory");
         if (to_copy > 0) copy_block();
-#pragma unroll
-        for (int w = 0; w < LW; ++w) {
-            const int n = now.n[w];
-            if (n > 0) {
-                multiply(b[w], n, w);
-                if (n > BATCH) {
-                    // (Requests inside are unconditional, the last one repeating the batch in hand: a load on one side of a
-                    // branch would be waited for as if nothing had been requested after the loads before it.)
-                    const int end = (n - 1) / BATCH;   // the last batch
-                    for (int i = 1;;) {
-                        const int j = min(i + 1, end);
-                        request(b[w], off_v + j * BATCH_V, off_l + j * BATCH_L, w);
-                        multiply(B2[w], n - i * BATCH, w);
-                        if (++i > end) break;
-                        const int k = min(i + 1, end);
-                        request(B2[w], off_v + k * BATCH_V, off_l + k * BATCH_L, w);
-                        multiply(b[w], n - i * BATCH, w);
-                        if (++i > end) break;
-                    }
+        if (n > 0) {
+            multiply(b, n);
+            if (n > BATCH) {
+                // (Requests inside are unconditional, the last one repeating the batch in hand: a load on one side of a
+                // branch would be waited for as if nothing had been requested after the loads before it.)
+                const int end = (n - 1) / BATCH;   // the last batch
+                for (int i = 1;;) {
+                    const int j = min(i + 1, end);
+                    request(b, off_v + j * BATCH_V, off_l + j * BATCH_L);
+                    multiply(B2, n - i * BATCH);
+                    if (++i > end) break;
+                    const int k = min(i + 1, end);
+                    request(B2, off_v + k * BATCH_V, off_l + k * BATCH_L);
+                    multiply(b, n - i * BATCH);
+                    if (++i > end) break;
                 }
             }
         }
-#pragma unroll
-        for (int w = 0; w < LW; ++w) {
-            if (next.n[w] > BATCH) request(B2[w], off_v + SEGB + BATCH_V, off_l + SEG_L + BATCH_L, w);
-            request(b[w], off_v + 2 * SEGB, off_l + 2 * SEG_L, w);
-        }
+        if (n_next > BATCH) request(B2, off_v + SEGB + BATCH_V, off_l + SEG_L + BATCH_L);
+        request(b, off_v + 2 * SEGB, off_l + 2 * SEG_L);
         off_v += SEGB;
         off_l += SEG_L;
     };
@@ -367,38 +356,23 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         for (int i = 0; i < RING - 1; ++i)
             if (to_copy > 0) copy_block();
         for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
-#pragma unroll
-        for (int w = 0; w < LW; ++w) request(B0[w], off_v, off_l, w);
-#pragma unroll
-        for (int w = 0; w < LW; ++w) request(B1[w], off_v + SEGB, off_l + SEG_L, w);
+        request(B0, off_v, off_l);
+        request(B1, off_v + SEGB, off_l + SEG_L);
         wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
         bool first = true;
         for (int done = 0; done < even_steps; done += 62) {   // lane i: length of the list of step done + i
             const int ch = chunk_begin + done + lane;
-            uint32_t counts[LW];
-#pragma unroll
-            for (int w = 0; w < LW; ++w) {
-                counts[w] = G0 + w * GW < p.NG && ch < chunk_end ? cnt0[w * GW * p.KBA + ch] : 0u;
-                asm volatile("" : "+v"(counts[w]));   // waited for here
-            }
-            auto lengths = [&](int i) __attribute__((always_inline)) {
-                Lengths l;
-#pragma unroll
-                for (int w = 0; w < LW; ++w) l.n[w] = (int)__builtin_amdgcn_readlane(counts[w], i);
-                return l;
-            };
-            Lengths now = lengths(0);
-            if (first)
-#pragma unroll
-                for (int w = 0; w < LW; ++w)
-                    if (now.n[w] > BATCH) request(B2[w], off_v + BATCH_V, off_l + BATCH_L, w);
+            uint32_t counts = active && ch < chunk_end ? cnt0[ch] : 0u;
+            asm volatile("" : "+v"(counts));   // waited for here
+            if (first && (int)__builtin_amdgcn_readlane(counts, 0) > BATCH) request(B2, off_v + BATCH_V, off_l + BATCH_L);
             first = false;
             const int here = min(62, even_steps - done);
+            int n = (int)__builtin_amdgcn_readlane(counts, 0);
             for (int i = 0; i < here; i += 2) {
-                const Lengths next = lengths(i + 1), after = lengths(i + 2);
-                step(now, next, B0);
-                step(next, after, B1);
-                now = after;
+                const int n1 = (int)__builtin_amdgcn_readlane(counts, i + 1), n2 = (int)__builtin_amdgcn_readlane(counts, i + 2);
+                step(n, n1, B0);
+                step(n1, n2, B1);
+                n = n2;
             }
         }
     } else if (KS > 1) {   // no step left for this range of K: only the barriers of the others
@@ -407,7 +381,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     __syncthreads();   // the rings are free: what follows reuses them
     if constexpr (KS > 1) {   // sums of the later ranges of K, added in order
         tile_t *sums = reinterpret_cast<tile_t *>(rings + RING_BYTES);   // (the first ring is what the layout below uses)
-        static_assert(LW == 1 && (KS - 1) * NW * 64 * GW * RT * (int)sizeof(tile_t) <= (KS - 1) * RING_BYTES, "room for them");
+        static_assert((KS - 1) * NW * 64 * GW * RT * (int)sizeof(tile_t) <= (KS - 1) * RING_BYTES, "room for them");
         if (ks > 0)
 #pragma unroll
             for (int g = 0; g < GW; ++g)
@@ -436,7 +410,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     static_assert(RP >= 1 && RT % RP == 0, "whole passes");
     const bool vec_ok = !F64 && reinterpret_cast<uintptr_t>(out) % 16 == 0 && ldo % 4 == 0;
 #pragma unroll
-    for (int g = 0; g < LW * GW; ++g) {
+    for (int g = 0; g < GW; ++g) {
         const int64_t col0 = (G0 + g) * 16;
         if (vec_ok && col0 + 16 <= p.N) {
             float *mine = reinterpret_cast<float *>(ring + wave * PIECE);
@@ -526,27 +500,22 @@ typedef void (*matmul_kernel_fn)(const MatmulParams);
 
 struct VariantEntry {
     mmm_variant_info info;
-    int32_t waves;              // of 16 columns each (64 x 512: of 32); 32-wide blocks: half as many waves of 32 columns
+    int32_t waves;              // of 16 columns each; 32-wide blocks: half as many waves of 32 columns
     matmul_kernel_fn fn[2][4];  // [bw == 32][element type]; null: not built
 };
 
-#define MMM_KERNELS(RT, GW, NW, KS, LW)                                                                                   \
-    mmm_matmul_kernel<RT, GW, NW, KS, LW, float>, mmm_matmul_kernel<RT, GW, NW, KS, LW, uint16_t>, mmm_matmul_kernel<RT, GW, NW, KS, LW, _Float16>
+#define MMM_KERNELS(RT, GW, NW, KS)                                                                                       \
+    mmm_matmul_kernel<RT, GW, NW, KS, float>, mmm_matmul_kernel<RT, GW, NW, KS, uint16_t>, mmm_matmul_kernel<RT, GW, NW, KS, _Float16>
 #define MMM_VARIANT(RT, NW)                                                                                               \
     {                                                                                                                     \
-        {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT, 1, true}, NW,                                              \
-            {{MMM_KERNELS(RT, 1, NW, 1, 1), mmm_matmul_kernel<RT, 1, NW, 1, 1, double>},                                  \
-             {MMM_KERNELS(RT, 2, NW / 2, 1, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, 1, double>}}                          \
+        {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT, 1, true}, NW,                                                    \
+            {{MMM_KERNELS(RT, 1, NW, 1), mmm_matmul_kernel<RT, 1, NW, 1, double>},                                        \
+             {MMM_KERNELS(RT, 2, NW / 2, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, double>}}                                \
     }
 #define MMM_VARIANT_K2(RT, NW) /* two rings: not for doubles */                                                           \
     {                                                                                                                     \
-        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false}, NW,                                          \
-            {{MMM_KERNELS(RT, 1, NW, 2, 1), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2, 1), nullptr}}                        \
-    }
-#define MMM_VARIANT_WIDE(RT) /* 512 columns, sixteen waves of two groups: too many accumulators for doubles */            \
-    {                                                                                                                     \
-        {"R" #RT "x16_TN32x16", TM, 512, KC, 16 * RT, 1, false}, 16,                                                      \
-            {{MMM_KERNELS(RT, 1, 16, 1, 2), nullptr}, {MMM_KERNELS(RT, 2, 16, 1, 1), nullptr}}                            \
+        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false}, NW,                                                 \
+            {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}                              \
     }
 
 const VariantEntry g_variants[] = {
@@ -558,7 +527,6 @@ const VariantEntry g_variants[] = {
     MMM_VARIANT(2, 4),      // 5: 32 x 64
     MMM_VARIANT_K2(4, 8),   // 6: 64 x 128, K in two ranges
     MMM_VARIANT_K2(4, 4),   // 7: 64 x 64, K in two ranges
-    MMM_VARIANT_WIDE(4),    // 8: 64 x 512
 };
 constexpr int32_t kVariants = (int32_t)(sizeof(g_variants) / sizeof(g_variants[0]));
 
@@ -628,7 +596,7 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     matmul_kernel_fn fn = v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
     if (fn == nullptr) return hipErrorInvalidValue;
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.info.TN == 512 ? v.waves : v.waves >> wide) * (uint32_t)v.info.k_ranges * 64), 0, s, p);
+    hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.waves >> wide) * (uint32_t)v.info.k_ranges * 64), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pl.split_k > 1) {
