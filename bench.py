@@ -227,13 +227,14 @@ def measure(w, steps, warmup, args, dense=True, trials=True):
     # matrix path: every occupied block of B against all rows of A; pair path: the surviving products only
     issued_flops = 2.0 * w.M * occ_b * w.bw if path == mm.MMM_PATH_MATRIX else useful_flops
 
-    # algorithmic bytes of one launch: what the method itself must move (lists, occupied blocks, maps, C)
+    # algorithmic bytes of one launch: what the method itself must move (image of A, packed B, maps, C)
     WA, NB = (w.K + 63) // 64, w.N // w.bw
     WB = (NB + 63) // 64
     a_bits_b, colany_b = w.M * WA * 8, ((w.M + 31) // 32) * WA * 8
     b_bits_b, bt_b = w.K * WB * 8, NB * WA * 8
-    a_blocks = ((w.M + 63) // 64) * ((w.K + 127) // 128)
-    a_list_b = nnz_a * 8 + a_blocks * 4            # {slab offset, value} per non-zero, one count per block
+    live = w.K if w.keep_rows is None else int(synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K).sum())
+    a_img_b = ((w.M + 63) // 64) * 64 * ((live + 127) // 128) * 128 * esz     # the live columns of X, zeros included
+    b_pack_b = occ_b * (w.bw * esz + 2)             # values and list entries (groups of 16 columns: at least these)
     kb = np.ones((w.K, NB), dtype=bool)             # blocks the keep bitmaps leave switched on: the builder must read them
     if w.keep_rows is not None:
         kb &= synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0][:, None]
@@ -244,9 +245,9 @@ def measure(w, steps, warmup, args, dense=True, trials=True):
     keep_in_b = (a_bits_b if w.keep_a is not None else 0) + (b_bits_b if w.keep_blocks is not None else 0) \
         + (WA * 8 if w.keep_rows is not None else 0)
     build_bytes = w.M * w.K * esz + kept_blocks * w.bw * esz + keep_in_b \
-        + a_bits_b + colany_b + a_list_b + b_bits_b + bt_b
-    if path == mm.MMM_PATH_MATRIX:   # lists of A, occupied blocks of Y, the two small maps, C
-        matmul_bytes = a_list_b + occ_b * w.bw * esz + colany_b + bt_b + w.M * w.N * csz
+        + a_bits_b + colany_b + a_img_b + b_bits_b + bt_b + b_pack_b
+    if path == mm.MMM_PATH_MATRIX:   # image of A, packed B, C
+        matmul_bytes = a_img_b + b_pack_b + w.M * w.N * csz
     else:                            # pair kernel: the non-zero elements of X, both bitmaps, occupied blocks of Y, C
         matmul_bytes = nnz_a * esz + a_bits_b + bt_b + occ_b * w.bw * esz + w.M * w.N * csz
 

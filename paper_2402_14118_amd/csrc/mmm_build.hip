@@ -478,28 +478,36 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
     const int64_t k_first = min(seg * SEG + wave * B_ROWS, p.K - 1);
     __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(p.Y) + (k_first * p.ldy + col0) * ESZ), 0,
                                                                  0x7fffffff, 0x00020000);
+    auto load_rows = [&](auto any_alignment) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < B_ROWS; ++j) {
-        const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)piece, j);   // nothing if there is no such row
-        const uint32_t off = (pj >> (lane / LPB)) & 1u ? lane_off : NO_LOAD;
-        uint32_t at = (uint32_t)j * row_bytes;
-        if (ROWS) {   // rows far from each other
-            const int64_t k = max((int64_t)readlane64((uint64_t)krow, j), (int64_t)0);
-            r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(p.Y) + (k * p.ldy + col0) * ESZ), 0, 0x7fffffff, 0x00020000);
-            at = 0;
-        }
-        if constexpr (WIDE) {
-            raw[j] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)at, 0);
-        } else if (!p.y_unaligned) {
-            const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)at, 0);
-            raw[j] = u32x4{v.x, v.y, 0, 0};
-        } else {
-            uint32_t e[4];
+        for (int j = 0; j < B_ROWS; ++j) {
+            const uint32_t pj = (uint32_t)__builtin_amdgcn_readlane((int)piece, j);   // nothing if there is no such row
+            const uint32_t off = (pj >> (lane / LPB)) & 1u ? lane_off : NO_LOAD;
+            uint32_t at = (uint32_t)j * row_bytes;
+            if (ROWS) {   // rows far from each other
+                const int64_t k = max((int64_t)readlane64((uint64_t)krow, j), (int64_t)0);
+                r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(static_cast<const char *>(p.Y) + (k * p.ldy + col0) * ESZ), 0, 0x7fffffff, 0x00020000);
+                at = 0;
+            }
+            if constexpr (WIDE) {
+                raw[j] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, (int)at, 0);
+            } else if constexpr (!decltype(any_alignment)::value) {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, (int)at, 0);
+                raw[j] = u32x4{v.x, v.y, 0, 0};
+            } else {
+                uint32_t e[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) e[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, (int)at + 2 * i, 0);
-            raw[j] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, 0, 0};
+                for (int i = 0; i < 4; ++i) e[i] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, (int)at + 2 * i, 0);
+                raw[j] = u32x4{e[0] | e[1] << 16, e[2] | e[3] << 16, 0, 0};
+            }
         }
-    }
+    };
+    // (One branch around all loads: one per load made the compiler bring back its spilled scalar registers eight times, 128 of
+    // 525 vector instructions per wave, on which half-precision B was bound.)
+    if (!WIDE && p.y_unaligned)
+        load_rows(std::true_type{});
+    else
+        load_rows(std::false_type{});
     uint32_t gb = 0, bbm = 0;   // rows (bit j) in which this lane's group / block is occupied
     uint64_t mine = 0;          // lane j: the lanes with a non-zero element in row j, then at multiples of LPB the occupied blocks
     {
