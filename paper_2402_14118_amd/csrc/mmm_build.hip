@@ -70,6 +70,15 @@ struct BuildParams {
     uint32_t *kmap;          // k' -> k
     uint64_t *btc_bits;      // transposed B map over k'
 };
+// The kernel reads its arguments where it needs them: as a by-value struct they were all loaded at its start, and bringing
+// them back from where the compiler had spilled them took a third of the vector instructions.
+typedef const __attribute__((address_space(4))) BuildParams ConstParams;
+__device__ __forceinline__ ConstParams &reread(ConstParams &p)   // what is used of the result is loaded after this point
+{
+    ConstParams *q = &p;
+    asm volatile("" : "+s"(q));
+    return *q;
+}
 
 template <typename T> __device__ __forceinline__ uint32_t f32_bits(T v);
 template <> __device__ __forceinline__ uint32_t f32_bits<float>(float v) { return __float_as_uint(v); }
@@ -140,8 +149,9 @@ template <typename T> struct ABlock {   // one block in a wave's registers: lane
 // several (columns 2048 x 16384: 28 -> 26 us for A, 41 -> 35.4 with B; with one or two blocks per workgroup the loads past
 // the last one cost more than they gain, 6.6 -> 9 us for 512 x 8192, and so do more bytes in flight for the wider types).
 template <typename T, int TEST, bool ROWS, bool DEEP>
-__device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
+__device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
 {
+    ConstParams &p = reread(p0);
     typedef typename Pattern<sizeof(T)>::type pattern;
     constexpr int ESZ = (int)sizeof(T);
     constexpr bool WIDE = ESZ >= 4;
@@ -220,6 +230,7 @@ __device__ __forceinline__ void scan_a(const BuildParams &p, int64_t bj, int64_t
         }
     }
     auto block = [&](int64_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
+        ConstParams &p = reread(p0);
         constexpr int AHEAD = decltype(ahead)::value;   // the block whose loads take this one's place
         char *const stage = sh.stage[st];
         uint64_t word[A_ROWS][A_WORDS];   // bitmap words: wave-uniform, the lane masks of what stays
@@ -374,7 +385,7 @@ struct BShared {
 };
 
 // Rows k' = seg*128 .. of the numbering given by `rows`, into sh.kk; returns K'.
-__device__ __forceinline__ uint32_t number_rows(const BuildParams &p, int64_t seg, int lane, int wave, BShared &sh)
+__device__ __forceinline__ uint32_t number_rows(ConstParams &p, int64_t seg, int lane, int wave, BShared &sh)
 {
     const int tid = threadIdx.x;
     if (tid < SEG) sh.kk[tid] = -1;
@@ -437,8 +448,9 @@ template <int LPB> __device__ __forceinline__ uint32_t squeeze(uint64_t x)
 // Returns false where ROWS finds no live row in the segment.  carry: doubles in 32-wide blocks fill half a
 // byte of a map row per column tile, so the map bits of an even tile are handed to the odd one after it.
 template <typename T, int BW, bool ROWS>
-__device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_t ct, int lane, int wave, BShared &sh, uint32_t &carry)
+__device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct, int lane, int wave, BShared &sh, uint32_t &carry)
 {
+    ConstParams &p = reread(p0);
     constexpr int ESZ = (int)sizeof(T);
     constexpr int LANE_COLS = Tile<T>::LANE_COLS, B_COLS = Tile<T>::B_COLS, B_GROUPS = Tile<T>::B_GROUPS;
     constexpr int LPB = BW / LANE_COLS;               // lanes per block
@@ -641,8 +653,9 @@ __device__ __forceinline__ bool scan_b(const BuildParams &p, int64_t seg, int64_
 
 // ROWS: row-compacted mode (A laid out over the live rows of B; B built over them).
 template <typename T, int TEST, int BW, bool ROWS, bool DEEP>
-__global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void mmm_build_kernel(const BuildParams p)
+__global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void mmm_build_kernel(const BuildParams)
 {
+    ConstParams &p = *(ConstParams *)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ __align__(16) union { AShared a; BShared b; } sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
