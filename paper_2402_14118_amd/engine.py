@@ -46,7 +46,7 @@ class MaskedMatmul:
 
     def matmul(self, X: torch.Tensor, Y: torch.Tensor, C: torch.Tensor, accumulate: bool = False, stream=None) -> None:
         B._check(B.native.matmul(self.maps, self.dtype, X.data_ptr(), X.stride(0), Y.data_ptr(), Y.stride(0), C.data_ptr(),
-                                 C.stride(0), accumulate, B._stream(stream)), "mmm_matmul")
+                                 C.stride(0), int(accumulate), B._stream(stream)), "mmm_matmul")
 
     def matmul_static_scratch(self, X: torch.Tensor, Y: torch.Tensor, C: torch.Tensor, accumulate: bool = False,
                               stream=None) -> None:
@@ -58,7 +58,7 @@ class MaskedMatmul:
                      stream=None) -> None:
         """C (+)= M(X) x B with M evaluated inside the multiplication; only the B side of the maps is used."""
         B._check(B.native.matmul_fused(self.maps, self.dtype, X.data_ptr(), X.stride(0), pred, threshold, B._ptr(keep_a),
-                                       Y.data_ptr(), Y.stride(0), C.data_ptr(), C.stride(0), accumulate, B._stream(stream)),
+                                       Y.data_ptr(), Y.stride(0), C.data_ptr(), C.stride(0), int(accumulate), B._stream(stream)),
                  "mmm_matmul_fused")
 
     def set_path(self, path: int = -1) -> None:
