@@ -99,18 +99,17 @@ typedef __attribute__((address_space(3))) char lds_char;
 template <int N> __device__ __forceinline__ void copy_to_lds(const char *base, uint32_t voff, uint32_t lds)
 {
     static_assert(N == 1 || N == 2 || N % 4 == 0, "");
+    // (m0 is an operand, so that the compiler sets it and knows what it holds; the nop keeps the distance its write needs.)
     if constexpr (N == 1) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
     } else if constexpr (N == 2) {
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" ::"s"(lds),
-                     "v"(voff), "s"(base)
-                     : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
     } else {
 #pragma unroll
         for (int i = 0; i < N / 4; ++i)
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024\n\t"
-                         "global_load_lds_dwordx4 %1, %2 offset:2048\n\tglobal_load_lds_dwordx4 %1, %2 offset:3072" ::"s"(lds + i * 4096),
-                         "v"(voff), "s"(base + i * 4096)
+            asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\t"
+                         "global_load_lds_dwordx4 %0, %1 offset:2048\n\tglobal_load_lds_dwordx4 %0, %1 offset:3072" ::"v"(voff),
+                         "s"(base + i * 4096), "{m0}"(lds + i * 4096)
                          : "memory");
     }
 }
