@@ -16,8 +16,8 @@
  *   - Pointers named X, Y, C, keep_*, dev_workspace are DEVICE pointers owned by
  *     the caller.  The library never allocates or frees device memory and never
  *     reads X, Y or C after the work of a call has run; the handle remembers the
- *     address and leading dimension of the X its A side was built from, only to
- *     compare them with what mmm_matmul is given.
+ *     address and leading dimension of the X and the Y its sides were built from,
+ *     only to compare them with what mmm_matmul is given.
  *   - Row-major; leading dimensions (ldx, ldy, ldc) are in elements and must be
  *     >= the row length; ldx and ldy must be below 2^22 (MMM_ERR_SHAPE
  *     otherwise, from mmm_build_maps and from mmm_matmul alike).  C is float
@@ -230,15 +230,20 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
  * Y are not read again), MMM_PATH_PAIRS from X and Y.
  * WARNING: after X or Y has been changed in place its side must be rebuilt
  * (mmm_build_maps with the other side NULL) before the next mmm_matmul; otherwise C
- * may be computed from the old values without any error.  What can be checked is: X
- * and ldx must be the ones the A side was built from (MMM_ERR_MAPS_MISMATCH).
+ * may be computed from the old values without any error.  What can be checked is
+ * the address: X and ldx must be the ones the A side was built from
+ * (MMM_ERR_MAPS_MISMATCH); with another Y or ldy than the B side was built from the
+ * product is that of the Y given, under the maps as built, by MMM_PATH_PAIRS
+ * whatever was chosen or asked for (MMM_ERR_MAPS_MISMATCH where that kernel cannot
+ * address this Y, see below).
  * Products the maps skip contribute exactly 0, whatever the skipped operands
  * hold (see the conventions above for non-finite kept values).  Every element
  * of C is written exactly once, zeros included.  float accumulation; the
  * result is bitwise reproducible from run to run for the same inputs and shape.
  * Errors: MMM_ERR_INVALID_ARG, MMM_ERR_SHAPE, MMM_ERR_DTYPE,
- * MMM_ERR_MAPS_MISMATCH (a side not built, dt differs from the build, or X / ldx
- * are not those of the build), MMM_ERR_DEVICE. */
+ * MMM_ERR_MAPS_MISMATCH (a side not built, dt differs from the build, X / ldx are not
+ * those of the build, or Y / ldy are not and only the packed form could serve),
+ * MMM_ERR_DEVICE. */
 mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
                       const void *X, int64_t ldx, const void *Y, int64_t ldy,
                       void *C, int64_t ldc, int32_t accumulate, void *hip_stream);
@@ -251,7 +256,7 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
  *       of B), found by AND-ing the bitmap row of A with the transposed B map.  Work grows with
  *       the product of both densities, at a higher cost per product.  Reads X and Y
  *       themselves.  Needs ldy * sizeof(element) below 2^20 bytes; beyond that mmm_matmul
- *       uses MATRIX whatever was asked for.
+ *       uses MATRIX whatever was asked for.  A Y other than the one built from always goes here.
  * Automatic choice (path -1): MATRIX if a tile variant has been fixed (mmm_maps_set_plan or the
  * "matmul_variant" option).  Else, once a mmm_maps_stats call on the handle has counted the
  * non-zeros, blocks and surviving products (the most recent counts are kept as the estimate

@@ -366,6 +366,8 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->build_stream = nullptr;
     m->a_src = nullptr;
     m->a_src_ld = 0;
+    m->b_src = nullptr;
+    m->b_src_ld = 0;
     m->plan_variant = -1;
     m->plan_split = 0;
     m->plan_path = -1;
@@ -445,6 +447,8 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
     if (Y != nullptr) {
         maps->b_built = true;
         maps->b_dtype = dt;
+        maps->b_src = Y;   // compared, never dereferenced
+        maps->b_src_ld = ldy;
     }
     return MMM_OK;
 }
@@ -583,7 +587,11 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
     if (maps->a_dtype != dt || maps->b_dtype != dt) return MMM_ERR_MAPS_MISMATCH;
     // the values of A travel in the image that was made from X at build time: another X is another A
     if (maps->a_src != X || maps->a_src_ld != ldx) return MMM_ERR_MAPS_MISMATCH;
-    if (choose_path(maps, dt) == MMM_PATH_PAIRS && mmm_pairs_supports(dt, ldy)) {   // no scratch at all on this path
+    // The matrix kernel has the values of B in the packed form that was made from Y at build time; the pair kernel reads the
+    // Y it is given, so that is what another Y (or the same at another leading dimension) is multiplied by.
+    const bool packed_y = maps->b_src == Y && maps->b_src_ld == ldy, pairs_can = mmm_pairs_supports(dt, ldy);
+    if (!packed_y && !pairs_can) return MMM_ERR_MAPS_MISMATCH;
+    if (pairs_can && (!packed_y || choose_path(maps, dt) == MMM_PATH_PAIRS)) {   // no scratch at all on this path
         hipError_t e = ensure_bt(maps, static_cast<hipStream_t>(hip_stream));
         if (e == hipSuccess)
             e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, false, 0, 0.f, nullptr,

@@ -133,6 +133,8 @@ struct mmm_maps {
     hipStream_t build_stream;   // of the last build: the inspection calls that derive something launch there
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)
     int64_t a_src_ld;
+    const void *b_src;   // the same of the Y the B side was built from
+    int64_t b_src_ld;
     // launch plan fixed for this handle (-1 / 0: none, follow the process-wide options)
     int32_t plan_variant, plan_split, plan_path;
     // what the most recent mmm_maps_stats call counted: the density estimate behind the choice of kernel

@@ -1,0 +1,56 @@
+"""What the calls promise beyond the numbers: which operands a product is made from, what a build leaves in the
+workspace and for whom, which products are skipped."""
+import numpy as np
+import pytest
+import torch
+
+import mmm_synth as synth
+import oracle
+import paper_2402_14118_amd as mm
+from hip_harness import HipRun
+
+pytestmark = pytest.mark.gpu
+
+DTYPES = [synth.DT_F32, synth.DT_BF16, synth.DT_F16, synth.DT_F64]
+IDS = ["f32", "bf16", "f16", "f64"]
+
+
+# ---- which Y a product is made from ------------------------------------------------------------
+@pytest.mark.parametrize("rows", [None, 0.5], ids=["all", "rows"])
+@pytest.mark.parametrize("asked", [-1, mm.MMM_PATH_MATRIX, mm.MMM_PATH_PAIRS], ids=["auto", "matrix", "pairs"])
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+def test_another_y_than_the_one_built_from(dtype, asked, rows):
+    """The product is that of the Y that is passed, whichever kernel is chosen: the matrix kernel has only the values of
+    the Y that the maps were built from."""
+    w = synth.random_masked(100, 300, 64, 16, 0.3, 0.3, 77, dist="smallint", dtype=dtype, p_rows=rows)
+    _, _, C_ref, _ = oracle.run_workload(w)
+    run = HipRun(w)
+    run.eng.set_path(asked)
+    run.build()
+    other = run.Y.clone()                                            # the same values elsewhere
+    halves = {synth.DT_BF16: torch.bfloat16, synth.DT_F16: torch.float16}
+    twice = run.Y.clone()
+    twice = (twice.view(halves[dtype]) * 2).view(torch.int16) if dtype in halves else twice * 2
+    wide = torch.zeros((w.K, w.N + 8), dtype=run.Y.dtype, device="cuda")    # another leading dimension
+    wide[:, : w.N] = run.Y
+    for Y, factor in ((run.Y, 1), (other, 1), (twice, 2), (wide, 1), (run.Y, 1)):
+        for call in (run.eng.matmul, run.eng.matmul_static_scratch):
+            run.Cbuf.fill_(float("nan"))
+            call(run.X, Y, run.C)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(run.C.cpu().numpy(), factor * C_ref)
+
+
+def test_another_y_that_no_kernel_can_read():
+    """Rows too far apart for the pair kernel, and not the Y whose values the matrix kernel has."""
+    w = synth.random_masked(40, 200, 64, 16, 0.3, 0.5, 88, dist="smallint")
+    run = HipRun(w, ldy=(1 << 18) + 8)
+    run.build()
+    other = torch.zeros((w.K + 1, (1 << 18) + 8), device="cuda")[1:, : w.N]
+    other.copy_(run.Y)
+    with pytest.raises(mm.MmmError) as e:
+        run.eng.matmul(run.X, other, run.C)
+    assert e.value.status == mm.binding.MMM_ERR_MAPS_MISMATCH
+    run.matmul()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(run.C.cpu().numpy(), oracle.run_workload(w)[2])
