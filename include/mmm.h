@@ -152,9 +152,8 @@ mmm_status mmm_maps_view(const mmm_maps *maps, const uint64_t **a_bits, int64_t 
 
 /* Device pointers to the derived maps, for inspection:
  *   a_colany: ceil(M/32) x ceil(K/64) words; bit k of row t = OR of a_bits[i,k], i in [32t, 32t+32)
- *   bt_bits : NB x ceil(K/64) words; bit k of row jb = b_bits[k,jb]   (the B map transposed; in
- *             row-compacted mode it may be this call that makes it, on the stream of the last mmm_build_maps)
- * Errors: MMM_ERR_INVALID_ARG, MMM_ERR_DEVICE. */
+ *   bt_bits : NB x ceil(K/64) words; bit k of row jb = b_bits[k,jb]   (the B map transposed)
+ * Errors: MMM_ERR_INVALID_ARG. */
 mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany, const uint64_t **bt_bits,
                                  int64_t *k_words);
 
