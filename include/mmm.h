@@ -27,7 +27,8 @@
  *     describes column c of row r.  (The paper prints patterns first-vector-
  *     leftmost; the layout here is this library's own.)
  *   - `hip_stream` is a hipStream_t passed as void* (NULL = the null stream).
- *     Calls enqueue work and return; only mmm_maps_stats waits for the stream.
+ *     Calls enqueue work and return; only mmm_maps_stats waits for the stream, and
+ *     the two inspection calls that make what they show wait for the device.
  *   - Errors are return codes.  Arguments are checked on the host before any
  *     device work is enqueued; on error nothing is launched and no output is
  *     touched.  No call aborts or prints.
@@ -167,8 +168,9 @@ mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany
  *   a_colany_c  : ceil(M/32) x ceil(K/64) words; bit k' of row t = OR of a_bits[i, kmap[k']], i in [32t, 32t+32)
  *   btc_bits    : NB x ceil(K/64) words; bit k' of row jb = b_bits[kmap[k'], jb]
  *   (bits k' >= K' up to the next multiple of 128 are zero; words beyond are unspecified)
- * and packs B and lays out A over k'.  a_colany_c serves inspection only: this call makes it (on the
- * stream of the last mmm_build_maps).  The blocked lists of A (mmm_maps_view_lists) are then over k' as well.
+ * and packs B and lays out A over k'.  a_colany_c serves inspection only: where it is asked for,
+ * this call waits for the device, makes it and waits again (so it cannot be asked for during stream
+ * capture), and the next build does not renew it.  The blocked lists of A (mmm_maps_view_lists) are then over k' as well.
  * *on says whether the B side was last built this way.  Because the image of A depends on the
  * numbering, building the B side alone (X == NULL) with keep_rows, or after it had been built with
  * keep_rows, leaves the A side unbuilt: build A in the same call or afterwards.
@@ -194,8 +196,9 @@ mmm_status mmm_debug_k_lists(const mmm_maps *maps, void *out, size_t out_bytes, 
                              void *hip_stream);
 
 /* Device pointers to the blocked non-zero lists of A (the count-and-offsets form of Fig. "Blocked
- * sparse row preprocessing", with the values), for inspection: this call makes them from the image
- * of A, on the stream of the last mmm_build_maps.  A is cut
+ * sparse row preprocessing", with the values), for inspection: this call waits for the device, makes
+ * them from the image of A and waits again (so it cannot be made during stream capture); the next
+ * build does not renew them.  A is cut
  * into *blocks_m x *blocks_k blocks of 64 rows x 128 columns (ragged at the far
  * edges); block (bm, bk) has index bm * *blocks_k + bk.
  *   counts [block]            : number of non-zero elements of A in the block

@@ -283,6 +283,19 @@ int32_t choose_path(const mmm_maps *m, int32_t dt)
     return pairs_cost(m, dt) < matrix ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
 }
 
+// What only inspection reads is made when it is asked for.  These calls take no stream: the build may have run on one that is
+// busy with something else by now or does not exist any more, and the caller may read on any.  So nothing is assumed about
+// streams: the device's work is waited for, and then what was made.
+mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_t (*launch)(const mmm_maps *, hipStream_t))
+{
+    hipError_t e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = launch(maps, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+    if (e == hipSuccess) return MMM_OK;
+    note_device_error(what, e);
+    return MMM_ERR_DEVICE;
+}
+
 }   // namespace
 
 extern "C" {
@@ -356,7 +369,6 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->a_built = m->b_built = false;
     m->a_compact = m->b_compact = false;
     m->a_dtype = m->b_dtype = -1;
-    m->build_stream = nullptr;
     m->a_src = nullptr;
     m->a_src_ld = 0;
     m->b_src = nullptr;
@@ -416,7 +428,6 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         note_device_error("map builder launch", e);
         return MMM_ERR_DEVICE;
     }
-    maps->build_stream = static_cast<hipStream_t>(hip_stream);
     if (Y != nullptr) {
         // an image of A made for another numbering of k (or for none) do not fit the new B side
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
@@ -468,12 +479,8 @@ mmm_status mmm_maps_view_compacted(const mmm_maps *maps, int32_t *on, const uint
     if (kmap) *kmap = maps->kmap;
     if (a_colany_c) *a_colany_c = maps->a_colany_c;
     if (btc_bits) *btc_bits = maps->btc_bits;
-    // the multiplication does not read the column-any words over k': they are made here
     if (a_colany_c != nullptr && maps->a_built && maps->a_compact)
-        if (hipError_t e = mmm_launch_colany_compact(maps, maps->build_stream); e != hipSuccess) {
-            note_device_error("column-any words over the live rows", e);
-            return MMM_ERR_DEVICE;
-        }
+        return make_for_inspection("column-any words over the live rows", maps, mmm_launch_colany_compact);
     return MMM_OK;
 }
 
@@ -503,12 +510,9 @@ mmm_status mmm_maps_view_lists(const mmm_maps *maps, const uint32_t **counts, co
     if (blocks_m) *blocks_m = maps->MBA;
     if (blocks_k) *blocks_k = maps->KBA;
     if (capacity) *capacity = MMM_AB_CAP;
-    // the multiplication reads the image of A, not lists: they are made here, from the image
+    // the multiplication reads the image of A, not lists: they are made from the image
     if ((counts != nullptr || entries != nullptr) && maps->a_built && maps->a_dtype != MMM_F64)
-        if (hipError_t e = mmm_launch_lists(maps, maps->build_stream); e != hipSuccess) {
-            note_device_error("lists of A", e);
-            return MMM_ERR_DEVICE;
-        }
+        return make_for_inspection("lists of A", maps, mmm_launch_lists);
     return MMM_OK;
 }
 

@@ -754,17 +754,18 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
 }
 
 // ---- forms that only inspection reads, made when they are asked for ---------------------------
+// (The numbering of the live rows is held against K: they may be asked for before the build that makes it has run.)
 // Column-any words of A over k': bit k' of a row is bit kmap[k'] of the row over k.
 __global__ __launch_bounds__(256) void mmm_colany_compact_kernel(const uint64_t *a_colany, const uint32_t *kinfo, const uint32_t *kmap,
-                                                                 uint64_t *a_colany_c, int64_t MT, int64_t WA)
+                                                                 uint64_t *a_colany_c, int64_t MT, int64_t WA, int64_t K)
 {
     const int64_t idx = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);   // one wave per word
     if (idx >= MT * WA) return;
     const int64_t t = idx / WA, w = idx % WA, kc = w * 64 + (threadIdx.x & 63);
     bool any = false;
-    if (kc < (int64_t)*kinfo) {
+    if (kc < min((int64_t)*kinfo, K)) {
         const uint32_t k = kmap[kc];
-        any = (a_colany[t * WA + (k >> 6)] >> (k & 63)) & 1ull;
+        any = k < K && ((a_colany[t * WA + (k >> 6)] >> (k & 63)) & 1ull);
     }
     const uint64_t m = ballot64(any);
     if ((threadIdx.x & 63) == 0) a_colany_c[idx] = m;
@@ -780,11 +781,11 @@ __global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_im
     __shared__ uint32_t off[MMM_AB_COLS];
     const int64_t b = blockIdx.x, bi = b / KBA, bj = b % KBA;
     const int c = threadIdx.x;
-    const int64_t kc = bj * MMM_AB_COLS + c, klim = kinfo ? (int64_t)*kinfo : K;
+    const int64_t kc = bj * MMM_AB_COLS + c, klim = kinfo ? min((int64_t)*kinfo, K) : K;
     if (kinfo && bj * MMM_AB_COLS >= klim) return;
-    const int64_t k = kc < klim ? (kinfo ? (int64_t)kmap[kc] : kc) : -1;
+    const int64_t k = kc < klim ? (kinfo ? (int64_t)kmap[kc] : kc) : K;
     uint64_t rows = 0;
-    if (k >= 0)
+    if (k < K)
         for (int r = 0; r < MMM_AB_ROWS; ++r) {
             const int64_t row = bi * MMM_AB_ROWS + r;
             if (row < M && ((a_bits[row * WA + (k >> 6)] >> (k & 63)) & 1ull)) rows |= 1ull << r;
@@ -997,7 +998,7 @@ hipError_t mmm_launch_colany_compact(const mmm_maps *m, hipStream_t s)
 {
     (void)hipGetLastError();
     hipLaunchKernelGGL(mmm_colany_compact_kernel, dim3((uint32_t)((m->MT * m->WA + 3) / 4)), dim3(256), 0, s, m->a_colany, m->kinfo,
-                       m->kmap, m->a_colany_c, m->MT, m->WA);
+                       m->kmap, m->a_colany_c, m->MT, m->WA, m->K);
     return hipGetLastError();
 }
 

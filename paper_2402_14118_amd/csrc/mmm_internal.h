@@ -129,7 +129,6 @@ struct mmm_maps {
     bool b_compact;   // the B side was built in row-compacted mode
     bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
-    hipStream_t build_stream;   // of the last build: the inspection calls that derive something launch there
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)
     int64_t a_src_ld;
     const void *b_src;   // the same of the Y the B side was built from

@@ -76,3 +76,29 @@ def test_build_leaves_the_transposed_map(K, N, bw, p_rows, dtype):
         run.build()
         torch.cuda.synchronize()
         np.testing.assert_array_equal(bt.cpu().numpy().view(np.uint64), synth.pack_bits(synth.unpack_bits(bb, w.NB).T))
+
+
+# ---- inspection ------------------------------------------------------------------------------
+def test_inspection_needs_no_stream_of_the_build():
+    """A program builds on a stream of its own, waits for it, gives that stream other work and looks at the lists from
+    another stream."""
+    w = synth.random_masked(100, 700, 96, 16, 0.3, 0.4, 5, dist="smallint", p_rows=0.5)
+    run = HipRun(w)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    run.eng.build_maps(run.X, run.Y, w.pred, w.threshold, run.keep_a, run.keep_rows, run.keep_blocks, stream=side)
+    side.synchronize()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(50_000_000)          # some 20 ms
+    counts, entries = run.eng.a_lists()
+    colany_c = run.eng.compacted()[2]
+    a = synth.unpack_bits(oracle.a_bits(w.X, w.pred, w.threshold, w.keep_a), w.K)
+    a = a[:, synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0]]
+    want = np.array([[a[i:i + 64, k:k + 128].sum() for k in range(0, a.shape[1], 128)] for i in range(0, w.M, 64)])
+    got, got_any = counts.clone(), colany_c.clone()
+    torch.cuda.current_stream().synchronize()
+    np.testing.assert_array_equal(got.cpu().numpy()[:, : want.shape[1]], want)
+    a = np.concatenate([a, np.zeros(((-w.M) % 32, a.shape[1]), bool)]).reshape(-1, 32, a.shape[1]).any(axis=1)
+    words = (a.shape[1] + 63) // 64
+    np.testing.assert_array_equal(got_any.cpu().numpy().view(np.uint64)[:, :words], synth.pack_bits(a))
+    torch.cuda.synchronize()
