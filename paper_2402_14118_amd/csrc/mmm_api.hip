@@ -64,7 +64,7 @@ Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw)
     l.bt_bits = off;
     off += align_up((size_t)NB * WA * 8);
     l.stats = off;
-    off += align_up(4 * 8);
+    off += align_up(6 * 8);
     // row-compacted mode: numbering of the live rows and maps over it
     l.kinfo = off;
     off += align_up(64);
@@ -145,6 +145,8 @@ struct MatrixProblem {
     int64_t steps;   // of 128 k that the kernel walks
     double units;    // per step and group: quads of listed k (16-bit: batches of 32)
     double batches;  // batches of 16 (32) slots
+    bool look;       // workgroups look for columns of A that are zero in their tile (floats)
+    bool filtered;   // and most will leave them out of their lists
 };
 MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt)
 {
@@ -152,8 +154,12 @@ MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt)
     const int64_t rows = known && m->b_compact ? std::max<int64_t>((int64_t)m->stats_rows_b, 1) : m->K;
     double p = known ? std::min(1.0, (double)m->stats_occ_b / ((double)rows * (double)m->NB)) : 0.2;
     if (m->bw == 8) p = 1.0 - (1.0 - p) * (1.0 - p);   // a group lists k if either of its blocks does
-    const double listed = p * MMM_AB_COLS, batch = elem_size(dt) == 2 ? 32.0 : 16.0;
+    const double batch = elem_size(dt) == 2 ? 32.0 : 16.0;
+    double listed = p * MMM_AB_COLS;
     MatrixProblem q;
+    q.look = dt == MMM_F32 && (!known || m->stats_active < 0.9);   // (looking takes about 1 us)
+    q.filtered = q.look && known && mmm_filter_pays((float)listed, (float)(listed * m->stats_active), m->bw);
+    if (q.filtered) listed *= m->stats_active;
     q.steps = (rows + MMM_AB_COLS - 1) / MMM_AB_COLS;
     q.batches = listed > 0.5 * batch ? listed / batch + 0.5 : 1.0;
     q.units = elem_size(dt) == 2 ? q.batches : listed / 4.0 + 0.5;
@@ -162,7 +168,11 @@ MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt)
 
 double matrix_cost(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const mmm_variant_info &vi, int64_t tiles, int64_t split)
 {
-    const MatrixCost &c = kMatrixCost[cost_class(dt)];
+    MatrixCost c = kMatrixCost[cost_class(dt)];
+    if (q.filtered) {   // lists made in the kernel (estimated from the timings at mmm_filter_pays, within 20 %)
+        c.multiply *= 1.35;
+        if (m->bw != 32) c.latency += 0.25, c.step += 0.2 * vi.TN / 256.0;
+    }
     const int64_t per_split = (q.steps + split - 1) / split, steps = (per_split + vi.k_ranges - 1) / vi.k_ranges;
     const int64_t wgs = tiles * split, per_cu = (wgs + 255) / 256;
     const double groups = vi.TN / MMM_GROUP_COLS, work = (double)steps * vi.k_ranges;
@@ -244,6 +254,7 @@ void compute_plan(const mmm_maps *m, int32_t dt, int64_t variant, int64_t fixed_
         }
     }
     plan->panel = panel_width(m, dt, q, *plan);
+    plan->filter = q.look ? 1 : 0;
     *cost = best;
 }
 
@@ -377,6 +388,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->plan_split = 0;
     m->plan_path = -1;
     m->stats_a_valid = m->stats_b_valid = false;
+    m->stats_active = 1.0;
     m->stats_nnz_a = m->stats_occ_b = m->stats_macs = m->stats_rows_b = m->stats_version = 0;
     m->plan_valid = false;
     *out = m;
@@ -523,7 +535,7 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
     if (!maps->a_built || !maps->b_built) return MMM_ERR_MAPS_MISMATCH;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = mmm_launch_stats(maps, s);
-    uint64_t host[4] = {0, 0, 0, 0};
+    uint64_t host[6] = {0, 0, 0, 0, 0, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(host, maps->stats, sizeof(host), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
@@ -534,6 +546,7 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
     maps->stats_occ_b = host[1];
     maps->stats_macs = host[2];
     maps->stats_rows_b = host[3];
+    maps->stats_active = host[5] != 0 ? (double)host[4] / ((double)host[5] * (double)maps->MBA) : 1.0;
     ++maps->stats_version;
     maps->stats_a_valid = maps->stats_b_valid = true;
     if (nnz_a) *nnz_a = host[0];

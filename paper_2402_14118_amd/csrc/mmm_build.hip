@@ -811,18 +811,29 @@ __global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_im
 // ---- statistics (off the hot path) -----------------------------------------------------------
 __global__ void mmm_stats_clear_kernel(uint64_t *stats)
 {
-    if (threadIdx.x < 4) stats[threadIdx.x] = 0;
+    if (threadIdx.x < 6) stats[threadIdx.x] = 0;
 }
 
 // One workgroup per 64 values of k: lane kb of every wave counts column k of A
-// over a slice of rows and row k of B over its words.
-__global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, const uint64_t *b_bits,
-                                                        int64_t M, int64_t K, int64_t WA, int64_t WB,
-                                                        int64_t bw, uint64_t *stats)
+// over a slice of rows and row k of B over its words.  Of the k that `rows` leaves on (all, if there is none) the number,
+// and in how many 64-row tiles each has a non-zero element.
+__global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, const uint64_t *b_bits, const uint64_t *a_colany,
+                                                        const uint64_t *rows, int64_t M, int64_t K, int64_t WA, int64_t WB,
+                                                        int64_t MT, int64_t bw, uint64_t *stats)
 {
     __shared__ uint32_t col[4 * 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int64_t w = blockIdx.x;
+    auto add = [&](int q, uint64_t x) {
+        for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
+        if (lane == 0 && x != 0) atomicAdd((unsigned long long *)&stats[q], (unsigned long long)x);
+    };
+    const uint64_t live = bits_below(rows != nullptr ? rows[w] : ~0ull, K - w * 64);
+    uint64_t active = 0;
+    for (int64_t t = 2 * (int64_t)threadIdx.x; t < MT; t += 512)
+        active += (uint64_t)__popcll((a_colany[t * WA + w] | a_colany[min(t + 1, MT - 1) * WA + w]) & live);
+    add(4, active);
+    if (wave == 3) add(5, lane == 0 ? (uint64_t)__popcll(live) : 0ull);
     uint32_t cnt = 0;
     for (int64_t r = wave; r < M; r += 4) cnt += (uint32_t)((a_bits[r * WA + w] >> lane) & 1ull);
     col[wave * 64 + lane] = cnt;
@@ -835,11 +846,7 @@ __global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, 
             for (int64_t j = 0; j < WB; ++j) rowcount += (uint64_t)__popcll(b_bits[k * WB + j]);
         uint64_t v[4] = {colcount, rowcount, colcount * rowcount * (uint64_t)bw, rowcount != 0 ? 1u : 0u};
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            uint64_t x = v[q];
-            for (int off = 32; off > 0; off >>= 1) x += __shfl_down(x, off, 64);
-            if (lane == 0 && x != 0) atomicAdd((unsigned long long *)&stats[q], (unsigned long long)x);
-        }
+        for (int q = 0; q < 4; ++q) add(q, v[q]);
     }
 }
 
@@ -1064,7 +1071,7 @@ hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s)
 {
     (void)hipGetLastError();
     hipLaunchKernelGGL(mmm_stats_clear_kernel, dim3(1), dim3(64), 0, s, m->stats);
-    hipLaunchKernelGGL(mmm_stats_kernel, dim3((uint32_t)m->WA), dim3(256), 0, s, m->a_bits, m->b_bits, m->M,
-                       m->K, m->WA, m->WB, (int64_t)m->bw, m->stats);
+    hipLaunchKernelGGL(mmm_stats_kernel, dim3((uint32_t)m->WA), dim3(256), 0, s, m->a_bits, m->b_bits, m->a_colany,
+                       m->b_compact ? m->rows_copy : nullptr, m->M, m->K, m->WA, m->WB, m->MT, (int64_t)m->bw, m->stats);
     return hipGetLastError();
 }

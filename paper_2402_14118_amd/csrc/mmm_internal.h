@@ -70,11 +70,22 @@ __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, 
 {
     return esz >= 4 ? slot * 16u + col : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
 }
+// Floats: per 128 k a group lists `all` k, of which `stay` have a non-zero column of A in the tile.  Whether the kernel is
+// faster when it makes the lists without the others (see `filtered` there) than with the lists as packed.  A step then costs
+// what about 10 listed k cost (half of that where a list serves two groups), and a listed k a quarter more.  Multiplication, plain
+// lists and without dead columns, us: 512 x 8192 x 4096, 12.8 listed: 52 and 52, 58 with a tenth, three tenths of the columns on;
+// 64 listed: 165 and 102, 134, 165 with .3, .5, .7; 4096^3, 6.4 listed: 93 and 112 with .02; 12.8: 149 and 134, 155 with
+// .1, .3; 128: 968 and 452, 866 with .3, .7; 2048 x 16384 x 4096, blocks of 32, 6.4 listed: 171 and 163, 188 with .1, .3.
+__host__ __device__ constexpr bool mmm_filter_pays(float all, float stay, int32_t bw)
+{
+    return all - stay >= 0.22f * all && all - stay >= (bw == 32 ? 5.5f : 10.f);
+}
 struct mmm_plan {
     int32_t variant;
     int32_t split_k;
     int32_t tiles_m, tiles_n;
     int32_t panel;             // tile columns that are gone through together (see panel_width)
+    int32_t filter;            // workgroups look whether to leave the columns that are zero in their tile out (floats)
     int32_t chunks_total;      // ceil(K / KC)
     int32_t chunks_per_split;
     int64_t workgroups;
@@ -108,7 +119,7 @@ struct mmm_maps {
     char *a_img64;     // image of A for double inputs, which have no lists: takes the place of a_ent
     uint64_t *b_bits;
     uint64_t *bt_bits;
-    uint64_t *stats;   // 4 words
+    uint64_t *stats;   // 6 words
     // Row-compacted mode (B side built with keep_rows): k' numbers the rows keep_rows leaves on, and the
     // matrix kernel walks k' instead of k.
     uint32_t *kinfo;       // [0] = number of live k (device)
@@ -138,6 +149,7 @@ struct mmm_maps {
     // what the most recent mmm_maps_stats call counted: the density estimate behind the choice of kernel
     mutable bool stats_a_valid, stats_b_valid;
     mutable uint64_t stats_nnz_a, stats_occ_b, stats_macs, stats_rows_b;   // non-zeros, blocks, surviving products, rows of B with a block
+    mutable double stats_active;   // share of the k that are on whose column of A has a non-zero element in a tile of 64 rows
     mutable int64_t stats_version;
     // the launch plan last made: it is made anew when its key changes
     mutable std::mutex plan_mutex;

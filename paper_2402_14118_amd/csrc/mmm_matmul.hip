@@ -55,7 +55,12 @@ struct MatmulParams {
     const uint16_t *bp_list;
     const uint32_t *bp_cnt;
     const uint32_t *kinfo;   // row-compacted mode: [0] = number of live k (everything above is then over k'); else null
-    int64_t M, N, KBA, NG;
+    // for the lists without the columns that are zero in the tile (4-byte types, see `filtered`)
+    const uint64_t *bt_bits;    // transposed B map, over k' in row-compacted mode
+    const uint64_t *a_colany;   // column-any words of A, over k
+    const uint32_t *kmap;       // row-compacted mode: k' -> k
+    int32_t bw;
+    int64_t M, N, KBA, NG, NB, WA, MT;
     int32_t tiles_m, tiles_n, panel, split_k, chunks_total, chunks_per_split;
     int32_t accumulate;
 };
@@ -113,6 +118,15 @@ template <int N> __device__ __forceinline__ void copy_to_lds(const char *base, u
                          : "memory");
     }
 }
+__device__ __forceinline__ uint32_t mbcnt64(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
+{
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), l) << 32) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)v, l);
+}
+
 // wait until at most N of the wave's vector-memory operations are outstanding (they complete in order)
 template <int N> __device__ __forceinline__ void wait_vmem()
 {
@@ -124,8 +138,9 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 //     workgroup: TN = 16*GW*NW columns
 // KS  groups of NW waves that share the tile and take consecutive ranges of its K (each with a ring of its own); their
 //     sums are added in LDS at the end, in order
-template <int RT, int GW, int NW, int KS, typename T>
-__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : 4))) void mmm_matmul_kernel(const MatmulParams p)
+// FILTER  floats: look whether to leave the columns of A out that are zero in the whole tile (see `filtered`)
+template <int RT, int GW, int NW, int KS, typename T, bool FILTER>
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
     constexpr bool WIDE = sizeof(T) >= 4, F64 = sizeof(T) == 8;
     constexpr int ESZ = (int)sizeof(T);
@@ -144,6 +159,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 
     constexpr int RING_BYTES = RING * SLAB + COLB;
     __shared__ __align__(1024) char rings[KS * RING_BYTES];
+    static_assert(!FILTER || ESZ == 4, "");
+    __shared__ __align__(16) uint16_t lists[FILTER ? KS * NW * 2 * KC : 1];   // of `filtered`: [wave][parity of the step][slot]
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -241,13 +258,10 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 
     const uint32_t c16 = (uint32_t)c * 16u;
     const uint32_t chunk8 = (uint32_t)(lane & 3) * 8u;
-    // left: slots of the list from the batch's first on (at least one)
-    auto multiply = [&](const Batch &b, int left) __attribute__((always_inline)) {
+    // 4- and 8-byte types: the operands of four quads, A's at these ring addresses; left: slots of the list from the batch's
+    // first on (at least one)
+    auto multiply_quads = [&](const uint32_t (&at)[4], const elem_t (&bf)[WIDE ? GW : 1][4], int left) __attribute__((always_inline)) {
         if constexpr (WIDE) {
-            // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
-            // entries count in 256)
-            const uint32_t at[4] = {__builtin_amdgcn_perm(b.list.x, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.x, c16, 0x0c070600u),
-                                    __builtin_amdgcn_perm(b.list.y, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.y, c16, 0x0c070600u)};
             avec a[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -272,9 +286,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll
                     for (int r = 0; r < RT; ++r) {
                         if constexpr (F64)
-                            acc[g][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
+                            acc[g][r] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u][r], bf[g][u], acc[g][r], 0, 0, 0);
                         else
-                            acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], b.bf[g][u], acc[g][r], 0, 0, 0);
+                            acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][r], bf[g][u], acc[g][r], 0, 0, 0);
                     }
             };
             quad(0);
@@ -285,6 +299,15 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     if (left > 12) quad(3);
                 }
             }
+        }
+    };
+    auto multiply = [&](const Batch &b, int left) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
+            // entries count in 256)
+            const uint32_t at[4] = {__builtin_amdgcn_perm(b.list.x, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.x, c16, 0x0c070600u),
+                                    __builtin_amdgcn_perm(b.list.y, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.y, c16, 0x0c070600u)};
+            multiply_quads(at, b.bf, left);
         } else {
             // ring address: entry * 16 with the rotation of the column's units in bits 5 and 6, plus this lane's four
             // rows; row tile r is 32 bytes on, before rotation
@@ -350,6 +373,132 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     };
 
     const int even_steps = (steps + 1) & ~1;   // steps go in pairs; the odd one past the end has no list
+
+    // ---- The same for an A whose columns are zero in all rows of the tile here and there (whole columns switched off, by
+    // context, for some rows or for all): the k of such columns are left out of the lists.  The wave makes the list of a step
+    // itself, one step ahead, from the occupancy of its group and the column-any words of the tile, and picks the rows of
+    // packed B by their slots, where the plain list reads them in order.  Nothing of it can be requested more than a step
+    // ahead, so a step takes 0.8 to 1.5 us however short its list is; it pays where the plain lists are long (2048 x 16384 x
+    // 4096, blocks of 32 all on, a tenth of the columns on in each tile: 1922 -> 348 us, a third of the blocks on 660 -> 212;
+    // 512 x 8192 x 4096 265 -> 70; see mmm_filter_pays).  Waves need not agree on it: the barriers and copies are the same.
+    // Floats only.  16-bit lists are multiplied in little more time than such steps take (2048 x 16384 x 4096 as above: 284 and
+    // 171 us with plain lists), doubles have the pair kernel, whose work is the surviving products.
+    const int64_t any_row0 = (int64_t)tile_m * (TM / MMM_COLANY_ROWS), any_row1 = min(any_row0 + 1, p.MT - 1);
+    const int64_t blk0 = p.bw == 8 ? Gc * 2 : Gc / GW, blk1 = min(p.bw == 8 ? blk0 + 1 : blk0, p.NB - 1);
+    auto filtered = [&]() __attribute__((always_inline)) {
+        struct Slots {
+            elem_t bf[WIDE ? GW : 1][4];
+            u32x2 e;   // slots 4u + s, 16 bits each: ring column | the row's place in the segment << 9
+        };
+        typedef u32x2 __attribute__((may_alias)) list_quad;
+        constexpr uint32_t ZERO = mmm_zero_col(RING);   // of slots past the end; no other column has this bit
+        static_assert(!FILTER || ZERO == 256, "nine bits");
+        uint16_t *const lst = lists + (FILTER ? wave_all * 2 * KC : 0);
+        const char *const vals = p.bp_val + Gc * p.KBA * SEGB;
+        typedef const __attribute__((address_space(4))) uint64_t scalar_words;   // (the same for all lanes)
+        scalar_words *const occ_row0 = (scalar_words *)(p.bt_bits + blk0 * p.WA), *const occ_row1 = (scalar_words *)(p.bt_bits + blk1 * p.WA);
+        scalar_words *const any_of0 = (scalar_words *)(p.a_colany + any_row0 * p.WA), *const any_of1 = (scalar_words *)(p.a_colany + any_row1 * p.WA);
+        struct Words { uint64_t occ[2], any[2]; };   // of a step
+        auto words_of = [&](int ch) __attribute__((always_inline)) -> Words {
+            Words w{{0, 0}, {0, 0}};
+            if (active && ch < chunk_end) {
+                const int64_t at = 2 * (int64_t)ch, at1 = min(at + 1, p.WA - 1);
+                w.occ[0] = occ_row0[at] | occ_row1[at];
+                w.occ[1] = occ_row0[at1] | occ_row1[at1];
+                w.any[0] = any_of0[at] | any_of1[at];
+                w.any[1] = any_of0[at1] | any_of1[at1];
+                if (at1 == at) w.occ[1] = 0;
+            }
+            return w;
+        };
+        Words next_words = words_of(chunk_begin);
+        // the list of step ch, whose words these are, to its half of the wave's list; its length.  Takes the words of the next.
+        auto prepare = [&](int ch) __attribute__((always_inline)) -> int {
+            const Words w = next_words;
+            next_words = words_of(ch + 1);
+            uint64_t m[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                m[h] = w.occ[h] & w.any[h];
+                if (p.kinfo != nullptr) {   // the column-any words are over k: the step's bits, one by one
+                    const uint32_t kc = (uint32_t)(ch * KC + 64 * h + lane);
+                    bool any = false;
+                    if (kc < *p.kinfo) {
+                        const uint32_t k = p.kmap[kc];
+                        any = ((p.a_colany[any_row0 * p.WA + (k >> 6)] | p.a_colany[any_row1 * p.WA + (k >> 6)]) >> (k & 63u)) & 1ull;
+                    }
+                    m[h] = w.occ[h] & __ballot(any);
+                }
+            }
+            const uint32_t n0 = (uint32_t)__popcll(m[0]), n = n0 + (uint32_t)__popcll(m[1]);
+            uint16_t *const out = lst + (ch & 1) * KC;
+            const uint32_t col = (uint32_t)(ch & (RING - 1)) * KC + (uint32_t)lane;
+            if (__builtin_amdgcn_inverse_ballot_w64(m[0])) out[mmm_list_pos(4, mbcnt64(m[0]))] = (uint16_t)(col | mbcnt64(w.occ[0]) << 9);
+            if (__builtin_amdgcn_inverse_ballot_w64(m[1]))
+                out[mmm_list_pos(4, n0 + mbcnt64(m[1]))] = (uint16_t)((col + 64u) | ((uint32_t)__popcll(w.occ[0]) + mbcnt64(w.occ[1])) << 9);
+            if ((uint32_t)lane < (0u - n) % BATCH) out[mmm_list_pos(4, n + (uint32_t)lane)] = (uint16_t)ZERO;
+            return (int)n;
+        };
+        auto fetch = [&](Slots &b, int ch, int batch) __attribute__((always_inline)) {
+            b.e = *reinterpret_cast<const list_quad *>(lst + (ch & 1) * KC + batch * BATCH + s * 4);
+            uint32_t at[4];   // slots past the end: past the segment's, which reads as zero
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t e = b.e[u >> 1] >> (16 * (u & 1));
+                at[u] = ((e & 0xfe00u) >> 3) + ((e & ZERO) << 8) + (uint32_t)c * 4u;
+            }
+#pragma unroll
+            for (int g = 0; g < (WIDE ? GW : 0); ++g) {
+                const __amdgpu_buffer_rsrc_t seg = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<char *>(vals) + (int64_t)ch * SEGB + (int64_t)g * val_next, 0, SEGB, 0x00020000);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) b.bf[g][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(seg, (int)at[u], 0, 0));
+            }
+        };
+        auto landed = [&](Slots &b) __attribute__((always_inline)) {   // waited for here
+#pragma unroll
+            for (int g = 0; g < (WIDE ? GW : 0); ++g) asm volatile("" : "+v"(b.bf[g][0]), "+v"(b.bf[g][1]), "+v"(b.bf[g][2]), "+v"(b.bf[g][3]));
+        };
+        auto multiply_slots = [&](const Slots &b, int left) __attribute__((always_inline)) {
+            const uint32_t e0 = b.e.x & 0x01ff01ffu, e1 = b.e.y & 0x01ff01ffu;
+            const uint32_t at[4] = {__builtin_amdgcn_perm(e0, c16, 0x0c050400u), __builtin_amdgcn_perm(e0, c16, 0x0c070600u),
+                                    __builtin_amdgcn_perm(e1, c16, 0x0c050400u), __builtin_amdgcn_perm(e1, c16, 0x0c070600u)};
+            multiply_quads(at, b.bf, left);
+        };
+        Slots S0{}, S1{}, S2{};
+        // b: the first batch of step ch (n slots), next: that of the step after; S2: the second of either
+        auto one = [&](int ch, int n, Slots &b, Slots &next) __attribute__((always_inline)) -> int {
+            landed(b);
+            landed(S2);
+            wait_vmem<0>();   // the block too
+            asm volatile("s_barrier" ::: "memory");
+            const int n_next = prepare(ch + 1);
+            const bool early = n <= BATCH;   // S2 is free
+            if (n_next > 0) fetch(next, ch + 1, 0);
+            if (early && n_next > BATCH) fetch(S2, ch + 1, 1);
+            if (to_copy > 0) copy_block();
+            if (n > 0) {
+                multiply_slots(b, n);
+                if (n > BATCH) {
+                    multiply_slots(S2, n - BATCH);
+                    for (int j = 2; j * BATCH < n; ++j) {
+                        fetch(b, ch, j);
+                        multiply_slots(b, n - j * BATCH);
+                    }
+                }
+            }
+            if (!early && n_next > BATCH) fetch(S2, ch + 1, 1);
+            return n_next;
+        };
+        int n = prepare(chunk_begin);
+        if (n > 0) fetch(S0, chunk_begin, 0);
+        if (n > BATCH) fetch(S2, chunk_begin, 1);
+        for (int i = 0; i < even_steps; i += 2) {
+            n = one(chunk_begin + i, n, S0, S1);
+            n = one(chunk_begin + i + 1, n, S1, S0);
+        }
+    };
+
     if (chunk_begin < chunk_end) {
 #pragma unroll
         for (int i = 0; i < RING - 1; ++i)
@@ -358,6 +507,32 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         request(B0, off_v, off_l);
         request(B1, off_v + SEGB, off_l + SEG_L);
         wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
+        bool filter = false;
+        if constexpr (FILTER) {   // does it pay here?  slots listed in some steps, and those that would stay
+            uint32_t all = 0, stay = 0;
+            const int ch = chunk_begin + (int)((int64_t)(chunk_end - chunk_begin) * lane / 64);   // a step per lane, from the whole range
+            if (active) {
+                const int64_t at = 2 * (int64_t)ch;
+                const uint64_t occ = p.bt_bits[blk0 * p.WA + at] | p.bt_bits[blk1 * p.WA + at];
+                all = (uint32_t)__popcll(occ);
+                stay = (uint32_t)__popcll(occ & (p.a_colany[any_row0 * p.WA + at] | p.a_colany[any_row1 * p.WA + at]));
+            }
+#pragma unroll
+            for (int d = 32; d > 0; d >>= 1) {
+                all += (uint32_t)__shfl_xor((int)all, d, 64);
+                stay += (uint32_t)__shfl_xor((int)stay, d, 64);
+            }
+            if (p.kinfo != nullptr) {   // (the words are over k: 64 columns of the range instead)
+                const uint32_t from = (uint32_t)chunk_begin * KC, count = min(*p.kinfo, (uint32_t)chunk_end * KC) - from;
+                const uint32_t k = p.kmap[from + (uint32_t)((uint64_t)count * (uint32_t)lane / 64u)];
+                const uint64_t any = p.a_colany[any_row0 * p.WA + (k >> 6)] | p.a_colany[any_row1 * p.WA + (k >> 6)];
+                stay = all * (uint32_t)__popcll(__ballot((any >> (k & 63u)) & 1ull)) / 64u;
+            }
+            filter = __builtin_amdgcn_readfirstlane(mmm_filter_pays((float)all / 32.f, (float)stay / 32.f, p.bw) ? 1 : 0) != 0;   // 64 times 64 k
+        }
+        if (filter) {
+            if constexpr (FILTER) filtered();
+        } else {
         bool first = true;
         for (int done = 0; done < even_steps; done += 62) {   // lane i: length of the list of step done + i
             const int ch = chunk_begin + done + lane;
@@ -373,6 +548,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 step(n1, n2, B1);
                 n = n2;
             }
+        }
         }
     } else if (KS > 1) {   // no step left for this range of K: only the barriers of the others
         for (int i = 0; i < even_steps; ++i) asm volatile("s_barrier" ::: "memory");
@@ -501,20 +677,24 @@ struct VariantEntry {
     mmm_variant_info info;
     int32_t waves;              // of 16 columns each; 32-wide blocks: half as many waves of 32 columns
     matmul_kernel_fn fn[2][4];  // [bw == 32][element type]; null: not built
+    matmul_kernel_fn filter[2]; // [bw == 32]: floats, without the columns of A that are zero in the tile
 };
 
 #define MMM_KERNELS(RT, GW, NW, KS)                                                                                       \
-    mmm_matmul_kernel<RT, GW, NW, KS, float>, mmm_matmul_kernel<RT, GW, NW, KS, uint16_t>, mmm_matmul_kernel<RT, GW, NW, KS, _Float16>
+    mmm_matmul_kernel<RT, GW, NW, KS, float, false>, mmm_matmul_kernel<RT, GW, NW, KS, uint16_t, false>,                  \
+        mmm_matmul_kernel<RT, GW, NW, KS, _Float16, false>
+#define MMM_FILTERS(RT, NW, KS) {mmm_matmul_kernel<RT, 1, NW, KS, float, true>, mmm_matmul_kernel<RT, 2, NW / 2, KS, float, true>}
 #define MMM_VARIANT(RT, NW)                                                                                               \
     {                                                                                                                     \
         {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT, 1, true}, NW,                                                    \
-            {{MMM_KERNELS(RT, 1, NW, 1), mmm_matmul_kernel<RT, 1, NW, 1, double>},                                        \
-             {MMM_KERNELS(RT, 2, NW / 2, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, double>}}                                \
+            {{MMM_KERNELS(RT, 1, NW, 1), mmm_matmul_kernel<RT, 1, NW, 1, double, false>},                                 \
+             {MMM_KERNELS(RT, 2, NW / 2, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, double, false>}},                        \
+            MMM_FILTERS(RT, NW, 1)                                                                                        \
     }
 #define MMM_VARIANT_K2(RT, NW) /* two rings: not for doubles */                                                           \
     {                                                                                                                     \
         {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false}, NW,                                                 \
-            {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}                              \
+            {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}, MMM_FILTERS(RT, NW, 2)      \
     }
 
 const VariantEntry g_variants[] = {
@@ -577,6 +757,13 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     p.bp_list = m->bp_list;
     p.bp_cnt = m->bp_cnt;
     p.kinfo = m->b_compact ? m->kinfo : nullptr;
+    p.bt_bits = m->b_compact ? m->btc_bits : m->bt_bits;
+    p.a_colany = m->a_colany;
+    p.kmap = m->kmap;
+    p.bw = m->bw;
+    p.NB = m->NB;
+    p.WA = m->WA;
+    p.MT = m->MT;
     p.M = m->M;
     p.N = m->N;
     p.KBA = m->KBA;
@@ -592,7 +779,7 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     if (pl.split_k > 1 && (size_t)pl.split_k * (size_t)m->M * (size_t)m->N * (f64 ? sizeof(double) : sizeof(float)) > partial_bytes)
         return hipErrorInvalidValue;
     const int wide = m->bw == 32 ? 1 : 0;
-    matmul_kernel_fn fn = v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
+    matmul_kernel_fn fn = pl.filter ? v.filter[wide] : v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
     if (fn == nullptr) return hipErrorInvalidValue;
     (void)hipGetLastError();   // drop any stale error another library left on this thread
     hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.waves >> wide) * (uint32_t)v.info.k_ranges * 64), 0, s, p);

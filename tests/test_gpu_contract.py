@@ -102,3 +102,73 @@ def test_inspection_needs_no_stream_of_the_build():
     words = (a.shape[1] + 63) // 64
     np.testing.assert_array_equal(got_any.cpu().numpy().view(np.uint64)[:, :words], synth.pack_bits(a))
     torch.cuda.synchronize()
+
+
+# ---- columns of A that are zero in all 64 rows of a tile ---------------------------------------
+def _structured(M, K, N, bw, p_cols, p_b, p_rows, seed):
+    """Every 64 rows of A have their own share p_cols of columns on, dense inside; rows of Y that meet only dead columns of
+    a tile hold Inf, which shows in that tile if they are multiplied."""
+    w = synth.random_masked(M, K, N, bw, 0.5, p_b, seed, dist="smallint", p_rows=p_rows)
+    rng = np.random.default_rng(seed)
+    on = rng.random(((M + 63) // 64, K)) < p_cols
+    keep = synth.unpack_bits(w.keep_a, K) & np.repeat(on, 64, axis=0)[:M]
+    w.keep_a = synth.pack_bits(keep)
+    return w, keep
+
+
+@pytest.mark.parametrize("counted", [True, False], ids=["stats", "no_stats"])
+@pytest.mark.parametrize("M,K,N,bw,p_cols,p_b,p_rows", [
+    (65, 1280, 48, 16, 0.1, 1.0, None), (200, 1111, 272, 8, 0.1, 0.9, None), (130, 2100, 288, 32, 0.05, 1.0, None),
+    (70, 9000, 96, 16, 0.1, 0.9, None),          # more steps than list lengths are held for at a time
+    (130, 6000, 272, 16, 0.1, 1.0, 0.3),         # over the live rows of B
+    (100, 128, 64, 16, 0.0, 1.0, None),          # nothing on
+])
+def test_dead_columns_are_not_multiplied(M, K, N, bw, p_cols, p_b, p_rows, counted):
+    w, keep = _structured(M, K, N, bw, p_cols, p_b, p_rows, M + K)
+    _, _, C_ref, _ = oracle.run_workload(w)
+    # the first tile's dead columns: Inf in those rows of Y
+    dead = ~keep[:64].any(axis=0)
+    w.Y = np.where(dead[:, None], np.float32(np.inf), w.Y)
+    run = HipRun(w)
+    run.eng.set_path(mm.MMM_PATH_MATRIX)
+    run.build()
+    if counted:
+        run.eng.stats()
+    for variant, split in [(-1, 0)] + [(v, 1 + v % 3) for v in range(mm.mmm_matmul_variant_count()) if not mm.mmm_matmul_variant_name(v).startswith("R2")]:
+        print("variant", variant, "split", split, flush=True)
+        run.eng.set_plan(variant, split)
+        run.Cbuf.fill_(float("nan"))
+        run.matmul()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy()[:64], C_ref[:64])
+
+
+@pytest.mark.parametrize("bw", [8, 16, 32])
+@pytest.mark.parametrize("M,p_rows", [(64, None), (30, None), (200, None), (30, 0.5), (200, 0.5)])
+def test_lists_without_dead_columns_of_every_length(M, p_rows, bw):
+    """Segments whose lists hold every number of slots around the batch and quad sizes, before and after the dead columns
+    are left out, in every tile; waves without columns; the last segment a short one."""
+    lengths = [0, 1, 3, 4, 5, 15, 16, 17, 31, 32, 33, 127, 128, 0, 64]
+    segs, N = 66, 160
+    K = segs * 128 - 70
+    rng = np.random.default_rng(bw + M)
+    w = synth.random_masked(M, K, N, bw, 1.0, 0.9, 177 + bw, dist="smallint", p_rows=p_rows)
+    on = np.zeros(((M + 63) // 64, segs * 128), bool)
+    for t in range(on.shape[0]):
+        for s in range(segs):
+            on[t, s * 128 + rng.permutation(128)[:lengths[(s + 7 * t) % len(lengths)]]] = True
+    w.keep_a = synth.pack_bits(np.repeat(on[:, :K], 64, axis=0)[:M] & (rng.random((M, K)) < 0.7))
+    _, _, C_ref, _ = oracle.run_workload(w)
+    run = HipRun(w)
+    run.eng.set_path(mm.MMM_PATH_MATRIX)
+    run.build()
+    for variant in range(mm.mmm_matmul_variant_count()):
+        if mm.mmm_matmul_variant_name(variant).startswith("R2") != (M <= 32):
+            continue
+        for split in (1, 2):
+            print("variant", variant, "split", split, flush=True)
+            run.eng.set_plan(variant, split)
+            run.Cbuf.fill_(float("nan"))
+            run.matmul()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
