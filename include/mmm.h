@@ -263,9 +263,9 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
  * "matmul_variant" option).  Else, once a mmm_maps_stats call on the handle has counted the
  * non-zeros, blocks and surviving products (the most recent counts are kept as the estimate
  * across rebuilds), the kernel whose estimated time is less; the estimates are fitted to timings
- * on an MI355X.  For A with fewer than 4 % of its elements and more than 64 rows: PAIRS iff
- * p_B * (1 - 24.5 * p_A) > 0.015.  Without counts the shape decides: PAIRS for at most 64 rows, else
- * MATRIX; double inputs: MATRIX iff M * K * N is at least 2^27 (and M above 64).  The paper
+ * on an MI355X.  (Double inputs of at most 24 tiles of 64 x 64: PAIRS.)  Without counts the shape
+ * decides: PAIRS for at most 64 rows, else MATRIX; double inputs: MATRIX iff M * K * N is at least
+ * 2^27 (and M above 64).  The paper
  * leaves this per-workload choice of method to the caller (section 6, choosing between methods
  * by sparsity). */
 #define MMM_PATH_MATRIX 0

@@ -102,11 +102,12 @@ size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 //
 // A table of thresholds cannot follow this choice: it depends on the shape, both densities and how evenly the
 // workgroups fall on 256 compute units.  So both kernels' times are estimated and the least is taken.  The
-// estimates are sums of terms with a meaning each; their coefficients are a least-squares fit to 2000 random problems (200
-// to 4096 in each dimension, few rows with K up to 16384, densities .05 to 1, all types), built and multiplied in turn with
-// every variant and a dozen splits.  They are within 8 % (matrix) and 12 % (pairs) of the measurements, and what is chosen
-// from them takes 1 to 2 % longer than the best choice; the former thresholds, 17 % among the matrix kernel's
-// plans and 17 (doubles) to 37 % (16-bit) over both kernels.
+// estimates are sums of terms with a meaning each; their coefficients are a least-squares fit to random problems (200 to 4096
+// in each dimension, few rows with K up to 16384, densities .05 to 1, all types), built and multiplied with every variant and
+// a dozen splits.  What is chosen from them, against other random problems (profiles/kernel_choice.txt): the kernel takes 1 % longer
+// than the faster one in the mean, 1 to 3 % where A keeps .2 to 5 % of its elements, outside the fit (a rule of thresholds fitted to
+// 4096^3 floats decided there before: 5 % floats, 7 % doubles, 22 % 16-bit); the tile and split 1 % (16-bit) to 3 % longer than the best.
+// The estimates themselves lie 10 to 25 % from back-to-back timings, mostly above, which hide the launch.
 struct MatrixCost {   // microseconds
     double launch;        // per call
     double latency;       // per step and batch of its longest lists: nobody hides the first wave's waiting
@@ -201,7 +202,9 @@ double pairs_cost(const mmm_maps *m, int32_t dt)
 {
     const PairsCost &c = kPairsCost[cost_class(dt)];
     const double spans = (double)m->M * (double)((m->N + 63) / 64), products = (double)m->stats_macs;
-    const int64_t ranges = (m->WA + 63) / 64, shares = (m->N + 511) / 512 * m->M >= 1024 ? 1 : 4;   // see mmm_launch_pairs
+    const int64_t ranges = (m->WA + 63) / 64, shares = (m->N + 511) / 512 * m->M >= 1024 ? 1 : 4;
+    // (4 shares for few workgroups whatever K is, as the coefficients were fitted; mmm_launch_pairs takes 1 for K <= 2048.  With its
+    // number here the choice was no better: 984 float problems 1.5 instead of 1.2 % longer than the faster kernel, refitted 1.6.)
     return c.launch + (double)((ranges + shares - 1) / shares) * c.range + 1e-5 * spans * (double)ranges * c.word +
            1e-9 * products * c.product[m->bw == 8 ? 0 : m->bw == 16 ? 1 : 2] + 0.01 * products / (spans * (double)shares * 64.0) * c.list;
 }
@@ -283,9 +286,6 @@ int32_t choose_path(const mmm_maps *m, int32_t dt)
         if (dt == MMM_F64) return (double)m->M * (double)m->K * (double)m->N >= 134217728.0 ? MMM_PATH_MATRIX : MMM_PATH_PAIRS;
         return m->M <= 64 ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
     }
-    // an A that keeps less than 4 % of its elements: outside the range of the fit, an earlier one holds (4096^3)
-    const double p_a = (double)m->stats_nnz_a / ((double)m->M * (double)m->K), p_b = (double)m->stats_occ_b / ((double)m->K * (double)m->NB);
-    if (m->M > 64 && p_a < 0.04) return p_b * (1.0 - 24.5 * p_a) > 0.015 ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
     // doubles of a few tiles: the matrix kernel leaves nearly all of the chip idle, and the estimates are poor there
     // (215 x 722 x 320: 7.1 against 8.7 us; from 28 tiles on it is the estimates that decide better)
     if (dt == MMM_F64 && ((m->M + 63) / 64) * ((m->N + 63) / 64) <= 24) return MMM_PATH_PAIRS;

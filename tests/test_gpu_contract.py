@@ -172,3 +172,14 @@ def test_lists_without_dead_columns_of_every_length(M, p_rows, bw):
             run.matmul()
             torch.cuda.synchronize()
             np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+
+
+# ---- the choice between the kernels where A keeps few of its elements --------------------------
+@pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16], ids=["bf16", "f16"])
+@pytest.mark.parametrize("M,K,N,p_a,p_b", [(512, 8192, 4096, 0.03, 0.1), (512, 8192, 4096, 0.03, 0.5)])
+def test_16_bit_inputs_with_few_elements_of_a_take_the_matrix_kernel(M, K, N, p_a, p_b, dtype):
+    w = synth.random_masked(M, K, N, 16, p_a, p_b, 9, dist="smallint", dtype=dtype)
+    run = HipRun(w)
+    run.build()
+    run.eng.stats()
+    assert run.eng.path() == mm.MMM_PATH_MATRIX
