@@ -5,8 +5,7 @@ A step is one pass of the whole path on device-resident inputs:
 mmm_build_maps (both sides) followed by mmm_matmul.
 
 With no --workload the run covers the sparsity sweep the metric is quoted on
-(benchmark configs[2]: M=K=N=4096 fp32, the same keep fraction for the
-elements of A and the 16-wide blocks of B, 0.40 ... 0.05, i.e. 60-95 % zeros;
+(M=K=N=4096 fp32, the same keep fraction for the elements of A and the 16-wide blocks of B, 0.40 ... 0.05, i.e. 60-95 % zeros;
 the counterpart of the paper's Fig. 1 and of its section 4 "Varying sparsity").
 `value` is the useful GFLOP/s of the point with 80 % zeros (the sparsity the
 paper's headline comparison is made at); every point of the sweep is in `sweep`,
@@ -30,7 +29,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0             # MI355X HBM3E, published
 FP32_VECTOR_PEAK_TFLOPS = 157.3   # 256 CUs x 4 SIMDs x 16 lanes x 2 (packed) x 2 flops x 2.4 GHz
 FP32_MFMA_PEAK_TFLOPS = 157.3
-FP64_VECTOR_PEAK_TFLOPS = 78.6    # published; the pair kernel's FMAs on double inputs
+FP64_VECTOR_PEAK_TFLOPS = 78.6    # published; the matrix instructions have the same peak
 BF16_MFMA_PEAK_TFLOPS = 2500.0    # dense bf16 / fp16 matrix peak, published
 HEADLINE_POINT = 2                # index into the sweep: keep fraction 0.20 = 80 % zeros
 
@@ -227,14 +226,12 @@ def measure(w, steps, warmup, args, dense=True, trials=True):
     # matrix path: every occupied block of B against all rows of A; pair path: the surviving products only
     issued_flops = 2.0 * w.M * occ_b * w.bw if path == mm.MMM_PATH_MATRIX else useful_flops
 
-    # algorithmic bytes of one launch: what the method itself must move (image of A, packed B, maps, C)
+    # Algorithmic bytes of one launch, the same whatever forms this library keeps its operands in: the builder reads X, the
+    # switched-on blocks of Y and the keep bitmaps and writes the two maps; the multiplication reads the maps, the non-zero elements
+    # of A and the occupied blocks of B and writes C.  (Images, packed copies, lists and derived maps are the design's own.)
     WA, NB = (w.K + 63) // 64, w.N // w.bw
     WB = (NB + 63) // 64
-    a_bits_b, colany_b = w.M * WA * 8, ((w.M + 31) // 32) * WA * 8
-    b_bits_b, bt_b = w.K * WB * 8, NB * WA * 8
-    live = w.K if w.keep_rows is None else int(synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K).sum())
-    a_img_b = ((w.M + 63) // 64) * 64 * ((live + 127) // 128) * 128 * esz     # the live columns of X, zeros included
-    b_pack_b = occ_b * (w.bw * esz + 2)             # values and list entries (groups of 16 columns: at least these)
+    a_bits_b, b_bits_b = w.M * WA * 8, w.K * WB * 8
     kb = np.ones((w.K, NB), dtype=bool)             # blocks the keep bitmaps leave switched on: the builder must read them
     if w.keep_rows is not None:
         kb &= synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0][:, None]
@@ -244,12 +241,8 @@ def measure(w, steps, warmup, args, dense=True, trials=True):
     del kb
     keep_in_b = (a_bits_b if w.keep_a is not None else 0) + (b_bits_b if w.keep_blocks is not None else 0) \
         + (WA * 8 if w.keep_rows is not None else 0)
-    build_bytes = w.M * w.K * esz + kept_blocks * w.bw * esz + keep_in_b \
-        + a_bits_b + colany_b + a_img_b + b_bits_b + bt_b + b_pack_b
-    if path == mm.MMM_PATH_MATRIX:   # image of A, packed B, C
-        matmul_bytes = a_img_b + b_pack_b + w.M * w.N * csz
-    else:                            # pair kernel: the non-zero elements of X, both bitmaps, occupied blocks of Y, C
-        matmul_bytes = nnz_a * esz + a_bits_b + bt_b + occ_b * w.bw * esz + w.M * w.N * csz
+    build_bytes = w.M * w.K * esz + kept_blocks * w.bw * esz + keep_in_b + a_bits_b + b_bits_b
+    matmul_bytes = nnz_a * esz + occ_b * w.bw * esz + a_bits_b + b_bits_b + w.M * w.N * csz
 
     # arithmetic peak the multiplication is priced against: fp32 inputs run on fp32 units (vector FMA and the fp32
     # matrix instruction share one peak); 16-bit inputs on the matrix path run on the 16-bit matrix instructions
