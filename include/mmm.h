@@ -39,7 +39,7 @@
  *     every row i whose a_bits[i,k] is set (as the definition gives), and for the
  *     remaining rows it is either the value of the definition or NaN (the matrix
  *     instruction path multiplies an occupied block by explicit zeros for rows
- *     whose element of A is zero).
+ *     whose element of A is zero, unless it leaves that k out for the whole tile).
  */
 #ifndef MMM_H
 #define MMM_H
@@ -183,7 +183,8 @@ mmm_status mmm_maps_view_compacted(const mmm_maps *maps, int32_t *on, const uint
  * columns and every step of 128 values of k (of k' in row-compacted mode), the ascending list of
  * the k in that step for which the group's block(s) of B are occupied and some row of the tile has a
  * non-zero element of A.  (The matrix kernel walks the lists of packed B, which are these without
- * the condition on A.)  Derived from the transposed B map and the column-any words and written to
+ * the condition on A, or makes these itself where that is faster.)  Read back from the counts and lists
+ * of packed B as the kernel takes them, held against the column-any words, and written to
  * `out` (device memory):
  *     record (tile t, group G, step c) at byte ((t * groups + G) * steps + c) * 132, where
  *     groups = 16 * ceil(N / 256), steps = ceil(K / 128):
@@ -252,7 +253,9 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
 
 /* Which kernel mmm_matmul uses.
  *   MMM_PATH_MATRIX: matrix instructions over the packed rows of each 16-column group; skips B's
- *       empty blocks exactly, multiplies A's zeros.  Work grows with B's density alone.
+ *       empty blocks exactly and multiplies A's zeros, but for float inputs, where it leaves out the k
+ *       whose column of A is zero in a whole tile of 64 rows if there are enough of them to pay.  Work
+ *       grows with B's density, and with that share.
  *   MMM_PATH_PAIRS : vector FMAs over exactly the products that survive both maps (the loop of
  *       Fig. "MMM Pseudocode": skip when the element of A is zero, skip the empty blocks of the row
  *       of B), found by AND-ing the bitmap row of A with the transposed B map.  Work grows with

@@ -500,7 +500,7 @@ mmm_status mmm_debug_k_lists(const mmm_maps *maps, void *out, size_t out_bytes, 
 {
     if (maps == nullptr) return MMM_ERR_INVALID_ARG;
     if (!maps->a_built || !maps->b_built) return MMM_ERR_MAPS_MISMATCH;
-    if (maps->a_dtype == MMM_F64) return MMM_ERR_DTYPE;   // double inputs have no matrix kernel
+    if (maps->a_dtype == MMM_F64 || !mmm_packs(maps->M, maps->b_dtype)) return MMM_ERR_DTYPE;
     size_t need = 0;
     const hipError_t e = mmm_launch_dump_lists(maps, static_cast<uint8_t *>(out), out_bytes, &need,
                                                static_cast<hipStream_t>(hip_stream));

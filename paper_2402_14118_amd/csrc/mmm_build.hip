@@ -1024,29 +1024,37 @@ hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s)
     return hipGetLastError();
 }
 
-// Per-tile active-k lists (see mmm_debug_k_lists): one wave per (row tile of 64, 16-column group,
-// step of 128 k).
-__global__ __launch_bounds__(64) void mmm_k_lists_kernel(const uint64_t *a_colany, const uint64_t *bt_bits, const uint32_t *kinfo,
-                                                         uint8_t *out, int64_t K, int64_t NB, int64_t WA, int64_t MT, int64_t bw,
+// Per-tile active-k lists (see mmm_debug_k_lists), read back from what the matrix kernel takes: counts and list entries of
+// packed B, held against the column-any words.  One wave per (row tile of 64, 16-column group, step of 128 k).
+template <typename T>
+__global__ __launch_bounds__(64) void mmm_k_lists_kernel(const uint64_t *a_colany, const uint16_t *bp_list, const uint32_t *bp_cnt,
+                                                         const uint32_t *kinfo, uint8_t *out, int64_t NG, int64_t WA, int64_t MT,
                                                          int64_t groups, int64_t steps)
 {
+    constexpr int RING = mmm_ring(sizeof(T));
     const int lane = threadIdx.x;
     const int64_t c = blockIdx.x % steps, G = (blockIdx.x / steps) % groups, t = blockIdx.x / (steps * groups);
     if (kinfo && c * MMM_AB_COLS >= (int64_t)*kinfo) return;
     uint8_t *rec = out + ((t * groups + G) * steps + c) * 132;
     uint32_t n = 0;
-    for (int h = 0; h < 2; ++h) {
-        const int64_t w = 2 * c + h;
-        uint64_t m = 0;
-        if (w < WA) {
-            const int64_t b0 = G * MMM_GROUP_COLS / bw, b1 = (G * MMM_GROUP_COLS + MMM_GROUP_COLS - 1) / bw;
-            for (int64_t b = b0; b <= b1 && b < NB; ++b) m |= bt_bits[b * WA + w];
-            uint64_t any = 0;
-            for (int64_t tt = 2 * t; tt < 2 * t + 2 && tt < MT; ++tt) any |= a_colany[tt * WA + w];
-            m &= any;
+    if (G < NG) {
+        const uint32_t slots = bp_cnt[G * steps + c];
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t slot = (uint32_t)(64 * h + lane);
+            const uint32_t entry = bp_list[(G * steps + c) * SEG + mmm_list_pos(sizeof(T), slot)];
+            const uint32_t k = (sizeof(T) == 2 ? entry >> 3 : sizeof(T) == 8 ? entry >> 1 : entry) - (uint32_t)(c & (RING - 1)) * SEG;   // see mmm_list_entry
+            bool in = false;
+            if (slot < slots && k < (uint32_t)SEG) {
+                const int64_t w = 2 * c + (k >> 6);
+                uint64_t any = 0;
+                if (w < WA)
+                    for (int64_t tt = 2 * t; tt < 2 * t + 2 && tt < MT; ++tt) any |= a_colany[tt * WA + w];
+                in = (any >> (k & 63u)) & 1ull;
+            }
+            const uint64_t m = ballot64(in);
+            if (in) rec[4 + n + mbcnt64(m)] = (uint8_t)k;
+            n += (uint32_t)__popcll(m);
         }
-        if ((m >> lane) & 1ull) rec[4 + n + mbcnt64(m)] = (uint8_t)(64 * h + lane);
-        n += (uint32_t)__popcll(m);
     }
     if (lane == 0) *reinterpret_cast<uint32_t *>(rec) = n;
 }
@@ -1061,9 +1069,9 @@ hipError_t mmm_launch_dump_lists(const mmm_maps *m, uint8_t *out, size_t out_byt
     if (m->b_compact)
         if (hipError_t e = mmm_launch_colany_compact(m, s); e != hipSuccess) return e;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(mmm_k_lists_kernel, dim3((uint32_t)wgs), dim3(64), 0, s, m->b_compact ? m->a_colany_c : m->a_colany,
-                       m->b_compact ? m->btc_bits : m->bt_bits, m->b_compact ? m->kinfo : nullptr, out, m->K, m->NB, m->WA, m->MT,
-                       (int64_t)m->bw, groups, m->KBA);
+    const auto kernel = m->b_dtype == MMM_F64 ? mmm_k_lists_kernel<double> : m->b_dtype == MMM_F32 ? mmm_k_lists_kernel<float> : mmm_k_lists_kernel<uint16_t>;
+    hipLaunchKernelGGL(kernel, dim3((uint32_t)wgs), dim3(64), 0, s, m->b_compact ? m->a_colany_c : m->a_colany, m->bp_list, m->bp_cnt,
+                       m->b_compact ? m->kinfo : nullptr, out, m->NG, m->WA, m->MT, groups, m->KBA);
     return hipGetLastError();
 }
 

@@ -101,8 +101,8 @@ def check_compacted(run, ab, bb, w, what):
 
 
 def check_k_lists(run, ab, bb, w, what):
-    """The per-tile active-k lists the matrix kernel walks, as its own list construction writes them out: for every row
-    tile of 64, 16-column group and step of 128 the ascending k with (some non-zero of A in the tile's column k) and
+    """The per-tile active-k lists, read back from the counts and lists of packed B that the matrix kernel takes: for every
+    row tile of 64, 16-column group and step of 128 the ascending k with (some non-zero of A in the tile's column k) and
     (the group's block(s) of B occupied in row k) -- over the live rows k' when keep_rows is given.  Expected lists
     come from the oracle's bitmaps alone."""
     got = run.eng.k_lists().cpu().numpy()
@@ -206,7 +206,7 @@ def test_every_variant_and_split(variant, split):
 @pytest.mark.parametrize("variant", range(mm.mmm_matmul_variant_count()))
 @pytest.mark.parametrize("bw,p_a,p_b", [(16, 0.9, 0.95), (8, 0.15, 0.5), (32, 0.5, 0.1)])
 def test_long_k_dense_lists(variant, bw, p_a, p_b):
-    """K long enough for several list windows in every variant; dense A (blocks with more entries than one round of the
+    """K long enough for many steps in every variant; dense A (blocks with more entries than one round of the
     workgroup) and dense B (k lists of many batches)."""
     mm.mmm_set_option("matmul_variant", variant)
     mm.mmm_set_option("split_k", 1)
@@ -217,7 +217,7 @@ def test_long_k_dense_lists(variant, bw, p_a, p_b):
 
 @pytest.mark.parametrize("bw", [8, 16, 32])
 def test_column_structured_a(bw, path):
-    """Whole columns of A and the same rows of B switched off: the k lists shrink to the shared set."""
+    """Whole columns of A and the same rows of B switched off: the steps run over the shared set."""
     w = synth.column_sparse(130, 1000, 320, bw, 0.15, 0.7, 0.8, 600 + bw)
     run, (ab, bb, *_rest) = check_workload(w, f"column sparse bw {bw}")
     selected = synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0]
@@ -529,7 +529,7 @@ def test_fused_exact_and_argument_checks():
     assert e.value.status == mm.binding.MMM_ERR_INVALID_ARG
 
 
-# ---- double-precision inputs (pair kernel only) -----------------------------------------------
+# ---- double-precision inputs -------------------------------------------------------------------
 @pytest.mark.parametrize("M,K,N,bw", SHAPES)
 def test_f64_small_shapes(M, K, N, bw):
     w = synth.random_masked(M, K, N, bw, 0.3, 0.4, 700 + M + K, dist="smallint", p_rows=0.8, dtype=synth.DT_F64)
