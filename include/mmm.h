@@ -28,7 +28,7 @@
  *     leftmost; the layout here is this library's own.)
  *   - `hip_stream` is a hipStream_t passed as void* (NULL = the null stream).
  *     Calls enqueue work and return; only mmm_maps_stats waits for the stream, and
- *     the two inspection calls that make what they show wait for the device.
+ *     the inspection calls that make what they show wait for the device.
  *   - Errors are return codes.  Arguments are checked on the host before any
  *     device work is enqueued; on error nothing is launched and no output is
  *     touched.  No call aborts or prints.
@@ -153,8 +153,10 @@ mmm_status mmm_maps_view(const mmm_maps *maps, const uint64_t **a_bits, int64_t 
 
 /* Device pointers to the derived maps, for inspection:
  *   a_colany: ceil(M/32) x ceil(K/64) words; bit k of row t = OR of a_bits[i,k], i in [32t, 32t+32)
- *   bt_bits : NB x ceil(K/64) words; bit k of row jb = b_bits[k,jb]   (the B map transposed)
- * Errors: MMM_ERR_INVALID_ARG. */
+ *   bt_bits : NB x ceil(K/64) words; bit k of row jb = b_bits[k,jb]   (the B map transposed; in
+ *             row-compacted mode it may be this call that makes it: it then waits for the device, before and
+ *             after, and cannot be made during stream capture)
+ * Errors: MMM_ERR_INVALID_ARG, MMM_ERR_DEVICE. */
 mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany, const uint64_t **bt_bits,
                                  int64_t *k_words);
 

@@ -307,6 +307,12 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
     return MMM_ERR_DEVICE;
 }
 
+// The transposed B map over k is read by the pair kernel and by inspection only.  In row-compacted mode it is made with
+// the B side where the pair kernel is what will run; where the matrix kernel is, a caller that wants it all the same
+// makes it in front of its use, on its own stream (again and again, to the same values, so that callers on several
+// streams need not know of each other).
+hipError_t ensure_bt(const mmm_maps *m, hipStream_t s) { return m->b_compact && !m->bt_ready ? mmm_launch_expand_rows(m, s) : hipSuccess; }
+
 }   // namespace
 
 extern "C" {
@@ -379,6 +385,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->ws_bytes = workspace_bytes;
     m->a_built = m->b_built = false;
     m->a_compact = m->b_compact = false;
+    m->bt_ready = true;
     m->a_dtype = m->b_dtype = -1;
     m->a_src = nullptr;
     m->a_src_ld = 0;
@@ -444,6 +451,14 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         // an image of A made for another numbering of k (or for none) do not fit the new B side
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
         maps->b_compact = a.b_compact;
+        maps->bt_ready = !a.b_compact;
+        if (a.b_compact && (maps->M <= 64 || choose_path(maps, dt) == MMM_PATH_PAIRS)) {
+            if (hipError_t e = mmm_launch_expand_rows(maps, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
+                note_device_error("transposed map launch", e);
+                return MMM_ERR_DEVICE;
+            }
+            maps->bt_ready = true;
+        }
     }
     if (X != nullptr) {
         maps->a_compact = a.a_compact;
@@ -479,6 +494,8 @@ mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany
     if (a_colany) *a_colany = maps->a_colany;
     if (bt_bits) *bt_bits = maps->bt_bits;
     if (k_words) *k_words = maps->WA;
+    if (bt_bits != nullptr && maps->b_built && maps->b_compact && !maps->bt_ready)
+        return make_for_inspection("transposed map", maps, mmm_launch_expand_rows);
     return MMM_OK;
 }
 
@@ -589,9 +606,11 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
     const bool packed_y = maps->b_src == Y && maps->b_src_ld == ldy, pairs_can = mmm_pairs_supports(dt, ldy);
     if (!packed_y && !pairs_can) return MMM_ERR_MAPS_MISMATCH;
     if (pairs_can && (!packed_y || choose_path(maps, dt) == MMM_PATH_PAIRS)) {   // no scratch at all on this path
-        if (hipError_t e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, false, 0, 0.f, nullptr,
-                                            static_cast<hipStream_t>(hip_stream));
-            e != hipSuccess) {
+        hipError_t e = ensure_bt(maps, static_cast<hipStream_t>(hip_stream));
+        if (e == hipSuccess)
+            e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, false, 0, 0.f, nullptr,
+                                 static_cast<hipStream_t>(hip_stream));
+        if (e != hipSuccess) {
             note_device_error("masked GEMM (pairs) launch", e);
             return MMM_ERR_DEVICE;
         }
@@ -646,9 +665,11 @@ mmm_status mmm_matmul_fused(const mmm_maps *maps, mmm_dtype dt, const void *X, i
         return MMM_ERR_DTYPE;
     if (!mmm_pairs_supports(dt, ldy)) return MMM_ERR_SHAPE;
     if (!maps->b_built || maps->b_dtype != dt) return MMM_ERR_MAPS_MISMATCH;
-    if (hipError_t e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, true, ma->pred, ma->threshold, ma->keep_bits,
-                                        static_cast<hipStream_t>(hip_stream));
-        e != hipSuccess) {
+    hipError_t e = ensure_bt(maps, static_cast<hipStream_t>(hip_stream));
+    if (e == hipSuccess)
+        e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, true, ma->pred, ma->threshold, ma->keep_bits,
+                             static_cast<hipStream_t>(hip_stream));
+    if (e != hipSuccess) {
         note_device_error("fused masked GEMM launch", e);
         return MMM_ERR_DEVICE;
     }

@@ -13,8 +13,8 @@
 // every group of 16 columns and segment of 128 k the occupied pieces of rows one after another, with
 // the list of their k.  A wave of the matrix kernel owns one group and reads both linearly.
 //
-// One launch covers both matrices.  Nothing needs clearing beforehand: every output word in device memory has exactly one
-// producer, but for the words that two segments of live rows share (see spread_rows).
+// One launch covers both matrices.  Every output word in device memory has exactly one producer, so no
+// global atomics are used and nothing needs clearing beforehand.
 #include "mmm_internal.h"
 #include <cstring>
 #include <type_traits>
@@ -380,16 +380,15 @@ struct BShared {
     uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
     uint16_t list[16][SEG];
     char pack[16 * (SEG * MMM_GROUP_COLS * 2 + 16)];   // 16-bit types: the packed groups
-    int32_t kk[1 + SEG];              // row-compacted mode: the last live row before the segment and the rows behind its k' (-1: none)
-    uint32_t live;                    // and how many live rows there are
+    int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
 };
 
-// Rows k' = seg*128 - 1 .. of the numbering given by `rows`, into sh.kk; returns K'.
+// Rows k' = seg*128 .. of the numbering given by `rows`, into sh.kk; returns K'.
 __device__ __forceinline__ uint32_t number_rows(ConstParams &p, int64_t seg, int lane, int wave, BShared &sh)
 {
     const int tid = threadIdx.x;
-    if (tid <= SEG) sh.kk[tid] = -1;
+    if (tid < SEG) sh.kk[tid] = -1;
     const int64_t per = (p.WA + BUILD_THREADS - 1) / BUILD_THREADS;   // every thread counts a run of words
     const int64_t w0 = tid * per, w1 = min(p.WA, w0 + per);
     uint32_t cnt = 0;
@@ -409,63 +408,14 @@ __device__ __forceinline__ uint32_t number_rows(ConstParams &p, int64_t seg, int
         if (w < wave) pos += s;
         total += s;
     }
-    if (tid == 0) sh.live = total;
     const uint32_t lo = (uint32_t)seg * SEG;
-    if (pos < lo + SEG && pos + cnt + 1 > lo) {
+    if (pos < lo + SEG && pos + cnt > lo) {
         for (int64_t w = w0; w < w1; ++w)
             for (uint64_t m = row_word(p.rows, w, p.K); m != 0; m &= m - 1, ++pos)
-                if (pos + 1 - lo <= SEG) sh.kk[pos + 1 - lo] = (int32_t)(w * 64 + __builtin_ctzll(m));
+                if (pos >= lo && pos < lo + SEG) sh.kk[pos - lo] = (int32_t)(w * 64 + __builtin_ctzll(m));
     }
     __syncthreads();
     return total;
-}
-
-// Row-compacted mode: the transposed map over k, from the segment's bits over k'.  A segment sees to the k from behind the
-// last live row before it up to its own last live row, the last segment to all that follow.  A word of 64 k that two
-// segments share is written by both, each touching its own bits only, by an atomic AND and an atomic OR: nothing has to be
-// cleared beforehand and the order does not matter.  A wave takes a word, a lane a block.  (Made here for whichever call
-// reads it next: as a launch of its own, in front of every call that found it missing, it took 5 us each time.  Here it adds
-// a chain of LDS reads and stores to the B side, 16384 x 4096 with a tenth of the rows on: floats 10.8 -> 11.3 us, 16-bit
-// 12.2 -> 12.9; with both sides 34.3 -> 34.8 and 31.4 -> 32.7.)
-template <typename T, int BW>
-__device__ __forceinline__ void spread_rows(ConstParams &p0, int64_t seg, int64_t ct, int lane, int wave, BShared &sh)
-{
-    ConstParams &p = reread(p0);
-    asm volatile("" : "+v"(lane));   // (what depends on the lane is worked out here, not kept from before)
-    const int64_t live = (int64_t)__builtin_amdgcn_readfirstlane(sh.live);
-    constexpr int LPB = BW / Tile<T>::LANE_COLS, BPW = Tile<T>::B_COLS / BW;
-    const int64_t blk = ct * BPW + lane;
-    const bool mine = lane < BPW && blk < p.NB;
-    const bool last = (seg + 1) * SEG >= live;
-    const int64_t k_lo = (int64_t)__builtin_amdgcn_readfirstlane(sh.kk[0]) + 1;
-    const int64_t k_hi = last ? p.WA * 64 : (int64_t)__builtin_amdgcn_readfirstlane(sh.kk[SEG]) + 1;
-    const uint64_t *t = reinterpret_cast<const uint64_t *>(BW < MMM_GROUP_COLS ? sh.bbits[lane * LPB & 63] : sh.gbits[lane * LPB & 63]);
-    const uint64_t t0 = live > 0 ? t[0] : 0ull, t1 = live > 0 ? t[1] : 0ull;
-    const uint32_t ka = (uint32_t)sh.kk[1 + lane], kb = (uint32_t)sh.kk[65 + lane];   // (no row: past every other)
-    for (int64_t w = (k_lo >> 6) + wave; w * 64 < k_hi; w += BUILD_WAVES) {
-        uint64_t own = ~0ull;
-        if (w * 64 < k_lo) own <<= k_lo - w * 64;
-        if (w * 64 + 64 > k_hi) own &= (1ull << (k_hi - w * 64)) - 1ull;
-        const uint32_t from = (uint32_t)(w * 64);
-        const int first = __popcll(ballot64(ka < from)) + __popcll(ballot64(kb < from));   // the word's live rows in the segment
-        const int end = __popcll(ballot64(ka < from + 64)) + __popcll(ballot64(kb < from + 64));
-        uint64_t bits = first >= 64 ? t1 >> (first & 63) : first == 0 ? t0 : t0 >> first | t1 << (64 - first);
-        uint64_t out = 0;
-        for (int j = first; j < end; ++j) {   // wave-uniform
-            const int k = __builtin_amdgcn_readlane((int)(j < 64 ? ka : kb), j & 63);
-            out |= (bits & 1ull) << (k & 63);
-            bits >>= 1;
-        }
-        if (mine) {
-            uint64_t *dst = p.bt_bits + blk * p.WA + w;
-            if (own == ~0ull) {
-                *dst = out;
-            } else {
-                __hip_atomic_fetch_and(dst, ~own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_or(dst, out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
 }
 
 // bits of x at multiples of LPB, moved together
@@ -495,10 +445,10 @@ template <int LPB> __device__ __forceinline__ uint32_t squeeze(uint64_t x)
 // lanes of a block for all rows at once), addresses come from one buffer resource per wave, and lanes with nothing to
 // store are given an offset past its end instead of being branched around.
 // ROWS (row-compacted mode): the rows are the live rows k' = 128 seg .., and the transposed map is over k'.
-// A segment without a live row is left alone.  carry: doubles in 32-wide blocks fill half a
+// Returns false where ROWS finds no live row in the segment.  carry: doubles in 32-wide blocks fill half a
 // byte of a map row per column tile, so the map bits of an even tile are handed to the odd one after it.
 template <typename T, int BW, bool ROWS>
-__device__ __forceinline__ void scan_b(ConstParams &p0, int64_t seg, int64_t ct, int lane, int wave, BShared &sh, uint32_t &carry)
+__device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct, int lane, int wave, BShared &sh, uint32_t &carry)
 {
     ConstParams &p = reread(p0);
     constexpr int ESZ = (int)sizeof(T);
@@ -513,23 +463,20 @@ __device__ __forceinline__ void scan_b(ConstParams &p0, int64_t seg, int64_t ct,
     if (ROWS) {
         const uint32_t live = number_rows(p, seg, lane, wave, sh);
         if (ct == 0) {   // publish the numbering
-            if (threadIdx.x < SEG && sh.kk[1 + threadIdx.x] >= 0) p.kmap[seg * SEG + threadIdx.x] = (uint32_t)sh.kk[1 + threadIdx.x];
+            if (threadIdx.x < SEG && sh.kk[threadIdx.x] >= 0) p.kmap[seg * SEG + threadIdx.x] = (uint32_t)sh.kk[threadIdx.x];
             if (seg == 0) {
                 if (threadIdx.x == 0) p.kinfo[0] = live;
                 for (int64_t w = threadIdx.x; w < p.WA; w += BUILD_THREADS) p.rows_copy[w] = row_word(p.rows, w, p.K);
             }
         }
-        if (seg * SEG >= (int64_t)live) {   // the whole workgroup
-            if (seg == 0) spread_rows<T, BW>(p0, seg, ct, lane, wave, sh);   // no live row at all: zeros
-            return;
-        }
+        if (seg * SEG >= (int64_t)live) return false;   // the whole workgroup
     }
     // lane j < 8: row j of the wave and which of its blocks are switched on
     int64_t krow = -1;
     uint32_t piece = 0;
     {
         const int j = lane & (B_ROWS - 1);
-        const int64_t k = ROWS ? (int64_t)sh.kk[1 + wave * B_ROWS + j] : seg * SEG + wave * B_ROWS + j;
+        const int64_t k = ROWS ? (int64_t)sh.kk[wave * B_ROWS + j] : seg * SEG + wave * B_ROWS + j;
         krow = k >= 0 && k < p.K ? k : -1;
         const int64_t kc = max(krow, (int64_t)0);
         uint64_t w = ~0ull;
@@ -629,7 +576,7 @@ __device__ __forceinline__ void scan_b(ConstParams &p0, int64_t seg, int64_t ct,
             if (seg * 2 + 1 < p.WA) dst[1] = t[1];
         }
     }
-    if (ESZ == 8 && !p.pack) return;
+    if (ESZ == 8 && !p.pack) return true;
     const uint64_t *gt = reinterpret_cast<const uint64_t *>(sh.gbits[lane]);
     const uint64_t glo = gt[0], ghi = gt[1];
     const uint32_t n = (uint32_t)__popcll(glo) + (uint32_t)__popcll(ghi);   // rows of this lane's group
@@ -700,7 +647,8 @@ __device__ __forceinline__ void scan_b(ConstParams &p0, int64_t seg, int64_t ct,
         if ((int)(threadIdx.x >> 6) < B_GROUPS && LG < p.NG)
             reinterpret_cast<uint32_t *>(p.bp_list + (LG * p.KBA + seg) * SEG)[lane] = reinterpret_cast<const uint32_t *>(sh.list)[threadIdx.x];
     }
-    if (ROWS) spread_rows<T, BW>(p0, seg, ct, lane, wave, sh);
+    if (ROWS) __syncthreads();   // the shared arrays may be reused
+    return true;
 }
 
 // ROWS: row-compacted mode (A laid out over the live rows of B; B built over them).
@@ -726,13 +674,10 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
                 for (uint32_t q = threadIdx.x; q < words; q += BUILD_THREADS)
                     if (!((live >> (q / (uint32_t)p.WB)) & 1ull)) p.b_bits[w * 64 * p.WB + q] = 0;
             }
-            for (uint32_t bb = i;;) {
+            for (uint32_t bb = i; bb < p.n_b; bb += p.n_b_wg) {   // ends at the first segment without a live row
                 int l = lane;
                 asm volatile("" : "+v"(l));   // keeps what depends on the lane from being carried around the loop (it would spill)
-                scan_b<T, BW, true>(p, bb / p.ctiles, bb % p.ctiles, l, wave, sh.b, carry);
-                bb += p.n_b_wg;   // (found out here: numbering the rows of a segment that has none would cost as much as of one that has)
-                if (bb >= p.n_b || (bb >= p.ctiles && bb / p.ctiles * SEG >= __builtin_amdgcn_readfirstlane(sh.b.live))) break;
-                __syncthreads();   // the shared arrays may be reused
+                if (!scan_b<T, BW, true>(p, bb / p.ctiles, bb % p.ctiles, l, wave, sh.b, carry)) break;
             }
         } else if (sizeof(T) < 8) {
             scan_b<T, BW, false>(p, i / p.ctiles, i % p.ctiles, lane, wave, sh.b, carry);
@@ -750,6 +695,33 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
     } else {
         const int64_t bi0 = (int64_t)(i / (uint32_t)p.a_units) * p.a_per_wg;
         scan_a<T, TEST, ROWS, DEEP>(p, i % (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+    }
+}
+
+// Row-compacted mode: bt_bits (over k) by spreading the bits of btc_bits to the places rows_copy names.  One wave per
+// word of 64 k.
+__global__ __launch_bounds__(256) void mmm_expand_rows_kernel(const uint64_t *rows, const uint64_t *btc_bits, uint64_t *bt_bits,
+                                                              int64_t K, int64_t NB, int64_t WA)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t w = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= WA) return;
+    uint32_t before = 0;
+    for (int64_t q = lane; q < w; q += 64) before += (uint32_t)__popcll(rows[q]);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) before += (uint32_t)__shfl_xor((int)before, d, 64);
+    const uint64_t live = readlane64(rows[w], 0);
+    const int64_t at = (int64_t)(before >> 6);
+    const int sh = (int)(before & 63u);
+    for (int64_t blk = lane; blk < NB; blk += 64) {
+        uint64_t bits = btc_bits[blk * WA + min(at, WA - 1)] >> sh;
+        if (sh != 0) bits |= btc_bits[blk * WA + min(at + 1, WA - 1)] << (64 - sh);
+        uint64_t out = 0;
+        for (uint64_t m = live; m != 0; m &= m - 1) {   // wave-uniform
+            out |= (bits & 1ull) << __builtin_ctzll(m);
+            bits >>= 1;
+        }
+        bt_bits[blk * WA + w] = out;
     }
 }
 
@@ -998,6 +970,14 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
     (void)hipGetLastError();   // drop any stale error another library left on this thread
     hipLaunchKernelGGL(build_kernel(a.dtype, p.test.mode, m->bw, p.rows != nullptr, per_wg >= 4), grid, block, 0, s, p);
+    return hipGetLastError();
+}
+
+hipError_t mmm_launch_expand_rows(const mmm_maps *m, hipStream_t s)
+{
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(mmm_expand_rows_kernel, dim3((uint32_t)((m->WA + 3) / 4)), dim3(256), 0, s, m->rows_copy, m->btc_bits, m->bt_bits,
+                       m->K, m->NB, m->WA);
     return hipGetLastError();
 }
 

@@ -138,6 +138,7 @@ struct mmm_maps {
     // state
     bool a_built, b_built;
     bool b_compact;   // the B side was built in row-compacted mode
+    bool bt_ready;    // bt_bits were made with the B side (otherwise: before each use, see ensure_bt)
     bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)
@@ -201,6 +202,8 @@ inline bool mmm_packs(int64_t M, int32_t dtype) { return dtype != MMM_F64 || M >
 hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s);
 // forms that only inspection reads: column-any words over k'; counts and lists of the blocks of A
 hipError_t mmm_launch_colany_compact(const mmm_maps *m, hipStream_t s);
+// row-compacted mode: bt_bits (over k) from btc_bits (over k')
+hipError_t mmm_launch_expand_rows(const mmm_maps *m, hipStream_t s);
 hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s);
 int32_t mmm_variant_count();
 const mmm_variant_info &mmm_variant(int32_t i);

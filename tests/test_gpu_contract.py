@@ -56,28 +56,6 @@ def test_another_y_that_no_kernel_can_read():
     np.testing.assert_array_equal(run.C.cpu().numpy(), oracle.run_workload(w)[2])
 
 
-# ---- row-compacted mode: the build leaves every map complete -----------------------------------
-@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16], ids=["f32", "bf16"])
-@pytest.mark.parametrize("K,N,bw,p_rows", [
-    (1, 8, 8, 1.0), (63, 272, 16, 0.5), (130, 544, 32, 1.0), (700, 264, 8, 0.0),   # one, partial, two segments; no live row
-    (1500, 528, 16, 0.3), (9000, 320, 32, 0.1), (9001, 80, 8, 0.005), (2500, 96, 16, 0.97),
-    (200, 66560, 16, 0.0), (200, 66560, 16, 0.3),    # more column tiles in a segment than workgroups that loop over B
-])
-def test_build_leaves_the_transposed_map(K, N, bw, p_rows, dtype):
-    """bt_bits, for whichever call and stream reads them next, whichever kernel is chosen: looked at through the address
-    alone, with no call behind the build that could still make them.  Segments of 128 live rows share words of 64 k."""
-    w = synth.random_masked(70, K, N, bw, 0.2, 0.4, K + N, dist="smallint", dtype=dtype, p_rows=p_rows)
-    run = HipRun(w)
-    run.eng.set_path(mm.MMM_PATH_MATRIX)
-    bt = run.eng.bt_bits()             # nothing built: the address alone
-    bt.fill_(-1)
-    bb = oracle.b_bits(w.Y, bw, w.keep_rows, w.keep_blocks)
-    for _ in range(2):                 # over junk, and over what the first build left
-        run.build()
-        torch.cuda.synchronize()
-        np.testing.assert_array_equal(bt.cpu().numpy().view(np.uint64), synth.pack_bits(synth.unpack_bits(bb, w.NB).T))
-
-
 # ---- inspection ------------------------------------------------------------------------------
 def test_inspection_needs_no_stream_of_the_build():
     """A program builds on a stream of its own, waits for it, gives that stream other work and looks at the lists from
