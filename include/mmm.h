@@ -116,7 +116,7 @@ mmm_status mmm_maps_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t blo
 mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M, int64_t K, int64_t N,
                          int32_t block_width, mmm_maps **out);
 
-/* Frees the host handle only (NULL is allowed). */
+/* Frees the host handle (NULL is allowed) and no device memory. */
 void mmm_maps_release(mmm_maps *maps);
 
 /* Evaluate the masks on the device and write the sparsity maps into the
@@ -154,8 +154,8 @@ mmm_status mmm_maps_view(const mmm_maps *maps, const uint64_t **a_bits, int64_t 
 /* Device pointers to the derived maps, for inspection:
  *   a_colany: ceil(M/32) x ceil(K/64) words; bit k of row t = OR of a_bits[i,k], i in [32t, 32t+32)
  *   bt_bits : NB x ceil(K/64) words; bit k of row jb = b_bits[k,jb]   (the B map transposed; in
- *             row-compacted mode it may be this call that makes it: it then waits for the device, before and
- *             after, and cannot be made during stream capture)
+ *             row-compacted mode it is made by the first call after a build that needs it, which may be this one:
+ *             it then waits for the device, before and after, and cannot be made during stream capture)
  * Errors: MMM_ERR_INVALID_ARG, MMM_ERR_DEVICE. */
 mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany, const uint64_t **bt_bits,
                                  int64_t *k_words);

@@ -308,10 +308,38 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
 }
 
 // The transposed B map over k is read by the pair kernel and by inspection only.  In row-compacted mode it is made with
-// the B side where the pair kernel is what will run; where the matrix kernel is, a caller that wants it all the same
-// makes it in front of its use, on its own stream (again and again, to the same values, so that callers on several
-// streams need not know of each other).
-hipError_t ensure_bt(const mmm_maps *m, hipStream_t s) { return m->b_compact && !m->bt_ready ? mmm_launch_expand_rows(m, s) : hipSuccess; }
+// the B side where the pair kernel is what will run (always for at most 64 rows); where the matrix kernel is, by the first
+// call that wants it all the same, once per build, on that call's stream (5 us; with every build it would cost the matrix
+// path 1 to 2).  Calls on other streams wait for it, by an event, until it is seen to have run.  A call that is being
+// captured makes its own: it runs when the graph does, and after builds that come in between.
+hipError_t ensure_bt(const mmm_maps *m, hipStream_t s)
+{
+    if (!m->b_compact || m->M <= 64) return hipSuccess;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return mmm_launch_expand_rows(m, s);
+    if (m->bt_state.load(std::memory_order_acquire) == BT_MADE) return hipSuccess;
+    std::lock_guard<std::mutex> lock(m->bt_mutex);
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // (another thread may be capturing: that is not disturbed by these calls)
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    hipError_t result = hipSuccess;
+    bool launch = true;
+    if (m->bt_state == BT_LAUNCHED) {
+        const hipError_t e = hipEventQuery(m->bt_event);
+        if (e == hipSuccess) m->bt_state.store(BT_MADE, std::memory_order_release);
+        launch = e != hipSuccess && !(e == hipErrorNotReady && hipStreamWaitEvent(s, m->bt_event, 0) == hipSuccess);
+    } else if (m->bt_state == BT_MADE) {
+        launch = false;
+    }
+    if (launch) {   // (where the event fails, each call makes it anew, to the same values)
+        result = mmm_launch_expand_rows(m, s);
+        if (result == hipSuccess && (m->bt_event != nullptr || hipEventCreateWithFlags(&m->bt_event, hipEventDisableTiming) == hipSuccess) &&
+            hipEventRecord(m->bt_event, s) == hipSuccess)
+            m->bt_state = BT_LAUNCHED;
+    }
+    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipGetLastError();   // "not ready" is no error of the caller's
+    return result;
+}
 
 }   // namespace
 
@@ -385,7 +413,8 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->ws_bytes = workspace_bytes;
     m->a_built = m->b_built = false;
     m->a_compact = m->b_compact = false;
-    m->bt_ready = true;
+    m->bt_state = BT_MADE;
+    m->bt_event = nullptr;
     m->a_dtype = m->b_dtype = -1;
     m->a_src = nullptr;
     m->a_src_ld = 0;
@@ -402,7 +431,11 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     return MMM_OK;
 }
 
-void mmm_maps_release(mmm_maps *maps) { delete maps; }
+void mmm_maps_release(mmm_maps *maps)
+{
+    if (maps != nullptr && maps->bt_event != nullptr) (void)hipEventDestroy(maps->bt_event);
+    delete maps;
+}
 
 mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t ldx, const mmm_mask_a *ma,
                           const void *Y, int64_t ldy, const mmm_mask_b *mb, void *hip_stream)
@@ -451,13 +484,13 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         // an image of A made for another numbering of k (or for none) do not fit the new B side
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
         maps->b_compact = a.b_compact;
-        maps->bt_ready = !a.b_compact;
+        maps->bt_state = a.b_compact ? BT_MISSING : BT_MADE;
         if (a.b_compact && (maps->M <= 64 || choose_path(maps, dt) == MMM_PATH_PAIRS)) {
             if (hipError_t e = mmm_launch_expand_rows(maps, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
                 note_device_error("transposed map launch", e);
                 return MMM_ERR_DEVICE;
             }
-            maps->bt_ready = true;
+            maps->bt_state = BT_MADE;
         }
     }
     if (X != nullptr) {
@@ -494,8 +527,11 @@ mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany
     if (a_colany) *a_colany = maps->a_colany;
     if (bt_bits) *bt_bits = maps->bt_bits;
     if (k_words) *k_words = maps->WA;
-    if (bt_bits != nullptr && maps->b_built && maps->b_compact && !maps->bt_ready)
-        return make_for_inspection("transposed map", maps, mmm_launch_expand_rows);
+    if (bt_bits != nullptr && maps->b_built && maps->bt_state != BT_MADE) {
+        if (mmm_status st = make_for_inspection("transposed map", maps, mmm_launch_expand_rows); st != MMM_OK) return st;
+        std::lock_guard<std::mutex> lock(maps->bt_mutex);
+        maps->bt_state = BT_MADE;
+    }
     return MMM_OK;
 }
 

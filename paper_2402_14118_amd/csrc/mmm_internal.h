@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 
 #include "mmm.h"
@@ -100,6 +101,8 @@ struct mmm_plan_key {
     }
 };
 
+enum { BT_MADE = 0, BT_MISSING = 1, BT_LAUNCHED = 2 };
+
 struct mmm_maps {
     int64_t M, K, N;
     int32_t bw;
@@ -138,7 +141,11 @@ struct mmm_maps {
     // state
     bool a_built, b_built;
     bool b_compact;   // the B side was built in row-compacted mode
-    bool bt_ready;    // bt_bits were made with the B side (otherwise: before each use, see ensure_bt)
+    // bt_bits in row-compacted mode: made with the B side, launched by a call that needed them (bt_event is behind that), or
+    // neither yet (see ensure_bt)
+    mutable std::atomic<int> bt_state;
+    mutable std::mutex bt_mutex;
+    mutable hipEvent_t bt_event;
     bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)

@@ -161,3 +161,88 @@ def test_16_bit_inputs_with_few_elements_of_a_take_the_matrix_kernel(M, K, N, p_
     run.build()
     run.eng.stats()
     assert run.eng.path() == mm.MMM_PATH_MATRIX
+
+
+# ---- row-compacted mode: the transposed map over k, for calls that want it where the matrix kernel was expected --------
+def _compacted(seed, dtype=synth.DT_F32, p_rows=0.3):
+    w = synth.random_masked(100, 1500, 288, 16, 0.3, 0.4, seed, dist="smallint", dtype=dtype, p_rows=p_rows)
+    run = HipRun(w)
+    run.eng.set_path(mm.MMM_PATH_MATRIX)
+    return w, run, oracle.run_workload(w)[2]
+
+
+def _fused(w, run, C, stream=None):
+    run.eng.matmul_fused(run.X, run.Y, C, w.pred, w.threshold, run.keep_a, stream=stream)
+
+
+def test_the_transposed_map_is_made_once_per_build():
+    """Seen by what a call does with a map that was cleared behind its back: a call that made it again would be right."""
+    w, run, C_ref = _compacted(11)
+    bt = run.eng.bt_bits()             # nothing built: the address alone
+    for _ in range(2):
+        bt.fill_(-1)
+        run.build()
+        for _ in range(2):
+            _fused(w, run, run.C)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+        run.eng.set_path(mm.MMM_PATH_PAIRS)
+        run.matmul()
+        run.eng.set_path(mm.MMM_PATH_MATRIX)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+        bt.zero_()
+        _fused(w, run, run.C)
+        torch.cuda.synchronize()
+        assert not run.C.any()
+
+
+def test_the_transposed_map_from_several_streams():
+    """The stream whose call makes the map is held up; calls on other streams, in front of that, wait for the map."""
+    w, run, C_ref = _compacted(12)
+    run.eng.bt_bits().fill_(-1)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    outs = [torch.full_like(run.C, float("nan")) for _ in streams]
+    for _ in range(3):
+        run.build()
+        for s in streams:
+            s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(streams[0]):
+            torch.cuda._sleep(20_000_000)          # some 10 ms
+        for s, C in zip(streams, outs):
+            _fused(w, run, C, stream=s)
+        torch.cuda.synchronize()
+        for C in outs:
+            np.testing.assert_array_equal(C.cpu().numpy(), C_ref)
+            C.fill_(float("nan"))
+        torch.cuda.synchronize()
+
+
+def test_the_transposed_map_in_a_graph():
+    """A captured call is right at every replay, also after builds of other rows between the replays."""
+    w, run, C_ref = _compacted(13)
+    w2, _, C2_ref = _compacted(14, p_rows=0.6)
+    w2.X, w2.keep_a = w.X, w.keep_a
+    C2_ref = oracle.run_workload(w2)[2]
+    run.build()
+    _fused(w, run, run.C)              # made and seen to be made before the capture
+    torch.cuda.synchronize()
+    _fused(w, run, run.C)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        _fused(w, run, run.C)
+    for source, want in ((w, C_ref), (w2, C2_ref), (w, C_ref), (w2, C2_ref)):
+        run.Y.copy_(torch.from_numpy(source.Y))
+        run.keep_rows.copy_(torch.from_numpy(source.keep_rows.view(np.int64)))
+        run.keep_blocks.copy_(torch.from_numpy(source.keep_blocks.view(np.int64)))
+        run.build()
+        for _ in range(2):
+            run.Cbuf.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(run.C.cpu().numpy(), want)
+        run.Cbuf.fill_(float("nan"))
+        _fused(w, run, run.C)          # and beside it, not captured
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), want)
