@@ -55,14 +55,15 @@ struct MatmulParams {
     const uint16_t *bp_list;
     const uint32_t *bp_cnt;
     const uint32_t *kinfo;   // row-compacted mode: [0] = number of live k (everything above is then over k'); else null
-    // for the lists without the columns that are zero in the tile (4-byte types, see `filtered`)
+    int64_t M, N, KBA, NG;
+    int32_t tiles_m, tiles_n, panel, split_k, chunks_total, chunks_per_split;
+    int32_t accumulate;
+    // for the lists without the columns that are zero in the tile (see `filtered`; behind what every kernel reads)
+    int32_t bw;
     const uint64_t *bt_bits;    // transposed B map, over k' in row-compacted mode
     const uint64_t *a_colany;   // column-any words of A, over k
     const uint32_t *kmap;       // row-compacted mode: k' -> k
-    int32_t bw;
-    int64_t M, N, KBA, NG, NB, WA, MT;
-    int32_t tiles_m, tiles_n, panel, split_k, chunks_total, chunks_per_split;
-    int32_t accumulate;
+    int64_t NB, WA, MT;
 };
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
