@@ -52,7 +52,8 @@ def parse_workload(name):
         return synth.random_masked(4096, 4096, 4096, 16, p, p, 3000 + 11 * ip, "uniform", -1.0, 1.0,
                                    name=f"cfg3_4096_p{int(p*100):02d}_bw16_f64", dtype=synth.DT_F64)
     if name == "colsparse_bf16":
-        return synth.column_sparse(2048, 16384, 4096, 32, 0.1, 1.0, 1.0, 2001, dtype=synth.DT_BF16)
+        return synth.column_sparse(2048, 16384, 4096, 32, 0.1, 1.0, 1.0, 2001, name="colsparse_2048x16384x4096_c10_bw32_bf16",
+                                   dtype=synth.DT_BF16)
     return synth.config(int(name[3:]))
 
 
