@@ -8,8 +8,9 @@
 // of their k.  The wave walks that list: it reads the packed rows linearly, picks the matching columns of
 // A out of an LDS copy of the 64 x 128 block of A, and feeds both to matrix instructions.  B's block
 // sparsity is skipped exactly: no unoccupied block is ever loaded or multiplied; the zeros of A inside the
-// 64 rows of a tile are multiplied (A's element sparsity is what the pair kernel exploits).  The iteration
-// is uniform across the wave.
+// 64 rows of a tile are multiplied (A's element sparsity is what the pair kernel exploits), but for floats
+// whose columns are zero in the whole tile often enough (see `filtered`).  The iteration is uniform across
+// the wave.
 //
 // A workgroup owns 64 rows of C and keeps a ring of two or four blocks of A in LDS (see mmm_ring), filled by asynchronous
 // global-to-LDS loads of the builder's image, whose byte order is the one the operand reads want: no
