@@ -294,11 +294,21 @@ int32_t choose_path(const mmm_maps *m, int32_t dt)
     return pairs_cost(m, dt) < matrix ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
 }
 
+struct RelaxedCapture {   // calls that another thread's stream capture would forbid, and that do not disturb it
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture()
+    {
+        if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
 // What only inspection reads is made when it is asked for.  These calls take no stream: the build may have run on one that is
 // busy with something else by now or does not exist any more, and the caller may read on any.  So nothing is assumed about
 // streams: the device's work is waited for, and then what was made.
 mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_t (*launch)(const mmm_maps *, hipStream_t))
 {
+    RelaxedCapture relaxed;
     hipError_t e = hipDeviceSynchronize();
     if (e == hipSuccess) e = launch(maps, nullptr);
     if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
@@ -307,20 +317,25 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
     return MMM_ERR_DEVICE;
 }
 
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
 // The transposed B map over k is read by the pair kernel and by inspection only.  In row-compacted mode it is made with
 // the B side where the pair kernel is what will run (always for at most 64 rows); where the matrix kernel is, by the first
 // call that wants it all the same, once per build, on that call's stream (5 us; with every build it would cost the matrix
 // path 1 to 2).  Calls on other streams wait for it, by an event, until it is seen to have run.  A call that is being
-// captured makes its own: it runs when the graph does, and after builds that come in between.
+// captured makes its own: it runs when the graph does, and after builds that come in between.  And once a build has been
+// captured every call makes its own: what is done when that graph runs again is not seen here.
 hipError_t ensure_bt(const mmm_maps *m, hipStream_t s)
 {
     if (!m->b_compact || m->M <= 64) return hipSuccess;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) return mmm_launch_expand_rows(m, s);
+    if (m->build_captured || capturing(s)) return mmm_launch_expand_rows(m, s);
     if (m->bt_state.load(std::memory_order_acquire) == BT_MADE) return hipSuccess;
     std::lock_guard<std::mutex> lock(m->bt_mutex);
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;   // (another thread may be capturing: that is not disturbed by these calls)
-    const bool exchanged = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    RelaxedCapture relaxed;
     hipError_t result = hipSuccess;
     bool launch = true;
     if (m->bt_state == BT_LAUNCHED) {
@@ -336,7 +351,6 @@ hipError_t ensure_bt(const mmm_maps *m, hipStream_t s)
             hipEventRecord(m->bt_event, s) == hipSuccess)
             m->bt_state = BT_LAUNCHED;
     }
-    if (exchanged) (void)hipThreadExchangeStreamCaptureMode(&mode);
     (void)hipGetLastError();   // "not ready" is no error of the caller's
     return result;
 }
@@ -415,6 +429,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->a_compact = m->b_compact = false;
     m->bt_state = BT_MADE;
     m->bt_event = nullptr;
+    m->build_captured = false;
     m->a_dtype = m->b_dtype = -1;
     m->a_src = nullptr;
     m->a_src_ld = 0;
@@ -485,6 +500,7 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
         maps->b_compact = a.b_compact;
         maps->bt_state = a.b_compact ? BT_MISSING : BT_MADE;
+        if (a.b_compact && !maps->build_captured) maps->build_captured = capturing(static_cast<hipStream_t>(hip_stream));
         if (a.b_compact && (maps->M <= 64 || choose_path(maps, dt) == MMM_PATH_PAIRS)) {
             if (hipError_t e = mmm_launch_expand_rows(maps, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
                 note_device_error("transposed map launch", e);
@@ -527,7 +543,7 @@ mmm_status mmm_maps_view_derived(const mmm_maps *maps, const uint64_t **a_colany
     if (a_colany) *a_colany = maps->a_colany;
     if (bt_bits) *bt_bits = maps->bt_bits;
     if (k_words) *k_words = maps->WA;
-    if (bt_bits != nullptr && maps->b_built && maps->bt_state != BT_MADE) {
+    if (bt_bits != nullptr && maps->b_built && maps->b_compact && (maps->bt_state != BT_MADE || maps->build_captured)) {
         if (mmm_status st = make_for_inspection("transposed map", maps, mmm_launch_expand_rows); st != MMM_OK) return st;
         std::lock_guard<std::mutex> lock(maps->bt_mutex);
         maps->bt_state = BT_MADE;

@@ -146,6 +146,7 @@ struct mmm_maps {
     mutable std::atomic<int> bt_state;
     mutable std::mutex bt_mutex;
     mutable hipEvent_t bt_event;
+    bool build_captured;   // a build of B in row-compacted mode has been captured into a graph
     bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)

@@ -246,3 +246,31 @@ def test_the_transposed_map_in_a_graph():
         _fused(w, run, run.C)          # and beside it, not captured
         torch.cuda.synchronize()
         np.testing.assert_array_equal(run.C.cpu().numpy(), want)
+
+
+def test_the_transposed_map_after_replayed_builds():
+    """Builds of other rows that come from a graph, which the handle does not see, and calls that are not captured."""
+    w, run, C_ref = _compacted(15)
+    w2, _, _ = _compacted(16, p_rows=0.6)
+    w2.X, w2.keep_a = w.X, w.keep_a
+    C2_ref = oracle.run_workload(w2)[2]
+    bt = run.eng.bt_bits()
+    run.build()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run.build()
+    for source, want in ((w, C_ref), (w2, C2_ref), (w, C_ref), (w2, C2_ref)):
+        run.Y.copy_(torch.from_numpy(source.Y))
+        run.keep_rows.copy_(torch.from_numpy(source.keep_rows.view(np.int64)))
+        run.keep_blocks.copy_(torch.from_numpy(source.keep_blocks.view(np.int64)))
+        bb = oracle.b_bits(source.Y, w.bw, source.keep_rows, source.keep_blocks)
+        graph.replay()
+        for _ in range(2):
+            run.Cbuf.fill_(float("nan"))
+            _fused(w, run, run.C)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(run.C.cpu().numpy(), want)
+        bt.fill_(-1)
+        got = run.eng.bt_bits()
+        np.testing.assert_array_equal(got.cpu().numpy().view(np.uint64), synth.pack_bits(synth.unpack_bits(bb, w.NB).T))
