@@ -256,8 +256,9 @@ mmm_status mmm_matmul(const mmm_maps *maps, mmm_dtype dt,
 /* Which kernel mmm_matmul uses.
  *   MMM_PATH_MATRIX: matrix instructions over the packed rows of each 16-column group; skips B's
  *       empty blocks exactly and multiplies A's zeros, but for float inputs, where it leaves out the k
- *       whose column of A is zero in a whole tile of 64 rows if there are enough of them to pay.  Work
- *       grows with B's density, and with that share.
+ *       whose column of A is zero in a whole tile of 64 rows if there are enough of them to pay and the
+ *       most recent mmm_maps_stats counted them (so call it once for an A with whole columns off).
+ *       Work grows with B's density, and with that share.
  *   MMM_PATH_PAIRS : vector FMAs over exactly the products that survive both maps (the loop of
  *       Fig. "MMM Pseudocode": skip when the element of A is zero, skip the empty blocks of the row
  *       of B), found by AND-ing the bitmap row of A with the transposed B map.  Work grows with

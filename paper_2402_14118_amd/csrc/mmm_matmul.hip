@@ -382,7 +382,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // packed B by their slots, where the plain list reads them in order.  Nothing of it can be requested more than a step
     // ahead, so a step takes 0.8 to 1.5 us however short its list is; it pays where the plain lists are long (2048 x 16384 x
     // 4096, blocks of 32 all on, a tenth of the columns on in each tile: 1922 -> 348 us, a third of the blocks on 660 -> 212;
-    // 512 x 8192 x 4096 265 -> 70; see mmm_filter_pays).  Waves need not agree on it: the barriers and copies are the same.
+    // 512 x 8192 x 4096 265 -> 70; see mmm_filter_pays).  Launched if the counts call for it (see matrix_problem).  Waves need not agree on it: the barriers and copies are the same.
     // Floats only.  16-bit lists are multiplied in little more time than such steps take (2048 x 16384 x 4096 as above: 284 and
     // 171 us with plain lists), doubles have the pair kernel, whose work is the surviving products.
     const int64_t any_row0 = (int64_t)tile_m * (TM / MMM_COLANY_ROWS), any_row1 = min(any_row0 + 1, p.MT - 1);
