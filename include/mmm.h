@@ -101,7 +101,7 @@ typedef struct {
 typedef struct mmm_maps mmm_maps;
 
 /* Bytes of device workspace that maps for this shape need: the maps and their
- * derived forms, the image of A (4 bytes per element of X), packed B at its
+ * derived forms, the image of A (4 bytes per element of X, 6 if M is above 64), packed B at its
  * worst-case size (8 bytes per element of Y, 4 if M is at most 64, and 2 bytes per
  * row of Y and 16 columns), room for the inspection lists of A or the image of a
  * double A (8 bytes per element of X), and
@@ -241,6 +241,10 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
  * product is that of the Y given, under the maps as built, by MMM_PATH_PAIRS
  * whatever was chosen or asked for (MMM_ERR_MAPS_MISMATCH where that kernel cannot
  * address this Y, see below).
+ * MMM_PATH_MATRIX multiplies floats as they are or, where the counts of mmm_maps_stats say that it is faster, as the exact
+ * sum of three bf16 parts each, six of whose nine products are accumulated in float (those left out are below 2^-24 of
+ * the whole; see the "float_form" option).  mmm_build_maps lays the operands out for one or the other; a side that is
+ * built alone takes the form of the side that is kept, and a build or multiplication that is captured into a graph fixes the handle's form.
  * Products the maps skip contribute exactly 0, whatever the skipped operands
  * hold (see the conventions above for non-finite kept values).  Every element
  * of C is written exactly once, zeros included.  float accumulation; the
@@ -323,6 +327,8 @@ mmm_status mmm_matmul_static_scratch(const mmm_maps *maps, mmm_dtype dt,
  *   "matmul_variant": -1 = automatic, else index of a compiled tile variant
  *   "split_k"       :  0 = automatic, else the number of K splits to use
  *   "matmul_path"   : -1 = automatic, else MMM_PATH_MATRIX or MMM_PATH_PAIRS
+ *   "float_form"    : -1 = automatic, 0 = floats are multiplied as floats, 1 = in three parts (M above 64; for
+ *                     the builds that follow)
  * Errors: MMM_ERR_INVALID_ARG (unknown name or value out of range). */
 mmm_status mmm_set_option(const char *name, int64_t value);
 

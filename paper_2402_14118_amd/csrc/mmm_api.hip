@@ -26,11 +26,12 @@ void note_device_error(const char *where, hipError_t e)
 std::atomic<int64_t> g_opt_variant{-1};
 std::atomic<int64_t> g_opt_split{0};
 std::atomic<int64_t> g_opt_path{-1};
+std::atomic<int64_t> g_opt_form{-1};
 
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t a_bits, a_colany, a_cnt, a_ent, a_img, b_bits, bt_bits, stats, kinfo, kmap, rows_copy, a_colany_c, btc_bits, bp_val, bp_list, bp_cnt, partials, partial_bytes, total;
+    size_t a_bits, a_colany, a_cnt, a_ent, a_img, a_wild, b_bits, bt_bits, stats, kinfo, kmap, rows_copy, a_colany_c, btc_bits, bp_val, bp_list, bp_cnt, partials, partial_bytes, total;
 };
 
 bool shape_ok(int64_t M, int64_t K, int64_t N, int32_t bw)
@@ -57,8 +58,10 @@ Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw)
     off += align_up(blocks * 4);
     l.a_ent = off;
     off += align_up(blocks * MMM_AB_CAP * 8);
-    l.a_img = off;   // room for the widest element type with an image
-    off += align_up(blocks * MMM_AB_CAP * 4);
+    l.a_img = off;   // room for the widest form (doubles have theirs in a_ent)
+    off += align_up(blocks * MMM_AB_CAP * (M > 64 ? MMM_PARTS_ESZ : 4));
+    l.a_wild = off;
+    off += align_up(blocks);
     l.b_bits = off;
     off += align_up((size_t)K * WB * 8);
     l.bt_bits = off;
@@ -119,10 +122,11 @@ struct MatrixCost {   // microseconds
     double reduce_mega;   // per 2^20 partial sums of C
     double image_giga;    // per 10^9 bytes of A copied to LDS
 };
-constexpr MatrixCost kMatrixCost[3] = {   // 2-, 4-, 8-byte elements
+constexpr MatrixCost kMatrixCost[4] = {   // 2-, 4-, 8-byte elements, floats in parts
     {3.162, 0.2208, 0.0321, 0.0011, 0.1084, 0.571, 2.0, 1.094, 47.1},
     {3.524, 0.1805, 0.1198, 0.0031, 0.0747, 0.561, 2.0, 1.159, 24.9},
     {3.210, 0.3107, 0.4623, 0.0059, 0.1092, 1.362, 3.3, 2.257, 30.9},
+    {3.210, 0.0308, 0.0266, 0.0139, 0.0, 1.607, 2.42, 1.661, 20.2},
 };
 struct PairsCost {   // microseconds
     double launch;     // per call
@@ -137,7 +141,7 @@ constexpr PairsCost kPairsCost[3] = {
     {3.90, 0.00, 30.2, {863, 549, 463}, 15.9},
 };
 
-int cost_class(int32_t dt) { return dt == MMM_F64 ? 2 : dt == MMM_F32 ? 1 : 0; }
+int cost_class(int32_t dt, int32_t form) { return form == MMM_FORM_PARTS ? 3 : dt == MMM_F64 ? 2 : dt == MMM_F32 ? 1 : 0; }
 bool stats_known(const mmm_maps *m) { return m->stats_a_valid && m->stats_b_valid; }
 
 // Densities are known only after a mmm_maps_stats call (the counts of the most recent one are kept as the estimate, also
@@ -149,29 +153,31 @@ struct MatrixProblem {
     bool look;       // workgroups look for columns of A that are zero in their tile (floats)
     bool filtered;   // and most will leave them out of their lists
 };
-MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt)
+MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt, int32_t form)
 {
+    const size_t esz = form == MMM_FORM_PARTS ? 2 : elem_size(dt);   // as the lists are laid out
     const bool known = stats_known(m);
     const int64_t rows = known && m->b_compact ? std::max<int64_t>((int64_t)m->stats_rows_b, 1) : m->K;
     double p = known ? std::min(1.0, (double)m->stats_occ_b / ((double)rows * (double)m->NB)) : 0.2;
     if (m->bw == 8) p = 1.0 - (1.0 - p) * (1.0 - p);   // a group lists k if either of its blocks does
-    const double batch = elem_size(dt) == 2 ? 32.0 : 16.0;
+    const double batch = esz == 2 ? 32.0 : 16.0;
     double listed = p * MMM_AB_COLS;
     MatrixProblem q;
     // The form that looks takes longer where it finds nothing: its registers, arguments and the looking cost 0.5 to 8 us (4096^3,
     // p = .05 121.3 and 128.0 us, 256^3 10.8 and 11.6, 60 problems 4.8 %).  So only where the counts say that there is something.
-    q.look = dt == MMM_F32 && known && m->stats_active < 0.9;
+    q.look = dt == MMM_F32 && form == MMM_FORM_PLAIN && known && m->stats_active < 0.9;
     q.filtered = q.look && mmm_filter_pays((float)listed, (float)(listed * m->stats_active), m->bw);
     if (q.filtered) listed *= m->stats_active;
     q.steps = (rows + MMM_AB_COLS - 1) / MMM_AB_COLS;
     q.batches = listed > 0.5 * batch ? listed / batch + 0.5 : 1.0;
-    q.units = elem_size(dt) == 2 ? q.batches : listed / 4.0 + 0.5;
+    q.units = esz == 2 ? q.batches : listed / 4.0 + 0.5;
     return q;
 }
 
-double matrix_cost(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const mmm_variant_info &vi, int64_t tiles, int64_t split)
+double matrix_cost(const mmm_maps *m, int32_t dt, int32_t form, const MatrixProblem &q, const mmm_variant_info &vi, int64_t tiles, int64_t split)
 {
-    MatrixCost c = kMatrixCost[cost_class(dt)];
+    MatrixCost c = kMatrixCost[cost_class(dt, form)];
+    const size_t esz = form == MMM_FORM_PARTS ? MMM_PARTS_ESZ : elem_size(dt);
     if (q.filtered) {   // lists made in the kernel (estimated from the timings at mmm_filter_pays, within 20 %)
         c.multiply *= 1.35;
         if (m->bw != 32) c.latency += 0.25, c.step += 0.2 * vi.TN / 256.0;
@@ -181,7 +187,7 @@ double matrix_cost(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const 
     const double groups = vi.TN / MMM_GROUP_COLS, work = (double)steps * vi.k_ranges;
     double t = c.launch + (double)steps * q.batches * c.latency +
                (double)per_cu * (work * (c.step + groups * (vi.rows / 16) * q.units * c.multiply) + groups * vi.k_ranges * c.wave + c.workgroup) +
-               1e-9 * c.image_giga * (double)wgs * work * (double)(MMM_AB_ROWS * MMM_AB_COLS * elem_size(dt));
+               1e-9 * c.image_giga * (double)wgs * work * (double)(MMM_AB_ROWS * MMM_AB_COLS * esz);
     if (split > 1) t += c.reduce + 1e-6 * c.reduce_mega * (double)split * (double)m->M * (double)m->N;
     return t;
 }
@@ -191,9 +197,9 @@ double matrix_cost(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const 
 // eighth of T tiles in panels of w columns is about T / w rows by w columns: least for w = sqrt(T * a / b), with a and b
 // the bytes of one row and one column tile.  (512 x 8192 x 4096 bf16, p = .1: one row and all of B per XCD, 143 MB in all
 // against 67, and 27.8 -> 22.7 us; columns bf16 2048 x 1638 of 16384 x 4096 46.2 -> 42.5.)
-int32_t panel_width(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const mmm_plan &p)
+int32_t panel_width(const mmm_maps *m, int32_t dt, int32_t form, const MatrixProblem &q, const mmm_plan &p)
 {
-    const double batch = elem_size(dt) == 2 ? 32.0 : 16.0;
+    const double batch = elem_size(dt) == 2 || form == MMM_FORM_PARTS ? 32.0 : 16.0;
     const double a = (double)(MMM_AB_ROWS * MMM_AB_COLS), b = (double)mmm_variant(p.variant).TN * q.batches * batch;   // elements per step
     const double t = std::max(1.0, (double)p.tiles_m * p.tiles_n / 8.0);
     const int64_t panels = std::max<int64_t>(1, (int64_t)((double)p.tiles_n / std::sqrt(t * a / b) + 0.5));   // of about equal width
@@ -202,7 +208,7 @@ int32_t panel_width(const mmm_maps *m, int32_t dt, const MatrixProblem &q, const
 
 double pairs_cost(const mmm_maps *m, int32_t dt)
 {
-    const PairsCost &c = kPairsCost[cost_class(dt)];
+    const PairsCost &c = kPairsCost[cost_class(dt, MMM_FORM_PLAIN)];
     const double spans = (double)m->M * (double)((m->N + 63) / 64), products = (double)m->stats_macs;
     const int64_t ranges = (m->WA + 63) / 64, shares = (m->N + 511) / 512 * m->M >= 1024 ? 1 : 4;
     // (4 shares for few workgroups whatever K is, as the coefficients were fitted; mmm_launch_pairs takes 1 for K <= 2048.  With its
@@ -222,21 +228,21 @@ mmm_plan tile_plan(const mmm_maps *m, int32_t variant)   // without the split
     return p;
 }
 
-bool variant_usable(const mmm_maps *m, int32_t dt, int64_t v)
+bool variant_usable(const mmm_maps *m, int32_t dt, int32_t form, int64_t v)
 {
     if (v < 0 || v >= mmm_variant_count()) return false;
     const mmm_variant_info &vi = mmm_variant((int32_t)v);
     return !(vi.rows < MMM_AB_ROWS && m->M > vi.rows)        // computes too few rows for this matrix
-           && !(dt == MMM_F64 && !vi.doubles);
+           && !(dt == MMM_F64 && !vi.doubles) && !(form == MMM_FORM_PARTS && !vi.parts);
 }
 
-void compute_plan(const mmm_maps *m, int32_t dt, int64_t variant, int64_t fixed_split, mmm_plan *plan, double *cost)
+void compute_plan(const mmm_maps *m, int32_t dt, int32_t form, int64_t variant, int64_t fixed_split, mmm_plan *plan, double *cost)
 {
-    const MatrixProblem q = matrix_problem(m, dt);
+    const MatrixProblem q = matrix_problem(m, dt, form);
     const size_t c_bytes = (size_t)m->M * (size_t)m->N * c_elem_size(dt);
     double best = -1.0;
     for (int32_t v = 0; v < mmm_variant_count(); ++v) {
-        if (!variant_usable(m, dt, v) || (variant_usable(m, dt, variant) && v != variant)) continue;
+        if (!variant_usable(m, dt, form, v) || (variant_usable(m, dt, form, variant) && v != variant)) continue;
         mmm_plan p = tile_plan(m, v);
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
         static constexpr int64_t kSplits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
@@ -248,7 +254,7 @@ void compute_plan(const mmm_maps *m, int32_t dt, int64_t variant, int64_t fixed_
             split = std::max<int64_t>(1, std::min<int64_t>(split, p.chunks_total));
             p.chunks_per_split = (int32_t)((p.chunks_total + split - 1) / split);
             split = (p.chunks_total + p.chunks_per_split - 1) / p.chunks_per_split;   // drop empty splits
-            const double t = matrix_cost(m, dt, q, mmm_variant(v), tiles, split);
+            const double t = matrix_cost(m, dt, form, q, mmm_variant(v), tiles, split);
             if (best < 0.0 || t < best) {
                 best = t;
                 p.split_k = (int32_t)split;
@@ -258,19 +264,19 @@ void compute_plan(const mmm_maps *m, int32_t dt, int64_t variant, int64_t fixed_
             if (fixed_split > 0 || split < s) break;
         }
     }
-    plan->panel = panel_width(m, dt, q, *plan);
+    plan->panel = panel_width(m, dt, form, q, *plan);
     plan->filter = q.look ? 1 : 0;
     *cost = best;
 }
 
-mmm_plan make_plan(const mmm_maps *m, int32_t dt, double *cost = nullptr)
+mmm_plan make_plan(const mmm_maps *m, int32_t dt, int32_t form, double *cost = nullptr)
 {
     const int64_t v = m->plan_variant >= 0 ? m->plan_variant : g_opt_variant.load();
     const int64_t split = m->plan_split > 0 ? m->plan_split : g_opt_split.load();
     std::lock_guard<std::mutex> lock(m->plan_mutex);
-    const mmm_plan_key key{dt, v, split, m->stats_version, m->b_compact};
+    const mmm_plan_key key{dt, v, split, m->stats_version, m->b_compact, form};
     if (!(m->plan_valid && key == m->plan_key)) {
-        compute_plan(m, dt, v, split, &m->plan, &m->plan_cost);
+        compute_plan(m, dt, form, v, split, &m->plan, &m->plan_cost);
         m->plan_key = key;
         m->plan_valid = true;
     }
@@ -278,7 +284,7 @@ mmm_plan make_plan(const mmm_maps *m, int32_t dt, double *cost = nullptr)
     return m->plan;
 }
 
-int32_t choose_path(const mmm_maps *m, int32_t dt)
+int32_t choose_path(const mmm_maps *m, int32_t dt, int32_t form)
 {
     if (!mmm_packs(m->M, dt)) return MMM_PATH_PAIRS;
     const int64_t path = m->plan_path >= 0 ? m->plan_path : g_opt_path.load();
@@ -292,8 +298,15 @@ int32_t choose_path(const mmm_maps *m, int32_t dt)
     // (215 x 722 x 320: 7.1 against 8.7 us; from 28 tiles on it is the estimates that decide better)
     if (dt == MMM_F64 && ((m->M + 63) / 64) * ((m->N + 63) / 64) <= 24) return MMM_PATH_PAIRS;
     double matrix = 0.0;
-    make_plan(m, dt, &matrix);
+    make_plan(m, dt, form, &matrix);
     return pairs_cost(m, dt) < matrix ? MMM_PATH_PAIRS : MMM_PATH_MATRIX;
+}
+
+// The form the operands are in, or would be if there are none yet.
+int32_t form_of(const mmm_maps *m, int32_t dt)
+{
+    if (dt != MMM_F32) return MMM_FORM_PLAIN;
+    return m->b_built && m->b_dtype == dt ? m->b_form : m->a_built && m->a_dtype == dt ? m->a_form : MMM_FORM_PLAIN;
 }
 
 struct RelaxedCapture {   // calls that another thread's stream capture would forbid, and that do not disturb it
@@ -319,10 +332,65 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
     return MMM_ERR_DEVICE;
 }
 
+// The form a build gives floats: that of the side it does not build (the kernel takes both from one form), that of a captured
+// call, or the one with which build and multiplication are estimated to take less; without counts the plain one.  Parts pay
+// for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 426 + 40 and 348 + 57 us, .2 240 + 34 and
+// 189 + 43, .1 139 + 31 and 169 + 39 (a list of 13 fills 40 % of a batch).
+int32_t choose_form(mmm_maps *m, const mmm_build_args &a, bool capture)
+{
+    if (a.dtype != MMM_F32 || m->M <= 64) return MMM_FORM_PLAIN;
+    const int64_t opt = g_opt_form.load();
+    const bool keeps_a = a.X == nullptr && m->a_built && m->a_dtype == MMM_F32 && !(m->b_compact || a.b_compact);
+    const bool keeps_b = a.Y == nullptr && m->b_built && m->b_dtype == MMM_F32;
+    const int32_t pinned = m->form_pinned.load();
+    int32_t form = MMM_FORM_PLAIN;
+    if (keeps_a || keeps_b) {
+        form = keeps_a ? m->a_form : m->b_form;
+    } else if (pinned >= 0) {
+        form = pinned;
+    } else if (opt >= 0) {
+        form = (int32_t)opt;
+    } else if (stats_known(m)) {
+        const int64_t v = m->plan_variant >= 0 ? m->plan_variant : g_opt_variant.load();
+        const int64_t split = m->plan_split > 0 ? m->plan_split : g_opt_split.load();
+        const int32_t path = m->plan_path >= 0 ? m->plan_path : (int32_t)g_opt_path.load();
+        const mmm_plan_key key{a.dtype, v, split, m->stats_version, m->b_compact, MMM_FORM_PLAIN};
+        if (!(m->form_valid && key == m->form_key && path == m->form_path)) {
+            mmm_plan plan;
+            double plain = 0.0, parts = 0.0;
+            compute_plan(m, a.dtype, MMM_FORM_PLAIN, v, split, &plan, &plain);
+            const bool filter = plan.filter != 0;
+            compute_plan(m, a.dtype, MMM_FORM_PARTS, v, split, &plan, &parts);
+            // What the build takes longer, fitted with the estimate of the parts to 400 random problems of 65 to 4096 rows and
+            // columns, K up to 16384, densities .05 to 1: the image and packed B are half as large again, and the rows of B are
+            // read twice.  Estimates err by 10 %, those of the plain form mostly downwards; with 15 % and 2 us between the two
+            // no problem took longer than before, the mean was .966 of it (without: .963, and up to 1.5 for the worst).
+            const MatrixProblem q = matrix_problem(m, a.dtype, MMM_FORM_PARTS);
+            const double b_rounds = std::ceil((double)q.steps * (double)((m->N + 255) / 256) / 512.0);
+            const double longer = 2.68e-7 * (double)m->M * (double)m->K + 7.7e-7 * (double)m->stats_occ_b * m->bw + 0.6 * q.batches * b_rounds;
+            const bool asked = v >= 0 && !variant_usable(m, a.dtype, MMM_FORM_PARTS, v);
+            const bool pairs = path == MMM_PATH_PAIRS || (path < 0 && v < 0 && pairs_cost(m, a.dtype) < std::min(plain, parts));
+            m->form_chosen = !filter && !asked && !pairs && 1.15 * parts + longer + 2.0 < plain ? MMM_FORM_PARTS : MMM_FORM_PLAIN;
+            m->form_key = key;
+            m->form_path = path;
+            m->form_valid = true;
+        }
+        form = m->form_chosen;
+    }
+    if (capture) m->form_pinned = form;
+    return form;
+}
+
 bool capturing(hipStream_t s)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
+// Whether this call is the first to be captured with a form.  (The null stream is never captured; asking takes 0.15 us.)
+bool form_is_captured(const mmm_maps *m, int32_t dt, hipStream_t s)
+{
+    return dt == MMM_F32 && m->M > 64 && s != nullptr && m->form_pinned.load(std::memory_order_relaxed) < 0 && capturing(s);
 }
 
 // The transposed B map over k is read by the pair kernel and by inspection only.  In row-compacted mode it is made with
@@ -410,6 +478,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->a_cnt = reinterpret_cast<uint32_t *>(base + l.a_cnt);
     m->NG = (N + MMM_GROUP_COLS - 1) / MMM_GROUP_COLS;
     m->a_img = base + l.a_img;
+    m->a_wild = reinterpret_cast<uint8_t *>(base + l.a_wild);
     m->a_img64 = base + l.a_ent;
     m->a_ent = reinterpret_cast<uint64_t *>(base + l.a_ent);
     m->b_bits = reinterpret_cast<uint64_t *>(base + l.b_bits);
@@ -433,6 +502,9 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->bt_event = nullptr;
     m->build_captured = false;
     m->a_dtype = m->b_dtype = -1;
+    m->a_form = m->b_form = MMM_FORM_PLAIN;
+    m->form_pinned = -1;
+    m->form_valid = false;
     m->a_src = nullptr;
     m->a_src_ld = 0;
     m->b_src = nullptr;
@@ -493,6 +565,7 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
     a.b_compact = Y != nullptr && mb->keep_rows != nullptr && dt != MMM_F64;
     const bool compact_after = Y != nullptr ? a.b_compact : maps->b_compact;
     a.a_compact = X != nullptr && compact_after;
+    a.form = choose_form(maps, a, form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream)));
     if (hipError_t e = mmm_launch_build(maps, a, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
         note_device_error("map builder launch", e);
         return MMM_ERR_DEVICE;
@@ -501,9 +574,10 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
         // an image of A made for another numbering of k (or for none) do not fit the new B side
         if (X == nullptr && (maps->b_compact || a.b_compact)) maps->a_built = false;
         maps->b_compact = a.b_compact;
+        maps->b_form = a.form;
         maps->bt_state = a.b_compact ? BT_MISSING : BT_MADE;
         if (a.b_compact && !maps->build_captured) maps->build_captured = capturing(static_cast<hipStream_t>(hip_stream));
-        if (a.b_compact && (maps->M <= 64 || choose_path(maps, dt) == MMM_PATH_PAIRS)) {
+        if (a.b_compact && (maps->M <= 64 || choose_path(maps, dt, a.form) == MMM_PATH_PAIRS)) {
             if (hipError_t e = mmm_launch_expand_rows(maps, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
                 note_device_error("transposed map launch", e);
                 return MMM_ERR_DEVICE;
@@ -513,6 +587,7 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
     }
     if (X != nullptr) {
         maps->a_compact = a.a_compact;
+        maps->a_form = a.form;
         maps->a_built = true;
         maps->a_dtype = dt;
         maps->a_src = X;   // compared, never dereferenced
@@ -630,7 +705,7 @@ mmm_status mmm_matmul_plan(const mmm_maps *maps, mmm_dtype dt, int32_t *variant,
 {
     if (maps == nullptr) return MMM_ERR_INVALID_ARG;
     if (!dtype_ok(dt)) return MMM_ERR_DTYPE;
-    const mmm_plan p = make_plan(maps, dt);
+    const mmm_plan p = make_plan(maps, dt, form_of(maps, dt));
     if (variant) *variant = p.variant;
     if (split_k) *split_k = p.split_k;
     if (workgroups) *workgroups = p.workgroups;
@@ -659,7 +734,7 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
     // Y it is given, so that is what another Y (or the same at another leading dimension) is multiplied by.
     const bool packed_y = maps->b_src == Y && maps->b_src_ld == ldy, pairs_can = mmm_pairs_supports(dt, ldy);
     if (!packed_y && !pairs_can) return MMM_ERR_MAPS_MISMATCH;
-    if (pairs_can && (!packed_y || choose_path(maps, dt) == MMM_PATH_PAIRS)) {   // no scratch at all on this path
+    if (pairs_can && (!packed_y || choose_path(maps, dt, maps->b_form) == MMM_PATH_PAIRS)) {   // no scratch at all on this path
         hipError_t e = ensure_bt(maps, static_cast<hipStream_t>(hip_stream));
         if (e == hipSuccess)
             e = mmm_launch_pairs(maps, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, false, 0, 0.f, nullptr,
@@ -670,7 +745,8 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
         }
         return MMM_OK;
     }
-    const mmm_plan p = make_plan(maps, dt);
+    const mmm_plan p = make_plan(maps, dt, maps->b_form);
+    if (form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream))) maps->form_pinned = maps->b_form;
     void *partials = maps->partials;
     size_t partial_bytes = maps->partial_bytes;
     if (static_scratch) {
@@ -687,7 +763,7 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
         }
         partial_bytes = (size_t)MMM_STATIC_SCRATCH_BYTES;
     }
-    if (hipError_t e = mmm_launch_matmul(maps, p, dt, C, ldc, accumulate ? 1 : 0, partials,
+    if (hipError_t e = mmm_launch_matmul(maps, p, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, partials,
                                          partial_bytes, static_cast<hipStream_t>(hip_stream));
         e != hipSuccess) {
         note_device_error("masked GEMM launch", e);
@@ -757,7 +833,8 @@ mmm_status mmm_maps_set_path(mmm_maps *maps, int32_t path)
 mmm_status mmm_matmul_path(const mmm_maps *maps, int32_t *path)
 {
     if (maps == nullptr || path == nullptr) return MMM_ERR_INVALID_ARG;
-    *path = choose_path(maps, maps->a_built ? maps->a_dtype : maps->b_built ? maps->b_dtype : MMM_F32);
+    const int32_t dt = maps->a_built ? maps->a_dtype : maps->b_built ? maps->b_dtype : MMM_F32;
+    *path = choose_path(maps, dt, form_of(maps, dt));
     return MMM_OK;
 }
 
@@ -772,6 +849,11 @@ mmm_status mmm_set_option(const char *name, int64_t value)
     if (std::strcmp(name, "matmul_variant") == 0) {
         if (value < -1 || value >= mmm_variant_count()) return MMM_ERR_INVALID_ARG;
         g_opt_variant.store(value);
+        return MMM_OK;
+    }
+    if (std::strcmp(name, "float_form") == 0) {
+        if (value < -1 || value > MMM_FORM_PARTS) return MMM_ERR_INVALID_ARG;
+        g_opt_form.store(value);
         return MMM_OK;
     }
     if (std::strcmp(name, "split_k") == 0) {

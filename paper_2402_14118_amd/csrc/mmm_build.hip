@@ -30,6 +30,16 @@ constexpr int A_ROWS = MMM_AB_ROWS / BUILD_WAVES;     // 4 rows of A per wave
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+struct PartedFloat { float v; };   // float elements that are laid out in three parts (see mmm_internal.h)
+template <typename T> struct Layout {   // of the operands
+    static constexpr size_t ESZ = sizeof(T);
+    static constexpr bool PARTED = false;
+};
+template <> struct Layout<PartedFloat> {
+    static constexpr size_t ESZ = MMM_PARTS_ESZ;
+    static constexpr bool PARTED = true;
+};
+
 template <typename T> struct Tile {   // what a workgroup takes at a time, by element size
     static constexpr int ESZ = (int)sizeof(T);
     static constexpr int A_WORDS = ESZ == 8 ? 1 : 2;             // A: 64 rows x 64 A_WORDS columns
@@ -45,6 +55,7 @@ struct BuildParams {
     uint64_t *a_bits;
     uint64_t *a_colany;
     char *a_img;
+    uint8_t *a_wild;      // floats in parts
     const void *Y;
     int64_t ldy;
     const uint64_t *keep_blocks;
@@ -105,6 +116,39 @@ __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)v, l);
 }
 
+// Two floats to bf16, rounded to nearest: one instruction.
+__device__ __forceinline__ uint32_t round2(float a, float b)
+{
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(floatx2{a, b}, bf16x2));
+}
+// The next part of two floats; they become the rests.
+__device__ __forceinline__ uint32_t take_part(uint32_t &a, uint32_t &b)
+{
+    const uint32_t part = round2(__uint_as_float(a), __uint_as_float(b));
+    a = __float_as_uint(__uint_as_float(a) - __uint_as_float(part << 16));
+    b = __float_as_uint(__uint_as_float(b) - __uint_as_float(part & 0xffff0000u));
+    return part;
+}
+// Whether an element that is not zero lies outside the range that three parts hold.
+struct OutOfRange {
+    uint32_t most = 0, least = ~0u;   // of the magnitudes, and of those less 1 (zero is no magnitude)
+    __device__ __forceinline__ void see(uint32_t bits)
+    {
+        const uint32_t m = bits & 0x7fffffffu;
+        most = max(most, m);
+        least = min(least, m - 1u);
+    }
+    __device__ __forceinline__ bool any() const { return most >= MMM_PARTS_HI || least < MMM_PARTS_LO - 1u; }
+};
+__device__ __forceinline__ bool out_of_range(uint32_t bits)
+{
+    OutOfRange o;
+    o.see(bits);
+    return o.any();
+}
+
 // OR of a value over aligned runs of LANES lanes (2 .. 16), in all of them, without leaving the vector registers
 template <int LANES> __device__ __forceinline__ uint32_t or_lanes(uint32_t x)
 {
@@ -133,6 +177,7 @@ __device__ __forceinline__ uint64_t row_word(const uint64_t *row, int64_t w, int
 struct AShared {
     char stage[2][MMM_AB_COLS * MMM_AB_ROWS * 4];
     uint64_t any[2][BUILD_WAVES][2][2];         // [stage][wave][32-row half of the block][word]
+    uint8_t wild[2][BUILD_WAVES];               // floats in parts: [stage][wave]
     uint8_t live[MMM_AB_COLS];                  // row-compacted mode: live columns of the blocks
     uint32_t before[BUILD_WAVES];               // row-compacted mode: live rows before them, by wave
 };
@@ -156,7 +201,9 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
     constexpr int ESZ = (int)sizeof(T);
     constexpr bool WIDE = ESZ >= 4;
     constexpr int A_WORDS = Tile<T>::A_WORDS, A_COLS = 64 * A_WORDS;
-    constexpr int UNITS = MMM_AB_ROWS * ESZ / 16;   // 16-byte units per column
+    constexpr bool PARTED = Layout<T>::PARTED;
+    constexpr bool WIDE_IMG = Layout<T>::ESZ % 4 == 0;   // rows w, w + 16, w + 32, w + 48 in the image, else in natural order
+    constexpr int UNITS = MMM_AB_ROWS * (PARTED ? 2 : ESZ) / 16;   // 16-byte units per column (and part)
     constexpr uint32_t OUTSIDE = 0x80000000u;       // past the end of every buffer resource below, whatever row offset is added
     const bool has_keep = p.keep_a != nullptr;
     constexpr bool compact = ROWS;
@@ -165,8 +212,8 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
     const int64_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;
     const int tail = (int)min(p.K - k_lo, (int64_t)A_COLS);   // columns of these blocks that exist
     const uint32_t row_bytes = (uint32_t)p.ldx * ESZ, map_bytes = (uint32_t)p.WA * 8u;
-    const uint32_t row0 = WIDE ? (uint32_t)wave : (uint32_t)wave * A_ROWS;
-    constexpr uint32_t ROW_STEP = WIDE ? BUILD_WAVES : 1;
+    const uint32_t row0 = WIDE_IMG ? (uint32_t)wave : (uint32_t)wave * A_ROWS;
+    constexpr uint32_t ROW_STEP = WIDE_IMG ? BUILD_WAVES : 1;
     uint32_t off[A_WORDS];
 #pragma unroll
     for (int h = 0; h < A_WORDS; ++h) off[h] = 64 * h + lane < tail ? (uint32_t)(64 * h + lane) * ESZ : OUTSIDE;
@@ -232,7 +279,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
     auto block = [&](int64_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
         ConstParams &p = reread(p0);
         constexpr int AHEAD = decltype(ahead)::value;   // the block whose loads take this one's place
-        char *const stage = sh.stage[st];
+        char *const stage = sh.stage[PARTED ? 0 : st];
         uint64_t word[A_ROWS][A_WORDS];   // bitmap words: wave-uniform, the lane masks of what stays
         uint32_t pair[2][A_WORDS];        // 16-bit: rows 2t and 2t + 1
         if constexpr (!WIDE)
@@ -270,6 +317,8 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             words(std::true_type{});
         else
             words(std::false_type{});
+        if (PARTED && bi > bi0) __syncthreads();   // one stage (48 KiB; two would leave a compute unit one workgroup): the block before has left it
+        OutOfRange range;
 #pragma unroll
         for (int h = 0; h < A_WORDS; ++h) {
             const int k = 64 * h + lane;
@@ -277,6 +326,34 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
                 pattern u[A_ROWS];
 #pragma unroll
                 for (int t = 0; t < A_ROWS; ++t) u[t] = __builtin_amdgcn_inverse_ballot_w64(word[t][h]) ? cur.x[t][h] : (pattern)0;
+                if constexpr (PARTED) {
+                    OutOfRange here;
+#pragma unroll
+                    for (int t = 0; t < A_ROWS; ++t) here.see(u[t]);
+                    range.most = max(range.most, here.most);
+                    range.least = min(range.least, here.least);
+                    u32x2 part[MMM_PARTS];
+                    uint32_t rest[A_ROWS] = {u[0], u[1], u[2], u[3]};
+#pragma unroll
+                    for (int q = 0; q < MMM_PARTS; ++q) part[q] = u32x2{take_part(rest[0], rest[1]), take_part(rest[2], rest[3])};
+                    if (ballot64(here.any()) != 0)   // seldom: such elements as they are
+#pragma unroll
+                        for (int t = 0; t < A_ROWS; ++t)
+                            if (out_of_range(u[t])) {
+                                auto put = [&](uint32_t &to, uint32_t v) { to = t & 1 ? (to & 0xffffu) | v << 16 : (to & 0xffff0000u) | v; };
+                                uint32_t v0 = part[0][t / 2], v1 = part[1][t / 2], v2 = part[2][t / 2];
+                                put(v0, u[t] >> 16);
+                                put(v1, u[t] & 0xffffu);
+                                put(v2, MMM_PARTS_RAW);
+                                part[0][t / 2] = v0;
+                                part[1][t / 2] = v1;
+                                part[2][t / 2] = v2;
+                            }
+#pragma unroll
+                    for (int q = 0; q < MMM_PARTS; ++q)
+                        *reinterpret_cast<u32x2 *>(stage + q * MMM_PART_BYTES + k * 128 + ((wave ^ (((k >> 1) & 7) << 1)) << 3)) = part[q];
+                    continue;
+                }
                 char *at = stage + k * (UNITS * 16) + ((wave ^ (k & 15)) << 4);
                 if constexpr (ESZ == 4) {
                     *reinterpret_cast<uint4 *>(at) = make_uint4(u[0], u[1], u[2], u[3]);
@@ -310,17 +387,21 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             auto any_of = [&](uint32_t v) {
                 if constexpr (ESZ == 8) return v | other(v, Swap1{});
                 v |= other(v, Swap2{});
-                if constexpr (ESZ == 2) v |= other(other(v, Mirror8{}), Swap1{});
+                if constexpr (!WIDE_IMG) v |= other(other(v, Mirror8{}), Swap1{});
                 return v;
             };
             const uint64_t any = (uint64_t)any_of(mine_hi) << 32 | any_of(mine_lo);
             if (ESZ == 8) {
                 if (lane < 4 && (lane & 1) == 0) sh.any[st][wave][lane >> 1][0] = any;
-            } else if (ESZ == 4) {
+            } else if (WIDE_IMG) {
                 if (lane < 8 && (lane & 2) == 0) sh.any[st][wave][lane >> 2][lane & 1] = any;
             } else {
                 if (lane < 4) sh.any[st][wave][lane >> 1][lane & 1] = lane >> 1 == wave / (BUILD_WAVES / 2) ? any : 0ull;
             }
+        }
+        if constexpr (PARTED) {
+            const bool wild = ballot64(range.any()) != 0;
+            if (lane == 0) sh.wild[st][wave] = wild ? 1 : 0;
         }
         if (AHEAD == 2 || bi + 1 < bi1) load(bi + AHEAD, cur);
         __builtin_amdgcn_raw_buffer_store_b64(u32x2{mine_lo, mine_hi}, map_rsrc(p.a_bits, bi, true), (int)map_at, 0, 0);
@@ -333,6 +414,10 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             hi = or_lanes<16>(hi);
             const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
             if ((lane & 15) == 0 && tile < p.MT && h < A_WORDS && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
+            if constexpr (PARTED) {
+                const uint64_t wild = ballot64(sh.wild[st][lane & 15] != 0);
+                if (lane == 0) p.a_wild[bi * p.KBA + bj] = wild != 0 ? 1 : 0;
+            }
         }
         // the image: column k (or k') of block row bi is one run of 64 elements
         if (compact && bi == bi0) {
@@ -342,9 +427,29 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
         char *img = p.a_img + ((size_t)bi * p.KBA * MMM_AB_COLS + base) * (UNITS * 16);
         auto stage_of = [&](int k, int unit, uint32_t col) -> int {   // where unit `unit` of image column `col` waits in the stage
             // (16-bit: undo the rotation of the stage, apply that of the image, see mmm_img_swizzle)
-            return WIDE ? k * (UNITS * 16) + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
+            return WIDE_IMG ? k * (UNITS * 16) + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
         };
-        if (compact) {
+        if constexpr (PARTED) {
+            if (compact) {
+                char *const blocks = p.a_img + (size_t)bi * p.KBA * MMM_BLOCK_PARTS_BYTES;
+                for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
+                    const int j = q / UNITS, k = (int)sh.live[j];
+                    const uint32_t col = base + (uint32_t)j;
+                    const int at = stage_of(k, q % UNITS, col);
+                    char *const to = blocks + (size_t)(col / MMM_AB_COLS) * MMM_BLOCK_PARTS_BYTES + (col % MMM_AB_COLS) * 128u + (uint32_t)(q % UNITS) * 16u;
+#pragma unroll
+                    for (int i = 0; i < MMM_PARTS; ++i)
+                        *reinterpret_cast<uint4 *>(to + i * MMM_PART_BYTES) = *reinterpret_cast<const uint4 *>(stage + i * MMM_PART_BYTES + at);
+                }
+            } else {   // a unit of each part per thread
+                static_assert(A_COLS * UNITS == BUILD_THREADS || !PARTED, "");
+                char *const to = p.a_img + ((size_t)bi * p.KBA + (size_t)bj) * MMM_BLOCK_PARTS_BYTES + threadIdx.x * 16u;
+                const int j = threadIdx.x / UNITS, at = stage_of(j, threadIdx.x % UNITS, (uint32_t)j);
+#pragma unroll
+                for (int i = 0; i < MMM_PARTS; ++i)
+                    *reinterpret_cast<uint4 *>(to + i * MMM_PART_BYTES) = *reinterpret_cast<const uint4 *>(stage + i * MMM_PART_BYTES + at);
+            }
+        } else if (compact) {
             for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
                 const int j = q / UNITS, k = (int)sh.live[j];
                 *reinterpret_cast<uint4 *>(img + (uint32_t)q * 16u) = *reinterpret_cast<const uint4 *>(stage + stage_of(k, q % UNITS, base + j));
@@ -378,7 +483,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
 struct BShared {
     uint8_t gbits[64][BUILD_WAVES];   // [lane][wave]: rows in which the lane's 16-column group is occupied
     uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
-    uint16_t list[16][SEG];
+    __align__(16) uint16_t list[16][SEG];
     char pack[16 * (SEG * MMM_GROUP_COLS * 2 + 16)];   // 16-bit types: the packed groups
     int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
@@ -458,6 +563,8 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
     constexpr int BPW = B_COLS / BW;                  // blocks per column tile
     constexpr bool WIDE = ESZ >= 4;
     constexpr bool SPLIT = BW < MMM_GROUP_COLS;       // a group holds two blocks
+    constexpr bool PARTED = Layout<T>::PARTED;
+    constexpr size_t LSZ = Layout<T>::ESZ;
     constexpr uint32_t NO_LOAD = 0x80000000u, NO_STORE = 0xfffffff0u;   // offsets past the ends of the buffer resources
     const int64_t col0 = ct * B_COLS, blk0 = ct * BPW;
     if (ROWS) {
@@ -562,8 +669,10 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
         if (ct == p.ctiles - 1)   // pad bits of the row
             for (int64_t q = (blk0 + BPW + 7) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
     }
-    constexpr int RING = mmm_ring(sizeof(T));
-    constexpr uint32_t ZERO_ENTRY = mmm_list_entry(sizeof(T), mmm_zero_col(RING));
+    constexpr int RING = mmm_ring(LSZ);
+    // (floats in parts: their ring has no zero column, and any that exists does)
+    // (floats in parts: their ring has no zero column; the block's first, which exists if there is a list, does as well)
+    const uint32_t ZERO_ENTRY = mmm_list_entry(LSZ, PARTED ? ((uint32_t)seg & (RING - 1u)) * SEG : mmm_zero_col(RING));
     static_assert(B_GROUPS * SEG * 2 <= BUILD_THREADS * 4, "at most one list word per thread");
     if (threadIdx.x < B_GROUPS * SEG / 2) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
     __syncthreads();
@@ -589,14 +698,14 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
     for (int j0 = 0; j0 < B_ROWS; j0 += LPG) {
         const uint32_t j = (uint32_t)(j0 + lane % LPG);
         if ((gb >> j) & 1u)
-            sh.list[lane / LPG][mmm_list_pos(sizeof(T), slot0 + (uint32_t)__popc(gb & ((1u << j) - 1u)))] =
-                (uint16_t)mmm_list_entry(sizeof(T), ((uint32_t)seg & (RING - 1u)) * SEG + (uint32_t)(wave * B_ROWS) + j);
+            sh.list[lane / LPG][mmm_list_pos(LSZ, slot0 + (uint32_t)__popc(gb & ((1u << j) - 1u)))] =
+                (uint16_t)mmm_list_entry(LSZ, ((uint32_t)seg & (RING - 1u)) * SEG + (uint32_t)(wave * B_ROWS) + j);
     }
-    if (wave == 0 && lane % LPG == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
+    if (!PARTED && wave == 0 && lane % LPG == 0 && group_ok) p.bp_cnt[G * p.KBA + seg] = n;
     uint32_t slots[B_ROWS];
 #pragma unroll
     for (int j = 0; j < B_ROWS; ++j) slots[j] = slot0 + (uint32_t)__popc(gb & ((1u << j) - 1u));
-    if constexpr (WIDE) {
+    if constexpr (LSZ % 4 == 0) {
         // slot-major rows of 64 or 128 bytes; the slots that fill up the last quad are zero
         constexpr uint32_t ROWB = MMM_GROUP_COLS * ESZ;
         // the segment of the tile's first group; a group's area is at most 2^28 bytes, 2^29 for doubles (K < 2^22), and a tile
@@ -610,37 +719,75 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
         if (wave < 3 && n + wave < ((n + 3u) & ~3u) && group_ok)
             __builtin_amdgcn_raw_buffer_store_b128(u32x4{0, 0, 0, 0}, out, (int)(mine_at + (n + wave) * ROWB), 0, 0);
         __syncthreads();
+    } else if constexpr (PARTED) {
+        // A wave takes a group, a thread eight slots of a column at a time, in the order of mmm_value_pos.  The values are read
+        // again, by the list (they are in the L2): kept in registers and turned round in LDS they took three times as long for B
+        // as plain floats do (4096^2, p = .2: 30.8 and 24.5 us, part by part and batch by batch; 9.8 plain).
+        __syncthreads();   // the lists
+        const int64_t CG = ct * B_GROUPS + wave;
+        const uint32_t n_out = (uint32_t)__builtin_amdgcn_readlane((int)n, wave * LPG);
+        if (CG < p.NG) {
+            const uint32_t c = (uint32_t)lane & 15u, s4 = (uint32_t)lane >> 4;
+            const bool col_ok = CG * MMM_GROUP_COLS + c < p.N;
+            const char *const ycol = static_cast<const char *>(p.Y) + (CG * MMM_GROUP_COLS + c) * ESZ;
+            char *out = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * LSZ) + lane * 16;
+            const uint8_t *const block_rows = sh.bbits[wave * LPG + (c >= 8u ? LPB : 0)];   // of this lane's half of the group, if it is one
+            OutOfRange range;
+#pragma unroll 1
+            for (uint32_t slot = 4u * s4; (int)(slot - 4u * s4) < (int)n_out; slot += 32, out += MMM_PARTS * 1024) {
+                const u32x4 entries = *reinterpret_cast<const u32x4 *>(&sh.list[wave][mmm_list_pos(LSZ, slot)]);
+                uint32_t v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {   // slot + 16 (i / 4) + i % 4
+                    const uint32_t k = (entries[i % 4] >> (i / 4 * 16 + 3)) & (SEG - 1u);   // see mmm_list_entry
+                    bool there = slot + (uint32_t)(i / 4 * 16 + i % 4) < n_out && col_ok;
+                    if (SPLIT) there = there && ((block_rows[k / 8] >> (k % 8)) & 1u);
+                    const int64_t row = ROWS ? (int64_t)sh.kk[k] : seg * SEG + k;
+                    v[i] = there ? *reinterpret_cast<const uint32_t *>(ycol + row * row_bytes) : 0u;
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) range.see(v[i]);
+#pragma unroll
+                for (int q = 0; q < MMM_PARTS; ++q) {
+                    u32x4 part;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) part[i] = take_part(v[2 * i], v[2 * i + 1]);
+                    *reinterpret_cast<u32x4 *>(out + q * 1024) = part;
+                }
+            }
+            const bool wild = ballot64(range.any()) != 0;
+            if (lane == 0) p.bp_cnt[CG * p.KBA + seg] = n_out | (wild ? 0x80000000u : 0u);
+        }
     } else {
         // Composed in LDS in the order of mmm_value_pos; the slots that fill up the last batch are zero.  Whole batches are
         // copied out, 1 KiB each.
-        constexpr int GROUPB = SEG * MMM_GROUP_COLS * ESZ + 16;   // bytes per group (4 banks apart)
+        constexpr int GROUPB = SEG * MMM_GROUP_COLS * ESZ + 16;     // bytes per group (4 banks apart)
         constexpr uint32_t SLOTS = 32;                            // per batch
         static_assert(B_GROUPS * GROUPB <= (int)sizeof(sh.pack), "room for the groups");
         uint16_t *g = reinterpret_cast<uint16_t *>(sh.pack + (lane / LPG) * GROUPB);
-        auto put = [&](uint32_t slot, const u32x4 &v) {
+        auto put = [&](uint32_t slot, u32x2 v) {
             uint16_t *at = g + mmm_value_pos(ESZ, slot, (uint32_t)(lane & 3) * 4u);
             at[0] = (uint16_t)v.x;
             at[8] = (uint16_t)(v.x >> 16);
             at[16] = (uint16_t)v.y;
             at[24] = (uint16_t)(v.y >> 16);
         };
-#pragma unroll
-        for (int j = 0; j < B_ROWS; ++j)
-            if ((gb >> j) & 1u) put(slots[j], raw[j]);
-#pragma unroll
-        for (uint32_t i = 0; i < SLOTS; i += BUILD_WAVES)
-            if (n + i + wave < ((n + SLOTS - 1) & ~(SLOTS - 1))) put(n + i + wave, u32x4{0, 0, 0, 0});
-        __syncthreads();
         constexpr int TPG = BUILD_THREADS / B_GROUPS;   // threads per group
         const int cg = threadIdx.x / TPG;
         const int64_t CG = ct * B_GROUPS + cg;
-        if (CG < p.NG) {
-            const uint64_t *bits = reinterpret_cast<const uint64_t *>(sh.gbits[cg * LPG]);
-            const uint32_t batches = ((uint32_t)(__popcll(bits[0]) + __popcll(bits[1])) + SLOTS - 1u) / SLOTS;
-            char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
+        const uint64_t *bits = reinterpret_cast<const uint64_t *>(sh.gbits[cg * LPG]);
+        const uint32_t batches = ((uint32_t)(__popcll(bits[0]) + __popcll(bits[1])) + SLOTS - 1u) / SLOTS;
+        char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
+#pragma unroll
+        for (int j = 0; j < B_ROWS; ++j)
+            if ((gb >> j) & 1u) put(slots[j], u32x2{raw[j].x, raw[j].y});
+#pragma unroll
+        for (uint32_t i = 0; i < SLOTS; i += BUILD_WAVES)
+            if (n + i + wave < ((n + SLOTS - 1) & ~(SLOTS - 1))) put(n + i + wave, u32x2{0, 0});
+        __syncthreads();
+        if (CG < p.NG)
             for (uint32_t q = threadIdx.x % TPG; q < batches * 64; q += TPG)
                 *reinterpret_cast<uint4 *>(cval + q * 16) = *reinterpret_cast<const uint4 *>(sh.pack + cg * GROUPB + q * 16);
-        }
     }
     {   // the lists, one word per thread
         const int64_t LG = ct * B_GROUPS + (threadIdx.x >> 6);
@@ -773,8 +920,17 @@ __global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_im
     const char *col = a_img + ((size_t)bi * KBA * MMM_AB_COLS + kc) * (MMM_AB_ROWS * sizeof(T));
     for (uint64_t m = rows; m != 0; m &= m - 1) {
         const int r = __builtin_ctzll(m);
-        const T v = *reinterpret_cast<const T *>(col + mmm_img_row(sizeof(T), (uint32_t)kc, (uint32_t)r));
-        ent[at++] = make_uint2(mmm_slab_pos((uint32_t)r, (uint32_t)c), f32_bits<T>(v));
+        uint32_t bits;
+        if constexpr (Layout<T>::PARTED) {
+            uint16_t part[MMM_PARTS];
+            for (int q = 0; q < MMM_PARTS; ++q)
+                part[q] = *reinterpret_cast<const uint16_t *>(a_img + (size_t)b * MMM_BLOCK_PARTS_BYTES + q * MMM_PART_BYTES + c * 128 + mmm_img_row(2, (uint32_t)kc, (uint32_t)r));
+            auto value = [&](int q) { return __uint_as_float((uint32_t)part[q] << 16); };
+            bits = part[2] == MMM_PARTS_RAW ? (uint32_t)part[0] << 16 | part[1] : __float_as_uint(value(0) + (value(1) + value(2)));
+        } else {
+            bits = f32_bits<T>(*reinterpret_cast<const T *>(col + mmm_img_row(sizeof(T), (uint32_t)kc, (uint32_t)r)));
+        }
+        ent[at++] = make_uint2(mmm_slab_pos((uint32_t)r, (uint32_t)c), bits);
     }
     if (c == 0) a_cnt[b] = total;
     if (total + c < ((total + 63u) & ~63u)) ent[total + c] = make_uint2(MMM_SLAB_SPARE, 0u);
@@ -900,8 +1056,9 @@ template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int
     if (deep && HALF) return rows ? build_kernel_test<T, true, HALF>(mode, bw) : build_kernel_test<T, false, HALF>(mode, bw);
     return rows ? build_kernel_test<T, true, false>(mode, bw) : build_kernel_test<T, false, false>(mode, bw);
 }
-static build_kernel_fn build_kernel(int32_t dtype, int32_t mode, int32_t bw, bool rows, bool deep)
+static build_kernel_fn build_kernel(int32_t dtype, int32_t form, int32_t mode, int32_t bw, bool rows, bool deep)
 {
+    if (form == MMM_FORM_PARTS) return build_kernel_rows<PartedFloat>(mode, bw, rows, deep);
     return dtype == MMM_F64  ? build_kernel_test<double, false, false>(mode, bw)   // no row-compacted mode
          : dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows, deep)
          : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows, deep)
@@ -917,6 +1074,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.a_bits = m->a_bits;
     p.a_colany = m->a_colany;
     p.a_img = a.dtype == MMM_F64 ? m->a_img64 : m->a_img;
+    p.a_wild = m->a_wild;
     p.Y = a.Y;
     p.ldy = a.ldy;
     p.keep_blocks = a.keep_blocks;
@@ -969,7 +1127,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.a_per_wg = (uint32_t)per_wg;
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    hipLaunchKernelGGL(build_kernel(a.dtype, p.test.mode, m->bw, p.rows != nullptr, per_wg >= 4), grid, block, 0, s, p);
+    hipLaunchKernelGGL(build_kernel(a.dtype, a.form, p.test.mode, m->bw, p.rows != nullptr, per_wg >= 4), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
@@ -999,6 +1157,8 @@ hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s)
         hipLaunchKernelGGL(mmm_lists_kernel<uint16_t>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
     else if (m->a_dtype == MMM_F16)
         hipLaunchKernelGGL(mmm_lists_kernel<_Float16>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
+    else if (m->a_form == MMM_FORM_PARTS)
+        hipLaunchKernelGGL(mmm_lists_kernel<PartedFloat>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
     else
         hipLaunchKernelGGL(mmm_lists_kernel<float>, grid, block, 0, s, m->a_img, m->a_bits, kinfo, m->kmap, m->a_cnt, ent, m->M, m->K, m->WA, m->KBA);
     return hipGetLastError();
@@ -1011,18 +1171,19 @@ __global__ __launch_bounds__(64) void mmm_k_lists_kernel(const uint64_t *a_colan
                                                          const uint32_t *kinfo, uint8_t *out, int64_t NG, int64_t WA, int64_t MT,
                                                          int64_t groups, int64_t steps)
 {
-    constexpr int RING = mmm_ring(sizeof(T));
+    constexpr size_t LSZ = Layout<T>::ESZ;
+    constexpr int RING = mmm_ring(LSZ);
     const int lane = threadIdx.x;
     const int64_t c = blockIdx.x % steps, G = (blockIdx.x / steps) % groups, t = blockIdx.x / (steps * groups);
     if (kinfo && c * MMM_AB_COLS >= (int64_t)*kinfo) return;
     uint8_t *rec = out + ((t * groups + G) * steps + c) * 132;
     uint32_t n = 0;
     if (G < NG) {
-        const uint32_t slots = bp_cnt[G * steps + c];
+        const uint32_t slots = bp_cnt[G * steps + c] & 0xffu;   // (without the mark of floats in parts)
         for (int h = 0; h < 2; ++h) {
             const uint32_t slot = (uint32_t)(64 * h + lane);
-            const uint32_t entry = bp_list[(G * steps + c) * SEG + mmm_list_pos(sizeof(T), slot)];
-            const uint32_t k = (sizeof(T) == 2 ? entry >> 3 : sizeof(T) == 8 ? entry >> 1 : entry) - (uint32_t)(c & (RING - 1)) * SEG;   // see mmm_list_entry
+            const uint32_t entry = bp_list[(G * steps + c) * SEG + mmm_list_pos(LSZ, slot)];
+            const uint32_t k = mmm_list_entry_k(LSZ, entry, (uint32_t)(c & (RING - 1)));
             bool in = false;
             if (slot < slots && k < (uint32_t)SEG) {
                 const int64_t w = 2 * c + (k >> 6);
@@ -1049,7 +1210,7 @@ hipError_t mmm_launch_dump_lists(const mmm_maps *m, uint8_t *out, size_t out_byt
     if (m->b_compact)
         if (hipError_t e = mmm_launch_colany_compact(m, s); e != hipSuccess) return e;
     (void)hipGetLastError();
-    const auto kernel = m->b_dtype == MMM_F64 ? mmm_k_lists_kernel<double> : m->b_dtype == MMM_F32 ? mmm_k_lists_kernel<float> : mmm_k_lists_kernel<uint16_t>;
+    const auto kernel = m->b_dtype == MMM_F64 ? mmm_k_lists_kernel<double> : m->b_form == MMM_FORM_PARTS ? mmm_k_lists_kernel<PartedFloat> : m->b_dtype == MMM_F32 ? mmm_k_lists_kernel<float> : mmm_k_lists_kernel<uint16_t>;
     hipLaunchKernelGGL(kernel, dim3((uint32_t)wgs), dim3(64), 0, s, m->b_compact ? m->a_colany_c : m->a_colany, m->bp_list, m->bp_cnt,
                        m->b_compact ? m->kinfo : nullptr, out, m->NG, m->WA, m->MT, groups, m->KBA);
     return hipGetLastError();

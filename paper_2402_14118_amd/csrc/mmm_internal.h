@@ -58,14 +58,36 @@ constexpr int MMM_GROUP_COLS = 16;
 // p = .1: 28.8 against 29.2 us) and leaves no room for a second ring or workgroup.
 constexpr int mmm_ring(size_t esz) { return esz == 2 ? 4 : 2; }
 __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t)ring * MMM_AB_COLS; }
+// Floats in parts.  The other form of float operands: every element as the sum of three bf16 numbers, each the rounded rest of
+// what the ones before leave (8 + 8 + 8 significant bits: nothing is lost), which the 16-bit matrix instructions multiply.  Of the
+// nine products of two elements the six that are not below 2^-24 of the whole are summed, those of the two first parts in one set
+// of accumulators and the others, 2^-8 of them and less, in another, so that the sums round seldom: 2-norm of the error over 256 to 4096 terms
+// 0.5 to 2.9e-7, of the float instruction 1.2 to 7.4e-7.  32 k of a row tile take 6 instructions of 16.7 cycles instead of 8 of 32.6.
+// An element outside [2^-110, 2^55) is not held exactly (or its cross products could overflow where the product does not; infinities and NaN are among
+// them): a block of A and a segment of a group of B that have one are marked, and are multiplied as floats from X and Y.
+// Image: [block of 64 x 128][part][column][64 rows], columns as of the 16-bit types.  Packed B: batches of 32 slots as of the
+// 16-bit types, [batch][part].  As an "element size": 6.
+constexpr int MMM_PARTS = 3;
+constexpr size_t MMM_PARTS_ESZ = 2 * MMM_PARTS;
+constexpr uint32_t MMM_PARTS_LO = (127 - 110) << 23, MMM_PARTS_HI = (127 + 55) << 23;   // bit patterns of the bounds
+constexpr uint32_t MMM_PART_BYTES = MMM_AB_ROWS * MMM_AB_COLS * 2;                      // of a block of A
+constexpr uint32_t MMM_BLOCK_PARTS_BYTES = MMM_PARTS * MMM_PART_BYTES;
+constexpr uint16_t MMM_PARTS_RAW = 0xffffu;   // as the third part: the first two are the bits of the element as it is (a marked block's)
+enum { MMM_FORM_PLAIN = 0, MMM_FORM_PARTS = 1 };
 // col: ring column (mmm_zero_col for the zero column: a multiple of 8, so the rotation is nil)
 __host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
 {
-    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3) | mmm_img_swizzle(col);
+    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3 | mmm_img_swizzle(col)) + (esz == MMM_PARTS_ESZ ? col / MMM_AB_COLS * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 0);
+}
+// and back, inside its block
+__host__ __device__ constexpr uint32_t mmm_list_entry_k(size_t esz, uint32_t entry, uint32_t block_in_ring)
+{
+    return (esz == 8 ? entry >> 1 : esz == 4 ? entry : (entry - (esz == MMM_PARTS_ESZ ? block_in_ring * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 0u)) >> 3) -
+           block_in_ring * MMM_AB_COLS;
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
 {
-    return esz >= 4 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
+    return esz % 4 == 0 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
 }
 __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, uint32_t col)   // in elements
 {
@@ -95,9 +117,10 @@ struct mmm_plan {
 struct mmm_plan_key {
     int64_t dtype, variant, split, stats_version;
     bool b_compact;
+    int32_t form;
     bool operator==(const mmm_plan_key &o) const
     {
-        return dtype == o.dtype && variant == o.variant && split == o.split && stats_version == o.stats_version && b_compact == o.b_compact;
+        return dtype == o.dtype && variant == o.variant && split == o.split && stats_version == o.stats_version && b_compact == o.b_compact && form == o.form;
     }
 };
 
@@ -116,6 +139,7 @@ struct mmm_maps {
     uint64_t *a_bits;
     uint64_t *a_colany;
     char *a_img;       // image of A (see above)
+    uint8_t *a_wild;   // [MBA][KBA] floats in parts: whether the 64 x 128 elements hold one that is out of range
     uint32_t *a_cnt;   // [MBA][KBA] non-zeros per block            (inspection: written by mmm_launch_lists)
     uint64_t *a_ent;   // [MBA*KBA][MMM_AB_CAP] entries {mmm_slab_pos(row, column), value bits}, padded to a
                        // multiple of 64 with {spare cell, 0}       (inspection)
@@ -149,6 +173,9 @@ struct mmm_maps {
     bool build_captured;   // a build of B in row-compacted mode has been captured into a graph
     bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
+    int32_t a_form, b_form;   // MMM_FORM_*: the same of both where both are built, with floats
+    // the form every build keeps to once a call has been captured into a graph, which may run between others (-1: none yet)
+    mutable std::atomic<int32_t> form_pinned;
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)
     int64_t a_src_ld;
     const void *b_src;   // the same of the Y the B side was built from
@@ -166,6 +193,11 @@ struct mmm_maps {
     mutable mmm_plan_key plan_key;
     mutable mmm_plan plan;
     mutable double plan_cost;   // estimated microseconds
+    // the form last chosen, and for what
+    bool form_valid;
+    mmm_plan_key form_key;
+    int32_t form_path;
+    int32_t form_chosen;
 };
 
 // Element predicate of M, decided on the bit pattern so that no denormal mode of the float pipeline can
@@ -195,12 +227,14 @@ struct mmm_build_args {
     int32_t dtype;
     bool a_compact;   // lay A out over the live k (the numbering exists or is made in this call)
     bool b_compact;   // number the live rows (keep_rows given) and pack those
+    int32_t form;     // MMM_FORM_*
 };
 
 struct mmm_variant_info {
     const char *name;
     int32_t TM, TN, KC, rows, k_ranges;   // rows: rows of C actually computed (64, or 32 for short matrices); k_ranges: ranges of K inside a workgroup
     bool doubles;                         // takes double inputs
+    bool parts;                           // takes floats in parts
 };
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
@@ -216,7 +250,8 @@ hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s);
 int32_t mmm_variant_count();
 const mmm_variant_info &mmm_variant(int32_t i);
 // partials / partial_bytes: where the split-K partial sums go (used only when p.split_k > 1)
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, void *C, int64_t ldc, int32_t accumulate, void *partials,
+// X, Y (with their leading dimensions): read for marked blocks of floats in parts only
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, const void *X, int64_t ldx, const void *Y, int64_t ldy, void *C, int64_t ldc, int32_t accumulate, void *partials,
                              size_t partial_bytes, hipStream_t s);
 // The multiplication over exactly the surviving products, on the vector ALUs.  fused: evaluate M
 // (pred, threshold, keep_a) on X inside the kernel; otherwise a_bits of the maps are used.

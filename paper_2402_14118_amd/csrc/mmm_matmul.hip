@@ -25,7 +25,15 @@
 // v_mfma_f32_16x16x32 on 32 listed k, with ds_read_b64_tr_b16 gathering their A operands and one load of 16 bytes per
 // lane for B's.
 //
-// What bounds it: dense lists, the matrix cores (4096^3 fp32, p = .4: 437 us, of which 360 are matrix instructions at
+// Floats whose lists are long are multiplied in three bf16 parts (FloatParts; see MMM_PARTS in mmm_internal.h and choose_form):
+// six 16-bit matrix instructions for 32 listed k take 100 cycles where the eight float instructions take 261.  A block of A
+// is half as large again, so a ring of two leaves room for one workgroup of 16 waves on a compute unit.  4096^3 p = .4: 426 -> 348 us
+// (matrix cores 55 % and LDS 50 % busy, clock 1.9 GHz), p = .2: 240 -> 189 us.  What is left is that between two barriers all
+// waves read from LDS first and multiply then.  Tried, and no faster: a third block in the ring, with the copies two steps ahead
+// (167 -> 181 us at p = .1) or the first operands read before the barrier (175); units of 32 slots as one stream over the steps, three
+// of them on their way (p = .1 182, p = .4 338); two lists per wave in turns, eight waves (237 and 378).
+//
+// What bounds it otherwise: dense lists, the matrix cores (4096^3 fp32, p = .4: 437 us, of which 360 are matrix instructions at
 // the rate a large product reaches); sparse ones, whose steps are one short batch, the compute unit's scalar unit and vector-memory issue,
 // which all waves share.  Hence the schedule of `step` below: 4096^3 p = .05 fp32 118 -> 106 us, 2048^3 p = .1
 // 29.3 -> 27.6, 512 x 8192 x 4096 bf16 35.1 -> 32.7, against clamped offsets, one request per quad and a count load per step.
@@ -65,7 +73,13 @@ struct MatmulParams {
     const uint64_t *a_colany;   // column-any words of A, over k
     const uint32_t *kmap;       // row-compacted mode: k' -> k
     int64_t NB, WA, MT;
+    // floats in parts: the marks of the blocks of A, and what marked blocks and segments are multiplied from
+    const uint8_t *a_wild;
+    const uint64_t *a_bits, *b_bits;
+    const float *X, *Y;
+    int64_t ldx, ldy, WB;
 };
+struct FloatParts { uint16_t part[MMM_PARTS]; };   // element type of floats in parts
 
 typedef double doublex2 __attribute__((ext_vector_type(2)));
 typedef double doublex4 __attribute__((ext_vector_type(4)));
@@ -81,6 +95,7 @@ template <> struct Mfma16<uint16_t> {   // bf16
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
 };
+template <> struct Mfma16<FloatParts> : Mfma16<uint16_t> {};
 template <> struct Mfma16<_Float16> {
     static __device__ __forceinline__ floatx4 k32(u32x4 a, u32x4 b, floatx4 c)
     {
@@ -105,12 +120,18 @@ typedef __attribute__((address_space(3))) char lds_char;
 // the others (see wait_vmem).
 template <int N> __device__ __forceinline__ void copy_to_lds(const char *base, uint32_t voff, uint32_t lds)
 {
-    static_assert(N == 1 || N == 2 || N % 4 == 0, "");
+    static_assert(N <= 3 || N % 2 == 0, "");
     // (m0 is an operand, so that the compiler sets it and knows what it holds; the nop keeps the distance its write needs.)
     if constexpr (N == 1) {
         asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
     } else if constexpr (N == 2) {
         asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
+    } else if constexpr (N == 3) {
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1\n\tglobal_load_lds_dwordx4 %0, %1 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %0, %1 offset:2048" ::"v"(voff), "s"(base), "{m0}"(lds) : "memory");
+    } else if constexpr (N % 4 != 0) {
+        copy_to_lds<N - 2>(base, voff, lds);
+        copy_to_lds<2>(base + (N - 2) * 1024, voff, lds + (N - 2) * 1024);
     } else {
 #pragma unroll
         for (int i = 0; i < N / 4; ++i)
@@ -142,9 +163,11 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 //     sums are added in LDS at the end, in order
 // FILTER  floats: look whether to leave the columns of A out that are zero in the whole tile (see `filtered`)
 template <int RT, int GW, int NW, int KS, typename T, bool FILTER>
-__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? NW / 4 : sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
-    constexpr bool WIDE = sizeof(T) >= 4, F64 = sizeof(T) == 8;
+    constexpr bool F64 = sizeof(T) == 8, WIDE = sizeof(T) == 4 || F64;
+    constexpr bool PARTED = sizeof(T) == MMM_PARTS_ESZ;
+    constexpr int PARTS = PARTED ? MMM_PARTS : 1;
     constexpr int ESZ = (int)sizeof(T);
     typedef typename Acc<T>::tile tile_t;
     typedef typename Acc<T>::element elem_t;
@@ -154,14 +177,16 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     constexpr int ZERO_AT = RING * SLAB;            // the ring's zero column (mmm_zero_col)
     constexpr int DMA = SLAB / 1024 / NW;           // copies per wave and block
     constexpr int BATCH = WIDE ? 16 : 32;           // list slots per batch
-    constexpr int OPS = WIDE ? 4 * GW + 1 : GW + 1;       // vector-memory operations request() makes
+    constexpr int OPS = WIDE ? 4 * GW + 1 : PARTS * GW + 1;   // vector-memory operations request() makes
     constexpr int SEGB = KC * MMM_GROUP_COLS * ESZ;       // bytes of a packed segment
     static_assert(DMA * NW * 1024 == SLAB, "whole copies");
     typedef elem_t avec __attribute__((ext_vector_type(RT)));   // 4- and 8-byte types: A operands of the RT row tiles for one k
 
-    constexpr int RING_BYTES = RING * SLAB + COLB;
+    constexpr int RING_BYTES = RING * SLAB + (PARTED ? 0 : COLB);
+    static_assert(!PARTED || (RT == TM / 16 && KS == 1 && RING == 2), "");
     __shared__ __align__(1024) char rings[KS * RING_BYTES];
     static_assert(!FILTER || ESZ == 4, "");
+    __shared__ uint32_t step_marks[PARTED ? 1024 : 1];   // marked steps of this row tile, if there are any: K is below 2^22
     __shared__ __align__(16) uint16_t lists[FILTER ? KS * NW * 2 * KC : 1];   // of `filtered`: [wave][parity of the step][slot]
 
     const int tid = threadIdx.x;
@@ -199,6 +224,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     for (int g = 0; g < GW; ++g)
 #pragma unroll
         for (int r = 0; r < RT; ++r) acc[g][r] = tile_t{0, 0, 0, 0};
+    tile_t rest[PARTED ? GW : 1][RT];   // floats in parts: the products that are not of two first parts
+#pragma unroll
+    for (int g = 0; g < (PARTED ? GW : 1); ++g)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) rest[g][r] = tile_t{0, 0, 0, 0};
 
     // this wave's groups; a wave past the last column walks the last group's addresses and multiplies nothing
     const int64_t G0 = ((int64_t)tile_n * NW + wave) * GW;
@@ -222,14 +252,14 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     auto copy_block = [&]() __attribute__((always_inline)) {
         copy_to_lds<DMA>(src, dma_v, place0 + place);
         src += SLAB;
-        place = (place + SLAB) & (RING * SLAB - 1);
+        place = PARTED ? place ^ SLAB : (place + SLAB) & (RING * SLAB - 1);
         --to_copy;
     };
 
     // ---- B: one batch of a group's list in registers
     struct Batch {
         elem_t bf[WIDE ? GW : 1][4];    // 4- and 8-byte types: slot 4u + s of column c, u = 0..3
-        u32x4 bh[WIDE ? 1 : GW];        // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
+        u32x4 bh[WIDE ? 1 : GW][PARTS]; // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
         u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
         uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each)
     };
@@ -253,7 +283,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         } else {
             b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, off_l, 0);
 #pragma unroll
-            for (int g = 0; g < GW; ++g) b.bh[g] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16, off_v + g * val_next, 0);
+            for (int g = 0; g < GW; ++g)
+#pragma unroll
+                for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16 + q * 1024, off_v + g * val_next, 0);
         }
         asm volatile("" ::: "memory");
     };
@@ -314,22 +346,35 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             // ring address: entry * 16 with the rotation of the column's units in bits 5 and 6, plus this lane's four
             // rows; row tile r is 32 bytes on, before rotation
             const uint32_t at[2] = {(b.entry << 4 & 0xffff0u) | chunk8, (b.entry >> 12 & 0xffff0u) | chunk8};
-            auto operand = [&](int h, int r) __attribute__((always_inline)) -> u32x2 {
+            auto operand = [&](int q, int h, int r) __attribute__((always_inline)) -> u32x2 {
                 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
-                return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(ring3 + (at[h] ^ (uint32_t)(r * 32)))));
+                return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(ring3 + (at[h] ^ (uint32_t)(r * 32)) + q * MMM_PART_BYTES)));
             };
-            // The whole batch whatever its length: slots past the end name the zero column and hold zeros.  (A branch to a
-            // 16-slot instruction for short lists costs more, in moved accumulators, than it saves in LDS reads.)
-            u32x2 a[2][RT];
+            // The whole batch whatever its length: slots past the end name the zero column (floats in parts: the block's
+            // first) and hold zeros.  (A branch to a 16-slot instruction for short lists costs more, in moved accumulators,
+            // than it saves in LDS reads, and that instruction takes as long.)
+            u32x2 a[PARTS][2][RT];
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+            for (int q = 0; q < PARTS; ++q)
 #pragma unroll
-                for (int r = 0; r < RT; ++r) a[h][r] = operand(h, r);
+                for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int r = 0; r < RT; ++r)
+                    for (int r = 0; r < RT; ++r) a[q][h][r] = operand(q, h, r);
+            auto products = [&](int qa, int qb, auto &sum) __attribute__((always_inline)) {
 #pragma unroll
-                for (int g = 0; g < GW; ++g)
-                    acc[g][r] = Mfma16<T>::k32(u32x4{a[0][r].x, a[0][r].y, a[1][r].x, a[1][r].y}, b.bh[g], acc[g][r]);
+                for (int r = 0; r < RT; ++r)
+#pragma unroll
+                    for (int g = 0; g < GW; ++g)
+                        sum[g][r] = Mfma16<T>::k32(u32x4{a[qa][0][r].x, a[qa][0][r].y, a[qa][1][r].x, a[qa][1][r].y}, b.bh[g][qb], sum[g][r]);
+            };
+            products(0, 0, acc);
+            if constexpr (PARTED) {
+                products(0, 1, rest);
+                products(0, 2, rest);
+                products(1, 0, rest);
+                products(1, 1, rest);
+                products(2, 0, rest);
+            }
         }
     };
 
@@ -502,10 +547,27 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     };
 
     if (chunk_begin < chunk_end) {
+        // Lane i: length of the list of step i from there on.
+        auto lengths = [&](int from) __attribute__((always_inline)) -> uint32_t {
+            const bool there = active && from + lane < chunk_end;
+            uint32_t n = there ? cnt0[from + lane] : 0u;
+            if (PARTED && GW > 1) n |= there ? cnt0[p.KBA + from + lane] & 0x80000000u : 0u;   // (the mark of either group)
+            return n;
+        };
+        // Floats in parts: those of the first steps, and whether a block of this row tile is marked, are asked for ahead of the
+        // copies, so that there is one round trip in front of the first step instead of three (4096^3, p = .4: 359 -> 348 us;
+        // where two workgroups share a compute unit it makes no difference).
+        uint32_t marks = 0, first_lengths = 0;
+        if constexpr (PARTED) {
+            first_lengths = lengths(chunk_begin);
+            for (int64_t i = lane; i < p.KBA; i += 64) marks |= p.a_wild[tile_m * p.KBA + i];
+            asm volatile("" ::: "memory");
+        }
 #pragma unroll
         for (int i = 0; i < RING - 1; ++i)
             if (to_copy > 0) copy_block();
-        for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
+        if constexpr (!PARTED)
+            for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
         request(B0, off_v, off_l);
         request(B1, off_v + SEGB, off_l + SEG_L);
         wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
@@ -535,10 +597,33 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         if (filter) {
             if constexpr (FILTER) filtered();
         } else {
+        // Floats in parts: a step whose block of A or segment of B is marked has no list in the loop below and is done behind it.
+        const bool a_marked = PARTED && __ballot(marks != 0) != 0;
+        bool some_marked = false;
+        if (a_marked) {   // (the same for all waves)
+            for (int w = tid; w * 32 < chunk_end - chunk_begin; w += NW * 64) {
+                uint32_t bits = 0;
+                for (int i = 0; i < 32 && chunk_begin + w * 32 + i < chunk_end; ++i) {
+                    const int ch = chunk_begin + w * 32 + i;
+                    int64_t k0 = (int64_t)ch * KC, k1 = k0;
+                    if (p.kinfo != nullptr) {   // the marks are over k: all blocks the step's columns come from
+                        k0 = p.kmap[(int64_t)ch * KC];
+                        k1 = p.kmap[min((uint32_t)(ch + 1) * KC, *p.kinfo) - 1u];
+                    }
+                    for (int64_t j = k0 / KC; j <= k1 / KC; ++j) bits |= p.a_wild[tile_m * p.KBA + j] != 0 ? 1u << i : 0u;
+                }
+                step_marks[w] = bits;
+            }
+            __syncthreads();
+        }
         bool first = true;
-        for (int done = 0; done < even_steps; done += 62) {   // lane i: length of the list of step done + i
-            const int ch = chunk_begin + done + lane;
-            uint32_t counts = active && ch < chunk_end ? cnt0[ch] : 0u;
+        for (int done = 0; done < even_steps; done += 62) {
+            uint32_t counts = PARTED && done == 0 ? first_lengths : lengths(chunk_begin + done);
+            if constexpr (PARTED) {
+                if (a_marked && done + lane < chunk_end - chunk_begin) counts |= step_marks[(done + lane) >> 5] << (31 - ((done + lane) & 31)) & 0x80000000u;
+                some_marked |= __ballot((int)counts < 0) != 0;
+                counts = (int)counts < 0 ? 0u : counts;
+            }
             asm volatile("" : "+v"(counts));   // waited for here
             if (first && (int)__builtin_amdgcn_readlane(counts, 0) > BATCH) request(B2, off_v + BATCH_V, off_l + BATCH_L);
             first = false;
@@ -551,6 +636,47 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 n = n2;
             }
         }
+        if constexpr (PARTED) {
+            if (some_marked && active) {   // the marked steps, as floats from X and Y.  Seldom: no more than correct.
+#pragma unroll 1
+                for (int ch = chunk_begin; ch < chunk_end; ++ch) {
+                    uint32_t m = cnt0[ch];
+                    const uint32_t n = m & 0xffu;
+                    if (GW > 1) m |= cnt0[p.KBA + ch];
+                    if (a_marked) m |= step_marks[(ch - chunk_begin) >> 5] << (31 - ((ch - chunk_begin) & 31)) & 0x80000000u;
+                    if ((int)m >= 0) continue;
+                    const uint16_t *const list = p.bp_list + (Gc * p.KBA + ch) * KC;
+#pragma unroll 1
+                    for (uint32_t i = 0; i < n; i += 4) {
+                        const uint32_t slot = min(i + (uint32_t)s, n - 1u);
+                        int64_t k = (int64_t)ch * KC + mmm_list_entry_k(ESZ, list[mmm_list_pos(ESZ, slot)], (uint32_t)ch & (RING - 1u));
+                        if (p.kinfo != nullptr) k = p.kmap[k];
+                        const bool there = i + (uint32_t)s < n;
+                        float a[RT];
+#pragma unroll
+                        for (int r = 0; r < RT; ++r) {
+                            const int64_t row = row0 + r * 16 + c;
+                            const bool kept = there && row < p.M && ((p.a_bits[min(row, p.M - 1) * p.WA + (k >> 6)] >> (k & 63)) & 1ull);
+                            a[r] = kept ? p.X[row * p.ldx + k] : 0.f;
+                        }
+#pragma unroll
+                        for (int g = 0; g < GW; ++g) {
+                            const int64_t col = (G0 + g) * 16 + c, blk = min(col / p.bw, p.NB - 1);
+                            const bool on = there && col < p.N && ((p.b_bits[k * p.WB + (blk >> 6)] >> (blk & 63)) & 1ull);
+                            const float b = on ? p.Y[k * p.ldy + col] : 0.f;
+#pragma unroll
+                            for (int r = 0; r < RT; ++r) acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b, acc[g][r], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+        }
+        }
+        if constexpr (PARTED) {
+#pragma unroll
+            for (int g = 0; g < GW; ++g)
+#pragma unroll
+                for (int r = 0; r < RT; ++r) acc[g][r] += rest[g][r];
         }
     } else if (KS > 1) {   // no step left for this range of K: only the barriers of the others
         for (int i = 0; i < even_steps; ++i) asm volatile("s_barrier" ::: "memory");
@@ -680,32 +806,35 @@ struct VariantEntry {
     int32_t waves;              // of 16 columns each; 32-wide blocks: half as many waves of 32 columns
     matmul_kernel_fn fn[2][4];  // [bw == 32][element type]; null: not built
     matmul_kernel_fn filter[2]; // [bw == 32]: floats, without the columns of A that are zero in the tile
+    matmul_kernel_fn parts[2];  // [bw == 32]: floats in parts
 };
 
 #define MMM_KERNELS(RT, GW, NW, KS)                                                                                       \
     mmm_matmul_kernel<RT, GW, NW, KS, float, false>, mmm_matmul_kernel<RT, GW, NW, KS, uint16_t, false>,                  \
         mmm_matmul_kernel<RT, GW, NW, KS, _Float16, false>
 #define MMM_FILTERS(RT, NW, KS) {mmm_matmul_kernel<RT, 1, NW, KS, float, true>, mmm_matmul_kernel<RT, 2, NW / 2, KS, float, true>}
-#define MMM_VARIANT(RT, NW)                                                                                               \
+#define MMM_PARTED(RT, NW) {mmm_matmul_kernel<RT, 1, NW, 1, FloatParts, false>, mmm_matmul_kernel<RT, 2, NW / 2, 1, FloatParts, false>}
+#define MMM_WHOLE(RT, NW) {nullptr, nullptr}
+#define MMM_VARIANT(RT, NW, PARTS, PARTS_KERNELS)                                                                         \
     {                                                                                                                     \
-        {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT, 1, true}, NW,                                                    \
+        {"R" #RT "x16_TN" #NW "x16", TM, 16 * NW, KC, 16 * RT, 1, true, PARTS}, NW,                                             \
             {{MMM_KERNELS(RT, 1, NW, 1), mmm_matmul_kernel<RT, 1, NW, 1, double, false>},                                 \
              {MMM_KERNELS(RT, 2, NW / 2, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, double, false>}},                        \
-            MMM_FILTERS(RT, NW, 1)                                                                                        \
+            MMM_FILTERS(RT, NW, 1), PARTS_KERNELS(RT, NW)                                                                 \
     }
 #define MMM_VARIANT_K2(RT, NW) /* two rings: not for doubles */                                                           \
     {                                                                                                                     \
-        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false}, NW,                                                 \
-            {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}, MMM_FILTERS(RT, NW, 2)      \
+        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false, false}, NW,                                                 \
+            {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}, MMM_FILTERS(RT, NW, 2), MMM_WHOLE(RT, NW) \
     }
 
 const VariantEntry g_variants[] = {
-    MMM_VARIANT(4, 8),      // 0: 64 x 128
-    MMM_VARIANT(4, 16),     // 1: 64 x 256
-    MMM_VARIANT(4, 4),      // 2: 64 x 64
-    MMM_VARIANT(2, 8),      // 3: 32 x 128   (matrices of at most 32 rows)
+    MMM_VARIANT(4, 8, false, MMM_WHOLE),      // 0: 64 x 128
+    MMM_VARIANT(4, 16, true, MMM_PARTED),     // 1: 64 x 256
+    MMM_VARIANT(4, 4, false, MMM_WHOLE),      // 2: 64 x 64
+    MMM_VARIANT(2, 8, false, MMM_WHOLE),      // 3: 32 x 128   (matrices of at most 32 rows)
     MMM_VARIANT_K2(2, 8),   // 4: 32 x 128, K in two ranges
-    MMM_VARIANT(2, 4),      // 5: 32 x 64
+    MMM_VARIANT(2, 4, false, MMM_WHOLE),      // 5: 32 x 64
     MMM_VARIANT_K2(4, 8),   // 6: 64 x 128, K in two ranges
     MMM_VARIANT_K2(4, 4),   // 7: 64 x 64, K in two ranges
 };
@@ -743,7 +872,7 @@ hipError_t mmm_static_scratch(float **ptr)
 int32_t mmm_variant_count() { return kVariants; }
 const mmm_variant_info &mmm_variant(int32_t i) { return g_variants[i].info; }
 
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtype, void *C, int64_t ldc, int32_t accumulate,
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtype, const void *X, int64_t ldx, const void *Y, int64_t ldy, void *C, int64_t ldc, int32_t accumulate,
                              void *partials, size_t partial_bytes, hipStream_t s)
 {
     if (pl.variant < 0 || pl.variant >= kVariants) return hipErrorInvalidValue;
@@ -781,7 +910,18 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     if (pl.split_k > 1 && (size_t)pl.split_k * (size_t)m->M * (size_t)m->N * (f64 ? sizeof(double) : sizeof(float)) > partial_bytes)
         return hipErrorInvalidValue;
     const int wide = m->bw == 32 ? 1 : 0;
-    matmul_kernel_fn fn = pl.filter ? v.filter[wide] : v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
+    const bool parts = m->b_form == MMM_FORM_PARTS;
+    if (parts) {
+        p.a_wild = m->a_wild;
+        p.a_bits = m->a_bits;
+        p.b_bits = m->b_bits;
+        p.X = static_cast<const float *>(X);
+        p.Y = static_cast<const float *>(Y);
+        p.ldx = ldx;
+        p.ldy = ldy;
+        p.WB = m->WB;
+    }
+    matmul_kernel_fn fn = parts ? v.parts[wide] : pl.filter ? v.filter[wide] : v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
     if (fn == nullptr) return hipErrorInvalidValue;
     (void)hipGetLastError();   // drop any stale error another library left on this thread
     hipLaunchKernelGGL(fn, dim3((uint32_t)pl.workgroups), dim3((uint32_t)(v.waves >> wide) * (uint32_t)v.info.k_ranges * 64), 0, s, p);

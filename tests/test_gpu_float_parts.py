@@ -1,0 +1,217 @@
+"""Floats in three bf16 parts: the form of the float operands that the 16-bit matrix instructions multiply.  Asked for here
+with the "float_form" option; by itself the library takes it where the estimates say that it is faster."""
+import numpy as np
+import pytest
+import torch
+
+import mmm_synth as synth
+import oracle
+import paper_2402_14118_amd as mm
+from hip_harness import HipRun, assert_close
+from test_gpu_parity import check_workload
+
+pytestmark = pytest.mark.gpu
+
+PLAIN, PARTS = 0, 1
+
+
+@pytest.fixture(autouse=True)
+def parts_on_the_matrix_path():
+    mm.mmm_set_option("float_form", PARTS)
+    mm.mmm_set_option("matmul_path", mm.MMM_PATH_MATRIX)
+    yield
+    mm.mmm_set_option("float_form", -1)
+    mm.mmm_set_option("matmul_path", -1)
+
+
+# ---- the edges of tiles, groups, segments, batches of 32 and the two blocks of the ring ----------
+@pytest.mark.parametrize("rows", [None, 0.6], ids=["all", "rows"])
+@pytest.mark.parametrize("M,K,N,bw", [(65, 1, 8, 8), (65, 2, 136, 8), (128, 65, 272, 16), (129, 127, 256, 16), (129, 128, 288, 32),
+                                      (66, 129, 264, 8), (190, 257, 544, 32), (70, 1030, 48, 16), (200, 8065, 32, 16)])
+def test_edges(M, K, N, bw, rows):
+    w = synth.random_masked(M, K, N, bw, 0.4, 0.4, 31 * M + K + N, dist="smallint", p_rows=rows)
+    run, (_, _, C_ref, _, _) = check_workload(w, "edges", exact=True)
+    run.eng.set_plan(-1, 3)
+    run.Cbuf.fill_(float("nan"))
+    run.matmul()
+    run.matmul(accumulate=True)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(run.C.cpu().numpy(), 2 * C_ref)
+
+
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_list_lengths(bw):
+    lengths = [0, 1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 95, 97, 127, 128, 0]
+    segs, N = 16, 256
+    K, NB = segs * 128, N // bw
+    keep = np.zeros((K, NB), bool)
+    rng = np.random.default_rng(bw)
+    for s in range(segs):
+        for b in range(NB):
+            keep[s * 128 + rng.permutation(128)[: lengths[(s + b * bw // max(16, bw)) % len(lengths)]], b] = True
+    w = synth.random_masked(80, K, N, bw, 0.5, 1.0, 77 + bw, dist="smallint")
+    w.keep_blocks = synth.pack_bits(keep)
+    check_workload(w, "lengths", exact=True, ldx=K + 3, ldy=N + 5, ldc=N + 1)
+
+
+# ---- no less exact than floats as they are ------------------------------------------------------
+@pytest.mark.parametrize("dist", ["normal", "uniform"])
+@pytest.mark.parametrize("scale_x,scale_y", [(1.0, 1.0), (2.0 ** -100, 2.0 ** 40), (1.0, 0.02)])
+@pytest.mark.parametrize("M,K,N,p", [(130, 300, 96, 0.1), (130, 2100, 96, 0.4)])
+def test_error_against_double_precision(M, K, N, p, scale_x, scale_y, dist):
+    w = synth.random_masked(M, K, N, 16, p, p, 5 + K, dist=dist)
+    w.X, w.Y = (w.X * np.float32(scale_x)).astype(np.float32), (w.Y * np.float32(scale_y)).astype(np.float32)
+    ab, bb, _, mag = oracle.run_workload(w)
+    A = np.where(synth.unpack_bits(ab, K), w.X, 0).astype(np.float64)
+    B = np.where(np.repeat(synth.unpack_bits(bb, N // 16), 16, axis=1), w.Y, 0).astype(np.float64)
+    exact = A @ B
+    error = {}
+    for form in (PLAIN, PARTS):
+        mm.mmm_set_option("float_form", form)
+        _, _, C = HipRun(w).run()
+        error[form] = np.linalg.norm(C - exact) / np.linalg.norm(exact)
+        # a sum of n products rounded once each is off by less than n 2^-24 |A||B| (six products of parts are left out or
+        # rounded below that)
+        assert (np.abs(C - exact) <= K * 2.0 ** -24 * mag + 1e-45).all()
+    assert error[PARTS] <= error[PLAIN]
+
+
+# ---- elements that the parts do not hold: multiplied as floats ----------------------------------
+@pytest.mark.parametrize("rows", [None, 0.7], ids=["all", "rows"])
+@pytest.mark.parametrize("bw", [8, 16, 32])
+@pytest.mark.parametrize("value", [2.0 ** -111, 3e-39, -1e-45, 2.0 ** 55, -3.4028235e38], ids=str)
+def test_finite_elements_out_of_range(value, bw, rows):
+    """One in A, one in B, in blocks of their own; the other factors are small integers, so every sum is exact in float or
+    dominated by the element."""
+    w = synth.random_masked(140, 700, 96, bw, 0.4, 0.6, 17 + bw, dist="smallint", p_rows=rows)
+    ab = oracle.run_workload(w)[0]
+    live = np.ones(w.K, bool) if rows is None else synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0]
+    b = synth.unpack_bits(oracle.b_bits(w.Y, bw, w.keep_rows, w.keep_blocks), w.NB)
+    i, k = [int(v) for v in np.argwhere(synth.unpack_bits(ab, w.K) & live)[300]]
+    w.X[i, k] = value
+    k2, jb = [int(v) for v in np.argwhere(b)[-1]]
+    assert k // 128 != k2 // 128
+    w.Y[k2, jb * bw + 1] = value
+    ab, bb, C_ref, mag = oracle.run_workload(w)
+    run = HipRun(w)
+    a_hip, b_hip, C = run.run()
+    np.testing.assert_array_equal(a_hip, ab)
+    np.testing.assert_array_equal(b_hip, bb)
+    finite = np.isfinite(C_ref)
+    np.testing.assert_array_equal(np.isfinite(C), finite)
+    assert (np.abs(C[finite] - C_ref[finite]) <= w.K * 2.0 ** -24 * mag[finite] + 1e-45).all()
+    mm.mmm_set_option("float_form", PLAIN)
+    plain = HipRun(w).run()[2]
+    clean = (C_ref == np.rint(C_ref)) & (np.abs(C_ref) < 2 ** 20)       # sums of small integers alone
+    np.testing.assert_array_equal(C[clean], plain[clean])
+
+
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan], ids=str)
+@pytest.mark.parametrize("where", ["x", "y"])
+def test_non_finite_elements(where, value):
+    """What the definition gives in the row or column of the element, and nothing elsewhere."""
+    w = synth.random_masked(140, 700, 96, 16, 0.4, 0.6, 29, dist="smallint")
+    ab, bb, C_ref, _ = oracle.run_workload(w)
+    a, b = synth.unpack_bits(ab, w.K), synth.unpack_bits(bb, w.NB)
+    i, k = [int(v) for v in np.argwhere(a)[500]]
+    jb = int(np.nonzero(b[k])[0][0])
+    hit = np.zeros(C_ref.shape, bool)
+    if where == "x":
+        w.X[i, k] = value
+        hit[i] = np.repeat(b[k], 16)
+    else:
+        w.Y[k, jb * 16 + 3] = value
+        hit[:, jb * 16 + 3] = True
+    bad = oracle.run_workload(w)[2]
+    _, _, C = HipRun(w).run()
+    np.testing.assert_array_equal(C[~hit], C_ref[~hit])
+    if where == "x":
+        np.testing.assert_array_equal(np.isfinite(C), np.isfinite(bad))
+        np.testing.assert_array_equal(np.isnan(C), np.isnan(bad))
+    else:
+        rows = a[:, k]
+        assert not np.isfinite(C[rows, jb * 16 + 3]).any()
+        rest = C[~rows, jb * 16 + 3]
+        assert np.all(np.isnan(rest) | (rest == C_ref[~rows, jb * 16 + 3]))
+
+
+def test_inspection_shows_the_elements_as_they_are():
+    rng = np.random.default_rng(3)
+    w = synth.random_masked(100, 300, 32, 16, 0.5, 0.5, 4, dist="normal")
+    bits = rng.integers(0, 1 << 32, w.X.shape, dtype=np.uint64).astype(np.uint32)       # every exponent, NaN payloads too
+    w.X = np.where(rng.random(w.X.shape) < 0.3, bits.view(np.float32), w.X)
+    from test_gpu_parity import check_lists
+    run = HipRun(w)
+    run.build()
+    torch.cuda.synchronize()
+    check_lists(run, oracle.a_bits(w.X, keep_bits=w.keep_a), w, "lists")
+
+
+# ---- which form a build takes ---------------------------------------------------------------------
+def test_the_form_follows_the_counts_and_the_side_that_is_kept():
+    """Seen by the bits of C, which the two forms round differently."""
+    mm.mmm_set_option("matmul_path", -1)
+    w = synth.random_masked(1500, 2100, 1024, 16, 0.4, 0.5, 8, dist="normal")
+    want = {}
+    for form in (PLAIN, PARTS):
+        mm.mmm_set_option("float_form", form)
+        run = HipRun(w)
+        run.eng.set_plan(1, 1)
+        want[form] = run.run()[2]
+    mm.mmm_set_option("float_form", -1)
+    assert (want[PLAIN] != want[PARTS]).any()
+
+    def check(run, form):
+        run.Cbuf.fill_(float("nan"))
+        run.matmul()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), want[form])
+
+    run = HipRun(w)
+    run.eng.set_plan(1, 1)
+    run.build()
+    check(run, PLAIN)                      # nothing is known
+    run.eng.stats()
+    check(run, PLAIN)                      # as it was built
+    run.build(a=True, b=False)
+    check(run, PLAIN)                      # B is kept
+    run.build(a=False, b=True)
+    check(run, PLAIN)                      # A is
+    run.build()
+    check(run, PARTS)
+    run.build(a=True, b=False)
+    check(run, PARTS)
+    run.eng.set_plan(0, 1)                 # a shape that parts do not have: the automatic one until the next build
+    check(run, PARTS)
+    run.build()
+    check(run, PLAIN)
+
+
+@pytest.mark.parametrize("captured", ["build", "matmul"])
+def test_a_captured_call_fixes_the_form(captured):
+    """A graph's build or multiplication runs between calls of other forms otherwise."""
+    w = synth.random_masked(200, 700, 288, 16, 0.4, 0.5, 9, dist="smallint")
+    C_ref = oracle.run_workload(w)[2]
+    mm.mmm_set_option("float_form", -1)
+    run = HipRun(w)
+    run.build()
+    run.matmul()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run.build() if captured == "build" else run.matmul()
+    mm.mmm_set_option("float_form", PARTS)
+    run.eng.stats()
+    for _ in range(3):
+        run.Cbuf.fill_(float("nan"))
+        if captured == "matmul":
+            run.build()
+        graph.replay()
+        if captured == "build":
+            run.matmul()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+        run.build()
+        run.matmul()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
