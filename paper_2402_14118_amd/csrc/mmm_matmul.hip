@@ -262,6 +262,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         u32x4 bh[WIDE ? 1 : GW][PARTS]; // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
         u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
         uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each)
+        uint32_t what;                  // 16-bit: see `plan`
     };
     Batch B0, B1, B2;
     // The batch whose values and entries lie at these byte offsets of the group's area.  Always OPS loads, so that the waits
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         }
     };
 
-    // ---- One step: the block in the ring against the n rows listed for it.  A compute unit has one scalar unit for all of
+    // ---- One step (4- and 8-byte types): the block in the ring against the n rows listed for it.  A compute unit has one scalar unit for all of
     // its waves, and steps are short (a sparse one is one batch), so what is done per step is kept to about two dozen scalar
     // instructions: offsets and pointers advance by constants, nothing is clamped, the list lengths sit in a register.
     // (With 55 of them a 512 x 8192 x 4096 half-precision multiplication spent 11 of its 31 us on control alone.)
@@ -419,7 +420,38 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         off_l += SEG_L;
     };
 
-    const int even_steps = (steps + 1) & ~1;   // steps go in pairs; the odd one past the end has no list
+    // ---- 16-bit types and floats in parts: the same with the batches of all steps in one queue, requested three ahead
+    // whatever steps they belong to.  Above, second batches are requested a step ahead, further ones only when they are next
+    // but one, and a list of several costs a request in vain; here none does.  What a turn has to know about its batch (place,
+    // slots, whether a step begins with it) stands ready in a lane of `plan`, made 64 batches at a time on the vector ALU, so
+    // that a turn takes 18 scalar instructions; with the same worked out by scalar selects it took 31, and short lists lost
+    // what long ones won.  The turns past the end, up to two, do nothing.
+    // 4096^3, p = .4: floats in parts 415 -> 373 us (the whole pass), bf16 multiplication 111 -> 102; 512 x 8192 x 4096, bf16,
+    // 24.3 -> 23.6, p = .4 38.0 -> 35.4.  4- and 8-byte types keep the steps above: their batches are half as large and mostly
+    // one to a step, and the queue's beginning costs more than it gives (4096^3, p = .05, floats 89.5 -> 93.7, 2048^3, p = .1,
+    // doubles 43.3 -> 45.2).
+    constexpr int PER_STEP = KC / BATCH;   // batches that fit in a segment
+    constexpr uint32_t PAST = 1u << 31, FRESH = 1u << 30, LEFT = 24, PLACE = (1u << LEFT) - 1u;
+    uint32_t plan = 0;                                       // lane j: the j-th of the next batches:
+                                                             //   PAST the last, FRESH: first of its step, slots << LEFT, place
+    int ahead_j = 0;                                         // the one requested last
+    auto request_at = [&](Batch &b, uint32_t what) __attribute__((always_inline)) {
+        b.what = what;
+        const int place = (int)(what & PLACE);
+        request(b, place * (BATCH * MMM_GROUP_COLS * ESZ), place * (BATCH * 2));
+    };
+    auto turn = [&](Batch &b) __attribute__((always_inline)) {
+        if (b.what & FRESH) {
+            wait_vmem<(RING - 1) * OPS>();
+            asm volatile("s_barrier" ::: "memory");
+            if (to_copy > 0) copy_block();
+        }
+        const int left = (int)(b.what >> LEFT & 63u);
+        if (left > 0) multiply(b, left);
+        request_at(b, (uint32_t)__builtin_amdgcn_readlane(plan, ++ahead_j));
+    };
+
+    const int all_steps = WIDE ? (steps + 1) & ~1 : steps;   // steps of `step` and `filtered` go in pairs; the odd one past the end has no list
 
     // ---- The same for an A whose columns are zero in all rows of the tile here and there (whole columns switched off, by
     // context, for some rows or for all): the k of such columns are left out of the lists.  The wave makes the list of a step
@@ -540,7 +572,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         int n = prepare(chunk_begin);
         if (n > 0) fetch(S0, chunk_begin, 0);
         if (n > BATCH) fetch(S2, chunk_begin, 1);
-        for (int i = 0; i < even_steps; i += 2) {
+        for (int i = 0; i < all_steps; i += 2) {
             n = one(chunk_begin + i, n, S0, S1);
             n = one(chunk_begin + i + 1, n, S1, S0);
         }
@@ -558,8 +590,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         // copies, so that there is one round trip in front of the first step instead of three (4096^3, p = .4: 359 -> 348 us;
         // where two workgroups share a compute unit it makes no difference).
         uint32_t marks = 0, first_lengths = 0;
-        if constexpr (PARTED) {
+        if constexpr (!WIDE) {
             first_lengths = lengths(chunk_begin);
+            request_at(B0, (uint32_t)chunk_begin * PER_STEP);
+        }
+        if constexpr (PARTED) {
             for (int64_t i = lane; i < p.KBA; i += 64) marks |= p.a_wild[tile_m * p.KBA + i];
             asm volatile("" ::: "memory");
         }
@@ -568,9 +603,12 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             if (to_copy > 0) copy_block();
         if constexpr (!PARTED)
             for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
-        request(B0, off_v, off_l);
-        request(B1, off_v + SEGB, off_l + SEG_L);
-        wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
+        if constexpr (WIDE) {
+            request(B0, off_v, off_l);
+            request(B1, off_v + SEGB, off_l + SEG_L);
+            wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
+        }
+        asm volatile("" : "+v"(first_lengths));   // waited for here, not earlier
         bool filter = false;
         if constexpr (FILTER) {   // does it pay here?  slots listed in some steps, and those that would stay
             uint32_t all = 0, stay = 0;
@@ -616,25 +654,71 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             }
             __syncthreads();
         }
-        bool first = true;
-        for (int done = 0; done < even_steps; done += 62) {
-            uint32_t counts = PARTED && done == 0 ? first_lengths : lengths(chunk_begin + done);
-            if constexpr (PARTED) {
-                if (a_marked && done + lane < chunk_end - chunk_begin) counts |= step_marks[(done + lane) >> 5] << (31 - ((done + lane) & 31)) & 0x80000000u;
-                some_marked |= __ballot((int)counts < 0) != 0;
-                counts = (int)counts < 0 ? 0u : counts;
+        if constexpr (WIDE) {
+            bool first = true;
+            for (int done = 0; done < all_steps; done += 62) {
+                uint32_t counts = lengths(chunk_begin + done);
+                asm volatile("" : "+v"(counts));   // waited for here
+                if (first && (int)__builtin_amdgcn_readlane(counts, 0) > BATCH) request(B2, off_v + BATCH_V, off_l + BATCH_L);
+                first = false;
+                const int here = min(62, all_steps - done);
+                int n = (int)__builtin_amdgcn_readlane(counts, 0);
+                for (int i = 0; i < here; i += 2) {
+                    const int n1 = (int)__builtin_amdgcn_readlane(counts, i + 1), n2 = (int)__builtin_amdgcn_readlane(counts, i + 2);
+                    step(n, n1, B0);
+                    step(n1, n2, B1);
+                    n = n2;
+                }
             }
-            asm volatile("" : "+v"(counts));   // waited for here
-            if (first && (int)__builtin_amdgcn_readlane(counts, 0) > BATCH) request(B2, off_v + BATCH_V, off_l + BATCH_L);
-            first = false;
-            const int here = min(62, even_steps - done);
-            int n = (int)__builtin_amdgcn_readlane(counts, 0);
-            for (int i = 0; i < here; i += 2) {
-                const int n1 = (int)__builtin_amdgcn_readlane(counts, i + 1), n2 = (int)__builtin_amdgcn_readlane(counts, i + 2);
-                step(n, n1, B0);
-                step(n1, n2, B1);
-                n = n2;
-            }
+        } else {
+            // The next 64 batches, from the lengths n of the steps from `from` on (lane i: step i), `skip` batches of the first
+            // left out: lane j finds the step of batch j as the last one that begins no later.
+            auto window = [&](uint32_t n, int from, int skip) __attribute__((always_inline)) {
+                if constexpr (PARTED) {
+                    if (a_marked && from + lane < chunk_end - chunk_begin) n |= step_marks[(from + lane) >> 5] << (31 - ((from + lane) & 31)) & 0x80000000u;
+                    some_marked |= __ballot((int)n < 0) != 0;
+                    n = (int)n < 0 ? 0u : n;
+                }
+                const int batches = max(((int)n + BATCH - 1) / BATCH, 1) - (lane == 0 ? skip : 0);
+                // (sums and ors over the lanes before, in the vector registers)
+                auto across = [](uint32_t v, auto op) __attribute__((always_inline)) {
+                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));    // row_shr 1, 2, 4, 8
+                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast 15, 31
+                    return op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+                };
+                const uint32_t begin = across((uint32_t)batches, [](uint32_t a, uint32_t b) { return a + b; }) - (uint32_t)batches;
+                const auto either = [](uint32_t a, uint32_t b) { return a | b; };
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(across(begin < 32 ? 1u << begin : 0u, either), 63);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(begin >= 32 && begin < 64 ? 1u << (begin - 32) : 0u, either), 63);
+                const uint64_t begun = ((uint64_t)hi << 32 | lo) & (~0ull >> (63 - lane));   // (bit 0 is set)
+                const int i = __popcll(begun) - 1, batch = lane - (63 - __builtin_clzll(begun)) + (i == 0 ? skip : 0);
+                const int left = min((int)__shfl(n, i, 64) - batch * BATCH, BATCH);
+                const uint32_t place = (uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch;
+                plan = from + i < all_steps ? (batch == 0 ? FRESH : 0u) | (uint32_t)max(left, 0) << LEFT | place : PAST | place;
+                asm volatile("" : "+v"(plan));   // waited for here
+                ahead_j = 0;
+            };
+            window(first_lengths, 0, 0);
+            B0.what = (uint32_t)__builtin_amdgcn_readlane(plan, 0) & ~FRESH;   // (begun here)
+            request_at(B1, (uint32_t)__builtin_amdgcn_readlane(plan, 1));
+            request_at(B2, (uint32_t)__builtin_amdgcn_readlane(plan, 2));
+            ahead_j = 2;
+            wait_vmem<2 * OPS>();   // the blocks so far have landed
+            asm volatile("s_barrier" ::: "memory");
+            if (to_copy > 0) copy_block();
+            do {
+                turn(B0);
+                turn(B1);
+                turn(B2);
+                if (ahead_j > 60) {
+                    const uint32_t place = B2.what & PLACE;
+                    const int step = (int)(place / PER_STEP);
+                    window(lengths(step), step - chunk_begin, (int)(place % PER_STEP));
+                }
+            } while ((int)B0.what >= 0);
         }
         if constexpr (PARTED) {
             if (some_marked && active) {   // the marked steps, as floats from X and Y.  Seldom: no more than correct.
@@ -679,7 +763,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 for (int r = 0; r < RT; ++r) acc[g][r] += rest[g][r];
         }
     } else if (KS > 1) {   // no step left for this range of K: only the barriers of the others
-        for (int i = 0; i < even_steps; ++i) asm volatile("s_barrier" ::: "memory");
+        for (int i = 0; i < all_steps; ++i) asm volatile("s_barrier" ::: "memory");
     }
     __syncthreads();   // the rings are free: what follows reuses them
     if constexpr (KS > 1) {   // sums of the later ranges of K, added in order
