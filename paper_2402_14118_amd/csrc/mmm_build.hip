@@ -484,7 +484,7 @@ struct BShared {
     uint8_t gbits[64][BUILD_WAVES];   // [lane][wave]: rows in which the lane's 16-column group is occupied
     uint8_t bbits[64][BUILD_WAVES];   // the same for the lane's block, where that is another set (8-wide blocks)
     __align__(16) uint16_t list[16][SEG];
-    char pack[16 * (SEG * MMM_GROUP_COLS * 2 + 16)];   // 16-bit types: the packed groups
+    __align__(16) char pack[16 * (SEG * MMM_GROUP_COLS * 2 + 16)];   // 16-bit types: the packed groups
     int32_t kk[SEG];                  // row-compacted mode: the rows behind the segment's k' (-1: none)
     uint32_t sums[BUILD_WAVES];
 };
@@ -759,35 +759,36 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
             if (lane == 0) p.bp_cnt[CG * p.KBA + seg] = n_out | (wild ? 0x80000000u : 0u);
         }
     } else {
-        // Composed in LDS in the order of mmm_value_pos; the slots that fill up the last batch are zero.  Whole batches are
-        // copied out, 1 KiB each.
-        constexpr int GROUPB = SEG * MMM_GROUP_COLS * ESZ + 16;     // bytes per group (4 banks apart)
-        constexpr uint32_t SLOTS = 32;                            // per batch
-        static_assert(B_GROUPS * GROUPB <= (int)sizeof(sh.pack), "room for the groups");
-        uint16_t *g = reinterpret_cast<uint16_t *>(sh.pack + (lane / LPG) * GROUPB);
-        auto put = [&](uint32_t slot, u32x2 v) {
-            uint16_t *at = g + mmm_value_pos(ESZ, slot, (uint32_t)(lane & 3) * 4u);
-            at[0] = (uint16_t)v.x;
-            at[8] = (uint16_t)(v.x >> 16);
-            at[16] = (uint16_t)v.y;
-            at[24] = (uint16_t)(v.y >> 16);
-        };
-        constexpr int TPG = BUILD_THREADS / B_GROUPS;   // threads per group
-        const int cg = threadIdx.x / TPG;
-        const int64_t CG = ct * B_GROUPS + cg;
-        const uint64_t *bits = reinterpret_cast<const uint64_t *>(sh.gbits[cg * LPG]);
-        const uint32_t batches = ((uint32_t)(__popcll(bits[0]) + __popcll(bits[1])) + SLOTS - 1u) / SLOTS;
-        char *cval = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * ESZ);
+        // The occupied rows go to LDS one after another, zeros behind them up to a whole batch, and come out through the
+        // transposing read, which yields four slots of a column to a lane: two of them are a lane's part of a batch in the
+        // order of mmm_value_pos.  One LDS write per row; put in place element by element it took four, and a workgroup of B was
+        // bound by them (512^3, p = .4, bf16: both sides 5.9 -> 5.0 us, 4096^2, p = .2: 23.2 -> 22.4).
+        constexpr uint32_t SLOTS = 32, ROWB = MMM_GROUP_COLS * ESZ;   // per batch; bytes per row
+        constexpr int GROUPB = SEG * ROWB + 16;                       // bytes per group (4 banks apart)
+        static_assert(B_GROUPS * GROUPB <= (int)sizeof(sh.pack) && B_GROUPS == BUILD_WAVES, "room for the groups, and a wave for each");
+        char *const mine = sh.pack + (lane / LPG) * GROUPB + (lane % LPG) * 8;
 #pragma unroll
         for (int j = 0; j < B_ROWS; ++j)
-            if ((gb >> j) & 1u) put(slots[j], u32x2{raw[j].x, raw[j].y});
+            if ((gb >> j) & 1u) *reinterpret_cast<u32x2 *>(mine + slots[j] * ROWB) = u32x2{raw[j].x, raw[j].y};
 #pragma unroll
         for (uint32_t i = 0; i < SLOTS; i += BUILD_WAVES)
-            if (n + i + wave < ((n + SLOTS - 1) & ~(SLOTS - 1))) put(n + i + wave, u32x2{0, 0});
+            if (n + i + wave < ((n + SLOTS - 1) & ~(SLOTS - 1))) *reinterpret_cast<u32x2 *>(mine + (n + i + wave) * ROWB) = u32x2{0, 0};
         __syncthreads();
-        if (CG < p.NG)
-            for (uint32_t q = threadIdx.x % TPG; q < batches * 64; q += TPG)
-                *reinterpret_cast<uint4 *>(cval + q * 16) = *reinterpret_cast<const uint4 *>(sh.pack + cg * GROUPB + q * 16);
+        const int64_t CG = ct * B_GROUPS + wave;   // the group this wave takes out
+        if (CG < p.NG) {
+            typedef short shortx4 __attribute__((ext_vector_type(4)));
+            typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+            typedef __attribute__((address_space(3))) char lds_char;
+            const uint32_t n_out = (uint32_t)__builtin_amdgcn_readlane((int)n, wave * LPG);
+            // (slot lane / 4 and four of its columns: lane c of 16 gets column c of those four slots)
+            lds_char *const in = (lds_char *)sh.pack + wave * GROUPB + (lane >> 2) * ROWB + (lane & 3) * 8;
+            char *const out = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * ROWB) + lane * 16;
+            for (uint32_t q = 0; q < n_out; q += SLOTS) {
+                const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(in + q * ROWB)));
+                const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(in + (q + 16) * ROWB)));
+                *reinterpret_cast<u32x4 *>(out + q * ROWB) = u32x4{lo.x, lo.y, hi.x, hi.y};
+            }
+        }
     }
     {   // the lists, one word per thread
         const int64_t LG = ct * B_GROUPS + (threadIdx.x >> 6);
