@@ -197,11 +197,15 @@ double matrix_cost(const mmm_maps *m, int32_t dt, int32_t form, const MatrixProb
 // eighth of T tiles in panels of w columns is about T / w rows by w columns: least for w = sqrt(T * a / b), with a and b
 // the bytes of one row and one column tile.  (512 x 8192 x 4096 bf16, p = .1: one row and all of B per XCD, 143 MB in all
 // against 67, and 27.8 -> 22.7 us; columns bf16 2048 x 1638 of 16384 x 4096 46.2 -> 42.5.)
+// Of a long eighth it is the 32 tiles or so under way at a time that have to find their rows and columns in the L2: what
+// earlier ones fetched does not stay (4096^3, a column tile of packed B is 4 MB).  Width 6 instead of all 16: bf16, p = .05,
+// 64.9 -> 56.9 us, .4 99.5 -> 98.1; floats p = .05 89.1 -> 87.5, .2 239 -> 236.7, in parts .4 311 -> 307.  With 64 tiles
+// 57.6, 89.2 and 237.0, with 16 57.0, 88.4 and 237.4 and the columns above 37.2 instead of 36.
 int32_t panel_width(const mmm_maps *m, int32_t dt, int32_t form, const MatrixProblem &q, const mmm_plan &p)
 {
     const double batch = elem_size(dt) == 2 || form == MMM_FORM_PARTS ? 32.0 : 16.0;
     const double a = (double)(MMM_AB_ROWS * MMM_AB_COLS), b = (double)mmm_variant(p.variant).TN * q.batches * batch;   // elements per step
-    const double t = std::max(1.0, (double)p.tiles_m * p.tiles_n / 8.0);
+    const double t = std::max(1.0, std::min((double)p.tiles_m * p.tiles_n / 8.0, 32.0));
     const int64_t panels = std::max<int64_t>(1, (int64_t)((double)p.tiles_n / std::sqrt(t * a / b) + 0.5));   // of about equal width
     return (int32_t)std::max<int64_t>(1, (p.tiles_n + panels - 1) / panels);
 }
