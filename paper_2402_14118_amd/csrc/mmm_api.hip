@@ -110,6 +110,9 @@ size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 // a dozen splits.  What is chosen from them, against other random problems (profiles/kernel_choice.txt): the kernel takes 1 % longer
 // than the faster one in the mean, 1 to 3 % where A keeps .2 to 5 % of its elements, outside the fit (a rule of thresholds fitted to
 // 4096^3 floats decided there before: 5 % floats, 7 % doubles, 22 % 16-bit); the tile and split 1 % (16-bit) to 3 % longer than the best.
+// The 2-byte row is from 700 problems (65 to 4096 rows, K to 16384, N to 8192) after the kernel took its batches from one queue, and
+// scaled to lie above timings as the others do: tile and split 1.4 % longer than the best on 700 others, 19 % at worst; with the
+// row from before, whose waiting per step is twice as long, 3.3 and 51 % (512 x 8192 x 4096, p = .1: 24.0 -> 21.9 us).
 // The estimates themselves lie 10 to 25 % from back-to-back timings, mostly above, which hide the launch.
 struct MatrixCost {   // microseconds
     double launch;        // per call
@@ -123,7 +126,7 @@ struct MatrixCost {   // microseconds
     double image_giga;    // per 10^9 bytes of A copied to LDS
 };
 constexpr MatrixCost kMatrixCost[4] = {   // 2-, 4-, 8-byte elements, floats in parts
-    {3.162, 0.2208, 0.0321, 0.0011, 0.1084, 0.571, 2.0, 1.094, 47.1},
+    {2.936, 0.0995, 0.0371, 0.0032, 0.0971, 0.866, 2.67, 1.241, 34.4},
     {3.524, 0.1805, 0.1198, 0.0031, 0.0747, 0.561, 2.0, 1.159, 24.9},
     {3.210, 0.3107, 0.4623, 0.0059, 0.1092, 1.362, 3.3, 2.257, 30.9},
     {3.210, 0.0308, 0.0266, 0.0139, 0.0, 1.607, 2.42, 1.661, 20.2},
