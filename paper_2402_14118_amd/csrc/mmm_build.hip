@@ -194,7 +194,7 @@ template <typename T> struct ABlock {   // one block in a wave's registers: lane
 // several (columns 2048 x 16384: 28 -> 26 us for A, 41 -> 35.4 with B; with one or two blocks per workgroup the loads past
 // the last one cost more than they gain, 6.6 -> 9 us for 512 x 8192, and so do more bytes in flight for the wider types).
 template <typename T, int TEST, bool ROWS, bool DEEP>
-__device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0, int64_t bi1, int lane, int wave, AShared &sh)
+__device__ __forceinline__ void scan_a(ConstParams &p0, int32_t bj, int32_t bi0, int32_t bi1, int lane, int wave, AShared &sh)
 {
     ConstParams &p = reread(p0);
     typedef typename Pattern<sizeof(T)>::type pattern;
@@ -209,7 +209,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
     constexpr bool compact = ROWS;
     // Buffer resources that end with the last row: what lies past it, and lanes past the last column, reads as +0, which
     // is never kept, and is not stored.  64 rows are at most 2^31 bytes (leading dimensions are below 2^22).
-    const int64_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;
+    const int32_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;   // (K < 2^22)
     const int tail = (int)min(p.K - k_lo, (int64_t)A_COLS);   // columns of these blocks that exist
     const uint32_t row_bytes = (uint32_t)p.ldx * ESZ, map_bytes = (uint32_t)p.WA * 8u;
     const uint32_t row0 = WIDE_IMG ? (uint32_t)wave : (uint32_t)wave * A_ROWS;
@@ -220,14 +220,17 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
     const uint32_t map_at = lane < A_ROWS * A_WORDS && w_lo + lane % A_WORDS < p.WA
                                 ? (row0 + ROW_STEP * (uint32_t)(lane / A_WORDS)) * map_bytes + (uint32_t)(lane % A_WORDS) * 8u
                                 : OUTSIDE;
-    auto rows_at = [&](int64_t bi) -> uint32_t { return (uint32_t)min(p.M - bi * MMM_AB_ROWS, (int64_t)MMM_AB_ROWS); };
-    auto map_rsrc = [&](const uint64_t *map, int64_t bi, bool any) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(map + bi * MMM_AB_ROWS * p.WA + w_lo), 0,
+    auto rows_at = [&](int32_t bi) -> uint32_t { return (uint32_t)min((int32_t)p.M - bi * MMM_AB_ROWS, MMM_AB_ROWS); };   // (M is at most 2^30)
+    // Per block, of some 125 scalar instructions for each of sixteen waves: 32 by 32 bits are two of them, 64 by 64 were six, and
+    // comparisons of 64 bits left the scalar unit (2048 x 16384, columns, bf16: A 25.3 -> 22.2 us; 2048^2 floats 7.8 -> 7.5).
+    auto block_rows = [](int32_t bi, uint32_t row) -> uint64_t { return (uint64_t)(uint32_t)bi * (row * MMM_AB_ROWS); };   // bytes up to block row bi
+    auto map_rsrc = [&](const uint64_t *map, int32_t bi, bool any) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(map) + block_rows(bi, map_bytes) + w_lo * 8), 0,
                                                  any ? (int)(rows_at(bi) * map_bytes - (uint32_t)w_lo * 8u) : 0, 0x00020000);
     };
     // DEEP: always the same number of loads, so that waiting for one block's does not mean waiting for the next one's: where
     // there is no block or no keep bitmap the buffer is empty.
-    auto load = [&](int64_t bi, ABlock<T> &r) __attribute__((always_inline)) {
+    auto load = [&](int32_t bi, ABlock<T> &r) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         const bool there = bi < bi1;
         r.kw = 0;
@@ -236,7 +239,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             r.kw = (uint64_t)k.y << 32 | k.x;
         }
         const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<T *>(static_cast<const T *>(p.X) + bi * MMM_AB_ROWS * p.ldx + k_lo), 0,
+            const_cast<char *>(static_cast<const char *>(p.X) + block_rows(bi, row_bytes) + k_lo * ESZ), 0,
             there ? (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)) : 0, 0x00020000);
 #pragma unroll
         for (int t = 0; t < A_ROWS; ++t) {
@@ -276,7 +279,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
         }
     }
-    auto block = [&](int64_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
+    auto block = [&](int32_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
         ConstParams &p = reread(p0);
         constexpr int AHEAD = decltype(ahead)::value;   // the block whose loads take this one's place
         char *const stage = sh.stage[PARTED ? 0 : st];
@@ -412,7 +415,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             uint32_t lo = (uint32_t)any, hi = (uint32_t)(any >> 32);
             lo = or_lanes<16>(lo);
             hi = or_lanes<16>(hi);
-            const int64_t tile = bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
+            const int64_t tile = (int64_t)bi * (MMM_AB_ROWS / MMM_COLANY_ROWS) + t32;
             if ((lane & 15) == 0 && tile < p.MT && h < A_WORDS && w_lo + h < p.WA) p.a_colany[tile * p.WA + w_lo + h] = ((uint64_t)hi << 32) | lo;
             if constexpr (PARTED) {
                 const uint64_t wild = ballot64(sh.wild[st][lane & 15] != 0);
@@ -424,14 +427,14 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
             base = 0;
             for (int w = 0; w < BUILD_WAVES; ++w) base += sh.before[w];
         }
-        char *img = p.a_img + ((size_t)bi * p.KBA * MMM_AB_COLS + base) * (UNITS * 16);
+        char *img = p.a_img + (uint64_t)(uint32_t)bi * ((uint32_t)p.KBA * (MMM_AB_COLS * UNITS * 16)) + (uint64_t)base * (UNITS * 16);
         auto stage_of = [&](int k, int unit, uint32_t col) -> int {   // where unit `unit` of image column `col` waits in the stage
             // (16-bit: undo the rotation of the stage, apply that of the image, see mmm_img_swizzle)
             return WIDE_IMG ? k * (UNITS * 16) + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
         };
         if constexpr (PARTED) {
             if (compact) {
-                char *const blocks = p.a_img + (size_t)bi * p.KBA * MMM_BLOCK_PARTS_BYTES;
+                char *const blocks = p.a_img + (uint64_t)(uint32_t)bi * ((uint32_t)p.KBA * MMM_BLOCK_PARTS_BYTES);
                 for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
                     const int j = q / UNITS, k = (int)sh.live[j];
                     const uint32_t col = base + (uint32_t)j;
@@ -464,12 +467,12 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int64_t bj, int64_t bi0,
         }
     };
     if constexpr (DEEP) {
-        for (int64_t bi = bi0; bi < bi1; bi += 2) {
+        for (int32_t bi = bi0; bi < bi1; bi += 2) {
             block(bi, even, 0, std::integral_constant<int, 2>{});
             if (bi + 1 < bi1) block(bi + 1, odd, 1, std::integral_constant<int, 2>{});
         }
     } else {
-        for (int64_t bi = bi0; bi < bi1; ++bi) block(bi, even, (int)(bi - bi0) & 1, std::integral_constant<int, 1>{});
+        for (int32_t bi = bi0; bi < bi1; ++bi) block(bi, even, (int)(bi - bi0) & 1, std::integral_constant<int, 1>{});
     }
 }
 
