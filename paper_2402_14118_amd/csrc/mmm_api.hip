@@ -341,8 +341,8 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
 
 // The form a build gives floats: that of the side it does not build (the kernel takes both from one form), that of a captured
 // call, or the one with which build and multiplication are estimated to take less; without counts the plain one.  Parts pay
-// for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 426 + 40 and 348 + 57 us, .2 240 + 34 and
-// 189 + 43, .1 139 + 31 and 169 + 39 (a list of 13 fills 40 % of a batch).
+// for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 432 + 39 and 326 + 56 us, .2 237 + 34 and
+// 190 + 43, .1 139 + 31 and 157 + 39 (a list of 13 fills 40 % of a batch).
 int32_t choose_form(mmm_maps *m, const mmm_build_args &a, bool capture)
 {
     if (a.dtype != MMM_F32 || m->M <= 64) return MMM_FORM_PLAIN;

@@ -27,11 +27,11 @@
 //
 // Floats whose lists are long are multiplied in three bf16 parts (FloatParts; see MMM_PARTS in mmm_internal.h and choose_form):
 // six 16-bit matrix instructions for 32 listed k take 100 cycles where the eight float instructions take 261.  A block of A
-// is half as large again, so a ring of two leaves room for one workgroup of 16 waves on a compute unit.  4096^3 p = .4: 426 -> 348 us
-// (matrix cores 55 % and LDS 50 % busy, clock 1.9 GHz), p = .2: 240 -> 189 us.  What is left is that between two barriers all
-// waves read from LDS first and multiply then.  Tried, and no faster: a third block in the ring, with the copies two steps ahead
-// (167 -> 181 us at p = .1) or the first operands read before the barrier (175); units of 32 slots as one stream over the steps, three
-// of them on their way (p = .1 182, p = .4 338); two lists per wave in turns, eight waves (237 and 378).
+// is half as large again, so a ring of two leaves room for one workgroup of 16 waves on a compute unit.  4096^3, p = .4: 426 ->
+// 310 to 326 us (matrix cores 55 % and LDS 50 % busy, clock 1.9 GHz), p = .2: 240 -> 185.  What is left is that between two barriers
+// all waves read from LDS first and multiply then, and that a quarter of the slots fill up last batches.  Tried, and no faster: a third
+// block in the ring, with the copies two steps ahead (167 -> 181 us at p = .1) or the first operands read before the barrier (175); two
+// lists per wave in turns, eight waves (237 and 378).
 //
 // What bounds it otherwise: dense lists, the matrix cores (4096^3 fp32, p = .4: 437 us, of which 360 are matrix instructions at
 // the rate a large product reaches); sparse ones, whose steps are one short batch, the compute unit's scalar unit and vector-memory issue,
