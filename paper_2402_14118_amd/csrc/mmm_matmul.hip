@@ -608,7 +608,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             request(B1, off_v + SEGB, off_l + SEG_L);
             wait_vmem<2 * OPS>();   // the blocks so far have landed (the waits of the first steps could not count on enough loads)
         }
-        asm volatile("" : "+v"(first_lengths));   // waited for here, not earlier
+        if constexpr (!WIDE) asm volatile("" : "+v"(first_lengths));   // waited for here, not earlier
         bool filter = false;
         if constexpr (FILTER) {   // does it pay here?  slots listed in some steps, and those that would stay
             uint32_t all = 0, stay = 0;
