@@ -200,8 +200,10 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 
     // Splits of K one after another, the tiles of each in panels of `panel` tile columns (see panel_width).
     // (Divisions run on the vector ALU; the results are put back where addresses are formed.)
-    const uint32_t L = xcd_contiguous_id(blockIdx.x, gridDim.x);
+    // (The number of workgroups is worked out: the launch's own word for it lies behind all arguments, a cache line on.  512 x 8192 x
+    // 4096 bf16, the pass: 27.66 -> 27.34 us.)
     const uint32_t tiles = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n, in_panel = (uint32_t)p.tiles_m * (uint32_t)p.panel;
+    const uint32_t L = xcd_contiguous_id(blockIdx.x, tiles * (uint32_t)p.split_k);
     const int split = __builtin_amdgcn_readfirstlane((int)(p.split_k > 1 ? L / tiles : 0u));
     const uint32_t t = L - (uint32_t)split * tiles, n0 = t / in_panel * (uint32_t)p.panel;
     const uint32_t width = min((uint32_t)p.panel, (uint32_t)p.tiles_n - n0), u = t - n0 * (uint32_t)p.tiles_m, row = u / width;
