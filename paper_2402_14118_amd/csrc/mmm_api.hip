@@ -770,8 +770,8 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
         }
         partial_bytes = (size_t)MMM_STATIC_SCRATCH_BYTES;
     }
-    if (hipError_t e = mmm_launch_matmul(maps, p, dt, X, ldx, Y, ldy, C, ldc, accumulate ? 1 : 0, partials,
-                                         partial_bytes, static_cast<hipStream_t>(hip_stream));
+    if (hipError_t e = mmm_launch_matmul(maps, p, dt, C, ldc, accumulate ? 1 : 0, partials, partial_bytes,
+                                         static_cast<hipStream_t>(hip_stream));
         e != hipSuccess) {
         note_device_error("masked GEMM launch", e);
         return MMM_ERR_DEVICE;

@@ -735,21 +735,24 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
             const char *const ycol = static_cast<const char *>(p.Y) + (CG * MMM_GROUP_COLS + c) * ESZ;
             char *out = p.bp_val + (size_t)(CG * p.KBA + seg) * (SEG * MMM_GROUP_COLS * LSZ) + lane * 16;
             const uint8_t *const block_rows = sh.bbits[wave * LPG + (c >= 8u ? LPB : 0)];   // of this lane's half of the group, if it is one
-            OutOfRange range;
+            bool wild = false;
 #pragma unroll 1
             for (uint32_t slot = 4u * s4; (int)(slot - 4u * s4) < (int)n_out; slot += 32, out += MMM_PARTS * 1024) {
+                auto value = [&](uint32_t entry, uint32_t at) __attribute__((always_inline)) -> uint32_t {
+                    const uint32_t k = (entry >> 3) & (SEG - 1u);   // see mmm_list_entry
+                    bool there = at < n_out && col_ok;
+                    if (SPLIT) there = there && ((block_rows[k / 8] >> (k % 8)) & 1u);
+                    const int64_t row = ROWS ? (int64_t)sh.kk[k] : seg * SEG + k;
+                    return there ? *reinterpret_cast<const uint32_t *>(ycol + row * row_bytes) : 0u;
+                };
                 const u32x4 entries = *reinterpret_cast<const u32x4 *>(&sh.list[wave][mmm_list_pos(LSZ, slot)]);
                 uint32_t v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {   // slot + 16 (i / 4) + i % 4
-                    const uint32_t k = (entries[i % 4] >> (i / 4 * 16 + 3)) & (SEG - 1u);   // see mmm_list_entry
-                    bool there = slot + (uint32_t)(i / 4 * 16 + i % 4) < n_out && col_ok;
-                    if (SPLIT) there = there && ((block_rows[k / 8] >> (k % 8)) & 1u);
-                    const int64_t row = ROWS ? (int64_t)sh.kk[k] : seg * SEG + k;
-                    v[i] = there ? *reinterpret_cast<const uint32_t *>(ycol + row * row_bytes) : 0u;
-                }
+                for (int i = 0; i < 8; ++i) v[i] = value(entries[i % 4] >> (i / 4 * 16), slot + (uint32_t)(i / 4 * 16 + i % 4));
+                OutOfRange here;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) range.see(v[i]);
+                for (int i = 0; i < 8; ++i) here.see(v[i]);
+                const bool odd = ballot64(here.any()) != 0;
 #pragma unroll
                 for (int q = 0; q < MMM_PARTS; ++q) {
                     u32x4 part;
@@ -757,8 +760,19 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
                     for (int i = 0; i < 4; ++i) part[i] = take_part(v[2 * i], v[2 * i + 1]);
                     *reinterpret_cast<u32x4 *>(out + q * 1024) = part;
                 }
+                if (odd) {   // seldom: such elements as they are, read once more
+                    wild = true;
+#pragma unroll 1
+                    for (uint32_t i = 0; i < 8; ++i) {
+                        const uint32_t at = slot + i / 4 * 16 + i % 4, bits = value(sh.list[wave][mmm_list_pos(LSZ, at)], at);
+                        if (!out_of_range(bits)) continue;
+                        uint16_t *const to = reinterpret_cast<uint16_t *>(out) + i;
+                        to[0] = (uint16_t)(bits >> 16);
+                        to[512] = (uint16_t)bits;
+                        to[1024] = MMM_PARTS_RAW;
+                    }
+                }
             }
-            const bool wild = ballot64(range.any()) != 0;
             if (lane == 0) p.bp_cnt[CG * p.KBA + seg] = n_out | (wild ? 0x80000000u : 0u);
         }
     } else {
@@ -926,11 +940,7 @@ __global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_im
         const int r = __builtin_ctzll(m);
         uint32_t bits;
         if constexpr (Layout<T>::PARTED) {
-            uint16_t part[MMM_PARTS];
-            for (int q = 0; q < MMM_PARTS; ++q)
-                part[q] = *reinterpret_cast<const uint16_t *>(a_img + (size_t)b * MMM_BLOCK_PARTS_BYTES + q * MMM_PART_BYTES + c * 128 + mmm_img_row(2, (uint32_t)kc, (uint32_t)r));
-            auto value = [&](int q) { return __uint_as_float((uint32_t)part[q] << 16); };
-            bits = part[2] == MMM_PARTS_RAW ? (uint32_t)part[0] << 16 | part[1] : __float_as_uint(value(0) + (value(1) + value(2)));
+            bits = __float_as_uint(mmm_whole_float(a_img + (size_t)b * MMM_BLOCK_PARTS_BYTES + c * 128 + mmm_img_row(2, (uint32_t)kc, (uint32_t)r), MMM_PART_BYTES));
         } else {
             bits = f32_bits<T>(*reinterpret_cast<const T *>(col + mmm_img_row(sizeof(T), (uint32_t)kc, (uint32_t)r)));
         }

@@ -64,7 +64,8 @@ __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t
 // of accumulators and the others, 2^-8 of them and less, in another, so that the sums round seldom: 2-norm of the error over 256 to 4096 terms
 // 0.5 to 2.9e-7, of the float instruction 1.2 to 7.4e-7.  32 k of a row tile take 6 instructions of 16.7 cycles instead of 8 of 32.6.
 // An element outside [2^-110, 2^55) is not held exactly (or its cross products could overflow where the product does not; infinities and NaN are among
-// them): a block of A and a segment of a group of B that have one are marked, and are multiplied as floats from X and Y.
+// them): its three parts hold its bits instead (MMM_PARTS_RAW), a block of A and a segment of a group of B that have one are marked,
+// and are multiplied as floats, put together again (mmm_whole_float).
 // Image: [block of 64 x 128][part][column][64 rows], columns as of the 16-bit types.  Packed B: batches of 32 slots as of the
 // 16-bit types, [batch][part].  As an "element size": 6.
 constexpr int MMM_PARTS = 3;
@@ -72,7 +73,14 @@ constexpr size_t MMM_PARTS_ESZ = 2 * MMM_PARTS;
 constexpr uint32_t MMM_PARTS_LO = (127 - 110) << 23, MMM_PARTS_HI = (127 + 55) << 23;   // bit patterns of the bounds
 constexpr uint32_t MMM_PART_BYTES = MMM_AB_ROWS * MMM_AB_COLS * 2;                      // of a block of A
 constexpr uint32_t MMM_BLOCK_PARTS_BYTES = MMM_PARTS * MMM_PART_BYTES;
-constexpr uint16_t MMM_PARTS_RAW = 0xffffu;   // as the third part: the first two are the bits of the element as it is (a marked block's)
+constexpr uint16_t MMM_PARTS_RAW = 0xffffu;   // as the third part (no rest is a NaN): the first two are the bits of the element as it is
+// the element behind three parts `step` bytes from each other
+__device__ inline float mmm_whole_float(const char *at, size_t step)
+{
+    auto part = [&](int q) -> uint32_t { return *reinterpret_cast<const uint16_t *>(at + q * step); };
+    const uint32_t p0 = part(0), p1 = part(1), p2 = part(2);
+    return p2 == MMM_PARTS_RAW ? __uint_as_float(p0 << 16 | p1) : __uint_as_float(p0 << 16) + (__uint_as_float(p1 << 16) + __uint_as_float(p2 << 16));
+}
 enum { MMM_FORM_PLAIN = 0, MMM_FORM_PARTS = 1 };
 // col: ring column (mmm_zero_col for the zero column: a multiple of 8, so the rotation is nil)
 __host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
@@ -250,8 +258,7 @@ hipError_t mmm_launch_lists(const mmm_maps *m, hipStream_t s);
 int32_t mmm_variant_count();
 const mmm_variant_info &mmm_variant(int32_t i);
 // partials / partial_bytes: where the split-K partial sums go (used only when p.split_k > 1)
-// X, Y (with their leading dimensions): read for marked blocks of floats in parts only
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, const void *X, int64_t ldx, const void *Y, int64_t ldy, void *C, int64_t ldc, int32_t accumulate, void *partials,
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &p, int32_t dtype, void *C, int64_t ldc, int32_t accumulate, void *partials,
                              size_t partial_bytes, hipStream_t s);
 // The multiplication over exactly the surviving products, on the vector ALUs.  fused: evaluate M
 // (pred, threshold, keep_a) on X inside the kernel; otherwise a_bits of the maps are used.

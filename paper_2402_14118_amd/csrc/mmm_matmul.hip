@@ -73,11 +73,7 @@ struct MatmulParams {
     const uint64_t *a_colany;   // column-any words of A, over k
     const uint32_t *kmap;       // row-compacted mode: k' -> k
     int64_t NB, WA, MT;
-    // floats in parts: the marks of the blocks of A, and what marked blocks and segments are multiplied from
-    const uint8_t *a_wild;
-    const uint64_t *a_bits, *b_bits;
-    const float *X, *Y;
-    int64_t ldx, ldy, WB;
+    const uint8_t *a_wild;      // floats in parts: the marks of the blocks of A
 };
 struct FloatParts { uint16_t part[MMM_PARTS]; };   // element type of floats in parts
 
@@ -723,7 +719,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             } while ((int)B0.what >= 0);
         }
         if constexpr (PARTED) {
-            if (some_marked && active) {   // the marked steps, as floats from X and Y.  Seldom: no more than correct.
+            if (some_marked && active) {   // the marked steps, as floats put together again.  Seldom: no more than correct.
 #pragma unroll 1
                 for (int ch = chunk_begin; ch < chunk_end; ++ch) {
                     uint32_t m = cnt0[ch];
@@ -732,24 +728,23 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     if (a_marked) m |= step_marks[(ch - chunk_begin) >> 5] << (31 - ((ch - chunk_begin) & 31)) & 0x80000000u;
                     if ((int)m >= 0) continue;
                     const uint16_t *const list = p.bp_list + (Gc * p.KBA + ch) * KC;
+                    const char *const block = p.a_img + ((size_t)tile_m * p.KBA + ch) * SLAB;   // (rows past M hold zeros)
 #pragma unroll 1
                     for (uint32_t i = 0; i < n; i += 4) {
                         const uint32_t slot = min(i + (uint32_t)s, n - 1u);
-                        int64_t k = (int64_t)ch * KC + mmm_list_entry_k(ESZ, list[mmm_list_pos(ESZ, slot)], (uint32_t)ch & (RING - 1u));
-                        if (p.kinfo != nullptr) k = p.kmap[k];
+                        const uint32_t col = mmm_list_entry_k(ESZ, list[mmm_list_pos(ESZ, slot)], (uint32_t)ch & (RING - 1u));
                         const bool there = i + (uint32_t)s < n;
                         float a[RT];
 #pragma unroll
                         for (int r = 0; r < RT; ++r) {
-                            const int64_t row = row0 + r * 16 + c;
-                            const bool kept = there && row < p.M && ((p.a_bits[min(row, p.M - 1) * p.WA + (k >> 6)] >> (k & 63)) & 1ull);
-                            a[r] = kept ? p.X[row * p.ldx + k] : 0.f;
+                            const float v = mmm_whole_float(block + col * 128u + mmm_img_row(2, col, (uint32_t)(r * 16 + c)), MMM_PART_BYTES);
+                            a[r] = there ? v : 0.f;
                         }
 #pragma unroll
-                        for (int g = 0; g < GW; ++g) {
-                            const int64_t col = (G0 + g) * 16 + c, blk = min(col / p.bw, p.NB - 1);
-                            const bool on = there && col < p.N && ((p.b_bits[k * p.WB + (blk >> 6)] >> (blk & 63)) & 1ull);
-                            const float b = on ? p.Y[k * p.ldy + col] : 0.f;
+                        for (int g = 0; g < GW; ++g) {   // (blocks that are off and columns past N hold zeros)
+                            const char *const seg = p.bp_val + ((Gc + g) * p.KBA + ch) * SEGB + (slot / BATCH) * (PARTS * 1024);
+                            const float v = mmm_whole_float(seg + mmm_value_pos(2, slot % BATCH, (uint32_t)c) * 2u, 1024);
+                            const float b = there ? v : 0.f;
 #pragma unroll
                             for (int r = 0; r < RT; ++r) acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b, acc[g][r], 0, 0, 0);
                         }
@@ -958,8 +953,8 @@ hipError_t mmm_static_scratch(float **ptr)
 int32_t mmm_variant_count() { return kVariants; }
 const mmm_variant_info &mmm_variant(int32_t i) { return g_variants[i].info; }
 
-hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtype, const void *X, int64_t ldx, const void *Y, int64_t ldy, void *C, int64_t ldc, int32_t accumulate,
-                             void *partials, size_t partial_bytes, hipStream_t s)
+hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtype, void *C, int64_t ldc, int32_t accumulate, void *partials,
+                             size_t partial_bytes, hipStream_t s)
 {
     if (pl.variant < 0 || pl.variant >= kVariants) return hipErrorInvalidValue;
     const VariantEntry &v = g_variants[pl.variant];
@@ -997,16 +992,7 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
         return hipErrorInvalidValue;
     const int wide = m->bw == 32 ? 1 : 0;
     const bool parts = m->b_form == MMM_FORM_PARTS;
-    if (parts) {
-        p.a_wild = m->a_wild;
-        p.a_bits = m->a_bits;
-        p.b_bits = m->b_bits;
-        p.X = static_cast<const float *>(X);
-        p.Y = static_cast<const float *>(Y);
-        p.ldx = ldx;
-        p.ldy = ldy;
-        p.WB = m->WB;
-    }
+    if (parts) p.a_wild = m->a_wild;
     matmul_kernel_fn fn = parts ? v.parts[wide] : pl.filter ? v.filter[wide] : v.fn[wide][f64 ? 3 : dtype == MMM_BF16 ? 1 : dtype == MMM_F16 ? 2 : 0];
     if (fn == nullptr) return hipErrorInvalidValue;
     (void)hipGetLastError();   // drop any stale error another library left on this thread

@@ -135,6 +135,32 @@ def test_non_finite_elements(where, value):
         assert np.all(np.isnan(rest) | (rest == C_ref[~rows, jb * 16 + 3]))
 
 
+@pytest.mark.parametrize("rows", [None, 0.7], ids=["all", "rows"])
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_the_multiplication_reads_neither_operand(bw, rows):
+    """Elements in and out of range in either operand; X and Y hold something else by the time of the multiplication."""
+    w = synth.random_masked(140, 700, 96 + bw, bw, 0.4, 0.6, 23 + bw, dist="normal", p_rows=rows)
+    rng = np.random.default_rng(bw)
+    odd = np.float32([2.0 ** -111, -3e-39, 1e-45, 2.0 ** 55, -2.0 ** 61])
+    # (in some of the blocks of A and in some of the segments of B)
+    for v, share in ((w.X[:, :200], 0.001), (w.Y[300:500], 0.002)):
+        at = rng.random(v.shape) < share
+        v[at] = rng.choice(odd, int(at.sum()))
+    _, _, C_ref, mag = oracle.run_workload(w)
+    run = HipRun(w)
+    run.build()
+    run.matmul()
+    torch.cuda.synchronize()
+    C = run.C.cpu().numpy()
+    assert (np.abs(C - C_ref) <= w.K * 2.0 ** -24 * mag + 1e-45).all()
+    run.X.fill_(float("nan"))
+    run.Y.fill_(float("nan"))
+    run.Cbuf.fill_(float("nan"))
+    run.matmul()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(run.C.cpu().numpy(), C)
+
+
 def test_inspection_shows_the_elements_as_they_are():
     rng = np.random.default_rng(3)
     w = synth.random_masked(100, 300, 32, 16, 0.5, 0.5, 4, dist="normal")
