@@ -100,7 +100,7 @@ typedef struct {
 /* Host-side handle describing maps that live in caller-provided device memory. */
 typedef struct mmm_maps mmm_maps;
 
-/* Bytes of device workspace that maps for this shape need: the maps and their
+/* Bytes of device workspace that maps for this shape need, whatever the element type: the maps and their
  * derived forms, the image of A (4 bytes per element of X, 6 if M is above 64), packed B at its
  * worst-case size (8 bytes per element of Y, 4 if M is at most 64, and 2 bytes per
  * row of Y and 16 columns), room for the inspection lists of A or the image of a
@@ -109,8 +109,13 @@ typedef struct mmm_maps mmm_maps;
  * Errors: MMM_ERR_SHAPE, MMM_ERR_INVALID_ARG (bytes NULL). */
 mmm_status mmm_maps_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t block_width, size_t *bytes);
 
+/* The same for one element type.  Types other than MMM_F32 need 2 bytes per element of X less if M is above 64.  A
+ * handle with a workspace of that size takes floats as well and never lays them out in parts (see mmm_matmul).
+ * Errors: as above, MMM_ERR_DTYPE. */
+mmm_status mmm_maps_workspace_bytes_for(int64_t M, int64_t K, int64_t N, int32_t block_width, mmm_dtype dt, size_t *bytes);
+
 /* Create the handle.  `dev_workspace` must be 256-byte aligned device memory of
- * at least mmm_maps_workspace_bytes(); it stays owned by the caller and must
+ * at least mmm_maps_workspace_bytes() or mmm_maps_workspace_bytes_for(); it stays owned by the caller and must
  * outlive the handle.  No device work is done here.  *out is written only on
  * success.  Errors: MMM_ERR_SHAPE, MMM_ERR_WORKSPACE, MMM_ERR_INVALID_ARG. */
 mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M, int64_t K, int64_t N,

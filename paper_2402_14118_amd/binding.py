@@ -26,7 +26,7 @@ MMM_PRED_NONZERO, MMM_PRED_GT, MMM_PRED_ABS_GT = 0, 1, 2
 MMM_PATH_AUTO, MMM_PATH_MATRIX, MMM_PATH_PAIRS = -1, 0, 1
 
 EXPORTS = [
-    "mmm_maps_workspace_bytes", "mmm_maps_init", "mmm_maps_release", "mmm_build_maps", "mmm_maps_view",
+    "mmm_maps_workspace_bytes", "mmm_maps_workspace_bytes_for", "mmm_maps_init", "mmm_maps_release", "mmm_build_maps", "mmm_maps_view",
     "mmm_maps_view_derived", "mmm_maps_view_compacted", "mmm_maps_view_lists", "mmm_debug_k_lists", "mmm_maps_stats", "mmm_matmul", "mmm_matmul_static_scratch", "mmm_matmul_fused",
     "mmm_maps_set_path", "mmm_matmul_path", "mmm_set_option", "mmm_matmul_variant_count",
     "mmm_matmul_variant_name", "mmm_matmul_plan", "mmm_maps_set_plan", "mmm_status_string", "mmm_last_device_error",
@@ -59,6 +59,7 @@ def _load() -> ctypes.CDLL:
     c = ctypes
     i64, i32, vp = c.c_int64, c.c_int32, c.c_void_p
     lib.mmm_maps_workspace_bytes.argtypes = [i64, i64, i64, i32, c.POINTER(c.c_size_t)]
+    lib.mmm_maps_workspace_bytes_for.argtypes = [i64, i64, i64, i32, i32, c.POINTER(c.c_size_t)]
     lib.mmm_maps_init.argtypes = [vp, c.c_size_t, i64, i64, i64, i32, c.POINTER(vp)]
     lib.mmm_maps_release.argtypes = [vp]
     lib.mmm_maps_release.restype = None
@@ -132,6 +133,12 @@ def _stream(stream) -> Optional[int]:
 def mmm_maps_workspace_bytes(M: int, K: int, N: int, block_width: int) -> int:
     out = ctypes.c_size_t(0)
     _check(lib.mmm_maps_workspace_bytes(M, K, N, block_width, ctypes.byref(out)), "mmm_maps_workspace_bytes")
+    return out.value
+
+
+def mmm_maps_workspace_bytes_for(M: int, K: int, N: int, block_width: int, dtype: int) -> int:
+    out = ctypes.c_size_t(0)
+    _check(lib.mmm_maps_workspace_bytes_for(M, K, N, block_width, dtype, ctypes.byref(out)), "mmm_maps_workspace_bytes_for")
     return out.value
 
 

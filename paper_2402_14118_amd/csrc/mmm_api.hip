@@ -44,8 +44,10 @@ bool shape_ok(int64_t M, int64_t K, int64_t N, int32_t bw)
     return true;
 }
 
-Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw)
+// parts: with room for floats in parts
+Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw, bool parts)
 {
+    parts = parts && M > 64;
     const int64_t NB = N / bw, WA = (K + 63) / 64, WB = (NB + 63) / 64, MT = (M + MMM_COLANY_ROWS - 1) / MMM_COLANY_ROWS;
     Layout l{};
     size_t off = 0;
@@ -58,8 +60,8 @@ Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw)
     off += align_up(blocks * 4);
     l.a_ent = off;
     off += align_up(blocks * MMM_AB_CAP * 8);
-    l.a_img = off;   // room for the widest form (doubles have theirs in a_ent)
-    off += align_up(blocks * MMM_AB_CAP * (M > 64 ? MMM_PARTS_ESZ : 4));
+    l.a_img = off;   // (doubles have theirs in a_ent)
+    off += align_up(blocks * MMM_AB_CAP * (parts ? MMM_PARTS_ESZ : 4));
     l.a_wild = off;
     off += align_up(blocks);
     l.b_bits = off;
@@ -345,7 +347,7 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
 // 190 + 43, .1 139 + 31 and 157 + 39 (a list of 13 fills 40 % of a batch).
 int32_t choose_form(mmm_maps *m, const mmm_build_args &a, bool capture)
 {
-    if (a.dtype != MMM_F32 || m->M <= 64) return MMM_FORM_PLAIN;
+    if (a.dtype != MMM_F32 || m->M <= 64 || !m->parts_room) return MMM_FORM_PLAIN;
     const int64_t opt = g_opt_form.load();
     const bool keeps_a = a.X == nullptr && m->a_built && m->a_dtype == MMM_F32 && !(m->b_compact || a.b_compact);
     const bool keeps_b = a.Y == nullptr && m->b_built && m->b_dtype == MMM_F32;
@@ -454,7 +456,16 @@ mmm_status mmm_maps_workspace_bytes(int64_t M, int64_t K, int64_t N, int32_t blo
 {
     if (bytes == nullptr) return MMM_ERR_INVALID_ARG;
     if (!shape_ok(M, K, N, block_width)) return MMM_ERR_SHAPE;
-    *bytes = make_layout(M, K, N, block_width).total;
+    *bytes = make_layout(M, K, N, block_width, true).total;
+    return MMM_OK;
+}
+
+mmm_status mmm_maps_workspace_bytes_for(int64_t M, int64_t K, int64_t N, int32_t block_width, mmm_dtype dt, size_t *bytes)
+{
+    if (bytes == nullptr) return MMM_ERR_INVALID_ARG;
+    if (!shape_ok(M, K, N, block_width)) return MMM_ERR_SHAPE;
+    if (!dtype_ok(dt)) return MMM_ERR_DTYPE;
+    *bytes = make_layout(M, K, N, block_width, dt == MMM_F32).total;
     return MMM_OK;
 }
 
@@ -463,7 +474,9 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
 {
     if (out == nullptr) return MMM_ERR_INVALID_ARG;
     if (!shape_ok(M, K, N, block_width)) return MMM_ERR_SHAPE;
-    const Layout l = make_layout(M, K, N, block_width);
+    Layout l = make_layout(M, K, N, block_width, true);
+    const bool parts_room = workspace_bytes >= l.total;
+    if (!parts_room) l = make_layout(M, K, N, block_width, false);
     if (dev_workspace == nullptr || reinterpret_cast<uintptr_t>(dev_workspace) % kAlign != 0 ||
         workspace_bytes < l.total)
         return MMM_ERR_WORKSPACE;
@@ -501,6 +514,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->bp_cnt = reinterpret_cast<uint32_t *>(base + l.bp_cnt);
     m->partials = reinterpret_cast<float *>(base + l.partials);
     m->partial_bytes = l.partial_bytes;
+    m->parts_room = parts_room;
     m->ws = dev_workspace;
     m->ws_bytes = workspace_bytes;
     m->a_built = m->b_built = false;

@@ -168,6 +168,7 @@ struct mmm_maps {
     uint32_t *bp_cnt;
     float *partials;   // split-K partial sums
     size_t partial_bytes;
+    bool parts_room;   // the workspace has room for floats in parts
     void *ws;
     size_t ws_bytes;
     // state

@@ -16,7 +16,7 @@ class MaskedMatmul:
     def __init__(self, M: int, K: int, N: int, block_width: int, dtype: int = B.MMM_F32, device="cuda:0"):
         self.M, self.K, self.N, self.bw, self.dtype = M, K, N, block_width, dtype
         self.device = torch.device(device)
-        nbytes = B.mmm_maps_workspace_bytes(M, K, N, block_width)
+        nbytes = B.mmm_maps_workspace_bytes_for(M, K, N, block_width, dtype)
         # torch's caching allocator hands out >= 512-byte aligned blocks
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         assert self.workspace.data_ptr() % 256 == 0

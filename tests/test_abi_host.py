@@ -42,6 +42,26 @@ def test_workspace_bytes_and_shape_errors():
     assert B.lib.mmm_maps_workspace_bytes(8, 8, 8, 8, None) == B.MMM_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("M,K,N,bw", [(64, 300, 64, 16), (65, 300, 64, 16), (2048, 2048, 2048, 16), (1, 1, 8, 8), (777, 3001, 1992, 8)])
+def test_room_for_floats_in_parts_is_asked_of_floats_alone(M, K, N, bw):
+    """Their image of A takes 6 bytes per element, in blocks of 64 x 128; that of any other type 4 at most (doubles keep
+    theirs elsewhere)."""
+    parts = -(-M // 64) * -(-K // 128) * 8192 * 2 if M > 64 else 0
+    full = mm.mmm_maps_workspace_bytes(M, K, N, bw)
+    assert mm.mmm_maps_workspace_bytes_for(M, K, N, bw, B.MMM_F32) == full
+    fake = 0x7000_0000_0000
+    for dt in (B.MMM_BF16, B.MMM_F16, B.MMM_F64):
+        need = mm.mmm_maps_workspace_bytes_for(M, K, N, bw, dt)
+        assert need == full - parts
+        mm.mmm_maps_release(mm.mmm_maps_init(fake, need, M, K, N, bw))
+        out = ctypes.c_void_p(None)
+        assert B.lib.mmm_maps_init(fake, need - 1, M, K, N, bw, ctypes.byref(out)) == B.MMM_ERR_WORKSPACE
+    n = ctypes.c_size_t(0)
+    assert B.lib.mmm_maps_workspace_bytes_for(M, K, N, bw, 4, ctypes.byref(n)) == B.MMM_ERR_DTYPE
+    assert B.lib.mmm_maps_workspace_bytes_for(0, K, N, bw, 0, ctypes.byref(n)) == B.MMM_ERR_SHAPE
+    assert B.lib.mmm_maps_workspace_bytes_for(M, K, N, bw, 0, None) == B.MMM_ERR_INVALID_ARG
+
+
 def test_init_and_call_validation_without_device():
     need = mm.mmm_maps_workspace_bytes(64, 128, 64, 16)
     fake = 0x7000_0000_0000          # never dereferenced on the host

@@ -213,6 +213,25 @@ def test_the_form_follows_the_counts_and_the_side_that_is_kept():
     check(run, PLAIN)
 
 
+def test_a_workspace_without_room_for_parts():
+    """That of another type: floats are multiplied as they are, whatever is asked for, and nothing behind it is written."""
+    w = synth.random_masked(200, 700, 288, 16, 0.4, 0.5, 9, dist="normal")
+    mm.mmm_set_option("float_form", PLAIN)
+    want = HipRun(w).run()[2]
+    mm.mmm_set_option("float_form", PARTS)
+    run = HipRun(w)
+    need = mm.mmm_maps_workspace_bytes_for(w.M, w.K, w.N, w.bw, mm.MMM_BF16)
+    room = run.eng.workspace.numel()
+    assert need < room
+    run.eng.close()
+    run.eng.workspace.fill_(0x5a)
+    run.eng.maps = mm.mmm_maps_init(run.eng.workspace, need, w.M, w.K, w.N, w.bw)
+    np.testing.assert_array_equal(run.run()[2], want)
+    run.eng.stats()
+    np.testing.assert_array_equal(run.run()[2], want)
+    assert (run.eng.workspace[need:] == 0x5a).all()
+
+
 @pytest.mark.parametrize("captured", ["build", "matmul"])
 def test_a_captured_call_fixes_the_form(captured):
     """A graph's build or multiplication runs between calls of other forms otherwise."""
