@@ -187,6 +187,12 @@ template <typename T> struct ABlock {   // one block in a wave's registers: lane
     uint64_t kw;   // keep word of (row t, half h), in lane t * A_WORDS + h
 };
 
+// Numbers of blocks, words and columns.  Of some 125 scalar instructions per block, which each of sixteen waves takes, 64-bit products were six
+// each where 32 by 32 bits are two, and comparisons of 64 bits leave the scalar unit (2048 x 16384, columns, bf16: A 25.3 -> 22.2 us; 2048^2
+// floats 7.8 -> 7.5).  Doubles, whose blocks are half as many elements and which wait for memory, are no faster for it (2048^3, p = .1, the whole
+// pass: 63.6 with 32 bits, 63.3 with 64).
+template <typename T> using block_no = typename std::conditional<sizeof(T) == 8, int64_t, int32_t>::type;
+
 // v_writelane_b32 and DPP instead of selects, wave-uniform words only where a lane mask is wanted, no branch per row and
 // one base per block: the sixteen waves of a block share one scalar unit, and the scan of half-precision matrices was
 // bound by it (2048 x 16384, one column in ten: 36.5 us with pairs of k per lane, whose masks had to be interleaved there).
@@ -194,10 +200,11 @@ template <typename T> struct ABlock {   // one block in a wave's registers: lane
 // several (columns 2048 x 16384: 28 -> 26 us for A, 41 -> 35.4 with B; with one or two blocks per workgroup the loads past
 // the last one cost more than they gain, 6.6 -> 9 us for 512 x 8192, and so do more bytes in flight for the wider types).
 template <typename T, int TEST, bool ROWS, bool DEEP>
-__device__ __forceinline__ void scan_a(ConstParams &p0, int32_t bj, int32_t bi0, int32_t bi1, int lane, int wave, AShared &sh)
+__device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no<T> bi0, block_no<T> bi1, int lane, int wave, AShared &sh)
 {
     ConstParams &p = reread(p0);
     typedef typename Pattern<sizeof(T)>::type pattern;
+    typedef block_no<T> no_t;
     constexpr int ESZ = (int)sizeof(T);
     constexpr bool WIDE = ESZ >= 4;
     constexpr int A_WORDS = Tile<T>::A_WORDS, A_COLS = 64 * A_WORDS;
@@ -209,7 +216,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int32_t bj, int32_t bi0,
     constexpr bool compact = ROWS;
     // Buffer resources that end with the last row: what lies past it, and lanes past the last column, reads as +0, which
     // is never kept, and is not stored.  64 rows are at most 2^31 bytes (leading dimensions are below 2^22).
-    const int32_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;   // (K < 2^22)
+    const no_t k_lo = bj * A_COLS, w_lo = bj * A_WORDS;   // (K < 2^22)
     const int tail = (int)min(p.K - k_lo, (int64_t)A_COLS);   // columns of these blocks that exist
     const uint32_t row_bytes = (uint32_t)p.ldx * ESZ, map_bytes = (uint32_t)p.WA * 8u;
     const uint32_t row0 = WIDE_IMG ? (uint32_t)wave : (uint32_t)wave * A_ROWS;
@@ -220,17 +227,17 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int32_t bj, int32_t bi0,
     const uint32_t map_at = lane < A_ROWS * A_WORDS && w_lo + lane % A_WORDS < p.WA
                                 ? (row0 + ROW_STEP * (uint32_t)(lane / A_WORDS)) * map_bytes + (uint32_t)(lane % A_WORDS) * 8u
                                 : OUTSIDE;
-    auto rows_at = [&](int32_t bi) -> uint32_t { return (uint32_t)min((int32_t)p.M - bi * MMM_AB_ROWS, MMM_AB_ROWS); };   // (M is at most 2^30)
-    // Per block, of some 125 scalar instructions for each of sixteen waves: 32 by 32 bits are two of them, 64 by 64 were six, and
-    // comparisons of 64 bits left the scalar unit (2048 x 16384, columns, bf16: A 25.3 -> 22.2 us; 2048^2 floats 7.8 -> 7.5).
-    auto block_rows = [](int32_t bi, uint32_t row) -> uint64_t { return (uint64_t)(uint32_t)bi * (row * MMM_AB_ROWS); };   // bytes up to block row bi
-    auto map_rsrc = [&](const uint64_t *map, int32_t bi, bool any) {
+    auto rows_at = [&](no_t bi) -> uint32_t { return (uint32_t)min((no_t)p.M - bi * MMM_AB_ROWS, (no_t)MMM_AB_ROWS); };   // (M is at most 2^30)
+    auto block_rows = [](no_t bi, uint32_t row) -> uint64_t {   // bytes up to block row bi
+        return ESZ == 8 ? (uint64_t)bi * ((uint64_t)row * MMM_AB_ROWS) : (uint64_t)(uint32_t)bi * (row * MMM_AB_ROWS);
+    };
+    auto map_rsrc = [&](const uint64_t *map, no_t bi, bool any) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(reinterpret_cast<const char *>(map) + block_rows(bi, map_bytes) + w_lo * 8), 0,
                                                  any ? (int)(rows_at(bi) * map_bytes - (uint32_t)w_lo * 8u) : 0, 0x00020000);
     };
     // DEEP: always the same number of loads, so that waiting for one block's does not mean waiting for the next one's: where
     // there is no block or no keep bitmap the buffer is empty.
-    auto load = [&](int32_t bi, ABlock<T> &r) __attribute__((always_inline)) {
+    auto load = [&](no_t bi, ABlock<T> &r) __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         const bool there = bi < bi1;
         r.kw = 0;
@@ -279,7 +286,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int32_t bj, int32_t bi0,
             if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
         }
     }
-    auto block = [&](int32_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
+    auto block = [&](no_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
         ConstParams &p = reread(p0);
         constexpr int AHEAD = decltype(ahead)::value;   // the block whose loads take this one's place
         char *const stage = sh.stage[PARTED ? 0 : st];
@@ -467,12 +474,12 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, int32_t bj, int32_t bi0,
         }
     };
     if constexpr (DEEP) {
-        for (int32_t bi = bi0; bi < bi1; bi += 2) {
+        for (no_t bi = bi0; bi < bi1; bi += 2) {
             block(bi, even, 0, std::integral_constant<int, 2>{});
             if (bi + 1 < bi1) block(bi + 1, odd, 1, std::integral_constant<int, 2>{});
         }
     } else {
-        for (int32_t bi = bi0; bi < bi1; ++bi) block(bi, even, (int)(bi - bi0) & 1, std::integral_constant<int, 1>{});
+        for (no_t bi = bi0; bi < bi1; ++bi) block(bi, even, (int)(bi - bi0) & 1, std::integral_constant<int, 1>{});
     }
 }
 
