@@ -290,6 +290,10 @@ mmm_status mmm_maps_set_path(mmm_maps *maps, int32_t path);
 /* The kernel mmm_matmul would use now.  Errors: MMM_ERR_INVALID_ARG. */
 mmm_status mmm_matmul_path(const mmm_maps *maps, int32_t *path);
 
+/* The form the operands have been laid out in: 0 = as they are, 1 = floats in three parts (see mmm_matmul and
+ * the "float_form" option).  Errors: MMM_ERR_INVALID_ARG. */
+mmm_status mmm_matmul_form(const mmm_maps *maps, int32_t *form);
+
 /* C (+)= M(X) x B with the mask M evaluated inside the multiplication: the A-side pass of
  * mmm_build_maps is not needed and X is read once (section 3 "Preprocessing": the cost of
  * preprocessing matters for small matrices; rows of B are preprocessed once and reused).  Only
@@ -341,7 +345,11 @@ mmm_status mmm_set_option(const char *name, int64_t value);
  * above / the automatic choice) and number of K splits (0 = likewise).  A
  * variant that computes too few rows for the matrix, or more splits than K has
  * steps or the workspace has room for, is adjusted as in the automatic choice;
- * mmm_matmul_plan reports what will be used.  This is the tuning knob the paper
+ * mmm_matmul_plan reports what will be used.  It holds from the next multiplication
+ * on; so it does for operands laid out in parts (see mmm_matmul), but for the tiles
+ * with K in two ranges, which parts do not have.  The builds that follow keep floats as
+ * they are for every tile but the one parts have by themselves (64 x 256).
+ * This is the tuning knob the paper
  * leaves to an autotuner (section 3, "Optimizations": the base vector multiple).
  * Errors: MMM_ERR_INVALID_ARG (maps NULL, values out of range). */
 mmm_status mmm_maps_set_plan(mmm_maps *maps, int32_t variant, int32_t split_k);

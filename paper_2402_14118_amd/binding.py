@@ -28,7 +28,7 @@ MMM_PATH_AUTO, MMM_PATH_MATRIX, MMM_PATH_PAIRS = -1, 0, 1
 EXPORTS = [
     "mmm_maps_workspace_bytes", "mmm_maps_workspace_bytes_for", "mmm_maps_init", "mmm_maps_release", "mmm_build_maps", "mmm_maps_view",
     "mmm_maps_view_derived", "mmm_maps_view_compacted", "mmm_maps_view_lists", "mmm_debug_k_lists", "mmm_maps_stats", "mmm_matmul", "mmm_matmul_static_scratch", "mmm_matmul_fused",
-    "mmm_maps_set_path", "mmm_matmul_path", "mmm_set_option", "mmm_matmul_variant_count",
+    "mmm_maps_set_path", "mmm_matmul_path", "mmm_matmul_form", "mmm_set_option", "mmm_matmul_variant_count",
     "mmm_matmul_variant_name", "mmm_matmul_plan", "mmm_maps_set_plan", "mmm_status_string", "mmm_last_device_error",
 ]
 
@@ -75,6 +75,7 @@ def _load() -> ctypes.CDLL:
     lib.mmm_matmul_fused.argtypes = [vp, i32, vp, i64, c.POINTER(MaskA), vp, i64, vp, i64, i32, vp]
     lib.mmm_maps_set_path.argtypes = [vp, i32]
     lib.mmm_matmul_path.argtypes = [vp, c.POINTER(i32)]
+    lib.mmm_matmul_form.argtypes = [vp, c.POINTER(i32)]
     lib.mmm_set_option.argtypes = [c.c_char_p, i64]
     lib.mmm_maps_set_plan.argtypes = [vp, i32, i32]
     lib.mmm_matmul_variant_count.restype = i32
@@ -235,6 +236,12 @@ def mmm_maps_set_path(maps: int, path: int = -1) -> None:
 def mmm_matmul_path(maps: int) -> int:
     v = ctypes.c_int32(0)
     _check(lib.mmm_matmul_path(maps, ctypes.byref(v)), "mmm_matmul_path")
+    return v.value
+
+
+def mmm_matmul_form(maps: int) -> int:
+    v = ctypes.c_int32(0)
+    _check(lib.mmm_matmul_form(maps, ctypes.byref(v)), "mmm_matmul_form")
     return v.value
 
 

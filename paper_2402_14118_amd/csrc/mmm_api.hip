@@ -242,7 +242,7 @@ bool variant_usable(const mmm_maps *m, int32_t dt, int32_t form, int64_t v)
     if (v < 0 || v >= mmm_variant_count()) return false;
     const mmm_variant_info &vi = mmm_variant((int32_t)v);
     return !(vi.rows < MMM_AB_ROWS && m->M > vi.rows)        // computes too few rows for this matrix
-           && !(dt == MMM_F64 && !vi.doubles) && !(form == MMM_FORM_PARTS && !vi.parts);
+           && !(dt == MMM_F64 && !vi.doubles) && !(form == MMM_FORM_PARTS && vi.parts == PARTS_NO);
 }
 
 void compute_plan(const mmm_maps *m, int32_t dt, int32_t form, int64_t variant, int64_t fixed_split, mmm_plan *plan, double *cost)
@@ -252,6 +252,7 @@ void compute_plan(const mmm_maps *m, int32_t dt, int32_t form, int64_t variant, 
     double best = -1.0;
     for (int32_t v = 0; v < mmm_variant_count(); ++v) {
         if (!variant_usable(m, dt, form, v) || (variant_usable(m, dt, form, variant) && v != variant)) continue;
+        if (form == MMM_FORM_PARTS && mmm_variant(v).parts != PARTS_OWN && v != variant) continue;
         mmm_plan p = tile_plan(m, v);
         const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
         static constexpr int64_t kSplits[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 28, 32};
@@ -377,7 +378,7 @@ int32_t choose_form(mmm_maps *m, const mmm_build_args &a, bool capture)
             const MatrixProblem q = matrix_problem(m, a.dtype, MMM_FORM_PARTS);
             const double b_rounds = std::ceil((double)q.steps * (double)((m->N + 255) / 256) / 512.0);
             const double longer = 2.68e-7 * (double)m->M * (double)m->K + 7.7e-7 * (double)m->stats_occ_b * m->bw + 0.6 * q.batches * b_rounds;
-            const bool asked = v >= 0 && !variant_usable(m, a.dtype, MMM_FORM_PARTS, v);
+            const bool asked = v >= 0 && mmm_variant((int32_t)v).parts != PARTS_OWN;   // another tile: floats as they are
             const bool pairs = path == MMM_PATH_PAIRS || (path < 0 && v < 0 && pairs_cost(m, a.dtype) < std::min(plain, parts));
             m->form_chosen = !filter && !asked && !pairs && 1.15 * parts + longer + 2.0 < plain ? MMM_FORM_PARTS : MMM_FORM_PLAIN;
             m->form_key = key;
@@ -856,6 +857,13 @@ mmm_status mmm_matmul_path(const mmm_maps *maps, int32_t *path)
     if (maps == nullptr || path == nullptr) return MMM_ERR_INVALID_ARG;
     const int32_t dt = maps->a_built ? maps->a_dtype : maps->b_built ? maps->b_dtype : MMM_F32;
     *path = choose_path(maps, dt, form_of(maps, dt));
+    return MMM_OK;
+}
+
+mmm_status mmm_matmul_form(const mmm_maps *maps, int32_t *form)
+{
+    if (maps == nullptr || form == nullptr) return MMM_ERR_INVALID_ARG;
+    *form = maps->b_built ? maps->b_form : maps->a_built ? maps->a_form : MMM_FORM_PLAIN;
     return MMM_OK;
 }
 

@@ -239,11 +239,12 @@ struct mmm_build_args {
     int32_t form;     // MMM_FORM_*
 };
 
+enum { PARTS_NO = 0, PARTS_FIXED = 1, PARTS_OWN = 2 };   // PARTS_FIXED: only where this tile has been fixed
 struct mmm_variant_info {
     const char *name;
     int32_t TM, TN, KC, rows, k_ranges;   // rows: rows of C actually computed (64, or 32 for short matrices); k_ranges: ranges of K inside a workgroup
     bool doubles;                         // takes double inputs
-    bool parts;                           // takes floats in parts
+    int32_t parts;                        // PARTS_*: whether it takes floats in parts
 };
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);

@@ -159,7 +159,7 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 //     sums are added in LDS at the end, in order
 // FILTER  floats: look whether to leave the columns of A out that are zero in the whole tile (see `filtered`)
 template <int RT, int GW, int NW, int KS, typename T, bool FILTER>
-__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? NW / 4 : sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? (NW + 3) / 4 : sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
     constexpr bool F64 = sizeof(T) == 8, WIDE = sizeof(T) == 4 || F64;
     constexpr bool PARTED = sizeof(T) == MMM_PARTS_ESZ;
@@ -903,19 +903,21 @@ struct VariantEntry {
              {MMM_KERNELS(RT, 2, NW / 2, 1), mmm_matmul_kernel<RT, 2, NW / 2, 1, double, false>}},                        \
             MMM_FILTERS(RT, NW, 1), PARTS_KERNELS(RT, NW)                                                                 \
     }
-#define MMM_VARIANT_K2(RT, NW) /* two rings: not for doubles */                                                           \
+#define MMM_VARIANT_K2(RT, NW) /* two rings: not for doubles and floats in parts */                                                           \
     {                                                                                                                     \
-        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false, false}, NW,                                                 \
+        {"R" #RT "x16_TN" #NW "x16_K2", TM, 16 * NW, KC, 16 * RT, 2, false, PARTS_NO}, NW,                                                 \
             {{MMM_KERNELS(RT, 1, NW, 2), nullptr}, {MMM_KERNELS(RT, 2, NW / 2, 2), nullptr}}, MMM_FILTERS(RT, NW, 2), MMM_WHOLE(RT, NW) \
     }
 
+// Floats in parts have 64 x 256 by themselves; the narrower tiles, which leave a compute unit 8 or 4 waves beside the same ring, where they
+// are fixed while the operands are in parts (4096^3, p = .4: 323, 375 and 572 us; 1500 x 2100 x 1024, p_B = .5: 33.5, 31.0 and 48.9).
 const VariantEntry g_variants[] = {
-    MMM_VARIANT(4, 8, false, MMM_WHOLE),      // 0: 64 x 128
-    MMM_VARIANT(4, 16, true, MMM_PARTED),     // 1: 64 x 256
-    MMM_VARIANT(4, 4, false, MMM_WHOLE),      // 2: 64 x 64
-    MMM_VARIANT(2, 8, false, MMM_WHOLE),      // 3: 32 x 128   (matrices of at most 32 rows)
+    MMM_VARIANT(4, 8, PARTS_FIXED, MMM_PARTED),   // 0: 64 x 128
+    MMM_VARIANT(4, 16, PARTS_OWN, MMM_PARTED),     // 1: 64 x 256
+    MMM_VARIANT(4, 4, PARTS_FIXED, MMM_PARTED),   // 2: 64 x 64
+    MMM_VARIANT(2, 8, PARTS_NO, MMM_WHOLE),       // 3: 32 x 128   (matrices of at most 32 rows)
     MMM_VARIANT_K2(2, 8),   // 4: 32 x 128, K in two ranges
-    MMM_VARIANT(2, 4, false, MMM_WHOLE),      // 5: 32 x 64
+    MMM_VARIANT(2, 4, PARTS_NO, MMM_WHOLE),       // 5: 32 x 64
     MMM_VARIANT_K2(4, 8),   // 6: 64 x 128, K in two ranges
     MMM_VARIANT_K2(4, 4),   // 7: 64 x 64, K in two ranges
 };

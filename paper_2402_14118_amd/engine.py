@@ -77,10 +77,17 @@ class MaskedMatmul:
         B.mmm_maps_set_plan(self.maps, variant, split_k)
 
     def autotune(self, X: torch.Tensor, Y: torch.Tensor, C: torch.Tensor, splits=(0,), reps: int = 20):
-        """Time every tile variant (and the given K splits) on the maps as built, with the caller's operands, and fix
-        the fastest as this handle's plan.  Returns [(microseconds, variant, split_k)] sorted by time.  C is
-        overwritten."""
+        """Time every tile variant that the operands as built can take (and the given K splits), with the caller's
+        operands, and fix the fastest as this handle's plan.  Returns [(microseconds, variant, split_k)] sorted by time.
+        C is overwritten.
+
+        Whether floats are laid out in parts is decided by the build, with the counts of stats(): tune behind a build
+        that has had them.  A tile that is fixed decides it too (only one keeps the parts), so on operands in parts the
+        fastest plan of that one is fixed, and a plan found before there were counts keeps floats as they are until
+        set_plan() gives the choice back."""
         results = []
+        self.set_plan()
+        own = self.plan()[0] if B.mmm_matmul_form(self.maps) else None   # the tile that keeps the parts
         for v in range(B.mmm_matmul_variant_count()):
             for sp in splits:
                 self.set_plan(v, sp)
@@ -97,7 +104,8 @@ class MaskedMatmul:
                 torch.cuda.synchronize()
                 results.append((e0.elapsed_time(e1) * 1e3 / reps, pv, ps))
         results.sort()
-        self.set_plan(results[0][1], results[0][2])
+        _, variant, split = next(r for r in results if own is None or r[1] == own)
+        self.set_plan(variant, split)
         return results
 
     def _bits_tensor(self, addr: int, rows: int, words: int) -> torch.Tensor:

@@ -232,6 +232,54 @@ def test_a_workspace_without_room_for_parts():
     assert (run.eng.workspace[need:] == 0x5a).all()
 
 
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_a_tile_that_is_fixed_holds_at_once(bw):
+    """The tiles with one range of K take parts as well; which tile it is does not change the sums."""
+    w = synth.random_masked(200, 1500, 544, bw, 0.4, 0.5, 41 + bw, dist="normal")
+    run = HipRun(w)
+    run.eng.set_plan(1, 1)
+    want = run.run()[2]
+    assert mm.mmm_matmul_form(run.eng.maps) == PARTS
+    for v in range(mm.mmm_matmul_variant_count()):
+        name = mm.mmm_matmul_variant_name(v)
+        print("variant", v, name, flush=True)
+        run.eng.set_plan(v, 1)
+        held = name.startswith("R4") and not name.endswith("K2")
+        assert run.eng.plan()[:2] == (v if held else 1, 1)
+        run.Cbuf.fill_(float("nan"))
+        run.matmul()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(run.C.cpu().numpy(), want)
+    mm.mmm_set_option("float_form", PLAIN)
+    run.build()
+    assert mm.mmm_matmul_form(run.eng.maps) == PLAIN
+
+
+@pytest.mark.parametrize("form", [PLAIN, PARTS])
+def test_autotune_times_the_tiles_of_the_form(form):
+    w = synth.random_masked(300, 2100, 384, 16, 0.4, 0.5, 12, dist="normal")
+    mm.mmm_set_option("float_form", form)
+    run = HipRun(w)
+    run.build()
+    results = run.eng.autotune(run.X, run.Y, run.C, splits=(1, 2), reps=2)
+    names = [mm.mmm_matmul_variant_name(v) for v in range(mm.mmm_matmul_variant_count())]
+    usable = [v for v, n in enumerate(names) if n.startswith("R4") and not (form == PARTS and n.endswith("K2"))]
+    assert sorted({r[1] for r in results}) == usable and results == sorted(results)
+    fixed = run.eng.plan()[:2]
+    assert fixed == (results[0][1:] if form == PLAIN else next(r[1:] for r in results if r[1] == 1))
+    # the form is decided anew by the builds that follow: a plan found for parts keeps them where they pay
+    mm.mmm_set_option("float_form", -1)
+    wide = synth.random_masked(1500, 2100, 1024, 16, 0.4, 0.5, 8, dist="normal")
+    run = HipRun(wide)
+    run.build()
+    run.eng.stats()
+    run.build()
+    assert mm.mmm_matmul_form(run.eng.maps) == PARTS
+    run.eng.autotune(run.X, run.Y, run.C, reps=2)
+    run.build()
+    assert mm.mmm_matmul_form(run.eng.maps) == PARTS and run.eng.plan()[0] == 1
+
+
 @pytest.mark.parametrize("captured", ["build", "matmul"])
 def test_a_captured_call_fixes_the_form(captured):
     """A graph's build or multiplication runs between calls of other forms otherwise."""
