@@ -249,7 +249,9 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
  * MMM_PATH_MATRIX multiplies floats as they are or, where the counts of mmm_maps_stats say that it is faster, as the exact
  * sum of three bf16 parts each, six of whose nine products are accumulated in float (those left out are below 2^-24 of
  * the whole; see the "float_form" option).  mmm_build_maps lays the operands out for one or the other; a side that is
- * built alone takes the form of the side that is kept, and a build or multiplication that is captured into a graph fixes the handle's form.
+ * built alone takes the form of the side that is kept, and a build or multiplication that is captured into a graph fixes the handle's form
+ * for as long as the graph, or what has been cloned or instantiated from it, exists (a graph that an executable one is updated from
+ * has to be kept by the caller as long as that one).
  * Products the maps skip contribute exactly 0, whatever the skipped operands
  * hold (see the conventions above for non-finite kept values).  Every element
  * of C is written exactly once, zeros included.  float accumulation; the

@@ -342,22 +342,65 @@ mmm_status make_for_inspection(const char *what, const mmm_maps *maps, hipError_
     return MMM_ERR_DEVICE;
 }
 
-// The form a build gives floats: that of the side it does not build (the kernel takes both from one form), that of a captured
-// call, or the one with which build and multiplication are estimated to take less; without counts the plain one.  Parts pay
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
+}
+
+// Whether this call is captured with a form.  (The null stream is never captured; asking takes 0.15 us.)
+bool form_is_captured(const mmm_maps *m, int32_t dt, hipStream_t s)
+{
+    return dt == MMM_F32 && m->M > 64 && m->parts_room && s != nullptr && capturing(s);
+}
+
+void release_captures(mmm_captures *c)
+{
+    if (c->owners.fetch_sub(1) == 1) delete c;
+}
+void graph_is_gone(void *captures)   // (called by the runtime: no calls of it in here)
+{
+    mmm_captures *c = static_cast<mmm_captures *>(captures);
+    c->graphs.fetch_sub(1);
+    release_captures(c);
+}
+
+// The graph under capture holds a call with this form.  Where the runtime cannot tell when the graph goes, it is taken to stay.
+void capture_form(const mmm_maps *m, int32_t form, hipStream_t s)
+{
+    m->form_captured = form;
+    mmm_captures *c = m->captures;
+    c->graphs.fetch_add(1);
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    hipGraph_t graph = nullptr;
+    hipUserObject_t object = nullptr;
+    if (hipStreamGetCaptureInfo_v2(s, &status, nullptr, &graph, nullptr, nullptr) == hipSuccess && graph != nullptr) {
+        c->owners.fetch_add(1);
+        if (hipUserObjectCreate(&object, c, graph_is_gone, 1, hipUserObjectNoDestructorSync) != hipSuccess)
+            release_captures(c);
+        else if (hipGraphRetainUserObject(graph, object, 1, hipGraphUserObjectMove) != hipSuccess) {
+            c->graphs.fetch_add(1);   // (what the release takes back)
+            (void)hipUserObjectRelease(object, 1);
+        }
+    }
+    (void)hipGetLastError();
+}
+
+// The form a build gives floats: that of the side it does not build (the kernel takes both from one form), that of captured
+// calls, or the one with which build and multiplication are estimated to take less; without counts the plain one.  Parts pay
 // for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 432 + 39 and 326 + 56 us, .2 237 + 34 and
 // 190 + 43, .1 139 + 31 and 157 + 39 (a list of 13 fills 40 % of a batch).
-int32_t choose_form(mmm_maps *m, const mmm_build_args &a, bool capture)
+int32_t choose_form(mmm_maps *m, const mmm_build_args &a)
 {
     if (a.dtype != MMM_F32 || m->M <= 64 || !m->parts_room) return MMM_FORM_PLAIN;
     const int64_t opt = g_opt_form.load();
     const bool keeps_a = a.X == nullptr && m->a_built && m->a_dtype == MMM_F32 && !(m->b_compact || a.b_compact);
     const bool keeps_b = a.Y == nullptr && m->b_built && m->b_dtype == MMM_F32;
-    const int32_t pinned = m->form_pinned.load();
     int32_t form = MMM_FORM_PLAIN;
     if (keeps_a || keeps_b) {
         form = keeps_a ? m->a_form : m->b_form;
-    } else if (pinned >= 0) {
-        form = pinned;
+    } else if (m->captures->graphs.load() > 0) {
+        form = m->form_captured;
     } else if (opt >= 0) {
         form = (int32_t)opt;
     } else if (stats_known(m)) {
@@ -387,20 +430,7 @@ int32_t choose_form(mmm_maps *m, const mmm_build_args &a, bool capture)
         }
         form = m->form_chosen;
     }
-    if (capture) m->form_pinned = form;
     return form;
-}
-
-bool capturing(hipStream_t s)
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(s, &status) != hipSuccess || status != hipStreamCaptureStatusNone;
-}
-
-// Whether this call is the first to be captured with a form.  (The null stream is never captured; asking takes 0.15 us.)
-bool form_is_captured(const mmm_maps *m, int32_t dt, hipStream_t s)
-{
-    return dt == MMM_F32 && m->M > 64 && s != nullptr && m->form_pinned.load(std::memory_order_relaxed) < 0 && capturing(s);
 }
 
 // The transposed B map over k is read by the pair kernel and by inspection only.  In row-compacted mode it is made with
@@ -481,8 +511,13 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     if (dev_workspace == nullptr || reinterpret_cast<uintptr_t>(dev_workspace) % kAlign != 0 ||
         workspace_bytes < l.total)
         return MMM_ERR_WORKSPACE;
-    mmm_maps *m = new (std::nothrow) mmm_maps();
-    if (m == nullptr) return MMM_ERR_INVALID_ARG;
+    mmm_captures *captures = new (std::nothrow) mmm_captures();
+    mmm_maps *m = captures != nullptr ? new (std::nothrow) mmm_maps() : nullptr;
+    if (m == nullptr) {
+        delete captures;
+        return MMM_ERR_INVALID_ARG;
+    }
+    m->captures = captures;
     m->M = M;
     m->K = K;
     m->N = N;
@@ -525,7 +560,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->build_captured = false;
     m->a_dtype = m->b_dtype = -1;
     m->a_form = m->b_form = MMM_FORM_PLAIN;
-    m->form_pinned = -1;
+    m->form_captured = MMM_FORM_PLAIN;
     m->form_valid = false;
     m->a_src = nullptr;
     m->a_src_ld = 0;
@@ -544,7 +579,9 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
 
 void mmm_maps_release(mmm_maps *maps)
 {
-    if (maps != nullptr && maps->bt_event != nullptr) (void)hipEventDestroy(maps->bt_event);
+    if (maps == nullptr) return;
+    if (maps->bt_event != nullptr) (void)hipEventDestroy(maps->bt_event);
+    release_captures(maps->captures);
     delete maps;
 }
 
@@ -587,7 +624,8 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
     a.b_compact = Y != nullptr && mb->keep_rows != nullptr && dt != MMM_F64;
     const bool compact_after = Y != nullptr ? a.b_compact : maps->b_compact;
     a.a_compact = X != nullptr && compact_after;
-    a.form = choose_form(maps, a, form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream)));
+    a.form = choose_form(maps, a);
+    if (form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream))) capture_form(maps, a.form, static_cast<hipStream_t>(hip_stream));
     if (hipError_t e = mmm_launch_build(maps, a, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
         note_device_error("map builder launch", e);
         return MMM_ERR_DEVICE;
@@ -768,7 +806,7 @@ static mmm_status matmul_common(const mmm_maps *maps, mmm_dtype dt, const void *
         return MMM_OK;
     }
     const mmm_plan p = make_plan(maps, dt, maps->b_form);
-    if (form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream))) maps->form_pinned = maps->b_form;
+    if (form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream))) capture_form(maps, maps->b_form, static_cast<hipStream_t>(hip_stream));
     void *partials = maps->partials;
     size_t partial_bytes = maps->partial_bytes;
     if (static_scratch) {

@@ -134,6 +134,13 @@ struct mmm_plan_key {
 
 enum { BT_MADE = 0, BT_MISSING = 1, BT_LAUNCHED = 2 };
 
+// Graphs that hold a captured call of a handle: counted for as long as they, or what has been instantiated from them, exist, which
+// may be longer than the handle.
+struct mmm_captures {
+    std::atomic<int> owners{1};   // the handle and the graphs
+    std::atomic<int> graphs{0};
+};
+
 struct mmm_maps {
     int64_t M, K, N;
     int32_t bw;
@@ -183,8 +190,9 @@ struct mmm_maps {
     bool a_compact;   // the image of A was built over k' (for the numbering of the current B side)
     int32_t a_dtype, b_dtype;
     int32_t a_form, b_form;   // MMM_FORM_*: the same of both where both are built, with floats
-    // the form every build keeps to once a call has been captured into a graph, which may run between others (-1: none yet)
-    mutable std::atomic<int32_t> form_pinned;
+    // the form every build keeps to while there is a graph with a captured call, which may run between others
+    mmm_captures *captures;
+    mutable std::atomic<int32_t> form_captured;
     const void *a_src;   // address and leading dimension of the X the A side was built from (identity only)
     int64_t a_src_ld;
     const void *b_src;   // the same of the Y the B side was built from

@@ -1,5 +1,7 @@
 """Floats in three bf16 parts: the form of the float operands that the 16-bit matrix instructions multiply.  Asked for here
 with the "float_form" option; by itself the library takes it where the estimates say that it is faster."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -308,3 +310,53 @@ def test_a_captured_call_fixes_the_form(captured):
         run.matmul()
         torch.cuda.synchronize()
         np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+
+
+def test_the_form_is_free_again_when_the_graphs_are_gone():
+    w = synth.random_masked(200, 700, 288, 16, 0.4, 0.5, 9, dist="smallint")
+    C_ref = oracle.run_workload(w)[2]
+    mm.mmm_set_option("float_form", PLAIN)
+    run = HipRun(w)
+    run.build()
+    run.matmul()
+    torch.cuda.synchronize()
+    graphs = [torch.cuda.CUDAGraph() for _ in range(3)]
+    for graph, calls in zip(graphs, ([run.build, run.matmul], [run.matmul], [run.matmul])):
+        with torch.cuda.graph(graph):
+            for call in calls:
+                call()
+    mm.mmm_set_option("float_form", PARTS)
+
+    def form_of_a_build():
+        for _ in range(3):             # (the runtime lets go of a graph that has run some calls later)
+            run.build()
+            torch.cuda.synchronize()
+        return mm.mmm_matmul_form(run.eng.maps)
+
+    while len(graphs) > 1:
+        assert form_of_a_build() == PLAIN
+        for graph in graphs:
+            run.Cbuf.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+        del graph, graphs[0]
+        gc.collect()
+        torch.cuda.synchronize()
+    assert form_of_a_build() == PLAIN
+    graphs.clear()
+    gc.collect()
+    torch.cuda.synchronize()
+    assert form_of_a_build() == PARTS
+    run.matmul()
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+    graph = torch.cuda.CUDAGraph()     # that outlives the handle
+    with torch.cuda.graph(graph):
+        run.matmul()
+    graph.replay()
+    torch.cuda.synchronize()
+    run.eng.close()
+    del graph
+    gc.collect()
+    torch.cuda.synchronize()
