@@ -226,7 +226,9 @@ mmm_status mmm_maps_view_lists(const mmm_maps *maps, const uint32_t **counts, co
 /* Counts taken from the maps (runs a small reduction on `hip_stream`, then
  * WAITS for the stream): non-zeros of A, occupied blocks of B, and useful
  * multiply-adds  sum_k nnz(A[:,k]) * bw * occupied(B[k,:])  -- the products the
- * loop of Fig. "MMM Pseudocode" performs.  Any out pointer may be NULL.
+ * loop of Fig. "MMM Pseudocode" performs.  Any out pointer may be NULL.  The counts
+ * are also what the library's own choices go by from then on (tile, kernel, form of
+ * floats); of floats the blocks with elements that parts do not hold are counted too.
  * Errors: MMM_ERR_INVALID_ARG, MMM_ERR_MAPS_MISMATCH (a side not built),
  * MMM_ERR_DEVICE. */
 mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occupied_blocks_b,
@@ -248,7 +250,9 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
  * address this Y, see below).
  * MMM_PATH_MATRIX multiplies floats as they are or, where the counts of mmm_maps_stats say that it is faster, as the exact
  * sum of three bf16 parts each, six of whose nine products are accumulated in float (those left out are below 2^-24 of
- * the whole; see the "float_form" option).  mmm_build_maps lays the operands out for one or the other; a side that is
+ * the whole; see the "float_form" option).  Blocks with an element that parts do not hold (magnitudes of 2^55 and more or
+ * below 2^-110, infinities, NaN) are multiplied as floats behind the others, up to seven times slower where all have one:
+ * floats are left as they are where mmm_maps_stats has counted more than a few.  mmm_build_maps lays the operands out for one or the other; a side that is
  * built alone takes the form of the side that is kept, and a build or multiplication that is captured into a graph fixes the handle's form
  * for as long as the graph, or what has been cloned or instantiated from it, exists (a graph that an executable one is updated from
  * has to be kept by the caller as long as that one).

@@ -69,7 +69,7 @@ Layout make_layout(int64_t M, int64_t K, int64_t N, int32_t bw, bool parts)
     l.bt_bits = off;
     off += align_up((size_t)NB * WA * 8);
     l.stats = off;
-    off += align_up(6 * 8);
+    off += align_up(MMM_STATS_WORDS * 8);
     // row-compacted mode: numbering of the live rows and maps over it
     l.kinfo = off;
     off += align_up(64);
@@ -155,6 +155,8 @@ struct MatrixProblem {
     int64_t steps;   // of 128 k that the kernel walks
     double units;    // per step and group: quads of listed k (16-bit: batches of 32)
     double batches;  // batches of 16 (32) slots
+    double marked;   // floats in parts: share of the steps of a wave with an element that they do not hold
+    double redone;   // and how long such a step takes, us
     bool look;       // workgroups look for columns of A that are zero in their tile (floats)
     bool filtered;   // and most will leave them out of their lists
 };
@@ -176,6 +178,9 @@ MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt, int32_t form)
     q.steps = (rows + MMM_AB_COLS - 1) / MMM_AB_COLS;
     q.batches = listed > 0.5 * batch ? listed / batch + 0.5 : 1.0;
     q.units = esz == 2 ? q.batches : listed / 4.0 + 0.5;
+    const double b_marked = m->bw == 32 ? 1.0 - (1.0 - m->stats_marked_b) * (1.0 - m->stats_marked_b) : m->stats_marked_b;   // (a wave has two groups)
+    q.marked = form == MMM_FORM_PARTS && known ? 1.0 - (1.0 - m->stats_marked_a) * (1.0 - b_marked) : 0.0;
+    q.redone = 1.65 * (listed / 4.0 + 0.5);
     return q;
 }
 
@@ -193,6 +198,13 @@ double matrix_cost(const mmm_maps *m, int32_t dt, int32_t form, const MatrixProb
     double t = c.launch + (double)steps * q.batches * c.latency +
                (double)per_cu * (work * (c.step + groups * (vi.rows / 16) * q.units * c.multiply) + groups * vi.k_ranges * c.wave + c.workgroup) +
                1e-9 * c.image_giga * (double)wgs * work * (double)(MMM_AB_ROWS * MMM_AB_COLS * esz);
+    if (q.marked > 0.0) {
+        // Marked steps are done again behind the loop, by a wave on its own and four k at a time.  The fullest compute unit has more of them
+        // than the mean: by about three times its root.  4096^3, p = .4, multiplication, with 0, 1, 10, 100 % of the blocks of A marked
+        // 365, 454, 782, 3052 us, of the segments of B 347, 465, 845, 3036; 2048^3, blocks of 32, p_B = .5, 53, 92, 211, 473 and 53, 98, 225, 471.
+        const double all = (double)steps * (double)per_cu, mean = q.marked * all;
+        t += q.redone * std::min(all, mean + 3.0 * std::sqrt(mean));
+    }
     if (split > 1) t += c.reduce + 1e-6 * c.reduce_mega * (double)split * (double)m->M * (double)m->N;
     return t;
 }
@@ -351,7 +363,7 @@ bool capturing(hipStream_t s)
 // Whether this call is captured with a form.  (The null stream is never captured; asking takes 0.15 us.)
 bool form_is_captured(const mmm_maps *m, int32_t dt, hipStream_t s)
 {
-    return dt == MMM_F32 && m->M > 64 && m->parts_room && s != nullptr && capturing(s);
+    return mmm_may_part(m, dt) && s != nullptr && capturing(s);
 }
 
 void release_captures(mmm_captures *c)
@@ -389,10 +401,11 @@ void capture_form(const mmm_maps *m, int32_t form, hipStream_t s)
 // The form a build gives floats: that of the side it does not build (the kernel takes both from one form), that of captured
 // calls, or the one with which build and multiplication are estimated to take less; without counts the plain one.  Parts pay
 // for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 432 + 39 and 326 + 56 us, .2 237 + 34 and
-// 190 + 43, .1 139 + 31 and 157 + 39 (a list of 13 fills 40 % of a batch).
+// 190 + 43, .1 139 + 31 and 157 + 39 (a list of 13 fills 40 % of a batch).  They do not where more than a few steps hold an element that
+// parts do not (see matrix_cost): mmm_maps_stats counts those too, in either form.
 int32_t choose_form(mmm_maps *m, const mmm_build_args &a)
 {
-    if (a.dtype != MMM_F32 || m->M <= 64 || !m->parts_room) return MMM_FORM_PLAIN;
+    if (!mmm_may_part(m, a.dtype)) return MMM_FORM_PLAIN;
     const int64_t opt = g_opt_form.load();
     const bool keeps_a = a.X == nullptr && m->a_built && m->a_dtype == MMM_F32 && !(m->b_compact || a.b_compact);
     const bool keeps_b = a.Y == nullptr && m->b_built && m->b_dtype == MMM_F32;
@@ -571,6 +584,7 @@ mmm_status mmm_maps_init(void *dev_workspace, size_t workspace_bytes, int64_t M,
     m->plan_path = -1;
     m->stats_a_valid = m->stats_b_valid = false;
     m->stats_active = 1.0;
+    m->stats_marked_a = m->stats_marked_b = 0.0;
     m->stats_nnz_a = m->stats_occ_b = m->stats_macs = m->stats_rows_b = m->stats_version = 0;
     m->plan_valid = false;
     *out = m;
@@ -741,7 +755,7 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
     if (!maps->a_built || !maps->b_built) return MMM_ERR_MAPS_MISMATCH;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     hipError_t e = mmm_launch_stats(maps, s);
-    uint64_t host[6] = {0, 0, 0, 0, 0, 0};
+    uint64_t host[MMM_STATS_WORDS] = {};
     if (e == hipSuccess) e = hipMemcpyAsync(host, maps->stats, sizeof(host), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
@@ -753,6 +767,9 @@ mmm_status mmm_maps_stats(const mmm_maps *maps, uint64_t *nnz_a, uint64_t *occup
     maps->stats_macs = host[2];
     maps->stats_rows_b = host[3];
     maps->stats_active = host[5] != 0 ? (double)host[4] / ((double)host[5] * (double)maps->MBA) : 1.0;
+    const double steps = (double)((host[5] + MMM_AB_COLS - 1) / MMM_AB_COLS);
+    maps->stats_marked_a = host[6] != 0 ? (double)host[6] / (steps * (double)maps->MBA) : 0.0;
+    maps->stats_marked_b = host[7] != 0 ? (double)host[7] / (steps * (double)maps->NG) : 0.0;
     ++maps->stats_version;
     maps->stats_a_valid = maps->stats_b_valid = true;
     if (nnz_a) *nnz_a = host[0];

@@ -680,7 +680,6 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, int64_t seg, int64_t ct,
             for (int64_t q = (blk0 + BPW + 7) / 8; q < p.WB * 8; ++q) reinterpret_cast<uint8_t *>(p.b_bits + krow * p.WB)[q] = 0;
     }
     constexpr int RING = mmm_ring(LSZ);
-    // (floats in parts: their ring has no zero column, and any that exists does)
     // (floats in parts: their ring has no zero column; the block's first, which exists if there is a list, does as well)
     const uint32_t ZERO_ENTRY = mmm_list_entry(LSZ, PARTED ? ((uint32_t)seg & (RING - 1u)) * SEG : mmm_zero_col(RING));
     static_assert(B_GROUPS * SEG * 2 <= BUILD_THREADS * 4, "at most one list word per thread");
@@ -960,7 +959,7 @@ __global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_im
 // ---- statistics (off the hot path) -----------------------------------------------------------
 __global__ void mmm_stats_clear_kernel(uint64_t *stats)
 {
-    if (threadIdx.x < 6) stats[threadIdx.x] = 0;
+    if (threadIdx.x < MMM_STATS_WORDS) stats[threadIdx.x] = 0;
 }
 
 // One workgroup per 64 values of k: lane kb of every wave counts column k of A
@@ -997,6 +996,41 @@ __global__ __launch_bounds__(256) void mmm_stats_kernel(const uint64_t *a_bits, 
 #pragma unroll
         for (int q = 0; q < 4; ++q) add(q, v[q]);
     }
+}
+
+// Floats that may come in parts: the steps of row tiles of A (stats[6]) and of groups of B (stats[7]) with an element that parts do
+// not hold, a wave for each.  In parts as the matrix kernel finds them marked, else from the elements themselves.
+template <bool PARTED>
+__global__ __launch_bounds__(256) void mmm_marks_kernel(const char *a_img, const uint8_t *a_wild, const char *bp_val, const uint32_t *bp_cnt,
+                                                        const uint32_t *kinfo, const uint32_t *kmap, int64_t K, int64_t KBA, int64_t MBA,
+                                                        int64_t NG, uint64_t *stats)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const bool of_a = item < MBA * KBA;
+    const int64_t at = of_a ? item : item - MBA * KBA, ch = at % KBA;
+    const int64_t live = kinfo != nullptr ? (int64_t)*kinfo : K;
+    if (at >= (of_a ? MBA : NG) * KBA || ch * MMM_AB_COLS >= live) return;
+    OutOfRange range;
+    auto scan = [&](const char *from, int64_t quads) {
+        for (int64_t q = lane; q < quads; q += 64) {
+            const uint4 v = reinterpret_cast<const uint4 *>(from)[q];
+            range.see(v.x), range.see(v.y), range.see(v.z), range.see(v.w);
+        }
+    };
+    bool marked = false;
+    if (PARTED && of_a) {
+        const int64_t k0 = kinfo != nullptr ? kmap[ch * MMM_AB_COLS] : ch * MMM_AB_COLS;
+        const int64_t k1 = kinfo != nullptr ? kmap[min((ch + 1) * MMM_AB_COLS, live) - 1] : k0;
+        for (int64_t j = k0 / MMM_AB_COLS + lane; j <= k1 / MMM_AB_COLS; j += 64) marked |= a_wild[at - ch + j] != 0;
+    } else if (PARTED) {
+        marked = (int32_t)bp_cnt[at] < 0;
+    } else if (of_a) {   // (columns past the last live one hold anything)
+        scan(a_img + at * (MMM_AB_CAP * 4), min(live - ch * MMM_AB_COLS, (int64_t)MMM_AB_COLS) * (MMM_AB_ROWS / 4));
+    } else {
+        scan(bp_val + at * (SEG * MMM_GROUP_COLS * 4), (int64_t)bp_cnt[at] * (MMM_GROUP_COLS / 4));
+    }
+    if (ballot64(marked || range.any()) != 0 && lane == 0) atomicAdd((unsigned long long *)&stats[of_a ? 6 : 7], 1ull);
 }
 
 }   // namespace
@@ -1243,5 +1277,11 @@ hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s)
     hipLaunchKernelGGL(mmm_stats_clear_kernel, dim3(1), dim3(64), 0, s, m->stats);
     hipLaunchKernelGGL(mmm_stats_kernel, dim3((uint32_t)m->WA), dim3(256), 0, s, m->a_bits, m->b_bits, m->a_colany,
                        m->b_compact ? m->rows_copy : nullptr, m->M, m->K, m->WA, m->WB, m->MT, (int64_t)m->bw, m->stats);
+    if (mmm_may_part(m, m->a_dtype) && m->b_dtype == MMM_F32 && m->a_form == m->b_form && m->a_compact == m->b_compact) {
+        const int64_t items = (m->MBA + m->NG) * m->KBA;
+        hipLaunchKernelGGL(m->b_form == MMM_FORM_PARTS ? mmm_marks_kernel<true> : mmm_marks_kernel<false>, dim3((uint32_t)((items + 3) / 4)),
+                           dim3(256), 0, s, m->a_img, m->a_wild, m->bp_val, m->bp_cnt, m->b_compact ? m->kinfo : nullptr, m->kmap, m->K, m->KBA,
+                           m->MBA, m->NG, m->stats);
+    }
     return hipGetLastError();
 }

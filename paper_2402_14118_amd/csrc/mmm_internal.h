@@ -132,6 +132,7 @@ struct mmm_plan_key {
     }
 };
 
+constexpr int MMM_STATS_WORDS = 8;
 enum { BT_MADE = 0, BT_MISSING = 1, BT_LAUNCHED = 2 };
 
 // Graphs that hold a captured call of a handle: counted for as long as they, or what has been instantiated from them, exist, which
@@ -161,7 +162,7 @@ struct mmm_maps {
     char *a_img64;     // image of A for double inputs, which have no lists: takes the place of a_ent
     uint64_t *b_bits;
     uint64_t *bt_bits;
-    uint64_t *stats;   // 6 words
+    uint64_t *stats;   // MMM_STATS_WORDS
     // Row-compacted mode (B side built with keep_rows): k' numbers the rows keep_rows leaves on, and the
     // matrix kernel walks k' instead of k.
     uint32_t *kinfo;       // [0] = number of live k (device)
@@ -202,6 +203,7 @@ struct mmm_maps {
     // what the most recent mmm_maps_stats call counted: the density estimate behind the choice of kernel
     mutable bool stats_a_valid, stats_b_valid;
     mutable uint64_t stats_nnz_a, stats_occ_b, stats_macs, stats_rows_b;   // non-zeros, blocks, surviving products, rows of B with a block
+    mutable double stats_marked_a, stats_marked_b;   // share of the steps of a row tile of A and of a group of B that are marked, or would be, in parts
     mutable double stats_active;   // share of the k that are on whose column of A has a non-zero element in a tile of 64 rows
     mutable int64_t stats_version;
     // the launch plan last made: it is made anew when its key changes
@@ -258,6 +260,7 @@ struct mmm_variant_info {
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s);
 // Whether B is packed (and the matrix kernel can run): always but for double inputs of so few rows that the pair kernel
 // is what runs, for which the workspace has no room.
+inline bool mmm_may_part(const mmm_maps *m, int32_t dtype) { return dtype == MMM_F32 && m->M > 64 && m->parts_room; }
 inline bool mmm_packs(int64_t M, int32_t dtype) { return dtype != MMM_F64 || M > 64; }
 hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s);
 // forms that only inspection reads: column-any words over k'; counts and lists of the blocks of A

@@ -215,6 +215,37 @@ def test_the_form_follows_the_counts_and_the_side_that_is_kept():
     check(run, PLAIN)
 
 
+@pytest.mark.parametrize("rows", [None, 0.7], ids=["all", "rows"])
+@pytest.mark.parametrize("bw", [8, 16, 32])
+@pytest.mark.parametrize("side", ["x", "y"])
+def test_the_form_follows_the_steps_that_parts_do_not_hold(side, bw, rows):
+    """stats() counts them in either form; where they are more than a few, floats stay as they are or become so again."""
+    mm.mmm_set_option("matmul_path", -1)
+    mm.mmm_set_option("float_form", -1)
+    w = synth.random_masked(1500, 4000, 1024, bw, 0.4, 0.5, 8, dist="normal", p_rows=rows)
+    run = HipRun(w)
+    clean = {"x": run.X.clone(), "y": run.Y.clone()}
+    given = run.X if side == "x" else run.Y
+    at = torch.rand(given.shape, generator=torch.Generator().manual_seed(bw)) < 0.001
+    odd = torch.where(at.cuda(), torch.full_like(given, 1e-38), given)
+
+    def form_after_stats():
+        run.build()
+        run.matmul()
+        run.eng.stats()
+        run.build()
+        return mm.mmm_matmul_form(run.eng.maps)
+
+    given.copy_(odd)
+    assert form_after_stats() == PLAIN     # counted among floats as they are
+    given.copy_(clean[side])
+    assert form_after_stats() == PARTS
+    given.copy_(odd)
+    assert form_after_stats() == PLAIN     # counted among parts
+    given.copy_(clean[side])
+    assert form_after_stats() == PARTS
+
+
 def test_a_workspace_without_room_for_parts():
     """That of another type: floats are multiplied as they are, whatever is asked for, and nothing behind it is written."""
     w = synth.random_masked(200, 700, 288, 16, 0.4, 0.5, 9, dist="normal")
