@@ -78,6 +78,36 @@ def test_error_against_double_precision(M, K, N, p, scale_x, scale_y, dist):
     assert error[PARTS] <= error[PLAIN]
 
 
+@pytest.mark.parametrize("products", [1, 2])
+@pytest.mark.parametrize("ex,ey", [(0, 0), (-110, 0), (-110, 53), (-110, -14), (54, 54), (54, -110), (-63, -63), (-58, -60), (-75, -74)])
+def test_few_products(ex, ey, products):
+    """Sums of one product and of two, up to the ends of the range that parts hold and where products or the parts' products
+    are subnormal.  In units of 2^-24 of the products' magnitudes: the three products of parts left out are below 1, the
+    others' sums are 2^-7 of the whole and off by less than 0.1, adding the two accumulators rounds by 1 (floats as they
+    are: 1), and the first parts' sum of two by 2 where the instruction cuts off.  Each of the six products and two additions
+    may lose 2^-149 among subnormals."""
+    M, K, N = 96, 128, 64
+    rng = np.random.default_rng(abs(1000 * ex + ey) + products)
+
+    def values(shape, e):
+        fraction = rng.integers(0, 1 << 23, shape)
+        fraction = np.where(rng.random(shape) < 0.3, rng.choice([0, 1, (1 << 23) - 1], shape), fraction)
+        return ((1 + fraction / 2.0 ** 23) * rng.choice([-1.0, 1.0], shape) * 2.0 ** e).astype(np.float32)
+
+    w = synth.random_masked(M, K, N, 16, 1.0, 1.0, 1)
+    w.Y = values((K, N), ey)
+    w.X[:] = 0
+    for i in range(M):
+        w.X[i, rng.permutation(K)[:products]] = values(products, ex)
+    exact = w.X.astype(np.float64) @ w.Y.astype(np.float64)
+    mag = np.abs(w.X.astype(np.float64)) @ np.abs(w.Y.astype(np.float64))
+    _, _, C = HipRun(w).run()
+    units = 2.1 if products == 1 else 4.1
+    err = np.abs(C - exact)
+    print("worst", (err / mag).max() * 2 ** 24)
+    assert (err <= units * 2.0 ** -24 * mag + 8 * 2.0 ** -149).all()
+
+
 # ---- elements that the parts do not hold: multiplied as floats ----------------------------------
 @pytest.mark.parametrize("rows", [None, 0.7], ids=["all", "rows"])
 @pytest.mark.parametrize("bw", [8, 16, 32])
@@ -106,6 +136,45 @@ def test_finite_elements_out_of_range(value, bw, rows):
     plain = HipRun(w).run()[2]
     clean = (C_ref == np.rint(C_ref)) & (np.abs(C_ref) < 2 ** 20)       # sums of small integers alone
     np.testing.assert_array_equal(C[clean], plain[clean])
+
+
+@pytest.mark.parametrize("rows", [None, 0.7], ids=["all", "rows"])
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_marked_steps_everywhere(bw, rows):
+    """Marked steps on either side of the 32 that share a word, of the 64 batches that are planned together and of the splits,
+    on both places of the ring, with lists of one batch and of several.  A marked step is left out of the loop and redone
+    behind it for all rows (A) or all 16 columns (B): those without the element, sums of small integers, show what is lost
+    or counted twice."""
+    w = synth.random_masked(140, 140 * 128 - 37, 96, bw, 0.1, 1.0, 51 + bw, dist="smallint", p_rows=rows)
+    live = np.arange(w.K) if rows is None else np.nonzero(synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0])[0]
+    steps = -(-len(live) // 128)
+    assert steps > 96
+    rng = np.random.default_rng(bw)
+    share = rng.choice([0.02, 0.2, 0.6], (w.K // 128 + 1, w.NB)).repeat(128, 0)[: w.K]
+    on = rng.random((w.K, w.NB)) < share
+    a_steps, b_steps = [0, 31, 32, 63, 64, steps - 1], [1, 33, 62, 65, steps // 3, 2 * (steps // 3) + 1, steps - 1]
+    a = synth.unpack_bits(w.keep_a, w.K).copy()
+    for i, st in enumerate(a_steps):
+        k = int(live[st * 128 + i])
+        a[7 + 22 * i, k], w.X[7 + 22 * i, k] = True, 2.0 ** 56
+    for i, st in enumerate(b_steps):
+        k = int(live[min(st * 128 + 3 * i, len(live) - 1)])
+        on[k, i % w.NB], w.Y[k, (i % w.NB) * bw + i % bw] = True, -(2.0 ** 57)
+    w.keep_a, w.keep_blocks = synth.pack_bits(a), synth.pack_bits(on)
+    _, _, C_ref, mag = oracle.run_workload(w)
+    clean = mag < 2.0 ** 24
+    assert 0.7 < clean.mean() < 1.0
+    run = HipRun(w)
+    run.build()
+    assert mm.mmm_matmul_form(run.eng.maps) == PARTS
+    for split in (1, 3):
+        run.eng.set_plan(1, split)
+        run.Cbuf.fill_(float("nan"))
+        run.matmul()
+        torch.cuda.synchronize()
+        C = run.C.cpu().numpy()
+        np.testing.assert_array_equal(C[clean], C_ref[clean])
+        assert (np.abs(C - C_ref) <= w.K * 2.0 ** -24 * mag).all()
 
 
 @pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan], ids=str)
