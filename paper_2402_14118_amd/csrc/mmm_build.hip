@@ -140,6 +140,11 @@ struct OutOfRange {
         most = max(most, m);
         least = min(least, m - 1u);
     }
+    __device__ __forceinline__ void add(const OutOfRange &o)
+    {
+        most = max(most, o.most);
+        least = min(least, o.least);
+    }
     __device__ __forceinline__ bool any() const { return most >= MMM_PARTS_HI || least < MMM_PARTS_LO - 1u; }
 };
 __device__ __forceinline__ bool out_of_range(uint32_t bits)
@@ -179,6 +184,7 @@ struct AShared {
     uint64_t any[2][BUILD_WAVES][2][2];         // [stage][wave][32-row half of the block][word]
     uint8_t wild[2][BUILD_WAVES];               // floats in parts: [stage][wave]
     uint8_t live[MMM_AB_COLS];                  // row-compacted mode: live columns of the blocks
+    uint8_t on[MMM_AB_COLS];                    // and floats in parts: whether a column is one (what is switched off marks nothing)
     uint32_t before[BUILD_WAVES];               // row-compacted mode: live rows before them, by wave
 };
 
@@ -279,6 +285,10 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
 #pragma unroll
         for (int d = 32; d > 0; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d, 64);
         if (lane == 0) sh.before[wave] = n;
+        if (PARTED) {   // (every wave the same: it reads them before a barrier)
+            sh.on[lane] = (uint8_t)((m0 >> lane) & 1ull);
+            sh.on[64 + lane] = (uint8_t)((m1 >> lane) & 1ull);
+        }
         const uint32_t n0 = (uint32_t)__popcll(m0);
         cols = (int)(n0 + (uint32_t)__popcll(m1));
         if (wave == 0) {
@@ -328,7 +338,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
         else
             words(std::false_type{});
         if (PARTED && bi > bi0) __syncthreads();   // one stage (48 KiB; two would leave a compute unit one workgroup): the block before has left it
-        OutOfRange range;
+        OutOfRange range;   // of the elements in columns that are on
 #pragma unroll
         for (int h = 0; h < A_WORDS; ++h) {
             const int k = 64 * h + lane;
@@ -340,13 +350,13 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
                     OutOfRange here;
 #pragma unroll
                     for (int t = 0; t < A_ROWS; ++t) here.see(u[t]);
-                    range.most = max(range.most, here.most);
-                    range.least = min(range.least, here.least);
                     u32x2 part[MMM_PARTS];
                     uint32_t rest[A_ROWS] = {u[0], u[1], u[2], u[3]};
 #pragma unroll
                     for (int q = 0; q < MMM_PARTS; ++q) part[q] = u32x2{take_part(rest[0], rest[1]), take_part(rest[2], rest[3])};
-                    if (ballot64(here.any()) != 0)   // seldom: such elements as they are
+                    if (!ROWS) range.add(here);
+                    if (ballot64(here.any()) != 0) {   // seldom: such elements as they are
+                        if (ROWS && sh.on[k] != 0) range.add(here);   // (no others matter)
 #pragma unroll
                         for (int t = 0; t < A_ROWS; ++t)
                             if (out_of_range(u[t])) {
@@ -359,6 +369,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
                                 part[1][t / 2] = v1;
                                 part[2][t / 2] = v2;
                             }
+                    }
 #pragma unroll
                     for (int q = 0; q < MMM_PARTS; ++q)
                         *reinterpret_cast<u32x2 *>(stage + q * MMM_PART_BYTES + k * 128 + ((wave ^ (((k >> 1) & 7) << 1)) << 3)) = part[q];

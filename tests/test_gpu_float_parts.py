@@ -315,6 +315,21 @@ def test_the_form_follows_the_steps_that_parts_do_not_hold(side, bw, rows):
     assert form_after_stats() == PARTS
 
 
+@pytest.mark.parametrize("value", [1e-38, float("nan")], ids=str)
+def test_columns_that_are_switched_off_mark_nothing(value):
+    """Whatever they hold.  Seen by the count of marked steps: more than a few would bring floats as they are."""
+    mm.mmm_set_option("matmul_path", -1)
+    mm.mmm_set_option("float_form", -1)
+    w = synth.random_masked(1500, 4000, 1024, 16, 0.4, 0.5, 8, dist="normal", p_rows=0.7)
+    off = ~synth.unpack_bits(w.keep_rows.reshape(1, -1), w.K)[0]
+    w.X[:, off] = np.float32(value)
+    run = HipRun(w)
+    for want in (PLAIN, PARTS, PARTS, PARTS):
+        run.build()
+        assert mm.mmm_matmul_form(run.eng.maps) == want
+        run.eng.stats()
+
+
 def test_a_workspace_without_room_for_parts():
     """That of another type: floats are multiplied as they are, whatever is asked for, and nothing behind it is written."""
     w = synth.random_masked(200, 700, 288, 16, 0.4, 0.5, 9, dist="normal")
