@@ -251,6 +251,9 @@ def measure(w, steps, warmup, args, dense=True, trials=True):
     arith_peak, arith_name = (BF16_MFMA_PEAK_TFLOPS, "mfma") if mfma16 else (FP32_VECTOR_PEAK_TFLOPS, "alu")
     if w.dtype == synth.DT_F64:
         arith_peak = FP64_VECTOR_PEAK_TFLOPS
+    # floats in three bf16 parts: six 16-bit products for each
+    if path == mm.MMM_PATH_MATRIX and mm.mmm_matmul_form(eng.maps) != 0:
+        arith_peak, arith_name = BF16_MFMA_PEAK_TFLOPS / 6, "mfma"
 
     def floors(nbytes, flops, t_ms):
         """Roofline of one kernel: the floor is the larger of the time its algorithmic bytes need at the HBM peak
