@@ -278,7 +278,7 @@ def test_the_form_follows_the_counts_and_the_side_that_is_kept():
     check(run, PARTS)
     run.build(a=True, b=False)
     check(run, PARTS)
-    run.eng.set_plan(0, 1)                 # a shape that parts do not have: the automatic one until the next build
+    run.eng.set_plan(0, 1)                 # parts take this tile too, and the builds that follow leave floats as they are
     check(run, PARTS)
     run.build()
     check(run, PLAIN)
