@@ -1016,32 +1016,42 @@ __global__ __launch_bounds__(256) void mmm_marks_kernel(const char *a_img, const
                                                         const uint32_t *kinfo, const uint32_t *kmap, int64_t K, int64_t KBA, int64_t MBA,
                                                         int64_t NG, uint64_t *stats)
 {
+    __shared__ uint32_t found[2];   // (one atomic per workgroup: one per wave took 100 us where all are marked)
     const int lane = threadIdx.x & 63;
-    const int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const bool of_a = item < MBA * KBA;
-    const int64_t at = of_a ? item : item - MBA * KBA, ch = at % KBA;
     const int64_t live = kinfo != nullptr ? (int64_t)*kinfo : K;
-    if (at >= (of_a ? MBA : NG) * KBA || ch * MMM_AB_COLS >= live) return;
-    OutOfRange range;
-    auto scan = [&](const char *from, int64_t quads) {
-        for (int64_t q = lane; q < quads; q += 64) {
-            const uint4 v = reinterpret_cast<const uint4 *>(from)[q];
-            range.see(v.x), range.see(v.y), range.see(v.z), range.see(v.w);
+    if (threadIdx.x < 2) found[threadIdx.x] = 0;
+    __syncthreads();
+    for (int64_t item = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); item < (MBA + NG) * KBA; item += (int64_t)gridDim.x * 4) {
+        const bool of_a = item < MBA * KBA;
+        const int64_t at = of_a ? item : item - MBA * KBA, ch = at % KBA;
+        if (ch * MMM_AB_COLS >= live) continue;
+        OutOfRange range;
+        auto scan = [&](const char *from, int64_t quads) {
+            for (int64_t q = lane; q < quads; q += 64 * 8) {   // (the last one again past the end)
+                uint4 v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = reinterpret_cast<const uint4 *>(from)[min(q + 64 * u, quads - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) range.see(v[u].x), range.see(v[u].y), range.see(v[u].z), range.see(v[u].w);
+            }
+        };
+        bool marked = false;
+        if (PARTED && of_a) {
+            const int64_t k0 = kinfo != nullptr ? kmap[ch * MMM_AB_COLS] : ch * MMM_AB_COLS;
+            const int64_t k1 = kinfo != nullptr ? kmap[min((ch + 1) * MMM_AB_COLS, live) - 1] : k0;
+            for (int64_t j = k0 / MMM_AB_COLS + lane; j <= k1 / MMM_AB_COLS; j += 64) marked |= a_wild[at - ch + j] != 0;
+        } else if (PARTED) {
+            marked = (int32_t)bp_cnt[at] < 0;
+        } else if (of_a) {   // (columns past the last live one hold anything)
+            scan(a_img + at * (MMM_AB_CAP * 4), min(live - ch * MMM_AB_COLS, (int64_t)MMM_AB_COLS) * (MMM_AB_ROWS / 4));
+        } else {
+            scan(bp_val + at * (SEG * MMM_GROUP_COLS * 4), (int64_t)bp_cnt[at] * (MMM_GROUP_COLS / 4));
         }
-    };
-    bool marked = false;
-    if (PARTED && of_a) {
-        const int64_t k0 = kinfo != nullptr ? kmap[ch * MMM_AB_COLS] : ch * MMM_AB_COLS;
-        const int64_t k1 = kinfo != nullptr ? kmap[min((ch + 1) * MMM_AB_COLS, live) - 1] : k0;
-        for (int64_t j = k0 / MMM_AB_COLS + lane; j <= k1 / MMM_AB_COLS; j += 64) marked |= a_wild[at - ch + j] != 0;
-    } else if (PARTED) {
-        marked = (int32_t)bp_cnt[at] < 0;
-    } else if (of_a) {   // (columns past the last live one hold anything)
-        scan(a_img + at * (MMM_AB_CAP * 4), min(live - ch * MMM_AB_COLS, (int64_t)MMM_AB_COLS) * (MMM_AB_ROWS / 4));
-    } else {
-        scan(bp_val + at * (SEG * MMM_GROUP_COLS * 4), (int64_t)bp_cnt[at] * (MMM_GROUP_COLS / 4));
+        if (ballot64(marked || range.any()) != 0 && lane == 0) atomicAdd(&found[of_a ? 0 : 1], 1u);
     }
-    if (ballot64(marked || range.any()) != 0 && lane == 0) atomicAdd((unsigned long long *)&stats[of_a ? 6 : 7], 1ull);
+    __syncthreads();
+    if (threadIdx.x < 2 && found[threadIdx.x] != 0)
+        atomicAdd((unsigned long long *)&stats[6 + threadIdx.x], (unsigned long long)found[threadIdx.x]);
 }
 
 }   // namespace
@@ -1290,7 +1300,7 @@ hipError_t mmm_launch_stats(const mmm_maps *m, hipStream_t s)
                        m->b_compact ? m->rows_copy : nullptr, m->M, m->K, m->WA, m->WB, m->MT, (int64_t)m->bw, m->stats);
     if (mmm_may_part(m, m->a_dtype) && m->b_dtype == MMM_F32 && m->a_form == m->b_form && m->a_compact == m->b_compact) {
         const int64_t items = (m->MBA + m->NG) * m->KBA;
-        hipLaunchKernelGGL(m->b_form == MMM_FORM_PARTS ? mmm_marks_kernel<true> : mmm_marks_kernel<false>, dim3((uint32_t)((items + 3) / 4)),
+        hipLaunchKernelGGL(m->b_form == MMM_FORM_PARTS ? mmm_marks_kernel<true> : mmm_marks_kernel<false>, dim3((uint32_t)std::min<int64_t>((items + 3) / 4, 2048)),
                            dim3(256), 0, s, m->a_img, m->a_wild, m->bp_val, m->bp_cnt, m->b_compact ? m->kinfo : nullptr, m->kmap, m->K, m->KBA,
                            m->MBA, m->NG, m->stats);
     }
