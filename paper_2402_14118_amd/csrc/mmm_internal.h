@@ -10,6 +10,17 @@
 
 #include "mmm.h"
 
+// Division of numbers below 2^31 by one that the host knows: q = n * mul / 2^(31 + shift) with shift = ceil(log2 d) and
+// mul = ceil(2^(31 + shift) / d), at most 2^32 - 1: the product exceeds n / d by less than 1 / d.
+struct mmm_divisor { uint32_t mul, shift; };
+inline mmm_divisor mmm_make_divisor(uint32_t d)
+{
+    uint32_t shift = 0;
+    while (shift < 31 && (1u << shift) < d) ++shift;
+    return {(uint32_t)(((1ull << (31 + shift)) + d - 1) / d), shift};
+}
+__host__ __device__ inline uint32_t mmm_divided(uint32_t n, const mmm_divisor &d) { return (uint32_t)((uint64_t)(n * 2u) * d.mul >> 32) >> d.shift; }
+
 // Rows of A summarised by one column-any word.
 constexpr int MMM_COLANY_ROWS = 32;
 // Geometry of the blocks of A: 64 rows x 128 columns, what one step of the matrix kernel keeps in LDS.

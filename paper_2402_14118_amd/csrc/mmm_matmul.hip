@@ -64,9 +64,11 @@ struct MatmulParams {
     const uint16_t *bp_list;
     const uint32_t *bp_cnt;
     const uint32_t *kinfo;   // row-compacted mode: [0] = number of live k (everything above is then over k'); else null
-    int64_t M, N, KBA, NG;
+    int64_t M, N;
+    int32_t KBA, NG;   // below 2^15 and 2^19: leading dimensions are below 2^22
     int32_t tiles_m, tiles_n, panel, split_k, chunks_total, chunks_per_split;
     int32_t accumulate;
+    mmm_divisor by_tiles, by_in_panel, by_panel, by_last_panel, by_split;   // tiles, those of a panel, its columns, those of the last one
     // for the lists without the columns that are zero in the tile (see `filtered`; behind what every kernel reads)
     int32_t bw;
     const uint64_t *bt_bits;    // transposed B map, over k' in row-compacted mode
@@ -194,26 +196,34 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     lds_char *const ring3 = (lds_char *)ring;
     const uint32_t ring_off = (uint32_t)(uintptr_t)ring3;
 
+    // What stands in front of the first load is a chain of round trips for arguments and of scalar arithmetic that sixteen waves share one
+    // unit for: 2700 cycles of a kernel's 26000 to 50000 (777 x 3001 x 1992 half, 2048^3 floats, p = .1).  So everything the start needs of
+    // the arguments is asked for at once (left to itself the compiler asks where it is used: four round trips), divisors come from the host, and
+    // products are 32 bits wide where sizes allow it: first barrier 5400 -> 4970 cycles behind the start with the first two.  Passes 35.30 -> 35.06 and 21.23 -> 21.10 us.
+    asm volatile("" ::"s"(p.a_img), "s"(p.bp_val), "s"(p.bp_list), "s"(p.bp_cnt), "s"(p.kinfo), "s"(p.KBA), "s"(p.NG), "s"(p.tiles_m), "s"(p.tiles_n),
+                 "s"(p.panel), "s"(p.split_k), "s"(p.chunks_total), "s"(p.chunks_per_split), "s"(p.by_tiles.mul), "s"(p.by_tiles.shift), "s"(p.by_in_panel.mul),
+                 "s"(p.by_in_panel.shift), "s"(p.by_panel.mul), "s"(p.by_panel.shift), "s"(p.by_last_panel.mul), "s"(p.by_last_panel.shift));
+
     // Splits of K one after another, the tiles of each in panels of `panel` tile columns (see panel_width).
-    // (Divisions run on the vector ALU; the results are put back where addresses are formed.)
     // (The number of workgroups is worked out: the launch's own word for it lies behind all arguments, a cache line on.  512 x 8192 x
     // 4096 bf16, the pass: 27.66 -> 27.34 us.)
     const uint32_t tiles = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n, in_panel = (uint32_t)p.tiles_m * (uint32_t)p.panel;
     const uint32_t L = xcd_contiguous_id(blockIdx.x, tiles * (uint32_t)p.split_k);
-    const int split = __builtin_amdgcn_readfirstlane((int)(p.split_k > 1 ? L / tiles : 0u));
-    const uint32_t t = L - (uint32_t)split * tiles, n0 = t / in_panel * (uint32_t)p.panel;
-    const uint32_t width = min((uint32_t)p.panel, (uint32_t)p.tiles_n - n0), u = t - n0 * (uint32_t)p.tiles_m, row = u / width;
-    const int tile_m = __builtin_amdgcn_readfirstlane((int)row);
-    const int tile_n = __builtin_amdgcn_readfirstlane((int)(n0 + u - row * width));
-    const int64_t row0 = (int64_t)tile_m * TM;
+    const int split = (int)mmm_divided(L, p.by_tiles);
+    const uint32_t t = L - (uint32_t)split * tiles, n0 = mmm_divided(t, p.by_in_panel) * (uint32_t)p.panel;
+    const bool last_panel = n0 + (uint32_t)p.panel >= (uint32_t)p.tiles_n;
+    const uint32_t width = last_panel ? (uint32_t)p.tiles_n - n0 : (uint32_t)p.panel, u = t - n0 * (uint32_t)p.tiles_m;
+    const uint32_t row = mmm_divided(u, last_panel ? p.by_last_panel : p.by_panel);
+    const int tile_m = (int)row;
+    const int tile_n = (int)(n0 + u - row * width);
     // steps of this workgroup; in row-compacted mode only the steps that hold a live k exist, shared out anew
     int chunks_live = p.chunks_total, per_split = p.chunks_per_split;
     if (p.kinfo != nullptr) {
         chunks_live = (int)((*p.kinfo + (uint32_t)KC - 1) / (uint32_t)KC);
-        per_split = __builtin_amdgcn_readfirstlane((chunks_live + p.split_k - 1) / p.split_k);
+        per_split = (int)mmm_divided((uint32_t)(chunks_live + p.split_k - 1), p.by_split);
     }
     const int wg_begin = min(split * per_split, chunks_live), wg_end = min(wg_begin + per_split, chunks_live);
-    const int steps = (wg_end - wg_begin + KS - 1) / KS;   // barriers of every wave
+    const int steps = (int)((uint32_t)(wg_end - wg_begin + KS - 1) / KS);   // barriers of every wave
     const int chunk_begin = min(wg_begin + ks * steps, wg_end);
     const int chunk_end = min(chunk_begin + steps, wg_end);
 
@@ -229,20 +239,21 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         for (int r = 0; r < RT; ++r) rest[g][r] = tile_t{0, 0, 0, 0};
 
     // this wave's groups; a wave past the last column walks the last group's addresses and multiplies nothing
-    const int64_t G0 = ((int64_t)tile_n * NW + wave) * GW;
+    const int G0 = (tile_n * NW + wave) * GW;
     const bool active = G0 < p.NG;
-    const int64_t Gc = min(G0, p.NG - 1);
+    const int Gc = min(G0, p.NG - 1);
+    const uint64_t seg0 = (uint64_t)(uint32_t)Gc * (uint32_t)p.KBA;   // the group's first segment
     // Buffer resources: an operand load is then a register of lane offsets, a scalar step offset and an immediate, with
     // no address arithmetic on the vector ALU.  A group's area is below 2^31 bytes (K < 2^22).
     const __amdgpu_buffer_rsrc_t val_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char *>(p.bp_val) + Gc * p.KBA * SEGB, 0, (int)(min(p.NG - Gc, (int64_t)GW) * p.KBA * SEGB), 0x00020000);
+        const_cast<char *>(p.bp_val) + seg0 * SEGB, 0, (GW == 1 ? 1 : min(p.NG - Gc, GW)) * p.KBA * SEGB, 0x00020000);
     const __amdgpu_buffer_rsrc_t list_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<uint16_t *>(p.bp_list) + Gc * p.KBA * KC, 0, (int)(p.KBA * KC * 2), 0x00020000);
-    const int val_next = (int)(p.KBA * SEGB);   // second group of a 32-wide block (N is a multiple of 32 then)
-    const uint32_t *const cnt0 = p.bp_cnt + Gc * p.KBA;
+        const_cast<uint16_t *>(p.bp_list) + seg0 * KC, 0, p.KBA * KC * 2, 0x00020000);
+    const int val_next = p.KBA * SEGB;   // second group of a 32-wide block (N is a multiple of 32 then)
+    const uint32_t *const cnt0 = p.bp_cnt + seg0;
 
     // ---- A: block ch of this row tile to place ch mod RING (the builder's list entries assume that place)
-    const char *src = p.a_img + ((size_t)tile_m * p.KBA + chunk_begin) * SLAB;   // the next block to copy
+    const char *src = p.a_img + ((uint64_t)(uint32_t)tile_m * (uint32_t)p.KBA + (uint32_t)chunk_begin) * SLAB;   // the next block to copy
     int to_copy = chunk_end - chunk_begin;                                       // blocks from there on
     const uint32_t dma_v = (uint32_t)(wave * DMA * 1024 + lane * 16);
     const uint32_t place0 = ring_off + (uint32_t)(wave * DMA * 1024);
@@ -461,7 +472,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // Floats only.  16-bit lists are multiplied in little more time than such steps take (2048 x 16384 x 4096 as above: 284 and
     // 171 us with plain lists), doubles have the pair kernel, whose work is the surviving products.
     const int64_t any_row0 = (int64_t)tile_m * (TM / MMM_COLANY_ROWS), any_row1 = min(any_row0 + 1, p.MT - 1);
-    const int64_t blk0 = p.bw == 8 ? Gc * 2 : Gc / GW, blk1 = min(p.bw == 8 ? blk0 + 1 : blk0, p.NB - 1);
+    const int64_t blk0 = p.bw == 8 ? (int64_t)Gc * 2 : Gc / GW, blk1 = min(p.bw == 8 ? blk0 + 1 : blk0, p.NB - 1);
     auto filtered = [&]() __attribute__((always_inline)) {
         struct Slots {
             elem_t bf[WIDE ? GW : 1][4];
@@ -471,7 +482,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         constexpr uint32_t ZERO = mmm_zero_col(RING);   // of slots past the end; no other column has this bit
         static_assert(!FILTER || ZERO == 256, "nine bits");
         uint16_t *const lst = lists + (FILTER ? wave_all * 2 * KC : 0);
-        const char *const vals = p.bp_val + Gc * p.KBA * SEGB;
+        const char *const vals = p.bp_val + seg0 * SEGB;
         typedef const __attribute__((address_space(4))) uint64_t scalar_words;   // (the same for all lanes)
         scalar_words *const occ_row0 = (scalar_words *)(p.bt_bits + blk0 * p.WA), *const occ_row1 = (scalar_words *)(p.bt_bits + blk1 * p.WA);
         scalar_words *const any_of0 = (scalar_words *)(p.a_colany + any_row0 * p.WA), *const any_of1 = (scalar_words *)(p.a_colany + any_row1 * p.WA);
@@ -579,9 +590,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     if (chunk_begin < chunk_end) {
         // Lane i: length of the list of step i from there on.
         auto lengths = [&](int from) __attribute__((always_inline)) -> uint32_t {
-            const bool there = active && from + lane < chunk_end;
-            uint32_t n = there ? cnt0[from + lane] : 0u;
-            if (PARTED && GW > 1) n |= there ? cnt0[p.KBA + from + lane] & 0x80000000u : 0u;   // (the mark of either group)
+            // (past the last step, and of a wave without columns: past the end of the buffer, which reads as zero)
+            const int bytes = active ? max(chunk_end - from, 0) * 4 : 0;
+            auto of_group = [&](int g) { return __builtin_amdgcn_raw_buffer_load_b32(__builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(cnt0) + g * p.KBA + from, 0, bytes, 0x00020000), lane * 4, 0, 0); };
+            uint32_t n = of_group(0);
+            if (PARTED && GW > 1) n |= of_group(1) & 0x80000000u;   // (the mark of either group)
             return n;
         };
         // Floats in parts: those of the first steps, and whether a block of this row tile is marked, are asked for ahead of the
@@ -593,7 +606,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             request_at(B0, (uint32_t)chunk_begin * PER_STEP);
         }
         if constexpr (PARTED) {
-            for (int64_t i = lane; i < p.KBA; i += 64) marks |= p.a_wild[tile_m * p.KBA + i];
+            for (int i = lane; i < p.KBA; i += 64) marks |= p.a_wild[(int64_t)tile_m * p.KBA + i];
             asm volatile("" ::: "memory");
         }
 #pragma unroll
@@ -646,7 +659,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                         k0 = p.kmap[(int64_t)ch * KC];
                         k1 = p.kmap[min((uint32_t)(ch + 1) * KC, *p.kinfo) - 1u];
                     }
-                    for (int64_t j = k0 / KC; j <= k1 / KC; ++j) bits |= p.a_wild[tile_m * p.KBA + j] != 0 ? 1u << i : 0u;
+                    for (int64_t j = k0 / KC; j <= k1 / KC; ++j) bits |= p.a_wild[(int64_t)tile_m * p.KBA + j] != 0 ? 1u << i : 0u;
                 }
                 step_marks[w] = bits;
             }
@@ -727,8 +740,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     if (GW > 1) m |= cnt0[p.KBA + ch];
                     if (a_marked) m |= step_marks[(ch - chunk_begin) >> 5] << (31 - ((ch - chunk_begin) & 31)) & 0x80000000u;
                     if ((int)m >= 0) continue;
-                    const uint16_t *const list = p.bp_list + (Gc * p.KBA + ch) * KC;
-                    const char *const block = p.a_img + ((size_t)tile_m * p.KBA + ch) * SLAB;   // (rows past M hold zeros)
+                    const uint16_t *const list = p.bp_list + (seg0 + ch) * KC;
+                    const char *const block = p.a_img + ((int64_t)tile_m * p.KBA + ch) * SLAB;   // (rows past M hold zeros)
 #pragma unroll 1
                     for (uint32_t i = 0; i < n; i += 4) {
                         const uint32_t slot = min(i + (uint32_t)s, n - 1u);
@@ -742,7 +755,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                         }
 #pragma unroll
                         for (int g = 0; g < GW; ++g) {   // (blocks that are off and columns past N hold zeros)
-                            const char *const seg = p.bp_val + ((Gc + g) * p.KBA + ch) * SEGB + (slot / BATCH) * (PARTS * 1024);
+                            const char *const seg = p.bp_val + ((int64_t)(Gc + g) * p.KBA + ch) * SEGB + (slot / BATCH) * (PARTS * 1024);
                             const float v = mmm_whole_float(seg + mmm_value_pos(2, slot % BATCH, (uint32_t)c) * 2u, 1024);
                             const float b = there ? v : 0.f;
 #pragma unroll
@@ -787,7 +800,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // time, then stores 64-byte row pieces with 16-byte lanes.
     // (A row of doubles is 128 bytes in 16 lanes as it is.)
     elem_t *out = p.split_k > 1 ? static_cast<elem_t *>(p.P) + (int64_t)split * p.M * p.N : static_cast<elem_t *>(p.C);
-    const int64_t ldo = p.split_k > 1 ? p.N : p.ldc;
+    const int64_t ldo = p.split_k > 1 ? p.N : p.ldc, row0 = (int64_t)tile_m * TM;
     const bool add = p.split_k == 1 && p.accumulate;
     constexpr int PIECE = RING * SLAB / NW;   // bytes of the (first) ring per wave
     constexpr int RP = PIECE / 1024 < RT ? PIECE / 1024 : RT;   // row tiles (1 KiB each) laid out at a time
@@ -795,7 +808,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     const bool vec_ok = !F64 && reinterpret_cast<uintptr_t>(out) % 16 == 0 && ldo % 4 == 0;
 #pragma unroll
     for (int g = 0; g < GW; ++g) {
-        const int64_t col0 = (G0 + g) * 16;
+        const int64_t col0 = (int64_t)(G0 + g) * 16;
         if (vec_ok && col0 + 16 <= p.N) {
             float *mine = reinterpret_cast<float *>(ring + wave * PIECE);
 #pragma unroll
@@ -980,8 +993,8 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     p.MT = m->MT;
     p.M = m->M;
     p.N = m->N;
-    p.KBA = m->KBA;
-    p.NG = m->NG;
+    p.KBA = (int32_t)m->KBA;
+    p.NG = (int32_t)m->NG;
     p.tiles_m = pl.tiles_m;
     p.tiles_n = pl.tiles_n;
     p.panel = pl.panel;
@@ -989,6 +1002,12 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     p.chunks_total = pl.chunks_total;
     p.chunks_per_split = pl.chunks_per_split;
     p.accumulate = accumulate;
+    const uint32_t tiles = (uint32_t)pl.tiles_m * (uint32_t)pl.tiles_n;
+    p.by_tiles = mmm_make_divisor(tiles);
+    p.by_in_panel = mmm_make_divisor((uint32_t)pl.tiles_m * (uint32_t)pl.panel);
+    p.by_panel = mmm_make_divisor((uint32_t)pl.panel);
+    p.by_last_panel = mmm_make_divisor((uint32_t)((pl.tiles_n - 1) % pl.panel + 1));
+    p.by_split = mmm_make_divisor((uint32_t)pl.split_k);
     if (pl.workgroups <= 0 || pl.workgroups > 0x7fffffffLL) return hipErrorInvalidValue;
     if (pl.split_k > 1 && (size_t)pl.split_k * (size_t)m->M * (size_t)m->N * (f64 ? sizeof(double) : sizeof(float)) > partial_bytes)
         return hipErrorInvalidValue;
