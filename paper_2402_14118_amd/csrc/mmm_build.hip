@@ -1211,8 +1211,14 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     // Blocks of A per workgroup: as many as leave every CU the two workgroups that fit, up to eight, so that one load
     // phase stands in front of several blocks and the others hide behind the stores of the block before (2048 x 16384
     // ReLU: 50.7, 42.1, 38.2 us with one, two, four; a 2048^2 matrix, 512 blocks, wants one: 10.0 against 13.4 with four).
+    // Between 512 and 1024 blocks one each leaves a second round of workgroups that is half empty: two each from 600 of
+    // them on, where both sides make 704 workgroups or more (one, then two each, floats and 16-bit: 640 blocks of A beside
+    // 80 workgroups of B 10.1 -> 9.8 and 8.7 -> 7.6 us, 784 beside 112 12.1 -> 11.2 and 9.6 -> 7.9, 784 of A alone
+    // 11.0 -> 10.3 and 8.7 -> 7.6).  With fewer the short second round costs less than two blocks in turn (640 of A alone
+    // 8.9 -> 9.2 and 7.2 -> 7.5, 512 beside 64 8.3 -> 8.7 and 7.2 -> 7.3; whole passes over 528 to 575 .98 to 1.01).
     int64_t per_wg = n_a / 512;
     per_wg = per_wg < 1 ? 1 : per_wg > 8 ? 8 : per_wg;
+    if (per_wg == 1 && n_a >= 600 && n_a + n_b_wg >= 704) per_wg = 2;
     if (per_wg > m->MBA) per_wg = m->MBA;
     const int64_t n_a_wg = a.X ? (m->MBA + per_wg - 1) / per_wg * p.a_units : 0;
     const int64_t n_all = n_a_wg + n_b_wg;

@@ -82,6 +82,16 @@ def test_many_blocks_per_builder_workgroup(M, p_rows, dtype):
     _run(w)
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16, synth.DT_F16], ids=["f32", "bf16", "f16"])
+@pytest.mark.parametrize("M,K,N,p_rows", [
+    (389, 11400, 32, 1.0),     # 630 blocks of A, seven below each other: two, two, two and a ragged one per workgroup
+    (129, 25600, 16, 0.1),     # 600 in three rows: the fewest that go in twos
+    (70, 65400, 16, 1.0),      # 1022 in two rows: the most
+])
+def test_two_blocks_per_builder_workgroup(M, K, N, p_rows, dtype):
+    _run(synth.random_masked(M, K, N, 16, 0.1, 0.1, M, dist="smallint", dtype=dtype, p_rows=p_rows))
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 def test_every_variant_and_row_count(dtype):
     for variant in range(mm.mmm_matmul_variant_count()):
