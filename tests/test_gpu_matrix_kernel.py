@@ -92,6 +92,14 @@ def test_two_blocks_per_builder_workgroup(M, K, N, p_rows, dtype):
     _run(synth.random_masked(M, K, N, 16, 0.1, 0.1, M, dist="smallint", dtype=dtype, p_rows=p_rows))
 
 
+@pytest.mark.parametrize("M,N,split", [(2100, 16, 1), (40, 4112, 3), (1000, 2576, 1), (1030, 3344, 4)])
+def test_numbering_of_tiles(M, N, split):
+    """One column of tiles, one row of them, panels of tile columns with a narrower last one: every tile once, whatever its size."""
+    for variant in range(mm.mmm_matmul_variant_count()):
+        print("variant", variant, flush=True)
+        _run(synth.random_masked(M, 260, N, 16, 0.2, 0.3, M + N, dist="smallint", dtype=synth.DT_BF16), split, variant)
+
+
 @pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
 def test_every_variant_and_row_count(dtype):
     for variant in range(mm.mmm_matmul_variant_count()):
@@ -154,3 +162,18 @@ def test_pair_kernel_shapes(M, K, N, bw, dtype):
         torch.cuda.synchronize()
         np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
         assert torch.isnan(run.Cbuf[:, N:]).all()
+
+
+@pytest.mark.parametrize("dtype", DTYPES, ids=IDS)
+@pytest.mark.parametrize("K", [1, 7, 8, 9, 63, 64, 65, 4097, 66001])
+@pytest.mark.parametrize("M,ldx_more", [(3, 0), (19, 1)])
+def test_fused_mask_without_a_bitmap(M, ldx_more, K, dtype):
+    """The multiplication that evaluates the mask, where no bitmap is given: whole groups of eight k and what is left of them."""
+    w = synth.random_masked(M, K, 72, 8, 0.5, 0.4, 7 * K + M, dist="smallint", dtype=dtype)
+    w.keep_a, w.pred, w.threshold = None, synth.PRED_GT, 0.0
+    C_ref = oracle.run_workload(w)[2]
+    run = HipRun(w, ldx=K + ldx_more)
+    run.build(a=False, b=True)
+    run.eng.matmul_fused(run.X, run.Y, run.C, w.pred, w.threshold, None)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
