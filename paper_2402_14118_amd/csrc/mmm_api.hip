@@ -177,6 +177,7 @@ MatrixProblem matrix_problem(const mmm_maps *m, int32_t dt, int32_t form)
     if (q.filtered) listed *= m->stats_active;
     q.steps = (rows + MMM_AB_COLS - 1) / MMM_AB_COLS;
     q.batches = listed > 0.5 * batch ? listed / batch + 0.5 : 1.0;
+    if (form == MMM_FORM_PARTS) q.batches = std::max(listed / MMM_UNIT + 0.5, 3.0) * MMM_UNIT / batch;   // (put together from units, three a step at least)
     q.units = esz == 2 ? q.batches : listed / 4.0 + 0.5;
     const double b_marked = m->bw == 32 ? 1.0 - (1.0 - m->stats_marked_b) * (1.0 - m->stats_marked_b) : m->stats_marked_b;   // (a wave has two groups)
     q.marked = form == MMM_FORM_PARTS && known ? 1.0 - (1.0 - m->stats_marked_a) * (1.0 - b_marked) : 0.0;

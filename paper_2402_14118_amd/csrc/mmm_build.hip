@@ -695,7 +695,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
     }
     constexpr int RING = mmm_ring(LSZ);
     // (floats in parts: their ring has no zero column; the block's first, which exists if there is a list, does as well)
-    const uint32_t ZERO_ENTRY = mmm_list_entry(LSZ, PARTED ? ((uint32_t)seg & (RING - 1u)) * SEG : mmm_zero_col(RING));
+    const uint32_t ZERO_ENTRY = mmm_list_entry(LSZ, PARTED ? (uint32_t)seg % (uint32_t)RING * SEG : mmm_zero_col(RING));
     static_assert(B_GROUPS * SEG * 2 <= BUILD_THREADS * 4, "at most one list word per thread");
     if (threadIdx.x < B_GROUPS * SEG / 2) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
     // (Read where all lanes are: a value first read, or made wider, on one side of a branch is taken for one of each lane, and a store through a
@@ -726,7 +726,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
         const uint32_t j = (uint32_t)(j0 + lane % LPG);
         if ((gb >> j) & 1u)
             sh.list[lane / LPG][mmm_list_pos(LSZ, slot0 + (uint32_t)__popc(gb & ((1u << j) - 1u)))] =
-                (uint16_t)mmm_list_entry(LSZ, ((uint32_t)seg & (RING - 1u)) * SEG + (uint32_t)(wave * B_ROWS) + j);
+                (uint16_t)mmm_list_entry(LSZ, (uint32_t)seg % (uint32_t)RING * SEG + (uint32_t)(wave * B_ROWS) + j);
     }
     if (!PARTED && wave == 0 && lane % LPG == 0 && group_ok) {
         uint32_t pitch = KBA, at = seg;
@@ -765,7 +765,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
             const uint8_t *const block_rows = sh.bbits[wave * LPG + (c >= 8u ? LPB : 0)];   // of this lane's half of the group, if it is one
             bool wild = false;
 #pragma unroll 1
-            for (uint32_t slot = 4u * s4; (int)(slot - 4u * s4) < (int)n_out; slot += 32, out += MMM_PARTS * 1024) {
+            for (uint32_t slot = MMM_UNIT * s4; slot < n_out; slot += 32, out += MMM_PARTS * 1024) {   // (units past the last are not read)
                 auto value = [&](uint32_t entry, uint32_t at) __attribute__((always_inline)) -> uint32_t {
                     const uint32_t k = (entry >> 3) & (SEG - 1u);   // see mmm_list_entry
                     bool there = at < n_out && col_ok;
@@ -776,7 +776,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
                 const u32x4 entries = *reinterpret_cast<const u32x4 *>(&sh.list[wave][mmm_list_pos(LSZ, slot)]);
                 uint32_t v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = value(entries[i % 4] >> (i / 4 * 16), slot + (uint32_t)(i / 4 * 16 + i % 4));
+                for (int i = 0; i < 8; ++i) v[i] = value(entries[i % 4] >> (i / 4 * 16), slot + (uint32_t)i);
                 OutOfRange here;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) here.see(v[i]);
@@ -792,7 +792,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
                     wild = true;
 #pragma unroll 1
                     for (uint32_t i = 0; i < 8; ++i) {
-                        const uint32_t at = slot + i / 4 * 16 + i % 4, bits = value(sh.list[wave][mmm_list_pos(LSZ, at)], at);
+                        const uint32_t at = slot + i, bits = value(sh.list[wave][mmm_list_pos(LSZ, at)], at);
                         if (!out_of_range(bits)) continue;
                         uint16_t *const to = reinterpret_cast<uint16_t *>(out) + i;
                         to[0] = (uint16_t)(bits >> 16);
@@ -1285,7 +1285,7 @@ __global__ __launch_bounds__(64) void mmm_k_lists_kernel(const uint64_t *a_colan
         for (int h = 0; h < 2; ++h) {
             const uint32_t slot = (uint32_t)(64 * h + lane);
             const uint32_t entry = bp_list[(G * steps + c) * SEG + mmm_list_pos(LSZ, slot)];
-            const uint32_t k = mmm_list_entry_k(LSZ, entry, (uint32_t)(c & (RING - 1)));
+            const uint32_t k = mmm_list_entry_k(LSZ, entry, (uint32_t)c % (uint32_t)RING);
             bool in = false;
             if (slot < slots && k < (uint32_t)SEG) {
                 const int64_t w = 2 * c + (k >> 6);

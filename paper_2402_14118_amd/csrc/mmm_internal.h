@@ -66,8 +66,9 @@ __host__ __device__ constexpr uint32_t mmm_img_row(size_t esz, uint32_t col, uin
 constexpr int MMM_GROUP_COLS = 16;
 // Blocks in the ring.  16-bit types take four (64 KiB): a step of the kernel is short then, and a block is requested three
 // steps before it is needed.  Floats and doubles take two (64, 128 KiB); four floats deep measured no faster (2048^3,
-// p = .1: 28.8 against 29.2 us) and leaves no room for a second ring or workgroup.
-constexpr int mmm_ring(size_t esz) { return esz == 2 ? 4 : 2; }
+// p = .1: 28.8 against 29.2 us) and leaves no room for a second ring or workgroup.  Floats in parts take three (144 KiB): a batch of their
+// lists reaches into the next block (see MMM_UNIT).
+constexpr int mmm_ring(size_t esz) { return esz == 2 ? 4 : esz == 6 ? 3 : 2; }
 __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t)ring * MMM_AB_COLS; }
 // Floats in parts.  The other form of float operands: every element as the sum of three bf16 numbers, each the rounded rest of
 // what the ones before leave (8 + 8 + 8 significant bits: nothing is lost), which the 16-bit matrix instructions multiply.  Of the
@@ -81,7 +82,10 @@ __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t
 // them): its three parts hold its bits instead (MMM_PARTS_RAW), a block of A and a segment of a group of B that have one are marked,
 // and are multiplied as floats, put together again (mmm_whole_float).
 // Image: [block of 64 x 128][part][column][64 rows], columns as of the 16-bit types.  Packed B: batches of 32 slots as of the
-// 16-bit types, [batch][part].  As an "element size": 6.
+// 16-bit types but for the order of slots, [batch][part].  As an "element size": 6.
+// Slots come in units of eight: slot 8u + 4h + e of a segment is value 4h + e of [u][c][8], entry h of [8u / 2 + e][2].  A unit is what sixteen
+// lanes of the kernel take, so that a batch can be put together from the units of two segments.
+constexpr int MMM_UNIT = 8;
 constexpr int MMM_PARTS = 3;
 constexpr size_t MMM_PARTS_ESZ = 2 * MMM_PARTS;
 constexpr uint32_t MMM_PARTS_LO = (127 - 110) << 23, MMM_PARTS_HI = (127 + 55) << 23;   // bit patterns of the bounds
@@ -109,11 +113,15 @@ __host__ __device__ constexpr uint32_t mmm_list_entry_k(size_t esz, uint32_t ent
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
 {
-    return esz % 4 == 0 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u) : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
+    return esz == MMM_PARTS_ESZ ? (slot & ~7u) | (slot & 3u) << 1 | ((slot >> 2) & 1u)
+           : esz % 4 == 0       ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u)
+                                : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
 }
 __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, uint32_t col)   // in elements
 {
-    return esz >= 4 ? slot * 16u + col : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
+    return esz == MMM_PARTS_ESZ ? (slot >> 3) * 128u + col * 8u + (slot & 7u)   // (inside a batch)
+           : esz >= 4           ? slot * 16u + col
+                                : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
 }
 // Floats: per 128 k a group lists `all` k, of which `stay` have a non-zero column of A in the tile.  Whether the kernel is
 // faster when it makes the lists without the others (see `filtered` there) than with the lists as packed.  A step then costs

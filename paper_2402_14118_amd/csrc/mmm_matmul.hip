@@ -27,10 +27,11 @@
 //
 // Floats whose lists are long are multiplied in three bf16 parts (FloatParts; see MMM_PARTS in mmm_internal.h and choose_form):
 // six 16-bit matrix instructions for 32 listed k take 100 cycles where the eight float instructions take 261.  A block of A
-// is half as large again, so a ring of two leaves room for one workgroup of 16 waves on a compute unit.  4096^3, p = .4: 426 ->
-// 310 to 326 us (matrix cores 55 % and LDS 50 % busy, clock 1.9 GHz), p = .2: 240 -> 185.  What is left is that between two barriers
-// all waves read from LDS first and multiply then, and that a quarter of the slots fill up last batches.  Tried, and no faster: a third
-// block in the ring, with the copies two steps ahead (167 -> 181 us at p = .1) or the first operands read before the barrier (175); two
+// is half as large again, so the ring leaves room for one workgroup of 16 waves on a compute unit.  4096^3, p = .4: 426 ->
+// 310 to 326 us (matrix cores 55 % and LDS 50 % busy, clock 1.9 GHz), p = .2: 240 -> 185.  There a fifth to a quarter of the slots filled up last
+// batches; now batches run from one list into the next (see `joined`).  What is left is the clock, and that operands come from LDS as fast as
+// the matrix cores take them: all of them read before the first product 366 -> 389 us for the pass, part by part a part ahead 370 -> 370.  Tried
+// before, and no faster: copies two steps ahead (167 -> 181 us at p = .1) or the first operands read before the barrier (175); two
 // lists per wave in turns, eight waves (237 and 378).
 //
 // What bounds it otherwise: dense lists, the matrix cores (4096^3 fp32, p = .4: 437 us, of which 360 are matrix instructions at
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     typedef elem_t avec __attribute__((ext_vector_type(RT)));   // 4- and 8-byte types: A operands of the RT row tiles for one k
 
     constexpr int RING_BYTES = RING * SLAB + (PARTED ? 0 : COLB);
-    static_assert(!PARTED || (RT == TM / 16 && KS == 1 && RING == 2), "");
+    static_assert(!PARTED || (RT == TM / 16 && KS == 1 && RING == 3), "");
     __shared__ __align__(1024) char rings[KS * RING_BYTES];
     static_assert(!FILTER || ESZ == 4, "");
     __shared__ uint32_t step_marks[PARTED ? 1024 : 1];   // marked steps of this row tile, if there are any: K is below 2^22
@@ -257,11 +258,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     int to_copy = chunk_end - chunk_begin;                                       // blocks from there on
     const uint32_t dma_v = (uint32_t)(wave * DMA * 1024 + lane * 16);
     const uint32_t place0 = ring_off + (uint32_t)(wave * DMA * 1024);
-    uint32_t place = (uint32_t)(chunk_begin & (RING - 1)) * SLAB;
+    uint32_t place = (uint32_t)chunk_begin % (uint32_t)RING * SLAB;
     auto copy_block = [&]() __attribute__((always_inline)) {
         copy_to_lds<DMA>(src, dma_v, place0 + place);
         src += SLAB;
-        place = PARTED ? place ^ SLAB : (place + SLAB) & (RING * SLAB - 1);
+        place = place == (RING - 1) * SLAB ? 0 : place + SLAB;
         --to_copy;
     };
 
@@ -429,13 +430,13 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         off_l += SEG_L;
     };
 
-    // ---- 16-bit types and floats in parts: the same with the batches of all steps in one queue, requested three ahead
+    // ---- 16-bit types: the same with the batches of all steps in one queue, requested three ahead
     // whatever steps they belong to.  Above, second batches are requested a step ahead, further ones only when they are next
     // but one, and a list of several costs a request in vain; here none does.  What a turn has to know about its batch (place,
     // slots, whether a step begins with it) stands ready in a lane of `plan`, made 64 batches at a time on the vector ALU, so
     // that a turn takes 18 scalar instructions; with the same worked out by scalar selects it took 31, and short lists lost
     // what long ones won.  The turns past the end, up to two, do nothing.
-    // 4096^3, p = .4: floats in parts 415 -> 373 us (the whole pass), bf16 multiplication 111 -> 102; 512 x 8192 x 4096, bf16,
+    // 4096^3, p = .4, bf16 multiplication 111 -> 102 us; 512 x 8192 x 4096, bf16,
     // 24.3 -> 23.6, p = .4 38.0 -> 35.4.  4- and 8-byte types keep the steps above: their batches are half as large and mostly
     // one to a step, and the queue's beginning costs more than it gives (4096^3, p = .05, floats 89.5 -> 93.7, 2048^3, p = .1,
     // doubles 43.3 -> 45.2).
@@ -458,6 +459,56 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         const int left = (int)(b.what >> LEFT & 63u);
         if (left > 0) multiply(b, left);
         request_at(b, (uint32_t)__builtin_amdgcn_readlane(plan, ++ahead_j));
+    };
+
+    // ---- Floats in parts: lists joined.  A batch takes its four units of eight slots (one for each sixteen lanes) from where the one before
+    // stopped, out of the lists of two neighbouring steps if need be, so that only units are padded and not batches.  A step whose list is short
+    // or empty counts as three units, those past its end empty, and so a batch never reaches further than the next step.  Before a
+    // batch that begins in step t there are the barriers of all steps up to t, two at times; behind that of step t block t + 1 has
+    // landed too, and block t + 2 is copied to the place of t - 1.  Whole passes, against a list's batches by themselves and a ring of two: 4096^3,
+    // p = .4, 378 -> 366 us, p = .2 235.3 -> 232.6, 2048 x 16384 x 4096 ReLU layer with blocks of 32 129.5 -> 121.9.  (Units of the short lists of
+    // 16-bit types, joined, would need their copies, three steps ahead, to be one ahead.)
+    // Lane 4j + s of `plan` holds unit s of the j-th of the next sixteen batches:
+    //   EMPTY | past the end (batch) | barriers before the batch << BARRIERS | the batch has a unit | the unit's place; an empty unit's is that of another of
+    //   its batch, whose columns of A it may name: what an empty step's block holds may be no numbers at all
+    constexpr uint32_t UNITS = KC / MMM_UNIT, EMPTY = 1u << 31, END = 1u << 30, BARRIERS = 21, SOME = 1u << 20, UNIT_PLACE = SOME - 1u;
+    uint32_t counts = 0, starts = 0;   // lane i: slots listed for step base + i, and units before it (less those of step `base` that are done)
+    int base = 0, unit0 = 0;           // unit0: that of lane 0 of `plan`
+    // The lanes' units are looked up a batch early, so that no round trip to LDS stands between the multiplication and the request (4096^3,
+    // p = .4 and .2, the pass: 366.0 -> 362.1 and 235.5 -> 232.6 us; not where a wave has two groups, 121.3 -> 121.9 for the ReLU layer).
+    constexpr bool AHEAD = GW == 1;
+    uint32_t next_unit = 0;
+    auto unit_of = [&](int j) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_ds_bpermute((j * 4 + s) * 4, (int)plan); };
+    auto request_joined = [&](Batch &b, int j) __attribute__((always_inline)) {
+        const uint32_t unit = AHEAD ? next_unit : unit_of(j), at = unit & UNIT_PLACE;
+        if (AHEAD) next_unit = unit_of(min(j + 1, 15));   // (a new plan follows the last)
+        b.what = (uint32_t)__builtin_amdgcn_readlane(plan, j * 4);
+        // (an empty unit's values: past the end of the buffer, which reads as zero)
+        const int at_v = (int)((at >> 2) * (PARTS * 1024u) + (at & 3u) * 256u + c16 | (unit & EMPTY)), at_l = (int)(at * 16u + (uint32_t)(lane & 12));
+        asm volatile("" ::: "memory");   // (as in `request`)
+        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, at_l, 0, 0);
+#pragma unroll
+        for (int g = 0; g < (PARTED ? GW : 0); ++g)
+#pragma unroll
+            for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, at_v + q * 1024, g * val_next, 0);
+        asm volatile("" ::: "memory");
+    };
+    int passed = 1;   // barriers
+    auto joined = [&](Batch &b) __attribute__((always_inline)) {
+        const uint32_t barriers = b.what >> BARRIERS & 3u;
+        if (barriers > 0) {
+            wait_vmem<OPS>();   // (a request at least came after the copies behind the barrier before)
+            asm volatile("s_barrier" ::: "memory");
+            if (to_copy > 0) copy_block();
+            if (barriers > 1) {
+                wait_vmem<0>();
+                asm volatile("s_barrier" ::: "memory");
+                if (to_copy > 0) copy_block();
+            }
+            passed += (int)barriers;
+        }
+        if (b.what & SOME) multiply(b, BATCH);
+        request_joined(b, ++ahead_j);
     };
 
     const int all_steps = WIDE ? (steps + 1) & ~1 : steps;   // steps of `step` and `filtered` go in pairs; the odd one past the end has no list
@@ -603,7 +654,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         uint32_t marks = 0, first_lengths = 0;
         if constexpr (!WIDE) {
             first_lengths = lengths(chunk_begin);
-            request_at(B0, (uint32_t)chunk_begin * PER_STEP);
+            if constexpr (!PARTED) request_at(B0, (uint32_t)chunk_begin * PER_STEP);
         }
         if constexpr (PARTED) {
             for (int i = lane; i < p.KBA; i += 64) marks |= p.a_wild[(int64_t)tile_m * p.KBA + i];
@@ -682,54 +733,109 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 }
             }
         } else {
-            // The next 64 batches, from the lengths n of the steps from `from` on (lane i: step i), `skip` batches of the first
-            // left out: lane j finds the step of batch j as the last one that begins no later.
-            auto window = [&](uint32_t n, int from, int skip) __attribute__((always_inline)) {
-                if constexpr (PARTED) {
-                    if (a_marked && from + lane < chunk_end - chunk_begin) n |= step_marks[(from + lane) >> 5] << (31 - ((from + lane) & 31)) & 0x80000000u;
-                    some_marked |= __ballot((int)n < 0) != 0;
-                    n = (int)n < 0 ? 0u : n;
-                }
-                const int batches = max(((int)n + BATCH - 1) / BATCH, 1) - (lane == 0 ? skip : 0);
-                // (sums and ors over the lanes before, in the vector registers)
-                auto across = [](uint32_t v, auto op) __attribute__((always_inline)) {
-                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));    // row_shr 1, 2, 4, 8
-                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
-                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
-                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
-                    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast 15, 31
-                    return op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
-                };
-                const uint32_t begin = across((uint32_t)batches, [](uint32_t a, uint32_t b) { return a + b; }) - (uint32_t)batches;
-                const auto either = [](uint32_t a, uint32_t b) { return a | b; };
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(across(begin < 32 ? 1u << begin : 0u, either), 63);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(begin >= 32 && begin < 64 ? 1u << (begin - 32) : 0u, either), 63);
-                const uint64_t begun = ((uint64_t)hi << 32 | lo) & (~0ull >> (63 - lane));   // (bit 0 is set)
-                const int i = __popcll(begun) - 1, batch = lane - (63 - __builtin_clzll(begun)) + (i == 0 ? skip : 0);
-                const int left = min((int)__shfl(n, i, 64) - batch * BATCH, BATCH);
-                const uint32_t place = (uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch;
-                plan = from + i < all_steps ? (batch == 0 ? FRESH : 0u) | (uint32_t)max(left, 0) << LEFT | place : PAST | place;
-                asm volatile("" : "+v"(plan));   // waited for here
-                ahead_j = 0;
+            // (sums and ors over the lanes before, in the vector registers)
+            auto across = [](uint32_t v, auto op) __attribute__((always_inline)) {
+                v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));    // row_shr 1, 2, 4, 8
+                v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
+                v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true));
+                v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true));
+                v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast 15, 31
+                return op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
             };
-            window(first_lengths, 0, 0);
-            B0.what = (uint32_t)__builtin_amdgcn_readlane(plan, 0) & ~FRESH;   // (begun here)
-            request_at(B1, (uint32_t)__builtin_amdgcn_readlane(plan, 1));
-            request_at(B2, (uint32_t)__builtin_amdgcn_readlane(plan, 2));
-            ahead_j = 2;
-            wait_vmem<2 * OPS>();   // the blocks so far have landed
-            asm volatile("s_barrier" ::: "memory");
-            if (to_copy > 0) copy_block();
-            do {
-                turn(B0);
-                turn(B1);
-                turn(B2);
-                if (ahead_j > 60) {
-                    const uint32_t place = B2.what & PLACE;
-                    const int step = (int)(place / PER_STEP);
-                    window(lengths(step), step - chunk_begin, (int)(place % PER_STEP));
-                }
-            } while ((int)B0.what >= 0);
+            const auto sum = [](uint32_t a, uint32_t b) { return a + b; };
+            const auto either = [](uint32_t a, uint32_t b) { return a | b; };
+            // bits `at` of all lanes that are below 64
+            auto bits = [&](uint32_t at) __attribute__((always_inline)) -> uint64_t {
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(across(at < 32 ? 1u << at : 0u, either), 63);
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(at >= 32 && at < 64 ? 1u << (at - 32) : 0u, either), 63);
+                return (uint64_t)hi << 32 | lo;
+            };
+            if constexpr (PARTED) {
+                // lengths n of the steps from `from` on (lane i: step i), `done` units of the first left out
+                auto measure = [&](uint32_t n, int from, int done) __attribute__((always_inline)) {
+                    if (a_marked && from + lane < steps) n |= step_marks[(from + lane) >> 5] << (31 - ((from + lane) & 31)) & 0x80000000u;
+                    some_marked |= __ballot((int)n < 0) != 0;
+                    counts = (int)n < 0 ? 0u : n;
+                    const uint32_t units = max((counts + MMM_UNIT - 1) / MMM_UNIT, 3u);
+                    starts = across(units, sum) - units - (uint32_t)done;
+                    base = from;
+                };
+                // `plan` from unit u on
+                auto join = [&](int u) __attribute__((always_inline)) {
+                    int before = __popcll(__ballot((int)starts <= u)) - 1;   // the step it is of; 64 units are of 22 steps at most
+                    if (before + 23 > 64) {
+                        const int done = u - (int)__builtin_amdgcn_readlane(starts, before);
+                        measure(lengths(chunk_begin + base + before), base + before, done);
+                        u = 0;
+                        before = 0;
+                    }
+                    unit0 = u;
+                    const int rel = (int)starts - u;   // (of the steps that begin behind u: 0 of the one in hand does not count)
+                    const int i = before + __popcll(bits(rel > 0 ? (uint32_t)rel : 64u) & (~0ull >> (63 - lane)));
+                    const uint32_t k = (uint32_t)(u + lane - (int)__shfl(starts, i, 64));
+                    const uint32_t listed = (uint32_t)__shfl(counts, i, 64);   // (by all lanes: one that is off gives nothing to others)
+                    const bool there = base + i < steps && k * MMM_UNIT < listed;
+                    const uint32_t at = (uint32_t)(chunk_begin + base + i) * UNITS + k;
+                    uint32_t other = there ? at + 1u : 0u;   // the largest of the batch, if there is one
+                    other = max(other, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)other, 0xb1, 0xf, 0xf, true));   // quad_perm 1 0 3 2, 2 3 0 1
+                    other = max(other, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)other, 0x4e, 0xf, 0xf, true));
+                    const int i_before = (int)__shfl(i, max(lane - 4, 0), 64);
+                    plan = (there ? at : EMPTY | (other > 0u ? other - 1u : 0u)) | (other > 0u ? SOME : 0u) |
+                           (base + i < steps ? (uint32_t)(i - i_before) << BARRIERS : END);
+                    asm volatile("" : "+v"(plan));   // waited for here
+                    ahead_j = 0;
+                    if (AHEAD) next_unit = unit_of(1);   // (batch 0 is in hand)
+                };
+                measure(first_lengths, 0, 0);
+                join(0);
+                if (AHEAD) next_unit = unit_of(0);
+                request_joined(B0, 0);
+                request_joined(B1, 1);
+                request_joined(B2, 2);
+                ahead_j = 2;
+                wait_vmem<3 * OPS>();   // the blocks so far have landed
+                asm volatile("s_barrier" ::: "memory");
+                if (to_copy > 0) copy_block();
+                do {
+                    joined(B0);
+                    joined(B1);
+                    joined(B2);
+                    if (ahead_j > 12) join(unit0 + 4 * ahead_j);
+                } while (!(B0.what & END));
+                for (; passed < steps; ++passed) asm volatile("s_barrier" ::: "memory");   // of the last step, if the last batch begins in the one before
+            } else {
+                // The next 64 batches, from the lengths n of the steps from `from` on (lane i: step i), `skip` batches of the first
+                // left out: lane j finds the step of batch j as the last one that begins no later.
+                auto window = [&](uint32_t n, int from, int skip) __attribute__((always_inline)) {
+                    const int batches = max(((int)n + BATCH - 1) / BATCH, 1) - (lane == 0 ? skip : 0);
+                    const uint32_t begin = across((uint32_t)batches, sum) - (uint32_t)batches;
+                    const uint64_t begun = bits(begin) & (~0ull >> (63 - lane));   // (bit 0 is set)
+                    const int i = __popcll(begun) - 1, batch = lane - (63 - __builtin_clzll(begun)) + (i == 0 ? skip : 0);
+                    const int left = min((int)__shfl(n, i, 64) - batch * BATCH, BATCH);
+                    const uint32_t place = (uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch;
+                    plan = from + i < all_steps ? (batch == 0 ? FRESH : 0u) | (uint32_t)max(left, 0) << LEFT | place : PAST | place;
+                    asm volatile("" : "+v"(plan));   // waited for here
+                    ahead_j = 0;
+                };
+                window(first_lengths, 0, 0);
+                B0.what = (uint32_t)__builtin_amdgcn_readlane(plan, 0) & ~FRESH;   // (begun here)
+                request_at(B1, (uint32_t)__builtin_amdgcn_readlane(plan, 1));
+                request_at(B2, (uint32_t)__builtin_amdgcn_readlane(plan, 2));
+                ahead_j = 2;
+                wait_vmem<2 * OPS>();   // the blocks so far have landed
+                asm volatile("s_barrier" ::: "memory");
+                if (to_copy > 0) copy_block();
+                do {
+                    turn(B0);
+                    turn(B1);
+                    turn(B2);
+                    if (ahead_j > 60) {
+                        const uint32_t place = B2.what & PLACE;
+                        const int step = (int)(place / PER_STEP);
+                        window(lengths(step), step - chunk_begin, (int)(place % PER_STEP));
+                    }
+                } while ((int)B0.what >= 0);
+            }
         }
         if constexpr (PARTED) {
             if (some_marked && active) {   // the marked steps, as floats put together again.  Seldom: no more than correct.
@@ -745,7 +851,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll 1
                     for (uint32_t i = 0; i < n; i += 4) {
                         const uint32_t slot = min(i + (uint32_t)s, n - 1u);
-                        const uint32_t col = mmm_list_entry_k(ESZ, list[mmm_list_pos(ESZ, slot)], (uint32_t)ch & (RING - 1u));
+                        const uint32_t col = mmm_list_entry_k(ESZ, list[mmm_list_pos(ESZ, slot)], (uint32_t)ch % (uint32_t)RING);
                         const bool there = i + (uint32_t)s < n;
                         float a[RT];
 #pragma unroll
@@ -756,7 +862,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll
                         for (int g = 0; g < GW; ++g) {   // (blocks that are off and columns past N hold zeros)
                             const char *const seg = p.bp_val + ((int64_t)(Gc + g) * p.KBA + ch) * SEGB + (slot / BATCH) * (PARTS * 1024);
-                            const float v = mmm_whole_float(seg + mmm_value_pos(2, slot % BATCH, (uint32_t)c) * 2u, 1024);
+                            const float v = mmm_whole_float(seg + mmm_value_pos(ESZ, slot % BATCH, (uint32_t)c) * 2u, 1024);
                             const float b = there ? v : 0.f;
 #pragma unroll
                             for (int r = 0; r < RT; ++r) acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b, acc[g][r], 0, 0, 0);

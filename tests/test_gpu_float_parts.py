@@ -56,6 +56,26 @@ def test_list_lengths(bw):
     check_workload(w, "lengths", exact=True, ldx=K + 3, ldy=N + 5, ldc=N + 1)
 
 
+@pytest.mark.parametrize("marked", [False, True], ids=["held", "marked"])
+@pytest.mark.parametrize("bw,steps", [(16, 47), (32, 23), (8, 9), (16, 3)])
+def test_joined_lists(bw, steps, marked):
+    """Batches take units of eight slots from two neighbouring lists: lengths around whole units, and around the three that a step
+    counts for at least; with every third block of A marked, whose step has no list for the batches around it."""
+    lengths = [0, 7, 8, 9, 24, 25, 1, 16, 17, 120, 0, 0, 23, 31, 33, 32, 26, 56]
+    K, N = steps * 128, 288
+    rng = np.random.default_rng(bw + steps)
+    keep = np.zeros((K, N // bw), bool)
+    for s in range(steps):
+        for b in range(N // bw):   # k = 5 of a segment is in no list
+            k = s * 128 + rng.permutation(np.delete(np.arange(128), 5))[: lengths[(s + b * bw // max(16, bw) * 5) % len(lengths)]]
+            keep[k, b] = True
+    w = synth.random_masked(70, K, N, bw, 0.5, 1.0, 91 + bw, dist="smallint")
+    if marked:
+        w.X[:, 5::384] = np.float32(2.0 ** 60)   # out of the range of parts, and multiplied by nothing
+    w.keep_blocks = synth.pack_bits(keep)
+    check_workload(w, "joined", exact=True)
+
+
 # ---- no less exact than floats as they are ------------------------------------------------------
 @pytest.mark.parametrize("dist", ["normal", "uniform"])
 @pytest.mark.parametrize("scale_x,scale_y", [(1.0, 1.0), (2.0 ** -100, 2.0 ** 40), (1.0, 0.02)])
