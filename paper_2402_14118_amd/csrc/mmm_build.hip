@@ -758,14 +758,14 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
         const uint32_t CG = ct * B_GROUPS + (uint32_t)wave;
         const uint32_t n_out = (uint32_t)__builtin_amdgcn_readlane((int)n, wave * LPG);
         if (CG < NG) {
-            const uint32_t c = (uint32_t)lane & 15u, s4 = (uint32_t)lane >> 4;
+            const uint32_t c = (uint32_t)lane & 15u, s4 = (uint32_t)lane >> 4, swap = (s4 & 1u) << 2;   // (of odd units the halves)
             const bool col_ok = CG * MMM_GROUP_COLS + c < (uint32_t)p.N;
             const char *const ycol = static_cast<const char *>(p.Y) + (CG * MMM_GROUP_COLS + c) * ESZ;
-            char *out = p.bp_val + ((uint64_t)CG * KBA + seg) * (SEG * MMM_GROUP_COLS * LSZ) + lane * 16;
+            char *out = p.bp_val + ((uint64_t)CG * KBA + seg) * (SEG * MMM_GROUP_COLS * LSZ) + s4 * (MMM_PARTS * MMM_UNIT_BYTES) + c * 16;
             const uint8_t *const block_rows = sh.bbits[wave * LPG + (c >= 8u ? LPB : 0)];   // of this lane's half of the group, if it is one
             bool wild = false;
 #pragma unroll 1
-            for (uint32_t slot = MMM_UNIT * s4; slot < n_out; slot += 32, out += MMM_PARTS * 1024) {   // (units past the last are not read)
+            for (uint32_t slot = MMM_UNIT * s4; slot < n_out; slot += 4 * MMM_UNIT, out += 4 * MMM_PARTS * MMM_UNIT_BYTES) {   // (units past the last are not read)
                 auto value = [&](uint32_t entry, uint32_t at) __attribute__((always_inline)) -> uint32_t {
                     const uint32_t k = (entry >> 3) & (SEG - 1u);   // see mmm_list_entry
                     bool there = at < n_out && col_ok;
@@ -773,10 +773,10 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
                     const uint32_t row = ROWS ? (uint32_t)sh.kk[k] : seg * SEG + k;
                     return there ? *reinterpret_cast<const uint32_t *>(ycol + (uint64_t)row * row_bytes) : 0u;
                 };
-                const u32x4 entries = *reinterpret_cast<const u32x4 *>(&sh.list[wave][mmm_list_pos(LSZ, slot)]);
+                const u32x4 entries = *reinterpret_cast<const u32x4 *>(&sh.list[wave][slot]);   // the unit's
                 uint32_t v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = value(entries[i % 4] >> (i / 4 * 16), slot + (uint32_t)i);
+                for (int i = 0; i < 8; ++i) v[i] = value(entries[i % 4] >> (i / 4 * 16), slot + ((uint32_t)i ^ swap));
                 OutOfRange here;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) here.see(v[i]);
@@ -786,18 +786,18 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
                     u32x4 part;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) part[i] = take_part(v[2 * i], v[2 * i + 1]);
-                    *reinterpret_cast<u32x4 *>(out + q * 1024) = part;
+                    *reinterpret_cast<u32x4 *>(out + q * MMM_UNIT_BYTES) = part;
                 }
                 if (odd) {   // seldom: such elements as they are, read once more
                     wild = true;
 #pragma unroll 1
                     for (uint32_t i = 0; i < 8; ++i) {
-                        const uint32_t at = slot + i, bits = value(sh.list[wave][mmm_list_pos(LSZ, at)], at);
+                        const uint32_t at = slot + (i ^ swap), bits = value(sh.list[wave][mmm_list_pos(LSZ, at)], at);
                         if (!out_of_range(bits)) continue;
                         uint16_t *const to = reinterpret_cast<uint16_t *>(out) + i;
                         to[0] = (uint16_t)(bits >> 16);
-                        to[512] = (uint16_t)bits;
-                        to[1024] = MMM_PARTS_RAW;
+                        to[MMM_UNIT_BYTES / 2] = (uint16_t)bits;
+                        to[MMM_UNIT_BYTES] = MMM_PARTS_RAW;
                     }
                 }
             }

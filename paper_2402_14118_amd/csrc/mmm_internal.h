@@ -82,10 +82,13 @@ __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t
 // them): its three parts hold its bits instead (MMM_PARTS_RAW), a block of A and a segment of a group of B that have one are marked,
 // and are multiplied as floats, put together again (mmm_whole_float).
 // Image: [block of 64 x 128][part][column][64 rows], columns as of the 16-bit types.  Packed B: batches of 32 slots as of the
-// 16-bit types but for the order of slots, [batch][part].  As an "element size": 6.
-// Slots come in units of eight: slot 8u + 4h + e of a segment is value 4h + e of [u][c][8], entry h of [8u / 2 + e][2].  A unit is what sixteen
-// lanes of the kernel take, so that a batch can be put together from the units of two segments.
+// 16-bit types but for the order of slots, [unit of slots][part].  As an "element size": 6.
+// Slots come in units of eight: slot 8u + 4h + e of a segment is value 4h' + e of [u][c][8], entry h' of [4u + e][2], with h' = h in even units and
+// 1 - h in odd ones.  A unit is what sixteen lanes of the kernel take, so that a batch can be put together from the units of two segments.  (The
+// columns of A that 32 lanes read at once are half a unit of one and half of the next: of a dense list k .. k + 3 and k + 12 .. k + 15, in different LDS
+// banks.  That half of the LDS cycles of sparse ones are conflicts does not bound the kernel: dealt out by k mod 8, or without any, no faster.)
 constexpr int MMM_UNIT = 8;
+constexpr uint32_t MMM_UNIT_BYTES = 256;   // of one part: [16 columns][8]
 constexpr int MMM_PARTS = 3;
 constexpr size_t MMM_PARTS_ESZ = 2 * MMM_PARTS;
 constexpr uint32_t MMM_PARTS_LO = (127 - 110) << 23, MMM_PARTS_HI = (127 + 55) << 23;   // bit patterns of the bounds
@@ -113,13 +116,13 @@ __host__ __device__ constexpr uint32_t mmm_list_entry_k(size_t esz, uint32_t ent
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
 {
-    return esz == MMM_PARTS_ESZ ? (slot & ~7u) | (slot & 3u) << 1 | ((slot >> 2) & 1u)
+    return esz == MMM_PARTS_ESZ ? (slot & ~7u) | (slot & 3u) << 1 | ((slot >> 2 ^ slot >> 3) & 1u)
            : esz % 4 == 0       ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u)
                                 : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
 }
 __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, uint32_t col)   // in elements
 {
-    return esz == MMM_PARTS_ESZ ? (slot >> 3) * 128u + col * 8u + (slot & 7u)   // (inside a batch)
+    return esz == MMM_PARTS_ESZ ? col * 8u + ((slot & 7u) ^ (slot >> 1 & 4u))   // (inside a unit)
            : esz >= 4           ? slot * 16u + col
                                 : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
 }

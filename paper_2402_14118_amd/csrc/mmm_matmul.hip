@@ -466,37 +466,44 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // or empty counts as three units, those past its end empty, and so a batch never reaches further than the next step.  Before a
     // batch that begins in step t there are the barriers of all steps up to t, two at times; behind that of step t block t + 1 has
     // landed too, and block t + 2 is copied to the place of t - 1.  Whole passes, against a list's batches by themselves and a ring of two: 4096^3,
-    // p = .4, 378 -> 366 us, p = .2 235.3 -> 232.6, 2048 x 16384 x 4096 ReLU layer with blocks of 32 129.5 -> 121.9.  (Units of the short lists of
+    // p = .4, 382 -> 366 us, p = .2 237.4 -> 230.2, 2048 x 16384 x 4096 ReLU layer with blocks of 32 129.1 -> 122.6, p = .3 with blocks of 8,
+    // multiplication, 380 -> 345.  (Units of the short lists of
     // 16-bit types, joined, would need their copies, three steps ahead, to be one ahead.)
-    // Lane 4j + s of `plan` holds unit s of the j-th of the next sixteen batches:
-    //   EMPTY | past the end (batch) | barriers before the batch << BARRIERS | the batch has a unit | the unit's place; an empty unit's is that of another of
-    //   its batch, whose columns of A it may name: what an empty step's block holds may be no numbers at all
-    constexpr uint32_t UNITS = KC / MMM_UNIT, EMPTY = 1u << 31, END = 1u << 30, BARRIERS = 21, SOME = 1u << 20, UNIT_PLACE = SOME - 1u;
+    // Lane j of `plan` holds the j-th of the next batches: END if there is none | barriers before it << BARRIERS | which of its units are
+    // EMPTY | units of the first list, less one << FIRST | units from there to the next segment << JUMP | place of the first unit (below 2^19).
+    // The other units follow the first, with the jump behind the first list's.  (Few scalar instructions to take apart: sixteen waves share one unit.)
+    // The plan is worked out once for 44 batches, as in `window`.  (With a unit in each lane, fetched from there by the lanes it is for, and
+    // sixteen batches to a plan, p = .2 gained 1.5 instead of 3 %.)  What it costs shows where nothing is padded: 2048 x 16384 x 4096, a tenth of the
+    // columns, blocks of 16 all on, multiplication 129 -> 132 us, pass 182 -> 183; three quarters of the blocks on it gains 5 %.
+    constexpr uint32_t UNITS = KC / MMM_UNIT, JUMP = 19, FIRST = 23, EMPTY = 15u << 25, BARRIERS = 29, END = 1u << 31, UNIT_PLACE = (1u << JUMP) - 1u;
+    constexpr int JOINED = 46;         // batches of a plan: 3 units a step at least, and lengths of 64 steps in hand
     uint32_t counts = 0, starts = 0;   // lane i: slots listed for step base + i, and units before it (less those of step `base` that are done)
-    int base = 0, unit0 = 0;           // unit0: that of lane 0 of `plan`
-    // The lanes' units are looked up a batch early, so that no round trip to LDS stands between the multiplication and the request (4096^3,
-    // p = .4 and .2, the pass: 366.0 -> 362.1 and 235.5 -> 232.6 us; not where a wave has two groups, 121.3 -> 121.9 for the ReLU layer).
-    constexpr bool AHEAD = GW == 1;
-    uint32_t next_unit = 0;
-    auto unit_of = [&](int j) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_ds_bpermute((j * 4 + s) * 4, (int)plan); };
-    auto request_joined = [&](Batch &b, int j) __attribute__((always_inline)) {
-        const uint32_t unit = AHEAD ? next_unit : unit_of(j), at = unit & UNIT_PLACE;
-        if (AHEAD) next_unit = unit_of(min(j + 1, 15));   // (a new plan follows the last)
-        b.what = (uint32_t)__builtin_amdgcn_readlane(plan, j * 4);
-        // (an empty unit's values: past the end of the buffer, which reads as zero)
-        const int at_v = (int)((at >> 2) * (PARTS * 1024u) + (at & 3u) * 256u + c16 | (unit & EMPTY)), at_l = (int)(at * 16u + (uint32_t)(lane & 12));
+    int base = 0, unit0 = 0;           // unit0: that lane 0 of `plan` begins with
+    auto request_units = [&](Batch &b, uint32_t what) __attribute__((always_inline)) {
+        b.what = what;
+        const uint32_t place = what & UNIT_PLACE, jump = what >> JUMP & (UNITS - 1u), first = what >> FIRST & 3u;
+        uint32_t at = place + (uint32_t)s + ((uint32_t)s > first ? jump : 0u), past = 0;
+        if (what & EMPTY) {
+            // An empty unit's values: past the end of the buffer, which reads as zero; its columns of A are those of another of its
+            // batch, since what an empty step's block holds may be no numbers at all.
+            const uint32_t empty = (what & EMPTY) / (EMPTY / 15u);
+            const bool there = (empty >> s & 1u) == 0;
+            at = there ? at : empty & 1u ? place + first + 1u + jump : place;
+            past = there ? 0u : 1u << 31;
+        }
+        const int at_v = (int)(at * (PARTS * MMM_UNIT_BYTES) + c16 | past), at_l = (int)(at * (MMM_UNIT * 2u) + (uint32_t)(lane & 12));
         asm volatile("" ::: "memory");   // (as in `request`)
         b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, at_l, 0, 0);
 #pragma unroll
         for (int g = 0; g < (PARTED ? GW : 0); ++g)
 #pragma unroll
-            for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, at_v + q * 1024, g * val_next, 0);
+            for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, at_v + q * (int)MMM_UNIT_BYTES, g * val_next, 0);
         asm volatile("" ::: "memory");
     };
     int passed = 1;   // barriers
     auto joined = [&](Batch &b) __attribute__((always_inline)) {
-        const uint32_t barriers = b.what >> BARRIERS & 3u;
-        if (barriers > 0) {
+        if (b.what & 3u << BARRIERS) {
+            const uint32_t barriers = b.what >> BARRIERS & 3u;
             wait_vmem<OPS>();   // (a request at least came after the copies behind the barrier before)
             asm volatile("s_barrier" ::: "memory");
             if (to_copy > 0) copy_block();
@@ -507,8 +514,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             }
             passed += (int)barriers;
         }
-        if (b.what & SOME) multiply(b, BATCH);
-        request_joined(b, ++ahead_j);
+        if (~b.what & EMPTY) multiply(b, BATCH);
+        request_units(b, (uint32_t)__builtin_amdgcn_readlane(plan, ++ahead_j));
     };
 
     const int all_steps = WIDE ? (steps + 1) & ~1 : steps;   // steps of `step` and `filtered` go in pairs; the odd one past the end has no list
@@ -649,12 +656,15 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             return n;
         };
         // Floats in parts: those of the first steps, and whether a block of this row tile is marked, are asked for ahead of the
-        // copies, so that there is one round trip in front of the first step instead of three (4096^3, p = .4: 359 -> 348 us;
+        // copies, and the first batch too, so that there is one round trip in front of the first step instead of three (4096^3, p = .4: 359 -> 348 us;
         // where two workgroups share a compute unit it makes no difference).
         uint32_t marks = 0, first_lengths = 0;
         if constexpr (!WIDE) {
             first_lengths = lengths(chunk_begin);
-            if constexpr (!PARTED) request_at(B0, (uint32_t)chunk_begin * PER_STEP);
+            if constexpr (PARTED)
+                request_units(B0, (uint32_t)chunk_begin * UNITS | (UNITS - 4u) << JUMP | 3u << FIRST);   // as if the first list had four units
+            else
+                request_at(B0, (uint32_t)chunk_begin * PER_STEP);
         }
         if constexpr (PARTED) {
             for (int i = lane; i < p.KBA; i += 64) marks |= p.a_wild[(int64_t)tile_m * p.KBA + i];
@@ -733,7 +743,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 }
             }
         } else {
-            // (sums and ors over the lanes before, in the vector registers)
+            // (sums, or ors, over the lanes before, in the vector registers)
             auto across = [](uint32_t v, auto op) __attribute__((always_inline)) {
                 v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true));    // row_shr 1, 2, 4, 8
                 v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true));
@@ -743,13 +753,6 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 return op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
             };
             const auto sum = [](uint32_t a, uint32_t b) { return a + b; };
-            const auto either = [](uint32_t a, uint32_t b) { return a | b; };
-            // bits `at` of all lanes that are below 64
-            auto bits = [&](uint32_t at) __attribute__((always_inline)) -> uint64_t {
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(across(at < 32 ? 1u << at : 0u, either), 63);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(at >= 32 && at < 64 ? 1u << (at - 32) : 0u, either), 63);
-                return (uint64_t)hi << 32 | lo;
-            };
             if constexpr (PARTED) {
                 // lengths n of the steps from `from` on (lane i: step i), `done` units of the first left out
                 auto measure = [&](uint32_t n, int from, int done) __attribute__((always_inline)) {
@@ -762,46 +765,49 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 };
                 // `plan` from unit u on
                 auto join = [&](int u) __attribute__((always_inline)) {
-                    int before = __popcll(__ballot((int)starts <= u)) - 1;   // the step it is of; 64 units are of 22 steps at most
-                    if (before + 23 > 64) {
-                        const int done = u - (int)__builtin_amdgcn_readlane(starts, before);
+                    if (base + 64 < steps) {   // lengths of the steps from that of u on
+                        const int before = __popcll(__ballot((int)starts <= u)) - 1, done = u - (int)__builtin_amdgcn_readlane(starts, before);
                         measure(lengths(chunk_begin + base + before), base + before, done);
                         u = 0;
-                        before = 0;
                     }
                     unit0 = u;
-                    const int rel = (int)starts - u;   // (of the steps that begin behind u: 0 of the one in hand does not count)
-                    const int i = before + __popcll(bits(rel > 0 ? (uint32_t)rel : 64u) & (~0ull >> (63 - lane)));
-                    const uint32_t k = (uint32_t)(u + lane - (int)__shfl(starts, i, 64));
-                    const uint32_t listed = (uint32_t)__shfl(counts, i, 64);   // (by all lanes: one that is off gives nothing to others)
-                    const bool there = base + i < steps && k * MMM_UNIT < listed;
-                    const uint32_t at = (uint32_t)(chunk_begin + base + i) * UNITS + k;
-                    uint32_t other = there ? at + 1u : 0u;   // the largest of the batch, if there is one
-                    other = max(other, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)other, 0xb1, 0xf, 0xf, true));   // quad_perm 1 0 3 2, 2 3 0 1
-                    other = max(other, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)other, 0x4e, 0xf, 0xf, true));
-                    const int i_before = (int)__shfl(i, max(lane - 4, 0), 64);
-                    plan = (there ? at : EMPTY | (other > 0u ? other - 1u : 0u)) | (other > 0u ? SOME : 0u) |
-                           (base + i < steps ? (uint32_t)(i - i_before) << BARRIERS : END);
+                    const int unit = u + 4 * lane;
+                    int i = 0;   // the last step that begins no later
+#pragma unroll
+                    for (int d = 32; d > 0; d >>= 1) {
+                        const int start = (int)__shfl(starts, i + d, 64);   // (of all lanes: one that is off gives nothing to others)
+                        i += start <= unit ? d : 0;
+                    }
+                    const uint32_t k = (uint32_t)(unit - (int)__shfl(starts, i, 64)), here = ((uint32_t)__shfl(counts, i, 64) + 7u) / MMM_UNIT;
+                    const uint32_t then = ((uint32_t)__shfl(counts, min(i + 1, 63), 64) + 7u) / MMM_UNIT;
+                    // (past the last step the lists are empty, and the last lane's is as long as it says)
+                    const uint32_t length = max(here, 3u), first = min(max(length, k + 1u) - k, 4u);
+                    const bool ended = base + i >= steps || k >= length;
+                    uint32_t filled = (1u << min(here > k ? here - k : 0u, first)) - 1u;
+                    if (i < 63) filled |= ((1u << min(then, 4u - first)) - 1u) << first;
+                    const uint32_t jump = UNITS - min(k + first, UNITS);
+                    const int i_before = (int)__shfl(i, max(lane - 1, 0), 64);
+                    plan = ended ? END | EMPTY
+                                 : (uint32_t)(chunk_begin + base + i) * UNITS + k | jump << JUMP | (first - 1u) << FIRST | (15u - filled) * (EMPTY / 15u) | (uint32_t)(i - i_before) << BARRIERS;
                     asm volatile("" : "+v"(plan));   // waited for here
                     ahead_j = 0;
-                    if (AHEAD) next_unit = unit_of(1);   // (batch 0 is in hand)
                 };
                 measure(first_lengths, 0, 0);
                 join(0);
-                if (AHEAD) next_unit = unit_of(0);
-                request_joined(B0, 0);
-                request_joined(B1, 1);
-                request_joined(B2, 2);
+                const uint32_t begin = (uint32_t)__builtin_amdgcn_readlane(plan, 0);
+                if (begin != B0.what) request_units(B0, begin);
+                request_units(B1, (uint32_t)__builtin_amdgcn_readlane(plan, 1));
+                request_units(B2, (uint32_t)__builtin_amdgcn_readlane(plan, 2));
                 ahead_j = 2;
-                wait_vmem<3 * OPS>();   // the blocks so far have landed
+                wait_vmem<2 * OPS>();   // the blocks so far have landed
                 asm volatile("s_barrier" ::: "memory");
                 if (to_copy > 0) copy_block();
                 do {
                     joined(B0);
                     joined(B1);
                     joined(B2);
-                    if (ahead_j > 12) join(unit0 + 4 * ahead_j);
-                } while (!(B0.what & END));
+                    if (ahead_j > JOINED - 4) join(unit0 + 4 * ahead_j);
+                } while ((int)B0.what >= 0);
                 for (; passed < steps; ++passed) asm volatile("s_barrier" ::: "memory");   // of the last step, if the last batch begins in the one before
             } else {
                 // The next 64 batches, from the lengths n of the steps from `from` on (lane i: step i), `skip` batches of the first
@@ -809,7 +815,10 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 auto window = [&](uint32_t n, int from, int skip) __attribute__((always_inline)) {
                     const int batches = max(((int)n + BATCH - 1) / BATCH, 1) - (lane == 0 ? skip : 0);
                     const uint32_t begin = across((uint32_t)batches, sum) - (uint32_t)batches;
-                    const uint64_t begun = bits(begin) & (~0ull >> (63 - lane));   // (bit 0 is set)
+                    const auto either = [](uint32_t a, uint32_t b) { return a | b; };
+                    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(across(begin < 32 ? 1u << begin : 0u, either), 63);
+                    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(begin >= 32 && begin < 64 ? 1u << (begin - 32) : 0u, either), 63);
+                    const uint64_t begun = ((uint64_t)hi << 32 | lo) & (~0ull >> (63 - lane));   // (bit 0 is set)
                     const int i = __popcll(begun) - 1, batch = lane - (63 - __builtin_clzll(begun)) + (i == 0 ? skip : 0);
                     const int left = min((int)__shfl(n, i, 64) - batch * BATCH, BATCH);
                     const uint32_t place = (uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch;
@@ -861,8 +870,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                         }
 #pragma unroll
                         for (int g = 0; g < GW; ++g) {   // (blocks that are off and columns past N hold zeros)
-                            const char *const seg = p.bp_val + ((int64_t)(Gc + g) * p.KBA + ch) * SEGB + (slot / BATCH) * (PARTS * 1024);
-                            const float v = mmm_whole_float(seg + mmm_value_pos(ESZ, slot % BATCH, (uint32_t)c) * 2u, 1024);
+                            const char *const unit = p.bp_val + ((int64_t)(Gc + g) * p.KBA + ch) * SEGB + slot / MMM_UNIT * (PARTS * MMM_UNIT_BYTES);
+                            const float v = mmm_whole_float(unit + mmm_value_pos(ESZ, slot, (uint32_t)c) * 2u, MMM_UNIT_BYTES);
                             const float b = there ? v : 0.f;
 #pragma unroll
                             for (int r = 0; r < RT; ++r) acc[g][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r], b, acc[g][r], 0, 0, 0);
@@ -1029,7 +1038,7 @@ struct VariantEntry {
     }
 
 // Floats in parts have 64 x 256 by themselves; the narrower tiles, which leave a compute unit 8 or 4 waves beside the same ring, where they
-// are fixed while the operands are in parts (4096^3, p = .4: 323, 375 and 572 us; 1500 x 2100 x 1024, p_B = .5: 33.5, 31.0 and 48.9).
+// are fixed while the operands are in parts (4096^3, p = .4: 302, 364 and 586 us; 1500 x 2100 x 1024, p_B = .5: 33.7, 30.8 and 47.3).
 const VariantEntry g_variants[] = {
     MMM_VARIANT(4, 8, PARTS_FIXED, MMM_PARTED),   // 0: 64 x 128
     MMM_VARIANT(4, 16, PARTS_OWN, MMM_PARTED),     // 1: 64 x 256
