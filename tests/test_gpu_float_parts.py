@@ -26,7 +26,7 @@ def parts_on_the_matrix_path():
     mm.mmm_set_option("matmul_path", -1)
 
 
-# ---- the edges of tiles, groups, segments, batches of 32 and the two blocks of the ring ----------
+# ---- the edges of tiles, groups, segments, batches of 32 and the blocks of the ring ----------
 @pytest.mark.parametrize("rows", [None, 0.6], ids=["all", "rows"])
 @pytest.mark.parametrize("M,K,N,bw", [(65, 1, 8, 8), (65, 2, 136, 8), (128, 65, 272, 16), (129, 127, 256, 16), (129, 128, 288, 32),
                                       (66, 129, 264, 8), (190, 257, 544, 32), (70, 1030, 48, 16), (200, 8065, 32, 16)])
