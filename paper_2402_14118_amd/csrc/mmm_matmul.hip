@@ -467,37 +467,50 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // batch that begins in step t there are the barriers of all steps up to t, two at times; behind that of step t block t + 1 has
     // landed too, and block t + 2 is copied to the place of t - 1.  Whole passes, against a list's batches by themselves and a ring of two: 4096^3,
     // p = .4, 382 -> 366 us, p = .2 237.4 -> 230.2, 2048 x 16384 x 4096 ReLU layer with blocks of 32 129.1 -> 122.6, p = .3 with blocks of 8,
-    // multiplication, 380 -> 345.  (Units of the short lists of
-    // 16-bit types, joined, would need their copies, three steps ahead, to be one ahead.)
+    // multiplication, 380 -> 345.
     // Lane j of `plan` holds the j-th of the next batches: END if there is none | barriers before it << BARRIERS | which of its units are
-    // EMPTY | units of the first list, less one << FIRST | units from there to the next segment << JUMP | place of the first unit (below 2^19).
-    // The other units follow the first, with the jump behind the first list's.  (Few scalar instructions to take apart: sixteen waves share one unit.)
-    // The plan is worked out once for 44 batches, as in `window`.  (With a unit in each lane, fetched from there by the lanes it is for, and
-    // sixteen batches to a plan, p = .2 gained 1.5 instead of 3 %.)  What it costs shows where nothing is padded: 2048 x 16384 x 4096, a tenth of the
-    // columns, blocks of 16 all on, multiplication 129 -> 132 us, pass 182 -> 183; three quarters of the blocks on it gains 5 %.
-    constexpr uint32_t UNITS = KC / MMM_UNIT, JUMP = 19, FIRST = 23, EMPTY = 15u << 25, BARRIERS = 29, END = 1u << 31, UNIT_PLACE = (1u << JUMP) - 1u;
-    constexpr int JOINED = 46;         // batches of a plan: 3 units a step at least, and lengths of 64 steps in hand
+    // EMPTY | four less its units of the first list << REST | units from there to the next segment << JUMP | place of the first unit (below 2^19).
+    // The other units follow the first, with the jump behind the first list's.  A batch that is four units of one list - most are where lists are
+    // long - is asked for by scalar offsets alone, as plain lists are.
+    // The plan is for the 64 next batches where the lengths in hand (of 64 steps) are known to reach so far or to the end, else for JOINED, and new lengths are
+    // fetched only where even those would not.  (With a unit in each lane, fetched from there by the lanes it is for, and
+    // sixteen batches to a plan, p = .2 gained 1.5 instead of 3 %.)  46 batches always, steps found by six dependent lane reads, lengths fetched for
+    // each plan of more than 64 steps and offsets on the vector ALU, before: multiplication 4096^3, p = .4, 305.4 -> 295 us, 512 x 16384 x 2048, p = .3, 69.3 -> 68.0,
+    // 1024 x 16384 x 4096, blocks of 32, 232 -> 226.5.
+    // Where every list is full, joining gains nothing and costs: 2048 x 16384 x 4096, a tenth of the columns, all blocks of 32 on, 116.4 (a list's batches by themselves),
+    // 119.3 (before), 117.7 now, blocks of 16 123.9, 129.1 and 128.0; three quarters of the blocks of 32 on 103.3, 100.4 and 99.0.
+    constexpr uint32_t UNITS = KC / MMM_UNIT, JUMP = 19, REST = 23, EMPTY = 15u << 25, BARRIERS = 29, END = 1u << 31, UNIT_PLACE = (1u << JUMP) - 1u;
+    constexpr int JOINED = 46;         // batches that the lengths of 64 steps are always enough for: 3 units a step at least
     uint32_t counts = 0, starts = 0;   // lane i: slots listed for step base + i, and units before it (less those of step `base` that are done)
-    int base = 0, unit0 = 0;           // unit0: that lane 0 of `plan` begins with
+    int base = 0, unit0 = 0, planned = 0;   // unit0: that lane 0 of `plan` begins with; planned: batches in it
+    const uint32_t unit_v = (uint32_t)s * (PARTS * MMM_UNIT_BYTES) + c16, unit_l = (uint32_t)lane & 60u;   // a lane's in its unit of four: [s][..]
     auto request_units = [&](Batch &b, uint32_t what) __attribute__((always_inline)) {
         b.what = what;
-        const uint32_t place = what & UNIT_PLACE, jump = what >> JUMP & (UNITS - 1u), first = what >> FIRST & 3u;
-        uint32_t at = place + (uint32_t)s + ((uint32_t)s > first ? jump : 0u), past = 0;
-        if (what & EMPTY) {
-            // An empty unit's values: past the end of the buffer, which reads as zero; its columns of A are those of another of its
-            // batch, since what an empty step's block holds may be no numbers at all.
-            const uint32_t empty = (what & EMPTY) / (EMPTY / 15u);
-            const bool there = (empty >> s & 1u) == 0;
-            at = there ? at : empty & 1u ? place + first + 1u + jump : place;
-            past = there ? 0u : 1u << 31;
+        const uint32_t place = what & UNIT_PLACE;
+        uint32_t at_v = unit_v, at_l = unit_l;   // from the first unit on
+        if ((what & (EMPTY | 3u << REST)) != 0) {   // not four units of one list
+            const uint32_t jump = what >> JUMP & (UNITS - 1u), first = 4u - (what >> REST & 3u);
+            const uint32_t over = unit_l >= first * (MMM_UNIT * 2u) ? jump : 0u;
+            at_v += over * (PARTS * MMM_UNIT_BYTES);
+            at_l += over * (MMM_UNIT * 2u);
+            if (what & EMPTY) {
+                // An empty unit's values: past the end of the buffer, which reads as zero; its columns of A are those of another of its
+                // batch, since what an empty step's block holds may be no numbers at all.
+                const uint32_t empty = (what & EMPTY) / (EMPTY / 15u);
+                uint32_t mine = unit_l;
+                asm volatile("" : "+v"(mine));   // (nothing of this is kept in registers over the loop)
+                const uint32_t off = empty >> (mine >> 4) & 1u;
+                at_v |= off << 31;
+                at_l = off ? (empty & 1u ? first + jump : 0u) * (MMM_UNIT * 2u) + (mine & 12u) : at_l;
+            }
         }
-        const int at_v = (int)(at * (PARTS * MMM_UNIT_BYTES) + c16 | past), at_l = (int)(at * (MMM_UNIT * 2u) + (uint32_t)(lane & 12));
+        const int off_v = (int)(place * (PARTS * MMM_UNIT_BYTES)), off_l = (int)(place * (MMM_UNIT * 2u));
         asm volatile("" ::: "memory");   // (as in `request`)
-        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, at_l, 0, 0);
+        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (int)at_l, off_l, 0);
 #pragma unroll
         for (int g = 0; g < (PARTED ? GW : 0); ++g)
 #pragma unroll
-            for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, at_v + q * (int)MMM_UNIT_BYTES, g * val_next, 0);
+            for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, (int)at_v + q * (int)MMM_UNIT_BYTES, off_v + g * val_next, 0);
         asm volatile("" ::: "memory");
     };
     int passed = 1;   // barriers
@@ -662,7 +675,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         if constexpr (!WIDE) {
             first_lengths = lengths(chunk_begin);
             if constexpr (PARTED)
-                request_units(B0, (uint32_t)chunk_begin * UNITS | (UNITS - 4u) << JUMP | 3u << FIRST);   // as if the first list had four units
+                request_units(B0, (uint32_t)chunk_begin * UNITS | (UNITS - 4u) << JUMP);   // as if the first list had four units
             else
                 request_at(B0, (uint32_t)chunk_begin * PER_STEP);
         }
@@ -765,19 +778,31 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 };
                 // `plan` from unit u on
                 auto join = [&](int u) __attribute__((always_inline)) {
-                    if (base + 64 < steps) {   // lengths of the steps from that of u on
-                        const int before = __popcll(__ballot((int)starts <= u)) - 1, done = u - (int)__builtin_amdgcn_readlane(starts, before);
+                    bool ends = base + 64 >= steps;   // the lengths in hand are all that are left
+                    int reach = (int)__builtin_amdgcn_readlane(starts, 62) - u;
+                    int before = __popcll(__ballot((int)starts <= u)) - 1;   // the step of unit u
+                    if (!ends && reach < 4 * JOINED) {   // lengths of the steps from that one on
+                        const int done = u - (int)__builtin_amdgcn_readlane(starts, before);
                         measure(lengths(chunk_begin + base + before), base + before, done);
-                        u = 0;
+                        u = before = 0;
+                        ends = base + 64 >= steps;
+                        reach = (int)__builtin_amdgcn_readlane(starts, 62);
                     }
+                    planned = ends || reach >= 4 * 64 ? 64 : JOINED;
                     unit0 = u;
                     const int unit = u + 4 * lane;
-                    int i = 0;   // the last step that begins no later
-#pragma unroll
-                    for (int d = 32; d > 0; d >>= 1) {
-                        const int start = (int)__shfl(starts, i + d, 64);   // (of all lanes: one that is off gives nothing to others)
-                        i += start <= unit ? d : 0;
-                    }
+                    // The last step that begins no later.  Bit j: a step begins in front of batch j + 1 and behind j, odd and even steps by
+                    // themselves, of which there is one at most.
+                    const uint32_t at = (uint32_t)((int)starts - u - 1) >> 2, bit = 1u << (at & 31u);   // (steps up to that of u: past the last bit)
+                    const auto either = [](uint32_t a, uint32_t b) { return a | b; };
+                    auto begins = [&](bool here) __attribute__((always_inline)) -> uint64_t {
+                        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane(across(here && at < 32u ? bit : 0u, either), 63);
+                        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(here && at >= 32u && at < 64u ? bit : 0u, either), 63);
+                        return (uint64_t)hi << 32 | lo;
+                    };
+                    const uint64_t even = begins((lane & 1) == 0), odd = begins((lane & 1) != 0);
+                    const int i = before + (int)mbcnt64(even) + (int)mbcnt64(odd);
+                    const uint32_t begun = (__builtin_amdgcn_inverse_ballot_w64(even << 1) ? 1u : 0u) + (__builtin_amdgcn_inverse_ballot_w64(odd << 1) ? 1u : 0u);
                     const uint32_t k = (uint32_t)(unit - (int)__shfl(starts, i, 64)), here = ((uint32_t)__shfl(counts, i, 64) + 7u) / MMM_UNIT;
                     const uint32_t then = ((uint32_t)__shfl(counts, min(i + 1, 63), 64) + 7u) / MMM_UNIT;
                     // (past the last step the lists are empty, and the last lane's is as long as it says)
@@ -786,9 +811,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     uint32_t filled = (1u << min(here > k ? here - k : 0u, first)) - 1u;
                     if (i < 63) filled |= ((1u << min(then, 4u - first)) - 1u) << first;
                     const uint32_t jump = UNITS - min(k + first, UNITS);
-                    const int i_before = (int)__shfl(i, max(lane - 1, 0), 64);
                     plan = ended ? END | EMPTY
-                                 : (uint32_t)(chunk_begin + base + i) * UNITS + k | jump << JUMP | (first - 1u) << FIRST | (15u - filled) * (EMPTY / 15u) | (uint32_t)(i - i_before) << BARRIERS;
+                                 : (uint32_t)(chunk_begin + base + i) * UNITS + k | jump << JUMP | (4u - first) << REST | (15u - filled) * (EMPTY / 15u) | begun << BARRIERS;
                     asm volatile("" : "+v"(plan));   // waited for here
                     ahead_j = 0;
                 };
@@ -806,7 +830,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     joined(B0);
                     joined(B1);
                     joined(B2);
-                    if (ahead_j > JOINED - 4) join(unit0 + 4 * ahead_j);
+                    if (ahead_j > planned - 4) join(unit0 + 4 * ahead_j);
                 } while ((int)B0.what >= 0);
                 for (; passed < steps; ++passed) asm volatile("s_barrier" ::: "memory");   // of the last step, if the last batch begins in the one before
             } else {

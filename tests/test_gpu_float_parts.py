@@ -57,10 +57,11 @@ def test_list_lengths(bw):
 
 
 @pytest.mark.parametrize("marked", [False, True], ids=["held", "marked"])
-@pytest.mark.parametrize("bw,steps", [(16, 47), (32, 23), (8, 9), (16, 3)])
+@pytest.mark.parametrize("bw,steps", [(16, 47), (32, 23), (8, 9), (16, 3), (16, 131), (8, 197), (32, 64), (16, 65)])
 def test_joined_lists(bw, steps, marked):
     """Batches take units of eight slots from two neighbouring lists: lengths around whole units, and around the three that a step
-    counts for at least; with every third block of A marked, whose step has no list for the batches around it."""
+    counts for at least; with every third block of A marked, whose step has no list for the batches around it.  Past 64 steps the
+    lengths in hand are at times enough for a plan of 64 batches, at times for 46 and at times to be fetched anew."""
     lengths = [0, 7, 8, 9, 24, 25, 1, 16, 17, 120, 0, 0, 23, 31, 33, 32, 26, 56]
     K, N = steps * 128, 288
     rng = np.random.default_rng(bw + steps)
