@@ -1113,6 +1113,7 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     if (pl.variant < 0 || pl.variant >= kVariants) return hipErrorInvalidValue;
     const VariantEntry &v = g_variants[pl.variant];
     if ((m->M > v.info.rows && v.info.rows < TM) || !mmm_packs(m->M, dtype)) return hipErrorInvalidValue;
+    if (pl.workgroups <= 0 || pl.workgroups > 0x7fffffffLL) return hipErrorInvalidValue;   // (ahead of the divisors: products of fewer tiles are 32 bits wide)
     const bool f64 = dtype == MMM_F64;
     MatmulParams p{};
     p.C = C;
@@ -1147,7 +1148,6 @@ hipError_t mmm_launch_matmul(const mmm_maps *m, const mmm_plan &pl, int32_t dtyp
     p.by_panel = mmm_make_divisor((uint32_t)pl.panel);
     p.by_last_panel = mmm_make_divisor((uint32_t)((pl.tiles_n - 1) % pl.panel + 1));
     p.by_split = mmm_make_divisor((uint32_t)pl.split_k);
-    if (pl.workgroups <= 0 || pl.workgroups > 0x7fffffffLL) return hipErrorInvalidValue;
     if (pl.split_k > 1 && (size_t)pl.split_k * (size_t)m->M * (size_t)m->N * (f64 ? sizeof(double) : sizeof(float)) > partial_bytes)
         return hipErrorInvalidValue;
     const int wide = m->bw == 32 ? 1 : 0;
