@@ -1215,10 +1215,18 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     // them on, where both sides make 704 workgroups or more (one, then two each, floats and 16-bit: 640 blocks of A beside
     // 80 workgroups of B 10.1 -> 9.8 and 8.7 -> 7.6 us, 784 beside 112 12.1 -> 11.2 and 9.6 -> 7.9, 784 of A alone
     // 11.0 -> 10.3 and 8.7 -> 7.6).  With fewer the short second round costs less than two blocks in turn (640 of A alone
-    // 8.9 -> 9.2 and 7.2 -> 7.5, 512 beside 64 8.3 -> 8.7 and 7.2 -> 7.3; whole passes over 528 to 575 .98 to 1.01).
+    // 8.9 -> 9.2 and 7.2 -> 7.5, 512 beside 64 8.3 -> 8.7 and 7.2 -> 7.3; whole passes over 528 to 575 .98 to 1.01).  Row-compacted
+    // ones gain more (896 blocks beside 224 workgroups of B, 16-bit, 10.3 -> 8.7, floats 840 beside 240 11.5 -> 10.5; 28 problems .94 in the mean, 1.00 at worst).
+    // Doubles and floats in parts gain beside some workgroups of B and not beside many (doubles, below 200 of them, .97 in the mean, 1.02 at worst, 200 to
+    // 320 1.05 and 1.14; in parts, below 400, .97 and 1.04, more 1.01 and 1.05).  Row-compacted blocks in parts, whose second waits at a barrier for the one
+    // stage while the first is read column by column, only where the second round was well filled and beside fewer than the 256 workgroups that B has at most
+    // (784 to 992 blocks .94 to 1.02, of A alone .84 to .98; 612 to 720 1.00 to 1.055; beside 256 1.015 in the mean).
     int64_t per_wg = n_a / 512;
     per_wg = per_wg < 1 ? 1 : per_wg > 8 ? 8 : per_wg;
-    if (per_wg == 1 && n_a >= 600 && n_a + n_b_wg >= 704) per_wg = 2;
+    const bool rows_in_parts = a.form == MMM_FORM_PARTS && p.rows != nullptr;
+    const int64_t b_below = f64 ? 200 : rows_in_parts ? 256 : a.form == MMM_FORM_PARTS ? 400 : INT64_MAX;
+    const bool two = n_a >= (rows_in_parts ? 768 : 600) && n_a + n_b_wg >= 704 && n_b_wg < b_below;
+    if (per_wg == 1 && two) per_wg = 2;
     if (per_wg > m->MBA) per_wg = m->MBA;
     const int64_t n_a_wg = a.X ? (m->MBA + per_wg - 1) / per_wg * p.a_units : 0;
     const int64_t n_all = n_a_wg + n_b_wg;

@@ -82,14 +82,22 @@ def test_many_blocks_per_builder_workgroup(M, p_rows, dtype):
     _run(w)
 
 
-@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_BF16, synth.DT_F16], ids=["f32", "bf16", "f16"])
+@pytest.mark.parametrize("dtype,form", [(synth.DT_F32, 0), (synth.DT_F32, 1), (synth.DT_BF16, -1), (synth.DT_F16, -1), (synth.DT_F64, -1)],
+                         ids=["f32", "parts", "bf16", "f16", "f64"])
 @pytest.mark.parametrize("M,K,N,p_rows", [
     (389, 11400, 32, 1.0),     # 630 blocks of A, seven below each other: two, two, two and a ragged one per workgroup
     (129, 25600, 16, 0.1),     # 600 in three rows: the fewest that go in twos
     (70, 65400, 16, 1.0),      # 1022 in two rows: the most
+    (389, 14000, 32, 0.3),     # 770 in seven rows: row-compacted floats in parts too
 ])
-def test_two_blocks_per_builder_workgroup(M, K, N, p_rows, dtype):
-    _run(synth.random_masked(M, K, N, 16, 0.1, 0.1, M, dist="smallint", dtype=dtype, p_rows=p_rows))
+def test_two_blocks_per_builder_workgroup(M, K, N, p_rows, dtype, form):
+    if dtype == synth.DT_F64:   # blocks half as wide
+        K //= 2
+    mm.mmm_set_option("float_form", form)
+    try:
+        _run(synth.random_masked(M, K, N, 16, 0.1, 0.1, M, dist="smallint", dtype=dtype, p_rows=p_rows))
+    finally:
+        mm.mmm_set_option("float_form", -1)
 
 
 @pytest.mark.parametrize("M,N,split", [(2100, 16, 1), (40, 4112, 3), (1000, 2576, 1), (1030, 3344, 4)])
