@@ -115,7 +115,9 @@ size_t c_elem_size(int32_t dt) { return dt == MMM_F64 ? 8 : 4; }
 // The 2-byte row is from 700 problems (65 to 4096 rows, K to 16384, N to 8192) after the kernel took its batches from one queue, and
 // scaled to lie above timings as the others do: tile and split 1.4 % longer than the best on 700 others, 19 % at worst; with the
 // row from before, whose waiting per step is twice as long, 3.3 and 51 % (512 x 8192 x 4096, p = .1: 24.0 -> 21.9 us).
-// The estimates themselves lie 10 to 25 % from back-to-back timings, mostly above, which hide the launch.
+// The row of floats in parts is from 800 problems (65 to 4096 rows, K to 16384, densities .05 to .6, up to three splits each) after their batches were joined:
+// 90 to 113 % of the timings of 800 others in nine of ten (with the row from before, whose batches were whole lists', 70 to 94 %).
+// The other estimates lie 10 to 25 % from back-to-back timings, those of 2-byte types mostly above, which hide the launch.
 struct MatrixCost {   // microseconds
     double launch;        // per call
     double latency;       // per step and batch of its longest lists: nobody hides the first wave's waiting
@@ -131,7 +133,7 @@ constexpr MatrixCost kMatrixCost[4] = {   // 2-, 4-, 8-byte elements, floats in 
     {2.936, 0.0995, 0.0371, 0.0032, 0.0971, 0.866, 2.67, 1.241, 34.4},
     {3.524, 0.1805, 0.1198, 0.0031, 0.0747, 0.561, 2.0, 1.159, 24.9},
     {3.210, 0.3107, 0.4623, 0.0059, 0.1092, 1.362, 3.3, 2.257, 30.9},
-    {3.210, 0.0308, 0.0266, 0.0139, 0.0, 1.607, 2.42, 1.661, 20.2},
+    {5.009, 0.0222, 0.2541, 0.0133, 0.0, 1.607, 2.07, 1.861, 20.3},
 };
 struct PairsCost {   // microseconds
     double launch;     // per call
@@ -202,7 +204,7 @@ double matrix_cost(const mmm_maps *m, int32_t dt, int32_t form, const MatrixProb
     if (q.marked > 0.0) {
         // Marked steps are done again behind the loop, by a wave on its own and four k at a time.  The fullest compute unit has more of them
         // than the mean: by about three times its root.  4096^3, p = .4, multiplication, with 0, 1, 10, 100 % of the blocks of A marked
-        // 365, 454, 782, 3052 us, of the segments of B 347, 465, 845, 3036; 2048^3, blocks of 32, p_B = .5, 53, 92, 211, 473 and 53, 98, 225, 471.
+        // 314, 390, 762, 2908 us, of the segments of B 311, 454, 879, 2911; 2048^3, blocks of 32, p_B = .5, 56, 123, 214, 360 and 52, 97, 211, 358.
         const double all = (double)steps * (double)per_cu, mean = q.marked * all;
         t += q.redone * std::min(all, mean + 3.0 * std::sqrt(mean));
     }
@@ -401,8 +403,8 @@ void capture_form(const mmm_maps *m, int32_t form, hipStream_t s)
 
 // The form a build gives floats: that of the side it does not build (the kernel takes both from one form), that of captured
 // calls, or the one with which build and multiplication are estimated to take less; without counts the plain one.  Parts pay
-// for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 432 + 39 and 326 + 56 us, .2 237 + 34 and
-// 190 + 43, .1 139 + 31 and 157 + 39 (a list of 13 fills 40 % of a batch).  They do not where more than a few steps hold an element that
+// for long lists: 4096^3, blocks of 16, multiplication and build, plain and in parts: p = .4 475 + 41 and 319 + 57 us, .2 248 + 36 and
+// 185 + 44, .1 138 + 33 and 155 + 39 (a list of 13 fills two of the three units it counts for).  They do not where more than a few steps hold an element that
 // parts do not (see matrix_cost): mmm_maps_stats counts those too, in either form.
 int32_t choose_form(mmm_maps *m, const mmm_build_args &a)
 {
@@ -428,10 +430,12 @@ int32_t choose_form(mmm_maps *m, const mmm_build_args &a)
             compute_plan(m, a.dtype, MMM_FORM_PLAIN, v, split, &plan, &plain);
             const bool filter = plan.filter != 0;
             compute_plan(m, a.dtype, MMM_FORM_PARTS, v, split, &plan, &parts);
-            // What the build takes longer, fitted with the estimate of the parts to 400 random problems of 65 to 4096 rows and
-            // columns, K up to 16384, densities .05 to 1: the image and packed B are half as large again, and the rows of B are
-            // read twice.  Estimates err by 10 %, those of the plain form mostly downwards; with 15 % and 2 us between the two
-            // no problem took longer than before, the mean was .966 of it (without: .963, and up to 1.5 for the worst).
+            // What the build takes longer, fitted to 400 random problems of 65 to 4096 rows and columns, K up to 16384, densities .05 to 1 (on 800
+            // others within 2.3 us in nine of ten): the image and packed B are half as large again, and the rows of B are read twice.
+            // With 15 % and 2 us between the two, 253 of 3700 float problems (p_B .05 to .6) are built in parts; their passes are .784 of plain ones in the
+            // mean, three take more than 2 % longer, 14 % at worst; 107 are plain where parts would be 5 % faster or more.  Less between them gives
+            // some of those to parts, and slower ones with them (10 %: of 1200 problems 102 in parts instead of 82, four of them slower, 29 % at worst; the row of
+            // the former kernel with lists joined: 145 and 19, 34 %), and more callers another order of rounding.
             const MatrixProblem q = matrix_problem(m, a.dtype, MMM_FORM_PARTS);
             const double b_rounds = std::ceil((double)q.steps * (double)((m->N + 255) / 256) / 512.0);
             const double longer = 2.68e-7 * (double)m->M * (double)m->K + 7.7e-7 * (double)m->stats_occ_b * m->bw + 0.6 * q.batches * b_rounds;

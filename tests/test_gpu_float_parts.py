@@ -336,6 +336,22 @@ def test_the_form_follows_the_steps_that_parts_do_not_hold(side, bw, rows):
     assert form_after_stats() == PARTS
 
 
+@pytest.mark.parametrize("M,K,N,bw,p,form", [
+    (3631, 206, 3456, 16, 0.169, PLAIN), (3157, 304, 3832, 8, 0.081, PLAIN), (3434, 737, 3680, 16, 0.121, PLAIN),   # passes in parts take 1.34, 1.18 and 1.20 times as long
+    (1969, 637, 2752, 16, 0.179, PLAIN),                                  # 1.10 times
+    (2048, 2048, 2048, 16, 0.4, PARTS), (1300, 4096, 3000, 8, 0.3, PARTS),   # long lists
+])
+def test_choice_of_form(M, K, N, bw, p, form):
+    """Short lists and a short K are multiplied as floats."""
+    mm.mmm_set_option("matmul_path", -1)
+    mm.mmm_set_option("float_form", -1)
+    run = HipRun(synth.random_masked(M, K, N, bw, 0.2, p, M + K, dist="normal"))
+    run.build()
+    run.eng.stats()
+    run.build()
+    assert mm.mmm_matmul_form(run.eng.maps) == form
+
+
 @pytest.mark.parametrize("value", [1e-38, float("nan")], ids=str)
 def test_columns_that_are_switched_off_mark_nothing(value):
     """Whatever they hold.  Seen by the count of marked steps: more than a few would bring floats as they are."""
