@@ -12,7 +12,7 @@
 // whose columns are zero in the whole tile often enough (see `filtered`).  The iteration is uniform across
 // the wave.
 //
-// A workgroup owns 64 rows of C and keeps a ring of two or four blocks of A in LDS (see mmm_ring), filled by asynchronous
+// A workgroup owns 64 rows of C and keeps a ring of two to four blocks of A in LDS (see mmm_ring), filled by asynchronous
 // global-to-LDS loads of the builder's image, whose byte order is the one the operand reads want: no
 // registers, no vector instruction and no LDS atomic is spent on A.  One barrier per step of 128 k.
 //
@@ -144,10 +144,6 @@ __device__ __forceinline__ uint32_t mbcnt64(uint64_t m)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
-__device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
-{
-    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), l) << 32) | (uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)v, l);
-}
 
 // wait until at most N of the wave's vector-memory operations are outstanding (they complete in order)
 template <int N> __device__ __forceinline__ void wait_vmem()
@@ -208,7 +204,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // Splits of K one after another, the tiles of each in panels of `panel` tile columns (see panel_width).
     // (The number of workgroups is worked out: the launch's own word for it lies behind all arguments, a cache line on.  512 x 8192 x
     // 4096 bf16, the pass: 27.66 -> 27.34 us.)
-    const uint32_t tiles = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n, in_panel = (uint32_t)p.tiles_m * (uint32_t)p.panel;
+    const uint32_t tiles = (uint32_t)p.tiles_m * (uint32_t)p.tiles_n;
     const uint32_t L = xcd_contiguous_id(blockIdx.x, tiles * (uint32_t)p.split_k);
     const int split = (int)mmm_divided(L, p.by_tiles);
     const uint32_t t = L - (uint32_t)split * tiles, n0 = mmm_divided(t, p.by_in_panel) * (uint32_t)p.panel;
@@ -269,10 +265,12 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // ---- B: one batch of a group's list in registers
     struct Batch {
         elem_t bf[WIDE ? GW : 1][4];    // 4- and 8-byte types: slot 4u + s of column c, u = 0..3
-        u32x4 bh[WIDE ? 1 : GW][PARTS]; // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch
+        u32x4 bh[WIDE ? 1 : GW][PARTS]; // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch; floats in parts: of each
+                                        // part, the eight slots of unit s (see MMM_UNIT for their order)
         u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
-        uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each)
-        uint32_t what;                  // 16-bit: see `plan`
+        uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each); floats in parts: of the
+                                        // two slots lane % 16 / 4 of unit s
+        uint32_t what;                  // 16-bit, floats in parts: see `plan`
     };
     Batch B0, B1, B2;
     // The batch whose values and entries lie at these byte offsets of the group's area.  Always OPS loads, so that the waits
@@ -295,8 +293,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, off_l, 0);
 #pragma unroll
             for (int g = 0; g < GW; ++g)
-#pragma unroll
-                for (int q = 0; q < PARTS; ++q) b.bh[g][q] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16 + q * 1024, off_v + g * val_next, 0);
+                b.bh[g][0] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16, off_v + g * val_next, 0);
         }
         asm volatile("" ::: "memory");
     };

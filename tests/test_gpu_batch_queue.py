@@ -1,4 +1,4 @@
-"""The matrix kernel's queue of list batches (16-bit types, floats in parts): 64 (parts: 44) are planned at a time, whatever steps they
+"""The matrix kernel's queue of list batches (16-bit types, floats in parts): 64 (parts: 46 to 64) are planned at a time, whatever steps they
 belong to, so lists of every length fall on the seams of the plan.  Small whole numbers: sums are exact in any order."""
 import numpy as np
 import pytest
