@@ -433,7 +433,7 @@ int32_t choose_form(mmm_maps *m, const mmm_build_args &a)
             // What the build takes longer, fitted to 400 random problems of 65 to 4096 rows and columns, K up to 16384, densities .05 to 1 (on 800
             // others within 2.3 us in nine of ten): the image and packed B are half as large again, and the rows of B are read twice.
             // With 15 % and 2 us between the two, 253 of 3700 float problems (p_B .05 to .6) are built in parts; their passes are .784 of plain ones in the
-            // mean, three take more than 2 % longer, 14 % at worst; 107 are plain where parts would be 5 % faster or more.  Less between them gives
+            // mean, three take more than 2 % longer, 14 % at worst; 107 or more are plain where parts would be 5 % faster.  Less between them gives
             // some of those to parts, and slower ones with them (10 %: of 1200 problems 102 in parts instead of 82, four of them slower, 29 % at worst; the row of
             // the former kernel with lists joined: 145 and 19, 34 %), and more callers another order of rounding.
             const MatrixProblem q = matrix_problem(m, a.dtype, MMM_FORM_PARTS);

@@ -1059,7 +1059,7 @@ struct VariantEntry {
     }
 
 // Floats in parts have 64 x 256 by themselves; the narrower tiles, which leave a compute unit 8 or 4 waves beside the same ring, where they
-// are fixed while the operands are in parts (4096^3, p = .4: 302, 364 and 586 us; 1500 x 2100 x 1024, p_B = .5: 33.7, 30.8 and 47.3).
+// are fixed while the operands are in parts (4096^3, p = .4: 323, 375 and 612 us; 1500 x 2100 x 1024, p_B = .5: 33.5, 29.8 and 49.3).
 const VariantEntry g_variants[] = {
     MMM_VARIANT(4, 8, PARTS_FIXED, MMM_PARTED),   // 0: 64 x 128
     MMM_VARIANT(4, 16, PARTS_OWN, MMM_PARTED),     // 1: 64 x 256
