@@ -695,7 +695,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
     }
     constexpr int RING = mmm_ring(LSZ);
     // (floats in parts: their ring has no zero column; the block's first, which exists if there is a list, does as well)
-    const uint32_t ZERO_ENTRY = mmm_list_entry(LSZ, PARTED ? (uint32_t)seg % (uint32_t)RING * SEG : mmm_zero_col(RING));
+    const uint32_t ZERO_ENTRY = WIDE && !PARTED ? mmm_list_entry(LSZ, mmm_zero_col(RING)) : PARTED ? mmm_list_entry(LSZ, (uint32_t)seg % (uint32_t)RING * SEG) : 0u;
     static_assert(B_GROUPS * SEG * 2 <= BUILD_THREADS * 4, "at most one list word per thread");
     if (threadIdx.x < B_GROUPS * SEG / 2) reinterpret_cast<uint32_t *>(sh.list)[threadIdx.x] = ZERO_ENTRY | ZERO_ENTRY << 16;
     // (Read where all lanes are: a value first read, or made wider, on one side of a branch is taken for one of each lane, and a store through a
@@ -804,20 +804,18 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
             if (lane == 0) p.bp_cnt[(uint64_t)CG * KBA + seg] = n_out | (wild ? 0x80000000u : 0u);
         }
     } else {
-        // The occupied rows go to LDS one after another, zeros behind them up to a whole batch, and come out through the
-        // transposing read, which yields four slots of a column to a lane: two of them are a lane's part of a batch in the
+        // The occupied rows go to LDS one after another, zeros behind them up to a whole unit, and come out through the
+        // transposing read, which yields four slots of a column to a lane: two of them are a lane's part of a unit in the
         // order of mmm_value_pos.  One LDS write per row; put in place element by element it took four, and a workgroup of B was
         // bound by them (512^3, p = .4, bf16: both sides 5.9 -> 5.0 us, 4096^2, p = .2: 23.2 -> 22.4).
-        constexpr uint32_t SLOTS = 32, ROWB = MMM_GROUP_COLS * ESZ;   // per batch; bytes per row
+        constexpr uint32_t SLOTS = 4 * MMM_UNIT, ROWB = MMM_GROUP_COLS * ESZ;   // taken out at a time; bytes per row
         constexpr int GROUPB = SEG * ROWB + 16;                       // bytes per group (4 banks apart)
         static_assert(B_GROUPS * GROUPB <= (int)sizeof(sh.pack) && B_GROUPS == BUILD_WAVES, "room for the groups, and a wave for each");
         char *const mine = sh.pack + (lane / LPG) * GROUPB + (lane % LPG) * 8;
 #pragma unroll
         for (int j = 0; j < B_ROWS; ++j)
             if ((gb >> j) & 1u) *reinterpret_cast<u32x2 *>(mine + slots[j] * ROWB) = u32x2{raw[j].x, raw[j].y};
-#pragma unroll
-        for (uint32_t i = 0; i < SLOTS; i += BUILD_WAVES)
-            if (n + i + wave < ((n + SLOTS - 1) & ~(SLOTS - 1))) *reinterpret_cast<u32x2 *>(mine + (n + i + wave) * ROWB) = u32x2{0, 0};
+        if (wave < MMM_UNIT && n + wave < ((n + MMM_UNIT - 1) & ~(MMM_UNIT - 1u))) *reinterpret_cast<u32x2 *>(mine + (n + wave) * ROWB) = u32x2{0, 0};
         __syncthreads();
         const uint32_t CG = ct * B_GROUPS + (uint32_t)wave;   // the group this wave takes out
         if (CG < NG) {
@@ -825,13 +823,14 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
             typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
             typedef __attribute__((address_space(3))) char lds_char;
             const uint32_t n_out = (uint32_t)__builtin_amdgcn_readlane((int)n, wave * LPG);
-            // (slot lane / 4 and four of its columns: lane c of 16 gets column c of those four slots)
-            lds_char *const in = (lds_char *)sh.pack + wave * GROUPB + (lane >> 2) * ROWB + (lane & 3) * 8;
+            // (four lanes name a slot and four of its columns each: lane c of sixteen gets column c of their four slots)
+            const uint32_t unit = (uint32_t)lane >> 4, half = unit * MMM_UNIT + (unit & 1u) * 4u + (((uint32_t)lane >> 2) & 3u);
+            lds_char *const in = (lds_char *)sh.pack + wave * GROUPB + (lane & 3) * 8;
             char *const out = p.bp_val + ((uint64_t)CG * KBA + seg) * (SEG * ROWB) + lane * 16;
             for (uint32_t q = 0; q < n_out; q += SLOTS) {
-                const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(in + q * ROWB)));
-                const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(in + (q + 16) * ROWB)));
-                *reinterpret_cast<u32x4 *>(out + q * ROWB) = u32x4{lo.x, lo.y, hi.x, hi.y};
+                const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(in + (q + half) * ROWB)));
+                const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(in + (q + (half ^ 4u)) * ROWB)));
+                if (q + unit * MMM_UNIT < n_out) *reinterpret_cast<u32x4 *>(out + q * ROWB) = u32x4{lo.x, lo.y, hi.x, hi.y};   // (units past the last are not read)
             }
         }
     }

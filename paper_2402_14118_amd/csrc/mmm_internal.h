@@ -55,14 +55,15 @@ __host__ __device__ constexpr uint32_t mmm_img_row(size_t esz, uint32_t col, uin
 // at [group][segment][128 slots][16 columns]; the number of slots; and per slot where its column of A
 // sits in the kernel's LDS ring of `ring` blocks: column 128 * (segment mod ring) + k, in units of 256 bytes (4- and
 // 8-byte elements) or of 16 bytes with the rotation folded in (16-bit elements).  Slots past the
-// last name the ring's zero column.
+// last name the ring's zero column, which stands behind the blocks (16-bit elements: in front of them, so that its entry is 0).
 // A vector-memory instruction occupies a compute unit for 8 cycles up to 4 bytes per lane and for 16 above, whether
 // it loads 8 or 16.  So the entries, and 16-bit values, are stored in the order in which the kernel's lanes take
 // them, one load per batch of slots.  s: lane / 16, c: column.
 // 4- and 8-byte elements, batches of 16 slots: slot 4u + s is entry u of [s][4]; values slot by slot.  (Floats in lane
 // order save the kernel 1 to 2% - 4096^3, p = .4: 431 against 437 us - and cost the builder more, for putting them
 // together in LDS: 2048 x 8192 x 2048 with half of B's blocks: 54 against 46 us.)
-// 16-bit elements, batches of 32: slot 16h + 4s + e is value 4h + e of [s][c][8], entry h of [4s + e][2].
+// 16-bit elements, batches of 32 in four units of eight (see MMM_UNIT), so that the sixteen lanes of a unit behind a list's last slot need
+// not read: 8-byte halves of two units per lane, as it was, 4096^3 bf16, p = .05, .1, .2: multiplication 60.6 -> 52.9, 59.9 -> 54.7, 64.0 -> 62.0 us.
 constexpr int MMM_GROUP_COLS = 16;
 // Blocks in the ring.  16-bit types take four (64 KiB): a step of the kernel is short then, and a block is requested three
 // steps before it is needed.  Floats and doubles take two (64, 128 KiB); four floats deep measured no faster (2048^3,
@@ -82,8 +83,8 @@ __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t
 // them): its three parts hold its bits instead (MMM_PARTS_RAW), a block of A and a segment of a group of B that have one are marked,
 // and are multiplied as floats, put together again (mmm_whole_float).
 // Image: [block of 64 x 128][part][column][64 rows], columns as of the 16-bit types.  Packed B: batches of 32 slots as of the
-// 16-bit types but for the order of slots, [unit of slots][part].  As an "element size": 6.
-// Slots come in units of eight: slot 8u + 4h + e of a segment is value 4h' + e of [u][c][8], entry h' of [4u + e][2], with h' = h in even units and
+// 16-bit types, [unit of slots][part].  As an "element size": 6.
+// Slots come in units of eight, as those of the 16-bit types: slot 8u + 4h + e of a segment is value 4h' + e of [u][c][8], entry h' of [4u + e][2], with h' = h in even units and
 // 1 - h in odd ones.  A unit is what sixteen lanes of the kernel take, so that a batch can be put together from the units of two segments.  (The
 // columns of A that 32 lanes read at once are half a unit of one and half of the next: of a dense list k .. k + 3 and k + 12 .. k + 15, in different LDS
 // banks.  That half of the LDS cycles of sparse ones are conflicts does not bound the kernel: dealt out by k mod 8, or without any, no faster.)
@@ -103,28 +104,25 @@ __device__ inline float mmm_whole_float(const char *at, size_t step)
     return p2 == MMM_PARTS_RAW ? __uint_as_float(p0 << 16 | p1) : __uint_as_float(p0 << 16) + (__uint_as_float(p1 << 16) + __uint_as_float(p2 << 16));
 }
 enum { MMM_FORM_PLAIN = 0, MMM_FORM_PARTS = 1 };
-// col: ring column (mmm_zero_col for the zero column: a multiple of 8, so the rotation is nil)
+// col: ring column (4- and 8-byte elements: mmm_zero_col for the zero column; 16-bit: the blocks begin behind it, 128 bytes on)
 __host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
 {
-    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3 | mmm_img_swizzle(col)) + (esz == MMM_PARTS_ESZ ? col / MMM_AB_COLS * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 0);
+    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3 | mmm_img_swizzle(col)) + (esz == MMM_PARTS_ESZ ? col / MMM_AB_COLS * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 8);
 }
 // and back, inside its block
 __host__ __device__ constexpr uint32_t mmm_list_entry_k(size_t esz, uint32_t entry, uint32_t block_in_ring)
 {
-    return (esz == 8 ? entry >> 1 : esz == 4 ? entry : (entry - (esz == MMM_PARTS_ESZ ? block_in_ring * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 0u)) >> 3) -
+    return (esz == 8 ? entry >> 1 : esz == 4 ? entry : (entry - (esz == MMM_PARTS_ESZ ? block_in_ring * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 8u)) >> 3) -
            block_in_ring * MMM_AB_COLS;
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)
 {
-    return esz == MMM_PARTS_ESZ ? (slot & ~7u) | (slot & 3u) << 1 | ((slot >> 2 ^ slot >> 3) & 1u)
-           : esz % 4 == 0       ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u)
-                                : (slot & ~31u) | (slot & 15u) << 1 | ((slot >> 4) & 1u);
+    return esz % 4 == 0 ? (slot & ~15u) | (slot & 3u) << 2 | ((slot >> 2) & 3u)
+                        : (slot & ~7u) | (slot & 3u) << 1 | ((slot >> 2 ^ slot >> 3) & 1u);
 }
 __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, uint32_t col)   // in elements
 {
-    return esz == MMM_PARTS_ESZ ? col * 8u + ((slot & 7u) ^ (slot >> 1 & 4u))   // (inside a unit)
-           : esz >= 4           ? slot * 16u + col
-                                : (slot >> 5) * 512u + ((slot >> 2) & 3u) * 128u + col * 8u + ((slot >> 4) & 1u) * 4u + (slot & 3u);
+    return esz % 4 == 0 ? slot * 16u + col : col * 8u + ((slot & 7u) ^ (slot >> 1 & 4u));   // (the latter inside a unit)
 }
 // Floats: per 128 k a group lists `all` k, of which `stay` have a non-zero column of A in the tile.  Whether the kernel is
 // faster when it makes the lists without the others (see `filtered` there) than with the lists as packed.  A step then costs

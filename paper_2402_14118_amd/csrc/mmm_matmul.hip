@@ -169,7 +169,8 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     constexpr int RING = mmm_ring(sizeof(T));
     constexpr int COLB = TM * ESZ;                  // bytes per LDS column
     constexpr int SLAB = KC * COLB;                 // bytes per block of A
-    constexpr int ZERO_AT = RING * SLAB;            // the ring's zero column (mmm_zero_col)
+    constexpr int ZERO_AT = ESZ == 2 ? 0 : RING * SLAB;   // the ring's zero column (see mmm_list_entry)
+    constexpr int BLOCKS_AT = ESZ == 2 ? COLB : 0;
     constexpr int DMA = SLAB / 1024 / NW;           // copies per wave and block
     constexpr int BATCH = WIDE ? 16 : 32;           // list slots per batch
     constexpr int OPS = WIDE ? 4 * GW + 1 : PARTS * GW + 1;   // vector-memory operations request() makes
@@ -253,7 +254,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     const char *src = p.a_img + ((uint64_t)(uint32_t)tile_m * (uint32_t)p.KBA + (uint32_t)chunk_begin) * SLAB;   // the next block to copy
     int to_copy = chunk_end - chunk_begin;                                       // blocks from there on
     const uint32_t dma_v = (uint32_t)(wave * DMA * 1024 + lane * 16);
-    const uint32_t place0 = ring_off + (uint32_t)(wave * DMA * 1024);
+    const uint32_t place0 = ring_off + (uint32_t)(BLOCKS_AT + wave * DMA * 1024);
     uint32_t place = (uint32_t)chunk_begin % (uint32_t)RING * SLAB;
     auto copy_block = [&]() __attribute__((always_inline)) {
         copy_to_lds<DMA>(src, dma_v, place0 + place);
@@ -265,11 +266,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // ---- B: one batch of a group's list in registers
     struct Batch {
         elem_t bf[WIDE ? GW : 1][4];    // 4- and 8-byte types: slot 4u + s of column c, u = 0..3
-        u32x4 bh[WIDE ? 1 : GW][PARTS]; // 16-bit: slots 4s .. 4s+3 of column c, for both halves of the batch; floats in parts: of each
-                                        // part, the eight slots of unit s (see MMM_UNIT for their order)
+        u32x4 bh[WIDE ? 1 : GW][PARTS]; // 16-bit, and of each part of floats in parts: the eight slots of unit s in column c (see MMM_UNIT for their order)
         u32x2 list;                     // 4- and 8-byte types: ring columns of those four slots (16 bits each)
-        uint32_t entry;                 // 16-bit: ring position of slot lane / 4 of both halves (16 bits each); floats in parts: of the
-                                        // two slots lane % 16 / 4 of unit s
+        uint32_t entry;                 // 16-bit, floats in parts: ring positions of the two slots lane % 16 / 4 of unit s (16 bits each)
         uint32_t what;                  // 16-bit, floats in parts: see `plan`
     };
     Batch B0, B1, B2;
@@ -289,11 +288,6 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                         b.bf[g][u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(val_rsrc, lane * 4 + u * 256, off_v + g * val_next, 0));
                 }
             }
-        } else {
-            b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, off_l, 0);
-#pragma unroll
-            for (int g = 0; g < GW; ++g)
-                b.bh[g][0] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, lane * 16, off_v + g * val_next, 0);
         }
         asm volatile("" ::: "memory");
     };
@@ -359,7 +353,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(ring3 + (at[h] ^ (uint32_t)(r * 32)) + q * MMM_PART_BYTES)));
             };
             // The whole batch whatever its length: slots past the end name the zero column (floats in parts: the block's
-            // first) and hold zeros.  (A branch to a 16-slot instruction for short lists costs more, in moved accumulators,
+            // first) and hold zeros, units past the end come as zeros.  (A branch to a 16-slot instruction for short lists costs more, in moved accumulators,
             // than it saves in LDS reads, and that instruction takes as long.)
             u32x2 a[PARTS][2][RT];
 #pragma unroll
@@ -445,7 +439,14 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     auto request_at = [&](Batch &b, uint32_t what) __attribute__((always_inline)) {
         b.what = what;
         const int place = (int)(what & PLACE);
-        request(b, place * (BATCH * MMM_GROUP_COLS * ESZ), place * (BATCH * 2));
+        // (the lanes of a unit without a slot read past the end of the buffer: zeros, and nothing is fetched)
+        const int at = (int)(what >> LEFT & 63u) > s * MMM_UNIT ? lane * 16 : (int)0x80000000u;
+        asm volatile("" ::: "memory");   // (as in `request`)
+        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, place * (BATCH * 2), 0);
+#pragma unroll
+        for (int g = 0; g < (WIDE ? 0 : GW); ++g)
+            b.bh[g][0] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, at, place * (BATCH * MMM_GROUP_COLS * ESZ) + g * val_next, 0);
+        asm volatile("" ::: "memory");
     };
     auto turn = [&](Batch &b) __attribute__((always_inline)) {
         if (b.what & FRESH) {
@@ -674,7 +675,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             if constexpr (PARTED)
                 request_units(B0, (uint32_t)chunk_begin * UNITS | (UNITS - 4u) << JUMP);   // as if the first list had four units
             else
-                request_at(B0, (uint32_t)chunk_begin * PER_STEP);
+                request_at(B0, (uint32_t)BATCH << LEFT | (uint32_t)chunk_begin * PER_STEP);
         }
         if constexpr (PARTED) {
             for (int i = lane; i < p.KBA; i += 64) marks |= p.a_wild[(int64_t)tile_m * p.KBA + i];
@@ -855,6 +856,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 wait_vmem<2 * OPS>();   // the blocks so far have landed
                 asm volatile("s_barrier" ::: "memory");
                 if (to_copy > 0) copy_block();
+                const bool filled = (int)(B0.what >> LEFT & 63u) > s * MMM_UNIT;   // (asked for as if all of its units were)
+#pragma unroll
+                for (int g = 0; g < (WIDE ? 0 : GW); ++g) B0.bh[g][0] = filled ? B0.bh[g][0] : u32x4{0, 0, 0, 0};
                 do {
                     turn(B0);
                     turn(B1);

@@ -185,3 +185,35 @@ def test_fused_mask_without_a_bitmap(M, ldx_more, K, dtype):
     run.eng.matmul_fused(run.X, run.Y, run.C, w.pred, w.threshold, None)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(run.C.cpu().numpy(), C_ref)
+
+
+@pytest.mark.parametrize("dtype,form", [(synth.DT_BF16, -1), (synth.DT_F16, -1), (synth.DT_F32, 0), (synth.DT_F32, 1), (synth.DT_F64, -1)],
+                         ids=["bf16", "f16", "f32", "parts", "f64"])
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_shorter_lists_over_longer_ones(bw, dtype, form):
+    """A build leaves what lies behind a list as it was: here infinities and NaN of a build with every block on.  Lists end one
+    slot before, at and behind each unit of eight, and what A holds at other k is not finite either (where A is masked out)."""
+    lengths = [0, 1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 31, 32, 33, 40, 127]
+    M, segs, N = 70, 9, 96
+    K, NB = segs * 128, N // bw
+    keep = np.zeros((K, NB), bool)
+    rng = np.random.default_rng(bw)
+    for s in range(segs):
+        for b in range(NB):
+            keep[s * 128 + rng.permutation(128)[: lengths[(5 * s + b) % len(lengths)]], b] = True
+    w = synth.random_masked(M, K, N, bw, 0.5, 1.0, 177 + bw, dist="smallint", dtype=dtype)
+    w.keep_blocks = synth.pack_bits(keep)
+    C_ref = oracle.run_workload(w)[2]
+    mm.mmm_set_option("float_form", form)
+    try:
+        run = HipRun(w)
+        run.eng.set_path(mm.MMM_PATH_MATRIX)
+        Y = run.Y.clone()
+        run.Y.copy_(torch.where(torch.rand(K, N, device="cuda") < 0.5, 0x7fff, 0x7f80).to(torch.int16) if Y.dtype == torch.int16
+                    else torch.where(torch.rand(K, N, device="cuda") < 0.5, float("nan"), float("inf")))
+        run.eng.build_maps(run.X, run.Y, w.pred, w.threshold, run.keep_a)
+        run.matmul()
+        run.Y.copy_(Y)
+        np.testing.assert_array_equal(run.run()[2], C_ref)
+    finally:
+        mm.mmm_set_option("float_form", -1)
