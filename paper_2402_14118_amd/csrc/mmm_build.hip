@@ -68,6 +68,7 @@ struct BuildParams {
     int64_t M, K, N, NB, WA, WB, MT, MBA, KBA, NG;
     ElementTest test;
     int32_t pack;         // write packed B
+    int32_t x_streams;    // X is read past the caches
     int32_t y_unaligned;  // 16-bit Y whose rows do not start on 4-byte boundaries
     uint32_t n_b;               // segments x column tiles of B
     uint32_t n_a_wg, n_b_wg;    // workgroups for them
@@ -254,22 +255,29 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
         const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(static_cast<const char *>(p.X) + block_rows(bi, row_bytes) + k_lo * ESZ), 0,
             there ? (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)) : 0, 0x00020000);
+        auto elements = [&](auto policy) __attribute__((always_inline)) {
+            constexpr int POLICY = decltype(policy)::value;   // 2: not kept in the caches
 #pragma unroll
-        for (int t = 0; t < A_ROWS; ++t) {
-            const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
+            for (int t = 0; t < A_ROWS; ++t) {
+                const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
 #pragma unroll
-            for (int h = 0; h < A_WORDS; ++h) {
-                const int at = (int)(off[h] + row);
-                if constexpr (ESZ == 8) {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, 0);
-                    r.x[t][h] = (uint64_t)v.y << 32 | v.x;
-                } else if constexpr (ESZ == 4) {
-                    r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, 0);
-                } else {
-                    r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, 0);
+                for (int h = 0; h < A_WORDS; ++h) {
+                    const int at = (int)(off[h] + row);
+                    if constexpr (ESZ == 8) {
+                        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, POLICY);
+                        r.x[t][h] = (uint64_t)v.y << 32 | v.x;
+                    } else if constexpr (ESZ == 4) {
+                        r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, POLICY);
+                    } else {
+                        r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, POLICY);
+                    }
                 }
             }
-        }
+        };
+        if (p.x_streams)
+            elements(std::integral_constant<int, 2>{});
+        else
+            elements(std::integral_constant<int, 0>{});
         asm volatile("" ::: "memory");
     };
 
@@ -1187,7 +1195,14 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.MBA = m->MBA;
     p.KBA = m->KBA;
     p.NG = m->NG;
+    const bool f64 = a.dtype == MMM_F64;
     p.pack = mmm_packs(m->M, a.dtype) ? 1 : 0;
+    // A large X goes past the caches: it is read once, and what the last-level cache (256 MB) keeps of it takes the place of the image and of packed B,
+    // which the multiplication reads next.  Whole passes over three sets of operands in turn, kept and not: X of 64 MB and more, 4096^3 floats, p = .05,
+    // 130.8 -> 128.3 us (both sides 39.3 -> 34.8), p = .2 231 -> 225, 2048 x 16384 x 4096 columns bf16 70.6 -> 67.0, ReLU floats 120 -> 117.8;
+    // 32 MB, 2048^3 doubles 64.7 -> 63.4, 1024 x 16384 x 4096 bf16 78.8 -> 75.4, 2900^3 floats the same; smaller ones may still be there from
+    // whoever wrote them: 2048^3 floats (16 MB) 37.4 and 39.1, 2900^3 bf16 45.4 and 47.4, 1448^3 doubles 40.9 and 44.6.
+    p.x_streams = (int64_t)m->M * m->K * (int64_t)(f64 ? 8 : a.dtype == MMM_F32 ? 4 : 2) >= (int64_t)32 << 20 ? 1 : 0;
     p.test = mmm_element_test(a.dtype, a.pred, a.threshold);
     p.y_unaligned = a.dtype != MMM_F32 && a.dtype != MMM_F64 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
     p.kinfo = m->kinfo;
@@ -1196,7 +1211,6 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.rows_copy = m->rows_copy;
     // the numbering the A side follows: that of the B side built in this call, or of the cached one
     p.rows = a.b_compact ? a.keep_rows : a.a_compact ? m->rows_copy : nullptr;
-    const bool f64 = a.dtype == MMM_F64;
     const int64_t b_cols = f64 ? Tile<double>::B_COLS : Tile<float>::B_COLS;
     p.ctiles = (uint32_t)((m->N + b_cols - 1) / b_cols);
     p.a_units = f64 ? m->WA : m->KBA;
