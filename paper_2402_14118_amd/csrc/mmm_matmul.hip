@@ -425,27 +425,30 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // whatever steps they belong to.  Above, second batches are requested a step ahead, further ones only when they are next
     // but one, and a list of several costs a request in vain; here none does.  What a turn has to know about its batch (place,
     // slots, whether a step begins with it) stands ready in a lane of `plan`, made 64 batches at a time on the vector ALU, so
-    // that a turn takes 18 scalar instructions; with the same worked out by scalar selects it took 31, and short lists lost
+    // that a turn takes some 20 scalar instructions; with the same worked out by scalar selects it took 31, and short lists lost
     // what long ones won.  The turns past the end, up to two, do nothing.
     // 4096^3, p = .4, bf16 multiplication 111 -> 102 us; 512 x 8192 x 4096, bf16,
     // 24.3 -> 23.6, p = .4 38.0 -> 35.4.  4- and 8-byte types keep the steps above: their batches are half as large and mostly
     // one to a step, and the queue's beginning costs more than it gives (4096^3, p = .05, floats 89.5 -> 93.7, 2048^3, p = .1,
     // doubles 43.3 -> 45.2).
     constexpr int PER_STEP = KC / BATCH;   // batches that fit in a segment
-    constexpr uint32_t PAST = 1u << 31, FRESH = 1u << 30, LEFT = 24, PLACE = (1u << LEFT) - 1u;
-    uint32_t plan = 0;                                       // lane j: the j-th of the next batches:
-                                                             //   PAST the last, FRESH: first of its step, slots << LEFT, place
+    constexpr uint32_t PAST = 1u << 31, FRESH = 1u << 30, PLACE = 11, BATCH_BYTES = BATCH * MMM_GROUP_COLS * ESZ, HELD = 7u * MMM_UNIT_BYTES;
+    static_assert(WIDE || PARTED || (BATCH_BYTES == 1u << (PLACE - 1) && MMM_UNIT * MMM_GROUP_COLS * ESZ == MMM_UNIT_BYTES), "");
+    uint32_t plan = 0;                                       // lane j: the j-th of the next batches: PAST the last, FRESH: first of its step, place << PLACE
+                                                             //   (below 2^17), bytes of its units that hold a slot
     int ahead_j = 0;                                         // the one requested last
     auto request_at = [&](Batch &b, uint32_t what) __attribute__((always_inline)) {
         b.what = what;
-        const int place = (int)(what & PLACE);
-        // (the lanes of a unit without a slot read past the end of the buffer: zeros, and nothing is fetched)
-        const int at = (int)(what >> LEFT & 63u) > s * MMM_UNIT ? lane * 16 : (int)0x80000000u;
+        const uint32_t off_v = (what & (FRESH - (1u << PLACE))) >> 1;
         asm volatile("" ::: "memory");   // (as in `request`)
-        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, place * (BATCH * 2), 0);
+        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, (int)(off_v / (BATCH_BYTES / (BATCH * 2))), 0);
 #pragma unroll
-        for (int g = 0; g < (WIDE ? 0 : GW); ++g)
-            b.bh[g][0] = __builtin_amdgcn_raw_buffer_load_b128(val_rsrc, at, place * (BATCH * MMM_GROUP_COLS * ESZ) + g * val_next, 0);
+        for (int g = 0; g < (WIDE ? 0 : GW); ++g) {
+            // the buffer ends behind the last unit that holds a slot: the lanes of the others get zeros, and nothing is fetched for them
+            // (hidden by a lane offset of their own, two vector instructions in front of the load: 171 x 2775 x 1904, p = .33, 10.2 instead of 9.7 us, 755 x 544 live x 2560 9.15 and 8.95)
+            const __amdgpu_buffer_rsrc_t held = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p.bp_val) + seg0 * SEGB, 0, (int)(off_v + (what & HELD)) + g * val_next, 0x00020000);
+            b.bh[g][0] = __builtin_amdgcn_raw_buffer_load_b128(held, lane * 16, (int)off_v + g * val_next, 0);
+        }
         asm volatile("" ::: "memory");
     };
     auto turn = [&](Batch &b) __attribute__((always_inline)) {
@@ -454,8 +457,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             asm volatile("s_barrier" ::: "memory");
             if (to_copy > 0) copy_block();
         }
-        const int left = (int)(b.what >> LEFT & 63u);
-        if (left > 0) multiply(b, left);
+        if (b.what & HELD) multiply(b, BATCH);
         request_at(b, (uint32_t)__builtin_amdgcn_readlane(plan, ++ahead_j));
     };
 
@@ -675,7 +677,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             if constexpr (PARTED)
                 request_units(B0, (uint32_t)chunk_begin * UNITS | (UNITS - 4u) << JUMP);   // as if the first list had four units
             else
-                request_at(B0, (uint32_t)BATCH << LEFT | (uint32_t)chunk_begin * PER_STEP);
+                request_at(B0, BATCH_BYTES | (uint32_t)chunk_begin * PER_STEP << PLACE);
         }
         if constexpr (PARTED) {
             for (int i = lane; i < p.KBA; i += 64) marks |= p.a_wild[(int64_t)tile_m * p.KBA + i];
@@ -842,9 +844,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane(across(begin >= 32 && begin < 64 ? 1u << (begin - 32) : 0u, either), 63);
                     const uint64_t begun = ((uint64_t)hi << 32 | lo) & (~0ull >> (63 - lane));   // (bit 0 is set)
                     const int i = __popcll(begun) - 1, batch = lane - (63 - __builtin_clzll(begun)) + (i == 0 ? skip : 0);
-                    const int left = min((int)__shfl(n, i, 64) - batch * BATCH, BATCH);
+                    const int left = max(min((int)__shfl(n, i, 64) - batch * BATCH, BATCH), 0);
                     const uint32_t place = (uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch;
-                    plan = from + i < all_steps ? (batch == 0 ? FRESH : 0u) | (uint32_t)max(left, 0) << LEFT | place : PAST | place;
+                    plan = (from + i < all_steps ? (batch == 0 ? FRESH : 0u) | (uint32_t)(left + MMM_UNIT - 1) / MMM_UNIT * MMM_UNIT_BYTES : PAST) | place << PLACE;
                     asm volatile("" : "+v"(plan));   // waited for here
                     ahead_j = 0;
                 };
@@ -856,15 +858,17 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 wait_vmem<2 * OPS>();   // the blocks so far have landed
                 asm volatile("s_barrier" ::: "memory");
                 if (to_copy > 0) copy_block();
-                const bool filled = (int)(B0.what >> LEFT & 63u) > s * MMM_UNIT;   // (asked for as if all of its units were)
+                if ((B0.what & HELD) < BATCH_BYTES) {   // (asked for as if all of its units held one)
+                    const bool held = (uint32_t)lane * 16u < (B0.what & HELD);
 #pragma unroll
-                for (int g = 0; g < (WIDE ? 0 : GW); ++g) B0.bh[g][0] = filled ? B0.bh[g][0] : u32x4{0, 0, 0, 0};
+                    for (int g = 0; g < (WIDE ? 0 : GW); ++g) B0.bh[g][0] = held ? B0.bh[g][0] : u32x4{0, 0, 0, 0};
+                }
                 do {
                     turn(B0);
                     turn(B1);
                     turn(B2);
                     if (ahead_j > 60) {
-                        const uint32_t place = B2.what & PLACE;
+                        const uint32_t place = (B2.what & (FRESH - 1u)) >> PLACE;
                         const int step = (int)(place / PER_STEP);
                         window(lengths(step), step - chunk_begin, (int)(place % PER_STEP));
                     }
