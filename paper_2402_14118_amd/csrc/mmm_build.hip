@@ -68,7 +68,6 @@ struct BuildParams {
     int64_t M, K, N, NB, WA, WB, MT, MBA, KBA, NG;
     ElementTest test;
     int32_t pack;         // write packed B
-    int32_t x_streams;    // X is read past the caches
     int32_t y_unaligned;  // 16-bit Y whose rows do not start on 4-byte boundaries
     uint32_t n_b;               // segments x column tiles of B
     uint32_t n_a_wg, n_b_wg;    // workgroups for them
@@ -204,10 +203,10 @@ template <typename T> using block_no = typename std::conditional<sizeof(T) == 8,
 // v_writelane_b32 and DPP instead of selects, wave-uniform words only where a lane mask is wanted, no branch per row and
 // one base per block: the sixteen waves of a block share one scalar unit, and the scan of half-precision matrices was
 // bound by it (2048 x 16384, one column in ten: 36.5 us with pairs of k per lane, whose masks had to be interleaved there).
-// DEEP: two blocks ahead in registers instead of one, for 16-bit types, whose blocks are half as large, where a workgroup has
+// LARGE: X is read past the caches (see mmm_launch_build).  And DEEP: two blocks ahead in registers instead of one, for 16-bit types, whose blocks are half as large, where a workgroup has
 // several (columns 2048 x 16384: 28 -> 26 us for A, 41 -> 35.4 with B; with one or two blocks per workgroup the loads past
 // the last one cost more than they gain, 6.6 -> 9 us for 512 x 8192, and so do more bytes in flight for the wider types).
-template <typename T, int TEST, bool ROWS, bool DEEP>
+template <typename T, int TEST, bool ROWS, bool LARGE>
 __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no<T> bi0, block_no<T> bi1, int lane, int wave, AShared &sh)
 {
     ConstParams &p = reread(p0);
@@ -215,7 +214,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
     typedef typename Pattern<sizeof(T)>::type pattern;
     typedef block_no<T> no_t;
     constexpr int ESZ = (int)sizeof(T);
-    constexpr bool WIDE = ESZ >= 4;
+    constexpr bool WIDE = ESZ >= 4, DEEP = LARGE && !WIDE;
     constexpr int A_WORDS = Tile<T>::A_WORDS, A_COLS = 64 * A_WORDS;
     constexpr bool PARTED = Layout<T>::PARTED;
     constexpr bool WIDE_IMG = Layout<T>::ESZ % 4 == 0;   // rows w, w + 16, w + 32, w + 48 in the image, else in natural order
@@ -255,29 +254,23 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
         const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(static_cast<const char *>(p.X) + block_rows(bi, row_bytes) + k_lo * ESZ), 0,
             there ? (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)) : 0, 0x00020000);
-        auto elements = [&](auto policy) __attribute__((always_inline)) {
-            constexpr int POLICY = decltype(policy)::value;   // 2: not kept in the caches
+        constexpr int POLICY = LARGE ? 2 : 0;   // 2: not kept in the caches
 #pragma unroll
-            for (int t = 0; t < A_ROWS; ++t) {
-                const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
+        for (int t = 0; t < A_ROWS; ++t) {
+            const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
 #pragma unroll
-                for (int h = 0; h < A_WORDS; ++h) {
-                    const int at = (int)(off[h] + row);
-                    if constexpr (ESZ == 8) {
-                        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, POLICY);
-                        r.x[t][h] = (uint64_t)v.y << 32 | v.x;
-                    } else if constexpr (ESZ == 4) {
-                        r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, POLICY);
-                    } else {
-                        r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, POLICY);
-                    }
+            for (int h = 0; h < A_WORDS; ++h) {
+                const int at = (int)(off[h] + row);
+                if constexpr (ESZ == 8) {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, POLICY);
+                    r.x[t][h] = (uint64_t)v.y << 32 | v.x;
+                } else if constexpr (ESZ == 4) {
+                    r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, POLICY);
+                } else {
+                    r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, POLICY);
                 }
             }
-        };
-        if (p.x_streams)
-            elements(std::integral_constant<int, 2>{});
-        else
-            elements(std::integral_constant<int, 0>{});
+        }
         asm volatile("" ::: "memory");
     };
 
@@ -852,7 +845,7 @@ __device__ __forceinline__ bool scan_b(ConstParams &p0, uint32_t seg, uint32_t c
 }
 
 // ROWS: row-compacted mode (A laid out over the live rows of B; B built over them).
-template <typename T, int TEST, int BW, bool ROWS, bool DEEP>
+template <typename T, int TEST, int BW, bool ROWS, bool LARGE>
 __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void mmm_build_kernel(const BuildParams)
 {
     ConstParams &p = *(ConstParams *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -901,7 +894,7 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
     } else {
         const uint32_t down = mmm_divided(i, mmm_divisor{p.by_units.mul, p.by_units.shift});
         const int64_t bi0 = (int64_t)down * p.a_per_wg;
-        scan_a<T, TEST, ROWS, DEEP>(p, i - down * (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+        scan_a<T, TEST, ROWS, LARGE>(p, i - down * (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
     }
 }
 
@@ -1139,31 +1132,35 @@ ElementTest mmm_element_test(int32_t dtype, int32_t pred, float threshold)
 
 typedef void (*build_kernel_fn)(const BuildParams);
 
-template <typename T, int TEST, bool ROWS, bool DEEP> static build_kernel_fn build_kernel_width(int32_t bw)
+template <typename T, int TEST, bool ROWS, bool LARGE> static build_kernel_fn build_kernel_width(int32_t bw)
 {
-    return bw == 8    ? mmm_build_kernel<T, TEST, 8, ROWS, DEEP>
-           : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS, DEEP>
-                      : mmm_build_kernel<T, TEST, 32, ROWS, DEEP>;
+    return bw == 8    ? mmm_build_kernel<T, TEST, 8, ROWS, LARGE>
+           : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS, LARGE>
+                      : mmm_build_kernel<T, TEST, 32, ROWS, LARGE>;
 }
-template <typename T, bool ROWS, bool DEEP> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
+template <typename T, bool ROWS, bool LARGE> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
 {
-    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS, DEEP>(bw)
-         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS, DEEP>(bw)
-                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS, DEEP>(bw);
+    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS, LARGE>(bw)
+         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS, LARGE>(bw)
+                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS, LARGE>(bw);
 }
-template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows, bool deep)
+template <typename T, bool LARGE> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows)
 {
-    constexpr bool HALF = sizeof(T) == 2;
-    if (deep && HALF) return rows ? build_kernel_test<T, true, HALF>(mode, bw) : build_kernel_test<T, false, HALF>(mode, bw);
-    return rows ? build_kernel_test<T, true, false>(mode, bw) : build_kernel_test<T, false, false>(mode, bw);
+    if constexpr (sizeof(T) < 8)   // no row-compacted mode of doubles
+        if (rows) return build_kernel_test<T, true, LARGE>(mode, bw);
+    return build_kernel_test<T, false, LARGE>(mode, bw);
 }
-static build_kernel_fn build_kernel(int32_t dtype, int32_t form, int32_t mode, int32_t bw, bool rows, bool deep)
+template <typename T> static build_kernel_fn build_kernel_size(int32_t mode, int32_t bw, bool rows, bool large)
 {
-    if (form == MMM_FORM_PARTS) return build_kernel_rows<PartedFloat>(mode, bw, rows, deep);
-    return dtype == MMM_F64  ? build_kernel_test<double, false, false>(mode, bw)   // no row-compacted mode
-         : dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows, deep)
-         : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows, deep)
-                             : build_kernel_rows<float>(mode, bw, rows, deep);
+    return large ? build_kernel_rows<T, true>(mode, bw, rows) : build_kernel_rows<T, false>(mode, bw, rows);
+}
+static build_kernel_fn build_kernel(int32_t dtype, int32_t form, int32_t mode, int32_t bw, bool rows, bool large)
+{
+    if (form == MMM_FORM_PARTS) return build_kernel_size<PartedFloat>(mode, bw, rows, large);
+    return dtype == MMM_F64  ? build_kernel_size<double>(mode, bw, rows, large)
+         : dtype == MMM_BF16 ? build_kernel_size<uint16_t>(mode, bw, rows, large)
+         : dtype == MMM_F16  ? build_kernel_size<_Float16>(mode, bw, rows, large)
+                             : build_kernel_size<float>(mode, bw, rows, large);
 }
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s)
@@ -1197,12 +1194,6 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.NG = m->NG;
     const bool f64 = a.dtype == MMM_F64;
     p.pack = mmm_packs(m->M, a.dtype) ? 1 : 0;
-    // A large X goes past the caches: it is read once, and what the last-level cache (256 MB) keeps of it takes the place of the image and of packed B,
-    // which the multiplication reads next.  Whole passes over three sets of operands in turn, kept and not: X of 64 MB and more, 4096^3 floats, p = .05,
-    // 130.8 -> 128.3 us (both sides 39.3 -> 34.8), p = .2 231 -> 225, 2048 x 16384 x 4096 columns bf16 70.6 -> 67.0, ReLU floats 120 -> 117.8;
-    // 32 MB, 2048^3 doubles 64.7 -> 63.4, 1024 x 16384 x 4096 bf16 78.8 -> 75.4, 2900^3 floats the same; smaller ones may still be there from
-    // whoever wrote them: 2048^3 floats (16 MB) 37.4 and 39.1, 2900^3 bf16 45.4 and 47.4, 1448^3 doubles 40.9 and 44.6.
-    p.x_streams = (int64_t)m->M * m->K * (int64_t)(f64 ? 8 : a.dtype == MMM_F32 ? 4 : 2) >= (int64_t)32 << 20 ? 1 : 0;
     p.test = mmm_element_test(a.dtype, a.pred, a.threshold);
     p.y_unaligned = a.dtype != MMM_F32 && a.dtype != MMM_F64 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
     p.kinfo = m->kinfo;
@@ -1248,9 +1239,16 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.n_a_wg = (uint32_t)n_a_wg;
     p.n_b_wg = (uint32_t)n_b_wg;
     p.a_per_wg = (uint32_t)per_wg;
+    // A large X goes past the caches: it is read once, and what the last-level cache (256 MB) keeps of it takes the place of the image and of packed B,
+    // which the multiplication reads next.  Whole passes over three sets of operands in turn, kept and not: X of 64 MB and more, 4096^3 floats, p = .05,
+    // 130.8 -> 128.3 us (both sides 39.3 -> 34.8), p = .2 231 -> 225, 2048 x 16384 x 4096 columns bf16 70.6 -> 67.0, ReLU floats 120 -> 117.8;
+    // 32 MB, 2048^3 doubles 64.7 -> 63.4, 1024 x 16384 x 4096 bf16 78.8 -> 75.4, 2900^3 floats the same; smaller ones may still be there from
+    // whoever wrote them: 2048^3 floats (16 MB) 37.4 and 39.1, 2900^3 bf16 45.4 and 47.4, 1448^3 doubles 40.9 and 44.6.
+    // As an instance of its own: a branch between two sets of loads cost the small ones .04 us.  (Of 16-bit types 32 MB are 2048 blocks, four to a workgroup.)
+    const bool large = f64 || a.dtype == MMM_F32 ? (int64_t)m->M * m->K * (f64 ? 8 : 4) >= (int64_t)32 << 20 : per_wg >= 4;
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    hipLaunchKernelGGL(build_kernel(a.dtype, a.form, p.test.mode, m->bw, p.rows != nullptr, per_wg >= 4), grid, block, 0, s, p);
+    hipLaunchKernelGGL(build_kernel(a.dtype, a.form, p.test.mode, m->bw, p.rows != nullptr, large), grid, block, 0, s, p);
     return hipGetLastError();
 }
 
