@@ -217,3 +217,31 @@ def test_shorter_lists_over_longer_ones(bw, dtype, form):
         np.testing.assert_array_equal(run.run()[2], C_ref)
     finally:
         mm.mmm_set_option("float_form", -1)
+
+
+@pytest.mark.parametrize("dtype,bw", [(synth.DT_F32, 16), (synth.DT_BF16, 8), (synth.DT_F16, 32)], ids=["f32", "bf16", "f16"])
+@pytest.mark.parametrize("K,live", [
+    (64, "none"), (65, "last"), (300, 127), (300, 128), (300, 129),     # no segment, the last bit of a row word, whole segments and one row more
+    (5000, 1), (5000, "all"), (4097, 640),                              # 40 segments of which one, all, five hold a row
+    (65536, 300), (65537, 300), (70001, "last"),                        # a row word per thread, and more
+])
+def test_numbering_of_rows(K, live, dtype, bw):
+    """Row-compacted builds behind a build with every row on: the numbering, map rows of rows that are off, C."""
+    N = 544 if K < 10000 else 32                                        # three column tiles; one
+    rng = np.random.default_rng(K)
+    on = np.zeros(K, bool)
+    on[{"none": [], "last": [K - 1], "all": np.arange(K)}.get(live) if isinstance(live, str) else rng.permutation(K)[:live]] = True
+    w = synth.random_masked(70, K, N, bw, 0.3, 0.6, K, dist="smallint", dtype=dtype)
+    run = HipRun(w)
+    run.eng.set_path(mm.MMM_PATH_MATRIX)
+    run.build()
+    w.keep_rows = synth.pack_bits(on[None, :])
+    ab, bb, C_ref, _ = oracle.run_workload(w)
+    run.keep_rows = torch.from_numpy(w.keep_rows.view(np.int64)).cuda()
+    a, b, C = run.run()
+    np.testing.assert_array_equal(a, ab)
+    np.testing.assert_array_equal(b, bb)
+    np.testing.assert_array_equal(C, C_ref)
+    count, kmap, _, _ = run.eng.compacted()
+    assert int(count.cpu()[0]) == on.sum()
+    np.testing.assert_array_equal(kmap.cpu().numpy()[: on.sum()], np.flatnonzero(on))
