@@ -219,6 +219,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
     constexpr bool PARTED = Layout<T>::PARTED;
     constexpr bool WIDE_IMG = Layout<T>::ESZ % 4 == 0;   // rows w, w + 16, w + 32, w + 48 in the image, else in natural order
     constexpr int UNITS = MMM_AB_ROWS * (PARTED ? 2 : ESZ) / 16;   // 16-byte units per column (and part)
+    constexpr uint32_t COPIES = PARTED ? MMM_PARTS : 1;
     constexpr uint32_t OUTSIDE = 0x80000000u;       // past the end of every buffer resource below, whatever row offset is added
     const bool has_keep = p.keep_a != nullptr;
     constexpr bool compact = ROWS;
@@ -297,6 +298,9 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
             if ((m1 >> lane) & 1ull) sh.live[n0 + mbcnt64(m1)] = (uint8_t)(64 + lane);
         }
     }
+    // 16-bit elements and parts: the rotation of column k's eight 16-byte units in the stage.  Pieces of 8 bytes are written column by column and two
+    // units of a plane read column by column: neither finds two of sixteen columns' in the same banks.
+    auto turned = [](int k) { return (k >> 1 & 3) << 1 | (k >> 3 & 1); };
     auto block = [&](no_t bi, ABlock<T> &cur, int st, auto ahead) __attribute__((always_inline)) {
         ConstParams &p = reread(p0);
         constexpr int AHEAD = decltype(ahead)::value;   // the block whose loads take this one's place
@@ -373,7 +377,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
                     }
 #pragma unroll
                     for (int q = 0; q < MMM_PARTS; ++q)
-                        *reinterpret_cast<u32x2 *>(stage + q * MMM_PART_BYTES + k * 128 + ((wave ^ (((k >> 1) & 7) << 1)) << 3)) = part[q];
+                        *reinterpret_cast<u32x2 *>(stage + q * MMM_PART_BYTES + k * 128 + ((wave ^ (turned(k) << 1)) << 3)) = part[q];
                     continue;
                 }
                 char *at = stage + k * (UNITS * 16) + ((wave ^ (k & 15)) << 4);
@@ -389,7 +393,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
                 for (int t = 0; t < 2; ++t)
                     d[t] = pair[t][h] & ((__builtin_amdgcn_inverse_ballot_w64(word[2 * t][h]) ? 0xffffu : 0u) |
                                           (__builtin_amdgcn_inverse_ballot_w64(word[2 * t + 1][h]) ? 0xffff0000u : 0u));
-                *reinterpret_cast<uint2 *>(stage + k * 128 + ((wave ^ (((k >> 1) & 7) << 1)) << 3)) = make_uint2(d[0], d[1]);
+                *reinterpret_cast<uint2 *>(stage + k * 128 + ((wave ^ (turned(k) << 1)) << 3)) = make_uint2(d[0], d[1]);
             }
         }
         // lane t * A_WORDS + h takes the word of (row t, half h)
@@ -441,48 +445,46 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
                 if (lane == 0) p.a_wild[bi * p.KBA + bj] = wild != 0 ? 1 : 0;
             }
         }
-        // the image: column k (or k') of block row bi is one run of 64 elements
+        // the image: 4- and 8-byte elements: column k (or k') of block row bi is one run of 64; else four planes of 16 rows
         if (compact && bi == bi0) {
             base = 0;
             for (int w = 0; w < BUILD_WAVES; ++w) base += sh.before[w];
         }
-        char *img = p.a_img + (uint64_t)(uint32_t)bi * ((uint32_t)p.KBA * (MMM_AB_COLS * UNITS * 16)) + (uint64_t)base * (UNITS * 16);
-        auto stage_of = [&](int k, int unit, uint32_t col) -> int {   // where unit `unit` of image column `col` waits in the stage
-            // (16-bit: undo the rotation of the stage, apply that of the image, see mmm_img_swizzle)
-            return WIDE_IMG ? k * (UNITS * 16) + ((unit ^ (k & 15)) << 4) : k * 128 + ((unit ^ (int)mmm_img_swizzle(col) ^ ((k >> 1) & 7)) << 4);
-        };
-        if constexpr (PARTED) {
+        constexpr uint32_t COL_BYTES = MMM_AB_ROWS * (PARTED ? 2 : ESZ), PLANE_UNITS = 2 * MMM_AB_COLS;   // units of a plane: two per column
+        if constexpr (!WIDE_IMG) {   // a unit (of each part) per thread
+            static_assert(MMM_AB_COLS * UNITS == BUILD_THREADS, "");
+            char *const blocks = p.a_img + (uint64_t)(uint32_t)bi * ((uint32_t)p.KBA * (MMM_PART_BYTES * COPIES));
+            auto put = [&](char *to, int k, int unit) __attribute__((always_inline)) {
+                const char *const from = stage + k * 128 + ((unit ^ turned(k)) << 4);
+#pragma unroll
+                for (int i = 0; i < (int)COPIES; ++i)
+                    *reinterpret_cast<uint4 *>(to + i * MMM_PART_BYTES) = *reinterpret_cast<const uint4 *>(from + i * MMM_PART_BYTES);
+            };
+            if (compact) {   // the eight units of a column side by side: few waves have any (as above, 31.3 -> 28.2; floats in parts, 45.0 -> 42.3)
+                if ((int)threadIdx.x < cols * UNITS) {
+                    const uint32_t col = base + threadIdx.x / UNITS, unit = threadIdx.x % UNITS;
+                    put(blocks + (col / MMM_AB_COLS * (MMM_PART_BYTES * COPIES) + unit / 2u * MMM_PLANE_BYTES + col % MMM_AB_COLS * MMM_PLANE_COL_BYTES + unit % 2u * 16u),
+                        (int)sh.live[threadIdx.x / UNITS], (int)unit);
+                }
+            } else {   // plane by plane
+                put(blocks + ((uint32_t)bj * (MMM_PART_BYTES * COPIES) + threadIdx.x * 16u), (int)(threadIdx.x % PLANE_UNITS / 2u),
+                    (int)(threadIdx.x / PLANE_UNITS * 2u + threadIdx.x % 2u));
+            }
+        } else {
+            char *img = p.a_img + (uint64_t)(uint32_t)bi * ((uint32_t)p.KBA * (MMM_AB_COLS * COL_BYTES)) + (uint64_t)base * COL_BYTES;
+            auto stage_of = [&](int k, int unit) -> int { return k * (int)COL_BYTES + ((unit ^ (k & 15)) << 4); };   // where it waits in the stage
             if (compact) {
-                char *const blocks = p.a_img + (uint64_t)(uint32_t)bi * ((uint32_t)p.KBA * MMM_BLOCK_PARTS_BYTES);
                 for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
                     const int j = q / UNITS, k = (int)sh.live[j];
-                    const uint32_t col = base + (uint32_t)j;
-                    const int at = stage_of(k, q % UNITS, col);
-                    char *const to = blocks + (size_t)(col / MMM_AB_COLS) * MMM_BLOCK_PARTS_BYTES + (col % MMM_AB_COLS) * 128u + (uint32_t)(q % UNITS) * 16u;
-#pragma unroll
-                    for (int i = 0; i < MMM_PARTS; ++i)
-                        *reinterpret_cast<uint4 *>(to + i * MMM_PART_BYTES) = *reinterpret_cast<const uint4 *>(stage + i * MMM_PART_BYTES + at);
+                    *reinterpret_cast<uint4 *>(img + (uint32_t)q * 16u) = *reinterpret_cast<const uint4 *>(stage + stage_of(k, q % UNITS));
                 }
-            } else {   // a unit of each part per thread
-                static_assert(A_COLS * UNITS == BUILD_THREADS || !PARTED, "");
-                char *const to = p.a_img + ((size_t)bi * p.KBA + (size_t)bj) * MMM_BLOCK_PARTS_BYTES + threadIdx.x * 16u;
-                const int j = threadIdx.x / UNITS, at = stage_of(j, threadIdx.x % UNITS, (uint32_t)j);
+            } else {   // two units per thread
+                const int at = stage_of(threadIdx.x / UNITS, threadIdx.x % UNITS);
 #pragma unroll
-                for (int i = 0; i < MMM_PARTS; ++i)
-                    *reinterpret_cast<uint4 *>(to + i * MMM_PART_BYTES) = *reinterpret_cast<const uint4 *>(stage + i * MMM_PART_BYTES + at);
+                for (int i = 0; i < A_COLS * UNITS / BUILD_THREADS; ++i)
+                    *reinterpret_cast<uint4 *>(img + (threadIdx.x * 16u + (uint32_t)(i * BUILD_THREADS * 16))) =
+                        *reinterpret_cast<const uint4 *>(stage + at + i * (BUILD_THREADS * 16));
             }
-        } else if (compact) {
-            for (int q = threadIdx.x; q < cols * UNITS; q += BUILD_THREADS) {
-                const int j = q / UNITS, k = (int)sh.live[j];
-                *reinterpret_cast<uint4 *>(img + (uint32_t)q * 16u) = *reinterpret_cast<const uint4 *>(stage + stage_of(k, q % UNITS, base + j));
-            }
-        } else {   // two (16-bit: one) units per thread
-            const int j = threadIdx.x / UNITS;
-            const int at = stage_of(j, threadIdx.x % UNITS, (uint32_t)j);
-#pragma unroll
-            for (int i = 0; i < A_COLS * UNITS / BUILD_THREADS; ++i)
-                *reinterpret_cast<uint4 *>(img + (threadIdx.x * 16u + (uint32_t)(i * BUILD_THREADS * 16))) =
-                    *reinterpret_cast<const uint4 *>(stage + at + i * (BUILD_THREADS * 16));
         }
     };
     if constexpr (DEEP) {
@@ -777,7 +779,8 @@ __device__ __forceinline__ uint32_t scan_b(ConstParams &p0, uint32_t seg, uint32
 #pragma unroll 1
             for (uint32_t slot = MMM_UNIT * s4; slot < n_out; slot += 4 * MMM_UNIT, out += 4 * MMM_PARTS * MMM_UNIT_BYTES) {   // (units past the last are not read)
                 auto value = [&](uint32_t entry, uint32_t at) __attribute__((always_inline)) -> uint32_t {
-                    const uint32_t k = (entry >> 3) & (SEG - 1u);   // see mmm_list_entry
+                    const uint32_t k = entry & (SEG - 1u);   // see mmm_list_entry
+                    static_assert(MMM_PARTS_PITCH % SEG == 0, "");
                     bool there = at < n_out && col_ok;
                     if (SPLIT) there = there && ((block_rows[k / 8] >> (k % 8)) & 1u);
                     const uint32_t row = ROWS ? (uint32_t)sh.kk[k] : seg * SEG + k;
@@ -907,9 +910,12 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
             }
         }
     } else {
-        const uint32_t down = mmm_divided(i, mmm_divisor{p.by_units.mul, p.by_units.shift});
+        // Row-compacted planes: the runs of columns of workgroups side by side share cache lines, and neighbours on one XCD put them together in its L2
+        // (2048 x 1638 of 16384 bf16, both sides: 33.1 -> 31.3 us).
+        const uint32_t at = ROWS && Layout<T>::ESZ % 4 != 0 ? (i & 7u) * (p.n_a_wg >> 3) + min(i & 7u, p.n_a_wg & 7u) + (i >> 3) : i;
+        const uint32_t down = mmm_divided(at, mmm_divisor{p.by_units.mul, p.by_units.shift});
         const int64_t bi0 = (int64_t)down * p.a_per_wg;
-        scan_a<T, TEST, ROWS, LARGE>(p, i - down * (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+        scan_a<T, TEST, ROWS, LARGE>(p, at - down * (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
     }
 }
 
@@ -985,14 +991,14 @@ __global__ __launch_bounds__(MMM_AB_COLS) void mmm_lists_kernel(const char *a_im
         total += off[q];
     }
     uint2 *ent = a_ent + (size_t)b * MMM_AB_CAP;
-    const char *col = a_img + ((size_t)bi * KBA * MMM_AB_COLS + kc) * (MMM_AB_ROWS * sizeof(T));
+    const char *block = a_img + (size_t)b * (MMM_AB_CAP * Layout<T>::ESZ);
     for (uint64_t m = rows; m != 0; m &= m - 1) {
         const int r = __builtin_ctzll(m);
         uint32_t bits;
         if constexpr (Layout<T>::PARTED) {
-            bits = __float_as_uint(mmm_whole_float(a_img + (size_t)b * MMM_BLOCK_PARTS_BYTES + c * 128 + mmm_img_row(2, (uint32_t)kc, (uint32_t)r), MMM_PART_BYTES));
+            bits = __float_as_uint(mmm_whole_float(block + mmm_img_pos(2, (uint32_t)c, (uint32_t)r), MMM_PART_BYTES));
         } else {
-            bits = f32_bits<T>(*reinterpret_cast<const T *>(col + mmm_img_row(sizeof(T), (uint32_t)kc, (uint32_t)r)));
+            bits = f32_bits<T>(*reinterpret_cast<const T *>(block + mmm_img_pos(sizeof(T), (uint32_t)c, (uint32_t)r)));
         }
         ent[at++] = make_uint2(mmm_slab_pos((uint32_t)r, (uint32_t)c), bits);
     }

@@ -42,20 +42,22 @@ constexpr uint32_t MMM_SLAB_SPARE = mmm_slab_pos(0, MMM_AB_COLS);
 // mask drops an element.  4-byte elements: the rows r, r+16, r+32, r+48 of a column are neighbours, so that
 // one 16-byte LDS read yields the operands of all four 16-row tiles for one k, and the 16 lanes of an
 // operand read 256 contiguous bytes.  8-byte elements: the same in two halves of a column, rows r, r+16 at
-// 16 r and rows r+32, r+48 at 256 + 16 r.  16-bit elements: natural order, as the transposing LDS read needs;
-// the column's 16-byte units are rotated with k (xor), so that the columns k .. k+7 of one row tile lie in
-// different LDS banks.
-__host__ __device__ constexpr uint32_t mmm_img_swizzle(uint32_t col) { return ((col >> 1) & 3u) << 1; }
-__host__ __device__ constexpr uint32_t mmm_img_row(size_t esz, uint32_t col, uint32_t row)   // byte offset inside a column
+// 16 r and rows r+32, r+48 at 256 + 16 r.  16-bit elements: a block is four planes of 16 rows, [plane][128 columns][16 rows], so that
+// the kernel reads the same place of each plane: one address for all row tiles and immediate offsets.  (With whole columns of 64 rows, their units
+// rotated with k against bank conflicts, the addresses took 15 vector instructions per batch instead of four: see `turn`.)
+constexpr uint32_t MMM_PLANE_ROWS = 16, MMM_PLANE_COL_BYTES = MMM_PLANE_ROWS * 2, MMM_PLANE_BYTES = MMM_AB_COLS * MMM_PLANE_COL_BYTES;
+// byte offset of an element inside its block (floats in parts: esz 2, inside the part's)
+__host__ __device__ constexpr uint32_t mmm_img_pos(size_t esz, uint32_t col, uint32_t row)
 {
-    return esz == 8   ? (row >> 5) * 256u + (row & 15u) * 16u + ((row >> 4) & 1u) * 8u
-           : esz == 4 ? (row & 15u) * 16u + (row >> 4) * 4u : (((row >> 3) ^ mmm_img_swizzle(col)) << 4) + (row & 7u) * 2u;
+    return esz == 8   ? col * 512u + (row >> 5) * 256u + (row & 15u) * 16u + ((row >> 4) & 1u) * 8u
+           : esz == 4 ? col * 256u + (row & 15u) * 16u + (row >> 4) * 4u
+                      : row / MMM_PLANE_ROWS * MMM_PLANE_BYTES + col * MMM_PLANE_COL_BYTES + row % MMM_PLANE_ROWS * 2u;
 }
 // Packed B: per group of 16 columns and segment of 128 k the occupied rows, one after another ("slots"),
 // at [group][segment][128 slots][16 columns]; the number of slots; and per slot where its column of A
 // sits in the kernel's LDS ring of `ring` blocks: column 128 * (segment mod ring) + k, in units of 256 bytes (4- and
-// 8-byte elements) or of 16 bytes with the rotation folded in (16-bit elements).  Slots past the
-// last name the ring's zero column, which stands behind the blocks (16-bit elements: in front of them, so that its entry is 0).
+// 8-byte elements) or of 32 bytes in a plane (16-bit elements).  Slots past the
+// last name the ring's zero column, which stands behind the blocks (16-bit elements: in front of each plane's columns, so that its entry is 0).
 // A vector-memory instruction occupies a compute unit for 8 cycles up to 4 bytes per lane and for 16 above, whether
 // it loads 8 or 16.  So the entries, and 16-bit values, are stored in the order in which the kernel's lanes take
 // them, one load per batch of slots.  s: lane / 16, c: column.
@@ -82,7 +84,7 @@ __host__ __device__ constexpr uint32_t mmm_zero_col(int ring) { return (uint32_t
 // An element outside [2^-110, 2^55) is not held exactly (or its cross products could overflow where the product does not; infinities and NaN are among
 // them): its three parts hold its bits instead (MMM_PARTS_RAW), a block of A and a segment of a group of B that have one are marked,
 // and are multiplied as floats, put together again (mmm_whole_float).
-// Image: [block of 64 x 128][part][column][64 rows], columns as of the 16-bit types.  Packed B: batches of 32 slots as of the
+// Image: [block of 64 x 128][part], parts as blocks of the 16-bit types.  Packed B: batches of 32 slots as of the
 // 16-bit types, [unit of slots][part].  As an "element size": 6.
 // Slots come in units of eight, as those of the 16-bit types: slot 8u + 4h + e of a segment is value 4h' + e of [u][c][8], entry h' of [4u + e][2], with h' = h in even units and
 // 1 - h in odd ones.  A unit is what sixteen lanes of the kernel take, so that a batch can be put together from the units of two segments.  (The
@@ -104,15 +106,17 @@ __device__ inline float mmm_whole_float(const char *at, size_t step)
     return p2 == MMM_PARTS_RAW ? __uint_as_float(p0 << 16 | p1) : __uint_as_float(p0 << 16) + (__uint_as_float(p1 << 16) + __uint_as_float(p2 << 16));
 }
 enum { MMM_FORM_PLAIN = 0, MMM_FORM_PARTS = 1 };
-// col: ring column (4- and 8-byte elements: mmm_zero_col for the zero column; 16-bit: the blocks begin behind it, 128 bytes on)
+// col: ring column (4- and 8-byte elements: mmm_zero_col for the zero column; 16-bit: a plane's columns, of all blocks of the ring, begin behind it; parts: blocks
+// one after another)
+constexpr uint32_t MMM_PARTS_PITCH = MMM_BLOCK_PARTS_BYTES / MMM_PLANE_COL_BYTES;   // from a block to the next, in those units
 __host__ __device__ constexpr uint32_t mmm_list_entry(size_t esz, uint32_t col)
 {
-    return esz == 8 ? col * 2 : esz == 4 ? col : (col << 3 | mmm_img_swizzle(col)) + (esz == MMM_PARTS_ESZ ? col / MMM_AB_COLS * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 8);
+    return esz == 8 ? col * 2 : esz == 4 ? col : esz == MMM_PARTS_ESZ ? col / MMM_AB_COLS * MMM_PARTS_PITCH + col % MMM_AB_COLS : col + 1;
 }
 // and back, inside its block
 __host__ __device__ constexpr uint32_t mmm_list_entry_k(size_t esz, uint32_t entry, uint32_t block_in_ring)
 {
-    return (esz == 8 ? entry >> 1 : esz == 4 ? entry : (entry - (esz == MMM_PARTS_ESZ ? block_in_ring * (MMM_BLOCK_PARTS_BYTES - MMM_PART_BYTES) / 16 : 8u)) >> 3) -
+    return (esz == 8 ? entry >> 1 : esz == 4 ? entry : esz == MMM_PARTS_ESZ ? entry - block_in_ring * (MMM_PARTS_PITCH - MMM_AB_COLS) : entry - 1) -
            block_in_ring * MMM_AB_COLS;
 }
 __host__ __device__ constexpr uint32_t mmm_list_pos(size_t esz, uint32_t slot)

@@ -22,7 +22,7 @@
 // so every vector instruction costs matrix time.  Per quad of four listed k the loop issues one v_perm_b32
 // (LDS address of the A operand), one ds_read_b128 (the operands of all four 16-row tiles), one
 // buffer_load_dword with an immediate offset (B) and four matrix instructions.  16-bit inputs use
-// v_mfma_f32_16x16x32 on 32 listed k, with ds_read_b64_tr_b16 gathering their A operands and one load of 16 bytes per
+// v_mfma_f32_16x16x32 on 32 listed k, with ds_read_b64_tr_b16 gathering their A operands, two addresses for all row tiles, and one load of 16 bytes per
 // lane for B's.
 //
 // Floats whose lists are long are multiplied in three bf16 parts (FloatParts; see MMM_PARTS in mmm_internal.h and choose_form):
@@ -169,16 +169,21 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     constexpr int RING = mmm_ring(sizeof(T));
     constexpr int COLB = TM * ESZ;                  // bytes per LDS column
     constexpr int SLAB = KC * COLB;                 // bytes per block of A
-    constexpr int ZERO_AT = ESZ == 2 ? 0 : RING * SLAB;   // the ring's zero column (see mmm_list_entry)
-    constexpr int BLOCKS_AT = ESZ == 2 ? COLB : 0;
-    constexpr int DMA = SLAB / 1024 / NW;           // copies per wave and block
+    // 16-bit types: the ring is four planes (two where 32 rows are computed), each a zero column and its columns of all blocks (see mmm_img_pos)
+    constexpr bool PLANES = ESZ == 2;
+    constexpr int PLANE_PITCH = PLANES ? RING * (int)MMM_PLANE_BYTES + (int)MMM_PLANE_COL_BYTES : (int)MMM_PLANE_BYTES;   // (in parts: inside a block's part)
+    constexpr int COPIED = PLANES ? RT * (int)MMM_PLANE_BYTES : SLAB;   // bytes of a block that are copied
+    constexpr int PLACE_BYTES = PLANES ? (int)MMM_PLANE_BYTES : SLAB;   // from a place of the ring to the next
+    constexpr int DMA = COPIED / 1024 / NW;         // copies per wave and block
+    constexpr int DMA_PLANES = PLANES && DMA > 4 ? DMA / 4 : 1;   // in so many planes
     constexpr int BATCH = WIDE ? 16 : 32;           // list slots per batch
     constexpr int OPS = WIDE ? 4 * GW + 1 : PARTS * GW + 1;   // vector-memory operations request() makes
     constexpr int SEGB = KC * MMM_GROUP_COLS * ESZ;       // bytes of a packed segment
-    static_assert(DMA * NW * 1024 == SLAB, "whole copies");
+    static_assert(DMA * NW * 1024 == COPIED && (!PLANES || DMA <= 4 || DMA % 4 == 0), "whole copies, inside a plane");
     typedef elem_t avec __attribute__((ext_vector_type(RT)));   // 4- and 8-byte types: A operands of the RT row tiles for one k
 
     constexpr int RING_BYTES = RING * SLAB + (PARTED ? 0 : COLB);
+    static_assert(!PLANES || TM / 16 * PLANE_PITCH == RING_BYTES, "");
     static_assert(!PARTED || (RT == TM / 16 && KS == 1 && RING == 3), "");
     __shared__ __align__(1024) char rings[KS * RING_BYTES];
     static_assert(!FILTER || ESZ == 4, "");
@@ -253,14 +258,30 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // ---- A: block ch of this row tile to place ch mod RING (the builder's list entries assume that place)
     const char *src = p.a_img + ((uint64_t)(uint32_t)tile_m * (uint32_t)p.KBA + (uint32_t)chunk_begin) * SLAB;   // the next block to copy
     int to_copy = chunk_end - chunk_begin;                                       // blocks from there on
-    const uint32_t dma_v = (uint32_t)(wave * DMA * 1024 + lane * 16);
-    const uint32_t place0 = ring_off + (uint32_t)(BLOCKS_AT + wave * DMA * 1024);
-    uint32_t place = (uint32_t)chunk_begin % (uint32_t)RING * SLAB;
+    uint32_t dma_v = (uint32_t)(wave * DMA * 1024 + lane * 16);
+    const uint32_t dma_plane = (uint32_t)(wave * DMA) * 1024u / MMM_PLANE_BYTES;
+    const uint32_t place0 = ring_off + (PLANES ? dma_plane * (uint32_t)PLANE_PITCH + MMM_PLANE_COL_BYTES + (uint32_t)(wave * DMA * 1024) % MMM_PLANE_BYTES
+                                               : (uint32_t)(wave * DMA * 1024));
+    uint32_t place = (uint32_t)chunk_begin % (uint32_t)RING * PLACE_BYTES;
+    // (16-bit types, whose turns are bound by their instructions: the place is the block's number, masked, and the source moves on in the lanes' offset)
+    uint32_t copy_at = (uint32_t)chunk_begin * MMM_PLANE_BYTES;
+    const uint32_t copy_end = (uint32_t)chunk_end * MMM_PLANE_BYTES;
+    auto more_to_copy = [&]() __attribute__((always_inline)) { return PLANES ? copy_at < copy_end : to_copy > 0; };
     auto copy_block = [&]() __attribute__((always_inline)) {
-        copy_to_lds<DMA>(src, dma_v, place0 + place);
-        src += SLAB;
-        place = place == (RING - 1) * SLAB ? 0 : place + SLAB;
-        --to_copy;
+        if constexpr (PLANES) {
+            static_assert((RING & (RING - 1)) == 0 || !PLANES, "");
+            const uint32_t to = place0 + (copy_at & (uint32_t)((RING - 1) * PLACE_BYTES));
+            copy_to_lds<DMA / DMA_PLANES>(src, dma_v, to);
+            if constexpr (DMA_PLANES > 1) copy_to_lds<DMA / DMA_PLANES>(src + MMM_PLANE_BYTES, dma_v, to + PLANE_PITCH);
+            static_assert(DMA_PLANES <= 2, "");
+            dma_v += SLAB;
+            copy_at += MMM_PLANE_BYTES;
+        } else {
+            copy_to_lds<DMA>(src, dma_v, place0 + place);
+            src += SLAB;
+            place = place == (RING - 1) * SLAB ? 0 : place + SLAB;
+            --to_copy;
+        }
     };
 
     // ---- B: one batch of a group's list in registers
@@ -293,7 +314,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     };
 
     const uint32_t c16 = (uint32_t)c * 16u;
-    const uint32_t chunk8 = (uint32_t)(lane & 3) * 8u;
+    const uint32_t operand_at = ring_off + (uint32_t)(lane & 3) * 8u;   // this lane's four rows of a plane's column
     // 4- and 8-byte types: the operands of four quads, A's at these ring addresses; left: slots of the list from the batch's
     // first on (at least one)
     auto multiply_quads = [&](const uint32_t (&at)[4], const elem_t (&bf)[WIDE ? GW : 1][4], int left) __attribute__((always_inline)) {
@@ -345,12 +366,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                                     __builtin_amdgcn_perm(b.list.y, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.y, c16, 0x0c070600u)};
             multiply_quads(at, b.bf, left);
         } else {
-            // ring address: entry * 16 with the rotation of the column's units in bits 5 and 6, plus this lane's four
-            // rows; row tile r is 32 bytes on, before rotation
-            const uint32_t at[2] = {(b.entry << 4 & 0xffff0u) | chunk8, (b.entry >> 12 & 0xffff0u) | chunk8};
+            // columns of 32 bytes; the plane of row tile r, and the part, are immediate offsets
+            const uint32_t at[2] = {operand_at + (b.entry & 0xffffu) * MMM_PLANE_COL_BYTES, operand_at + (b.entry >> 16) * MMM_PLANE_COL_BYTES};
             auto operand = [&](int q, int h, int r) __attribute__((always_inline)) -> u32x2 {
                 typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
-                return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(ring3 + (at[h] ^ (uint32_t)(r * 32)) + q * MMM_PART_BYTES)));
+                return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)((lds_char *)(uintptr_t)at[h] + (r * PLANE_PITCH + q * (int)MMM_PART_BYTES))));
             };
             // The whole batch whatever its length: slots past the end name the zero column (floats in parts: the block's
             // first) and hold zeros, units past the end come as zeros.  (A branch to a 16-slot instruction for short lists costs more, in moved accumulators,
@@ -396,7 +416,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     auto step = [&](int n, int n_next, Batch &b) __attribute__((always_inline)) {
         wait_vmem<(RING - 1) * OPS>();
         asm volatile("s_barrier" ::: "memory");
-        if (to_copy > 0) copy_block();
+        if (more_to_copy()) copy_block();
         if (n > 0) {
             multiply(b, n);
             if (n > BATCH) {
@@ -432,33 +452,45 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // one to a step, and the queue's beginning costs more than it gives (4096^3, p = .05, floats 89.5 -> 93.7, 2048^3, p = .1,
     // doubles 43.3 -> 45.2).
     constexpr int PER_STEP = KC / BATCH;   // batches that fit in a segment
-    constexpr uint32_t PAST = 1u << 31, FRESH = 1u << 30, PLACE = 11, BATCH_BYTES = BATCH * MMM_GROUP_COLS * ESZ, HELD = 7u * MMM_UNIT_BYTES;
-    static_assert(WIDE || PARTED || (BATCH_BYTES == 1u << (PLACE - 1) && MMM_UNIT * MMM_GROUP_COLS * ESZ == MMM_UNIT_BYTES), "");
-    uint32_t plan = 0;                                       // lane j: the j-th of the next batches: PAST the last, FRESH: first of its step, place << PLACE
-                                                             //   (below 2^17), bytes of its units that hold a slot
+    constexpr uint32_t PAST = 1u << 31, FRESH = 1u, BATCH_BYTES = BATCH * MMM_GROUP_COLS * ESZ, PLACE = PAST - BATCH_BYTES;
+    static_assert(WIDE || PARTED || (BATCH_BYTES == 1024 && MMM_UNIT * MMM_GROUP_COLS * ESZ == MMM_UNIT_BYTES), "");
+    uint32_t plan = 0;                                       // lane j: the j-th of the next batches: PAST the last, FRESH: first of its step, bytes up to it in
+                                                             //   the group's area (below 2^27)
+    uint32_t ends = 0;                                       // and where its last unit that holds a slot ends there
     int ahead_j = 0;                                         // the one requested last
-    auto request_at = [&](Batch &b, uint32_t what) __attribute__((always_inline)) {
+    auto request_at = [&](Batch &b, uint32_t what, uint32_t end) __attribute__((always_inline)) {
         b.what = what;
-        const uint32_t off_v = (what & (FRESH - (1u << PLACE))) >> 1;
+        const uint32_t off_v = what & PLACE;
+        constexpr uint32_t PER_ENTRY = BATCH_BYTES / (BATCH * 2);
+        // The buffers end behind the last unit that holds a slot: lanes of the others get zeros, which as entries name the zero column, and nothing is fetched
+        // for them (hidden by a lane offset of their own, two vector instructions in front of the load: 171 x 2775 x 1904, p = .33, 10.2 instead of 9.7 us, 755 x 544
+        // live x 2560 9.15 and 8.95).  So a batch without any, of an empty list or behind the last one, needs no branch either.
+        const __amdgpu_buffer_rsrc_t entries = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(p.bp_list) + seg0 * KC, 0, (int)(end / PER_ENTRY), 0x00020000);
         asm volatile("" ::: "memory");   // (as in `request`)
-        b.entry = __builtin_amdgcn_raw_buffer_load_b32(list_rsrc, (lane >> 2) * 4, (int)(off_v / (BATCH_BYTES / (BATCH * 2))), 0);
+        b.entry = __builtin_amdgcn_raw_buffer_load_b32(entries, (lane >> 2) * 4, (int)(off_v / PER_ENTRY), 0);
 #pragma unroll
         for (int g = 0; g < (WIDE ? 0 : GW); ++g) {
-            // the buffer ends behind the last unit that holds a slot: the lanes of the others get zeros, and nothing is fetched for them
-            // (hidden by a lane offset of their own, two vector instructions in front of the load: 171 x 2775 x 1904, p = .33, 10.2 instead of 9.7 us, 755 x 544 live x 2560 9.15 and 8.95)
-            const __amdgpu_buffer_rsrc_t held = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p.bp_val) + seg0 * SEGB, 0, (int)(off_v + (what & HELD)) + g * val_next, 0x00020000);
+            const __amdgpu_buffer_rsrc_t held = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(p.bp_val) + seg0 * SEGB, 0, (int)end + g * val_next, 0x00020000);
             b.bh[g][0] = __builtin_amdgcn_raw_buffer_load_b128(held, lane * 16, (int)off_v + g * val_next, 0);
         }
         asm volatile("" ::: "memory");
     };
+    auto request_planned = [&](Batch &b, int j) __attribute__((always_inline)) {
+        request_at(b, (uint32_t)__builtin_amdgcn_readlane(plan, j), (uint32_t)__builtin_amdgcn_readlane(ends, j));
+    };
+    // A turn is bound by its instructions, which are a chain that all waves of a workgroup go through between two barriers: one branch and three scalar
+    // instructions more cost 80 cycles of 1000 (512 x 8192 x 4096: 19.8 -> 20.9 us), copies that never wait, batches asked for twice as early, one barrier for two
+    // steps nothing or less.  Hence planes (4 instead of 15 vector instructions for addresses), no branch around empty lists, blocks copied by their
+    // number.  Multiplication, us: 777 x 3001 x 1992 half, blocks of 8, 13.1 -> 12.1, 256 x 8192 x 4096, blocks of 32, p = .2, 17.55 -> 16.95,
+    // 512 x 8192 x 4096 19.8 -> 19.5, columns 2048 x 1638 of 16384 x 4096 32.9 -> 32.2; floats in parts, 4096^3, p = .2, 176 -> 169, .4 295 -> 282.
     auto turn = [&](Batch &b) __attribute__((always_inline)) {
         if (b.what & FRESH) {
             wait_vmem<(RING - 1) * OPS>();
             asm volatile("s_barrier" ::: "memory");
-            if (to_copy > 0) copy_block();
+            if (more_to_copy()) copy_block();
         }
-        if (b.what & HELD) multiply(b, BATCH);
-        request_at(b, (uint32_t)__builtin_amdgcn_readlane(plan, ++ahead_j));
+        multiply(b, BATCH);
+        request_planned(b, ++ahead_j);
     };
 
     // ---- Floats in parts: lists joined.  A batch takes its four units of eight slots (one for each sixteen lanes) from where the one before
@@ -519,11 +551,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             const uint32_t barriers = b.what >> BARRIERS & 3u;
             wait_vmem<OPS>();   // (a request at least came after the copies behind the barrier before)
             asm volatile("s_barrier" ::: "memory");
-            if (to_copy > 0) copy_block();
+            if (more_to_copy()) copy_block();
             if (barriers > 1) {
                 wait_vmem<0>();
                 asm volatile("s_barrier" ::: "memory");
-                if (to_copy > 0) copy_block();
+                if (more_to_copy()) copy_block();
             }
             passed += (int)barriers;
         }
@@ -639,7 +671,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             const bool early = n <= BATCH;   // S2 is free
             if (n_next > 0) fetch(next, ch + 1, 0);
             if (early && n_next > BATCH) fetch(S2, ch + 1, 1);
-            if (to_copy > 0) copy_block();
+            if (more_to_copy()) copy_block();
             if (n > 0) {
                 multiply_slots(b, n);
                 if (n > BATCH) {
@@ -681,7 +713,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             if constexpr (PARTED)
                 request_units(B0, (uint32_t)chunk_begin * UNITS | (UNITS - 4u) << JUMP);   // as if the first list had four units
             else
-                request_at(B0, BATCH_BYTES | (uint32_t)chunk_begin * PER_STEP << PLACE);
+                request_at(B0, (uint32_t)chunk_begin * (PER_STEP * BATCH_BYTES), ((uint32_t)chunk_begin * PER_STEP + 1u) * BATCH_BYTES);
         }
         if constexpr (PARTED) {
             for (int i = lane; i < p.KBA; i += 64) marks |= p.a_wild[(int64_t)tile_m * p.KBA + i];
@@ -689,9 +721,13 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         }
 #pragma unroll
         for (int i = 0; i < RING - 1; ++i)
-            if (to_copy > 0) copy_block();
-        if constexpr (!PARTED)
-            for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + ZERO_AT)[i] = 0;
+            if (more_to_copy()) copy_block();
+        if constexpr (PLANES) {
+            for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64)
+                reinterpret_cast<uint32_t *>(ring)[i / (int)(MMM_PLANE_COL_BYTES / 4) * (PLANE_PITCH / 4) + i % (int)(MMM_PLANE_COL_BYTES / 4)] = 0;
+        } else if constexpr (!PARTED) {   // the ring's zero column (see mmm_list_entry)
+            for (int i = wave * 64 + lane; i < COLB / 4; i += NW * 64) reinterpret_cast<uint32_t *>(ring + RING * SLAB)[i] = 0;
+        }
         if constexpr (WIDE) {
             request(B0, off_v, off_l);
             request(B1, off_v + SEGB, off_l + SEG_L);
@@ -829,7 +865,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                 ahead_j = 2;
                 wait_vmem<2 * OPS>();   // the blocks so far have landed
                 asm volatile("s_barrier" ::: "memory");
-                if (to_copy > 0) copy_block();
+                if (more_to_copy()) copy_block();
                 do {
                     joined(B0);
                     joined(B1);
@@ -849,21 +885,22 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     const uint64_t begun = ((uint64_t)hi << 32 | lo) & (~0ull >> (63 - lane));   // (bit 0 is set)
                     const int i = __popcll(begun) - 1, batch = lane - (63 - __builtin_clzll(begun)) + (i == 0 ? skip : 0);
                     const int left = max(min((int)__shfl(n, i, 64) - batch * BATCH, BATCH), 0);
-                    const uint32_t place = (uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch;
-                    plan = (from + i < all_steps ? (batch == 0 ? FRESH : 0u) | (uint32_t)(left + MMM_UNIT - 1) / MMM_UNIT * MMM_UNIT_BYTES : PAST) | place << PLACE;
-                    asm volatile("" : "+v"(plan));   // waited for here
+                    const uint32_t place = ((uint32_t)(chunk_begin + from + i) * PER_STEP + (uint32_t)batch) * BATCH_BYTES;
+                    plan = place | (from + i >= all_steps ? PAST : batch == 0 ? FRESH : 0u);
+                    ends = place + (uint32_t)(left + MMM_UNIT - 1) / MMM_UNIT * MMM_UNIT_BYTES;   // (behind the last step nothing is left)
+                    asm volatile("" : "+v"(plan), "+v"(ends));   // waited for here
                     ahead_j = 0;
                 };
                 window(first_lengths, 0, 0);
                 B0.what = (uint32_t)__builtin_amdgcn_readlane(plan, 0) & ~FRESH;   // (begun here)
-                request_at(B1, (uint32_t)__builtin_amdgcn_readlane(plan, 1));
-                request_at(B2, (uint32_t)__builtin_amdgcn_readlane(plan, 2));
+                request_planned(B1, 1);
+                request_planned(B2, 2);
                 ahead_j = 2;
                 wait_vmem<2 * OPS>();   // the blocks so far have landed
                 asm volatile("s_barrier" ::: "memory");
-                if (to_copy > 0) copy_block();
-                if ((B0.what & HELD) < BATCH_BYTES) {   // (asked for as if all of its units held one)
-                    const bool held = (uint32_t)lane * 16u < (B0.what & HELD);
+                if (more_to_copy()) copy_block();
+                {   // (asked for as if all of its units held a slot; the entries of the others name the zero column)
+                    const bool held = (uint32_t)lane * 16u < (uint32_t)__builtin_amdgcn_readlane(ends, 0) - (B0.what & PLACE);
 #pragma unroll
                     for (int g = 0; g < (WIDE ? 0 : GW); ++g) B0.bh[g][0] = held ? B0.bh[g][0] : u32x4{0, 0, 0, 0};
                 }
@@ -872,7 +909,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     turn(B1);
                     turn(B2);
                     if (ahead_j > 60) {
-                        const uint32_t place = (B2.what & (FRESH - 1u)) >> PLACE;
+                        const uint32_t place = (B2.what & PLACE) / BATCH_BYTES;
                         const int step = (int)(place / PER_STEP);
                         window(lengths(step), step - chunk_begin, (int)(place % PER_STEP));
                     }
@@ -898,7 +935,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                         float a[RT];
 #pragma unroll
                         for (int r = 0; r < RT; ++r) {
-                            const float v = mmm_whole_float(block + col * 128u + mmm_img_row(2, col, (uint32_t)(r * 16 + c)), MMM_PART_BYTES);
+                            const float v = mmm_whole_float(block + mmm_img_pos(2, col, (uint32_t)(r * 16 + c)), MMM_PART_BYTES);
                             a[r] = there ? v : 0.f;
                         }
 #pragma unroll
