@@ -158,7 +158,7 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 //     sums are added in LDS at the end, in order
 // FILTER  floats: look whether to leave the columns of A out that are zero in the whole tile (see `filtered`)
 template <int RT, int GW, int NW, int KS, typename T, bool FILTER>
-__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? (NW + 3) / 4 : sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? (NW + 3) / 4 : sizeof(T) == 8 && GW == 2 ? 2 : sizeof(T) <= 4 && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
     constexpr bool F64 = sizeof(T) == 8, WIDE = sizeof(T) == 4 || F64;
     constexpr bool PARTED = sizeof(T) == MMM_PARTS_ESZ;
@@ -317,9 +317,10 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     const uint32_t operand_at = ring_off + (uint32_t)(lane & 3) * 8u;   // this lane's four rows of a plane's column
     // 4- and 8-byte types: the operands of four quads, A's at these ring addresses; left: slots of the list from the batch's
     // first on (at least one)
-    auto multiply_quads = [&](const uint32_t (&at)[4], const elem_t (&bf)[WIDE ? GW : 1][4], int left) __attribute__((always_inline)) {
+    struct Quads { avec a[WIDE ? 4 : 1]; };
+    auto read_quads = [&](const uint32_t (&at)[4], Quads &o) __attribute__((always_inline)) {
         if constexpr (WIDE) {
-            avec a[4];
+            auto &a = o.a;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if constexpr (F64) {
@@ -336,6 +337,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                     a[u] = *reinterpret_cast<const __attribute__((address_space(3))) avec *>(ring3 + at[u]);
                 }
             }
+        }
+    };
+    auto multiply_quads = [&](Quads &o, const elem_t (&bf)[WIDE ? GW : 1][4], int left) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            auto &a = o.a;
             asm volatile("" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));   // all four requested before the first is used
             auto quad = [&](int u) __attribute__((always_inline)) {
 #pragma unroll
@@ -358,13 +364,18 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             }
         }
     };
+    auto read = [&](const Batch &b, Quads &o) __attribute__((always_inline)) {   // 4- and 8-byte types: A's operands of a batch
+        // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
+        // entries count in 256)
+        const uint32_t at[4] = {__builtin_amdgcn_perm(b.list.x, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.x, c16, 0x0c070600u),
+                                __builtin_amdgcn_perm(b.list.y, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.y, c16, 0x0c070600u)};
+        read_quads(at, o);
+    };
     auto multiply = [&](const Batch &b, int left) __attribute__((always_inline)) {
         if constexpr (WIDE) {
-            // ring address of a column: entry * 256 + 16 c, put together from bytes (doubles: columns are 512 bytes and
-            // entries count in 256)
-            const uint32_t at[4] = {__builtin_amdgcn_perm(b.list.x, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.x, c16, 0x0c070600u),
-                                    __builtin_amdgcn_perm(b.list.y, c16, 0x0c050400u), __builtin_amdgcn_perm(b.list.y, c16, 0x0c070600u)};
-            multiply_quads(at, b.bf, left);
+            Quads o;
+            read(b, o);
+            multiply_quads(o, b.bf, left);
         } else {
             // columns of 32 bytes; the plane of row tile r, and the part, are immediate offsets
             const uint32_t at[2] = {operand_at + (b.entry & 0xffffu) * MMM_PLANE_COL_BYTES, operand_at + (b.entry >> 16) * MMM_PLANE_COL_BYTES};
@@ -416,9 +427,16 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     auto step = [&](int n, int n_next, Batch &b) __attribute__((always_inline)) {
         wait_vmem<(RING - 1) * OPS>();
         asm volatile("s_barrier" ::: "memory");
+        // The next copy's instructions while the operands are on their way: multiplication, us, 2048^3 floats, p = .1, 25.9 -> 25.45, blocks of 32, p = .05,
+        // 18.95 -> 18.35, doubles 43.65 -> 43.15; 4096^3, p = .05, 85.5 -> 85.1.  Not where two ranges share the workgroup (1024^3 9.14 -> 9.2).  (Two conditions, no
+        // else: with a product on both sides of one, the compiler moves accumulators.)
+        constexpr bool READ_FIRST = !FILTER && KS == 1;
+        Quads o;
+        if (READ_FIRST && n > 0) read(b, o);
         if (more_to_copy()) copy_block();
         if (n > 0) {
-            multiply(b, n);
+            if (!READ_FIRST) read(b, o);
+            multiply_quads(o, b.bf, n);
             if (n > BATCH) {
                 // (Requests inside are unconditional, the last one repeating the batch in hand: a load on one side of a
                 // branch would be waited for as if nothing had been requested after the loads before it.)
@@ -658,7 +676,9 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
             const uint32_t e0 = b.e.x & 0x01ff01ffu, e1 = b.e.y & 0x01ff01ffu;
             const uint32_t at[4] = {__builtin_amdgcn_perm(e0, c16, 0x0c050400u), __builtin_amdgcn_perm(e0, c16, 0x0c070600u),
                                     __builtin_amdgcn_perm(e1, c16, 0x0c050400u), __builtin_amdgcn_perm(e1, c16, 0x0c070600u)};
-            multiply_quads(at, b.bf, left);
+            Quads o;
+            read_quads(at, o);
+            multiply_quads(o, b.bf, left);
         };
         Slots S0{}, S1{}, S2{};
         // b: the first batch of step ch (n slots), next: that of the step after; S2: the second of either
