@@ -270,3 +270,22 @@ def test_planes_of_every_tile(M, bw, dtype):
                 continue   # computes fewer rows than there are
             print(variant, split, flush=True)
             np.testing.assert_array_equal(run.run()[2], C_ref)
+
+
+@pytest.mark.parametrize("M,dtype", [(4097, synth.DT_F32), (4097, synth.DT_BF16), (8193, synth.DT_BF16), (1025, synth.DT_F64)], ids=["f32", "bf16_kept", "bf16", "f64"])
+@pytest.mark.parametrize("rows", [False, True])
+def test_large_x(M, dtype, rows):
+    """An X just above the size (64 MB, doubles 32) from which it is read past the caches, if the matrix kernel multiplies and floats are not
+    row-compacted; half of that in 16 bits."""
+    K, N = 4099, 48
+    w = synth.random_masked(M, K, N, 16, 0.05, 0.1, M, dist="smallint", dtype=dtype)
+    if rows:
+        w.keep_rows = synth.pack_bits((np.arange(K) % 5 == 1)[None, :])
+    ab, bb, C_ref, _ = oracle.run_workload(w)
+    run = HipRun(w)
+    for path in (mm.MMM_PATH_MATRIX, mm.MMM_PATH_PAIRS):
+        run.eng.set_path(path)
+        a, b, C = run.run()
+        np.testing.assert_array_equal(a, ab)
+        np.testing.assert_array_equal(b, bb)
+        np.testing.assert_array_equal(C, C_ref)
