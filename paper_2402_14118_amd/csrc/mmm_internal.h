@@ -128,6 +128,9 @@ __host__ __device__ constexpr uint32_t mmm_value_pos(size_t esz, uint32_t slot, 
 {
     return esz % 4 == 0 ? slot * 16u + col : col * 8u + ((slot & 7u) ^ (slot >> 1 & 4u));   // (the latter inside a unit)
 }
+// The groups whose lists a wave walks: its own, or the last ones where it stands past the last column (and multiplies nothing).  All
+// `width` of them exist: blocks of 32 columns, which go two groups to a wave, make an even number.
+__host__ __device__ constexpr int mmm_walked_group(int group, int groups, int width) { return group < groups - width ? group : groups - width; }
 // Floats: per 128 k a group lists `all` k, of which `stay` have a non-zero column of A in the tile.  Whether the kernel is
 // faster when it makes the lists without the others (see `filtered` there) than with the lists as packed.  A step then costs
 // what about 10 listed k cost (half of that where a list serves two groups), and a listed k a quarter more.  Multiplication, plain

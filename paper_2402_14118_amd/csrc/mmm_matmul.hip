@@ -241,15 +241,15 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll
         for (int r = 0; r < RT; ++r) rest[g][r] = tile_t{0, 0, 0, 0};
 
-    // this wave's groups; a wave past the last column walks the last group's addresses and multiplies nothing
+    // this wave's groups; a wave past the last column walks the last ones' addresses and multiplies nothing
     const int G0 = (tile_n * NW + wave) * GW;
     const bool active = G0 < p.NG;
-    const int Gc = min(G0, p.NG - 1);
+    const int Gc = mmm_walked_group(G0, p.NG, GW);
     const uint64_t seg0 = (uint64_t)(uint32_t)Gc * (uint32_t)p.KBA;   // the group's first segment
     // Buffer resources: an operand load is then a register of lane offsets, a scalar step offset and an immediate, with
     // no address arithmetic on the vector ALU.  A group's area is below 2^31 bytes (K < 2^22).
     const __amdgpu_buffer_rsrc_t val_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<char *>(p.bp_val) + seg0 * SEGB, 0, (GW == 1 ? 1 : min(p.NG - Gc, GW)) * p.KBA * SEGB, 0x00020000);
+        const_cast<char *>(p.bp_val) + seg0 * SEGB, 0, GW * p.KBA * SEGB, 0x00020000);
     const __amdgpu_buffer_rsrc_t list_rsrc = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint16_t *>(p.bp_list) + seg0 * KC, 0, p.KBA * KC * 2, 0x00020000);
     const int val_next = p.KBA * SEGB;   // second group of a 32-wide block (N is a multiple of 32 then)
