@@ -644,7 +644,6 @@ mmm_status mmm_build_maps(mmm_maps *maps, mmm_dtype dt, const void *X, int64_t l
     const bool compact_after = Y != nullptr ? a.b_compact : maps->b_compact;
     a.a_compact = X != nullptr && compact_after;
     a.form = choose_form(maps, a);
-    a.x_again = X != nullptr && choose_path(maps, dt, a.form) == MMM_PATH_PAIRS;
     if (form_is_captured(maps, dt, static_cast<hipStream_t>(hip_stream))) capture_form(maps, a.form, static_cast<hipStream_t>(hip_stream));
     if (hipError_t e = mmm_launch_build(maps, a, static_cast<hipStream_t>(hip_stream)); e != hipSuccess) {
         note_device_error("map builder launch", e);

@@ -200,15 +200,13 @@ template <typename T> struct ABlock {   // one block in a wave's registers: lane
 // pass: 63.6 with 32 bits, 63.3 with 64).
 template <typename T> using block_no = typename std::conditional<sizeof(T) == 8, int64_t, int32_t>::type;
 
-enum { X_SMALL, X_KEPT, X_PASSED };   // X_KEPT: 16-bit types, several blocks per workgroup; X_PASSED: and any type, past the caches
-
 // v_writelane_b32 and DPP instead of selects, wave-uniform words only where a lane mask is wanted, no branch per row and
 // one base per block: the sixteen waves of a block share one scalar unit, and the scan of half-precision matrices was
 // bound by it (2048 x 16384, one column in ten: 36.5 us with pairs of k per lane, whose masks had to be interleaved there).
-// SIZE_X: see mmm_launch_build.  DEEP: two blocks ahead in registers instead of one, for 16-bit types, whose blocks are half as large, where a workgroup has
+// DEEP: two blocks ahead in registers instead of one, for 16-bit types, whose blocks are half as large, where a workgroup has
 // several (columns 2048 x 16384: 28 -> 26 us for A, 41 -> 35.4 with B; with one or two blocks per workgroup the loads past
 // the last one cost more than they gain, 6.6 -> 9 us for 512 x 8192, and so do more bytes in flight for the wider types).
-template <typename T, int TEST, bool ROWS, int SIZE_X>
+template <typename T, int TEST, bool ROWS, bool DEEP>
 __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no<T> bi0, block_no<T> bi1, int lane, int wave, AShared &sh)
 {
     ConstParams &p = reread(p0);
@@ -216,7 +214,7 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
     typedef typename Pattern<sizeof(T)>::type pattern;
     typedef block_no<T> no_t;
     constexpr int ESZ = (int)sizeof(T);
-    constexpr bool WIDE = ESZ >= 4, DEEP = SIZE_X != X_SMALL && !WIDE;
+    constexpr bool WIDE = ESZ >= 4;
     constexpr int A_WORDS = Tile<T>::A_WORDS, A_COLS = 64 * A_WORDS;
     constexpr bool PARTED = Layout<T>::PARTED;
     constexpr bool WIDE_IMG = Layout<T>::ESZ % 4 == 0;   // rows w, w + 16, w + 32, w + 48 in the image, else in natural order
@@ -257,7 +255,6 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
         const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<char *>(static_cast<const char *>(p.X) + block_rows(bi, row_bytes) + k_lo * ESZ), 0,
             there ? (int)((rows_at(bi) - 1u) * row_bytes + (uint32_t)(tail * ESZ)) : 0, 0x00020000);
-        constexpr int POLICY = SIZE_X == X_PASSED ? 2 : 0;   // 2: not kept in the caches
 #pragma unroll
         for (int t = 0; t < A_ROWS; ++t) {
             const uint32_t row = (row0 + ROW_STEP * (uint32_t)t) * row_bytes;
@@ -265,12 +262,12 @@ __device__ __forceinline__ void scan_a(ConstParams &p0, block_no<T> bj, block_no
             for (int h = 0; h < A_WORDS; ++h) {
                 const int at = (int)(off[h] + row);
                 if constexpr (ESZ == 8) {
-                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, POLICY);
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(x, at, 0, 0);
                     r.x[t][h] = (uint64_t)v.y << 32 | v.x;
                 } else if constexpr (ESZ == 4) {
-                    r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, POLICY);
+                    r.x[t][h] = __builtin_amdgcn_raw_buffer_load_b32(x, at, 0, 0);
                 } else {
-                    r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, POLICY);
+                    r.x[t][h] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(x, at, 0, 0);
                 }
             }
         }
@@ -859,7 +856,7 @@ __device__ __forceinline__ uint32_t scan_b(ConstParams &p0, uint32_t seg, uint32
 }
 
 // ROWS: row-compacted mode (A laid out over the live rows of B; B built over them).
-template <typename T, int TEST, int BW, bool ROWS, int SIZE_X>
+template <typename T, int TEST, int BW, bool ROWS, bool DEEP>
 __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8, 8))) void mmm_build_kernel(const BuildParams)
 {
     ConstParams &p = *(ConstParams *)__builtin_amdgcn_kernarg_segment_ptr();
@@ -917,7 +914,7 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
         const uint32_t at = ROWS && Layout<T>::ESZ % 4 != 0 ? (i & 7u) * (p.n_a_wg >> 3) + min(i & 7u, p.n_a_wg & 7u) + (i >> 3) : i;
         const uint32_t down = mmm_divided(at, mmm_divisor{p.by_units.mul, p.by_units.shift});
         const int64_t bi0 = (int64_t)down * p.a_per_wg;
-        scan_a<T, TEST, ROWS, SIZE_X>(p, at - down * (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
+        scan_a<T, TEST, ROWS, DEEP>(p, at - down * (uint32_t)p.a_units, bi0, min(bi0 + p.a_per_wg, p.MBA), lane, wave, sh.a);
     }
 }
 
@@ -1155,37 +1152,31 @@ ElementTest mmm_element_test(int32_t dtype, int32_t pred, float threshold)
 
 typedef void (*build_kernel_fn)(const BuildParams);
 
-template <typename T, int TEST, bool ROWS, int SIZE_X> static build_kernel_fn build_kernel_width(int32_t bw)
+template <typename T, int TEST, bool ROWS, bool DEEP> static build_kernel_fn build_kernel_width(int32_t bw)
 {
-    return bw == 8    ? mmm_build_kernel<T, TEST, 8, ROWS, SIZE_X>
-           : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS, SIZE_X>
-                      : mmm_build_kernel<T, TEST, 32, ROWS, SIZE_X>;
+    return bw == 8    ? mmm_build_kernel<T, TEST, 8, ROWS, DEEP>
+           : bw == 16 ? mmm_build_kernel<T, TEST, 16, ROWS, DEEP>
+                      : mmm_build_kernel<T, TEST, 32, ROWS, DEEP>;
 }
-template <typename T, bool ROWS, int SIZE_X> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
+template <typename T, bool ROWS, bool DEEP> static build_kernel_fn build_kernel_test(int32_t mode, int32_t bw)
 {
-    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS, SIZE_X>(bw)
-         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS, SIZE_X>(bw)
-                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS, SIZE_X>(bw);
+    return mode == TEST_MAGNITUDE ? build_kernel_width<T, TEST_MAGNITUDE, ROWS, DEEP>(bw)
+         : mode == TEST_ONE_RANGE ? build_kernel_width<T, TEST_ONE_RANGE, ROWS, DEEP>(bw)
+                                  : build_kernel_width<T, TEST_TWO_RANGES, ROWS, DEEP>(bw);
 }
-template <typename T, int SIZE_X> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows)
+template <typename T> static build_kernel_fn build_kernel_rows(int32_t mode, int32_t bw, bool rows, bool deep)
 {
-    if constexpr (sizeof(T) < 8)   // no row-compacted mode of doubles
-        if (rows) return build_kernel_test<T, true, SIZE_X>(mode, bw);
-    return build_kernel_test<T, false, SIZE_X>(mode, bw);
+    constexpr bool HALF = sizeof(T) == 2;
+    if (deep && HALF) return rows ? build_kernel_test<T, true, HALF>(mode, bw) : build_kernel_test<T, false, HALF>(mode, bw);
+    return rows ? build_kernel_test<T, true, false>(mode, bw) : build_kernel_test<T, false, false>(mode, bw);
 }
-template <typename T> static build_kernel_fn build_kernel_size(int32_t mode, int32_t bw, bool rows, int32_t size_x)
+static build_kernel_fn build_kernel(int32_t dtype, int32_t form, int32_t mode, int32_t bw, bool rows, bool deep)
 {
-    if constexpr (sizeof(T) == 2)   // (else nothing but the way past the caches depends on the size)
-        if (size_x == X_KEPT) return build_kernel_rows<T, X_KEPT>(mode, bw, rows);
-    return size_x == X_PASSED ? build_kernel_rows<T, X_PASSED>(mode, bw, rows) : build_kernel_rows<T, X_SMALL>(mode, bw, rows);
-}
-static build_kernel_fn build_kernel(int32_t dtype, int32_t form, int32_t mode, int32_t bw, bool rows, int32_t size_x)
-{
-    if (form == MMM_FORM_PARTS) return build_kernel_size<PartedFloat>(mode, bw, rows, size_x);
-    return dtype == MMM_F64  ? build_kernel_size<double>(mode, bw, rows, size_x)
-         : dtype == MMM_BF16 ? build_kernel_size<uint16_t>(mode, bw, rows, size_x)
-         : dtype == MMM_F16  ? build_kernel_size<_Float16>(mode, bw, rows, size_x)
-                             : build_kernel_size<float>(mode, bw, rows, size_x);
+    if (form == MMM_FORM_PARTS) return build_kernel_rows<PartedFloat>(mode, bw, rows, deep);
+    return dtype == MMM_F64  ? build_kernel_test<double, false, false>(mode, bw)   // no row-compacted mode
+         : dtype == MMM_BF16 ? build_kernel_rows<uint16_t>(mode, bw, rows, deep)
+         : dtype == MMM_F16  ? build_kernel_rows<_Float16>(mode, bw, rows, deep)
+                             : build_kernel_rows<float>(mode, bw, rows, deep);
 }
 
 hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStream_t s)
@@ -1217,7 +1208,6 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.MBA = m->MBA;
     p.KBA = m->KBA;
     p.NG = m->NG;
-    const bool f64 = a.dtype == MMM_F64;
     p.pack = mmm_packs(m->M, a.dtype) ? 1 : 0;
     p.test = mmm_element_test(a.dtype, a.pred, a.threshold);
     p.y_unaligned = a.dtype != MMM_F32 && a.dtype != MMM_F64 && ((reinterpret_cast<uintptr_t>(a.Y) & 3u) != 0 || (a.ldy & 1) != 0);
@@ -1227,6 +1217,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.rows_copy = m->rows_copy;
     // the numbering the A side follows: that of the B side built in this call, or of the cached one
     p.rows = a.b_compact ? a.keep_rows : a.a_compact ? m->rows_copy : nullptr;
+    const bool f64 = a.dtype == MMM_F64;
     const int64_t b_cols = f64 ? Tile<double>::B_COLS : Tile<float>::B_COLS;
     p.ctiles = (uint32_t)((m->N + b_cols - 1) / b_cols);
     p.a_units = f64 ? m->WA : m->KBA;
@@ -1264,21 +1255,9 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.n_a_wg = (uint32_t)n_a_wg;
     p.n_b_wg = (uint32_t)n_b_wg;
     p.a_per_wg = (uint32_t)per_wg;
-    // A large X goes past the caches: what the last-level cache (256 MB) keeps of it takes the place of the image and of packed B, which the
-    // multiplication reads next.  Passes, us, X kept and not, over three sets of operands in turn; with X written right before; and the same X again,
-    // unchanged: 4096^3 floats, p = .05, 126.8 and 125.0, 142.8 and 142.5, 116.3 and 118.0, p = .2 227.3 and 224.0, 240.6 and 239.6, 214.6 and 216; 2048^3
-    // doubles 63.9 and 60.9, 69.4 and 68.2, 56.9 and 60.2; 2048 x 16384 x 4096 columns bf16 66.8 and 63.5, 84.8 and 86.2, 58.5 and 62.0.  So the first two gain
-    // and an X that nobody has written since loses.  Kept where there is less to gain than to lose: 32 MB of floats (2900^3 100.2 and 100.2, 107.4 and
-    // 112.2) and of 16-bit types (1024 x 16384 x 4096 87.8 and 88.1), row-compacted floats (2048 x 16384 x 4096 ReLU 121.4 and 120.1, 164.5 and 168.0), 16 MB (2048^3 floats
-    // 37.4 and 39.1, 1448^3 doubles 40.9 and 44.6); and where the pair kernel multiplies, which reads X itself (4096^3 doubles, p = .05, 267 and 295).
-    // As an instance of its own: a branch between two sets of loads cost the small ones .04 us.
-    constexpr int64_t MB = 1 << 20;
-    const bool half = a.dtype == MMM_BF16 || a.dtype == MMM_F16, long_run = per_wg >= 4;
-    const bool past = !a.x_again && (int64_t)m->M * m->K * (f64 ? 8 : half ? 2 : 4) >= (f64 ? 32 : 64) * MB && (half ? long_run : f64 || p.rows == nullptr);
-    const int32_t size_x = past ? X_PASSED : half && long_run ? X_KEPT : X_SMALL;
     const dim3 grid((uint32_t)n_all), block(BUILD_THREADS);
     (void)hipGetLastError();   // drop any stale error another library left on this thread
-    hipLaunchKernelGGL(build_kernel(a.dtype, a.form, p.test.mode, m->bw, p.rows != nullptr, size_x), grid, block, 0, s, p);
+    hipLaunchKernelGGL(build_kernel(a.dtype, a.form, p.test.mode, m->bw, p.rows != nullptr, per_wg >= 4), grid, block, 0, s, p);
     return hipGetLastError();
 }
 

@@ -277,7 +277,6 @@ struct mmm_build_args {
     bool a_compact;   // lay A out over the live k (the numbering exists or is made in this call)
     bool b_compact;   // number the live rows (keep_rows given) and pack those
     int32_t form;     // MMM_FORM_*
-    bool x_again;     // the multiplication will read X itself (pair kernel)
 };
 
 enum { PARTS_NO = 0, PARTS_FIXED = 1, PARTS_OWN = 2 };   // PARTS_FIXED: only where this tile has been fixed

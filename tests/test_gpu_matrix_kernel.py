@@ -275,8 +275,7 @@ def test_planes_of_every_tile(M, bw, dtype):
 @pytest.mark.parametrize("M,dtype", [(4097, synth.DT_F32), (4097, synth.DT_BF16), (8193, synth.DT_BF16), (1025, synth.DT_F64)], ids=["f32", "bf16_kept", "bf16", "f64"])
 @pytest.mark.parametrize("rows", [False, True])
 def test_large_x(M, dtype, rows):
-    """An X just above the size (64 MB, doubles 32) from which it is read past the caches, if the matrix kernel multiplies and floats are not
-    row-compacted; half of that in 16 bits."""
+    """An X of more than 64 MB (doubles 32; half of that in 16 bits), several blocks of A for each workgroup of the builder, under both kernels."""
     K, N = 4099, 48
     w = synth.random_masked(M, K, N, 16, 0.05, 0.1, M, dist="smallint", dtype=dtype)
     if rows:
