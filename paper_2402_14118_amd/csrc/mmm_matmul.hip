@@ -581,10 +581,6 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
         request_units(b, (uint32_t)__builtin_amdgcn_readlane(plan, ++ahead_j));
     };
 
-    // Where two workgroups share a compute unit, waves of one go first: it is not held up at its barriers by the other's, which fills the gaps.
-    // (256 numbers apart, as workgroups are dealt out.)  Multiplication, us: 4096^3 floats, p = .05, 90.6 -> 88.5, .1 137.5 -> 136.0, bf16, p = .05,
-    // 53.3 -> 51.8, .2 63.2 -> 61.7, .4 89.9 -> 87.5.  Four levels for the waves of a SIMD: .05 the same, others less.
-    if (!PARTED && (blockIdx.x & 256u) != 0) __builtin_amdgcn_s_setprio(1);
     const int all_steps = WIDE ? (steps + 1) & ~1 : steps;   // steps of `step` and `filtered` go in pairs; the odd one past the end has no list
 
     // ---- The same for an A whose columns are zero in all rows of the tile here and there (whole columns switched off, by
