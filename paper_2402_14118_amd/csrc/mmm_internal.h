@@ -21,6 +21,15 @@ inline mmm_divisor mmm_make_divisor(uint32_t d)
 }
 __host__ __device__ inline uint32_t mmm_divided(uint32_t n, const mmm_divisor &d) { return (uint32_t)((uint64_t)(n * 2u) * d.mul >> 32) >> d.shift; }
 
+// Which blocks of A the builder's workgroup i takes: `down` of the rows of workgroups, `unit` across.  xcd: units side by side go to one XCD (workgroups are
+// dealt out to the eight in turn), each row by itself, since the last one may have fewer blocks.
+struct mmm_a_place { uint32_t down, unit; };
+__host__ __device__ inline mmm_a_place mmm_place_of_a(uint32_t i, uint32_t units, const mmm_divisor &by_units, bool xcd)
+{
+    const uint32_t down = mmm_divided(i, by_units), unit = i - down * units;
+    return {down, xcd ? (unit & 7u) * (units >> 3) + ((unit & 7u) < (units & 7u) ? unit & 7u : units & 7u) + (unit >> 3) : unit};
+}
+
 // Rows of A summarised by one column-any word.
 constexpr int MMM_COLANY_ROWS = 32;
 // Geometry of the blocks of A: 64 rows x 128 columns, what one step of the matrix kernel keeps in LDS.

@@ -47,6 +47,36 @@ int main()
 }
 """
 
+PLACES = r"""
+#include <cstdio>
+#include <vector>
+#include "mmm_internal.h"
+int main()
+{
+    int bad = 0;
+    for (uint32_t units = 1; units <= 300; units += units < 20 ? 1 : 7)
+        for (uint32_t blocks = 1; blocks <= 33; ++blocks)           // below each other
+            for (uint32_t per : {1u, 2u, 6u, 8u}) {                // for each workgroup, the last row of them less
+                const uint32_t rows = (blocks + per - 1) / per, last = blocks - (rows - 1) * per;
+                for (bool xcd : {false, true}) {
+                    std::vector<int> taken(rows * units, 0);
+                    long work[8] = {};
+                    for (uint32_t i = 0; i < rows * units; ++i) {
+                        const mmm_a_place at = mmm_place_of_a(i, units, mmm_make_divisor(units), xcd);
+                        if (at.down >= rows || at.unit >= units) { ++bad; continue; }
+                        ++taken[at.down * units + at.unit];
+                        work[i & 7u] += at.down == rows - 1 ? last : per;
+                    }
+                    for (int t : taken) bad += t != 1;
+                    for (long w : work)
+                        for (long v : work) bad += w - v > (long)per;   // XCDs differ by one workgroup
+                }
+            }
+    std::printf("%d\n", bad);
+    return 0;
+}
+"""
+
 
 def _printed(tmp_path, text):
     source, program = tmp_path / "launch.cpp", tmp_path / "launch"
@@ -68,3 +98,9 @@ def test_more_workgroups_than_a_grid_holds(tmp_path):
 def test_groups_that_a_wave_walks(tmp_path):
     """All of them exist, also those of a wave past the last column, whose first batch is asked for before it is known to be empty."""
     assert _printed(tmp_path, GROUPS) == "0 1"
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no compiler")
+def test_blocks_of_a_over_the_workgroups(tmp_path):
+    """Every block once, and as many for each XCD, also where the last row of workgroups has fewer blocks than the others."""
+    assert _printed(tmp_path, PLACES) == "0"
