@@ -80,7 +80,7 @@ struct BuildParams {
     uint32_t *kinfo;         // [0] = K'
     uint32_t *kmap;          // k' -> k
     uint64_t *btc_bits;      // transposed B map over k'
-    mmm_divisor by_units, by_ctiles;   // of a_units; of ctiles (doubles: of half of them)
+    mmm_divisor by_units, by_ctiles, by_wb;   // of a_units; of ctiles (doubles: of half of them); of WB
 };
 // The kernel reads its arguments where it needs them: as a by-value struct they were all loaded at its start, and bringing
 // them back from where the compiler had spilled them took a third of the vector instructions.
@@ -885,13 +885,14 @@ __global__ __launch_bounds__(BUILD_THREADS) __attribute__((amdgpu_waves_per_eu(8
                 live = scan_b<T, BW, true>(p, seg, bb - seg * p.ctiles, l, wave, sh.b, carry);
             }
             // Zero map rows for the rows that are off, behind the packing, which they would hold up, and from the last workgroup on: that has
-            // nothing to pack where few rows are on.  A wave takes a word of 64 rows.
+            // nothing to pack where few rows are on.  64 rows at a time, whose words are side by side.  (A row to each lane stored words a row apart: 128 x 4096 x 65536
+            // bf16, a tenth of the rows on, blocks of 8, both sides 33.5 us, 30.4 so; 128 x 16384 x 32768 31.4 and 29.5.)
             const uint32_t WA = (uint32_t)p.WA, WB = (uint32_t)p.WB;
             for (uint32_t w = p.n_b_wg - 1u - i; w < WA; w += p.n_b_wg) {
                 const uint64_t on = row_word(p.rows, w, p.K);
-                const uint32_t row = w * 64u + (uint32_t)lane;
-                if (!((on >> lane) & 1ull) && row < (uint32_t)p.K)
-                    for (uint32_t q = (uint32_t)wave; q < WB; q += BUILD_WAVES) p.b_bits[(uint64_t)row * WB + q] = 0;
+                const uint32_t words = min(64u, (uint32_t)p.K - w * 64u) * WB;
+                for (uint32_t q = threadIdx.x; q < words; q += BUILD_THREADS)
+                    if (!((on >> mmm_divided(q, mmm_divisor{p.by_wb.mul, p.by_wb.shift})) & 1ull)) p.b_bits[(uint64_t)(w * 64u) * WB + q] = 0;
             }
         } else if (sizeof(T) < 8) {
             const uint32_t seg = mmm_divided(i, mmm_divisor{p.by_ctiles.mul, p.by_ctiles.shift});
@@ -1223,6 +1224,7 @@ hipError_t mmm_launch_build(const mmm_maps *m, const mmm_build_args &a, hipStrea
     p.a_units = f64 ? m->WA : m->KBA;
     p.by_units = mmm_make_divisor((uint32_t)p.a_units);
     p.by_ctiles = mmm_make_divisor(f64 ? (p.ctiles + 1) / 2 : p.ctiles);
+    p.by_wb = mmm_make_divisor((uint32_t)m->WB);
     const int64_t n_a = a.X ? m->MBA * p.a_units : 0;
     const int64_t n_b = a.Y ? m->KBA * (f64 ? (p.ctiles + 1) / 2 : p.ctiles) : 0;
     // Row-compacted B: how many segments have a live row is known on the device only; at most one workgroup per CU loops

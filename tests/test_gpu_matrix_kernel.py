@@ -247,6 +247,20 @@ def test_numbering_of_rows(K, live, dtype, bw):
     np.testing.assert_array_equal(kmap.cpu().numpy()[: on.sum()], np.flatnonzero(on))
 
 
+@pytest.mark.parametrize("dtype", [synth.DT_F32, synth.DT_F16], ids=["f32", "f16"])
+@pytest.mark.parametrize("K,N,bw", [(1, 8, 8), (63, 520, 8), (129, 1032, 8), (200, 8192, 8), (130, 8200, 8), (127, 16416, 16), (65, 66048, 32), (70, 65536, 8)])
+def test_map_rows_that_are_off(K, N, bw, dtype):
+    """Their words are cleared, whatever a build before had there: 1 to 128 words per row."""
+    w = synth.random_masked(3, K, N, bw, 0.5, 1.0, K + N, dist="smallint", dtype=dtype)
+    run = HipRun(w)
+    run.build()
+    assert (run.maps_host()[1] != 0).any()
+    w.keep_rows = synth.pack_bits((np.arange(K) % 3 == 1)[None, :])
+    run.keep_rows = torch.from_numpy(w.keep_rows.view(np.int64)).cuda()
+    run.build()
+    np.testing.assert_array_equal(run.maps_host()[1], oracle.run_workload(w)[1])
+
+
 @pytest.mark.parametrize("dtype", [synth.DT_BF16, synth.DT_F16], ids=["bf16", "f16"])
 @pytest.mark.parametrize("bw", [8, 16, 32])
 @pytest.mark.parametrize("M", [1, 31, 32, 33, 64, 65])
