@@ -464,7 +464,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // but one, and a list of several costs a request in vain; here none does.  What a turn has to know about its batch (place,
     // slots, whether a step begins with it) stands ready in a lane of `plan`, made 64 batches at a time on the vector ALU, so
     // that a turn takes some 20 scalar instructions; with the same worked out by scalar selects it took 31, and short lists lost
-    // what long ones won.  The turns past the end, up to two, do nothing.
+    // what long ones won.
     // 4096^3, p = .4, bf16 multiplication 111 -> 102 us; 512 x 8192 x 4096, bf16,
     // 24.3 -> 23.6, p = .4 38.0 -> 35.4.  4- and 8-byte types keep the steps above: their batches are half as large and mostly
     // one to a step, and the queue's beginning costs more than it gives (4096^3, p = .05, floats 89.5 -> 93.7, 2048^3, p = .1,
@@ -501,6 +501,16 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     // steps nothing or less.  Hence planes (4 instead of 15 vector instructions for addresses), no branch around empty lists, blocks copied by their
     // number.  Multiplication, us: 777 x 3001 x 1992 half, blocks of 8, 13.1 -> 12.1, 256 x 8192 x 4096, blocks of 32, p = .2, 17.55 -> 16.95,
     // 512 x 8192 x 4096 19.8 -> 19.5, columns 2048 x 1638 of 16384 x 4096 32.9 -> 32.2; floats in parts, 4096^3, p = .2, 176 -> 169, .4 295 -> 282.
+    // (The last one or two turns stand behind the loop: as turns past the end they multiplied zeros.  1472 x 458 x 4832, p = .04, 11.0 -> 10.2 us,
+    // 1472 x 128 8.85 -> 8.1, 4096^3, p = .01, 46.4 -> 45.2.  A branch in each turn instead costs what it gives: 4096 x 4096 x 528, p = .4, 25.2 -> 27.1.)
+    auto last_turn = [&](Batch &b) __attribute__((always_inline)) {
+        if (b.what & FRESH) {
+            wait_vmem<0>();
+            asm volatile("s_barrier" ::: "memory");
+            if (more_to_copy()) copy_block();
+        }
+        multiply(b, BATCH);
+    };
     auto turn = [&](Batch &b) __attribute__((always_inline)) {
         if (b.what & FRESH) {
             wait_vmem<(RING - 1) * OPS>();
@@ -933,7 +943,7 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
 #pragma unroll
                         for (int g = 0; g < (WIDE ? 0 : GW); ++g) B0.bh[g][0] = held ? B0.bh[g][0] : u32x4{0, 0, 0, 0};
                     }
-                    do {
+                    while ((int)B2.what >= 0) {
                         turn(B0);
                         turn(B1);
                         turn(B2);
@@ -942,7 +952,11 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
                             const int step = (int)(place / PER_STEP);
                             window(lengths(step), step - chunk_begin, (int)(place % PER_STEP));
                         }
-                    } while ((int)B0.what >= 0);
+                    }
+                    if ((int)B0.what >= 0) {   // one batch or two are left
+                        last_turn(B0);
+                        if ((int)B1.what >= 0) last_turn(B1);
+                    }
                 }
             }
         }
