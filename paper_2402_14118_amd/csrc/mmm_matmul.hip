@@ -158,7 +158,7 @@ template <int N> __device__ __forceinline__ void wait_vmem()
 //     sums are added in LDS at the end, in order
 // FILTER  floats: look whether to leave the columns of A out that are zero in the whole tile (see `filtered`)
 template <int RT, int GW, int NW, int KS, typename T, bool FILTER>
-__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? (NW + 3) / 4 : sizeof(T) == 8 && GW == 2 ? 2 : sizeof(T) <= 4 && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
+__global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == MMM_PARTS_ESZ ? (NW + 3) / 4 : sizeof(T) == 8 && GW == 2 ? 2 : FILTER && GW == 1 && NW == 16 ? 8 : 4))) void mmm_matmul_kernel(const MatmulParams p)
 {
     constexpr bool F64 = sizeof(T) == 8, WIDE = sizeof(T) == 4 || F64;
     constexpr bool PARTED = sizeof(T) == MMM_PARTS_ESZ;
@@ -427,15 +427,17 @@ __global__ __launch_bounds__(NW * KS * 64) __attribute__((amdgpu_waves_per_eu(si
     auto step = [&](int n, int n_next, Batch &b) __attribute__((always_inline)) {
         wait_vmem<(RING - 1) * OPS>();
         asm volatile("s_barrier" ::: "memory");
-        // The next copy's instructions while the operands are on their way: multiplication, us, 2048^3 floats, p = .1, 25.9 -> 25.45, blocks of 32, p = .05,
-        // 18.95 -> 18.35, doubles 43.65 -> 43.15; 4096^3, p = .05, 85.5 -> 85.1.  Not where two ranges share the workgroup (1024^3 9.14 -> 9.2).  (Two conditions, no
-        // else: with a product on both sides of one, the compiler moves accumulators.)
-        constexpr bool READ_FIRST = !FILTER && KS == 1;
+        // Doubles in the widest tile go through the next copy's instructions while the operands are on their way, where the list is long: 2048^3, p = .1,
+        // multiplication, 43.8 -> 42.9 us, 6666 x 5547 x 1864, blocks of 8, 455 -> 446.  With a short one the step waits for that copy, which then went out
+        // later: with all lists so 2253 x 1036 x 1152, p = .016, 17.5 -> 17.9, in the narrower tile 2626 x 1899 x 384, p = .05, 20.0 -> 22.1, floats 1317 x 5614 x 1776,
+        // p = .018, 34.1 -> 38.6 (2048^3, p = .1, 27.7 -> 27.2).  (Two conditions, no else: with a product on both sides of one, the compiler moves accumulators.)
+        constexpr bool EARLY = F64 && KS == 1 && NW * GW == 16;
+        constexpr int SHORT = 10;
         Quads o;
-        if (READ_FIRST && n > 0) read(b, o);
+        if (EARLY && n > SHORT) read(b, o);
         if (more_to_copy()) copy_block();
         if (n > 0) {
-            if (!READ_FIRST) read(b, o);
+            if (!EARLY || n <= SHORT) read(b, o);
             multiply_quads(o, b.bf, n);
             if (n > BATCH) {
                 // (Requests inside are unconditional, the last one repeating the batch in hand: a load on one side of a
