@@ -286,19 +286,36 @@ def test_planes_of_every_tile(M, bw, dtype):
             np.testing.assert_array_equal(run.run()[2], C_ref)
 
 
-@pytest.mark.parametrize("M,dtype", [(4097, synth.DT_F32), (4097, synth.DT_BF16), (8193, synth.DT_BF16), (1025, synth.DT_F64)], ids=["f32", "bf16_kept", "bf16", "f64"])
+@pytest.mark.parametrize("M,dtype,form", [(4097, synth.DT_F32, 0), (4097, synth.DT_F32, 1), (4097, synth.DT_BF16, -1), (8193, synth.DT_BF16, -1), (1025, synth.DT_F64, -1)],
+                         ids=["f32", "parts", "bf16_4097", "bf16", "f64"])
 @pytest.mark.parametrize("rows", [False, True])
-def test_large_x(M, dtype, rows):
-    """An X of more than 64 MB (doubles 32; half of that in 16 bits), several blocks of A for each workgroup of the builder, under both kernels."""
+def test_large_x(M, dtype, form, rows):
+    """An X of 32 to 67 MB, several blocks of A for each workgroup of the builder, under both kernels.  Floats: a row of A is one element that parts
+    do not hold, in the last block."""
     K, N = 4099, 48
     w = synth.random_masked(M, K, N, 16, 0.05, 0.1, M, dist="smallint", dtype=dtype)
     if rows:
         w.keep_rows = synth.pack_bits((np.arange(K) % 5 == 1)[None, :])
+    if dtype == synth.DT_F32:
+        keep = synth.unpack_bits(w.keep_a, K).astype(bool)
+        keep[M - 1] = np.arange(K) == K - 3          # 4096 is on
+        w.keep_a = synth.pack_bits(keep)
+        w.X[M - 1, K - 3] = 2.0**60
+        blocks = synth.unpack_bits(w.keep_blocks, N // 16).astype(bool)
+        blocks[K - 3] = True
+        w.keep_blocks = synth.pack_bits(blocks)
     ab, bb, C_ref, _ = oracle.run_workload(w)
-    run = HipRun(w)
-    for path in (mm.MMM_PATH_MATRIX, mm.MMM_PATH_PAIRS):
-        run.eng.set_path(path)
-        a, b, C = run.run()
-        np.testing.assert_array_equal(a, ab)
-        np.testing.assert_array_equal(b, bb)
-        np.testing.assert_array_equal(C, C_ref)
+    mm.mmm_set_option("float_form", form)
+    try:
+        run = HipRun(w)
+        for path in (mm.MMM_PATH_MATRIX, mm.MMM_PATH_PAIRS):
+            run.eng.set_path(path)
+            a, b, C = run.run()
+            assert mm.mmm_matmul_form(run.eng.maps) == max(form, 0)
+            np.testing.assert_array_equal(a, ab)
+            np.testing.assert_array_equal(b, bb)
+            np.testing.assert_array_equal(C, C_ref)
+            if dtype == synth.DT_F32:
+                assert (np.abs(C[M - 1]) >= 2.0**60).any()
+    finally:
+        mm.mmm_set_option("float_form", -1)
