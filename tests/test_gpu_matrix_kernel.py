@@ -319,3 +319,37 @@ def test_large_x(M, dtype, form, rows):
                 assert (np.abs(C[M - 1]) >= 2.0**60).any()
     finally:
         mm.mmm_set_option("float_form", -1)
+
+
+@pytest.mark.parametrize("dtype,bw", [(synth.DT_BF16, 16), (synth.DT_F16, 32), (synth.DT_F16, 8)], ids=["bf16", "f16_32", "f16_8"])
+@pytest.mark.parametrize("batches", [[1], [4], [0, 0], [1, 0, 2], [0, 1, 1, 4, 3], [1] * 6, [1] * 7, [0] * 8, [2, 3] * 4, [1] * 64 + [4], [4] * 16 + [1] * 3], ids=lambda b: f"{len(b)}_{sum(b)}")
+def test_batches_of_a_queue(batches, dtype, bw):
+    """16-bit types take three batches at a time and the last one or two by themselves: any number of them over the steps, in one and two ranges of
+    K; the last tiles have waves without columns, which only copy."""
+    M, K, N = 65, 128 * len(batches), 288 if bw == 32 else 272
+    keep = np.zeros((K, N // bw), bool)
+    rng = np.random.default_rng(K + bw)
+    for s, b in enumerate(batches):
+        keep[s * 128 + rng.permutation(128)[: max(32 * b - 5, 0)]] = True
+    w = synth.random_masked(M, K, N, bw, 0.5, 1.0, K, dist="smallint", dtype=dtype)
+    w.keep_blocks = synth.pack_bits(keep)
+    for variant in (0, 1, 2, 6, 7):
+        for split in (1, 2):
+            print(variant, split, flush=True)
+            _run(w, split, variant)
+
+
+@pytest.mark.parametrize("bw", [8, 16, 32])
+def test_order_in_a_step(bw):
+    """Doubles in the widest tile read the operands of lists of more than ten k ahead of the next copy: lists around that, and of several batches."""
+    lengths = [0, 1, 9, 10, 11, 12, 16, 17, 31, 33, 128, 0, 10, 11]
+    M, segs, N = 70, len(lengths), 288
+    keep = np.zeros((segs * 128, N // bw), bool)
+    rng = np.random.default_rng(bw)
+    for s in range(segs):
+        for b in range(N // bw):
+            keep[s * 128 + rng.permutation(128)[: lengths[(s + b * bw // 32) % segs]], b] = True
+    w = synth.random_masked(M, segs * 128, N, bw, 0.5, 1.0, bw, dist="smallint", dtype=synth.DT_F64)
+    w.keep_blocks = synth.pack_bits(keep)
+    for split in (1, 3):
+        _run(w, split, 1)
